@@ -1,8 +1,15 @@
 // bf16 MFMA GEMM tile for gfx950: D[256 x 256] (fp32) = A[256 x K] * B[256 x K]^T, both
 // operands row-major with K contiguous.  One workgroup of 8 waves (2 x 4, two per SIMD) owns
-// the tile; each wave accumulates a 128 x 64 sub-tile as 4 x 2 blocks of
-// v_mfma_f32_32x32x16_bf16.  Two waves per SIMD let one wave's waits (barrier, LDS latency,
+// the tile; each wave accumulates a 128 x 64 sub-tile as 8 x 4 blocks of
+// v_mfma_f32_16x16x32_bf16.  Two waves per SIMD let one wave's waits (barrier, LDS latency,
 // epilogue arithmetic) hide behind the other's matrix instructions.
+//
+// The loop is bound by the power limit: on Gaussian operands the clock settles near 1.75 GHz
+// (2.4 GHz on zeros), so the energy per flop of the matrix instruction sets the rate.  A stream
+// of nothing but 16 x 16 x 32 reaches 2.11 PFLOP/s on Gaussian data where 32 x 32 x 16 reaches
+// 1.85 (both 2.4-2.5 on zeros), and 2.13 when consecutive instructions always share one operand
+// (the column order alternates from row to row).  The bare loop below: 1.45 PFLOP/s at
+// 151936 x 16384 x 1536 and 1.44 at 152064 x 32768 x 3584, against 1.36 / 1.34 with 32 x 32 x 16.
 //
 // Two main loops share the accumulator layout:
 //   gemm_tile_dma  operands go HBM -> LDS directly (buffer_load ... lds), two stages of
@@ -15,32 +22,33 @@
 namespace aero {
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-typedef float f32x16_t __attribute__((ext_vector_type(16)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int kTile = 256;          // tile edge in both output dimensions
 constexpr int kGemmNT = 512;        // threads per workgroup (8 waves)
-constexpr int kMB = 4, kNB = 2;     // 32 x 32 blocks per wave: 128 rows x 64 columns
+constexpr int kMB = 8, kNB = 4;     // 16 x 16 blocks per wave: 128 rows x 64 columns
 constexpr size_t kGemmStageBytes = 131072;  // two stages of (256 + 256) x 64 bf16
 constexpr size_t kWarmSinkOff = 135168;     // past the stages (128 KB) and the largest epilogue staging area (256 x 256 bf16)
 constexpr size_t kGemmLdsBytes = kWarmSinkOff + 2048;   // + a 256-byte sink per wave for the warm-up loads
 
 // Position of an accumulator element inside the 256 x 256 tile.
 //   block (mb, nb) of wave (wm in 0..1, wn in 0..3); register i of lane l:
-//   row = wm*128 + mb*32 + 8*(i/4) + 4*(l/32) + i%4,   col = wn*64 + nb*32 + l%32
-__device__ __forceinline__ int acc_row(int wm, int mb, int i, int lane) {
-  return wm * 128 + mb * 32 + 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3);
-}
-__device__ __forceinline__ int acc_col(int wn, int nb, int lane) { return wn * 64 + nb * 32 + (lane & 31); }
+//   row = wm*128 + mb*16 + 4*(l/16) + i,   col = wn*64 + nb*16 + l%16
+// SWAP (a template argument of the loops): the operands of the matrix instruction are exchanged, and
+//   row = wm*128 + mb*16 + l%16,           col = wn*64 + nb*16 + 4*(l/16) + i
+// i.e. a lane holds four consecutive columns of one row instead of four rows of one column.
+__device__ __forceinline__ int acc_row(int wm, int mb, int i, int lane) { return wm * 128 + mb * 16 + 4 * (lane >> 4) + i; }
+__device__ __forceinline__ int acc_col(int wn, int nb, int lane) { return wn * 64 + nb * 16 + (lane & 15); }
+__device__ __forceinline__ int acc_row_swapped(int wm, int mb, int lane) { return wm * 128 + mb * 16 + (lane & 15); }
+__device__ __forceinline__ int acc_col_swapped(int wn, int nb, int lane) { return wn * 64 + nb * 16 + 4 * (lane >> 4); }
 
-typedef f32x16_t Acc[kMB][kNB];
+typedef f32x4_t Acc[kMB][kNB];
 
 __device__ __forceinline__ void acc_zero(Acc& acc) {
 #pragma unroll
   for (int mb = 0; mb < kMB; ++mb)
 #pragma unroll
-    for (int nb = 0; nb < kNB; ++nb)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) acc[mb][nb][i] = 0.f;
+    for (int nb = 0; nb < kNB; ++nb) acc[mb][nb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 }
 
 // Workgroup id -> tile.  Consecutive hardware workgroup ids go to different XCDs (8 of them,
@@ -94,16 +102,22 @@ __device__ __forceinline__ bool tile_of_block(int tiles_m, int tiles_n, int tile
   return true;
 }
 
-struct Frags {
-  bf16x8_t a[kMB], b[kNB];
-};
+// Fragments of one 32-wide K step: lane l holds K 8 (l/16) .. + 7 of row l%16 of a 16-row block.
+// A wave's 128 rows of A come in two halves of four blocks.
+constexpr int kFragBlocks = 4;
+typedef bf16x8_t Frags[kFragBlocks];
 
-__device__ __forceinline__ void frags_mma(const Frags& f, Acc& acc) {
+template <bool SWAP>
+__device__ __forceinline__ void frags_mma(const Frags& a, const Frags& b, int half, Acc& acc) {
 #pragma unroll
-  for (int mb = 0; mb < kMB; ++mb)
+  for (int i = 0; i < kFragBlocks; ++i)
 #pragma unroll
-    for (int nb = 0; nb < kNB; ++nb)
-      acc[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[mb], f.b[nb], acc[mb][nb], 0, 0, 0);
+    for (int jj = 0; jj < kNB; ++jj) {
+      const int j = (i & 1) ? kNB - 1 - jj : jj;   // neighbours in the sequence share an operand (see the top)
+      f32x4_t& c = acc[half * kFragBlocks + i][j];
+      c = SWAP ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[j], a[i], c, 0, 0, 0)
+               : __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], c, 0, 0, 0);
+    }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -143,23 +157,30 @@ __device__ __forceinline__ void slice_store(uint16_t* lds, const u32x4_t (&r)[kV
   }
 }
 
+// Fragments of K step ks (0, 1) of a 64-wide slice held in LDS: four 16-row blocks from row0 on.
+__device__ __forceinline__ void frags_load(Frags& f, const uint16_t* lds, int row0, int ks, int lane) {
+#pragma unroll
+  for (int i = 0; i < kFragBlocks; ++i)
+    f[i] = *reinterpret_cast<const bf16x8_t*>(lds + lds_off(row0 + i * 16 + (lane & 15), ks * 4 + (lane >> 4)));
+}
+
+template <bool SWAP>
 __device__ __forceinline__ void slice_mma(const uint16_t* As, const uint16_t* Bs, int wm, int wn, int lane, Acc& acc) {
 #pragma unroll
-  for (int ks = 0; ks < kBK / 16; ++ks) {
-    Frags f;
-    const int chunk = ks * 2 + (lane >> 5);
+  for (int ks = 0; ks < kBK / 32; ++ks) {
+    Frags a, b;
+    frags_load(b, Bs, wn * 64, ks, lane);
 #pragma unroll
-    for (int mb = 0; mb < kMB; ++mb)
-      f.a[mb] = *reinterpret_cast<const bf16x8_t*>(As + lds_off(wm * 128 + mb * 32 + (lane & 31), chunk));
-#pragma unroll
-    for (int nb = 0; nb < kNB; ++nb)
-      f.b[nb] = *reinterpret_cast<const bf16x8_t*>(Bs + lds_off(wn * 64 + nb * 32 + (lane & 31), chunk));
-    frags_mma(f, acc);
+    for (int half = 0; half < 2; ++half) {
+      frags_load(a, As, wm * 128 + half * 64, ks, lane);
+      frags_mma<SWAP>(a, b, half, acc);
+    }
   }
 }
 
 // Full K loop for one tile.  A rows [m0, m0+256) clipped to M, B rows [n0, n0+256) clipped to
 // N, columns [0, K).  smem: kGemmLdsBytes.  Ends with a barrier: smem is free afterwards.
+template <bool SWAP>
 __device__ __forceinline__ void gemm_tile(const uint16_t* __restrict__ A, int64_t lda, int M,
                                           const uint16_t* __restrict__ B, int64_t ldb, int N, int K,
                                           int m0, int n0, uint16_t* smem, Acc& acc) {
@@ -183,7 +204,7 @@ __device__ __forceinline__ void gemm_tile(const uint16_t* __restrict__ A, int64_
       slice_load(A, lda, m0, M, (kt + 1) * kBK, K, ra);
       slice_load(B, ldb, n0, N, (kt + 1) * kBK, K, rb);
     }
-    slice_mma(As[cur], Bs[cur], wm, wn, lane, acc);
+    slice_mma<SWAP>(As[cur], Bs[cur], wm, wn, lane, acc);
     if (more) {
       slice_store(As[cur ^ 1], ra);
       slice_store(Bs[cur ^ 1], rb);
@@ -259,21 +280,9 @@ __device__ __forceinline__ void dma_issue(__amdgpu_buffer_rsrc_t ra, __amdgpu_bu
   }
 }
 
-__device__ __forceinline__ void frags_load(Frags& f, const uint16_t* stage, int ks, int wm, int wn, int lane) {
-  const uint16_t* As = stage;
-  const uint16_t* Bs = stage + kTile * kDK;
-  const int chunk = ks * 2 + (lane >> 5);
-#pragma unroll
-  for (int mb = 0; mb < kMB; ++mb)
-    f.a[mb] = *reinterpret_cast<const bf16x8_t*>(As + lds_off(wm * 128 + mb * 32 + (lane & 31), chunk));
-#pragma unroll
-  for (int nb = 0; nb < kNB; ++nb)
-    f.b[nb] = *reinterpret_cast<const bf16x8_t*>(Bs + lds_off(wn * 64 + nb * 32 + (lane & 31), chunk));
-}
-
 // WARM: L2 warm-up two slices ahead (see below); a few per cent on the contractions whose
 // operands come from large read-only arrays, a loss on the split-K dhidden contraction.
-template <bool WARM>
+template <bool WARM, bool SWAP>
 __device__ __forceinline__ void gemm_tile_dma(const DmaOperand& A, const DmaOperand& B, int K, int m0, int n0,
                                               uint16_t* smem, Acc& acc) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -300,11 +309,11 @@ __device__ __forceinline__ void gemm_tile_dma(const DmaOperand& A, const DmaOper
   const uint32_t warm_off = uint32_t(int64_t(warm_row) * (warm_a ? A.ld : B.ld) * 2) + (warm_a ? 0u : uint32_t(lane >> 5) * 64u);
   const uint32_t warm_kstep = uint32_t((warm_a ? A.kstep : B.kstep) * 2);
   uint16_t* const warm_sink = smem + kWarmSinkOff / 2 + wave * 128;
-  // One iteration = one 64-wide slice = four 16-wide steps of 8 MFMAs per wave.  The order is
-  // pinned with scheduling barriers: both fragment sets of the first two steps are read up
-  // front, the next slice is requested only after the first MFMA group (issuing the 8 loads
-  // right after the barrier would hold back every wave's first MFMAs: measured 8 % slower),
-  // and the fragment reads of steps 2 and 3 are interleaved one-to-one with MFMAs.
+  // One iteration = one 64-wide slice = two 32-wide K steps of two halves, 16 MFMAs per wave each.
+  // The order is pinned with scheduling barriers: the first step's fragments are read up front, the
+  // next slice is requested only after the first MFMA group (issuing the 8 loads right after the
+  // barrier would hold back every wave's first MFMAs: measured 8 % slower), and the other fragment
+  // reads are interleaved with MFMAs, two per read.
   // warm: touch slice kt + kWarmAhead; warm_pending: the previous slice issued a touch.
   auto slice = [&](int kt, bool prefetch, bool warm, bool warm_pending) {
     // slice kt landed (the youngest load may be a touch: loads return in order), own LDS reads done
@@ -313,37 +322,37 @@ __device__ __forceinline__ void gemm_tile_dma(const DmaOperand& A, const DmaOper
     AERO_CFENCE();
     __builtin_amdgcn_s_barrier();
     AERO_CFENCE();
-    const uint16_t* st = smem + (kt & 1) * kDStageElems;
-    Frags f0, f1;
-    frags_load(f0, st, 0, wm, wn, lane);
-    frags_load(f1, st, 1, wm, wn, lane);
-    frags_mma(f0, acc);
+    const uint16_t* As = smem + (kt & 1) * kDStageElems;
+    const uint16_t* Bs = As + kTile * kDK;
+    Frags b0, b1, a0, a1, a2;
+    frags_load(a0, As, wm * 128, 0, lane);
+    frags_load(b0, Bs, wn * 64, 0, lane);
+    frags_load(a1, As, wm * 128 + 64, 0, lane);
+    frags_mma<SWAP>(a0, b0, 0, acc);
     if (prefetch) dma_issue(ra, rb, la, lb, kt + 1, smem + ((kt + 1) & 1) * kDStageElems, wave);
-    frags_load(f0, st, 2, wm, wn, lane);
-    frags_mma(f1, acc);
-    frags_load(f1, st, 3, wm, wn, lane);
-    frags_mma(f0, acc);
+    frags_load(a2, As, wm * 128, 1, lane);
+    frags_load(b1, Bs, wn * 64, 1, lane);
+    frags_mma<SWAP>(a1, b0, 1, acc);
+    frags_load(a0, As, wm * 128 + 64, 1, lane);
+    frags_mma<SWAP>(a2, b1, 0, acc);
     constexpr int kMfma = 0x008, kVmemRd = 0x020, kDsRd = 0x100;
-    constexpr int kFragReads = kMB + kNB, kMfmas = kMB * kNB;
-    __builtin_amdgcn_sched_group_barrier(kDsRd, 2 * kFragReads, 0);
+    constexpr int kMfmas = kFragBlocks * kNB;
+    __builtin_amdgcn_sched_group_barrier(kDsRd, 3 * kFragBlocks, 0);
     __builtin_amdgcn_sched_group_barrier(kMfma, kMfmas, 0);
     if (prefetch) __builtin_amdgcn_sched_group_barrier(kVmemRd, 8, 0);
 #pragma unroll
-    for (int rep = 0; rep < 2; ++rep) {
-#pragma unroll
-      for (int r = 0; r < kFragReads; ++r) {
-        __builtin_amdgcn_sched_group_barrier(kMfma, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(kDsRd, 1, 0);
-      }
-      __builtin_amdgcn_sched_group_barrier(kMfma, kMfmas - kFragReads, 0);
+    for (int r = 0; r < 3 * kFragBlocks; ++r) {
+      __builtin_amdgcn_sched_group_barrier(kMfma, 2, 0);
+      __builtin_amdgcn_sched_group_barrier(kDsRd, 1, 0);
     }
+    __builtin_amdgcn_sched_group_barrier(kMfma, 2 * kMfmas - 6 * kFragBlocks, 0);
     if (WARM) {
       __builtin_amdgcn_sched_barrier(0);
       if (warm && warm_wave)
         __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, warm_sink, 4, warm_off + uint32_t(kt + kWarmAhead) * warm_kstep, 0, 0, 0);
       __builtin_amdgcn_sched_barrier(0);
     }
-    frags_mma(f1, acc);
+    frags_mma<SWAP>(a0, b1, 1, acc);
     if (!WARM) __builtin_amdgcn_sched_group_barrier(kMfma, kMfmas, 0);
   };
   // Every call site passes constants, so that each copy of the slice is one scheduling region.
@@ -368,8 +377,8 @@ __device__ __forceinline__ void gemm_tile_auto(const uint16_t* __restrict__ A, i
   const bool fast = (K % kDK == 0) && (lda % 8 == 0) && (ldb % 8 == 0) &&
                     (reinterpret_cast<uintptr_t>(A) % 16 == 0) && (reinterpret_cast<uintptr_t>(B) % 16 == 0) &&
                     ((int64_t(M) - 1) * lda + K) < (int64_t(1) << 31) && ((int64_t(N) - 1) * ldb + K) < (int64_t(1) << 31);
-  if (fast) gemm_tile_dma<true>(operand_row_major(A, lda, M, K), operand_row_major(B, ldb, N, K), K, m0, n0, smem, acc);
-  else gemm_tile(A, lda, M, B, ldb, N, K, m0, n0, smem, acc);
+  if (fast) gemm_tile_dma<true, false>(operand_row_major(A, lda, M, K), operand_row_major(B, ldb, N, K), K, m0, n0, smem, acc);
+  else gemm_tile<false>(A, lda, M, B, ldb, N, K, m0, n0, smem, acc);
 }
 
 }  // namespace aero
