@@ -125,6 +125,26 @@ size_t fused_workspace_bytes(int64_t T, int32_t V, int32_t H) {
   return make_plan(T, V, H).total;
 }
 
+// Split-K factor for dhidden, from the number of candidate token tiles (device side; one wave, lane s - 1
+// prices s splits).  A workgroup's time is its share of the K slices plus a fixed tail (storing its fp32
+// partial tile, worth about 8 slices of main loop); the launch takes ceil(workgroups / 256) such rounds.
+// S minimises rounds x (slices / S + 8) among the S whose splits stay addressable: a split's
+// slab operands (rows_max rows per 64-wide slice) must span less than 4 GiB.  Chosen once per call: the
+// 64-bit divisions are 50 us of latency when one thread walks the candidates, and every workgroup of
+// the contraction and of the scatter used to (400 of the 530 us of the contraction of 600 tokens).
+__device__ __forceinline__ int dh_splits(int active_tiles, int tiles_h, int grid, int slices, int64_t rows_max) {
+  const int base = active_tiles * tiles_h;
+  if (base == 0) return 0;
+  const int s = int(threadIdx.x & 63) + 1;
+  const int per = (slices + s - 1) / s;
+  const bool ok = int64_t(base) * s <= grid && s <= slices && int64_t(per) * kDK * rows_max * 2 < (int64_t(1) << 32);
+  const int64_t cost = (int64_t(base) * s + 255) / 256 * (per + 8);
+  int64_t best = ok ? cost * 64 + (s - 1) : INT64_MAX;   // the fewest splits among equals
+#pragma unroll
+  for (int off = kWave / 2; off > 0; off >>= 1) best = min(best, int64_t(__shfl_xor((long long)best, off, kWave)));
+  return best == INT64_MAX ? 0 : int(best & 63) + 1;
+}
+
 // ------------------------------------------------------------------------------------------
 // forward: rows with a target, compacted
 // ------------------------------------------------------------------------------------------
@@ -134,8 +154,8 @@ size_t fused_workspace_bytes(int64_t T, int32_t V, int32_t H) {
 // every_weighted: an entropy or KL term is on) - then the other rows with a target.
 //   fidx[j] = row of position j (-1 past the count), nf = {rows with a target, that rounded up to a tile,
 //   candidates, that rounded up to a tile}; pos[t] = position of candidate t, -1 for every other row;
-//   nact = {candidates, rounded up, 0}: nact[2] is the flag the forward pass raises when a stored
-//   exponential left its safe range (see k_fused_stats).
+//   nact = {candidates, rounded up, 0, splits}: nact[2] is the flag the forward pass raises when a stored
+//   exponential left its safe range (see k_fused_stats), nact[3] the split count of the dhidden contraction.
 // token_rollout == null (forward-only call): no candidates, pos / nact are not written.
 // Ignored rows get their zero outputs here; a target >= V raises the device error bit.
 __global__ __launch_bounds__(1024) void k_compact_valid(
@@ -143,7 +163,7 @@ __global__ __launch_bounds__(1024) void k_compact_valid(
     const float* __restrict__ adv, const float* __restrict__ weight, int R, int every_weighted,
     int32_t* __restrict__ fidx, int32_t* __restrict__ nf, int32_t* __restrict__ pos, int32_t* __restrict__ nact,
     float* __restrict__ logprob, float* __restrict__ entropy, float* __restrict__ lse_out,
-    int32_t* __restrict__ err_flag) {
+    int32_t* __restrict__ err_flag, int tiles_h, int dh_grid, int slices, int64_t rows_max) {
   // each of the 16 waves owns one contiguous range of rows and walks it 64 rows at a time (coalesced
   // reads, ballot + popcount inside the wave): count, exchange the 16 counts, then place
   __shared__ int wsum_c[16], wsum_o[16];
@@ -205,6 +225,7 @@ __global__ __launch_bounds__(1024) void k_compact_valid(
   }
   if (bad && err_flag) atomicOr(err_flag, AERO_DERR_BAD_TARGET);
   for (int64_t j = total + tid; j < T_pad; j += 1024) fidx[j] = -1;
+  const int splits = wave == 0 && nact ? dh_splits((total_c + kTile - 1) / kTile, tiles_h, dh_grid, slices, rows_max) : 0;
   if (tid == 0) {
     nf[0] = total;
     nf[1] = (total + kTile - 1) / kTile * kTile;
@@ -214,6 +235,7 @@ __global__ __launch_bounds__(1024) void k_compact_valid(
       nact[0] = total_c;
       nact[1] = (total_c + kTile - 1) / kTile * kTile;
       nact[2] = 0;
+      nact[3] = splits;
     }
   }
 }
@@ -749,30 +771,6 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_fused_dz(
 // ------------------------------------------------------------------------------------------
 // backward: the two gradient GEMMs
 // ------------------------------------------------------------------------------------------
-// Split-K factor for dhidden, from the number of candidate token tiles (uniform, device side).
-// A workgroup's time is its share of the K slices plus a fixed tail (storing its fp32 partial
-// tile, worth about 8 slices of main loop); the launch takes ceil(workgroups / 256) such rounds.
-// S minimises rounds x (slices / S + 8) among the S whose splits stay addressable: a split's
-// slab operands (rows_max rows per 64-wide slice) must span less than 4 GiB.
-__device__ __forceinline__ int dh_splits(int active_tiles, int tiles_h, int grid, int slices, int64_t rows_max) {
-  const int base = active_tiles * tiles_h;
-  if (base == 0) return 0;
-  int best = 0;
-  int64_t best_cost = INT64_MAX;
-  for (int s = 1; base * s <= grid && s <= slices; ++s) {
-    const int per = (slices + s - 1) / s;
-    if (int64_t(per) * kDK * rows_max * 2 >= (int64_t(1) << 32)) continue;   // not addressable with 32-bit offsets
-    const int64_t rounds = (int64_t(base) * s + 255) / 256;
-    const int64_t cost = rounds * (per + 8);
-    if (cost < best_cost) {
-      best_cost = cost;
-      best = s;
-    }
-    if (s >= 64) break;
-  }
-  return best;
-}
-
 // dh_part[s][t][h] = sum_{k in split s} X[t][k] W[k][h], X = the stored exponentials P (or dz itself on the recompute
 // route)     M = candidate tokens, N = H, K = vocabulary (padded)
 __global__ __launch_bounds__(kGemmNT, 2) void k_gemm_dh(
@@ -782,7 +780,7 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_gemm_dh(
   const int n_pad = nact[1];
   const int tiles_t = n_pad / kTile;
   const int nslices = vK / kDK;
-  const int S = dh_splits(tiles_t, tiles_h, gridDim.x, nslices, T_pad > H_pad ? T_pad : H_pad);
+  const int S = nact[3];
   const int base = tiles_t * tiles_h;
   const int pid = blockIdx.x;
   if (S == 0 || pid >= base * S) return;   // uniform exit
@@ -890,8 +888,7 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_gemm_dw(
 // dhidden[t] = bf16(scale[pos[t]] * sum over the split-K partials of row pos[t]) or +0.  One workgroup per
 // row; the partials are summed in split order, so the result does not depend on scheduling.
 __global__ __launch_bounds__(256) void k_scatter_dh(const float* __restrict__ dh_part, const int32_t* __restrict__ pos,
-                                                    const int32_t* __restrict__ nact, int H, int tiles_h,
-                                                    int dh_grid, int slices, int64_t rows_max,
+                                                    const int32_t* __restrict__ nact, int H,
                                                     const float* __restrict__ scale, uint16_t* __restrict__ dhidden) {
   const int64_t t = blockIdx.x;
   const int j = pos[t];
@@ -902,7 +899,7 @@ __global__ __launch_bounds__(256) void k_scatter_dh(const float* __restrict__ dh
     return;
   }
   const int n_pad = nact[1];
-  const int S = dh_splits(n_pad / kTile, tiles_h, dh_grid, slices, rows_max);   // as the contraction chose it
+  const int S = nact[3];
   for (int k = threadIdx.x * 4; k < H; k += 256 * 4) {
     f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
     const float* src = dh_part + int64_t(j) * H + k;
@@ -978,6 +975,9 @@ extern "C" aero_status aero_lmhead_logprob_fused(
   float* part_s = part_m + size_t(p.tiles_v) * p.T_pad;
   float* part_sz = part_s + size_t(p.tiles_v) * p.T_pad;
   const int tiles_t = int(p.T_pad / kTile);
+  const int tiles_h = (H + kTile - 1) / kTile;
+  const int grid_dh = dh_grid(p.T_pad, H, p.V_ld);
+  const int64_t rows_max = p.T_pad > p.H_pad ? p.T_pad : int64_t(p.H_pad);
 
   // raising the dynamic-LDS limit is per function; done once per process, safely from any thread
   static std::once_flag attr_once;
@@ -1010,7 +1010,8 @@ extern "C" aero_status aero_lmhead_logprob_fused(
   if (T > 0) {
     hipLaunchKernelGGL(k_compact_valid, dim3(1), dim3(1024), 0, s, targets, T, p.T_pad, V,
                        bwd ? token_rollout : nullptr, adv, weight_rollout, R, (ent || kl_coef != 0.f) ? 1 : 0, fidx, nf,
-                       bwd ? pos : nullptr, bwd ? nact : nullptr, logprob, ent_arr, lse, err_flag);
+                       bwd ? pos : nullptr, bwd ? nact : nullptr, logprob, ent_arr, lse, err_flag, tiles_h, grid_dh,
+                       p.V_ld / kDK, rows_max);
     hipLaunchKernelGGL(k_gather_rows, dim3(unsigned(p.T_pad / 4)), dim3(256), 0, s, Hp, H, fidx, p.T_pad, hf);
     hipLaunchKernelGGL(k_target_logit, dim3(unsigned(p.T_pad / 4)), dim3(256), 0, s, Wp, hf, H, p.T_pad, fidx, nf,
                        targets, zy);
@@ -1052,13 +1053,11 @@ extern "C" aero_status aero_lmhead_logprob_fused(
   const int force = stored ? 0 : 1;
   if (T == 0) {   // no forward kernel ran: an empty candidate set for the kernels below
     hipLaunchKernelGGL(k_compact_valid, dim3(1), dim3(1024), 0, s, targets, T, p.T_pad, V, token_rollout, adv,
-                       weight_rollout, R, 0, fidx, nf, pos, nact, logprob, ent_arr, lse, err_flag);
+                       weight_rollout, R, 0, fidx, nf, pos, nact, logprob, ent_arr, lse, err_flag, tiles_h, grid_dh, p.V_ld / kDK,
+                       rows_max);
   }
   hipLaunchKernelGGL(k_candidate_scalars, dim3(unsigned(p.T_pad / 256)), dim3(256), 0, s, fidx, nact, g, ea, eb, lse,
                      logprob, targets, p.T_pad, p.VC, force, gc, lsec, yc, ac, bc, scale, dz, dzT);
-  const int tiles_h = (H + kTile - 1) / kTile;
-  const int grid_dh = dh_grid(p.T_pad, H, p.V_ld);
-  const int64_t rows_max = p.T_pad > p.H_pad ? p.T_pad : int64_t(p.H_pad);
   if (T > 0) {   // recompute mode only (the kernel leaves at once otherwise)
     const int n = p.tiles_v * tiles_t;
     if (ent)
@@ -1099,7 +1098,6 @@ extern "C" aero_status aero_lmhead_logprob_fused(
     }
   }
   if (T > 0)
-    hipLaunchKernelGGL(k_scatter_dh, dim3(unsigned(T)), dim3(256), 0, s, dh_acc, pos, nact, H, tiles_h, grid_dh,
-                       p.V_ld / kDK, rows_max, scale, reinterpret_cast<uint16_t*>(dhidden));
+    hipLaunchKernelGGL(k_scatter_dh, dim3(unsigned(T)), dim3(256), 0, s, dh_acc, pos, nact, H, scale, reinterpret_cast<uint16_t*>(dhidden));
   return launch_status();
 }
