@@ -75,11 +75,11 @@ __global__ __launch_bounds__(256) void k_signal_mask(
 
 // ---------------------------------------------------------------- token terms
 // LP_GIVEN: the current log-prob is read from `logprob_in` (fused LM-head path) instead of
-// being formed as z[t, y] - lse[t].
+// being formed as z[t, y] - lse[t]; lp_low holds what its rounding to 32 bits left off.
 template <int DT, bool LP_GIVEN>
 __global__ __launch_bounds__(256) void k_token_terms(
     const void* __restrict__ logits, int64_t T, int V, int64_t ld, const int32_t* __restrict__ targets,
-    const float* __restrict__ lse, const float* __restrict__ logprob_in,
+    const float* __restrict__ lse, const float* __restrict__ logprob_in, const float* __restrict__ lp_low,
     const float* __restrict__ old_logprob, const int32_t* __restrict__ token_rollout,
     const float* __restrict__ adv, const float* __restrict__ weight, int R,
     float eps_lo, float eps_hi, float grad_scale, float ent_coef, const float* __restrict__ entropy,
@@ -91,7 +91,7 @@ __global__ __launch_bounds__(256) void k_token_terms(
   if (t >= T) return;
   const int i = token_rollout[t];
   const int y = targets[t];
-  float g = 0.f, term = 0.f, lp = 0.f, ea = 0.f, eb = 0.f;
+  float g = 0.f, term = 0.f, lp = 0.f, low = 0.f, ea = 0.f, eb = 0.f;
   int flag = 0;
   if (i < 0 || y < 0) {
     // padding / ignored row: whatever its other index holds is not looked at
@@ -102,11 +102,12 @@ __global__ __launch_bounds__(256) void k_token_terms(
     if (w != 0.f && (A != 0.f || ent_coef != 0.f || kl_coef != 0.f)) {   // decided before the ratio is touched
       if constexpr (LP_GIVEN) {
         lp = logprob_in[t];
+        low = lp_low[t];
       } else {
         lp = load_elt<DT>(logits, int64_t(t) * ld + y) - lse[t];
       }
       if (A != 0.f) {
-        const float rho = expf(lp - old_logprob[t]);
+        const float rho = expf(lp - old_logprob[t] + low);
         const float lo = 1.f - eps_lo, hi = 1.f + eps_hi;
         const float clipped = fminf(fmaxf(rho, lo), hi);
         const float s = fminf(rho * A, clipped * A);
@@ -116,7 +117,7 @@ __global__ __launch_bounds__(256) void k_token_terms(
         flag = unclipped ? 1 : 2;
       }
       if (kl_coef != 0.f) {   // Eq. 2's beta term, per-token estimator exp(d) - d - 1, d = log pi_ref - log pi
-        const float d = ref_logprob[t] - lp;
+        const float d = ref_logprob[t] - lp - low;
         const float ed = expf(d);
         term += kl_coef * w * (ed - d - 1.f);
         g += grad_scale * kl_coef * w * (1.f - ed);
@@ -365,7 +366,7 @@ static void dispatch_dlogits_dtype(int32_t dtype, bool vec, const void* logits, 
 
 // Shared with the fused LM-head path: token terms from given log-probs, then the reduction.
 aero_status token_terms_from_logprob(int64_t T, int V, const int32_t* targets, const float* logprob,
-                                     const float* lse, const float* entropy, const float* old_logprob,
+                                     const float* lp_low, const float* lse, const float* entropy, const float* old_logprob,
                                      const int32_t* token_rollout, const float* adv, const float* weight, int R,
                                      float eps_lo, float eps_hi, float grad_scale, float ent_coef, float kl_coef,
                                      const float* ref_logprob, float* g, float* term, int32_t* flag, float* ea,
@@ -373,7 +374,7 @@ aero_status token_terms_from_logprob(int64_t T, int V, const int32_t* targets, c
   const unsigned blocks = unsigned((T + 255) / 256);
   if (T > 0)
     hipLaunchKernelGGL((k_token_terms<kBF16, true>), dim3(blocks), dim3(256), 0, s, nullptr, T, V, int64_t(0),
-                       targets, lse, logprob, old_logprob, token_rollout, adv, weight, R, eps_lo, eps_hi,
+                       targets, lse, logprob, lp_low, old_logprob, token_rollout, adv, weight, R, eps_lo, eps_hi,
                        grad_scale, ent_coef, entropy, kl_coef, ref_logprob, g, term, flag, ea, eb, nullptr, err_flag);
   hipLaunchKernelGGL(k_loss_reduce, dim3(1), dim3(kReduceNT), 0, s, term, flag, T, loss, clip_frac);
   return launch_status();
@@ -438,7 +439,8 @@ static aero_status loss_bwd_run(
                      : dtype == AERO_F16 ? k_token_terms<kF16, false>
                      : dtype == AERO_F8E4M3 ? k_token_terms<kF8, false> : k_token_terms<kF32, false>;
   hipLaunchKernelGGL(token_terms, dim3(blocks), dim3(256), 0, s, logits, T, V, ld, targets, lse,
-                     static_cast<const float*>(nullptr), old_logprob, token_rollout, adv, weight, R, eps_lo, eps_hi,
+                     static_cast<const float*>(nullptr), static_cast<const float*>(nullptr), old_logprob, token_rollout, adv, weight,
+                     R, eps_lo, eps_hi,
                      grad_scale, entropy_coef, entropy, kl_coef, ref_logprob, ws.g, ws.loss_term, ws.flag,
                      ent ? ws.ea : nullptr, ent ? ws.eb : nullptr, lp_dst, err_flag);
   hipLaunchKernelGGL(k_loss_reduce, dim3(1), dim3(kReduceNT), 0, s, ws.loss_term, ws.flag, T, loss, clip_frac);

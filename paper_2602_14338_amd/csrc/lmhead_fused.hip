@@ -32,7 +32,7 @@
 namespace aero {
 
 aero_status token_terms_from_logprob(int64_t T, int V, const int32_t* targets, const float* logprob,
-                                     const float* lse, const float* entropy, const float* old_logprob,
+                                     const float* lp_low, const float* lse, const float* entropy, const float* old_logprob,
                                      const int32_t* token_rollout, const float* adv, const float* weight, int R,
                                      float eps_lo, float eps_hi, float grad_scale, float ent_coef, float kl_coef,
                                      const float* ref_logprob, float* g, float* term, int32_t* flag, float* ea,
@@ -48,7 +48,7 @@ struct FusedPlan {
   int64_t T, T_pad;
   int V, V_ld, H, H_pad, tiles_v, VC, n_chunks;   // VC: vocabulary rows per chunk of the transposed dz
   size_t off_part, off_fidx, off_nf, off_g, off_term, off_flag, off_ea, off_eb, off_ent, off_zy, off_pos, off_nact,
-      off_gc, off_lsec, off_yc, off_ac, off_bc, off_scale,
+      off_lplow, off_gc, off_lsec, off_yc, off_ac, off_bc, off_scale,
       off_hc, off_hTc, off_WT, off_dz, off_dzT, off_dhacc, total;
 };
 
@@ -104,6 +104,7 @@ static FusedPlan make_plan(int64_t T, int V, int H) {
   p.off_zy = take(size_t(p.T_pad) * 4);
   p.off_pos = take(size_t(p.T_pad) * 4);
   p.off_nact = take(16);
+  p.off_lplow = take(size_t(p.T_pad) * 4);
   p.off_gc = take(size_t(p.T_pad) * 4);
   p.off_lsec = take(size_t(p.T_pad) * 4);
   p.off_yc = take(size_t(p.T_pad) * 4);
@@ -523,44 +524,56 @@ __global__ __launch_bounds__(256) void k_target_logit(
 
 // 64 consecutive compact rows per workgroup of 16 waves.  Phase 1: lane <-> row, the tiles_v
 // partials are split over the waves (every load is one coalesced 256-byte row segment) and merged
-// through LDS.  Phase 2: each wave takes 4 of the rows, merges their 16 partials and subtracts the
-// log-partition from the sampled token's logit (zy, from k_target_logit); results go to the row's
-// original position.
+// through LDS; a few hundred tokens are a handful of workgroups, so the loads of kCombineAhead partials are
+// issued before the first is merged (one at a time: 27 us whatever the token count up to 16384).  Phase 2: each
+// wave takes 4 of the rows, merges their 16 partials and subtracts the log-partition from the sampled token's
+// logit (zy, from k_target_logit); results go to the row's original position.  The log-partition and the
+// log-prob are formed in 64 bits: what their rounding to 32 loses of the log-prob goes to lp_low (nullable), so
+// that the ratio of the loss terms, whose sum cancels inside a group, does not carry it.
 constexpr int kCombineTokens = 64;
 constexpr int kCombineWaves = 16;
+constexpr int kCombineAhead = 8;
 __global__ __launch_bounds__(kCombineWaves * kWave) void k_fused_combine(
     int tiles_v, int64_t T_pad, const int32_t* __restrict__ fidx, const int32_t* __restrict__ nf,
     const float* __restrict__ part_m, const float* __restrict__ part_s, const float* __restrict__ part_sz,
     const float* __restrict__ zy, float* __restrict__ logprob, float* __restrict__ entropy,
-    float* __restrict__ lse_out) {
+    float* __restrict__ lse_out, float* __restrict__ lp_low) {
   __shared__ RowStat xs[kCombineWaves][kCombineTokens];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t j0 = int64_t(blockIdx.x) * kCombineTokens;   // j0 + 63 < T_pad
   const int n = nf[0];
   if (j0 >= n) return;
   RowStat st = stat_identity();
-  for (int tv = wave; tv < tiles_v; tv += kCombineWaves) {
-    const int64_t o = int64_t(tv) * T_pad + j0 + lane;
-    st = stat_merge(st, RowStat{part_m[o], part_s[o], part_sz[o]});
+  for (int tv = wave; tv < tiles_v; tv += kCombineAhead * kCombineWaves) {
+    RowStat v[kCombineAhead];
+#pragma unroll
+    for (int u = 0; u < kCombineAhead; ++u) {
+      const int at = tv + u * kCombineWaves;   // uniform over the wave
+      const int64_t o = int64_t(at) * T_pad + j0 + lane;
+      v[u] = at < tiles_v ? RowStat{part_m[o], part_s[o], part_sz[o]} : stat_identity();
+    }
+#pragma unroll
+    for (int u = 0; u < kCombineAhead; ++u) st = stat_merge(st, v[u]);
   }
   xs[wave][lane] = st;
   __syncthreads();
   constexpr int kPerWave = kCombineTokens / kCombineWaves;
-  for (int k4 = 0; k4 < kPerWave; ++k4) {
-    const int c = wave * kPerWave + k4;
-    const int64_t j = j0 + c;
-    if (j >= n) break;   // uniform per wave
-    const int64_t t = fidx[j];
-    // the 16 wave partials of this row, merged by a 16-lane tree in a fixed order
-    RowStat r = lane < kCombineWaves ? xs[lane][c] : stat_identity();
+  // the 16 wave partials of a row, merged by a 16-lane tree in a fixed order: 16 lanes per row
+  static_assert(kPerWave * kCombineWaves == kWave, "a wave's rows fill its lanes");
+  const int c = wave * kPerWave + lane / kCombineWaves;
+  RowStat r = xs[lane % kCombineWaves][c];
 #pragma unroll
-    for (int off = kCombineWaves / 2; off > 0; off >>= 1) r = stat_merge(r, stat_shfl_xor(r, off));
-    if (lane == 0) {
-      const float lse = r.m + logf(r.s);
-      logprob[t] = zy[j] - lse;
-      lse_out[t] = lse;
-      if (entropy) entropy[t] = lse - r.sz / r.s;
-    }
+  for (int off = kCombineWaves / 2; off > 0; off >>= 1) r = stat_merge(r, stat_shfl_xor(r, off));
+  const int64_t j = j0 + c;
+  if (lane % kCombineWaves == 0 && j < n) {
+    const int64_t t = fidx[j];
+    const double lse = double(r.m) + log(double(r.s));
+    const double lp = double(zy[j]) - lse;
+    const float lp32 = float(lp);
+    logprob[t] = lp32;
+    lse_out[t] = float(lse);
+    if (lp_low) lp_low[t] = float(lp - double(lp32));
+    if (entropy) entropy[t] = float(lse - double(r.sz) / double(r.s));
   }
 }
 
@@ -1000,6 +1013,7 @@ extern "C" aero_status aero_lmhead_logprob_fused(
   int32_t* pos = reinterpret_cast<int32_t*>(ws + p.off_pos);
   int32_t* nact = reinterpret_cast<int32_t*>(ws + p.off_nact);
   float* zy = reinterpret_cast<float*>(ws + p.off_zy);
+  float* lp_low = bwd ? reinterpret_cast<float*>(ws + p.off_lplow) : nullptr;
   uint16_t* hf = reinterpret_cast<uint16_t*>(ws + p.off_hc);   // rows with a target, candidates first
   uint16_t* dz = reinterpret_cast<uint16_t*>(ws + p.off_dz);
   uint16_t* dzT = reinterpret_cast<uint16_t*>(ws + p.off_dzT);
@@ -1025,7 +1039,7 @@ extern "C" aero_status aero_lmhead_logprob_fused(
                            V, H, p.tiles_v, p.T_pad, nf, part_m, part_s, part_sz, zy, p.VC, nact, dz, dzT);
     }
     hipLaunchKernelGGL(k_fused_combine, dim3(unsigned(p.T_pad / kCombineTokens)), dim3(kCombineWaves * kWave), 0, s,
-                       p.tiles_v, p.T_pad, fidx, nf, part_m, part_s, part_sz, zy, logprob, ent_arr, lse);
+                       p.tiles_v, p.T_pad, fidx, nf, part_m, part_s, part_sz, zy, logprob, ent_arr, lse, lp_low);
   }
   if (!bwd) return launch_status();
 
@@ -1035,7 +1049,7 @@ extern "C" aero_status aero_lmhead_logprob_fused(
   int32_t* flag = reinterpret_cast<int32_t*>(ws + p.off_flag);
   float* ea = ent ? reinterpret_cast<float*>(ws + p.off_ea) : nullptr;
   float* eb = ent ? reinterpret_cast<float*>(ws + p.off_eb) : nullptr;
-  aero_status st = token_terms_from_logprob(T, V, targets, logprob, lse, ent_arr, old_logprob, token_rollout, adv,
+  aero_status st = token_terms_from_logprob(T, V, targets, logprob, lp_low, lse, ent_arr, old_logprob, token_rollout, adv,
                                             weight_rollout, R, eps_lo, eps_hi, grad_scale, entropy_coef, kl_coef,
                                             ref_logprob, g, term, flag, ea, eb, loss, clip_frac, err_flag, s);
   if (st != AERO_OK) return st;
