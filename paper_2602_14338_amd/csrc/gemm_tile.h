@@ -280,9 +280,40 @@ __device__ __forceinline__ void dma_issue(__amdgpu_buffer_rsrc_t ra, __amdgpu_bu
   }
 }
 
+// An operand stored the other way round (BT): a row-major matrix whose rows are the contraction index, [K][rows],
+// e.g. the weight in dhidden = dz weight.  A slice is 64 rows of 256 columns (512 bytes, whole lines again); its LDS
+// image keeps that orientation, [64][256], and fragments come out of it with the transposing LDS read
+// (ds_read_b64_tr_b16): of every 16 lanes, lane j names four consecutive columns 4 (j % 4) .. of row j / 4, and
+// receives column j of those four rows, so two reads make the eight K values of a fragment.  The 32-byte
+// segments of a row are XORed with f(row) = row % 4 + 4 ((row / 8) % 2): the eight rows that 32 lanes touch at once
+// fall on distinct banks.
+__device__ __forceinline__ DmaLane dma_lane_bt(int col0, int64_t ld, int wave, int lane) {
+  // wave w fills rows [8 w, 8 w + 8) with 4 instructions of 2 rows; lane l covers chunk l % 32 of row l / 32
+  const uint32_t row = uint32_t(int64_t(wave * 8 + (lane >> 5)) * ld * 2 + int64_t(col0) * 2) + uint32_t(lane & 1) * 16;
+  const uint32_t seg = (lane & 31) >> 1, f = uint32_t(lane >> 5) | uint32_t(wave & 1) << 2;
+  return DmaLane{row + (seg ^ f) * 32, row + (seg ^ (f | 2)) * 32, uint32_t(4 * ld), uint32_t(kDK * ld * 2)};
+}
+__device__ __forceinline__ void frags_load_bt(Frags& f, const uint16_t* lds, int col0, int ks, int lane) {
+  typedef short s16x4_t __attribute__((ext_vector_type(4)));
+  typedef short s16x8_t __attribute__((ext_vector_type(8)));
+  typedef __attribute__((address_space(3))) s16x4_t lds_s16x4_t;
+  const int group = lane >> 4, j = lane & 15;
+  const int swz = (j >> 2) | (group & 1) << 2;
+  const uint16_t* base = lds + (ks * 32 + group * 8 + (j >> 2)) * kTile + (j & 3) * 4;
+#pragma unroll
+  for (int i = 0; i < kFragBlocks; ++i) {
+    const uint16_t* at = base + ((col0 / 16 + i) ^ swz) * 16;
+    const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)at);
+    const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)(at + 4 * kTile));
+    const s16x8_t both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    f[i] = __builtin_bit_cast(bf16x8_t, both);
+  }
+}
+
 // WARM: L2 warm-up two slices ahead (see below); a few per cent on the contractions whose
 // operands come from large read-only arrays, a loss on the split-K dhidden contraction.
-template <bool WARM, bool SWAP>
+// BT: operand B is [K][rows] (B.base, B.ld, B.bytes; B.kstep is not looked at).
+template <bool WARM, bool SWAP, bool BT = false>
 __device__ __forceinline__ void gemm_tile_dma(const DmaOperand& A, const DmaOperand& B, int K, int m0, int n0,
                                               uint16_t* smem, Acc& acc) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -291,7 +322,12 @@ __device__ __forceinline__ void gemm_tile_dma(const DmaOperand& A, const DmaOper
   const int nk = K / kDK;
   if (nk == 0) return;
   const __amdgpu_buffer_rsrc_t ra = operand_rsrc(A), rb = operand_rsrc(B);
-  const DmaLane la = dma_lane(m0, A, wave, lane), lb = dma_lane(n0, B, wave, lane);
+  static_assert(!(WARM && BT), "the warm-up assumes K-contiguous operands");
+  const DmaLane la = dma_lane(m0, A, wave, lane), lb = BT ? dma_lane_bt(n0, B.ld, wave, lane) : dma_lane(n0, B, wave, lane);
+  auto load_b = [&](Frags& f, const uint16_t* Bs, int ks) {
+    if constexpr (BT) frags_load_bt(f, Bs, wn * 64, ks, lane);
+    else frags_load(f, Bs, wn * 64, ks, lane);
+  };
   dma_issue(ra, rb, la, lb, 0, smem, wave);
   // L2 warm-up.  A fifth of a slice's lines miss L2 (the 32 workgroups resident on an XCD form an
   // 8 x 4 block of tiles: 12 operand slices for 32 tiles), and loads return in order, so one late
@@ -326,22 +362,30 @@ __device__ __forceinline__ void gemm_tile_dma(const DmaOperand& A, const DmaOper
     const uint16_t* Bs = As + kTile * kDK;
     Frags b0, b1, a0, a1, a2;
     frags_load(a0, As, wm * 128, 0, lane);
-    frags_load(b0, Bs, wn * 64, 0, lane);
+    load_b(b0, Bs, 0);
     frags_load(a1, As, wm * 128 + 64, 0, lane);
     frags_mma<SWAP>(a0, b0, 0, acc);
     if (prefetch) dma_issue(ra, rb, la, lb, kt + 1, smem + ((kt + 1) & 1) * kDStageElems, wave);
     frags_load(a2, As, wm * 128, 1, lane);
-    frags_load(b1, Bs, wn * 64, 1, lane);
+    load_b(b1, Bs, 1);
     frags_mma<SWAP>(a1, b0, 1, acc);
     frags_load(a0, As, wm * 128 + 64, 1, lane);
     frags_mma<SWAP>(a2, b1, 0, acc);
     constexpr int kMfma = 0x008, kVmemRd = 0x020, kDsRd = 0x100;
     constexpr int kMfmas = kFragBlocks * kNB;
-    __builtin_amdgcn_sched_group_barrier(kDsRd, 3 * kFragBlocks, 0);
+    constexpr int kReadsB = BT ? 2 * kFragBlocks : kFragBlocks;
+    __builtin_amdgcn_sched_group_barrier(kDsRd, 2 * kFragBlocks + kReadsB, 0);
     __builtin_amdgcn_sched_group_barrier(kMfma, kMfmas, 0);
     if (prefetch) __builtin_amdgcn_sched_group_barrier(kVmemRd, 8, 0);
 #pragma unroll
-    for (int r = 0; r < 3 * kFragBlocks; ++r) {
+    for (int r = 0; r < kFragBlocks; ++r) {
+      __builtin_amdgcn_sched_group_barrier(kMfma, 2, 0);
+      __builtin_amdgcn_sched_group_barrier(kDsRd, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(kMfma, 2, 0);
+      __builtin_amdgcn_sched_group_barrier(kDsRd, kReadsB / kFragBlocks, 0);
+    }
+#pragma unroll
+    for (int r = 0; r < kFragBlocks; ++r) {
       __builtin_amdgcn_sched_group_barrier(kMfma, 2, 0);
       __builtin_amdgcn_sched_group_barrier(kDsRd, 1, 0);
     }

@@ -47,6 +47,7 @@ inline size_t up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 struct FusedPlan {
   int64_t T, T_pad;
   int V, V_ld, H, H_pad, tiles_v, VC, n_chunks;   // VC: vocabulary rows per chunk of the transposed dz
+  bool direct;   // dhidden reads the weight as it is, no transposed copy
   size_t off_part, off_fidx, off_nf, off_g, off_term, off_flag, off_ea, off_eb, off_ent, off_zy, off_pos, off_nact,
       off_lplow, off_gc, off_lsec, off_yc, off_ac, off_bc, off_scale,
       off_hc, off_hTc, off_WT, off_dz, off_dzT, off_dhacc, total;
@@ -73,6 +74,15 @@ static int64_t dh_part_rows(int64_t T_pad, int H, int V_ld) {
   const int64_t by_cap = 64 * T_pad;                                                // S <= 64
   return by_grid < by_cap ? by_grid : by_cap;                                       // >= S * active rows for every S
 }
+
+// The dhidden contraction wants the weight with the vocabulary as the contiguous index.  Copying it into
+// that form costs a read and a write of the weight per call whatever the token count (165 us at H = 1536, 430 at
+// H = 3584 with V = 152 K); reading it as it is through the transposing LDS read makes the contraction
+// itself 13-15 % slower (LDS bound).  The two meet near 2800 candidate rows whatever V and H are, and candidates
+// are about two thirds of a call's rows.  Whole calls, copy against as it is, at H = 1536, V = 151936: 300 tokens
+// 1012 / 841 us, 1200 tokens 1676 / 1538, 4000 tokens 4222 / 4105, 5000 and 7000 tokens even; at H = 3584: 1200 tokens
+// 3396 / 3080, 4000 tokens even.
+constexpr int64_t kDirectRows = 4096;
 
 static FusedPlan make_plan(int64_t T, int V, int H) {
   FusedPlan p{};
@@ -113,7 +123,8 @@ static FusedPlan make_plan(int64_t T, int V, int H) {
   p.off_scale = take(size_t(p.T_pad) * 4);
   p.off_hc = take(size_t(p.T_pad) * H * 2);
   p.off_hTc = take(size_t(p.H_pad) * p.T_pad * 2);
-  p.off_WT = take(size_t(p.H_pad) * p.V_ld * 2);
+  p.direct = p.T_pad <= kDirectRows;
+  p.off_WT = take(p.direct ? 0 : size_t(p.H_pad) * p.V_ld * 2);
   p.off_dz = take(size_t(p.T_pad) * p.V_ld * 2);
   p.off_dzT = take(size_t(p.n_chunks) * p.VC * p.T_pad * 2);
   p.off_dhacc = take(size_t(dh_part_rows(p.T_pad, H, p.V_ld)) * H * 4);
@@ -786,9 +797,12 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_fused_dz(
 // ------------------------------------------------------------------------------------------
 // dh_part[s][t][h] = sum_{k in split s} X[t][k] W[k][h], X = the stored exponentials P (or dz itself on the recompute
 // route)     M = candidate tokens, N = H, K = vocabulary (padded)
+// DIRECT: the weight as the caller holds it, [V][H], through the transposing LDS read; otherwise WT, its copy in
+// K-slabs (see kDirectRows).
+template <bool DIRECT>
 __global__ __launch_bounds__(kGemmNT, 2) void k_gemm_dh(
-    const uint16_t* __restrict__ dz, const uint16_t* __restrict__ WT, int H_pad, int vK,
-    int H, int tiles_h, int64_t T_pad, const int32_t* __restrict__ nact, float* __restrict__ dh_part) {
+    const uint16_t* __restrict__ dz, const uint16_t* __restrict__ W, const uint16_t* __restrict__ WT, int V, int H_pad,
+    int vK, int H, int tiles_h, int64_t T_pad, const int32_t* __restrict__ nact, float* __restrict__ dh_part) {
   extern __shared__ __align__(16) uint16_t smem[];
   const int n_pad = nact[1];
   const int tiles_t = n_pad / kTile;
@@ -808,10 +822,15 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_gemm_dh(
   const int k_begin = min(vK, split * per * kDK);
   const int k_len = max(0, min(vK, (split + 1) * per * kDK) - k_begin);
   Acc acc;
-  // both operands are K-slabs over the vocabulary
-  gemm_tile_dma<false, true>(operand_slabs(dz + int64_t(k_begin / kDK) * T_pad * kDK, T_pad, k_len),
-                             operand_slabs(WT + int64_t(k_begin / kDK) * H_pad * kDK, H_pad, k_len), k_len, m0, n0, smem,
-                             acc);
+  const DmaOperand x = operand_slabs(dz + int64_t(k_begin / kDK) * T_pad * kDK, T_pad, k_len);
+  if constexpr (DIRECT) {
+    // weight rows past the vocabulary (the split may start there) lie past the operand's bytes and read as zeros
+    const DmaOperand w{W + int64_t(min(k_begin, V)) * H, H, 0, int64_t(max(V - k_begin, 0)) * H * 2};
+    gemm_tile_dma<false, true, true>(x, w, k_len, m0, n0, smem, acc);
+  } else {
+    gemm_tile_dma<false, true>(x, operand_slabs(WT + int64_t(k_begin / kDK) * H_pad * kDK, H_pad, k_len), k_len, m0, n0,
+                               smem, acc);
+  }
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wm = wave >> 2, wn = wave & 3;
   float* out = dh_part + int64_t(split) * n_pad * H;
@@ -1000,7 +1019,8 @@ extern "C" aero_status aero_lmhead_logprob_fused(
         set_lds(reinterpret_cast<const void*>(k_fused_stats<true>)) != AERO_OK ||
         set_lds(reinterpret_cast<const void*>(k_fused_dz<false>), kDzLdsBytes) != AERO_OK ||
         set_lds(reinterpret_cast<const void*>(k_fused_dz<true>), kDzLdsBytes) != AERO_OK ||
-        set_lds(reinterpret_cast<const void*>(k_gemm_dh)) != AERO_OK ||
+        set_lds(reinterpret_cast<const void*>(k_gemm_dh<true>)) != AERO_OK ||
+        set_lds(reinterpret_cast<const void*>(k_gemm_dh<false>)) != AERO_OK ||
         set_lds(reinterpret_cast<const void*>(k_gemm_dw<true>)) != AERO_OK ||
         set_lds(reinterpret_cast<const void*>(k_gemm_dw<false>)) != AERO_OK)
       attr_rc = AERO_ERR_HIP;
@@ -1087,14 +1107,19 @@ extern "C" aero_status aero_lmhead_logprob_fused(
   hipLaunchKernelGGL(transpose, dim3(unsigned(p.T_pad / 64), unsigned(p.H_pad / 64)), dim3(256), 0, s, hf,
                      int64_t(H), p.T_pad, H, p.H_pad, nullptr, p.T_pad, hTc, nullptr, int64_t(0), scale);
   // weight transposed to WT, K-slabs over the vocabulary; rows V..V_ld of the source do not exist -> zeros
-  hipLaunchKernelGGL(transpose, dim3(unsigned(p.V_ld / 64), unsigned(p.H_pad / 64)), dim3(256), 0, s, Wp,
-                     int64_t(H), int64_t(V), H, p.H_pad, nullptr, int64_t(p.V_ld), WT, nullptr, int64_t(0), nullptr);
+  if (!p.direct)
+    hipLaunchKernelGGL(transpose, dim3(unsigned(p.V_ld / 64), unsigned(p.H_pad / 64)), dim3(256), 0, s, Wp,
+                       int64_t(H), int64_t(V), H, p.H_pad, nullptr, int64_t(p.V_ld), WT, nullptr, int64_t(0), nullptr);
 
   // ---- the two gradient contractions over the whole vocabulary ----
   if (T > 0) {
     // dz columns [V, V_ld) are zero and WT is zero past V: the contraction runs over the padded vocabulary
-    hipLaunchKernelGGL(k_gemm_dh, dim3(unsigned(grid_dh)), dim3(kGemmNT), kGemmLdsBytes, s, dz, WT, p.H_pad, p.V_ld, H,
-                       tiles_h, p.T_pad, nact, dh_acc);
+    if (p.direct)
+      hipLaunchKernelGGL(k_gemm_dh<true>, dim3(unsigned(grid_dh)), dim3(kGemmNT), kGemmLdsBytes, s, dz, Wp, nullptr, V,
+                         p.H_pad, p.V_ld, H, tiles_h, p.T_pad, nact, dh_acc);
+    else
+      hipLaunchKernelGGL(k_gemm_dh<false>, dim3(unsigned(grid_dh)), dim3(kGemmNT), kGemmLdsBytes, s, dz, Wp, WT, V,
+                         p.H_pad, p.V_ld, H, tiles_h, p.T_pad, nact, dh_acc);
   }
   // dweight: one launch per chunk of the transposed dz.  VC is sized so that a full chunk is a whole
   // number of rounds of 256 tiles at the two model shapes (measured: 1 % faster than one long launch)
