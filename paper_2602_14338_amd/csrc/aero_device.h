@@ -66,6 +66,7 @@ constexpr int kF32 = AERO_F32, kBF16 = AERO_BF16, kF16 = AERO_F16, kF8 = AERO_F8
 template <int DT> struct Storage {
   static constexpr int kBytes = DT == kF32 ? 4 : DT == kF8 ? 1 : 2;
   static constexpr int kPerVec = 16 / kBytes;   // elements per 16-byte vector
+  static constexpr int kLogPerVec = DT == kF32 ? 2 : DT == kF8 ? 4 : 3;
 };
 inline bool storage_dtype_ok(int32_t dtype) {
   return dtype == AERO_BF16 || dtype == AERO_F32 || dtype == AERO_F16 || dtype == AERO_F8E4M3;
@@ -106,26 +107,63 @@ __device__ __forceinline__ RowStat stat_shfl_xor(RowStat a, int mask) {
   return RowStat{__shfl_xor(a.m, mask, kWave), __shfl_xor(a.s, mask, kWave), __shfl_xor(a.sz, mask, kWave)};
 }
 
-__device__ __forceinline__ RowStat stat_wave_reduce(RowStat a) {
-#pragma unroll
-  for (int off = kWave / 2; off > 0; off >>= 1) a = stat_merge(a, stat_shfl_xor(a, off));
-  return a;
+// All-reduce over the 16 lanes of a row, or over the wave, by lane permutations of the vector ALU (no LDS
+// round trips).  The mirrors stand for exchanges at distance 4 and 8: the lanes they mix are equal by then.
+template <int CTRL> __device__ __forceinline__ float dpp_move(float x) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
+}
+template <class Op> __device__ __forceinline__ float row16_reduce(float x, Op op) {
+  x = op(x, dpp_move<0xB1>(x));    // quad_perm [1,0,3,2]
+  x = op(x, dpp_move<0x4E>(x));    // quad_perm [2,3,0,1]
+  x = op(x, dpp_move<0x141>(x));   // row_half_mirror
+  return op(x, dpp_move<0x140>(x));   // row_mirror
+}
+template <class Op> __device__ __forceinline__ float wave_reduce(float x, Op op) {
+  x = row16_reduce(x, op);
+  const auto r16 = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  x = op(__uint_as_float(r16[0]), __uint_as_float(r16[1]));
+  const auto r32 = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return op(__uint_as_float(r32[0]), __uint_as_float(r32[1]));
 }
 
-// Workgroup-wide merge; every thread gets the result.  NT = threads per workgroup.
+// The common offset is reduced first, so that each lane rescales its sums once; WAVE: 64 lanes, else 16.
+template <bool WAVE> __device__ __forceinline__ RowStat stat_reduce(RowStat a) {
+  auto all = [](float x, auto op) { return WAVE ? wave_reduce(x, op) : row16_reduce(x, op); };
+  auto add = [](float x, float y) { return x + y; };
+  const float M = all(a.m, [](float x, float y) { return fmaxf(x, y); });
+  const float f = (a.m == M) ? 1.f : exp2_fast((a.m - M) * kLog2e);   // also -inf on both sides
+  return RowStat{M, all(a.s * f, add), all(a.sz * f, add)};
+}
+
+// Workgroup-wide merge; every thread gets the result.  NT = threads per workgroup (at most 1024).
+// (Merging pairs of states through LDS shuffles, then the waves' states one after the other in every
+// thread, cost 1.5 us of the 27 us a row of 151936 bf16 logits takes.)
 template <int NT>
 __device__ __forceinline__ RowStat stat_block_reduce(RowStat a, RowStat* lds /*[NT/64]*/) {
-  a = stat_wave_reduce(a);
-  if constexpr (NT > kWave) {
+  a = stat_reduce<true>(a);
+  constexpr int kWaves = NT / kWave;
+  static_assert(kWaves <= 16, "one lane per wave in the second step");
+  if constexpr (kWaves > 1) {
     const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
     if (lane == 0) lds[wave] = a;
     __syncthreads();
-    RowStat r = lds[0];
-#pragma unroll
-    for (int w = 1; w < NT / kWave; ++w) r = stat_merge(r, lds[w]);
-    a = r;
+    a = stat_reduce<false>(lane % 16 < kWaves ? lds[lane % 16] : stat_identity());
   }
   return a;
+}
+
+// What a row's state says about its sampled token: log-partition, log-prob, and what rounding the log-prob to 32
+// bits left off (for the ratio of the loss, whose terms cancel inside a group).  log s is corrected by
+// s exp(-log s) - 1, so that neither its own rounding nor that of the sum with the offset enters.
+struct RowLogProb {
+  float lse, lp, low;
+};
+__device__ __forceinline__ RowLogProb row_logprob(const RowStat& st, float zy) {
+  const float l = logf(st.s), fix = fmaf(st.s, expf(-l), -1.f);
+  const float d = zy - st.m;            // an exact difference of stored values, unless they are 32-bit
+  const float lp = d - l;
+  const float back = d - lp;            // two-sum: (d - l) - lp, exactly
+  return RowLogProb{st.m + (l + fix), lp, ((d - (lp + back)) + (back - l)) - fix};
 }
 
 // Fold N logits into a thread's running state.  The offset m is only moved when a value

@@ -1,9 +1,9 @@
 // Forward statistics, clipped loss terms and dlogits of one token row in a single pass over
-// HBM (softmax policy of App. C, surrogate of Eq. 2, gradient of App. A.1): the bf16 row is
-// read once into registers (19 x 16 bytes per thread at V = 151936 with 1024 threads), the
-// log-partition is reduced across the workgroup, and the gradient row is produced from the
-// registers - 4 bytes of traffic per logit instead of 6 for a forward pass followed by a
-// backward pass.
+// HBM (softmax policy of App. C, surrogate of Eq. 2, gradient of App. A.1): the row is read once
+// into registers (and LDS where it is long: 20 x 16 bytes per thread of 1024 at V = 151936 in bf16),
+// the log-partition is reduced across the workgroup, and the gradient row is produced from the
+// copy on chip - twice the row's bytes of traffic instead of three times for a forward pass followed
+// by a backward pass.  All storage types, any row length up to 20 x 1024 vectors, any row alignment.
 #include <mutex>
 
 #include "aero_device.h"
@@ -12,25 +12,66 @@ namespace aero {
 
 constexpr int kSpNT = 1024;
 
-// NV vectors of 16 bytes per thread: the first NV - NL live in registers, the last NL in LDS
-// (filled directly by buffer_load ... lds, each lane reads back only what its own wave loaded),
-// because 20 x 4 data registers plus the working set exceed the 128 VGPRs a 1024-thread
-// workgroup may use and the overflow would otherwise go to scratch memory in HBM.
+// A row as 16-byte aligned vectors: `head` elements in front of the first one, nvec vectors, and fewer than a
+// vector's worth behind.  Rows of a tensor whose pitch is not a multiple of 16 bytes differ in head, and
+// logits and dlogits of a row have the same one (single_pass_applicable).
+struct RowGeom {
+  int head, nvec;
+};
+template <int DT>
+__device__ __forceinline__ RowGeom row_geom(const void* base, int64_t t, int64_t ld, int V) {
+  constexpr int E = Storage<DT>::kPerVec;
+  const uint32_t first = uint32_t(reinterpret_cast<uintptr_t>(base) / Storage<DT>::kBytes) + uint32_t(t * ld);
+  const int head = min(int((E - first % E) % E), V);
+  return RowGeom{head, (V - head) / E};
+}
+// The element outside the vectors that this thread looks after, -1: none.  Threads 0 .. E-1 take the head,
+// E .. 2E-1 what is behind the last vector.
+template <int DT>
+__device__ __forceinline__ int ragged_elt(RowGeom r, int V, int tid) {
+  constexpr int E = Storage<DT>::kPerVec;
+  if (tid < E) return tid < r.head ? tid : -1;
+  const int j = r.head + r.nvec * E + tid - E;
+  return tid < 2 * E && j < V ? j : -1;
+}
+template <int DT> __device__ __forceinline__ char* row_ptr(const void* base, int64_t t, int64_t ld, int j = 0) {
+  return const_cast<char*>(reinterpret_cast<const char*>(base)) + (size_t(t) * size_t(ld) + size_t(j)) * Storage<DT>::kBytes;
+}
+template <int DT>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t row_vectors(const void* base, int64_t t, int64_t ld, RowGeom r) {
+  return __builtin_amdgcn_make_buffer_rsrc(row_ptr<DT>(base, t, ld, r.head), 0, r.nvec * 16, 0x00020000);
+}
+
+// One vector of the gradient row: dz_j = pi_j (a z_j + b) + g 1[j = y]; without the entropy bonus a = 0, b = -g.
+// own: the vector holds the sampled token, as its element ye.
+template <int DT, bool ENT>
+__device__ __forceinline__ u32x4_t grad_vec(const u32x4_t& src, float a, float b, float c, float g, bool own, int ye) {
+  constexpr int E = Storage<DT>::kPerVec;
+  float z[E], d[E];
+  unpack_vec<DT>(src, z);
+#pragma unroll
+  for (int e = 0; e < E; ++e) d[e] = (ENT ? fmaf(a, z[e], b) : b) * exp2_fast(fmaf(z[e], kLog2e, c));
+  if (own) {
+#pragma unroll
+    for (int e = 0; e < E; ++e) d[e] += (e == ye) ? g : 0.f;
+  }
+  return pack_vec<DT>(d);
+}
+
+// One workgroup per row, NV vectors of 16 bytes per thread in registers.
 // ENT: the optional terms are on: the entropy bonus (loss and gradient row) and / or the KL penalty
 // (a per-token scalar added to the loss term and to g); either coefficient may be 0.
-template <int NV, int NL, bool ENT>
-__global__ __launch_bounds__(kSpNT) void k_row_single_pass(
-    const uint16_t* logits, int64_t T, int V, int64_t ld, const int32_t* __restrict__ targets,
+template <int DT, int NT, int NV, bool ENT>
+__global__ __launch_bounds__(NT) void k_row_single_pass(
+    const void* logits, int64_t T, int V, int64_t ld, const int32_t* __restrict__ targets,
     const float* __restrict__ old_logprob, const int32_t* __restrict__ token_rollout,
     const float* __restrict__ adv, const float* __restrict__ weight, int R, float eps_lo, float eps_hi,
     float grad_scale, float ent_coef, float kl_coef, const float* __restrict__ ref_logprob, int stats_all,
     float* __restrict__ g_out, float* __restrict__ term_out,
     int32_t* __restrict__ flag_out, float* __restrict__ logprob_out, float* __restrict__ entropy_out,
-    float* __restrict__ lse_out, uint16_t* dlogits, int32_t* __restrict__ err_flag) {
-  __shared__ RowStat lds[kSpNT / kWave];
-  extern __shared__ __align__(16) u32x4_t parked_raw[];   // NL x kSpNT vectors (dynamic LDS)
-  u32x4_t(*parked)[kSpNT] = reinterpret_cast<u32x4_t(*)[kSpNT]>(parked_raw);
-  constexpr int NR = NV - NL;
+    float* __restrict__ lse_out, void* dlogits, int32_t* __restrict__ err_flag) {
+  __shared__ RowStat lds[NT / kWave];
+  constexpr int E = Storage<DT>::kPerVec;
   const int64_t t = blockIdx.x;
   const int tid = threadIdx.x;
   const int i = token_rollout[t];
@@ -44,18 +85,17 @@ __global__ __launch_bounds__(kSpNT) void k_row_single_pass(
   const bool signal = valid && A != 0.f && w != 0.f;
   const bool bonus = ENT && valid && w != 0.f;          // entropy bonus: every token of a weighted rollout
   const bool need = signal || bonus || (valid && stats_all);   // uniform over the workgroup
-  const size_t row_off = size_t(t) * size_t(ld);
-  const uint16_t* zrow = logits + row_off;
-  uint16_t* drow = dlogits ? dlogits + row_off : nullptr;
-  const int nvec = V / 8;
+  const RowGeom geom = row_geom<DT>(logits, t, ld, V);
+  const int nvec = geom.nvec, jr = ragged_elt<DT>(geom, V, tid);
+  const char* zrow = row_ptr<DT>(logits, t, ld);
+  char* drow = dlogits ? row_ptr<DT>(dlogits, t, ld) : nullptr;
   const u32x4_t zero = {0u, 0u, 0u, 0u};
 
   auto zero_fill = [&]() {
     if (!drow) return;
-    u32x4_t* dv = reinterpret_cast<u32x4_t*>(drow);
-    for (int k = tid; k < nvec; k += kSpNT) __builtin_nontemporal_store(zero, dv + k);
-    const int j = nvec * 8 + tid;
-    if (j < V) drow[j] = 0;
+    u32x4_t* dv = reinterpret_cast<u32x4_t*>(drow + geom.head * Storage<DT>::kBytes);
+    for (int k = tid; k < nvec; k += NT) __builtin_nontemporal_store(zero, dv + k);
+    if (jr >= 0) store_elt<DT>(drow, jr, 0.f);
   };
 
   if (!need) {
@@ -77,61 +117,38 @@ __global__ __launch_bounds__(kSpNT) void k_row_single_pass(
   // ---- the row -> registers.  Buffer loads: one 32-bit offset register instead of a 64-bit
   // pointer per vector, and the descriptor's bounds check returns zeros past the row's end
   // (validity is decided again at use).  aux = 2: non-temporal.
-  const __amdgpu_buffer_rsrc_t zsrc =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(zrow), 0, nvec * 16, 0x00020000);
+  const __amdgpu_buffer_rsrc_t zsrc = row_vectors<DT>(logits, t, ld, geom);
   const uint32_t voff = uint32_t(tid) * 16u;
-  u32x4_t v[NR];
+  u32x4_t v[NV];
 #pragma unroll
-  for (int u = 0; u < NR; ++u)
-    v[u] = __builtin_amdgcn_raw_buffer_load_b128(zsrc, voff + uint32_t(u) * (kSpNT * 16u), 0, 2);
-#pragma unroll
-  for (int u = NR; u < NV; ++u)   // lane l of wave w lands at parked[u - NR][64 w + l]
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(zsrc, &parked[u - NR][(tid >> 6) << 6], 16,
-                                             voff + uint32_t(u) * (kSpNT * 16u), 0, 0, 2);
-  const int jt = nvec * 8 + tid;   // ragged tail shorter than one vector
-  const bool has_tail = jt < V;
-  const float ztail = has_tail ? bf16_to_f32(zrow[jt]) : 0.f;
-  const float zy = bf16_to_f32(zrow[y]);   // read before any thread may overwrite the row in place
+  for (int u = 0; u < NV; ++u)
+    v[u] = __builtin_amdgcn_raw_buffer_load_b128(zsrc, voff + uint32_t(u) * (NT * 16u), 0, 2);
+  const float zr = jr >= 0 ? load_elt<DT>(zrow, jr) : 0.f;
+  const float zy = load_elt<DT>(zrow, y);   // read before any thread may overwrite the row in place
 
   RowStat st = stat_identity();
 #pragma unroll
-  for (int u = 0; u < NR; ++u)
-  {
-    if (tid + u * kSpNT < nvec) {
-      float z[8];
-      unpack8(v[u], z);
-      stat_update<8>(st, z);
+  for (int u = 0; u < NV; ++u) {
+    if (tid < nvec - u * NT) {
+      float z[E];
+      unpack_vec<DT>(v[u], z);
+      stat_update<E>(st, z);
     }
     __builtin_amdgcn_sched_barrier(0);   // one vector at a time: keeps temporaries from piling up
   }
-  if constexpr (NL > 0) {
-    // the compiler does not track loads that land in LDS: wait for this wave's own
-    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
-    asm volatile("" ::: "memory");
-#pragma unroll
-    for (int u = NR; u < NV; ++u) {
-      if (tid + u * kSpNT < nvec) {
-        const u32x4_t pv = parked[u - NR][tid];
-        float z[8];
-        unpack8(pv, z);
-        stat_update<8>(st, z);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  }
-  if (has_tail) {
-    float z[1] = {ztail};
+  if (jr >= 0) {
+    float z[1] = {zr};
     stat_update<1>(st, z);
   }
-  st = stat_block_reduce<kSpNT>(st, lds);   // contains the barrier that orders loads before stores
-  const float lse = st.m + logf(st.s);
-  const float lp = zy - lse;
+  st = stat_block_reduce<NT>(st, lds);   // contains the barrier that orders loads before stores
+  const RowLogProb own = row_logprob(st, zy);
+  const float lse = own.lse, lp = own.lp;
 
   // ---- token terms (every thread computes the same scalars) ----
   float g = 0.f, term = 0.f;
   int flag = 0;
   if (signal) {
-    const float rho = expf(lp - old_logprob[t]);
+    const float rho = expf(lp - old_logprob[t] + own.low);
     const float lo = 1.f - eps_lo, hi = 1.f + eps_hi;
     const float clipped = fminf(fmaxf(rho, lo), hi);
     const float s = fminf(rho * A, clipped * A);
@@ -143,7 +160,7 @@ __global__ __launch_bounds__(kSpNT) void k_row_single_pass(
   const float ent = lse - st.sz / st.s;
   // gradient row: dz_j = pi_j (a z_j + b) + g 1[j = y]; without the entropy bonus a = 0, b = -g
   if (bonus && kl_coef != 0.f) {   // Eq. 2's beta term: exp(d) - d - 1, d = log pi_ref - log pi
-    const float d = ref_logprob[t] - lp;
+    const float d = ref_logprob[t] - lp - own.low;
     const float ed = expf(d);
     term += kl_coef * w * (ed - d - 1.f);
     g += grad_scale * kl_coef * w * (1.f - ed);
@@ -170,44 +187,23 @@ __global__ __launch_bounds__(kSpNT) void k_row_single_pass(
 
   // ---- gradient row from the registers ----
   const float c = -lse * kLog2e;
-  const __amdgpu_buffer_rsrc_t dsrc = __builtin_amdgcn_make_buffer_rsrc(drow, 0, nvec * 16, 0x00020000);
+  const __amdgpu_buffer_rsrc_t dsrc = row_vectors<DT>(dlogits, t, ld, geom);
   // the store offsets are formed again from an opaque copy of the lane offset; otherwise the
   // compiler keeps all NV load offsets alive across the reduction just to reuse them here
   uint32_t voff_st = voff;
   asm volatile("" : "+v"(voff_st));
-  const int yvec = y >> 3;
+  const int yvec = (y - geom.head) >> Storage<DT>::kLogPerVec, ye = (y - geom.head) & (E - 1);   // head: yvec = -1
 #pragma unroll
   for (int u = 0; u < NV; ++u) {
-    const int k = tid + u * kSpNT;
-    if (k < nvec) {
-      float z[8], d[8];
-      u32x4_t src;
-      if constexpr (NL > 0) {
-        if (u < NR) src = v[u < NR ? u : 0];
-        else src = parked[u >= NR ? u - NR : 0][tid];
-      } else {
-        src = v[u];
-      }
-      unpack8(src, z);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) d[e] = (ENT ? fmaf(a, z[e], ng) : ng) * exp2_fast(fmaf(z[e], kLog2e, c));
-      if (k == yvec) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) d[e] += (e == (y & 7)) ? g : 0.f;
-      }
-      u32x4_t o;
-      o.x = pack_bf16x2(d[0], d[1]);
-      o.y = pack_bf16x2(d[2], d[3]);
-      o.z = pack_bf16x2(d[4], d[5]);
-      o.w = pack_bf16x2(d[6], d[7]);
-      __builtin_amdgcn_raw_buffer_store_b128(o, dsrc, voff_st + uint32_t(u) * (kSpNT * 16u), 0, 2);
-    }
+    if (tid < nvec - u * NT)
+      __builtin_amdgcn_raw_buffer_store_b128(grad_vec<DT, ENT>(v[u], a, ng, c, g, tid == yvec - u * NT, ye), dsrc,
+                                             voff_st + uint32_t(u) * (NT * 16u), 0, 2);
     __builtin_amdgcn_sched_barrier(0);
   }
-  if (has_tail) {
-    float d = (ENT ? fmaf(a, ztail, ng) : ng) * exp2_fast(fmaf(ztail, kLog2e, c));
-    if (jt == y) d += g;
-    drow[jt] = f32_to_bf16(d);
+  if (jr >= 0) {
+    float d = (ENT ? fmaf(a, zr, ng) : ng) * exp2_fast(fmaf(zr, kLog2e, c));
+    if (jr == y) d += g;
+    store_elt<DT>(drow, jr, d);
   }
 }
 
@@ -292,15 +288,15 @@ __global__ __launch_bounds__(256) void k_row_order(int64_t T, int V, int R, cons
   if (in && !need && !untouched) order[T - 1 - (base_rest + __popcll(m_rest & below))] = int32_t(t);
 }
 
-template <int NV, int NL, bool ENT>
+template <int DT, int NV, int NL, bool ENT>
 __global__ __launch_bounds__(kSpNT) void k_row_stream(
-    const uint16_t* logits, int64_t T, int V, int64_t ld, const int32_t* __restrict__ targets,
+    const void* logits, int64_t T, int V, int64_t ld, const int32_t* __restrict__ targets,
     const float* __restrict__ old_logprob, const int32_t* __restrict__ token_rollout,
     const float* __restrict__ adv, const float* __restrict__ weight, int R, float eps_lo, float eps_hi,
     float grad_scale, float ent_coef, float kl_coef, const float* __restrict__ ref_logprob, int stats_all,
     float* __restrict__ g_out, float* __restrict__ term_out,
     int32_t* __restrict__ flag_out, float* __restrict__ logprob_out, float* __restrict__ entropy_out,
-    float* __restrict__ lse_out, uint16_t* dlogits, int32_t* __restrict__ err_flag, int32_t* row_counter,
+    float* __restrict__ lse_out, void* dlogits, int32_t* __restrict__ err_flag, int32_t* row_counter,
     const int32_t* __restrict__ order) {
   // positions 0 .. P of the hand-out skip the gap that the untouched rows leave in the row order
   const int n_front = row_counter[1];
@@ -313,16 +309,9 @@ __global__ __launch_bounds__(kSpNT) void k_row_stream(
   u32x4_t(*slots)[kSpNT] = reinterpret_cast<u32x4_t(*)[kSpNT]>(slots_raw);
   constexpr int NR = NV - NL;
   const int tid = threadIdx.x;
-  const int nvec = V / 8;
+  constexpr int E = Storage<DT>::kPerVec;
   const uint32_t voff = uint32_t(tid) * 16u;
   const u32x4_t zero = {0u, 0u, 0u, 0u};
-  const int jt = nvec * 8 + tid;   // ragged tail shorter than one vector
-  const bool has_tail = jt < V;
-
-  auto row_rsrc = [&](const uint16_t* base, int64_t row) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(base + size_t(row) * size_t(ld)), 0, nvec * 16,
-                                             0x00020000);
-  };
   auto dma_slot = [&](__amdgpu_buffer_rsrc_t src, int u) {   // lane l of wave w lands at slots[u][64 w + l]
     __builtin_amdgcn_raw_ptr_buffer_load_lds(src, &slots[u][(tid >> 6) << 6], 16,
                                              voff + uint32_t(u) * (kSpNT * 16u), 0, 0, 2);
@@ -333,11 +322,14 @@ __global__ __launch_bounds__(kSpNT) void k_row_stream(
   int64_t t = row_at(blockIdx.x);
   if (tid == 0) s_next = atomicAdd(row_counter, 1);
   __syncthreads();
-  int64_t pn = s_next;
+  // uniform values read from LDS look divergent to the compiler: said explicitly, the row's pointers, descriptors
+  // and scalars live in scalar registers
+  int64_t pn = __builtin_amdgcn_readfirstlane(s_next);
   int64_t tn = row_at(pn);
   RowInfo cur = row_info(t, T, V, R, targets, token_rollout, adv, weight, stats_all, ENT);
+  RowGeom geom = row_geom<DT>(logits, t, ld, V);
   if (cur.need) {
-    const __amdgpu_buffer_rsrc_t src = row_rsrc(logits, t);
+    const __amdgpu_buffer_rsrc_t src = row_vectors<DT>(logits, t, ld, geom);
 #pragma unroll
     for (int u = 0; u < NL; ++u) dma_slot(src, u);
   }
@@ -345,22 +337,28 @@ __global__ __launch_bounds__(kSpNT) void k_row_stream(
   int reduces = 0;   // selects the LDS buffer of the next reduction
   while (t < T) {
     const RowInfo nxt = row_info(tn, T, V, R, targets, token_rollout, adv, weight, stats_all, ENT);
-    const uint16_t* zrow = logits + size_t(t) * size_t(ld);
-    uint16_t* drow = dlogits ? dlogits + size_t(t) * size_t(ld) : nullptr;
-    const __amdgpu_buffer_rsrc_t nsrc = row_rsrc(logits, nxt.need ? tn : t);
+    const int nvec = geom.nvec, jr = ragged_elt<DT>(geom, V, tid);
+    const char* zrow = row_ptr<DT>(logits, t, ld);
+    char* drow = dlogits ? row_ptr<DT>(dlogits, t, ld) : nullptr;
+    const RowGeom ngeom = nxt.need ? row_geom<DT>(logits, tn, ld, V) : geom;
+    const __amdgpu_buffer_rsrc_t nsrc = row_vectors<DT>(logits, nxt.need ? tn : t, ld, ngeom);
     float g = 0.f, term = 0.f, lp = 0.f, ent = 0.f, lse = 0.f;
     float ea = 0.f;   // entropy bonus: grad_scale c w of this row (ENT only)
     int flag = 0;
     u32x4_t v[NR];
-    float ztail = 0.f;
+    float zr = 0.f;
 
     if (cur.need) {   // uniform over the workgroup
-      const __amdgpu_buffer_rsrc_t zsrc = row_rsrc(logits, t);
+      const __amdgpu_buffer_rsrc_t zsrc = row_vectors<DT>(logits, t, ld, geom);
+      // thread offsets are formed per row from opaque copies (and bounds compared on the scalar side): hoisted out
+      // of the row loop they are forty registers, which the variants with the optional terms would spill
+      uint32_t voff_ld = voff;
+      asm volatile("" : "+v"(voff_ld));
 #pragma unroll
       for (int u = 0; u < NR; ++u)
-        v[u] = __builtin_amdgcn_raw_buffer_load_b128(zsrc, voff + uint32_t(NL + u) * (kSpNT * 16u), 0, 2);
-      ztail = has_tail ? bf16_to_f32(zrow[jt]) : 0.f;
-      const float zy = bf16_to_f32(zrow[cur.y]);   // read before any thread may overwrite the row in place
+        v[u] = __builtin_amdgcn_raw_buffer_load_b128(zsrc, voff_ld + uint32_t(NL + u) * (kSpNT * 16u), 0, 2);
+      zr = jr >= 0 ? load_elt<DT>(zrow, jr) : 0.f;
+      const float zy = load_elt<DT>(zrow, cur.y);   // read before any thread may overwrite the row in place
       // Loads return in order and at least NR + 1 of them were issued just above: once no more
       // than NR memory operations are outstanding, the older loads into this wave's LDS slots
       // have landed (the compiler does not track those; stores may retire in any order, they
@@ -372,33 +370,34 @@ __global__ __launch_bounds__(kSpNT) void k_row_stream(
       RowStat st = stat_identity();
 #pragma unroll
       for (int u = 0; u < NL; ++u) {
-        if (tid + u * kSpNT < nvec) {
+        if (tid < nvec - u * kSpNT) {
           const u32x4_t pv = slots[u][tid];
-          float z[8];
-          unpack8(pv, z);
-          stat_update<8>(st, z);
+          float z[E];
+          unpack_vec<DT>(pv, z);
+          stat_update<E>(st, z);
         }
         __builtin_amdgcn_sched_barrier(0);   // one vector at a time: keeps temporaries from piling up
       }
 #pragma unroll
       for (int u = 0; u < NR; ++u) {
-        if (tid + (NL + u) * kSpNT < nvec) {
-          float z[8];
-          unpack8(v[u], z);
-          stat_update<8>(st, z);
+        if (tid < nvec - (NL + u) * kSpNT) {
+          float z[E];
+          unpack_vec<DT>(v[u], z);
+          stat_update<E>(st, z);
         }
         __builtin_amdgcn_sched_barrier(0);
       }
-      if (has_tail) {
-        float z[1] = {ztail};
+      if (jr >= 0) {
+        float z[1] = {zr};
         stat_update<1>(st, z);
       }
       st = stat_block_reduce<kSpNT>(st, lds[reduces++ & 1]);   // its barrier also orders loads before stores
-      lse = st.m + logf(st.s);
-      lp = zy - lse;
+      const RowLogProb own = row_logprob(st, zy);
+      lse = own.lse;
+      lp = own.lp;
       ent = lse - st.sz / st.s;
       if (cur.signal) {   // every thread computes the same scalars
-        const float rho = expf(lp - old_logprob[t]);
+        const float rho = expf(lp - old_logprob[t] + own.low);
         const float lo = 1.f - eps_lo, hi = 1.f + eps_hi;
         const float clipped = fminf(fmaxf(rho, lo), hi);
         const float s = fminf(rho * cur.A, clipped * cur.A);
@@ -410,7 +409,7 @@ __global__ __launch_bounds__(kSpNT) void k_row_stream(
       if constexpr (ENT) {
         if (cur.bonus) {
           if (kl_coef != 0.f) {   // Eq. 2's beta term: exp(d) - d - 1, d = log pi_ref - log pi
-            const float d = ref_logprob[t] - lp;
+            const float d = ref_logprob[t] - lp - own.low;
             const float ed = expf(d);
             term += kl_coef * cur.w * (ed - d - 1.f);
             g += grad_scale * kl_coef * cur.w * (1.f - ed);
@@ -439,45 +438,31 @@ __global__ __launch_bounds__(kSpNT) void k_row_stream(
       // gradient row: dz_j = pi_j (a z_j + ng) + g 1[j = y]; without the entropy bonus a = 0, ng = -g
       const float a = ea;
       const float ng = ENT ? ea * (ent - lse) - g : -g;
-      const __amdgpu_buffer_rsrc_t dsrc = row_rsrc(dlogits, t);
-      uint32_t voff_st = voff;   // opaque copy: keeps the load offsets from being kept alive for reuse
+      const __amdgpu_buffer_rsrc_t dsrc = row_vectors<DT>(dlogits, t, ld, geom);
+      uint32_t voff_st = voff;
       asm volatile("" : "+v"(voff_st));
-      const int y = cur.y, yvec = y >> 3;
-      auto grad_vec = [&](const u32x4_t& src, int k) -> u32x4_t {
-        float z[8], d[8];
-        unpack8(src, z);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) d[e] = (ENT ? fmaf(a, z[e], ng) : ng) * exp2_fast(fmaf(z[e], kLog2e, c));
-        if (k == yvec) {
-#pragma unroll
-          for (int e = 0; e < 8; ++e) d[e] += (e == (y & 7)) ? g : 0.f;
-        }
-        u32x4_t o;
-        o.x = pack_bf16x2(d[0], d[1]);
-        o.y = pack_bf16x2(d[2], d[3]);
-        o.z = pack_bf16x2(d[4], d[5]);
-        o.w = pack_bf16x2(d[6], d[7]);
-        return o;
-      };
+      const int y = cur.y, yvec = (y - geom.head) >> Storage<DT>::kLogPerVec, ye = (y - geom.head) & (E - 1);
 #pragma unroll
       for (int u = 0; u < NL; ++u) {   // LDS part first: each slot is refilled right after its last use
-        const int k = tid + u * kSpNT;
         const u32x4_t pv = slots[u][tid];
-        if (k < nvec) __builtin_amdgcn_raw_buffer_store_b128(grad_vec(pv, k), dsrc, voff_st + uint32_t(u) * (kSpNT * 16u), 0, 2);
+        if (tid < nvec - u * kSpNT)
+          __builtin_amdgcn_raw_buffer_store_b128(grad_vec<DT, ENT>(pv, a, ng, c, g, tid == yvec - u * kSpNT, ye), dsrc,
+                                                 voff_st + uint32_t(u) * (kSpNT * 16u), 0, 2);
         asm volatile("" ::: "memory");
         if (nxt.need) dma_slot(nsrc, u);
         __builtin_amdgcn_sched_barrier(0);
       }
 #pragma unroll
       for (int u = 0; u < NR; ++u) {
-        const int k = tid + (NL + u) * kSpNT;
-        if (k < nvec) __builtin_amdgcn_raw_buffer_store_b128(grad_vec(v[u], k), dsrc, voff_st + uint32_t(NL + u) * (kSpNT * 16u), 0, 2);
+        if (tid < nvec - (NL + u) * kSpNT)
+          __builtin_amdgcn_raw_buffer_store_b128(grad_vec<DT, ENT>(v[u], a, ng, c, g, tid == yvec - (NL + u) * kSpNT, ye), dsrc,
+                                                 voff_st + uint32_t(NL + u) * (kSpNT * 16u), 0, 2);
         __builtin_amdgcn_sched_barrier(0);
       }
-      if (has_tail) {
-        float d = (ENT ? fmaf(a, ztail, ng) : ng) * exp2_fast(fmaf(ztail, kLog2e, c));
-        if (jt == y) d += g;
-        drow[jt] = f32_to_bf16(d);
+      if (jr >= 0) {
+        float d = (ENT ? fmaf(a, zr, ng) : ng) * exp2_fast(fmaf(zr, kLog2e, c));
+        if (jr == y) d += g;
+        store_elt<DT>(drow, jr, d);
       }
     } else {
       // this row's slots are no longer needed: make sure every read of them has returned
@@ -488,9 +473,9 @@ __global__ __launch_bounds__(kSpNT) void k_row_stream(
         for (int u = 0; u < NL; ++u) dma_slot(nsrc, u);
       }
       if (drow) {   // zero fill
-        u32x4_t* dv = reinterpret_cast<u32x4_t*>(drow);
+        u32x4_t* dv = reinterpret_cast<u32x4_t*>(drow + geom.head * Storage<DT>::kBytes);
         for (int k = tid; k < nvec; k += kSpNT) __builtin_nontemporal_store(zero, dv + k);
-        if (has_tail) drow[jt] = 0;
+        if (jr >= 0) store_elt<DT>(drow, jr, 0.f);
       }
     }
     // hand-over: the row after the next one is drawn now (all threads have read s_next)
@@ -498,8 +483,9 @@ __global__ __launch_bounds__(kSpNT) void k_row_stream(
     if (tid == 0) s_next = pn < P ? atomicAdd(row_counter, 1) : int(T);
     __syncthreads();
     cur = nxt;
+    geom = row_geom<DT>(logits, tn, ld, V);
     t = tn;
-    pn = s_next;
+    pn = __builtin_amdgcn_readfirstlane(s_next);
     tn = row_at(pn);
   }
 }
@@ -513,71 +499,104 @@ __global__ void k_set_counter(int32_t* ctr, int32_t v) {
   ctr[3] = 0;
 }
 
-// True when the single-pass kernel applies: bf16, 16-byte aligned rows, and a row that fits
-// the register budget of one 1024-thread workgroup.
-bool single_pass_applicable(int32_t dtype, int V, int64_t ld, const void* logits, const void* dlogits) {
-  const int nvec = V / 8;
-  return dtype == AERO_BF16 && nvec >= kSpNT && nvec <= 20 * kSpNT && (ld % 8) == 0 &&
-         reinterpret_cast<uintptr_t>(logits) % 16 == 0 && reinterpret_cast<uintptr_t>(dlogits) % 16 == 0;
+// True when a single-pass kernel applies: element-aligned rows of at most 20 vectors per thread of 1024, and
+// logits and dlogits alike in their position relative to 16 bytes.
+constexpr int kStreamVecs = 20;
+bool single_pass_applicable(int32_t dtype, int V, const void* logits, const void* dlogits) {
+  const uintptr_t z = reinterpret_cast<uintptr_t>(logits), d = reinterpret_cast<uintptr_t>(dlogits);
+  const size_t elt = storage_bytes(dtype);
+  return size_t(V) * elt / 16 <= size_t(kStreamVecs) * kSpNT && z % elt == 0 && (!dlogits || z % 16 == d % 16);
 }
 
-template <bool ENT>
-static aero_status single_pass_launch_t(const uint16_t* z, int64_t T, int V, int64_t ld, const int32_t* targets,
-                                        const float* old_logprob, const int32_t* token_rollout, const float* adv,
-                                        const float* weight, int R, float eps_lo, float eps_hi, float grad_scale,
-                                        float ent_coef, float kl_coef, const float* ref_logprob, int stats_all,
-                                        float* g, float* term, int32_t* flag,
-                                        float* logprob_out, float* entropy_out, float* lse_out, uint16_t* dz,
-                                        int32_t* err_flag, int32_t* row_counter, int32_t* row_order, hipStream_t s) {
-  if (V / 8 <= 8 * kSpNT) {
-    hipLaunchKernelGGL((k_row_single_pass<8, 0, ENT>), dim3(unsigned(T)), dim3(kSpNT), 0, s, z, T, V, ld, targets,
-                       old_logprob, token_rollout, adv, weight, R, eps_lo, eps_hi, grad_scale, ent_coef, kl_coef, ref_logprob,
-                       stats_all, g, term, flag, logprob_out, entropy_out, lse_out, dz, err_flag);
-    return AERO_OK;
+struct RowArgs {
+  const void* logits;
+  int64_t T;
+  int V;
+  int64_t ld;
+  const int32_t* targets;
+  const float* old_logprob;
+  const int32_t* token_rollout;
+  const float *adv, *weight;
+  int R;
+  float eps_lo, eps_hi, grad_scale, ent_coef, kl_coef;
+  const float* ref_logprob;
+  int stats_all;
+  float *g, *term;
+  int32_t* flag;
+  float *logprob_out, *entropy_out, *lse_out;
+  void* dlogits;
+  int32_t* err_flag;
+};
+
+template <int DT, int NT, bool ENT>
+static void launch_rows(const RowArgs& r, hipStream_t s) {
+  hipLaunchKernelGGL((k_row_single_pass<DT, NT, 8, ENT>), dim3(unsigned(r.T)), dim3(NT), 0, s, r.logits, r.T, r.V, r.ld,
+                     r.targets, r.old_logprob, r.token_rollout, r.adv, r.weight, r.R, r.eps_lo, r.eps_hi, r.grad_scale,
+                     r.ent_coef, r.kl_coef, r.ref_logprob, r.stats_all, r.g, r.term, r.flag, r.logprob_out,
+                     r.entropy_out, r.lse_out, r.dlogits, r.err_flag);
+}
+
+template <int DT, bool ENT>
+static aero_status single_pass_launch_t(const RowArgs& r, int32_t* row_counter, int32_t* row_order, hipStream_t s) {
+  // the smallest workgroup whose threads hold the row in 8 vectors each, so that a CU works on several rows
+  const int nvec = r.V / Storage<DT>::kPerVec;
+  if (nvec <= 8 * 64) launch_rows<DT, 64, ENT>(r, s);
+  else if (nvec <= 8 * 256) launch_rows<DT, 256, ENT>(r, s);
+  else if (nvec <= 8 * 512) launch_rows<DT, 512, ENT>(r, s);
+  else if (nvec <= 8 * kSpNT) launch_rows<DT, kSpNT, ENT>(r, s);
+  else {
+    constexpr int NL = 9;
+    constexpr int kLdsBytes = NL * kSpNT * 16;   // 144 KB of wave-private slots
+    const auto kernel = k_row_stream<DT, kStreamVecs, NL, ENT>;
+    // raising the dynamic-LDS limit is per function; done once per process, safely from any thread
+    static std::once_flag attr_once;
+    static hipError_t attr_rc = hipSuccess;
+    std::call_once(attr_once, [&] {
+      attr_rc = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    kLdsBytes);
+    });
+    if (attr_rc != hipSuccess) return AERO_ERR_HIP;
+    int dev = 0, cus = 256;
+    if (hipGetDevice(&dev) == hipSuccess) {
+      int n = 0;
+      if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0) cus = n;
+    }
+    const unsigned grid = unsigned(r.T < cus ? r.T : cus);   // one persistent workgroup per CU
+    hipLaunchKernelGGL(k_set_counter, dim3(1), dim3(1), 0, s, row_counter, int32_t(grid));
+    hipLaunchKernelGGL(k_row_order, dim3(unsigned((r.T + 255) / 256)), dim3(256), 0, s, r.T, r.V, r.R, r.targets,
+                       r.token_rollout, r.adv, r.weight, r.stats_all, ENT ? 1 : 0, row_counter, row_order, r.g, r.term,
+                       r.flag, r.logprob_out, r.entropy_out, r.lse_out);
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(kSpNT), kLdsBytes, s, r.logits, r.T, r.V, r.ld, r.targets,
+                       r.old_logprob, r.token_rollout, r.adv, r.weight, r.R, r.eps_lo, r.eps_hi, r.grad_scale, r.ent_coef,
+                       r.kl_coef, r.ref_logprob, r.stats_all, r.g, r.term, r.flag, r.logprob_out, r.entropy_out, r.lse_out,
+                       r.dlogits, r.err_flag, row_counter, row_order);
   }
-  constexpr int NL = 9;
-  constexpr int kLdsBytes = NL * kSpNT * 16;   // 144 KB of wave-private slots
-  // raising the dynamic-LDS limit is per function; done once per process, safely from any thread
-  static std::once_flag attr_once;
-  static hipError_t attr_rc = hipSuccess;
-  std::call_once(attr_once, [] {
-    attr_rc = hipFuncSetAttribute(reinterpret_cast<const void*>(k_row_stream<20, NL, ENT>),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
-  });
-  if (attr_rc != hipSuccess) return AERO_ERR_HIP;
-  int dev = 0, cus = 256;
-  if (hipGetDevice(&dev) == hipSuccess) {
-    int n = 0;
-    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0) cus = n;
-  }
-  const unsigned grid = unsigned(T < cus ? T : cus);   // one persistent workgroup per CU
-  hipLaunchKernelGGL(k_set_counter, dim3(1), dim3(1), 0, s, row_counter, int32_t(grid));
-  hipLaunchKernelGGL(k_row_order, dim3(unsigned((T + 255) / 256)), dim3(256), 0, s, T, V, R, targets, token_rollout,
-                     adv, weight, stats_all, ENT ? 1 : 0, row_counter, row_order, g, term, flag, logprob_out,
-                     entropy_out, lse_out);
-  hipLaunchKernelGGL((k_row_stream<20, NL, ENT>), dim3(grid), dim3(kSpNT), kLdsBytes, s, z, T, V, ld, targets,
-                     old_logprob, token_rollout, adv, weight, R, eps_lo, eps_hi, grad_scale, ent_coef, kl_coef, ref_logprob,
-                     stats_all, g, term, flag, logprob_out, entropy_out, lse_out, dz, err_flag, row_counter, row_order);
   return AERO_OK;
 }
 
-// A non-zero entropy or KL coefficient selects the kernels that carry the optional terms.
-aero_status single_pass_launch(const void* logits, int64_t T, int V, int64_t ld, const int32_t* targets,
+template <int DT>
+static aero_status single_pass_launch_dt(const RowArgs& r, int32_t* row_counter, int32_t* row_order, hipStream_t s) {
+  // a non-zero entropy or KL coefficient selects the kernels that carry the optional terms
+  return r.ent_coef != 0.f || r.kl_coef != 0.f ? single_pass_launch_t<DT, true>(r, row_counter, row_order, s)
+                                               : single_pass_launch_t<DT, false>(r, row_counter, row_order, s);
+}
+
+aero_status single_pass_launch(const void* logits, int32_t dtype, int64_t T, int V, int64_t ld, const int32_t* targets,
                                const float* old_logprob, const int32_t* token_rollout, const float* adv,
                                const float* weight, int R, float eps_lo, float eps_hi, float grad_scale,
                                float ent_coef, float kl_coef, const float* ref_logprob, int stats_all, float* g,
                                float* term, int32_t* flag, float* logprob_out, float* entropy_out, float* lse_out,
                                void* dlogits, int32_t* err_flag, int32_t* row_counter, int32_t* row_order,
                                hipStream_t s) {
-  const uint16_t* z = reinterpret_cast<const uint16_t*>(logits);
-  uint16_t* dz = reinterpret_cast<uint16_t*>(dlogits);
-  if (ent_coef != 0.f || kl_coef != 0.f)
-    return single_pass_launch_t<true>(z, T, V, ld, targets, old_logprob, token_rollout, adv, weight, R, eps_lo, eps_hi,
-                                      grad_scale, ent_coef, kl_coef, ref_logprob, stats_all, g, term, flag, logprob_out,
-                                      entropy_out, lse_out, dz, err_flag, row_counter, row_order, s);
-  return single_pass_launch_t<false>(z, T, V, ld, targets, old_logprob, token_rollout, adv, weight, R, eps_lo, eps_hi,
-                                     grad_scale, 0.f, 0.f, nullptr, stats_all, g, term, flag, logprob_out, entropy_out,
-                                     lse_out, dz, err_flag, row_counter, row_order, s);
+  const RowArgs r{logits, T, V, ld, targets, old_logprob, token_rollout, adv, weight, R, eps_lo, eps_hi, grad_scale,
+                  ent_coef, kl_coef, ref_logprob, stats_all, g, term, flag, logprob_out, entropy_out, lse_out, dlogits,
+                  err_flag};
+  switch (dtype) {
+    case AERO_BF16: return single_pass_launch_dt<kBF16>(r, row_counter, row_order, s);
+    case AERO_F16: return single_pass_launch_dt<kF16>(r, row_counter, row_order, s);
+    case AERO_F8E4M3: return single_pass_launch_dt<kF8>(r, row_counter, row_order, s);
+    default: return single_pass_launch_dt<kF32>(r, row_counter, row_order, s);
+  }
 }
 
 }  // namespace aero

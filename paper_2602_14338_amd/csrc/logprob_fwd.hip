@@ -76,11 +76,10 @@ __global__ __launch_bounds__(NT) void k_logprob_fwd(
   RowStat st = row_partial<NT, DT, VEC, 4>(row, V);
   st = stat_block_reduce<NT>(st, lds);
   if (threadIdx.x == 0) {
-    const float lse = st.m + logf(st.s);
-    const float zy = load_elt<DT>(row, y);
-    logprob[t] = zy - lse;
-    lse_out[t] = lse;
-    if (entropy) entropy[t] = lse - st.sz / st.s;
+    const RowLogProb own = row_logprob(st, load_elt<DT>(row, y));
+    logprob[t] = own.lp;
+    lse_out[t] = own.lse;
+    if (entropy) entropy[t] = own.lse - st.sz / st.s;
   }
 }
 

@@ -468,6 +468,55 @@ def test_f8_gradient_rounding_bit_exact(gh):
         assert not (got[:, 2:] & 0x7F).any()              # -x * 0: a zero of either sign
 
 
+# One pass over the logits: a row of n 16-byte vectors goes to workgroups of 64 / 256 / 512 / 1024 threads up to
+# n = 512 / 2048 / 4096 / 8192, to the streaming kernel up to 20480 and takes two passes beyond; an odd pitch puts every
+# row at another offset from 16 bytes.
+@pytest.mark.parametrize("dtype,V,ld,slots", [
+    ("bf16", 4096, 4096, 9), ("bf16", 4104, 4107, 9), ("bf16", 16391, 16391, 6), ("bf16", 32775, 32777, 5),
+    ("bf16", 65543, 65543, 4), ("bf16", 163847, 163849, 3), ("bf16", 3, 5, 40), ("bf16", 9, 9, 40),
+    ("f16", 16393, 16395, 6), ("f16", 151937, 151939, 3),
+    ("f32", 2048, 2049, 9), ("f32", 8197, 8197, 6), ("f32", 81920, 81922, 3), ("f32", 81927, 81927, 3), ("f32", 2, 3, 40),
+    ("f8e4m3", 8207, 8209, 6), ("f8e4m3", 131103, 131107, 3), ("f8e4m3", 17, 19, 40)])
+def test_single_pass_edges(gh, dtype, V, ld, slots):
+    def wl():
+        return ai.make_config("cfg2", V=V, ld=ld, slots=slots, len_lo=1, len_hi=slots - 1, dtype=dtype)
+    gs = {"f16": 4096.0, "f8e4m3": 256.0}.get(dtype, 1.0)
+    check_loss_bwd(gh, wl(), dict(), sigma_old=0.3, use_oracle_lse=False, stats=True, grad_scale=gs, untouched="half")
+    check_loss_bwd(gh, wl(), dict(reject_enable=1, posterior_mode=1), sigma_old=0.3, use_oracle_lse=False, inplace=True,
+                   grad_scale=gs, entropy_coef=0.01, kl_coef=0.04)
+
+
+@pytest.mark.parametrize("off_z,off_d", [(1, 1), (3, 11), (5, 13), (2, 7)])
+@pytest.mark.parametrize("V", [777, 70003])
+def test_loss_bwd_at_element_offsets(gh, V, off_z, off_d):
+    """Logits and gradient that start off the 16-byte grid, alike (one pass) and differently (two passes): the same
+    results as from aligned buffers up to a rounding of the stored entry, nothing written around the rows."""
+    wl = ai.make_config("cfg2", V=V, slots=5, len_lo=1, len_hi=5)
+    host = wl.logits_rows(0, wl.T)
+    ga = orc.group_advantage(wl.rewards, wl.lengths, wl.group_offsets, wl.keep_priority, AdvParams())
+    old = np.full(wl.T, -12.0, np.float32)
+    n = wl.T * V
+
+    def run(oz, od):
+        z = torch.zeros(n + 16, dtype=torch.bfloat16, device=gh.DEV)
+        z[oz:oz + n] = gh.logits_to_dev(host, "bf16").reshape(-1)
+        dz = torch.full((n + 32,), 7.0, dtype=torch.bfloat16, device=gh.DEV)
+        ws = torch.empty(gh.aero.aero_workspace_bytes(gh.binding.OP_GRPO_LOSS_BWD, T=wl.T, V=V, R=wl.R), dtype=torch.uint8,
+                         device=gh.DEV)
+        loss = torch.zeros(1, device=gh.DEV)
+        gh.aero.aero_grpo_loss_bwd(z[oz:oz + n].view(wl.T, V), wl.T, V, V, gh.dev(wl.targets), None, gh.dev(old),
+                                gh.dev(wl.token_rollout), gh.dev(ga["adv"].astype(np.float32)),
+                                gh.dev(ga["weight"].astype(np.float32)), wl.R, 0.2, 0.2, 1.0, loss, None, None,
+                                dz[od:od + n].view(wl.T, V), ws)
+        assert (dz[:od] == 7.0).all() and (dz[od + n:] == 7.0).all()
+        return loss.item(), dz[od:od + n].double()
+    loss_a, dz_a = run(0, 0)
+    loss_b, dz_b = run(off_z, off_d)
+    assert abs(loss_a - loss_b) <= 1e-5 * abs(loss_a) + 1e-9
+    # the same sums in another order: 32-bit differences, which move a stored entry by one step of bf16 at most
+    assert ((dz_a - dz_b).abs() <= 2.0 ** -7 * dz_a.abs() + 1e-30).all()
+
+
 @pytest.mark.parametrize("seed", range(16))
 def test_random_shapes_all_storage_types(gh, seed):
     """Seeded random vocabulary sizes, row pitches (aligned and not), batch shapes, storage types and call
