@@ -260,6 +260,37 @@ template <int DT> __device__ __forceinline__ u32x4_t pack_vec(const float (&d)[S
   return o;
 }
 
+// A row as 16-byte aligned vectors: `head` elements in front of the first one, nvec vectors, and fewer than a
+// vector's worth behind.  Rows of a tensor whose pitch is not a multiple of 16 bytes differ in head, and
+// a kernel that reads logits and writes dlogits requires the two to agree in it (rows_alike).
+struct RowGeom {
+  int head, nvec;
+};
+template <int DT>
+__device__ __forceinline__ RowGeom row_geom(const void* base, int64_t t, int64_t ld, int V) {
+  constexpr int E = Storage<DT>::kPerVec;
+  const uint32_t first = uint32_t(reinterpret_cast<uintptr_t>(base) / Storage<DT>::kBytes) + uint32_t(t * ld);
+  const int head = min(int((E - first % E) % E), V);
+  return RowGeom{head, (V - head) / E};
+}
+// The element outside the vectors that this thread looks after, -1: none.  Threads 0 .. E-1 take the head,
+// E .. 2E-1 what is behind the last vector.
+template <int DT>
+__device__ __forceinline__ int ragged_elt(RowGeom r, int V, int tid) {
+  constexpr int E = Storage<DT>::kPerVec;
+  if (tid < E) return tid < r.head ? tid : -1;
+  const int j = r.head + r.nvec * E + tid - E;
+  return tid < 2 * E && j < V ? j : -1;
+}
+template <int DT> __device__ __forceinline__ char* row_ptr(const void* base, int64_t t, int64_t ld, int j = 0) {
+  return const_cast<char*>(reinterpret_cast<const char*>(base)) + (size_t(t) * size_t(ld) + size_t(j)) * Storage<DT>::kBytes;
+}
+// Host side of the same: element-aligned logits, and a gradient (nullable) at the same offset from 16 bytes.
+inline bool rows_alike(const void* logits, const void* dlogits, size_t elt) {
+  const uintptr_t z = reinterpret_cast<uintptr_t>(logits), d = reinterpret_cast<uintptr_t>(dlogits);
+  return z % elt == 0 && (!dlogits || z % 16 == d % 16);
+}
+
 inline hipStream_t as_stream(void* s) { return reinterpret_cast<hipStream_t>(s); }
 
 inline aero_status launch_status() {

@@ -198,7 +198,8 @@ __device__ __forceinline__ float grad_elt(float z, float a, float b, float c) {
   return (ENT ? fmaf(a, z, b) : b) * exp2_fast(fmaf(z, kLog2e, c));
 }
 
-// One 16-byte vector of logits -> one of gradient; k = index of the vector in its row.
+// One 16-byte vector of logits -> one of gradient; k = index of the vector in its row, y = sampled token counted
+// from the first vector (negative: in the row's head).
 template <int DT, bool ENT>
 __device__ __forceinline__ u32x4_t dlogits_vec(const u32x4_t& v, int k, int y, float g, float a, float b, float c) {
   constexpr int E = Storage<DT>::kPerVec;
@@ -206,9 +207,9 @@ __device__ __forceinline__ u32x4_t dlogits_vec(const u32x4_t& v, int k, int y, f
   unpack_vec<DT>(v, z);
 #pragma unroll
   for (int e = 0; e < E; ++e) d[e] = grad_elt<ENT>(z[e], a, b, c);
-  if (k == y / E) {
+  if (k == (y >> Storage<DT>::kLogPerVec)) {
 #pragma unroll
-    for (int e = 0; e < E; ++e) d[e] += (e == y % E) ? g : 0.f;
+    for (int e = 0; e < E; ++e) d[e] += (e == (y & (E - 1))) ? g : 0.f;
   }
   return pack_vec<DT>(d);
 }
@@ -223,22 +224,19 @@ __global__ __launch_bounds__(NT) void k_dlogits(
   const float g = g_arr[t];
   float a = 0.f;
   if constexpr (ENT) a = ea[t];
-  constexpr size_t kEltBytes = Storage<DT>::kBytes;
-  constexpr int E = Storage<DT>::kPerVec;
-  const size_t row_off = size_t(t) * size_t(ld) * kEltBytes;
-  const char* zrow = reinterpret_cast<const char*>(logits) + row_off;
-  char* drow = reinterpret_cast<char*>(dlogits) + row_off;
+  const char* zrow = row_ptr<DT>(logits, t, ld);
+  char* drow = row_ptr<DT>(dlogits, t, ld);
   const int tid = threadIdx.x;
+  const RowGeom geom = VEC ? row_geom<DT>(logits, t, ld, V) : RowGeom{0, 0};
+  const int nvec = geom.nvec, jr = VEC ? ragged_elt<DT>(geom, V, tid) : -1;
 
   if (g == 0.f && a == 0.f) {   // uniform over the workgroup: nothing to read
     if (__float_as_uint(g) >> 31) return;   // -0: the row is not to be written
     if constexpr (VEC) {
-      u32x4_t* dv = reinterpret_cast<u32x4_t*>(drow);
-      const int nvec = V / E;
+      u32x4_t* dv = reinterpret_cast<u32x4_t*>(drow + geom.head * Storage<DT>::kBytes);
       const u32x4_t zero = {0u, 0u, 0u, 0u};
       for (int i = tid; i < nvec; i += NT) __builtin_nontemporal_store(zero, dv + i);
-      const int j = nvec * E + tid;
-      if (j < V) store_elt<DT>(drow, j, 0.f);
+      if (jr >= 0) store_elt<DT>(drow, jr, 0.f);
     } else {
       for (int j = tid; j < V; j += NT) store_elt<DT>(drow, j, 0.f);
     }
@@ -254,9 +252,9 @@ __global__ __launch_bounds__(NT) void k_dlogits(
     return j == y ? d + g : d;
   };
   if constexpr (VEC) {
-    const u32x4_t* zv = reinterpret_cast<const u32x4_t*>(zrow);
-    u32x4_t* dv = reinterpret_cast<u32x4_t*>(drow);
-    const int nvec = V / E;
+    const u32x4_t* zv = reinterpret_cast<const u32x4_t*>(zrow + geom.head * Storage<DT>::kBytes);
+    u32x4_t* dv = reinterpret_cast<u32x4_t*>(drow + geom.head * Storage<DT>::kBytes);
+    const int yr = y - geom.head;
     constexpr int UNROLL = 4;
     int i = tid;
     for (; i + (UNROLL - 1) * NT < nvec; i += UNROLL * NT) {
@@ -265,73 +263,61 @@ __global__ __launch_bounds__(NT) void k_dlogits(
       for (int u = 0; u < UNROLL; ++u) v[u] = __builtin_nontemporal_load(zv + i + u * NT);
 #pragma unroll
       for (int u = 0; u < UNROLL; ++u)
-        __builtin_nontemporal_store(dlogits_vec<DT, ENT>(v[u], i + u * NT, y, g, a, b, c), dv + i + u * NT);
+        __builtin_nontemporal_store(dlogits_vec<DT, ENT>(v[u], i + u * NT, yr, g, a, b, c), dv + i + u * NT);
     }
     for (; i < nvec; i += NT) {
       u32x4_t v = __builtin_nontemporal_load(zv + i);
-      __builtin_nontemporal_store(dlogits_vec<DT, ENT>(v, i, y, g, a, b, c), dv + i);
+      __builtin_nontemporal_store(dlogits_vec<DT, ENT>(v, i, yr, g, a, b, c), dv + i);
     }
-    const int j = nvec * E + tid;
-    if (j < V) store_elt<DT>(drow, j, grad(load_elt<DT>(zrow, j), j));
+    if (jr >= 0) store_elt<DT>(drow, jr, grad(load_elt<DT>(zrow, jr), jr));
   } else {
     for (int j = tid; j < V; j += NT) store_elt<DT>(drow, j, grad(load_elt<DT>(zrow, j), j));
   }
 }
 
-// Long aligned rows: one 16-byte vector per thread, (row, segment) per workgroup.  Workgroups
+// Long rows: one 16-byte vector per thread, (row, segment) per workgroup.  Workgroups
 // are small and start in address order, so the whole GPU sweeps the tensor as one linear stream
 // of reads and one of writes (a workgroup that loops over its row reaches 5.2 TB/s, this form
 // 5.7; two or four vectors per thread were 8 % slower, 512 and 1024 threads 1-2 % slower).  The
 // vector load is issued as soon as g_t is known, ahead of the other per-row scalars: with
 // one load per thread every dependent scalar fetch in front of it costs throughput (7 % here).
 constexpr int kSegNT = 256;
-constexpr int kSegVPT = 1;
-constexpr int kSegVecs = kSegNT * kSegVPT;   // vectors per segment
 
 template <int DT, bool ENT>
 __global__ __launch_bounds__(kSegNT) void k_dlogits_seg(
     const void* logits, int V, int64_t ld, int segs, const int32_t* __restrict__ targets,
     const float* __restrict__ lse, const float* __restrict__ g_arr, const float* __restrict__ ea,
     const float* __restrict__ eb, void* dlogits) {
-  constexpr int E = Storage<DT>::kPerVec;
-  constexpr size_t kEltBytes = Storage<DT>::kBytes;
   const int64_t t = blockIdx.x / segs;
   const int seg = blockIdx.x % segs;
   const float g = g_arr[t];
   float a = 0.f;
   if constexpr (ENT) a = ea[t];
-  const size_t row_off = size_t(t) * size_t(ld) * kEltBytes;
-  const char* zrow = reinterpret_cast<const char*>(logits) + row_off;
-  char* drow = reinterpret_cast<char*>(dlogits) + row_off;
-  const int nvec = V / E;
-  const int k0 = seg * kSegVecs + threadIdx.x;
-  const int j = nvec * E + threadIdx.x;          // ragged tail, done by segment 0
-  const bool tail = seg == 0 && j < V;
+  const RowGeom geom = row_geom<DT>(logits, t, ld, V);
+  const char* zrow = row_ptr<DT>(logits, t, ld);
+  char* drow = row_ptr<DT>(dlogits, t, ld);
+  const u32x4_t* zv = reinterpret_cast<const u32x4_t*>(zrow + geom.head * Storage<DT>::kBytes);
+  u32x4_t* dv = reinterpret_cast<u32x4_t*>(drow + geom.head * Storage<DT>::kBytes);
+  const int k = seg * kSegNT + threadIdx.x;
+  const bool in = k < geom.nvec;
+  const int jr = seg == 0 ? ragged_elt<DT>(geom, V, threadIdx.x) : -1;   // the ragged ends: segment 0
   if (g == 0.f && a == 0.f) {   // uniform over the workgroup: nothing to read
     if (__float_as_uint(g) >> 31) return;   // -0: the row is not to be written
-#pragma unroll
-    for (int i = 0; i < kSegVPT; ++i)
-      if (k0 + i * kSegNT < nvec) reinterpret_cast<u32x4_t*>(drow)[k0 + i * kSegNT] = u32x4_t{0u, 0u, 0u, 0u};
-    if (tail) store_elt<DT>(drow, j, 0.f);
+    if (in) dv[k] = u32x4_t{0u, 0u, 0u, 0u};
+    if (jr >= 0) store_elt<DT>(drow, jr, 0.f);
     return;
   }
-  u32x4_t v[kSegVPT];
-#pragma unroll
-  for (int i = 0; i < kSegVPT; ++i)
-    if (k0 + i * kSegNT < nvec) v[i] = reinterpret_cast<const u32x4_t*>(zrow)[k0 + i * kSegNT];
+  u32x4_t v = {0u, 0u, 0u, 0u};
+  if (in) v = zv[k];
   const int y = targets[t];
   const float c = -lse[t] * kLog2e;
   float b = -g;
   if constexpr (ENT) b = eb[t];
-#pragma unroll
-  for (int i = 0; i < kSegVPT; ++i) {
-    const int k = k0 + i * kSegNT;
-    if (k < nvec) reinterpret_cast<u32x4_t*>(drow)[k] = dlogits_vec<DT, ENT>(v[i], k, y, g, a, b, c);
-  }
-  if (tail) {
-    float d = grad_elt<ENT>(load_elt<DT>(zrow, j), a, b, c);
-    if (j == y) d += g;
-    store_elt<DT>(drow, j, d);
+  if (in) dv[k] = dlogits_vec<DT, ENT>(v, k, y - geom.head, g, a, b, c);
+  if (jr >= 0) {
+    float d = grad_elt<ENT>(load_elt<DT>(zrow, jr), a, b, c);
+    if (jr == y) d += g;
+    store_elt<DT>(drow, jr, d);
   }
 }
 
@@ -342,7 +328,7 @@ static void dispatch_dlogits(const void* logits, int64_t T, int V, int64_t ld, c
   const int per_vec = VEC ? Storage<DT>::kPerVec : 1;
   const int64_t work = (V + per_vec - 1) / per_vec;
   if constexpr (VEC) {
-    const int64_t segs = (V / per_vec + kSegVecs - 1) / kSegVecs;
+    const int64_t segs = (V / per_vec + kSegNT - 1) / kSegNT;
     if (work > 16 * 256 && T * segs < (int64_t(1) << 31)) {
       hipLaunchKernelGGL((k_dlogits_seg<DT, ENT>), dim3(unsigned(T * segs)), dim3(kSegNT), 0, s, logits, V, ld,
                          int(segs), targets, lse, g, ea, eb, dlogits);
@@ -460,9 +446,7 @@ static aero_status loss_bwd_run(
                      ent ? ws.ea : nullptr, ent ? ws.eb : nullptr, lp_dst, err_flag);
   hipLaunchKernelGGL(k_loss_reduce, dim3(1), dim3(kReduceNT), 0, s, ws.loss_term, ws.flag, T, loss, clip_frac);
   if (dlogits) {
-    const size_t elt = storage_bytes(dtype);
-    const bool vec = reinterpret_cast<uintptr_t>(logits) % 16 == 0 && reinterpret_cast<uintptr_t>(dlogits) % 16 == 0 &&
-                     (size_t(ld) * elt) % 16 == 0;
+    const bool vec = rows_alike(logits, dlogits, storage_bytes(dtype));
     if (ent) dispatch_dlogits_dtype<true>(dtype, vec, logits, T, V, ld, targets, lse, ws.g, ws.ea, ws.eb, dlogits, s);
     else dispatch_dlogits_dtype<false>(dtype, vec, logits, T, V, ld, targets, lse, ws.g, nullptr, nullptr, dlogits, s);
   }

@@ -12,31 +12,6 @@ namespace aero {
 
 constexpr int kSpNT = 1024;
 
-// A row as 16-byte aligned vectors: `head` elements in front of the first one, nvec vectors, and fewer than a
-// vector's worth behind.  Rows of a tensor whose pitch is not a multiple of 16 bytes differ in head, and
-// logits and dlogits of a row have the same one (single_pass_applicable).
-struct RowGeom {
-  int head, nvec;
-};
-template <int DT>
-__device__ __forceinline__ RowGeom row_geom(const void* base, int64_t t, int64_t ld, int V) {
-  constexpr int E = Storage<DT>::kPerVec;
-  const uint32_t first = uint32_t(reinterpret_cast<uintptr_t>(base) / Storage<DT>::kBytes) + uint32_t(t * ld);
-  const int head = min(int((E - first % E) % E), V);
-  return RowGeom{head, (V - head) / E};
-}
-// The element outside the vectors that this thread looks after, -1: none.  Threads 0 .. E-1 take the head,
-// E .. 2E-1 what is behind the last vector.
-template <int DT>
-__device__ __forceinline__ int ragged_elt(RowGeom r, int V, int tid) {
-  constexpr int E = Storage<DT>::kPerVec;
-  if (tid < E) return tid < r.head ? tid : -1;
-  const int j = r.head + r.nvec * E + tid - E;
-  return tid < 2 * E && j < V ? j : -1;
-}
-template <int DT> __device__ __forceinline__ char* row_ptr(const void* base, int64_t t, int64_t ld, int j = 0) {
-  return const_cast<char*>(reinterpret_cast<const char*>(base)) + (size_t(t) * size_t(ld) + size_t(j)) * Storage<DT>::kBytes;
-}
 template <int DT>
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t row_vectors(const void* base, int64_t t, int64_t ld, RowGeom r) {
   return __builtin_amdgcn_make_buffer_rsrc(row_ptr<DT>(base, t, ld, r.head), 0, r.nvec * 16, 0x00020000);
@@ -503,9 +478,8 @@ __global__ void k_set_counter(int32_t* ctr, int32_t v) {
 // logits and dlogits alike in their position relative to 16 bytes.
 constexpr int kStreamVecs = 20;
 bool single_pass_applicable(int32_t dtype, int V, const void* logits, const void* dlogits) {
-  const uintptr_t z = reinterpret_cast<uintptr_t>(logits), d = reinterpret_cast<uintptr_t>(dlogits);
   const size_t elt = storage_bytes(dtype);
-  return size_t(V) * elt / 16 <= size_t(kStreamVecs) * kSpNT && z % elt == 0 && (!dlogits || z % 16 == d % 16);
+  return size_t(V) * elt / 16 <= size_t(kStreamVecs) * kSpNT && rows_alike(logits, dlogits, elt);
 }
 
 struct RowArgs {

@@ -15,16 +15,18 @@ __device__ __forceinline__ void vec_update(RowStat& st, const u32x4_t& v) {
   stat_update<Storage<DT>::kPerVec>(st, z);
 }
 
-// Streams one row and returns this thread's partial state.  VEC: row base and stride are
-// 16-byte aligned.  UNROLL independent 16-byte loads are issued before any is consumed.
+// Streams one row and returns this thread's partial state.  VEC: 16-byte loads between the row's ragged
+// ends, any element-aligned row.  UNROLL independent 16-byte loads are issued before any is consumed.
 template <int NT, int DT, bool VEC, int UNROLL>
-__device__ __forceinline__ RowStat row_partial(const void* row, int V) {
+__device__ __forceinline__ RowStat row_partial(const void* logits, int64_t t, int64_t ld, int V) {
   RowStat st = stat_identity();
   const int tid = threadIdx.x;
+  const char* row = row_ptr<DT>(logits, t, ld);
   if constexpr (VEC) {
-    constexpr int E = Storage<DT>::kPerVec;
-    const u32x4_t* rv = reinterpret_cast<const u32x4_t*>(row);
-    const int nvec = V / E;
+    const RowGeom geom = row_geom<DT>(logits, t, ld, V);
+    const u32x4_t* rv = reinterpret_cast<const u32x4_t*>(row + geom.head * Storage<DT>::kBytes);
+    const int nvec = geom.nvec, j = ragged_elt<DT>(geom, V, tid);
+    const float zr = j >= 0 ? load_elt<DT>(row, j) : 0.f;
     int i = tid;
     for (; i + (UNROLL - 1) * NT < nvec; i += UNROLL * NT) {
       u32x4_t v[UNROLL];
@@ -37,9 +39,8 @@ __device__ __forceinline__ RowStat row_partial(const void* row, int V) {
       u32x4_t v = __builtin_nontemporal_load(rv + i);
       vec_update<DT>(st, v);
     }
-    const int j = nvec * E + tid;   // ragged tail shorter than one vector
-    if (j < V) {
-      float z[1] = {load_elt<DT>(row, j)};
+    if (j >= 0) {
+      float z[1] = {zr};
       stat_update<1>(st, z);
     }
   } else {
@@ -71,12 +72,10 @@ __global__ __launch_bounds__(NT) void k_logprob_fwd(
     }
     return;
   }
-  constexpr size_t kEltBytes = Storage<DT>::kBytes;
-  const char* row = reinterpret_cast<const char*>(logits) + size_t(t) * size_t(ld) * kEltBytes;
-  RowStat st = row_partial<NT, DT, VEC, 4>(row, V);
+  RowStat st = row_partial<NT, DT, VEC, 4>(logits, t, ld, V);
   st = stat_block_reduce<NT>(st, lds);
   if (threadIdx.x == 0) {
-    const RowLogProb own = row_logprob(st, load_elt<DT>(row, y));
+    const RowLogProb own = row_logprob(st, load_elt<DT>(row_ptr<DT>(logits, t, ld), y));
     logprob[t] = own.lp;
     lse_out[t] = own.lse;
     if (entropy) entropy[t] = own.lse - st.sz / st.s;
@@ -108,8 +107,7 @@ aero_status logprob_fwd_launch(const void* logits, int32_t dtype, int64_t T, int
                                const int32_t* targets, const uint8_t* row_active, float* logprob,
                                float* entropy, float* lse, int32_t* err_flag, hipStream_t s) {
   if (T == 0) return AERO_OK;
-  const size_t elt = storage_bytes(dtype);
-  const bool vec = (reinterpret_cast<uintptr_t>(logits) % 16 == 0) && ((size_t(ld) * elt) % 16 == 0);
+  const bool vec = rows_alike(logits, nullptr, storage_bytes(dtype));
   if (dtype == AERO_BF16) {
     if (vec) dispatch_nt<kBF16, true>(logits, T, V, ld, targets, row_active, logprob, entropy, lse, err_flag, s);
     else dispatch_nt<kBF16, false>(logits, T, V, ld, targets, row_active, logprob, entropy, lse, err_flag, s);
