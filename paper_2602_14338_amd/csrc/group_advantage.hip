@@ -3,13 +3,17 @@
 //
 // Groups are ragged (CSR offsets).  One wave64 owns one group and walks it in strides of 64,
 // so any group size works; counts are integers, the few floating-point statistics are formed
-// in fp64 from those counts and rounded once to fp32.  Three launches on one stream:
-//   k_group     per group: c, category, keep mask, advantages, weights, kept count
-//   k_scan      one workgroup: exclusive scan of the kept counts -> kept_offsets
-//   k_compact   per group: kept rollout indices, ascending, written at kept_offsets[q]
-// or, for a micro-batch's handful of groups (at most two per wave of one workgroup), the same three
-// stages in one launch (k_group_small): the call is latency bound there, and two launches less are
-// half of its time.  With more groups the three-launch form wins again (64 groups: 13.5 us against 18.7).
+// in fp64 from those counts and rounded once to fp32.  The call is latency bound, so what counts is
+// launches and dependent loads:
+//   at most 32 groups (a micro-batch)   k_group_small: everything in one workgroup, one launch
+//   up to 65536 rollouts (a step)       k_group (c, category, keep mask, advantages, weights), then k_place:
+//                                       every workgroup counts the kept rollouts in front of its groups
+//                                       straight from the keep mask (a byte each), so no scan stands between
+//   more                                k_group, k_scan (exclusive scan of the kept counts, one
+//                                       workgroup) and k_compact: the mask would be read too often
+// 256 groups of 8 to 32 rollouts took 15.8 us with the third form and a rank search that loaded rewards and
+// keys one at a time; a group of at most 64 rollouts now stays in the lanes of its wave.  (One workgroup
+// for 64 groups serialises them: 18.7 us against 13.5.)
 #include "aero_device.h"
 
 namespace aero {
@@ -55,15 +59,26 @@ __device__ __forceinline__ int group_body(
   const int n = e - b;
   const bool curation = p.reject_enable || p.posterior_mode;
 
-  // 1. c = number of rollouts with reward exactly 1
-  int c_l = 0, bad_l = 0;
-  for (int i = b + lane; i < e; i += kWave) {
-    const float r = rewards[i];
-    c_l += r == 1.f;
-    bad_l += (r != 0.f && r != 1.f);
+  // 1. c = number of rollouts with reward exactly 1; what the lane's first rollout holds, loaded at once
+  const int i0 = b + lane;
+  const bool in0 = i0 < e;
+  const float r0 = in0 ? rewards[i0] : 0.f;
+  const uint32_t key0 = in0 && keys ? keys[i0] : 0u;
+  const int len0 = in0 ? lengths[i0] : 0;
+  const uint64_t ones = __ballot(in0 && r0 == 1.f);   // of the group's first 64 rollouts
+  int c = __popcll(ones);
+  bool bad = __ballot(in0 && r0 != 0.f && r0 != 1.f) != 0;
+  if (n > kWave) {
+    int c_l = 0, bad_l = 0;
+    for (int i = i0 + kWave; i < e; i += kWave) {
+      const float r = rewards[i];
+      c_l += r == 1.f;
+      bad_l += (r != 0.f && r != 1.f);
+    }
+    c += wave_sum_i(c_l);
+    bad |= wave_sum_i(bad_l) != 0;
   }
-  const int c = wave_sum_i(c_l);
-  if (curation && wave_sum_i(bad_l) && lane == 0 && err_flag) atomicOr(err_flag, AERO_DERR_NONBINARY_REWARD);
+  if (curation && bad && lane == 0 && err_flag) atomicOr(err_flag, AERO_DERR_NONBINARY_REWARD);
 
   // 2. category by u = c/n against tau, integer compares
   int cat;
@@ -84,15 +99,27 @@ __device__ __forceinline__ int group_body(
       m = min(p.zero_keep, n);
     }
   }
+  bool keep0 = false;
   int nk_l = 0;                    // kept
   double sum_l = 0.0;              // sum of kept rewards
+  // a group that fits the wave: ranks from the lanes' registers, one candidate of the group at a time
+  int ahead0 = 0;
+  if (n <= kWave && mode >= 2) {
+    uint64_t cand = __ballot(in0) & (mode == 3 ? ~uint64_t(0) : ~ones);
+    while (cand) {   // uniform
+      const int j = __ffsll((unsigned long long)cand) - 1;
+      cand &= cand - 1;
+      ahead0 += before(uint32_t(__builtin_amdgcn_readlane(int(key0), j)), j, key0, lane);
+    }
+  }
   float mx_l = -INFINITY, mn_l = INFINITY;
   for (int i = b + lane; i < e; i += kWave) {
-    const float r = rewards[i];
+    const float r = i == i0 ? r0 : rewards[i];
     bool k;
     if (mode == 0) k = true;
     else if (mode == 1) k = false;
     else if (mode == 2 && r == 1.f) k = true;
+    else if (n <= kWave) k = ahead0 < m;
     else {
       // rank among the candidates (incorrect rollouts in mode 2, everyone in mode 3)
       const uint32_t ki = keys ? keys[i] : 0u;
@@ -104,6 +131,7 @@ __device__ __forceinline__ int group_body(
       k = ahead < m;
     }
     keep_mask[i] = k ? 1 : 0;
+    if (i == i0) keep0 = k;
     if (k) {
       ++nk_l;
       sum_l += double(r);
@@ -121,8 +149,8 @@ __device__ __forceinline__ int group_body(
     mu = wave_sum_d(sum_l) / double(nk);
     double ss_l = 0.0;
     for (int i = b + lane; i < e; i += kWave)
-      if (keep_mask[i]) {   // written by this same lane above
-        const double d = double(rewards[i]) - mu;
+      if (i == i0 ? keep0 : keep_mask[i] != 0) {   // written by this same lane above
+        const double d = double(i == i0 ? r0 : rewards[i]) - mu;
         ss_l += d * d;
       }
     inv_sigma = 1.0 / sqrt(wave_sum_d(ss_l) / double(nk));
@@ -135,11 +163,11 @@ __device__ __forceinline__ int group_body(
 
   // 6. weights 1 / (Q n' L_i)
   for (int i = b + lane; i < e; i += kWave) {
-    const bool k = keep_mask[i] != 0;
+    const bool k = i == i0 ? keep0 : keep_mask[i] != 0;
     float a = 0.f, w = 0.f;
     if (k) {
-      if (signal) a = float((double(rewards[i]) - mu) * inv_sigma);
-      const int L = lengths[i];
+      if (signal) a = float((double(i == i0 ? r0 : rewards[i]) - mu) * inv_sigma);
+      const int L = i == i0 ? len0 : lengths[i];
       if (L > 0) w = float(1.0 / (double(Q) * double(nk) * double(L)));
     }
     adv[i] = a;
@@ -215,9 +243,53 @@ __global__ __launch_bounds__(kGroupsPerBlock* kWave) void k_compact(
   compact_body(q, lane, group_offsets, keep_mask, kept_offsets[q], R, kept_index);
 }
 
+// kept_offsets and kept_index from the keep mask alone: a workgroup counts the kept rollouts in front of its four
+// groups, each wave those of its own group.
+__global__ __launch_bounds__(kGroupsPerBlock* kWave) void k_place(
+    const int32_t* __restrict__ group_offsets, const uint8_t* __restrict__ keep_mask, int Q, int R,
+    int32_t* __restrict__ kept_offsets, int32_t* __restrict__ kept_index) {
+  __shared__ int front[kGroupsPerBlock], own[kGroupsPerBlock];
+  const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
+  const int q0 = blockIdx.x * kGroupsPerBlock, q = q0 + wave;
+  const int end = max(0, min(group_offsets[q0], R));   // bytes of the mask in front of the first group
+  int n = 0;
+  if (reinterpret_cast<uintptr_t>(keep_mask) % 4 == 0) {   // a byte is 0 or 1: set bits of whole words
+    const uint32_t* words = reinterpret_cast<const uint32_t*>(keep_mask);
+    for (int i = tid; i < end / 4; i += kGroupsPerBlock * kWave) n += __popc(words[i]);
+    const int i = end / 4 * 4 + tid;
+    if (i < end) n += keep_mask[i];
+  } else {
+    for (int i = tid; i < end; i += kGroupsPerBlock * kWave) n += keep_mask[i];
+  }
+  n = wave_sum_i(n);
+  int mine = 0;
+  if (q < Q) {
+    int b = group_offsets[q], e = group_offsets[q + 1];
+    b = max(0, min(b, R));
+    e = max(b, min(e, R));
+    for (int i = b + lane; i < e; i += kWave) mine += keep_mask[i];
+    mine = wave_sum_i(mine);
+  }
+  if (lane == 0) {
+    front[wave] = n;
+    own[wave] = mine;
+  }
+  __syncthreads();
+  int out = 0;
+#pragma unroll
+  for (int w = 0; w < kGroupsPerBlock; ++w) out += front[w] + (w < wave ? own[w] : 0);
+  if (q >= Q) return;
+  if (lane == 0) {
+    if (q == 0) kept_offsets[0] = 0;
+    kept_offsets[q + 1] = out + mine;
+  }
+  compact_body(q, lane, group_offsets, keep_mask, out, R, kept_index);
+}
+
 // The three stages in one workgroup of 16 waves, for Q <= kSmallQ groups: wave w takes groups w and w + 16;
 // the kept counts and their scan stay in LDS; every wave then places the kept indices of the groups it
 // processed (it reads back the keep mask its own lanes wrote).
+constexpr int kPlaceR = 1 << 16;
 constexpr int kSmallQ = 32, kSmallR = 1 << 16, kSmallNT = 1024;
 __global__ __launch_bounds__(kSmallNT) void k_group_small(
     const float* __restrict__ rewards, const int32_t* __restrict__ lengths,
@@ -284,6 +356,11 @@ extern "C" aero_status aero_group_advantage(
     hipLaunchKernelGGL(k_group, dim3(blocks), dim3(kGroupsPerBlock * kWave), 0, s, rewards, lengths, group_offsets,
                        keep_priority, Q, R, *p, adv, weight, keep_mask, kept_offsets, group_zero_var,
                        group_category, err_flag);
+  if (Q > 0 && R <= kPlaceR) {
+    hipLaunchKernelGGL(k_place, dim3(blocks), dim3(kGroupsPerBlock * kWave), 0, s, group_offsets, keep_mask, Q, R,
+                       kept_offsets, kept_index);
+    return launch_status();
+  }
   hipLaunchKernelGGL(k_scan, dim3(1), dim3(kScanNT), 0, s, kept_offsets, Q);
   if (Q > 0)
     hipLaunchKernelGGL(k_compact, dim3(blocks), dim3(kGroupsPerBlock * kWave), 0, s, group_offsets, keep_mask,
