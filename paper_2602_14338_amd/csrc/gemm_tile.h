@@ -28,7 +28,7 @@ constexpr int kTile = 256;          // tile edge in both output dimensions
 constexpr int kGemmNT = 512;        // threads per workgroup (8 waves)
 constexpr int kMB = 8, kNB = 4;     // 16 x 16 blocks per wave: 128 rows x 64 columns
 constexpr size_t kGemmStageBytes = 131072;  // two stages of (256 + 256) x 64 bf16
-constexpr size_t kWarmSinkOff = 135168;     // past the stages (128 KB) and the largest epilogue staging area (256 x 256 bf16)
+constexpr size_t kWarmSinkOff = kGemmStageBytes;   // past the stages
 constexpr size_t kGemmLdsBytes = kWarmSinkOff + 2048;   // + a 256-byte sink per wave for the warm-up loads
 
 // Position of an accumulator element inside the 256 x 256 tile.
@@ -246,6 +246,14 @@ __device__ __forceinline__ DmaOperand operand_row_major(const uint16_t* base, in
 __device__ __forceinline__ DmaOperand operand_slabs(const uint16_t* base, int64_t rows, int K) {
   return DmaOperand{base, kDK, rows * kDK, int64_t(K / kDK) * rows * kDK * 2};
 }
+// K-slabs in fragment order (AF): inside a slab every 16 rows are one 2 KB block, the two 32-wide K steps one after
+// the other, each as the 16 x 16 x 32 instruction's lanes hold it: element (row, k) at
+//   (row / 16) * 1024 + (k % 64 / 32) * 512 + (k % 32 / 8) * 128 + (row % 16) * 8 + k % 8
+// A wave's accumulators can be stored in it straight from registers, 1 KB per instruction, and a fragment is 1 KB of
+// LDS read lane by lane.
+__device__ __forceinline__ int64_t frag_order_offset(int64_t rows, int64_t row, int64_t k) {
+  return (k / 64) * rows * 64 + (row / 16) * 1024 + (k % 64 / 32) * 512 + (k % 32 / 8) * 128 + (row % 16) * 8 + k % 8;
+}
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t operand_rsrc(const DmaOperand& o) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(o.base), 0, int(o.bytes), 0x00020000);
 }
@@ -263,6 +271,12 @@ __device__ __forceinline__ DmaLane dma_lane(int row0, const DmaOperand& o, int w
   const uint32_t row = uint32_t((int64_t(row0 + wave * 32 + (lane >> 3)) * o.ld) * 2);
   const uint32_t c0 = uint32_t((lane & 7) ^ ((lane >> 4) & 7)), c1 = uint32_t((lane & 7) ^ ((4 + (lane >> 4)) & 7));
   return DmaLane{row + c0 * 16, row + c1 * 16, uint32_t(8 * o.ld * 2), uint32_t(o.kstep * 2)};
+}
+
+// The same for an operand in fragment order: a wave's 32 rows are 4 KB in one piece.
+__device__ __forceinline__ DmaLane dma_lane_af(int row0, const DmaOperand& o, int wave, int lane) {
+  const uint32_t at = uint32_t((row0 + wave * 32) * kDK * 2 + lane * 16);
+  return DmaLane{at, at, 1024u, uint32_t(o.kstep * 2)};
 }
 
 // The whole byte offset travels in the vector offset: the hardware bounds check covers the
@@ -312,8 +326,9 @@ __device__ __forceinline__ void frags_load_bt(Frags& f, const uint16_t* lds, int
 
 // WARM: L2 warm-up two slices ahead (see below); a few per cent on the contractions whose
 // operands come from large read-only arrays, a loss on the split-K dhidden contraction.
-// BT: operand B is [K][rows] (B.base, B.ld, B.bytes; B.kstep is not looked at).
-template <bool WARM, bool SWAP, bool BT = false>
+// BT: operand B is [K][rows] (B.base, B.ld, B.bytes; B.kstep is not looked at).  AF: operand A is in K-slabs in
+// fragment order (m0 a multiple of 16).
+template <bool WARM, bool SWAP, bool BT = false, bool AF = false>
 __device__ __forceinline__ void gemm_tile_dma(const DmaOperand& A, const DmaOperand& B, int K, int m0, int n0,
                                               uint16_t* smem, Acc& acc) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -323,10 +338,20 @@ __device__ __forceinline__ void gemm_tile_dma(const DmaOperand& A, const DmaOper
   if (nk == 0) return;
   const __amdgpu_buffer_rsrc_t ra = operand_rsrc(A), rb = operand_rsrc(B);
   static_assert(!(WARM && BT), "the warm-up assumes K-contiguous operands");
-  const DmaLane la = dma_lane(m0, A, wave, lane), lb = BT ? dma_lane_bt(n0, B.ld, wave, lane) : dma_lane(n0, B, wave, lane);
+  const DmaLane la = AF ? dma_lane_af(m0, A, wave, lane) : dma_lane(m0, A, wave, lane);
+  const DmaLane lb = BT ? dma_lane_bt(n0, B.ld, wave, lane) : dma_lane(n0, B, wave, lane);
   auto load_b = [&](Frags& f, const uint16_t* Bs, int ks) {
     if constexpr (BT) frags_load_bt(f, Bs, wn * 64, ks, lane);
     else frags_load(f, Bs, wn * 64, ks, lane);
+  };
+  auto load_a = [&](Frags& f, const uint16_t* As, int half, int ks) {
+    if constexpr (AF) {
+#pragma unroll
+      for (int i = 0; i < kFragBlocks; ++i)
+        f[i] = *reinterpret_cast<const bf16x8_t*>(As + (wm * 8 + half * kFragBlocks + i) * 1024 + ks * 512 + lane * 8);
+    } else {
+      frags_load(f, As, wm * 128 + half * 64, ks, lane);
+    }
   };
   dma_issue(ra, rb, la, lb, 0, smem, wave);
   // L2 warm-up.  A fifth of a slice's lines miss L2 (the 32 workgroups resident on an XCD form an
@@ -361,15 +386,15 @@ __device__ __forceinline__ void gemm_tile_dma(const DmaOperand& A, const DmaOper
     const uint16_t* As = smem + (kt & 1) * kDStageElems;
     const uint16_t* Bs = As + kTile * kDK;
     Frags b0, b1, a0, a1, a2;
-    frags_load(a0, As, wm * 128, 0, lane);
+    load_a(a0, As, 0, 0);
     load_b(b0, Bs, 0);
-    frags_load(a1, As, wm * 128 + 64, 0, lane);
+    load_a(a1, As, 1, 0);
     frags_mma<SWAP>(a0, b0, 0, acc);
     if (prefetch) dma_issue(ra, rb, la, lb, kt + 1, smem + ((kt + 1) & 1) * kDStageElems, wave);
-    frags_load(a2, As, wm * 128, 1, lane);
+    load_a(a2, As, 0, 1);
     load_b(b1, Bs, 1);
     frags_mma<SWAP>(a1, b0, 1, acc);
-    frags_load(a0, As, wm * 128 + 64, 1, lane);
+    load_a(a0, As, 1, 1);
     frags_mma<SWAP>(a2, b1, 0, acc);
     constexpr int kMfma = 0x008, kVmemRd = 0x020, kDsRd = 0x100;
     constexpr int kMfmas = kFragBlocks * kNB;

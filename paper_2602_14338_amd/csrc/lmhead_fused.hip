@@ -9,8 +9,8 @@
 //           k_fused_stats    tile of z^T (vocab rows x token columns): every lane owns one token column
 //                            per block, so the running (offset, sum exp, sum exp*z) is a per-lane
 //                            register recurrence with no shuffles.  On the candidates' token tiles it
-//                            also leaves P = exp(z - zy) in bf16 in the K-slab layouts
-//                            [vocab/64][token][64] and [vocab chunk][token/64][vocab in chunk][64] that
+//                            also leaves P = exp(z - zy) in bf16 in K-slabs [vocab/64][token][64] and
+//                            [vocab chunk][token/64][vocab in chunk][64], both in fragment order, that
 //                            the two gradient contractions read (2 x T x V x 2 bytes are held)
 //           k_fused_combine  merges the per-tile partials of a token -> logprob, entropy, lse
 // Backward  token terms + loss reduce (shared with the logits path), then
@@ -272,86 +272,65 @@ template <int CTRL> __device__ __forceinline__ uint32_t quad_perm(uint32_t v) {
   return uint32_t(__builtin_amdgcn_update_dpp(0, int(v), CTRL, 0xf, 0xf, true));
 }
 constexpr int kQuadXor1 = 0xB1, kQuadXor2 = 0x4E;   // quad_perm [1,0,3,2] and [2,3,0,1]
+// The value of the lane four apart (lane ^ 4): a shift down for the lower four of eight, a shift up for the others.
+__device__ __forceinline__ uint32_t xor4_lane(uint32_t v) {
+  const int low = __builtin_amdgcn_update_dpp(0, int(v), 0x104, 0xf, 0x5, false);       // row_shl:4
+  return uint32_t(__builtin_amdgcn_update_dpp(low, int(v), 0x114, 0xf, 0xa, false));    // row_shr:4
+}
 
 // A 256 x 256 bf16 tile (vocabulary rows m0.., token columns n0..) held as packed pairs in the accumulator
 // layout, pk[nb][mb] = the four rows acc_row(wm, mb, 0 .. 3) of column acc_col(wn, nb), leaves in the two
-// K-slab layouts the gradient contractions read: [v / 64][token][64] and [v / VC][token / 64][v % VC][64].
-// smem: 128 KB, free on entry (every wave past its last read of it).
-__device__ __forceinline__ void store_tile_both_layouts(const uint32_t (&pk)[kNB][kMB][2], uint16_t* smem, int m0,
-                                                        int n0, int64_t T_pad, int VC, uint16_t* __restrict__ dz,
-                                                        uint16_t* __restrict__ dzT) {
+// layouts the gradient contractions read, both K-slabs in fragment order (frag_order_offset): tokens x vocabulary, and
+// vocabulary chunk by chunk x tokens.  Lanes exchange until each holds eight consecutive K values, and every
+// instruction stores one 1 KB block, so nothing is staged in LDS and no wave waits for another.  (Staged through LDS in
+// both orientations, with four barriers: k_fused_stats 6.98 ms with 16384 tokens at H = 1536, 6.81 this way; whole
+// calls 15.24 / 15.06 ms, with 600 tokens 1045 / 1020 us.)
+__device__ __forceinline__ void store_tile_both_layouts(const uint32_t (&pk)[kNB][kMB][2], int m0, int n0, int64_t T_pad,
+                                                        int VC, uint16_t* __restrict__ dz, uint16_t* __restrict__ dzT) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wm = wave >> 2, wn = wave & 3;
-  // The tile leaves through LDS so that both layouts are written with 16-byte coalesced stores.
-  // Both LDS images are 256 rows of 512 bytes without padding; a row starts at bank 0, so the
-  // positions inside a row are XOR-swizzled with bits of the row index, chosen so that the lanes
-  // of every LDS instruction below fall on distinct banks (64 banks of 4 bytes):
-  //   image 1, L1[token][vocab]: the 16-byte chunk c = vocab / 8 sits at chunk position
-  //     c ^ g(token) (low four bits), g = ((token & 1) << 3) | ((token >> 1) & 7).  Writes:
-  //     32 lanes = 16 consecutive tokens x the two 8-byte halves of one chunk -> 16 distinct chunks.
-  //     Reads: 16 lanes = 2 tokens x 8 chunks -> the two tokens use different halves of the banks.
-  //   image 2, L2[vocab][token]: the 32-byte segment index (16 tokens) is XORed with
-  //     f(vocab) = ((vocab & 1) << 2) | ((vocab >> 1) & 3).  Writes: 32 lanes = 8 consecutive
-  //     vocabulary rows x the four 8-byte parts of one segment -> 8 distinct segments.  Reads:
-  //     16 lanes = 2 rows x 8 chunks, the rows in different halves of the banks.
-  auto l1_chunk = [](int tok, int c) -> int {
-    const int g = ((tok & 1) << 3) | ((tok >> 1) & 7);
-    return (c & ~15) | ((c ^ g) & 15);
-  };
-  // ---- [token][vocab] ----
+  const int group = lane >> 4;
+  // ---- tokens x vocabulary: the odd 16-lane rows of one block change places with the even ones of the next; lane
+  // group 0 then holds vocabulary 0..7 of its token, group 2 8..15, group 1 16..23, group 3 24..31 ----
+  const int v0 = m0 + wm * 128, t0 = n0 + wn * 64;   // multiples of 64: the wave's slab and token positions
+  uint16_t* const dst = dz + frag_order_offset(T_pad, t0 + (lane & 15), v0 + (group & 1) * 16 + (group >> 1) * 8);
 #pragma unroll
-  for (int nb = 0; nb < kNB; ++nb) {
-    const int tcol = acc_col(wn, nb, lane);
+  for (int nb = 0; nb < kNB; ++nb)
 #pragma unroll
-    for (int mb = 0; mb < kMB; ++mb) {
-      const int row0 = acc_row(wm, mb, 0, lane);   // a multiple of 4
-      uint2 two = {pk[nb][mb][0], pk[nb][mb][1]};
-      *reinterpret_cast<uint2*>(smem + tcol * kTile + l1_chunk(tcol, row0 >> 3) * 8 + (row0 & 4)) = two;
+    for (int mb = 0; mb < kMB; mb += 2) {
+      const auto lo = __builtin_amdgcn_permlane16_swap(pk[nb][mb][0], pk[nb][mb + 1][0], false, false);
+      const auto hi = __builtin_amdgcn_permlane16_swap(pk[nb][mb][1], pk[nb][mb + 1][1], false, false);
+      __builtin_nontemporal_store(u32x4_t{lo[0], hi[0], lo[1], hi[1]},
+                                  reinterpret_cast<u32x4_t*>(dst + int64_t(mb / 4) * T_pad * 64 + (mb / 2 % 2) * 512 + nb * 1024));
     }
-  }
-  __syncthreads();
-  // four 64-wide slabs per tile; consecutive threads walk one slab row by row (8 x 16 bytes per
-  // row), so each slab receives one contiguous 32 KB block
-#pragma unroll
-  for (int k = 0; k < kTile * (kTile / 8) / kGemmNT; ++k) {
-    const int u = threadIdx.x + k * kGemmNT;
-    const int sl = u >> 11, r = (u >> 3) & 255, c8 = u & 7;
-    const u32x4_t val = *reinterpret_cast<const u32x4_t*>(smem + r * kTile + l1_chunk(r, sl * 8 + c8) * 8);
-    __builtin_nontemporal_store(val, reinterpret_cast<u32x4_t*>(dz + (int64_t(m0 / 64 + sl) * T_pad + n0 + r) * 64 + c8 * 8));
-  }
-  __syncthreads();
-  // ---- [vocab][token]: the four lanes of a quad hold rows r .. r + 3 of tokens t .. t + 3 and transpose
-  // that 4 x 4 block in two exchanges, so that lane q writes row r + q of all four tokens ----
-  auto l2_off = [](int voc, int tok) -> int { return tok ^ ((((voc & 1) << 2) | ((voc >> 1) & 3)) << 4); };
-  const bool odd = lane & 1, upper = lane & 2;
-#pragma unroll
-  for (int nb = 0; nb < kNB; ++nb) {
-    const int tok0 = acc_col(wn, nb, lane) & ~3;
-#pragma unroll
-    for (int mb = 0; mb < kMB; ++mb) {
-      uint32_t pair[2];   // rows r + (lane & 1) and r + 2 + (lane & 1), tokens of this lane pair
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const uint32_t own = pk[nb][mb][h], got = quad_perm<kQuadXor1>(own);
-        pair[h] = odd ? ((got >> 16) | (own & 0xffff0000u)) : ((own & 0xffffu) | (got << 16));
-      }
-      const uint32_t got = quad_perm<kQuadXor2>(upper ? pair[0] : pair[1]);
-      const uint2 four = upper ? uint2{got, pair[1]} : uint2{pair[0], got};
-      const int row = acc_row(wm, mb, lane & 3, lane);
-      *reinterpret_cast<uint2*>(smem + row * kTile + l2_off(row, tok0)) = four;
-    }
-  }
-  __syncthreads();
+  // ---- vocabulary x tokens: the four lanes of a quad hold rows r .. r + 3 of tokens t .. t + 3 and transpose that
+  // 4 x 4 block in two exchanges, so that lane q holds row r + q of all four tokens; lanes four apart then swap
+  // halves between two neighbouring token blocks, which leaves eight tokens of a row in each ----
+  const bool odd = lane & 1, upper = lane & 2, far = lane & 4;
   // a tile lies inside one chunk (VC is a multiple of the tile height)
-  uint16_t* const dzT_chunk = dzT + int64_t(m0 / VC) * VC * T_pad;
-  const int m_in_chunk = m0 % VC;
+  uint16_t* const dstT = dzT + int64_t(m0 / VC) * VC * T_pad +
+                         frag_order_offset(VC, m0 % VC + wm * 128 + group * 4 + (lane & 3), t0 + (far ? 16 : 0) + (lane & 8));
 #pragma unroll
-  for (int k = 0; k < kTile * (kTile / 8) / kGemmNT; ++k) {
-    const int u = threadIdx.x + k * kGemmNT;
-    const int sl = u >> 11, r = (u >> 3) & 255, c8 = u & 7;
-    const u32x4_t val = *reinterpret_cast<const u32x4_t*>(smem + r * kTile + l2_off(r, sl * 64 + c8 * 8));
-    __builtin_nontemporal_store(val, reinterpret_cast<u32x4_t*>(dzT_chunk + (int64_t(n0 / 64 + sl) * VC + m_in_chunk + r) * 64 + c8 * 8));
-  }
+  for (int nb = 0; nb < kNB; nb += 2)
+#pragma unroll
+    for (int mb = 0; mb < kMB; ++mb) {
+      uint32_t four[2][2];   // of blocks nb, nb + 1: this lane's row, four tokens
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        uint32_t pair[2];    // rows r + (lane & 1) and r + 2 + (lane & 1), tokens of this lane pair
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const uint32_t own = pk[nb + k][mb][h], got = quad_perm<kQuadXor1>(own);
+          pair[h] = odd ? ((got >> 16) | (own & 0xffff0000u)) : ((own & 0xffffu) | (got << 16));
+        }
+        const uint32_t got = quad_perm<kQuadXor2>(upper ? pair[0] : pair[1]);
+        four[k][0] = upper ? got : pair[0];
+        four[k][1] = upper ? pair[1] : got;
+      }
+      const uint32_t got0 = xor4_lane(far ? four[0][0] : four[1][0]), got1 = xor4_lane(far ? four[0][1] : four[1][1]);
+      const u32x4_t eight = far ? u32x4_t{got0, got1, four[1][0], four[1][1]} : u32x4_t{four[0][0], four[0][1], got0, got1};
+      __builtin_nontemporal_store(eight, reinterpret_cast<u32x4_t*>(dstT + mb * 1024 + (nb / 2) * 512));
+    }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -500,8 +479,7 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_fused_stats(
   if constexpr (STORE) {
     if (store) {
       if (__any(wide) && lane == 0) atomicOr(nact + 2, 1);
-      __syncthreads();   // the exchange area is read: LDS is free for the staging of the tile
-      store_tile_both_layouts(pk, smem, m0, n0, T_pad, VC, dz, dzT);
+      store_tile_both_layouts(pk, m0, n0, T_pad, VC, dz, dzT);
     }
   }
 }
@@ -632,8 +610,8 @@ __global__ __launch_bounds__(256) void k_candidate_scalars(
   const float lp = logprob[t];
   scale[j] = -gv * expf(lp);
   const uint16_t own = f32_to_bf16(-expm1f(-lp));
-  dz[(int64_t(y / 64) * T_pad + j) * 64 + y % 64] = own;
-  dzT[int64_t(y / VC) * VC * T_pad + (int64_t(j / 64) * VC + y % VC) * 64 + j % 64] = own;
+  dz[frag_order_offset(T_pad, j, y)] = own;
+  dzT[int64_t(y / VC) * VC * T_pad + frag_order_offset(VC, y % VC, j)] = own;
 }
 
 // Transposes (and optionally gathers) a row-major bf16 matrix into the K-slab layout the GEMM
@@ -732,7 +710,7 @@ __global__ __launch_bounds__(256) void k_gather_transpose_vec(
 // z^T tile rows = vocab [m0, m0 + 256), columns = compacted tokens.  The bf16 gradient leaves in
 // the two K-slab layouts the next two contractions read: dz as [v / 64][token][64] (K = vocab)
 // and dzT as [v / VC][token / 64][v % VC][64] (K = tokens, in vocabulary chunks of VC rows so that
-// one chunk stays below the 4 GiB a buffer descriptor can address); entries outside the
+// one chunk, whose slabs are in fragment order like those of dz, stays below the 4 GiB a buffer descriptor can address); entries outside the
 // vocabulary or the candidate tokens are zero.
 // ENT: rows also carry the entropy-bonus term, dz = pi (ac z + bc) + gc onehot; otherwise ac = 0
 // and the scale is the per-token constant bc = -g.
@@ -789,7 +767,7 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_fused_dz(
       pk[nb][mb][1] = pack_bf16x2(d[2], d[3]);
     }
   }
-  store_tile_both_layouts(pk, smem, m0, n0, T_pad, VC, dz, dzT);
+  store_tile_both_layouts(pk, m0, n0, T_pad, VC, dz, dzT);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -826,9 +804,9 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_gemm_dh(
   if constexpr (DIRECT) {
     // weight rows past the vocabulary (the split may start there) lie past the operand's bytes and read as zeros
     const DmaOperand w{W + int64_t(min(k_begin, V)) * H, H, 0, int64_t(max(V - k_begin, 0)) * H * 2};
-    gemm_tile_dma<false, true, true>(x, w, k_len, m0, n0, smem, acc);
+    gemm_tile_dma<false, true, true, true>(x, w, k_len, m0, n0, smem, acc);
   } else {
-    gemm_tile_dma<false, true>(x, operand_slabs(WT + int64_t(k_begin / kDK) * H_pad * kDK, H_pad, k_len), k_len, m0, n0,
+    gemm_tile_dma<false, true, false, true>(x, operand_slabs(WT + int64_t(k_begin / kDK) * H_pad * kDK, H_pad, k_len), k_len, m0, n0,
                                smem, acc);
   }
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -858,7 +836,7 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_gemm_dw(
   // the tile's rows lie inside one vocabulary chunk of the transposed dz
   const uint16_t* const dzT_chunk = dzT + int64_t(m0 / VC) * VC * T_pad;
   Acc acc;
-  gemm_tile_dma<true, true>(operand_slabs(dzT_chunk, VC, nact[1]), operand_slabs(hTc, H_pad, nact[1]), nact[1], m0 % VC,
+  gemm_tile_dma<true, true, false, true>(operand_slabs(dzT_chunk, VC, nact[1]), operand_slabs(hTc, H_pad, nact[1]), nact[1], m0 % VC,
                             n0, smem, acc);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wm = wave >> 2, wn = wave & 3;
@@ -952,12 +930,8 @@ __global__ __launch_bounds__(256) void k_scatter_dh(const float* __restrict__ dh
   }
 }
 
-// the dz kernel stages a 256 x 256 bf16 tile in LDS after its main loop
-static_assert(size_t(kTile) * kTile * 2 <= kWarmSinkOff, "the dz staging tile must end before the warm-up sink");
-constexpr size_t kDzLdsBytes = kGemmLdsBytes;
-
-static aero_status set_lds(const void* fn, size_t bytes = kGemmLdsBytes) {
-  return hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes)) == hipSuccess
+static aero_status set_lds(const void* fn) {
+  return hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, int(kGemmLdsBytes)) == hipSuccess
              ? AERO_OK : AERO_ERR_HIP;
 }
 
@@ -1017,8 +991,8 @@ extern "C" aero_status aero_lmhead_logprob_fused(
   std::call_once(attr_once, [] {
     if (set_lds(reinterpret_cast<const void*>(k_fused_stats<false>)) != AERO_OK ||
         set_lds(reinterpret_cast<const void*>(k_fused_stats<true>)) != AERO_OK ||
-        set_lds(reinterpret_cast<const void*>(k_fused_dz<false>), kDzLdsBytes) != AERO_OK ||
-        set_lds(reinterpret_cast<const void*>(k_fused_dz<true>), kDzLdsBytes) != AERO_OK ||
+        set_lds(reinterpret_cast<const void*>(k_fused_dz<false>)) != AERO_OK ||
+        set_lds(reinterpret_cast<const void*>(k_fused_dz<true>)) != AERO_OK ||
         set_lds(reinterpret_cast<const void*>(k_gemm_dh<true>)) != AERO_OK ||
         set_lds(reinterpret_cast<const void*>(k_gemm_dh<false>)) != AERO_OK ||
         set_lds(reinterpret_cast<const void*>(k_gemm_dw<true>)) != AERO_OK ||
@@ -1095,10 +1069,10 @@ extern "C" aero_status aero_lmhead_logprob_fused(
   if (T > 0) {   // recompute mode only (the kernel leaves at once otherwise)
     const int n = p.tiles_v * tiles_t;
     if (ent)
-      hipLaunchKernelGGL(k_fused_dz<true>, dim3(unsigned(xcd_grid(n))), dim3(kGemmNT), kDzLdsBytes, s, Wp, hf, V,
+      hipLaunchKernelGGL(k_fused_dz<true>, dim3(unsigned(xcd_grid(n))), dim3(kGemmNT), kGemmLdsBytes, s, Wp, hf, V,
                          H, p.tiles_v, p.T_pad, p.VC, force, nact, gc, lsec, yc, ac, bc, dz, dzT);
     else
-      hipLaunchKernelGGL(k_fused_dz<false>, dim3(unsigned(xcd_grid(n))), dim3(kGemmNT), kDzLdsBytes, s, Wp, hf, V,
+      hipLaunchKernelGGL(k_fused_dz<false>, dim3(unsigned(xcd_grid(n))), dim3(kGemmNT), kGemmLdsBytes, s, Wp, hf, V,
                          H, p.tiles_v, p.T_pad, p.VC, force, nact, gc, lsec, yc, ac, bc, dz, dzT);
   }
   // the candidates' hidden rows, each times its scale, transposed to hTc: K-slabs over the candidate positions

@@ -138,6 +138,33 @@ def test_fused_backward(gh, T, H, V):
     check_bwd(gh, wl, h, W, dict(reject_enable=1, posterior_mode=1), dweight_dtype=torch.bfloat16, grad_scale=8.0)
 
 
+# up to 4096 rows dhidden reads the weight as it is, beyond through a transposed copy; splits that start past the
+# vocabulary, columns past H in the last tile, a tile of rows with one candidate
+@pytest.mark.parametrize("T,H,V", [(4096, 136, 520), (4097, 136, 520), (257, 264, 130), (33, 320, 1217)])
+def test_fused_backward_weight_forms(gh, T, H, V):
+    wl, h, W = make(T, H, V, sigma_w=2.0 / np.sqrt(H), len_hi=200 if T > 300 else None, Q=40 if T > 300 else 6)
+    check_bwd(gh, wl, h, W, dict())
+    check_bwd(gh, wl, h, W, dict(reject_enable=1, posterior_mode=1), entropy_coef=0.01, dweight_dtype=torch.bfloat16)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("H", [72, 320])
+def test_fused_dweight_off_the_16_byte_grid(gh, dtype, H):
+    """A dweight buffer that starts one element off takes element-wise stores: the same bits as an aligned one, the
+    neighbours untouched, with and without accumulation."""
+    T, V = 300, 515
+    wl, h, W = make(T, H, V, sigma_w=2.0 / np.sqrt(H))
+    ga = orc.group_advantage(wl.rewards, wl.lengths, wl.group_offsets, wl.keep_priority, AdvParams())
+    bwd = dict(old=np.full(T, -6.0), adv=ga["adv"], weight=ga["weight"])
+
+    def into(offset):
+        flat = torch.full((V * H + 8,), 0.25, dtype=dtype, device=gh.DEV)
+        run_fused(gh, wl, h, W, wl.targets, bwd=bwd, dw_into=flat[offset:offset + V * H].view(V, H))
+        assert (flat[:offset] == 0.25).all() and (flat[offset + V * H:] == 0.25).all()
+        return flat[offset:offset + V * H]
+    assert torch.equal(into(0), into(1))
+
+
 @pytest.mark.parametrize("seed", range(10))
 def test_fused_random_shapes(gh, seed):
     """Seeded random token counts, hidden sizes (multiples of 8, with and without whole 64-wide K slices)
