@@ -80,10 +80,12 @@ class _Lazy:
     """Loads the library on first use so that the package can be imported to build it."""
     _cdll = None
 
-    def __getattr__(self, name):
+    def __getattr__(self, name):   # first use of an entry point: kept as a plain attribute from then on
         if _Lazy._cdll is None:
             _Lazy._cdll = _load()
-        return getattr(_Lazy._cdll, name)
+        fn = getattr(_Lazy._cdll, name)
+        setattr(self, name, fn)
+        return fn
 
 
 _lib = _Lazy()
@@ -106,20 +108,40 @@ def _ptr(t: Optional[torch.Tensor], dtype=None, name: str = "") -> Optional[int]
     return t.data_ptr()
 
 
+class _Marshal:
+    """``pointers(t, dtype, name, ...)``: `_ptr` of every triple in one native call (csrc/marshal.cpp)."""
+
+    def __getattr__(self, name):
+        if name != "pointers":
+            raise AttributeError(name)
+        try:
+            from . import _marshal
+        except ImportError as e:
+            raise AeroError("the package's _marshal module is missing: build it with "
+                            "`python -m paper_2602_14338_amd.build` (there is no fallback path)") from e
+        _marshal.setup(AeroError, _ptr)
+        self.pointers = _marshal.pointers
+        return self.pointers
+
+
+_m = _Marshal()
+_F32, _I32, _U8, _BF16 = torch.float32, torch.int32, torch.uint8, torch.bfloat16
+
+
 def _stream(t: torch.Tensor) -> int:
-    return torch.cuda.current_stream(t.device).cuda_stream
+    """Handle of torch's current stream on the tensor's device (a GPU tensor: its pointer was taken before)."""
+    return torch._C._cuda_getCurrentRawStream(t.get_device())
+
+
+_DTYPE_CODES = {torch.bfloat16: AERO_BF16, torch.float32: AERO_F32, torch.float16: AERO_F16,
+                torch.float8_e4m3fn: AERO_F8E4M3}
 
 
 def _dtype_code(t: torch.Tensor) -> int:
-    if t.dtype == torch.bfloat16:
-        return AERO_BF16
-    if t.dtype == torch.float32:
-        return AERO_F32
-    if t.dtype == torch.float16:
-        return AERO_F16
-    if t.dtype == torch.float8_e4m3fn:
-        return AERO_F8E4M3
-    raise AeroError(f"unsupported dtype {t.dtype}")
+    code = _DTYPE_CODES.get(t.dtype)
+    if code is None:
+        raise AeroError(f"unsupported dtype {t.dtype}")
+    return code
 
 
 def aero_workspace_bytes(op: int, T: int = 0, V: int = 0, H: int = 0, R: int = 0, Q: int = 0) -> int:
@@ -130,44 +152,45 @@ def aero_group_advantage(rewards, lengths, group_offsets, keep_priority, Q: int,
                          adv, weight, keep_mask, kept_index, kept_offsets, group_zero_var, group_category,
                          err_flag=None) -> None:
     pc = params.to_c()
-    st = _lib.aero_group_advantage(
-        _ptr(rewards, torch.float32, "rewards"), _ptr(lengths, torch.int32, "lengths"),
-        _ptr(group_offsets, torch.int32, "group_offsets"), _ptr(keep_priority, None, "keep_priority"),
-        Q, R, C.byref(pc), _ptr(adv, torch.float32, "adv"), _ptr(weight, torch.float32, "weight"),
-        _ptr(keep_mask, torch.uint8, "keep_mask"), _ptr(kept_index, torch.int32, "kept_index"),
-        _ptr(kept_offsets, torch.int32, "kept_offsets"), _ptr(group_zero_var, torch.uint8, "group_zero_var"),
-        _ptr(group_category, torch.uint8, "group_category"), _ptr(err_flag, torch.int32, "err_flag"),
-        _stream(group_offsets))
+    p = _m.pointers(rewards, _F32, "rewards", lengths, _I32, "lengths", group_offsets, _I32, "group_offsets",
+                    keep_priority, None, "keep_priority", adv, _F32, "adv", weight, _F32, "weight",
+                    keep_mask, _U8, "keep_mask", kept_index, _I32, "kept_index", kept_offsets, _I32, "kept_offsets",
+                    group_zero_var, _U8, "group_zero_var", group_category, _U8, "group_category",
+                    err_flag, _I32, "err_flag")
+    st = _lib.aero_group_advantage(*p[:4], Q, R, C.byref(pc), *p[4:], _stream(group_offsets))
     _check(st, "aero_group_advantage")
 
 
 def aero_logprob_fwd(logits, T: int, V: int, ld: int, targets, row_active, logprob, entropy, lse,
                      err_flag=None) -> None:
-    st = _lib.aero_logprob_fwd(
-        _ptr(logits, None, "logits"), _dtype_code(logits), T, V, ld, _ptr(targets, torch.int32, "targets"),
-        _ptr(row_active, torch.uint8, "row_active"), _ptr(logprob, torch.float32, "logprob"),
-        _ptr(entropy, torch.float32, "entropy"), _ptr(lse, torch.float32, "lse"),
-        _ptr(err_flag, torch.int32, "err_flag"), _stream(logits))
+    z, *p = _m.pointers(logits, None, "logits", targets, _I32, "targets", row_active, _U8, "row_active",
+                        logprob, _F32, "logprob", entropy, _F32, "entropy", lse, _F32, "lse",
+                        err_flag, _I32, "err_flag")
+    st = _lib.aero_logprob_fwd(z, _dtype_code(logits), T, V, ld, *p, _stream(logits))
     _check(st, "aero_logprob_fwd")
+
+
+def _loss_pointers(logits, targets, lse, entropy, old_logprob, token_rollout, adv, weight, ref_logprob, loss, clip_frac,
+                   logprob_out, entropy_out, lse_out, dlogits, err_flag):
+    if dlogits is not None and dlogits.dtype != logits.dtype:
+        raise AeroError("dlogits must have the dtype of logits")
+    return _m.pointers(
+        logits, None, "logits", targets, _I32, "targets", lse, _F32, "lse", entropy, _F32, "entropy",
+        old_logprob, _F32, "old_logprob", token_rollout, _I32, "token_rollout", adv, _F32, "adv",
+        weight, _F32, "weight", ref_logprob, _F32, "ref_logprob", loss, _F32, "loss", clip_frac, _F32, "clip_frac",
+        logprob_out, _F32, "logprob_out", entropy_out, _F32, "entropy_out", lse_out, _F32, "lse_out",
+        dlogits, None, "dlogits", err_flag, _I32, "err_flag")
 
 
 def aero_grpo_loss_bwd(logits, T: int, V: int, ld: int, targets, lse, old_logprob, token_rollout, adv, weight,
                        R: int, eps_lo: float, eps_hi: float, grad_scale: float, loss, clip_frac, logprob_out,
                        dlogits, workspace, err_flag=None, entropy_out=None, lse_out=None,
                        entropy_coef: float = 0.0, entropy=None, kl_coef: float = 0.0, ref_logprob=None) -> None:
-    if dlogits is not None and dlogits.dtype != logits.dtype:
-        raise AeroError("dlogits must have the dtype of logits")
+    z, *p = _loss_pointers(logits, targets, lse, entropy, old_logprob, token_rollout, adv, weight, ref_logprob, loss,
+                           clip_frac, logprob_out, entropy_out, lse_out, dlogits, err_flag)
+    ws, = _m.pointers(workspace, None, "workspace")
     st = _lib.aero_grpo_loss_bwd(
-        _ptr(logits, None, "logits"), _dtype_code(logits), T, V, ld, _ptr(targets, torch.int32, "targets"),
-        _ptr(lse, torch.float32, "lse"), _ptr(entropy, torch.float32, "entropy"),
-        _ptr(old_logprob, torch.float32, "old_logprob"),
-        _ptr(token_rollout, torch.int32, "token_rollout"), _ptr(adv, torch.float32, "adv"),
-        _ptr(weight, torch.float32, "weight"), R, eps_lo, eps_hi, grad_scale, entropy_coef,
-        kl_coef, _ptr(ref_logprob, torch.float32, "ref_logprob"),
-        _ptr(loss, torch.float32, "loss"), _ptr(clip_frac, torch.float32, "clip_frac"),
-        _ptr(logprob_out, torch.float32, "logprob_out"), _ptr(entropy_out, torch.float32, "entropy_out"),
-        _ptr(lse_out, torch.float32, "lse_out"), _ptr(dlogits, None, "dlogits"),
-        _ptr(err_flag, torch.int32, "err_flag"), _ptr(workspace, None, "workspace"),
+        z, _dtype_code(logits), T, V, ld, *p[:7], R, eps_lo, eps_hi, grad_scale, entropy_coef, kl_coef, *p[7:], ws,
         workspace.numel() * workspace.element_size() if workspace is not None else 0, _stream(logits))
     _check(st, "aero_grpo_loss_bwd")
 
@@ -178,19 +201,10 @@ def aero_grpo_loss_bwd_noalloc(logits, T: int, V: int, ld: int, targets, lse, ol
                                entropy_coef: float = 0.0, entropy=None, kl_coef: float = 0.0,
                                ref_logprob=None) -> None:
     """aero_grpo_loss_bwd without a workspace argument: the library's own fixed scratch is used."""
-    if dlogits is not None and dlogits.dtype != logits.dtype:
-        raise AeroError("dlogits must have the dtype of logits")
-    st = _lib.aero_grpo_loss_bwd_noalloc(
-        _ptr(logits, None, "logits"), _dtype_code(logits), T, V, ld, _ptr(targets, torch.int32, "targets"),
-        _ptr(lse, torch.float32, "lse"), _ptr(entropy, torch.float32, "entropy"),
-        _ptr(old_logprob, torch.float32, "old_logprob"),
-        _ptr(token_rollout, torch.int32, "token_rollout"), _ptr(adv, torch.float32, "adv"),
-        _ptr(weight, torch.float32, "weight"), R, eps_lo, eps_hi, grad_scale, entropy_coef,
-        kl_coef, _ptr(ref_logprob, torch.float32, "ref_logprob"),
-        _ptr(loss, torch.float32, "loss"), _ptr(clip_frac, torch.float32, "clip_frac"),
-        _ptr(logprob_out, torch.float32, "logprob_out"), _ptr(entropy_out, torch.float32, "entropy_out"),
-        _ptr(lse_out, torch.float32, "lse_out"), _ptr(dlogits, None, "dlogits"),
-        _ptr(err_flag, torch.int32, "err_flag"), _stream(logits))
+    z, *p = _loss_pointers(logits, targets, lse, entropy, old_logprob, token_rollout, adv, weight, ref_logprob, loss,
+                           clip_frac, logprob_out, entropy_out, lse_out, dlogits, err_flag)
+    st = _lib.aero_grpo_loss_bwd_noalloc(z, _dtype_code(logits), T, V, ld, *p[:7], R, eps_lo, eps_hi, grad_scale,
+                                         entropy_coef, kl_coef, *p[7:], _stream(logits))
     _check(st, "aero_grpo_loss_bwd_noalloc")
 
 
@@ -200,18 +214,15 @@ def aero_lmhead_logprob_fused(hidden, weight, T: int, H: int, V: int, targets, l
                               loss=None, clip_frac=None, dhidden=None, dweight=None, workspace=None,
                               err_flag=None, entropy_coef: float = 0.0, kl_coef: float = 0.0,
                               ref_logprob=None, dweight_accumulate: bool = False) -> None:
+    p = _m.pointers(
+        hidden, _BF16, "hidden", weight, _BF16, "weight", targets, _I32, "targets", logprob, _F32, "logprob",
+        entropy, _F32, "entropy", lse, _F32, "lse", old_logprob, _F32, "old_logprob",
+        token_rollout, _I32, "token_rollout", adv, _F32, "adv", weight_rollout, _F32, "weight_rollout",
+        ref_logprob, _F32, "ref_logprob", loss, _F32, "loss", clip_frac, _F32, "clip_frac", dhidden, _BF16, "dhidden",
+        dweight, None, "dweight", err_flag, _I32, "err_flag", workspace, None, "workspace")
+    dweight_dtype = (_dtype_code(dweight) if dweight is not None else AERO_F32) | \
+        (AERO_DW_ACCUMULATE if dweight_accumulate else 0)
     st = _lib.aero_lmhead_logprob_fused(
-        _ptr(hidden, torch.bfloat16, "hidden"), _ptr(weight, torch.bfloat16, "weight"), T, H, V,
-        _ptr(targets, torch.int32, "targets"), _ptr(logprob, torch.float32, "logprob"),
-        _ptr(entropy, torch.float32, "entropy"), _ptr(lse, torch.float32, "lse"),
-        _ptr(old_logprob, torch.float32, "old_logprob"), _ptr(token_rollout, torch.int32, "token_rollout"),
-        _ptr(adv, torch.float32, "adv"), _ptr(weight_rollout, torch.float32, "weight_rollout"), R,
-        eps_lo, eps_hi, grad_scale, entropy_coef, kl_coef, _ptr(ref_logprob, torch.float32, "ref_logprob"),
-        _ptr(loss, torch.float32, "loss"),
-        _ptr(clip_frac, torch.float32, "clip_frac"),
-        _ptr(dhidden, torch.bfloat16, "dhidden"), _ptr(dweight, None, "dweight"),
-        (_dtype_code(dweight) if dweight is not None else AERO_F32) | (AERO_DW_ACCUMULATE if dweight_accumulate else 0),
-        _ptr(err_flag, torch.int32, "err_flag"),
-        _ptr(workspace, None, "workspace"),
-        workspace.numel() * workspace.element_size() if workspace is not None else 0, _stream(hidden))
+        *p[:2], T, H, V, *p[2:10], R, eps_lo, eps_hi, grad_scale, entropy_coef, kl_coef, *p[10:15], dweight_dtype,
+        *p[15:], workspace.numel() * workspace.element_size() if workspace is not None else 0, _stream(hidden))
     _check(st, "aero_lmhead_logprob_fused")
