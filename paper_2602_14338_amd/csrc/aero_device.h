@@ -166,6 +166,38 @@ __device__ __forceinline__ RowLogProb row_logprob(const RowStat& st, float zy) {
   return RowLogProb{st.m + (l + fix), lp, ((d - (lp + back)) + (back - l)) - fix};
 }
 
+// Loss term, its derivative with respect to the log-prob and the clip decision of one token whose rollout has
+// weight w != 0 (Eq. 2; the KL term in its per-token form exp(d) - d - 1, d = log pi_ref - log pi).  flag:
+// 0 = no advantage, 1 = unclipped, 2 = clipped.  ref is looked at only with kl_coef != 0.
+struct LossHyper {
+  float eps_lo, eps_hi, grad_scale, ent_coef, kl_coef;
+};
+struct TokenTerm {
+  float g, term;
+  int flag;
+};
+__device__ __forceinline__ TokenTerm token_term(const LossHyper& h, float A, float w, float lp, float low, float old_lp,
+                                                float ref) {
+  TokenTerm r{0.f, 0.f, 0};
+  if (A != 0.f) {
+    const float rho = expf(lp - old_lp + low);
+    const float lo = 1.f - h.eps_lo, hi = 1.f + h.eps_hi;
+    const float clipped = fminf(fmaxf(rho, lo), hi);
+    const float s = fminf(rho * A, clipped * A);
+    const bool unclipped = A > 0.f ? (rho <= hi) : (rho >= lo);
+    r.term = -w * s;
+    r.g = unclipped ? -h.grad_scale * w * A * rho : 0.f;
+    r.flag = unclipped ? 1 : 2;
+  }
+  if (h.kl_coef != 0.f) {
+    const float d = ref - lp - low;
+    const float ed = expf(d);
+    r.term += h.kl_coef * w * (ed - d - 1.f);
+    r.g += h.grad_scale * h.kl_coef * w * (1.f - ed);
+  }
+  return r;
+}
+
 // Fold N logits into a thread's running state.  The offset m is only moved when a value
 // exceeds it by more than kLazy nats, so the rescale is rare and exp(z - m) stays below
 // e^kLazy; sums of 2^24 such terms stay far inside fp32 range.

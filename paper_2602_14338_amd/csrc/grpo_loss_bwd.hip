@@ -74,16 +74,12 @@ __global__ __launch_bounds__(256) void k_signal_mask(
 }
 
 // ---------------------------------------------------------------- token terms
-// LP_GIVEN: the current log-prob is read from `logprob_in` (fused LM-head path) instead of
-// being formed as z[t, y] - lse[t]; lp_low holds what its rounding to 32 bits left off.
-template <int DT, bool LP_GIVEN>
+template <int DT>
 __global__ __launch_bounds__(256) void k_token_terms(
     const void* __restrict__ logits, int64_t T, int V, int64_t ld, const int32_t* __restrict__ targets,
-    const float* __restrict__ lse, const float* __restrict__ logprob_in, const float* __restrict__ lp_low,
-    const float* __restrict__ old_logprob, const int32_t* __restrict__ token_rollout,
-    const float* __restrict__ adv, const float* __restrict__ weight, int R,
-    float eps_lo, float eps_hi, float grad_scale, float ent_coef, const float* __restrict__ entropy,
-    float kl_coef, const float* __restrict__ ref_logprob,
+    const float* __restrict__ lse, const float* __restrict__ old_logprob, const int32_t* __restrict__ token_rollout,
+    const float* __restrict__ adv, const float* __restrict__ weight, int R, LossHyper h,
+    const float* __restrict__ entropy, const float* __restrict__ ref_logprob,
     float* __restrict__ g_out, float* __restrict__ term_out, int32_t* __restrict__ flag_out,
     float* __restrict__ ea_out, float* __restrict__ eb_out,
     float* __restrict__ logprob_out, int32_t* __restrict__ err_flag) {
@@ -91,54 +87,34 @@ __global__ __launch_bounds__(256) void k_token_terms(
   if (t >= T) return;
   const int i = token_rollout[t];
   const int y = targets[t];
-  float g = 0.f, term = 0.f, lp = 0.f, low = 0.f, ea = 0.f, eb = 0.f;
-  int flag = 0;
+  TokenTerm r{0.f, 0.f, 0};
+  float lp = 0.f, ea = 0.f, eb = 0.f;
   if (i < 0 || y < 0) {
     // padding / ignored row: whatever its other index holds is not looked at
   } else if (i >= R || y >= V) {
     if (err_flag) atomicOr(err_flag, i >= R ? AERO_DERR_BAD_ROLLOUT : AERO_DERR_BAD_TARGET);
   } else {
     const float A = adv[i], w = weight[i];
-    if (w != 0.f && (A != 0.f || ent_coef != 0.f || kl_coef != 0.f)) {   // decided before the ratio is touched
-      if constexpr (LP_GIVEN) {
-        lp = logprob_in[t];
-        low = lp_low[t];
-      } else {
-        const float zy = load_elt<DT>(logits, int64_t(t) * ld + y), l = lse[t];
-        lp = zy - l;
-        const float back = zy - lp;   // two-sum: what the rounding of the difference left off
-        low = (zy - (lp + back)) + (back - l);
-      }
-      if (A != 0.f) {
-        const float rho = expf(lp - old_logprob[t] + low);
-        const float lo = 1.f - eps_lo, hi = 1.f + eps_hi;
-        const float clipped = fminf(fmaxf(rho, lo), hi);
-        const float s = fminf(rho * A, clipped * A);
-        const bool unclipped = A > 0.f ? (rho <= hi) : (rho >= lo);
-        term = -w * s;
-        g = unclipped ? -grad_scale * w * A * rho : 0.f;
-        flag = unclipped ? 1 : 2;
-      }
-      if (kl_coef != 0.f) {   // Eq. 2's beta term, per-token estimator exp(d) - d - 1, d = log pi_ref - log pi
-        const float d = ref_logprob[t] - lp - low;
-        const float ed = expf(d);
-        term += kl_coef * w * (ed - d - 1.f);
-        g += grad_scale * kl_coef * w * (1.f - ed);
-      }
-      if (ent_coef != 0.f) {
+    if (w != 0.f && (A != 0.f || h.ent_coef != 0.f || h.kl_coef != 0.f)) {   // decided before the ratio is touched
+      const float zy = load_elt<DT>(logits, int64_t(t) * ld + y), l = lse[t];
+      lp = zy - l;
+      const float back = zy - lp;   // two-sum: what the rounding of the difference left off
+      const float low = (zy - (lp + back)) + (back - l);
+      r = token_term(h, A, w, lp, low, A != 0.f ? old_logprob[t] : 0.f, h.kl_coef != 0.f ? ref_logprob[t] : 0.f);
+      if (h.ent_coef != 0.f) {
         const float H = entropy[t];
-        term -= ent_coef * w * H;
-        ea = grad_scale * ent_coef * w;
-        eb = ea * (H - lse[t]) - g;
+        r.term -= h.ent_coef * w * H;
+        ea = h.grad_scale * h.ent_coef * w;
+        eb = ea * (H - l) - r.g;
       }
     }
   }
   // the sign of a zero carries "leave the gradient row alone" to the gradient kernels, which have g_t in hand
   // before anything else: +0 = fill the row with zeros, -0 = do not write it
-  if (g == 0.f) g = (i == AERO_ROW_UNTOUCHED) ? -0.f : 0.f;
-  g_out[t] = g;
-  term_out[t] = term;
-  flag_out[t] = flag;
+  if (r.g == 0.f) r.g = (i == AERO_ROW_UNTOUCHED) ? -0.f : 0.f;
+  g_out[t] = r.g;
+  term_out[t] = r.term;
+  flag_out[t] = r.flag;
   if (ea_out) {
     ea_out[t] = ea;
     eb_out[t] = eb;
@@ -148,9 +124,11 @@ __global__ __launch_bounds__(256) void k_token_terms(
 
 // ---------------------------------------------------------------- loss reduce
 constexpr int kReduceNT = 1024;
+// count: number of terms when only the device knows it (nullable, then T)
 __global__ __launch_bounds__(kReduceNT) void k_loss_reduce(
-    const float* __restrict__ term, const int32_t* __restrict__ flag, int64_t T,
+    const float* __restrict__ term, const int32_t* __restrict__ flag, int64_t T, const int32_t* __restrict__ count,
     float* __restrict__ loss, float* __restrict__ clip_frac) {
+  if (count) T = *count;
   __shared__ double s_sum[kReduceNT];
   __shared__ int s_sig[kReduceNT], s_clip[kReduceNT];
   double acc = 0.0;
@@ -365,20 +343,10 @@ static void dispatch_dlogits_dtype(int32_t dtype, bool vec, const void* logits, 
   }
 }
 
-// Shared with the fused LM-head path: token terms from given log-probs, then the reduction.
-aero_status token_terms_from_logprob(int64_t T, int V, const int32_t* targets, const float* logprob,
-                                     const float* lp_low, const float* lse, const float* entropy, const float* old_logprob,
-                                     const int32_t* token_rollout, const float* adv, const float* weight, int R,
-                                     float eps_lo, float eps_hi, float grad_scale, float ent_coef, float kl_coef,
-                                     const float* ref_logprob, float* g, float* term, int32_t* flag, float* ea,
-                                     float* eb, float* loss, float* clip_frac, int32_t* err_flag, hipStream_t s) {
-  const unsigned blocks = unsigned((T + 255) / 256);
-  if (T > 0)
-    hipLaunchKernelGGL((k_token_terms<kBF16, true>), dim3(blocks), dim3(256), 0, s, nullptr, T, V, int64_t(0),
-                       targets, lse, logprob, lp_low, old_logprob, token_rollout, adv, weight, R, eps_lo, eps_hi,
-                       grad_scale, ent_coef, entropy, kl_coef, ref_logprob, g, term, flag, ea, eb, nullptr, err_flag);
-  hipLaunchKernelGGL(k_loss_reduce, dim3(1), dim3(kReduceNT), 0, s, term, flag, T, loss, clip_frac);
-  return launch_status();
+// Shared with the fused LM-head path: the reduction over `count` (device) terms.
+void loss_reduce_launch(const float* term, const int32_t* flag, const int32_t* count, float* loss, float* clip_frac,
+                        hipStream_t s) {
+  hipLaunchKernelGGL(k_loss_reduce, dim3(1), dim3(kReduceNT), 0, s, term, flag, int64_t(0), count, loss, clip_frac);
 }
 
 // The loss call proper; both entry points below end here.
@@ -403,7 +371,7 @@ static aero_status loss_bwd_run(
     return AERO_ERR_WORKSPACE;
   LossWorkspace ws = carve(workspace, T);
   if (T == 0) {
-    hipLaunchKernelGGL(k_loss_reduce, dim3(1), dim3(kReduceNT), 0, s, nullptr, nullptr, T, loss, clip_frac);
+    hipLaunchKernelGGL(k_loss_reduce, dim3(1), dim3(kReduceNT), 0, s, nullptr, nullptr, T, nullptr, loss, clip_frac);
     return launch_status();
   }
   const unsigned blocks = unsigned((T + 255) / 256);
@@ -419,7 +387,7 @@ static aero_status loss_bwd_run(
                                                 logprob_out, entropy_out, lse_out, dlogits, err_flag, ws.counter,
                                                 reinterpret_cast<int32_t*>(ws.lp_tmp), s);
       if (sp != AERO_OK) return sp;
-      hipLaunchKernelGGL(k_loss_reduce, dim3(1), dim3(kReduceNT), 0, s, ws.loss_term, ws.flag, T, loss, clip_frac);
+      hipLaunchKernelGGL(k_loss_reduce, dim3(1), dim3(kReduceNT), 0, s, ws.loss_term, ws.flag, T, nullptr, loss, clip_frac);
       return launch_status();
     }
     hipLaunchKernelGGL(k_signal_mask, dim3(blocks), dim3(256), 0, s, T, V, targets, token_rollout, adv, weight,
@@ -436,15 +404,14 @@ static aero_status loss_bwd_run(
   } else if (entropy_out || lse_out) {
     return AERO_ERR_NULL;   // these outputs exist only when the statistics are computed here
   }
-  auto token_terms = dtype == AERO_BF16 ? k_token_terms<kBF16, false>
-                     : dtype == AERO_F16 ? k_token_terms<kF16, false>
-                     : dtype == AERO_F8E4M3 ? k_token_terms<kF8, false> : k_token_terms<kF32, false>;
-  hipLaunchKernelGGL(token_terms, dim3(blocks), dim3(256), 0, s, logits, T, V, ld, targets, lse,
-                     static_cast<const float*>(nullptr), static_cast<const float*>(nullptr), old_logprob, token_rollout, adv, weight,
-                     R, eps_lo, eps_hi,
-                     grad_scale, entropy_coef, entropy, kl_coef, ref_logprob, ws.g, ws.loss_term, ws.flag,
+  auto token_terms = dtype == AERO_BF16 ? k_token_terms<kBF16>
+                     : dtype == AERO_F16 ? k_token_terms<kF16>
+                     : dtype == AERO_F8E4M3 ? k_token_terms<kF8> : k_token_terms<kF32>;
+  const LossHyper hyper{eps_lo, eps_hi, grad_scale, entropy_coef, kl_coef};
+  hipLaunchKernelGGL(token_terms, dim3(blocks), dim3(256), 0, s, logits, T, V, ld, targets, lse, old_logprob,
+                     token_rollout, adv, weight, R, hyper, entropy, ref_logprob, ws.g, ws.loss_term, ws.flag,
                      ent ? ws.ea : nullptr, ent ? ws.eb : nullptr, lp_dst, err_flag);
-  hipLaunchKernelGGL(k_loss_reduce, dim3(1), dim3(kReduceNT), 0, s, ws.loss_term, ws.flag, T, loss, clip_frac);
+  hipLaunchKernelGGL(k_loss_reduce, dim3(1), dim3(kReduceNT), 0, s, ws.loss_term, ws.flag, T, nullptr, loss, clip_frac);
   if (dlogits) {
     const bool vec = rows_alike(logits, dlogits, storage_bytes(dtype));
     if (ent) dispatch_dlogits_dtype<true>(dtype, vec, logits, T, V, ld, targets, lse, ws.g, ws.ea, ws.eb, dlogits, s);

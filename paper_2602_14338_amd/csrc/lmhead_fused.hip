@@ -4,20 +4,21 @@
 // Forward   k_compact_valid  rows that have a target are compacted (padding rows take no part in any
 //                            contraction; their outputs are written as zeros) and gathered; when a
 //                            backward pass follows, the candidates - rows whose rollout has weight and
-//                            advantage, i.e. the set AERO's curation leaves - come first
-//           k_target_logit   zy = logit of the sampled token (one H-long dot product per row)
+//                            advantage, i.e. the set AERO's curation leaves - come first; zy = logit of a
+//                            row's sampled token (one H-long dot product)
 //           k_fused_stats    tile of z^T (vocab rows x token columns): every lane owns one token column
 //                            per block, so the running (offset, sum exp, sum exp*z) is a per-lane
 //                            register recurrence with no shuffles.  On the candidates' token tiles it
 //                            also leaves P = exp(z - zy) in bf16 in K-slabs [vocab/64][token][64] and
 //                            [vocab chunk][token/64][vocab in chunk][64], both in fragment order, that
 //                            the two gradient contractions read (2 x T x V x 2 bytes are held)
-//           k_fused_combine  merges the per-tile partials of a token -> logprob, entropy, lse
-// Backward  token terms + loss reduce (shared with the logits path), then
-//           k_candidate_scalars  dz = g (onehot - exp(z - lse)) = scale * P with scale = -g exp(logprob)
+//           k_fused_rows     merges the per-tile partials of a token -> logprob, entropy, lse, and in the same
+//                            breath the candidates' loss terms and gradient scalars:
+//                            dz = g (onehot - exp(z - lse)) = scale * P with scale = -g exp(logprob)
 //                            per token, except the sampled token's own entry, which is written here; the
 //                            scale travels with the other operand (dweight) or is applied after the
 //                            contraction (dhidden), so z is never formed a second time
+// Backward  loss reduce (shared with the logits path), then
 //           k_fused_dz       only when that does not apply (an entropy term in the rows, or a sampled
 //                            token more than 40 nats below another logit, where P would leave its safe
 //                            range): recompute the z^T tile and store dz itself in the same layouts
@@ -31,12 +32,8 @@
 
 namespace aero {
 
-aero_status token_terms_from_logprob(int64_t T, int V, const int32_t* targets, const float* logprob,
-                                     const float* lp_low, const float* lse, const float* entropy, const float* old_logprob,
-                                     const int32_t* token_rollout, const float* adv, const float* weight, int R,
-                                     float eps_lo, float eps_hi, float grad_scale, float ent_coef, float kl_coef,
-                                     const float* ref_logprob, float* g, float* term, int32_t* flag, float* ea,
-                                     float* eb, float* loss, float* clip_frac, int32_t* err_flag, hipStream_t s);
+void loss_reduce_launch(const float* term, const int32_t* flag, const int32_t* count, float* loss, float* clip_frac,
+                        hipStream_t s);
 
 constexpr size_t kWsAlign = 256;
 inline size_t up(size_t x, size_t a) { return (x + a - 1) / a * a; }
@@ -48,8 +45,7 @@ struct FusedPlan {
   int64_t T, T_pad;
   int V, V_ld, H, H_pad, tiles_v, VC, n_chunks;   // VC: vocabulary rows per chunk of the transposed dz
   bool direct;   // dhidden reads the weight as it is, no transposed copy
-  size_t off_part, off_fidx, off_nf, off_g, off_term, off_flag, off_ea, off_eb, off_ent, off_zy, off_pos, off_nact,
-      off_lplow, off_gc, off_lsec, off_yc, off_ac, off_bc, off_scale,
+  size_t off_part, off_fidx, off_nf, off_term, off_flag, off_zy, off_pos, off_nact, off_gc, off_lsec, off_yc, off_ac, off_bc, off_scale,
       off_hc, off_hTc, off_WT, off_dz, off_dzT, off_dhacc, total;
 };
 
@@ -105,16 +101,11 @@ static FusedPlan make_plan(int64_t T, int V, int H) {
   p.off_part = take(size_t(3) * p.tiles_v * p.T_pad * 4);
   p.off_fidx = take(size_t(p.T_pad) * 4);
   p.off_nf = take(16);
-  p.off_g = take(size_t(p.T_pad) * 4);
   p.off_term = take(size_t(p.T_pad) * 4);
   p.off_flag = take(size_t(p.T_pad) * 4);
-  p.off_ea = take(size_t(p.T_pad) * 4);
-  p.off_eb = take(size_t(p.T_pad) * 4);
-  p.off_ent = take(size_t(p.T_pad) * 4);
   p.off_zy = take(size_t(p.T_pad) * 4);
   p.off_pos = take(size_t(p.T_pad) * 4);
   p.off_nact = take(16);
-  p.off_lplow = take(size_t(p.T_pad) * 4);
   p.off_gc = take(size_t(p.T_pad) * 4);
   p.off_lsec = take(size_t(p.T_pad) * 4);
   p.off_yc = take(size_t(p.T_pad) * 4);
@@ -169,7 +160,7 @@ __device__ __forceinline__ int dh_splits(int active_tiles, int tiles_h, int grid
 //   nact = {candidates, rounded up, 0, splits}: nact[2] is the flag the forward pass raises when a stored
 //   exponential left its safe range (see k_fused_stats), nact[3] the split count of the dhidden contraction.
 // token_rollout == null (forward-only call): no candidates, pos / nact are not written.
-// Ignored rows get their zero outputs here; a target >= V raises the device error bit.
+// Ignored rows get their zero outputs here; a target >= V or a rollout index >= R raises its device error bit.
 __global__ __launch_bounds__(1024) void k_compact_valid(
     const int32_t* __restrict__ targets, int64_t T, int64_t T_pad, int V, const int32_t* __restrict__ token_rollout,
     const float* __restrict__ adv, const float* __restrict__ weight, int R, int every_weighted,
@@ -213,7 +204,7 @@ __global__ __launch_bounds__(1024) void k_compact_valid(
   }
   run_o += total_c;   // the other rows follow the candidates
   const int total = total_c + total_o;
-  bool bad = false;
+  bool bad_y = false, bad_i = false;
   for (int64_t t0 = lo; t0 < hi; t0 += 64) {
     const int64_t t = t0 + lane;
     const bool in = t < hi;
@@ -229,13 +220,15 @@ __global__ __launch_bounds__(1024) void k_compact_valid(
       logprob[t] = 0.f;
       lse_out[t] = 0.f;
       if (entropy) entropy[t] = 0.f;
-      bad |= targets[t] >= V;
+      bad_y |= targets[t] >= V;
     }
+    if (in && token_rollout) bad_i |= targets[t] >= 0 && token_rollout[t] >= R;
     if (in && pos) pos[t] = at;
     run_c += __popcll(m_c);
     run_o += __popcll(m_o);
   }
-  if (bad && err_flag) atomicOr(err_flag, AERO_DERR_BAD_TARGET);
+  if ((bad_y || bad_i) && err_flag)
+    atomicOr(err_flag, (bad_y ? AERO_DERR_BAD_TARGET : 0) | (bad_i ? AERO_DERR_BAD_ROLLOUT : 0));
   for (int64_t j = total + tid; j < T_pad; j += 1024) fidx[j] = -1;
   const int splits = wave == 0 && nact ? dh_splits((total_c + kTile - 1) / kTile, tiles_h, dh_grid, slices, rows_max) : 0;
   if (tid == 0) {
@@ -252,19 +245,33 @@ __global__ __launch_bounds__(1024) void k_compact_valid(
   }
 }
 
-// out[j][:] = in[idx[j]][:] (zeros where idx[j] < 0), H % 8 == 0, 16-byte vectors; one wave per row.
-__global__ __launch_bounds__(256) void k_gather_rows(const uint16_t* __restrict__ in, int H,
-                                                     const int32_t* __restrict__ idx, int64_t n_rows,
-                                                     uint16_t* __restrict__ out) {
+// Row j of `out` = hidden row fidx[j] (zeros where fidx[j] < 0), and zy[j] = logit of its sampled token = <hidden
+// row, weight row>, fp32 accumulation of the bf16 products in a fixed order (0 past the count).  H % 8 == 0,
+// 16-byte vectors; one wave per row, n_rows a multiple of 4.
+__global__ __launch_bounds__(256) void k_gather_rows(const uint16_t* __restrict__ in, const uint16_t* __restrict__ W, int H,
+                                                     const int32_t* __restrict__ fidx,
+                                                     const int32_t* __restrict__ targets, uint16_t* __restrict__ out,
+                                                     float* __restrict__ zy) {
   const int lane = threadIdx.x & 63;
   const int64_t j = int64_t(blockIdx.x) * 4 + (threadIdx.x >> 6);
-  if (j >= n_rows) return;
-  const int src = idx[j];
+  const int src = fidx[j];
+  const uint16_t* hr = in + int64_t(max(src, 0)) * H;
+  const uint16_t* wr = W + int64_t(src >= 0 ? targets[src] : 0) * H;   // 0 <= target < V by construction of fidx
+  float dot = 0.f;
   for (int k = lane * 8; k < H; k += kWave * 8) {
     u32x4_t v = {0u, 0u, 0u, 0u};
-    if (src >= 0) v = *reinterpret_cast<const u32x4_t*>(in + int64_t(src) * H + k);
+    if (src >= 0) {
+      v = *reinterpret_cast<const u32x4_t*>(hr + k);
+      float a[8], b[8];
+      unpack8(v, a);
+      unpack8(*reinterpret_cast<const u32x4_t*>(wr + k), b);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) dot = fmaf(a[e], b[e], dot);
+    }
     *reinterpret_cast<u32x4_t*>(out + j * H + k) = v;
   }
+  dot = wave_reduce(dot, [](float x, float y) { return x + y; });
+  if (lane == 0) zy[j] = dot;
 }
 
 // Exchange with a neighbouring lane inside a quad by a lane permutation of the vector ALU (no LDS traffic).
@@ -340,11 +347,11 @@ __device__ __forceinline__ void store_tile_both_layouts(const uint32_t (&pk)[kNB
 // past the count); part_* are [tiles_v][T_pad], indexed by compact row.
 //
 // STORE (a backward pass follows and its rows have the plain form dz = g (onehot - pi)): the token tiles that
-// hold candidates also leave P = exp(z - zy) in bf16, zy = the sampled token's own logit (k_target_logit), in
+// hold candidates also leave P = exp(z - zy) in bf16, zy = the sampled token's own logit (k_gather_rows), in
 // the two K-slab layouts of the gradient contractions, so that the backward pass need not form z again:
 //   dz[t, v] = s_t P[t, v] (v != y_t),  s_t = -g_t exp(logprob_t),  because exp(z - lse) = exp(z - zy) exp(zy - lse);
 // the per-token factor s_t moves into the other operand (dweight) or behind the contraction (dhidden), and the
-// one entry per row that differs, v = y_t, is overwritten once the log-prob is known (k_candidate_scalars).
+// one entry per row that differs, v = y_t, is overwritten once the log-prob is known (candidate_row).
 // bf16 keeps fp32's exponent range, so P is safe as long as z - zy stays far below 88, and so is the scale
 // (about g times the sampled token's probability, which must stay a normal number after it is multiplied
 // into a bf16 hidden row) as long as that probability is not below e^-52 or so; a tile that sees
@@ -484,93 +491,12 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_fused_stats(
   }
 }
 
-// zy[j] = logit of the sampled token of compact row j = <hidden row, weight row>, fp32 accumulation of the
-// bf16 products in a fixed order; 0 past the count.  One wave per row.
-__global__ __launch_bounds__(256) void k_target_logit(
-    const uint16_t* __restrict__ W, const uint16_t* __restrict__ Hf, int H, int64_t T_pad,
-    const int32_t* __restrict__ fidx, const int32_t* __restrict__ nf, const int32_t* __restrict__ targets,
-    float* __restrict__ zy) {
-  const int lane = threadIdx.x & 63;
-  const int64_t j = int64_t(blockIdx.x) * 4 + (threadIdx.x >> 6);
-  if (j >= T_pad) return;
-  float dot = 0.f;
-  if (j < nf[0]) {   // uniform over the wave
-    const int y = targets[fidx[j]];   // 0 <= y < V by construction of fidx
-    const uint16_t* hr = Hf + j * H;
-    const uint16_t* wr = W + int64_t(y) * H;
-    for (int k = lane * 8; k < H; k += kWave * 8) {
-      float a[8], b[8];
-      unpack8(*reinterpret_cast<const u32x4_t*>(hr + k), a);
-      unpack8(*reinterpret_cast<const u32x4_t*>(wr + k), b);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) dot = fmaf(a[e], b[e], dot);
-    }
-#pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) dot += __shfl_xor(dot, off, kWave);
-  }
-  if (lane == 0) zy[j] = dot;
-}
-
-// 64 consecutive compact rows per workgroup of 16 waves.  Phase 1: lane <-> row, the tiles_v
-// partials are split over the waves (every load is one coalesced 256-byte row segment) and merged
-// through LDS; a few hundred tokens are a handful of workgroups, so the loads of kCombineAhead partials are
-// issued before the first is merged (one at a time: 27 us whatever the token count up to 16384).  Phase 2: each
-// wave takes 4 of the rows, merges their 16 partials and subtracts the log-partition from the sampled token's
-// logit (zy, from k_target_logit); results go to the row's original position.  The log-partition and the
-// log-prob are formed in 64 bits: what their rounding to 32 loses of the log-prob goes to lp_low (nullable), so
-// that the ratio of the loss terms, whose sum cancels inside a group, does not carry it.
-constexpr int kCombineTokens = 64;
-constexpr int kCombineWaves = 16;
-constexpr int kCombineAhead = 8;
-__global__ __launch_bounds__(kCombineWaves * kWave) void k_fused_combine(
-    int tiles_v, int64_t T_pad, const int32_t* __restrict__ fidx, const int32_t* __restrict__ nf,
-    const float* __restrict__ part_m, const float* __restrict__ part_s, const float* __restrict__ part_sz,
-    const float* __restrict__ zy, float* __restrict__ logprob, float* __restrict__ entropy,
-    float* __restrict__ lse_out, float* __restrict__ lp_low) {
-  __shared__ RowStat xs[kCombineWaves][kCombineTokens];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t j0 = int64_t(blockIdx.x) * kCombineTokens;   // j0 + 63 < T_pad
-  const int n = nf[0];
-  if (j0 >= n) return;
-  RowStat st = stat_identity();
-  for (int tv = wave; tv < tiles_v; tv += kCombineAhead * kCombineWaves) {
-    RowStat v[kCombineAhead];
-#pragma unroll
-    for (int u = 0; u < kCombineAhead; ++u) {
-      const int at = tv + u * kCombineWaves;   // uniform over the wave
-      const int64_t o = int64_t(at) * T_pad + j0 + lane;
-      v[u] = at < tiles_v ? RowStat{part_m[o], part_s[o], part_sz[o]} : stat_identity();
-    }
-#pragma unroll
-    for (int u = 0; u < kCombineAhead; ++u) st = stat_merge(st, v[u]);
-  }
-  xs[wave][lane] = st;
-  __syncthreads();
-  constexpr int kPerWave = kCombineTokens / kCombineWaves;
-  // the 16 wave partials of a row, merged by a 16-lane tree in a fixed order: 16 lanes per row
-  static_assert(kPerWave * kCombineWaves == kWave, "a wave's rows fill its lanes");
-  const int c = wave * kPerWave + lane / kCombineWaves;
-  RowStat r = xs[lane % kCombineWaves][c];
-#pragma unroll
-  for (int off = kCombineWaves / 2; off > 0; off >>= 1) r = stat_merge(r, stat_shfl_xor(r, off));
-  const int64_t j = j0 + c;
-  if (lane % kCombineWaves == 0 && j < n) {
-    const int64_t t = fidx[j];
-    const double lse = double(r.m) + log(double(r.s));
-    const double lp = double(zy[j]) - lse;
-    const float lp32 = float(lp);
-    logprob[t] = lp32;
-    lse_out[t] = float(lse);
-    if (lp_low) lp_low[t] = float(lp - double(lp32));
-    if (entropy) entropy[t] = float(lse - double(r.sz) / double(r.s));
-  }
-}
-
 // ------------------------------------------------------------------------------------------
-// backward: compaction, transposes
+// per token: statistics, loss term, scalars of the gradient row
 // ------------------------------------------------------------------------------------------
-// Per-candidate scalars, in candidate order (position j <-> token fidx[j]; positions from the count up to
-// T_pad are padding without gradient).  The gradient row of a candidate is
+// What the backward part needs of a row, all nullptr / unused in a forward-only call.  Per-candidate outputs are in
+// candidate order (position j <-> token fidx[j]; positions from the count up to T_pad are padding without
+// gradient).  The gradient row of a candidate is
 //   dz_v = pi_v (ac z_v + bc) + gc 1[v = y],   (ac, bc) = (0, -g) without an entropy term.
 // Two ways to get there, chosen here for the whole call (recompute = the caller forces it, or the forward
 // pass raised nact[2]):
@@ -578,42 +504,111 @@ __global__ __launch_bounds__(kCombineWaves * kWave) void k_fused_combine(
 //                entry v = y, g (1 - pi_y) = scale * (-(exp(-logprob) - 1)), is written into both layouts here
 //   recompute    k_fused_dz forms dz from gc / lsec / yc / ac / bc; scale = 1
 // scale is 0 on padding positions, so that rows the forward tile stored past the candidates drop out.
-__global__ __launch_bounds__(256) void k_candidate_scalars(
-    const int32_t* __restrict__ fidx, const int32_t* __restrict__ nact, const float* __restrict__ g,
-    const float* __restrict__ ea, const float* __restrict__ eb, const float* __restrict__ lse,
-    const float* __restrict__ logprob, const int32_t* __restrict__ targets, int64_t T_pad, int VC, int force_recompute,
-    float* __restrict__ gc, float* __restrict__ lsec, int32_t* __restrict__ yc, float* __restrict__ ac,
-    float* __restrict__ bc, float* __restrict__ scale, uint16_t* __restrict__ dz, uint16_t* __restrict__ dzT) {
-  const int64_t j = int64_t(blockIdx.x) * 256 + threadIdx.x;
-  if (j >= T_pad) return;
-  if (j >= nact[0]) {
-    gc[j] = 0.f;
-    lsec[j] = 1e30f;   // exp(z - lsec) = 0 whatever z is
-    yc[j] = -1;
-    ac[j] = 0.f;
-    bc[j] = 0.f;
-    scale[j] = 0.f;
+struct FusedTerms {
+  const int32_t *targets, *token_rollout;
+  const float *old_logprob, *adv, *weight, *ref_logprob;
+  LossHyper hyper;
+  const int32_t* nact;
+  int64_t T_pad;
+  int VC, force_recompute;
+  float* term;
+  int32_t* flag;
+  float *gc, *lsec;
+  int32_t* yc;
+  float *ac, *bc, *scale;
+  uint16_t *dz, *dzT;
+};
+
+__device__ __forceinline__ void candidate_row(const FusedTerms& q, int64_t j, int64_t t, float lse, float lp, float low,
+                                              float entropy) {
+  const int i = q.token_rollout[t], y = q.targets[t];
+  const LossHyper& h = q.hyper;
+  const float A = q.adv[i], w = q.weight[i];
+  TokenTerm r = token_term(h, A, w, lp, low, A != 0.f ? q.old_logprob[t] : 0.f, h.kl_coef != 0.f ? q.ref_logprob[t] : 0.f);
+  float ac = 0.f, bc = -r.g;
+  if (h.ent_coef != 0.f) {
+    r.term -= h.ent_coef * w * entropy;
+    ac = h.grad_scale * h.ent_coef * w;
+    bc = ac * (entropy - lse) - r.g;
+  }
+  q.term[j] = r.term;
+  q.flag[j] = r.flag;
+  q.gc[j] = r.g;
+  q.lsec[j] = lse;
+  q.yc[j] = y;
+  q.ac[j] = ac;
+  q.bc[j] = bc;
+  if (q.force_recompute || q.nact[2] != 0) {
+    q.scale[j] = 1.f;
     return;
   }
-  const int64_t t = fidx[j];
-  const float gv = g[t];
-  const int y = targets[t];
-  gc[j] = gv;
-  lsec[j] = lse[t];
-  yc[j] = y;
-  ac[j] = ea ? ea[t] : 0.f;
-  bc[j] = ea ? eb[t] : -gv;
-  if (force_recompute || nact[2] != 0) {
-    scale[j] = 1.f;
-    return;
-  }
-  const float lp = logprob[t];
-  scale[j] = -gv * expf(lp);
+  q.scale[j] = -r.g * expf(lp);
   const uint16_t own = f32_to_bf16(-expm1f(-lp));
-  dz[frag_order_offset(T_pad, j, y)] = own;
-  dzT[int64_t(y / VC) * VC * T_pad + frag_order_offset(VC, y % VC, j)] = own;
+  q.dz[frag_order_offset(q.T_pad, j, y)] = own;
+  q.dzT[int64_t(y / q.VC) * q.VC * q.T_pad + frag_order_offset(q.VC, y % q.VC, j)] = own;
 }
 
+// TOK consecutive compact rows per workgroup of 1024 threads.  The tiles_v partials of a row are split over
+// 1024 / TOK threads, which keep kRowsAhead of them in flight, merged through LDS and a lane reduction.  The
+// log-partition and the log-prob are formed in 64 bits: what their rounding to 32 bits leaves off the log-prob
+// goes into the ratio, whose terms cancel inside a group.  Results go to the row's original position, and a candidate
+// row's loss term and gradient scalars are formed on the spot.  TOK: 64 reads whole 256-byte segments; a few
+// hundred tokens are a handful of workgroups that way (16 us at 600 tokens whatever the prefetch), so up to
+// kFewRows rows are taken 16 at a time.
+constexpr int kRowsNT = 1024, kRowsAhead = 8;
+constexpr int64_t kFewRows = 4096;
+template <int TOK>
+__global__ __launch_bounds__(kRowsNT) void k_fused_rows(
+    int tiles_v, int64_t T_pad, const int32_t* __restrict__ fidx, const int32_t* __restrict__ nf,
+    const float* __restrict__ part_m, const float* __restrict__ part_s, const float* __restrict__ part_sz,
+    const float* __restrict__ zy, float* __restrict__ logprob, float* __restrict__ entropy,
+    float* __restrict__ lse_out, FusedTerms q) {
+  constexpr int kStreams = kRowsNT / TOK;   // threads per row: 16 or 64
+  __shared__ RowStat xs[kStreams][TOK];
+  const int tid = threadIdx.x, stream = tid / TOK;
+  const int64_t j0 = int64_t(blockIdx.x) * TOK;   // j0 + TOK <= T_pad
+  const int n = nf[0];
+  const int n_cand = q.nact ? q.nact[0] : 0;
+  const int64_t mine = j0 + tid / kStreams;   // the row this thread finishes
+  const bool leader = tid % kStreams == 0;
+  if (q.nact && leader && mine >= n_cand) {   // padding position of the gradient operands
+    q.gc[mine] = 0.f;
+    q.lsec[mine] = 1e30f;   // exp(z - lsec) = 0 whatever z is
+    q.yc[mine] = -1;
+    q.ac[mine] = 0.f;
+    q.bc[mine] = 0.f;
+    q.scale[mine] = 0.f;
+  }
+  if (j0 >= n) return;   // uniform over the workgroup
+  RowStat st = stat_identity();
+  for (int tv = stream; tv < tiles_v; tv += kRowsAhead * kStreams) {
+    RowStat v[kRowsAhead];
+#pragma unroll
+    for (int u = 0; u < kRowsAhead; ++u) {
+      const int at = tv + u * kStreams;
+      const int64_t o = int64_t(at) * T_pad + j0 + tid % TOK;
+      v[u] = at < tiles_v ? RowStat{part_m[o], part_s[o], part_sz[o]} : stat_identity();
+    }
+#pragma unroll
+    for (int u = 0; u < kRowsAhead; ++u) st = stat_merge(st, v[u]);
+  }
+  xs[stream][tid % TOK] = st;
+  __syncthreads();
+  const RowStat r = stat_reduce<kStreams == kWave>(xs[tid % kStreams][tid / kStreams]);
+  if (!leader || mine >= n) return;
+  const int64_t t = fidx[mine];
+  const double lse = double(r.m) + log(double(r.s));
+  const double lp = double(zy[mine]) - lse;
+  const float lp32 = float(lp), lse32 = float(lse), ent = float(lse - double(r.sz) / double(r.s));
+  logprob[t] = lp32;
+  lse_out[t] = lse32;
+  if (entropy) entropy[t] = ent;
+  if (mine < n_cand) candidate_row(q, mine, t, lse32, lp32, float(lp - double(lp32)), ent);
+}
+
+// ------------------------------------------------------------------------------------------
+// backward: transposes
+// ------------------------------------------------------------------------------------------
 // Transposes (and optionally gathers) a row-major bf16 matrix into the K-slab layout the GEMM
 // tile reads: source row r becomes K index r, source column c becomes operand row c:
 //   out[(r / 64) * C_pad * 64 + c * 64 + r % 64] = in[src(r)][c]
@@ -714,7 +709,7 @@ __global__ __launch_bounds__(256) void k_gather_transpose_vec(
 // vocabulary or the candidate tokens are zero.
 // ENT: rows also carry the entropy-bonus term, dz = pi (ac z + bc) + gc onehot; otherwise ac = 0
 // and the scale is the per-token constant bc = -g.
-// The kernel is the recompute mode of the backward pass (see k_candidate_scalars): with force == 0 it
+// The kernel is the recompute mode of the backward pass (see FusedTerms): with force == 0 it
 // leaves at once unless the forward pass raised nact[2].
 template <bool ENT>
 __global__ __launch_bounds__(kGemmNT, 2) void k_fused_dz(
@@ -1007,22 +1002,26 @@ extern "C" aero_status aero_lmhead_logprob_fused(
   int32_t* pos = reinterpret_cast<int32_t*>(ws + p.off_pos);
   int32_t* nact = reinterpret_cast<int32_t*>(ws + p.off_nact);
   float* zy = reinterpret_cast<float*>(ws + p.off_zy);
-  float* lp_low = bwd ? reinterpret_cast<float*>(ws + p.off_lplow) : nullptr;
   uint16_t* hf = reinterpret_cast<uint16_t*>(ws + p.off_hc);   // rows with a target, candidates first
   uint16_t* dz = reinterpret_cast<uint16_t*>(ws + p.off_dz);
   uint16_t* dzT = reinterpret_cast<uint16_t*>(ws + p.off_dzT);
   const bool ent = bwd && entropy_coef != 0.f;
   // rows with an entropy term are not a multiple of exp(z - zy): their gradient is formed by recomputing z
   const bool stored = bwd && !ent;
-  float* ent_arr = entropy ? entropy : (ent ? reinterpret_cast<float*>(ws + p.off_ent) : nullptr);
+  FusedTerms terms{};
+  if (bwd)
+    terms = FusedTerms{targets, token_rollout, old_logprob, adv, weight_rollout, ref_logprob,
+                       LossHyper{eps_lo, eps_hi, grad_scale, entropy_coef, kl_coef}, nact, p.T_pad, p.VC, stored ? 0 : 1,
+                       reinterpret_cast<float*>(ws + p.off_term), reinterpret_cast<int32_t*>(ws + p.off_flag),
+                       reinterpret_cast<float*>(ws + p.off_gc), reinterpret_cast<float*>(ws + p.off_lsec),
+                       reinterpret_cast<int32_t*>(ws + p.off_yc), reinterpret_cast<float*>(ws + p.off_ac),
+                       reinterpret_cast<float*>(ws + p.off_bc), reinterpret_cast<float*>(ws + p.off_scale), dz, dzT};
   if (T > 0) {
     hipLaunchKernelGGL(k_compact_valid, dim3(1), dim3(1024), 0, s, targets, T, p.T_pad, V,
                        bwd ? token_rollout : nullptr, adv, weight_rollout, R, (ent || kl_coef != 0.f) ? 1 : 0, fidx, nf,
-                       bwd ? pos : nullptr, bwd ? nact : nullptr, logprob, ent_arr, lse, err_flag, tiles_h, grid_dh,
+                       bwd ? pos : nullptr, bwd ? nact : nullptr, logprob, entropy, lse, err_flag, tiles_h, grid_dh,
                        p.V_ld / kDK, rows_max);
-    hipLaunchKernelGGL(k_gather_rows, dim3(unsigned(p.T_pad / 4)), dim3(256), 0, s, Hp, H, fidx, p.T_pad, hf);
-    hipLaunchKernelGGL(k_target_logit, dim3(unsigned(p.T_pad / 4)), dim3(256), 0, s, Wp, hf, H, p.T_pad, fidx, nf,
-                       targets, zy);
+    hipLaunchKernelGGL(k_gather_rows, dim3(unsigned(p.T_pad / 4)), dim3(256), 0, s, Hp, Wp, H, fidx, targets, hf, zy);
     {
       const int n = p.tiles_v * tiles_t;
       if (stored)
@@ -1032,54 +1031,43 @@ extern "C" aero_status aero_lmhead_logprob_fused(
         hipLaunchKernelGGL(k_fused_stats<false>, dim3(unsigned(xcd_grid(n))), dim3(kGemmNT), kGemmLdsBytes, s, Wp, hf,
                            V, H, p.tiles_v, p.T_pad, nf, part_m, part_s, part_sz, zy, p.VC, nact, dz, dzT);
     }
-    hipLaunchKernelGGL(k_fused_combine, dim3(unsigned(p.T_pad / kCombineTokens)), dim3(kCombineWaves * kWave), 0, s,
-                       p.tiles_v, p.T_pad, fidx, nf, part_m, part_s, part_sz, zy, logprob, ent_arr, lse, lp_low);
+    if (p.T_pad <= kFewRows)
+      hipLaunchKernelGGL(k_fused_rows<16>, dim3(unsigned(p.T_pad / 16)), dim3(kRowsNT), 0, s, p.tiles_v, p.T_pad, fidx, nf,
+                         part_m, part_s, part_sz, zy, logprob, entropy, lse, terms);
+    else
+      hipLaunchKernelGGL(k_fused_rows<64>, dim3(unsigned(p.T_pad / 64)), dim3(kRowsNT), 0, s, p.tiles_v, p.T_pad, fidx, nf,
+                         part_m, part_s, part_sz, zy, logprob, entropy, lse, terms);
   }
   if (!bwd) return launch_status();
 
-  // ---- loss and g_t ----
-  float* g = reinterpret_cast<float*>(ws + p.off_g);
-  float* term = reinterpret_cast<float*>(ws + p.off_term);
-  int32_t* flag = reinterpret_cast<int32_t*>(ws + p.off_flag);
-  float* ea = ent ? reinterpret_cast<float*>(ws + p.off_ea) : nullptr;
-  float* eb = ent ? reinterpret_cast<float*>(ws + p.off_eb) : nullptr;
-  aero_status st = token_terms_from_logprob(T, V, targets, logprob, lp_low, lse, ent_arr, old_logprob, token_rollout, adv,
-                                            weight_rollout, R, eps_lo, eps_hi, grad_scale, entropy_coef, kl_coef,
-                                            ref_logprob, g, term, flag, ea, eb, loss, clip_frac, err_flag, s);
-  if (st != AERO_OK) return st;
-
-  // ---- per-candidate scalars and operand copies ----
-  float* gc = reinterpret_cast<float*>(ws + p.off_gc);
-  float* lsec = reinterpret_cast<float*>(ws + p.off_lsec);
-  int32_t* yc = reinterpret_cast<int32_t*>(ws + p.off_yc);
-  float* ac = reinterpret_cast<float*>(ws + p.off_ac);
-  float* bc = reinterpret_cast<float*>(ws + p.off_bc);
-  float* scale = reinterpret_cast<float*>(ws + p.off_scale);
+  // ---- loss, operand copies ----
   uint16_t* hTc = reinterpret_cast<uint16_t*>(ws + p.off_hTc);
   uint16_t* WT = reinterpret_cast<uint16_t*>(ws + p.off_WT);
   float* dh_acc = reinterpret_cast<float*>(ws + p.off_dhacc);
-  const int force = stored ? 0 : 1;
   if (T == 0) {   // no forward kernel ran: an empty candidate set for the kernels below
     hipLaunchKernelGGL(k_compact_valid, dim3(1), dim3(1024), 0, s, targets, T, p.T_pad, V, token_rollout, adv,
-                       weight_rollout, R, 0, fidx, nf, pos, nact, logprob, ent_arr, lse, err_flag, tiles_h, grid_dh, p.V_ld / kDK,
-                       rows_max);
+                       weight_rollout, R, 0, fidx, nf, pos, nact, logprob, entropy, lse, err_flag, tiles_h, grid_dh,
+                       p.V_ld / kDK, rows_max);
+    hipLaunchKernelGGL(k_fused_rows<16>, dim3(unsigned(p.T_pad / 16)), dim3(kRowsNT), 0, s, p.tiles_v, p.T_pad, fidx, nf,
+                       part_m, part_s, part_sz, zy, logprob, entropy, lse, terms);
   }
-  hipLaunchKernelGGL(k_candidate_scalars, dim3(unsigned(p.T_pad / 256)), dim3(256), 0, s, fidx, nact, g, ea, eb, lse,
-                     logprob, targets, p.T_pad, p.VC, force, gc, lsec, yc, ac, bc, scale, dz, dzT);
+  loss_reduce_launch(terms.term, terms.flag, nact, loss, clip_frac, s);
   if (T > 0) {   // recompute mode only (the kernel leaves at once otherwise)
     const int n = p.tiles_v * tiles_t;
     if (ent)
       hipLaunchKernelGGL(k_fused_dz<true>, dim3(unsigned(xcd_grid(n))), dim3(kGemmNT), kGemmLdsBytes, s, Wp, hf, V,
-                         H, p.tiles_v, p.T_pad, p.VC, force, nact, gc, lsec, yc, ac, bc, dz, dzT);
+                         H, p.tiles_v, p.T_pad, p.VC, terms.force_recompute, nact, terms.gc, terms.lsec, terms.yc, terms.ac,
+                         terms.bc, dz, dzT);
     else
       hipLaunchKernelGGL(k_fused_dz<false>, dim3(unsigned(xcd_grid(n))), dim3(kGemmNT), kGemmLdsBytes, s, Wp, hf, V,
-                         H, p.tiles_v, p.T_pad, p.VC, force, nact, gc, lsec, yc, ac, bc, dz, dzT);
+                         H, p.tiles_v, p.T_pad, p.VC, terms.force_recompute, nact, terms.gc, terms.lsec, terms.yc, terms.ac,
+                         terms.bc, dz, dzT);
   }
   // the candidates' hidden rows, each times its scale, transposed to hTc: K-slabs over the candidate positions
   const bool vec_tr = (H % 8 == 0) && (reinterpret_cast<uintptr_t>(Hp) % 16 == 0) && (reinterpret_cast<uintptr_t>(Wp) % 16 == 0);
   const auto transpose = vec_tr ? k_gather_transpose_vec : k_gather_transpose;
   hipLaunchKernelGGL(transpose, dim3(unsigned(p.T_pad / 64), unsigned(p.H_pad / 64)), dim3(256), 0, s, hf,
-                     int64_t(H), p.T_pad, H, p.H_pad, nullptr, p.T_pad, hTc, nullptr, int64_t(0), scale);
+                     int64_t(H), p.T_pad, H, p.H_pad, nullptr, p.T_pad, hTc, nullptr, int64_t(0), terms.scale);
   // weight transposed to WT, K-slabs over the vocabulary; rows V..V_ld of the source do not exist -> zeros
   if (!p.direct)
     hipLaunchKernelGGL(transpose, dim3(unsigned(p.V_ld / 64), unsigned(p.H_pad / 64)), dim3(256), 0, s, Wp,
@@ -1111,6 +1099,6 @@ extern "C" aero_status aero_lmhead_logprob_fused(
     }
   }
   if (T > 0)
-    hipLaunchKernelGGL(k_scatter_dh, dim3(unsigned(T)), dim3(256), 0, s, dh_acc, pos, nact, H, scale, reinterpret_cast<uint16_t*>(dhidden));
+    hipLaunchKernelGGL(k_scatter_dh, dim3(unsigned(T)), dim3(256), 0, s, dh_acc, pos, nact, H, terms.scale, reinterpret_cast<uint16_t*>(dhidden));
   return launch_status();
 }
