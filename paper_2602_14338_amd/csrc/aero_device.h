@@ -163,7 +163,10 @@ __device__ __forceinline__ RowLogProb row_logprob(const RowStat& st, float zy) {
   const float d = zy - st.m;            // an exact difference of stored values, unless they are 32-bit
   const float lp = d - l;
   const float back = d - lp;            // two-sum: (d - l) - lp, exactly
-  return RowLogProb{st.m + (l + fix), lp, ((d - (lp + back)) + (back - l)) - fix};
+  const float sum = st.m + l;           // the same for m + l, whose remainder and fix are added before rounding
+  const float part = sum - st.m;
+  const float rest = (st.m - (sum - part)) + (l - part);
+  return RowLogProb{sum + (rest + fix), lp, ((d - (lp + back)) + (back - l)) - fix};
 }
 
 // Loss term, its derivative with respect to the log-prob and the clip decision of one token whose rollout has
