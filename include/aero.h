@@ -136,8 +136,8 @@ aero_status aero_group_advantage(
  *   entropy[t] = lse[t] - sum_j softmax(z[t])_j z[t,j]          (natural log, temperature 1)
  *
  * logits   [T, ld] row-major, dtype AERO_BF16, AERO_F16, AERO_F8E4M3 or AERO_F32, ld >= V; columns >= V are never
- *          read.  Any alignment works; rows whose base and ld*sizeof(elt) are multiples of
- *          16 bytes take the 128-bit load path.
+ *          read.  Any alignment works; rows are read as 16-byte vectors between their ragged ends unless the base
+ *          is not even a multiple of the element size.
  * targets  i32[T] sampled-token ids; row_active u8[T] or NULL.
  * Outputs  logprob[T], lse[T] f32; entropy[T] f32 or NULL.  Ignored rows get 0.
  * Accumulation is fp32.  T = 0 is valid.  1 <= V <= 2^24.
@@ -172,8 +172,8 @@ aero_status aero_logprob_fwd(
  *
  * logits / dlogits  [T, ld], same dtype and ld; dlogits may alias logits (in place).
  * lse      f32[T] from aero_logprob_fwd, or NULL: then the statistics are computed here.  With
- *          lse == NULL, bf16 logits, 16-byte aligned rows and 8192 <= V <= 163840 the whole call
- *          is one pass over HBM (the row is held in registers: 4 bytes of traffic per logit);
+ *          lse == NULL and rows of at most 320 KB (163840 2-byte logits, 81920 fp32, 327680 8-bit ones) the whole call
+ *          is one pass over HBM (the row is held on chip: read once, written once);
  *          otherwise a forward pass into the workspace precedes the gradient pass.
  * entropy  f32[T] from aero_logprob_fwd; read only when lse != NULL and entropy_coef != 0
  *          (AERO_ERR_NULL if missing then), may be NULL otherwise.
