@@ -42,6 +42,20 @@ __device__ __forceinline__ int acc_col(int wn, int nb, int lane) { return wn * 6
 __device__ __forceinline__ int acc_row_swapped(int wm, int mb, int lane) { return wm * 128 + mb * 16 + (lane & 15); }
 __device__ __forceinline__ int acc_col_swapped(int wn, int nb, int lane) { return wn * 64 + nb * 16 + 4 * (lane >> 4); }
 
+// Which part of the tile a wave owns.  Waves w and w + 4 run on the same SIMD; the two that share one are the halves
+// of the dimension that may be ragged, so that skipping waves whose rows or columns are all padding halves the work
+// of every SIMD: rows of A (wave_pos<false>) or columns of B, in steps of two blocks of 64 (wave_pos<true>).
+// Whole calls at H = 1536, V = 151936: 600 tokens (a third tile with 88) 905 -> 873 us, 1100 and 16384 tokens even;
+// 1400 tokens at H = 3584, V = 32000 826 -> 815; 300 tokens at H = 896, V = 8000 102.2 -> 103.7.
+struct WavePos {
+  int wm, wn;
+  bool active;   // false: all of the wave's rows (columns) are padding, its accumulators stay zero
+};
+template <bool RAGGED_COLS> __device__ __forceinline__ WavePos wave_pos() {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  return RAGGED_COLS ? WavePos{wave & 1, wave >> 1, true} : WavePos{wave >> 2, wave & 3, true};
+}
+
 typedef f32x4_t Acc[kMB][kNB];
 
 __device__ __forceinline__ void acc_zero(Acc& acc) {
@@ -183,9 +197,9 @@ __device__ __forceinline__ void slice_mma(const uint16_t* As, const uint16_t* Bs
 template <bool SWAP>
 __device__ __forceinline__ void gemm_tile(const uint16_t* __restrict__ A, int64_t lda, int M,
                                           const uint16_t* __restrict__ B, int64_t ldb, int N, int K,
-                                          int m0, int n0, uint16_t* smem, Acc& acc) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wm = wave >> 2, wn = wave & 3;
+                                          int m0, int n0, const WavePos& pos, uint16_t* smem, Acc& acc) {
+  const int lane = threadIdx.x & 63;
+  const int wm = pos.wm, wn = pos.wn;
   acc_zero(acc);
   const int nk = (K + kBK - 1) / kBK;
   if (nk == 0) return;
@@ -327,12 +341,12 @@ __device__ __forceinline__ void frags_load_bt(Frags& f, const uint16_t* lds, int
 // WARM: L2 warm-up two slices ahead (see below); a few per cent on the contractions whose
 // operands come from large read-only arrays, a loss on the split-K dhidden contraction.
 // BT: operand B is [K][rows] (B.base, B.ld, B.bytes; B.kstep is not looked at).  AF: operand A is in K-slabs in
-// fragment order (m0 a multiple of 16).
-template <bool WARM, bool SWAP, bool BT = false, bool AF = false>
+// fragment order (m0 a multiple of 16).  SKIP: waves with pos.active == false only move operands.
+template <bool WARM, bool SWAP, bool BT = false, bool AF = false, bool SKIP = false>
 __device__ __forceinline__ void gemm_tile_dma(const DmaOperand& A, const DmaOperand& B, int K, int m0, int n0,
-                                              uint16_t* smem, Acc& acc) {
+                                              const WavePos& pos, uint16_t* smem, Acc& acc) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wm = wave >> 2, wn = wave & 3;
+  const int wm = pos.wm, wn = pos.wn;
   acc_zero(acc);
   const int nk = K / kDK;
   if (nk == 0) return;
@@ -370,6 +384,19 @@ __device__ __forceinline__ void gemm_tile_dma(const DmaOperand& A, const DmaOper
   const uint32_t warm_off = uint32_t(int64_t(warm_row) * (warm_a ? A.ld : B.ld) * 2) + (warm_a ? 0u : uint32_t(lane >> 5) * 64u);
   const uint32_t warm_kstep = uint32_t((warm_a ? A.kstep : B.kstep) * 2);
   uint16_t* const warm_sink = smem + kWarmSinkOff / 2 + wave * 128;
+  if constexpr (SKIP) {
+    if (!pos.active) {   // uniform over the wave: its part of the transfers, the same barriers, no arithmetic
+      for (int kt = 0; kt < nk; ++kt) {
+        __builtin_amdgcn_s_waitcnt(0x0070);   // vmcnt(0) lgkmcnt(0)
+        AERO_CFENCE();
+        __builtin_amdgcn_s_barrier();
+        AERO_CFENCE();
+        if (kt + 1 < nk) dma_issue(ra, rb, la, lb, kt + 1, smem + ((kt + 1) & 1) * kDStageElems, wave);
+      }
+      __syncthreads();
+      return;
+    }
+  }
   // One iteration = one 64-wide slice = two 32-wide K steps of two halves, 16 MFMAs per wave each.
   // The order is pinned with scheduling barriers: the first step's fragments are read up front, the
   // next slice is requested only after the first MFMA group (issuing the 8 loads right after the
@@ -442,12 +469,13 @@ __device__ __forceinline__ void gemm_tile_dma(const DmaOperand& A, const DmaOper
 // Picks the fast loop when its preconditions hold (uniform over the launch).
 __device__ __forceinline__ void gemm_tile_auto(const uint16_t* __restrict__ A, int64_t lda, int M,
                                                const uint16_t* __restrict__ B, int64_t ldb, int N, int K,
-                                               int m0, int n0, uint16_t* smem, Acc& acc) {
+                                               int m0, int n0, const WavePos& pos, uint16_t* smem, Acc& acc) {
   const bool fast = (K % kDK == 0) && (lda % 8 == 0) && (ldb % 8 == 0) &&
                     (reinterpret_cast<uintptr_t>(A) % 16 == 0) && (reinterpret_cast<uintptr_t>(B) % 16 == 0) &&
                     ((int64_t(M) - 1) * lda + K) < (int64_t(1) << 31) && ((int64_t(N) - 1) * ldb + K) < (int64_t(1) << 31);
-  if (fast) gemm_tile_dma<true, false>(operand_row_major(A, lda, M, K), operand_row_major(B, ldb, N, K), K, m0, n0, smem, acc);
-  else gemm_tile<false>(A, lda, M, B, ldb, N, K, m0, n0, smem, acc);
+  if (fast) gemm_tile_dma<true, false, false, false, true>(operand_row_major(A, lda, M, K), operand_row_major(B, ldb, N, K), K, m0,
+                                                           n0, pos, smem, acc);
+  else gemm_tile<false>(A, lda, M, B, ldb, N, K, m0, n0, pos, smem, acc);
 }
 
 }  // namespace aero

@@ -292,10 +292,10 @@ __device__ __forceinline__ uint32_t xor4_lane(uint32_t v) {
 // instruction stores one 1 KB block, so nothing is staged in LDS and no wave waits for another.  (Staged through LDS in
 // both orientations, with four barriers: k_fused_stats 6.98 ms with 16384 tokens at H = 1536, 6.81 this way; whole
 // calls 15.24 / 15.06 ms, with 600 tokens 1045 / 1020 us.)
-__device__ __forceinline__ void store_tile_both_layouts(const uint32_t (&pk)[kNB][kMB][2], int m0, int n0, int64_t T_pad,
-                                                        int VC, uint16_t* __restrict__ dz, uint16_t* __restrict__ dzT) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wm = wave >> 2, wn = wave & 3;
+__device__ __forceinline__ void store_tile_both_layouts(const uint32_t (&pk)[kNB][kMB][2], const WavePos& wp, int m0, int n0,
+                                                        int64_t T_pad, int VC, uint16_t* __restrict__ dz, uint16_t* __restrict__ dzT) {
+  const int lane = threadIdx.x & 63;
+  const int wm = wp.wm, wn = wp.wn;
   const int group = lane >> 4;
   // ---- tokens x vocabulary: the odd 16-lane rows of one block change places with the even ones of the next; lane
   // group 0 then holds vocabulary 0..7 of its token, group 2 8..15, group 1 16..23, group 3 24..31 ----
@@ -401,10 +401,12 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_fused_stats(
   if (!tile_of_block(tiles_v, tiles_t_act, 0, tiles_v * tiles_t_act, tv, tt)) return;
   const int m0 = tv * kTile, n0 = tt * kTile;
   Acc acc;
-  gemm_tile_auto(W, H, V, Hf, H, int(T_pad), H, m0, n0, smem, acc);
+  WavePos wp = wave_pos<true>();
+  wp.active = n0 + wp.wn * 64 < nf[0];
+  gemm_tile_auto(W, H, V, Hf, H, int(T_pad), H, m0, n0, wp, smem, acc);
 
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wm = wave >> 2, wn = wave & 3;
+  const int lane = threadIdx.x & 63;
+  const int wm = wp.wm, wn = wp.wn;
   const bool full = m0 + kTile <= V;
   const int n_cand = STORE ? nf[2] : 0;
   const bool store = STORE && n0 < n_cand;   // uniform over the workgroup
@@ -486,7 +488,7 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_fused_stats(
   if constexpr (STORE) {
     if (store) {
       if (__any(wide) && lane == 0) atomicOr(nact + 2, 1);
-      store_tile_both_layouts(pk, m0, n0, T_pad, VC, dz, dzT);
+      store_tile_both_layouts(pk, wp, m0, n0, T_pad, VC, dz, dzT);
     }
   }
 }
@@ -726,10 +728,12 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_fused_dz(
   if (!tile_of_block(tiles_v, tiles_t_act, 0, tiles_v * tiles_t_act, tv, tt)) return;
   const int m0 = tv * kTile, n0 = tt * kTile;
   Acc acc;
-  gemm_tile_auto(W, H, V, Hc, H, int(T_pad), H, m0, n0, smem, acc);
+  WavePos wp = wave_pos<true>();
+  wp.active = n0 + wp.wn * 64 < nact[0];
+  gemm_tile_auto(W, H, V, Hc, H, int(T_pad), H, m0, n0, wp, smem, acc);
 
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wm = wave >> 2, wn = wave & 3;
+  const int lane = threadIdx.x & 63;
+  const int wm = wp.wm, wn = wp.wn;
   // dz for this lane's columns, packed to bf16 pairs: pk[nb][mb] = four consecutive rows
   uint32_t pk[kNB][kMB][2];
 #pragma unroll
@@ -762,7 +766,7 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_fused_dz(
       pk[nb][mb][1] = pack_bf16x2(d[2], d[3]);
     }
   }
-  store_tile_both_layouts(pk, m0, n0, T_pad, VC, dz, dzT);
+  store_tile_both_layouts(pk, wp, m0, n0, T_pad, VC, dz, dzT);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -795,17 +799,20 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_gemm_dh(
   const int k_begin = min(vK, split * per * kDK);
   const int k_len = max(0, min(vK, (split + 1) * per * kDK) - k_begin);
   Acc acc;
+  WavePos wp = wave_pos<false>();
+  wp.active = m0 + wp.wm * 128 < nact[0];
   const DmaOperand x = operand_slabs(dz + int64_t(k_begin / kDK) * T_pad * kDK, T_pad, k_len);
   if constexpr (DIRECT) {
     // weight rows past the vocabulary (the split may start there) lie past the operand's bytes and read as zeros
     const DmaOperand w{W + int64_t(min(k_begin, V)) * H, H, 0, int64_t(max(V - k_begin, 0)) * H * 2};
-    gemm_tile_dma<false, true, true, true>(x, w, k_len, m0, n0, smem, acc);
+    gemm_tile_dma<false, true, true, true, true>(x, w, k_len, m0, n0, wp, smem, acc);
   } else {
-    gemm_tile_dma<false, true, false, true>(x, operand_slabs(WT + int64_t(k_begin / kDK) * H_pad * kDK, H_pad, k_len), k_len, m0, n0,
-                               smem, acc);
+    gemm_tile_dma<false, true, false, true, true>(x, operand_slabs(WT + int64_t(k_begin / kDK) * H_pad * kDK, H_pad, k_len),
+                                                  k_len, m0, n0, wp, smem, acc);
   }
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wm = wave >> 2, wn = wave & 3;
+  if (!wp.active) return;   // padding rows of the partials are not read
+  const int lane = threadIdx.x & 63;
+  const int wm = wp.wm, wn = wp.wn;
   float* out = dh_part + int64_t(split) * n_pad * H;
 #pragma unroll
   for (int mb = 0; mb < kMB; ++mb) {
@@ -834,10 +841,11 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_gemm_dw(
   // the contraction ends with the slice of the last candidate, not with its tile: the positions behind it are zeros
   // (whole calls at H = 1536, V = 151936: 600 tokens 949 -> 905 us, 1100 tokens 1376 -> 1357, 16384 tokens -0.4 %)
   const int K = (nact[0] + kDK - 1) / kDK * kDK;
+  const WavePos wp = wave_pos<false>();
   gemm_tile_dma<true, true, false, true>(operand_slabs(dzT_chunk, VC, K), operand_slabs(hTc, H_pad, K), K, m0 % VC, n0,
-                                         smem, acc);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wm = wave >> 2, wn = wave & 3;
+                                         wp, smem, acc);
+  const int lane = threadIdx.x & 63;
+  const int wm = wp.wm, wn = wp.wn;
   // accumulate (uniform): the tile is added to what the caller's buffer holds (gradient accumulation over
   // micro-batches).  vec (uniform): that buffer is 16-byte aligned, as every allocation is.  Plain stores: an
   // instruction writes 64 bytes per row and L2 joins the two halves of a line; non-temporal ones leave it in
