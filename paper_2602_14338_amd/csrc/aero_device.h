@@ -136,8 +136,8 @@ template <bool WAVE> __device__ __forceinline__ RowStat stat_reduce(RowStat a) {
 }
 
 // Workgroup-wide merge; every thread gets the result.  NT = threads per workgroup (at most 1024).
-// (Merging pairs of states through LDS shuffles, then the waves' states one after the other in every
-// thread, cost 1.5 us of the 27 us a row of 151936 bf16 logits takes.)
+// (Against merging pairs of states through LDS shuffles and the waves' states one after the other in every thread:
+// 0.4 % of the one-pass loss call on 151936 bf16 logits a row.)
 template <int NT>
 __device__ __forceinline__ RowStat stat_block_reduce(RowStat a, RowStat* lds /*[NT/64]*/) {
   a = stat_reduce<true>(a);
