@@ -513,6 +513,7 @@ static void launch_rows(const RowArgs& r, hipStream_t s) {
 template <int DT, bool ENT>
 static aero_status single_pass_launch_t(const RowArgs& r, int32_t* row_counter, int32_t* row_order, hipStream_t s) {
   // the smallest workgroup whose threads hold the row in 8 vectors each, so that a CU works on several rows
+  // (against 4 vectors each, 8192 bf16 rows: V = 3000 25.0 / 29.6 us, 6000 even, 12000 78.7 / 76.7, 24000 140 / 161, 50000 even)
   const int nvec = r.V / Storage<DT>::kPerVec;
   if (nvec <= 8 * 64) launch_rows<DT, 64, ENT>(r, s);
   else if (nvec <= 8 * 256) launch_rows<DT, 256, ENT>(r, s);

@@ -109,15 +109,15 @@ def test_group_advantage_random_structures(gh, seed):
     check_groups(gh, (rewards, lengths, off, keys), params, keys=None)
 
 
-@pytest.mark.parametrize("Q,lo,hi", [(33, 1, 8), (257, 60, 68), (1500, 20, 60), (2600, 16, 40)])
+@pytest.mark.parametrize("Q,lo,hi", [(33, 1, 8), (121, 60, 68), (401, 8, 30), (257, 60, 68), (1500, 20, 60)])
 def test_group_advantage_placement_forms(gh, Q, lo, hi):
-    """Kept rollouts placed from the keep mask (up to 65536 rollouts) and by a scan of the counts (2600 groups: more),
+    """Kept rollouts placed from the keep mask (up to 8192 rollouts) and by a scan of the counts (more),
     groups on both sides of the 64 that a wave holds, the number of groups no multiple of a workgroup's four."""
     rng = np.random.default_rng(Q)
     sizes = rng.integers(lo, hi + 1, size=Q)
     off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
     R = int(off[-1])
-    assert (R > 65536) == (Q == 2600)
+    assert (R > 8192) == (Q in (257, 1500))
     rewards = (rng.random(R) < np.repeat(rng.beta(0.5, 0.5, size=Q), sizes)).astype(np.float32)
     check_groups(gh, (rewards, rng.integers(1, 3000, size=R).astype(np.int32), off,
                       rng.integers(0, 4, size=R).astype(np.uint32)), dict(reject_enable=1, posterior_mode=1, k_ratio=2))
