@@ -6,13 +6,15 @@
 // in fp64 from those counts and rounded once to fp32.  The call is latency bound, so what counts is
 // launches and dependent loads:
 //   at most 32 groups (a micro-batch)   k_group_small: everything in one workgroup, one launch
-//   up to 8192 rollouts (a step)        k_group (c, category, keep mask, advantages, weights), then k_place:
-//                                       every workgroup counts the kept rollouts in front of its groups
-//                                       straight from the keep mask (a byte each), so no scan stands between
+//   up to 8192 groups (a step)          k_group (c, category, keep mask, advantages, weights), then k_place:
+//                                       every workgroup adds up the kept counts in front of its groups
+//                                       itself, so no scan stands between
 //   more                                k_group, k_scan (exclusive scan of the kept counts, one
-//                                       workgroup) and k_compact: the mask would be read too often.
-//                                       k_place against these two: 12.3 / 14.5 us for 1024 rollouts in 64 groups,
-//                                       12.4 / 14.6 for 5120 in 256, 28 / 17 for 60000 in 1500
+//                                       workgroup) and k_compact: the counts would be read too often.
+// Whole calls, k_place against the last two kernels: 64 groups (1024 rollouts) 8.8 / 11.2 us, 400 (7831) 9.0 / 11.4,
+// 410 (8296) 8.9 / 11.3, 600 (12108) 9.0 / 11.3, 1500 (24384) 9.3 / 11.6, 3000 (60325) 10.2 / 12.9, 4000 (80187)
+// 11.0 / 14.5, 8000 (159965) 18.1 / 24.1.  (Counting the bytes of the keep mask instead, up to 8192 rollouts,
+// takes as long, and reads bytes that nobody wrote where offsets start above 0.)
 // 256 groups of 8 to 32 rollouts took 15.8 us with the third form and a rank search that loaded rewards and
 // keys one at a time; a group of at most 64 rollouts now stays in the lanes of its wave.  (One workgroup
 // for 64 groups serialises them: 18.7 us against 13.5.)
@@ -23,6 +25,11 @@ namespace aero {
 __device__ __forceinline__ int wave_sum_i(int v) {
 #pragma unroll
   for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, kWave);
+  return v;
+}
+__device__ __forceinline__ int wave_max_i(int v) {
+#pragma unroll
+  for (int off = kWave / 2; off > 0; off >>= 1) v = max(v, __shfl_xor(v, off, kWave));
   return v;
 }
 __device__ __forceinline__ double wave_sum_d(double v) {
@@ -47,6 +54,7 @@ __device__ __forceinline__ bool before(uint32_t ka, int ia, uint32_t kb, int ib)
 }
 
 constexpr int kGroupsPerBlock = 4;   // 4 waves of 64
+constexpr int kPlaceQ = 1 << 13;     // k_place up to this many groups (see the top)
 
 // One group, one wave: everything but the position of its kept rollouts in kept_index.  Returns the
 // number of kept rollouts (the same value in every lane).
@@ -182,7 +190,8 @@ __device__ __forceinline__ int group_body(
   return nk;
 }
 
-// Kept rollout indices of one group, ascending, written from position `out` on (one wave).
+// Kept rollout indices of one group, ascending, written from position `out` on (one wave).  Groups that overlap can
+// keep more than R rollouts between them: what does not fit kept_index is dropped.
 __device__ __forceinline__ void compact_body(int q, int lane, const int32_t* __restrict__ group_offsets,
                                              const uint8_t* __restrict__ keep_mask, int out, int R,
                                              int32_t* __restrict__ kept_index) {
@@ -193,7 +202,8 @@ __device__ __forceinline__ void compact_body(int q, int lane, const int32_t* __r
     const int i = base + lane;
     const bool k = i < e && keep_mask[i] != 0;
     const uint64_t bal = __ballot(k);
-    if (k) kept_index[out + __popcll(bal & ((uint64_t(1) << lane) - 1))] = i;
+    const int at = out + __popcll(bal & ((uint64_t(1) << lane) - 1));
+    if (k && at < R) kept_index[at] = i;
     out += __popcll(bal);
   }
 }
@@ -202,14 +212,14 @@ __global__ __launch_bounds__(kGroupsPerBlock* kWave) void k_group(
     const float* __restrict__ rewards, const int32_t* __restrict__ lengths,
     const int32_t* __restrict__ group_offsets, const uint32_t* __restrict__ keys, int Q, int R,
     aero_adv_params p, float* __restrict__ adv, float* __restrict__ weight, uint8_t* __restrict__ keep_mask,
-    int32_t* __restrict__ kept_offsets, uint8_t* __restrict__ zero_var, uint8_t* __restrict__ category,
+    int32_t* __restrict__ kept_offsets, int count_mask, uint8_t* __restrict__ zero_var, uint8_t* __restrict__ category,
     int32_t* __restrict__ err_flag) {
   const int lane = threadIdx.x % kWave;
   const int q = blockIdx.x * kGroupsPerBlock + threadIdx.x / kWave;
   if (q >= Q) return;   // whole wave leaves together
   const int nk = group_body(q, lane, rewards, lengths, group_offsets, keys, Q, R, p, adv, weight, keep_mask, zero_var,
                             category, err_flag);
-  if (lane == 0) kept_offsets[q + 1] = nk;
+  if (lane == 0) kept_offsets[q + 1] = nk ^ count_mask;   // count_mask: 0, or -1 for k_place
 }
 
 // Exclusive scan of counts held in kept_offsets[1..Q] (in place), kept_offsets[0] = 0.
@@ -245,45 +255,71 @@ __global__ __launch_bounds__(kGroupsPerBlock* kWave) void k_compact(
   compact_body(q, lane, group_offsets, keep_mask, kept_offsets[q], R, kept_index);
 }
 
-// kept_offsets and kept_index from the keep mask alone: a workgroup counts the kept rollouts in front of its four
-// groups, each wave those of its own group.
-__global__ __launch_bounds__(kGroupsPerBlock* kWave) void k_place(
+// kept_offsets and kept_index from the counts that k_group left in kept_offsets, without a scan in between: a
+// workgroup adds up the counts in front of its four groups by itself.  Workgroups that are through replace counts by
+// offsets meanwhile, so counts are stored as ~count: a negative entry is a count, any other the offset behind that
+// group, and an offset stands for everything in front of it.  Whatever mixture a workgroup sees, the last offset
+// plus the counts behind it is the sum it is after.
+constexpr int kPlaceNT = kGroupsPerBlock * kWave;
+// LOADS: counts per thread, all in flight at once; Q <= LOADS * kPlaceNT.
+template <int LOADS>
+__global__ __launch_bounds__(kPlaceNT) void k_place(
     const int32_t* __restrict__ group_offsets, const uint8_t* __restrict__ keep_mask, int Q, int R,
-    int32_t* __restrict__ kept_offsets, int32_t* __restrict__ kept_index) {
-  __shared__ int front[kGroupsPerBlock], own[kGroupsPerBlock];
+    int32_t* kept_offsets, int32_t* __restrict__ kept_index) {
+  __shared__ int last[kGroupsPerBlock], front[kGroupsPerBlock], own[kGroupsPerBlock];
   const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
   const int q0 = blockIdx.x * kGroupsPerBlock, q = q0 + wave;
-  const int end = max(0, min(group_offsets[q0], R));   // bytes of the mask in front of the first group
+  auto entry = [&](int p) { return __hip_atomic_load(kept_offsets + p + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); };
+  int v[LOADS];
+#pragma unroll
+  for (int u = 0; u < LOADS; ++u) {
+    const int p = u * kPlaceNT + tid;
+    v[u] = -1;   // a count of 0
+    if (u * kPlaceNT < q0 && p < q0) v[u] = entry(p);
+  }
+  const int mine = q < Q ? ~entry(q) : 0;   // nobody else replaces it
   int n = 0;
-  if (reinterpret_cast<uintptr_t>(keep_mask) % 4 == 0) {   // a byte is 0 or 1: set bits of whole words
-    const uint32_t* words = reinterpret_cast<const uint32_t*>(keep_mask);
-    for (int i = tid; i < end / 4; i += kGroupsPerBlock * kWave) n += __popc(words[i]);
-    const int i = end / 4 * 4 + tid;
-    if (i < end) n += keep_mask[i];
-  } else {
-    for (int i = tid; i < end; i += kGroupsPerBlock * kWave) n += keep_mask[i];
+  bool offset_seen = false;
+#pragma unroll
+  for (int u = 0; u < LOADS; ++u) {
+    n += ~v[u];
+    offset_seen |= v[u] >= 0;
   }
   n = wave_sum_i(n);
-  int mine = 0;
-  if (q < Q) {
-    int b = group_offsets[q], e = group_offsets[q + 1];
-    b = max(0, min(b, R));
-    e = max(b, min(e, R));
-    for (int i = b + lane; i < e; i += kWave) mine += keep_mask[i];
-    mine = wave_sum_i(mine);
-  }
+  const int seen = __any(offset_seen);
   if (lane == 0) {
     front[wave] = n;
+    last[wave] = seen;
     own[wave] = mine;
   }
   __syncthreads();
+  static_assert(kGroupsPerBlock == 4, "four flags");
+  if (last[0] | last[1] | last[2] | last[3]) {   // uniform: counts from the last offset on
+    int at = -1;
+#pragma unroll
+    for (int u = 0; u < LOADS; ++u)
+      if (v[u] >= 0) at = u * kPlaceNT + tid;
+    at = wave_max_i(at);
+    __syncthreads();   // the flags have been read
+    if (lane == 0) last[wave] = at;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kGroupsPerBlock; ++w) at = max(at, last[w]);
+    n = 0;
+#pragma unroll
+    for (int u = 0; u < LOADS; ++u)
+      if (u * kPlaceNT + tid >= at) n += v[u] < 0 ? ~v[u] : v[u];   // at itself: the offset
+    n = wave_sum_i(n);
+    if (lane == 0) front[wave] = n;
+    __syncthreads();
+  }
   int out = 0;
 #pragma unroll
   for (int w = 0; w < kGroupsPerBlock; ++w) out += front[w] + (w < wave ? own[w] : 0);
   if (q >= Q) return;
   if (lane == 0) {
     if (q == 0) kept_offsets[0] = 0;
-    kept_offsets[q + 1] = out + mine;
+    __hip_atomic_store(kept_offsets + q + 1, out + mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
   }
   compact_body(q, lane, group_offsets, keep_mask, out, R, kept_index);
 }
@@ -291,7 +327,6 @@ __global__ __launch_bounds__(kGroupsPerBlock* kWave) void k_place(
 // The three stages in one workgroup of 16 waves, for Q <= kSmallQ groups: wave w takes groups w and w + 16;
 // the kept counts and their scan stay in LDS; every wave then places the kept indices of the groups it
 // processed (it reads back the keep mask its own lanes wrote).
-constexpr int kPlaceR = 1 << 13;
 constexpr int kSmallQ = 32, kSmallR = 1 << 16, kSmallNT = 1024;
 __global__ __launch_bounds__(kSmallNT) void k_group_small(
     const float* __restrict__ rewards, const int32_t* __restrict__ lengths,
@@ -354,12 +389,15 @@ extern "C" aero_status aero_group_advantage(
     return launch_status();
   }
   const unsigned blocks = unsigned((Q + kGroupsPerBlock - 1) / kGroupsPerBlock);
+  const bool place = Q > 0 && Q <= kPlaceQ;
   if (Q > 0)
     hipLaunchKernelGGL(k_group, dim3(blocks), dim3(kGroupsPerBlock * kWave), 0, s, rewards, lengths, group_offsets,
-                       keep_priority, Q, R, *p, adv, weight, keep_mask, kept_offsets, group_zero_var,
+                       keep_priority, Q, R, *p, adv, weight, keep_mask, kept_offsets, place ? -1 : 0, group_zero_var,
                        group_category, err_flag);
-  if (Q > 0 && R <= kPlaceR) {
-    hipLaunchKernelGGL(k_place, dim3(blocks), dim3(kGroupsPerBlock * kWave), 0, s, group_offsets, keep_mask, Q, R,
+  if (place) {
+    // sixteen loads do for 4096 groups; thirty-two everywhere cost 0.5 us
+    const auto kernel = Q <= 16 * kPlaceNT ? k_place<16> : k_place<kPlaceQ / kPlaceNT>;
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kGroupsPerBlock * kWave), 0, s, group_offsets, keep_mask, Q, R,
                        kept_offsets, kept_index);
     return launch_status();
   }

@@ -111,8 +111,8 @@ def test_group_advantage_random_structures(gh, seed):
 
 @pytest.mark.parametrize("Q,lo,hi", [(33, 1, 8), (121, 60, 68), (401, 8, 30), (257, 60, 68), (1500, 20, 60)])
 def test_group_advantage_placement_forms(gh, Q, lo, hi):
-    """Kept rollouts placed from the keep mask (up to 8192 rollouts) and by a scan of the counts (more),
-    groups on both sides of the 64 that a wave holds, the number of groups no multiple of a workgroup's four."""
+    """Kept rollouts placed by every workgroup for itself, around and above 8192 rollouts, groups on both sides of the
+    64 that a wave holds, the number of groups no multiple of a workgroup's four."""
     rng = np.random.default_rng(Q)
     sizes = rng.integers(lo, hi + 1, size=Q)
     off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
@@ -121,6 +121,57 @@ def test_group_advantage_placement_forms(gh, Q, lo, hi):
     rewards = (rng.random(R) < np.repeat(rng.beta(0.5, 0.5, size=Q), sizes)).astype(np.float32)
     check_groups(gh, (rewards, rng.integers(1, 3000, size=R).astype(np.int32), off,
                       rng.integers(0, 4, size=R).astype(np.uint32)), dict(reject_enable=1, posterior_mode=1, k_ratio=2))
+
+
+@pytest.mark.parametrize("mask_off", [0, 1, 2, 3])
+@pytest.mark.parametrize("Q,lo,hi", [(9, 1, 40), (33, 1, 8), (402, 8, 30), (4095, 0, 3), (4097, 0, 3), (8191, 0, 3),
+                                     (8195, 0, 3)])
+def test_group_advantage_rollouts_outside_the_groups(gh, Q, lo, hi, mask_off):
+    """Offsets that start above 0 (all placement forms: one workgroup, every workgroup for itself up to 8192 groups, by a
+    scan): the rollouts in front stay unwritten whatever they hold, everything else is as if they were not there, no
+    index leaves [0, R).  The same with an empty group in front whose range lies behind the others (8192 groups, and
+    8196).  The mask also starts off the 4-byte grid."""
+    rng = np.random.default_rng(10 * Q + mask_off)
+    sizes = rng.integers(lo, hi + 1, size=Q)
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    n = int(off[-1])
+    rewards = (rng.random(n) < np.repeat(rng.beta(0.5, 0.5, size=Q), sizes)).astype(np.float32)
+    lengths = rng.integers(1, 3000, size=n).astype(np.int32)
+    keys = rng.integers(0, 4, size=n).astype(np.uint32)
+    params = dict(reject_enable=1, posterior_mode=1, k_ratio=2)
+
+    def run(rewards, lengths, off, keys):
+        nQ, R = len(off) - 1, len(rewards)
+        mask = torch.full((R + 8,), 0xFF, dtype=torch.uint8, device=gh.DEV)
+        idx = torch.full((R + 64,), -5, dtype=torch.int32, device=gh.DEV)
+        adv, weight = torch.full((R,), 7.0, device=gh.DEV), torch.full((R,), 7.0, device=gh.DEV)
+        ko = torch.full((nQ + 1,), -5, dtype=torch.int32, device=gh.DEV)
+        zv, cat = (torch.full((nQ,), 9, dtype=torch.uint8, device=gh.DEV) for _ in range(2))
+        gh.aero.aero_group_advantage(gh.dev(rewards), gh.dev(lengths), gh.dev(off), gh.dev(keys.view(np.int32)), nQ, R,
+                                     gh.aero.AdvParams(**params), adv, weight, mask[mask_off:mask_off + R], idx[:R], ko, zv, cat)
+        m = mask.cpu().numpy()
+        assert (m[:mask_off] == 0xFF).all() and (m[mask_off + R:] == 0xFF).all() and (idx[R:] == -5).all()
+        return dict(adv=adv.cpu().numpy(), weight=weight.cpu().numpy(), keep_mask=m[mask_off:mask_off + R],
+                    kept_index=idx[:R].cpu().numpy(), kept_offsets=ko.cpu().numpy(), zero_var=zv.cpu().numpy(),
+                    category=cat.cpu().numpy())
+
+    ref = orc.group_advantage(rewards, lengths, off, keys, AdvParams(**params))
+    nk = int(ref["kept_offsets"][-1])
+    for gap in (0, 1, 37):
+        pad = lambda a, v: np.concatenate([np.full(gap, v, a.dtype), a])
+        out = run(pad(rewards, 1), pad(lengths, 5), (off + gap).astype(np.int32), pad(keys, 0))
+        assert np.array_equal(out["kept_offsets"], ref["kept_offsets"])
+        assert np.array_equal(out["kept_index"][:nk], ref["kept_index"] + gap)
+        assert np.array_equal(out["keep_mask"][gap:], ref["keep_mask"]) and (out["keep_mask"][:gap] == 0xFF).all()
+        assert np.array_equal(out["zero_var"], ref["zero_var"]) and np.array_equal(out["category"], ref["category"])
+        for k in ("adv", "weight"):
+            assert np.allclose(out[k][gap:], ref[k], rtol=1e-6, atol=0) and (out[k][:gap] == 7.0).all()
+    back = np.concatenate([[n], off]).astype(np.int32)           # offsets that descend once: an empty group [n, 0)
+    ref = orc.group_advantage(rewards, lengths, back, keys, AdvParams(**params))
+    out = run(rewards, lengths, back, keys)
+    for k in ("kept_offsets", "keep_mask", "zero_var", "category"):
+        assert np.array_equal(out[k], ref[k]), k
+    assert np.array_equal(out["kept_index"][:nk], ref["kept_index"])
 
 
 def test_group_advantage_general_rewards_and_error_flag(gh):
