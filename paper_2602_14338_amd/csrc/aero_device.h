@@ -152,6 +152,10 @@ __device__ __forceinline__ RowStat stat_block_reduce(RowStat a, RowStat* lds /*[
   return a;
 }
 
+// What rounding left off a log-prob; nothing where the log-prob itself is infinite (a sampled token at -inf), whose
+// remainder is formed as inf - inf.
+__device__ __forceinline__ float remainder_of(float lp, float low) { return fabsf(lp) < INFINITY ? low : 0.f; }
+
 // What a row's state says about its sampled token: log-partition, log-prob, and what rounding the log-prob to 32
 // bits left off (for the ratio of the loss, whose terms cancel inside a group).  log s is corrected by
 // s exp(-log s) - 1, so that neither its own rounding nor that of the sum with the offset enters.
@@ -166,7 +170,7 @@ __device__ __forceinline__ RowLogProb row_logprob(const RowStat& st, float zy) {
   const float sum = st.m + l;           // the same for m + l, whose remainder and fix are added before rounding
   const float part = sum - st.m;
   const float rest = (st.m - (sum - part)) + (l - part);
-  return RowLogProb{sum + (rest + fix), lp, ((d - (lp + back)) + (back - l)) - fix};
+  return RowLogProb{sum + (rest + fix), lp, remainder_of(lp, ((d - (lp + back)) + (back - l)) - fix)};
 }
 
 // Loss term, its derivative with respect to the log-prob and the clip decision of one token whose rollout has

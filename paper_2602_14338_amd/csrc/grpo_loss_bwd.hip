@@ -99,7 +99,7 @@ __global__ __launch_bounds__(256) void k_token_terms(
       const float zy = load_elt<DT>(logits, int64_t(t) * ld + y), l = lse[t];
       lp = zy - l;
       const float back = zy - lp;   // two-sum: what the rounding of the difference left off
-      const float low = (zy - (lp + back)) + (back - l);
+      const float low = remainder_of(lp, (zy - (lp + back)) + (back - l));
       r = token_term(h, A, w, lp, low, A != 0.f ? old_logprob[t] : 0.f, h.kl_coef != 0.f ? ref_logprob[t] : 0.f);
       if (h.ent_coef != 0.f) {
         const float H = entropy[t];

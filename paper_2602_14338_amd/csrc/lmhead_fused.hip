@@ -605,7 +605,7 @@ __global__ __launch_bounds__(kRowsNT) void k_fused_rows(
   logprob[t] = lp32;
   lse_out[t] = lse32;
   if (entropy) entropy[t] = ent;
-  if (mine < n_cand) candidate_row(q, mine, t, lse32, lp32, float(lp - double(lp32)), ent);
+  if (mine < n_cand) candidate_row(q, mine, t, lse32, lp32, remainder_of(lp32, float(lp - double(lp32))), ent);
 }
 
 // ------------------------------------------------------------------------------------------

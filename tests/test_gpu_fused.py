@@ -250,6 +250,27 @@ def test_fused_loss_strict_tolerance(gh, T, H, V):
     assert (ref["g"] != 0).any() and ref["loss"] > 0
 
 
+def test_fused_sampled_token_at_minus_infinity(gh):
+    """A sampled token's logit that overflows to -inf in 32 bits (the checker's stays at -1e40): ratio 0, finite loss and
+    gradients."""
+    T, H, V = 300, 64, 1000
+    wl, h, W = make(T, H, V, sigma_w=2.0 / np.sqrt(H))
+    t, y = 5, 321
+    assert wl.token_rollout[t] >= 0
+    wl.targets[t] = y
+    h[:, 0] = W[:, 0] = 0
+    h[t, 0], W[y, 0] = ai.f32_to_bf16_bits(np.float32([1e20, -1e20]))
+    for sign in (1, -1):
+        a32 = np.full(wl.R, 0.5 * sign, np.float32)
+        w32 = np.full(wl.R, 1.0 / T, np.float32)
+        old = np.full(T, -8.0, np.float32)
+        ref = orc.lmhead_fused(h, W, wl.targets, old, wl.token_rollout, a32, w32, np.float32(0.2), np.float32(0.2), 1.0)
+        out = run_fused(gh, wl, h, W, wl.targets, bwd=dict(old=old, adv=a32, weight=w32))
+        gh.assert_loss(out["loss"].item(), ref["loss"], ref["loss_terms"])
+        for k in ("dhidden", "dweight"):
+            assert rowwise_close(out[k].double().cpu().numpy(), ref[k]), k
+
+
 def test_fused_all_groups_zero_variance(gh):
     wl, h, W = make(300, 64, 1000, sigma_w=0.25)
     wl.rewards[:] = 1.0

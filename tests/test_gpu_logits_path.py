@@ -696,6 +696,32 @@ def test_loss_is_run_to_run_identical_and_loss_only_mode(gh):
     assert torch.equal(outs[0]["dlogits"].view(torch.int16), outs[1]["dlogits"].view(torch.int16))
 
 
+@pytest.mark.parametrize("dtype,V,ld,slots", [("bf16", 500, 503, 9), ("bf16", 9000, 9000, 6), ("f32", 40001, 40003, 5)])
+def test_sampled_token_at_minus_infinity(gh, dtype, V, ld, slots):
+    """A sampled token whose logit is -inf: probability and ratio are 0, so the row is clipped or without gradient and
+    the loss stays finite, as with a logit of -1e30 (one workgroup per row, streaming, and two calls)."""
+    wl = ai.make_config("cfg2", V=V, ld=ld, slots=slots, len_lo=2, len_hi=slots, dtype=dtype)
+    host = wl.logits_rows(0, wl.T)
+    rows = np.flatnonzero(wl.token_rollout >= 0)[::3]
+    def masked(x):
+        h = host.copy()
+        h[rows, wl.targets[rows]] = ai.f32_to_bf16_bits(np.float32([x]))[0] if dtype == "bf16" else np.float32(x)
+        return h
+    ga = orc.group_advantage(wl.rewards, wl.lengths, wl.group_offsets, wl.keep_priority, AdvParams())
+    old = np.full(wl.T, -12.0, np.float32)
+    a32, w32 = ga["adv"].astype(np.float32), ga["weight"].astype(np.float32)
+    ref = orc.grpo_loss_bwd(masked(-1e30), dtype, V, wl.targets, old, wl.token_rollout, a32, w32, np.float32(0.2),
+                            np.float32(0.2), 1.0)
+    assert (a32[wl.token_rollout[rows]] > 0).any() and (a32[wl.token_rollout[rows]] < 0).any()
+    z = gh.logits_to_dev(masked(-np.inf), dtype)
+    _, _, lse, _ = gh.run_fwd(z, wl.T, V, ld, wl.targets, want_entropy=False)
+    for given in (None, lse):
+        out = gh.run_loss_bwd(z, wl.T, V, ld, wl.targets, given, old, wl.token_rollout, a32, w32)
+        gh.assert_loss(out["loss"].item(), ref["loss"], ref["loss_terms"])
+        dz = gh.to_np64(out["dlogits"])[:, :V]
+        assert (np.abs(dz - ref["dlogits"]) <= 1e-2 * np.abs(ref["g"])[:, None] + 2.0 ** -8 * np.abs(ref["dlogits"])).all()
+
+
 def test_bad_rollout_index_and_empty_batch(gh):
     wl = ai.make_config("cfg2", V=512, slots=4, len_lo=4, len_hi=4)
     host = wl.logits_rows(0, wl.T)
