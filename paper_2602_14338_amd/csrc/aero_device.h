@@ -156,21 +156,38 @@ __device__ __forceinline__ RowStat stat_block_reduce(RowStat a, RowStat* lds /*[
 // remainder is formed as inf - inf.
 __device__ __forceinline__ float remainder_of(float lp, float low) { return fabsf(lp) < INFINITY ? low : 0.f; }
 
+// a + b as the rounded sum and what the rounding left off (Knuth's two-sum).
+struct Split {
+  float sum, rest;
+};
+__device__ __forceinline__ Split two_sum(float a, float b) {
+  const float s = a + b, bb = s - a;
+  return Split{s, (a - (s - bb)) + (b - bb)};
+}
+
 // What a row's state says about its sampled token: log-partition, log-prob, and what rounding the log-prob to 32
-// bits left off (for the ratio of the loss, whose terms cancel inside a group).  log s is corrected by
-// s exp(-log s) - 1, so that neither its own rounding nor that of the sum with the offset enters.
+// bits left off (for the ratio of the loss, whose terms cancel inside a group).  log s = k log 2 + log f with f in
+// [1/sqrt 2, sqrt 2): k times the leading bits of log 2 (355/512, Cody and Waite's split) is exact, and the rest stays
+// below 0.36 whatever s is, so that its rounding is 1.5e-8 at most and only the results are rounded at their own size.
 struct RowLogProb {
   float lse, lp, low;
 };
 __device__ __forceinline__ RowLogProb row_logprob(const RowStat& st, float zy) {
-  const float l = logf(st.s), fix = fmaf(st.s, expf(-l), -1.f);
+  constexpr float kLn2Hi = 0.693359375f, kLn2Lo = -2.12194440e-4f;
+  float f = __builtin_amdgcn_frexp_mantf(st.s);   // [1/2, 1)
+  int k = __builtin_amdgcn_frexp_expf(st.s);
+  if (f < 0.70710678f) {
+    f *= 2.f;
+    --k;
+  }
+  const float hi = float(k) * kLn2Hi, lo = fmaf(float(k), kLn2Lo, logf(f));
+  const Split sum = two_sum(st.m, hi);
+  const float lse = sum.sum + (sum.rest + lo);
   const float d = zy - st.m;            // an exact difference of stored values, unless they are 32-bit
-  const float lp = d - l;
-  const float back = d - lp;            // two-sum: (d - l) - lp, exactly
-  const float sum = st.m + l;           // the same for m + l, whose remainder and fix are added before rounding
-  const float part = sum - st.m;
-  const float rest = (st.m - (sum - part)) + (l - part);
-  return RowLogProb{sum + (rest + fix), lp, remainder_of(lp, ((d - (lp + back)) + (back - l)) - fix)};
+  const Split a = two_sum(d, -hi);
+  const Split b = two_sum(a.sum, a.rest - lo);
+  if (!(fabsf(d) < INFINITY)) return RowLogProb{lse, d - (hi + lo), 0.f};   // a sampled token at -inf: no remainders
+  return RowLogProb{lse, b.sum, b.rest};
 }
 
 // Loss term, its derivative with respect to the log-prob and the clip decision of one token whose rollout has

@@ -696,6 +696,22 @@ def test_loss_is_run_to_run_identical_and_loss_only_mode(gh):
     assert torch.equal(outs[0]["dlogits"].view(torch.int16), outs[1]["dlogits"].view(torch.int16))
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_log_of_the_row_sum_is_rounded_once(gh, dtype):
+    """Rows of n zeros among logits of -200: the sum of exponentials is n exactly, so what is left of the error is the
+    logarithm's.  Log-partition and log-prob within half a step of the result, and 4.5e-8: the logarithm of
+    a factor of n in [1/sqrt 2, sqrt 2), below 0.36, is off by a step of at most 3e-8, and its sum with the
+    remainder of n's power of two by half a step of 1.5e-8."""
+    V = T = 4096
+    z = np.where(np.arange(V)[None, :] <= np.arange(T)[:, None], np.float32(0), np.float32(-200))
+    want = np.log(np.arange(1, T + 1, dtype=np.float64))
+    bound = np.spacing(want.astype(np.float32)).astype(np.float64) / 2 + 4.5e-8
+    host = ai.f32_to_bf16_bits(z).reshape(T, V) if dtype == "bf16" else z
+    lp, _, lse, _ = gh.run_fwd(gh.logits_to_dev(host, dtype), T, V, V, np.zeros(T, np.int32), want_entropy=False)
+    assert (np.abs(gh.to_np64(lse) - want) <= bound).all()
+    assert (np.abs(gh.to_np64(lp) + want) <= bound).all()
+
+
 @pytest.mark.parametrize("dtype,V,ld,slots", [("bf16", 500, 503, 9), ("bf16", 9000, 9000, 6), ("f32", 40001, 40003, 5)])
 def test_sampled_token_at_minus_infinity(gh, dtype, V, ld, slots):
     """A sampled token whose logit is -inf: probability and ratio are 0, so the row is clipped or without gradient and
