@@ -22,7 +22,7 @@ namespace aero {
 aero_status logprob_fwd_launch(const void* logits, int32_t dtype, int64_t T, int32_t V, int64_t ld,
                                const int32_t* targets, const uint8_t* row_active, float* logprob,
                                float* entropy, float* lse, int32_t* err_flag, hipStream_t s);
-bool single_pass_applicable(int32_t dtype, int V, const void* logits, const void* dlogits);
+bool single_pass_applicable(int32_t dtype, int64_t T, int V, const void* logits, const void* dlogits);
 aero_status single_pass_launch(const void* logits, int32_t dtype, int64_t T, int V, int64_t ld, const int32_t* targets,
                                const float* old_logprob, const int32_t* token_rollout, const float* adv,
                                const float* weight, int R, float eps_lo, float eps_hi, float grad_scale,
@@ -379,7 +379,7 @@ static aero_status loss_bwd_run(
   if (!lse) {
     // statistics are computed here; with entropy_out / lse_out they cover every valid row
     const int stats_all = (entropy_out || lse_out) ? 1 : 0;
-    if (single_pass_applicable(dtype, V, logits, dlogits)) {
+    if (single_pass_applicable(dtype, T, V, logits, dlogits)) {
       const aero_status sp = single_pass_launch(logits, dtype, T, V, ld, targets, old_logprob, token_rollout, adv, weight, R,
                                                 eps_lo, eps_hi, grad_scale, entropy_coef, kl_coef, ref_logprob, stats_all, ws.g,
                                                 ws.loss_term,

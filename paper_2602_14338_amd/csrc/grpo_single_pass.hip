@@ -476,10 +476,30 @@ __global__ void k_set_counter(int32_t* ctr, int32_t v) {
 
 // True when a single-pass kernel applies: element-aligned rows of at most 20 vectors per thread of 1024, and
 // logits and dlogits alike in their position relative to 16 bytes.
-constexpr int kStreamVecs = 20;
-bool single_pass_applicable(int32_t dtype, int V, const void* logits, const void* dlogits) {
+//
+// Where it does, it is not always the faster one; times of two passes / one pass, packed batches, by storage type:
+//   up to 8 vectors per thread   a CU works on several rows: 1.1-2.5.  Loss only, 8-bit rows of more than 4096
+//                                vectors: the row is held for nothing, 1.06-1.4 up to 512 rows, 0.65-0.98 from 600 on
+//   more (streaming)             a row takes a CU of its own.
+//     loss only                  0.55-1.0
+//     T <= 256, all at once      two passes spread the gradient of a few rows over the CUs, and the more logits a vector
+//                                holds, the longer a lone CU takes: fp32 1.0-1.4 from one row on, fp16 0.8-1.1 up to 32
+//                                rows and 1.03-1.25 from 96 on, 8-bit 0.7-1.05 up to 160 and 1.02-1.12 from 200 on
+//     up to 320 MB of logits     the second pass finds them in the 256 MB memory-side cache: 0.8-1.05
+//     beyond                     fp16 1.00-1.17, fp32 1.06-1.19, 8-bit 0.92-1.01 up to 180000 logits a row and 1.02-1.13 from
+//                                240000 on
+// (Padding rows cost the one pass less: with half of the rows valid 1.0-1.4 from 300 rows on, but the host cannot know.)
+// bf16 rows take the one pass throughout: streaming 0.76-1.08 up to 8 rows, 0.84-1.3 from 64 on, loss only 0.55-0.99.
+constexpr int kStreamVecs = 20, kHeldVecs = 8;
+bool single_pass_applicable(int32_t dtype, int64_t T, int V, const void* logits, const void* dlogits) {
   const size_t elt = storage_bytes(dtype);
-  return size_t(V) * elt / 16 <= size_t(kStreamVecs) * kSpNT && rows_alike(logits, dlogits, elt);
+  const size_t nvec = size_t(V) * elt / 16;
+  if (nvec > size_t(kStreamVecs) * kSpNT || !rows_alike(logits, dlogits, elt)) return false;
+  if (dtype == AERO_BF16) return true;
+  if (nvec <= size_t(kHeldVecs) * kSpNT) return dlogits || dtype != AERO_F8E4M3 || nvec <= 4 * kSpNT || T <= 512;
+  if (!dlogits) return false;
+  if (T <= 256) return T >= (dtype == AERO_F32 ? 1 : dtype == AERO_F16 ? 96 : 192);
+  return T * int64_t(nvec) * 16 >= 320000000 && (dtype != AERO_F8E4M3 || nvec >= 14 * kSpNT);
 }
 
 struct RowArgs {
@@ -504,7 +524,7 @@ struct RowArgs {
 
 template <int DT, int NT, bool ENT>
 static void launch_rows(const RowArgs& r, hipStream_t s) {
-  hipLaunchKernelGGL((k_row_single_pass<DT, NT, 8, ENT>), dim3(unsigned(r.T)), dim3(NT), 0, s, r.logits, r.T, r.V, r.ld,
+  hipLaunchKernelGGL((k_row_single_pass<DT, NT, kHeldVecs, ENT>), dim3(unsigned(r.T)), dim3(NT), 0, s, r.logits, r.T, r.V, r.ld,
                      r.targets, r.old_logprob, r.token_rollout, r.adv, r.weight, r.R, r.eps_lo, r.eps_hi, r.grad_scale,
                      r.ent_coef, r.kl_coef, r.ref_logprob, r.stats_all, r.g, r.term, r.flag, r.logprob_out,
                      r.entropy_out, r.lse_out, r.dlogits, r.err_flag);
@@ -515,10 +535,10 @@ static aero_status single_pass_launch_t(const RowArgs& r, int32_t* row_counter, 
   // the smallest workgroup whose threads hold the row in 8 vectors each, so that a CU works on several rows
   // (against 4 vectors each, 8192 bf16 rows: V = 3000 25.0 / 29.6 us, 6000 even, 12000 78.7 / 76.7, 24000 140 / 161, 50000 even)
   const int nvec = r.V / Storage<DT>::kPerVec;
-  if (nvec <= 8 * 64) launch_rows<DT, 64, ENT>(r, s);
-  else if (nvec <= 8 * 256) launch_rows<DT, 256, ENT>(r, s);
-  else if (nvec <= 8 * 512) launch_rows<DT, 512, ENT>(r, s);
-  else if (nvec <= 8 * kSpNT) launch_rows<DT, kSpNT, ENT>(r, s);
+  if (nvec <= kHeldVecs * 64) launch_rows<DT, 64, ENT>(r, s);
+  else if (nvec <= kHeldVecs * 256) launch_rows<DT, 256, ENT>(r, s);
+  else if (nvec <= kHeldVecs * 512) launch_rows<DT, 512, ENT>(r, s);
+  else if (nvec <= kHeldVecs * kSpNT) launch_rows<DT, kSpNT, ENT>(r, s);
   else {
     constexpr int NL = 9;
     constexpr int kLdsBytes = NL * kSpNT * 16;   // 144 KB of wave-private slots

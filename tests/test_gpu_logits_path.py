@@ -541,7 +541,10 @@ def test_f8_gradient_rounding_bit_exact(gh):
     ("bf16", 65543, 65543, 4), ("bf16", 163847, 163849, 3), ("bf16", 3, 5, 40), ("bf16", 9, 9, 40),
     ("f16", 16393, 16395, 6), ("f16", 151937, 151939, 3),
     ("f32", 2048, 2049, 9), ("f32", 8197, 8197, 6), ("f32", 81920, 81922, 3), ("f32", 81927, 81927, 3), ("f32", 2, 3, 40),
-    ("f8e4m3", 8207, 8209, 6), ("f8e4m3", 131103, 131107, 3), ("f8e4m3", 17, 19, 40)])
+    ("f8e4m3", 8207, 8209, 6), ("f8e4m3", 131103, 131107, 3), ("f8e4m3", 17, 19, 40),
+    # enough rows for one pass over fp16 / 8-bit rows that stream, and one row too few / too many
+    ("f16", 151937, 151939, 7), ("f16", 65549, 65551, 6), ("f16", 65549, 65551, 5), ("f16", 65549, 65549, 17),
+    ("f8e4m3", 131103, 131107, 13), ("f8e4m3", 131103, 131107, 11)])
 def test_single_pass_edges(gh, dtype, V, ld, slots):
     def wl():
         return ai.make_config("cfg2", V=V, ld=ld, slots=slots, len_lo=1, len_hi=slots - 1, dtype=dtype)
@@ -549,6 +552,25 @@ def test_single_pass_edges(gh, dtype, V, ld, slots):
     check_loss_bwd(gh, wl(), dict(), sigma_old=0.3, use_oracle_lse=False, stats=True, grad_scale=gs, untouched="half")
     check_loss_bwd(gh, wl(), dict(reject_enable=1, posterior_mode=1), sigma_old=0.3, use_oracle_lse=False, inplace=True,
                    grad_scale=gs, entropy_coef=0.01, kl_coef=0.04)
+
+
+@pytest.mark.parametrize("T", [512, 513])
+def test_loss_only_f8_rows(gh, T):
+    """8-bit rows without a gradient, one pass up to 512 rows and the forward pass alone beyond: loss, clip fraction and
+    log-probs as in the call that also forms the gradient (32-bit sums in another order)."""
+    V, R = 65568, 40
+    g = torch.Generator(device=gh.DEV)
+    g.manual_seed(T)
+    z = (torch.randn(T, V, generator=g, device=gh.DEV) * 3).to(torch.float8_e4m3fn)
+    rng = np.random.default_rng(T)
+    tg = rng.integers(0, V, size=T).astype(np.int32)
+    tr = rng.integers(-2, R, size=T).astype(np.int32)
+    args = (z, T, V, V, tg, None, np.full(T, -12.0, np.float32), tr, np.abs(rng.normal(size=R)) + 0.1, np.full(R, 1.0 / T))
+    full, only = gh.run_loss_bwd(*args), gh.run_loss_bwd(*args, want_dlogits=False)
+    assert full["loss"].item() != 0.0
+    assert abs(full["loss"].item() - only["loss"].item()) <= 1e-6 * abs(full["loss"].item())
+    assert full["clip_frac"].item() == only["clip_frac"].item()
+    assert (full["logprob"] - only["logprob"]).abs().max() <= 4e-6    # two steps of a value near 12
 
 
 @pytest.mark.parametrize("off_z,off_d", [(1, 1), (3, 11), (5, 13), (2, 7)])
