@@ -347,6 +347,9 @@ inline bool rows_alike(const void* logits, const void* dlogits, size_t elt) {
   return z % elt == 0 && (!dlogits || z % 16 == d % 16);
 }
 
+// A launch has fewer than 2^32 threads in all (and fewer than 2^31 workgroups).
+inline bool grid_fits(int64_t blocks, int threads) { return blocks < (int64_t(1) << 31) && blocks * threads < (int64_t(1) << 32); }
+
 inline hipStream_t as_stream(void* s) { return reinterpret_cast<hipStream_t>(s); }
 
 inline aero_status launch_status() {

@@ -307,7 +307,7 @@ static void dispatch_dlogits(const void* logits, int64_t T, int V, int64_t ld, c
   const int64_t work = (V + per_vec - 1) / per_vec;
   if constexpr (VEC) {
     const int64_t segs = (V / per_vec + kSegNT - 1) / kSegNT;
-    if (work > 16 * 256 && T * segs < (int64_t(1) << 31)) {
+    if (work > 16 * 256 && grid_fits(T * segs, kSegNT)) {
       hipLaunchKernelGGL((k_dlogits_seg<DT, ENT>), dim3(unsigned(T * segs)), dim3(kSegNT), 0, s, logits, V, ld,
                          int(segs), targets, lse, g, ea, eb, dlogits);
       return;

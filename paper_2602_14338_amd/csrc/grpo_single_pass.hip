@@ -474,6 +474,15 @@ __global__ void k_set_counter(int32_t* ctr, int32_t v) {
   ctr[3] = 0;
 }
 
+constexpr int kStreamVecs = 20, kHeldVecs = 8;
+
+// Threads of the workgroup that takes a row of at most kHeldVecs x 1024 vectors: the fewest that hold it in kHeldVecs
+// vectors each, so that a CU works on several rows.
+// (against 4 vectors each, 8192 bf16 rows: V = 3000 25.0 / 29.6 us, 6000 even, 12000 78.7 / 76.7, 24000 140 / 161, 50000 even)
+inline int row_threads(int nvec) {
+  return nvec <= kHeldVecs * 64 ? 64 : nvec <= kHeldVecs * 256 ? 256 : nvec <= kHeldVecs * 512 ? 512 : kSpNT;
+}
+
 // True when a single-pass kernel applies: element-aligned rows of at most 20 vectors per thread of 1024, and
 // logits and dlogits alike in their position relative to 16 bytes.
 //
@@ -490,11 +499,11 @@ __global__ void k_set_counter(int32_t* ctr, int32_t v) {
 //                                240000 on
 // (Padding rows cost the one pass less: with half of the rows valid 1.0-1.4 from 300 rows on, but the host cannot know.)
 // bf16 rows take the one pass throughout: streaming 0.76-1.08 up to 8 rows, 0.84-1.3 from 64 on, loss only 0.55-0.99.
-constexpr int kStreamVecs = 20, kHeldVecs = 8;
 bool single_pass_applicable(int32_t dtype, int64_t T, int V, const void* logits, const void* dlogits) {
   const size_t elt = storage_bytes(dtype);
   const size_t nvec = size_t(V) * elt / 16;
   if (nvec > size_t(kStreamVecs) * kSpNT || !rows_alike(logits, dlogits, elt)) return false;
+  if (nvec <= size_t(kHeldVecs) * kSpNT && !grid_fits(T, row_threads(int(nvec)))) return false;
   if (dtype == AERO_BF16) return true;
   if (nvec <= size_t(kHeldVecs) * kSpNT) return dlogits || dtype != AERO_F8E4M3 || nvec <= 4 * kSpNT || T <= 512;
   if (!dlogits) return false;
@@ -532,14 +541,15 @@ static void launch_rows(const RowArgs& r, hipStream_t s) {
 
 template <int DT, bool ENT>
 static aero_status single_pass_launch_t(const RowArgs& r, int32_t* row_counter, int32_t* row_order, hipStream_t s) {
-  // the smallest workgroup whose threads hold the row in 8 vectors each, so that a CU works on several rows
-  // (against 4 vectors each, 8192 bf16 rows: V = 3000 25.0 / 29.6 us, 6000 even, 12000 78.7 / 76.7, 24000 140 / 161, 50000 even)
   const int nvec = r.V / Storage<DT>::kPerVec;
-  if (nvec <= kHeldVecs * 64) launch_rows<DT, 64, ENT>(r, s);
-  else if (nvec <= kHeldVecs * 256) launch_rows<DT, 256, ENT>(r, s);
-  else if (nvec <= kHeldVecs * 512) launch_rows<DT, 512, ENT>(r, s);
-  else if (nvec <= kHeldVecs * kSpNT) launch_rows<DT, kSpNT, ENT>(r, s);
-  else {
+  if (nvec <= kHeldVecs * kSpNT) {
+    switch (row_threads(nvec)) {
+      case 64: launch_rows<DT, 64, ENT>(r, s); break;
+      case 256: launch_rows<DT, 256, ENT>(r, s); break;
+      case 512: launch_rows<DT, 512, ENT>(r, s); break;
+      default: launch_rows<DT, kSpNT, ENT>(r, s);
+    }
+  } else {
     constexpr int NL = 9;
     constexpr int kLdsBytes = NL * kSpNT * 16;   // 144 KB of wave-private slots
     const auto kernel = k_row_stream<DT, kStreamVecs, NL, ENT>;
