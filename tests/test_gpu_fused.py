@@ -25,8 +25,9 @@ def gh():
     return gpu_helpers
 
 
-def run_fused(gh, wl, h_bits, w_bits, targets, bwd=None, dweight_dtype=torch.float32, dw_into=None):
-    """dw_into: a dweight buffer to accumulate into (AERO_DW_ACCUMULATE) instead of a fresh one."""
+def run_fused(gh, wl, h_bits, w_bits, targets, bwd=None, dweight_dtype=torch.float32, dw_into=None, accumulate=True):
+    """dw_into: a dweight buffer to use instead of a fresh one, to accumulate into (AERO_DW_ACCUMULATE) unless
+    accumulate is False."""
     import paper_2602_14338_amd as aero
     from paper_2602_14338_amd import binding
     dev = gh.DEV
@@ -50,7 +51,7 @@ def run_fused(gh, wl, h_bits, w_bits, targets, bwd=None, dweight_dtype=torch.flo
             wl.R, 0.2, 0.2, bwd.get("grad_scale", 1.0), loss, clip, dh, dw, ws, err,
             entropy_coef=bwd.get("entropy_coef", 0.0), kl_coef=bwd.get("kl_coef", 0.0),
             ref_logprob=gh.dev(bwd["ref_lp"].astype(np.float32)) if bwd.get("ref_lp") is not None else None,
-            dweight_accumulate=dw_into is not None)
+            dweight_accumulate=dw_into is not None and accumulate)
         out.update(loss=loss, clip_frac=clip, dhidden=dh, dweight=dw)
     torch.cuda.synchronize()
     out["err"] = int(err.item())
@@ -147,22 +148,38 @@ def test_fused_backward_weight_forms(gh, T, H, V):
     check_bwd(gh, wl, h, W, dict(reject_enable=1, posterior_mode=1), entropy_coef=0.01, dweight_dtype=torch.bfloat16)
 
 
+@pytest.mark.parametrize("accumulate", [False, True])
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("H", [72, 320])
-def test_fused_dweight_off_the_16_byte_grid(gh, dtype, H):
-    """A dweight buffer that starts one element off takes element-wise stores: the same bits as an aligned one, the
-    neighbours untouched, with and without accumulation."""
-    T, V = 300, 515
+def test_fused_dweight_off_the_16_byte_grid(gh, dtype, H, accumulate):
+    """A dweight buffer that starts one element off takes element-wise stores: the same bits as an aligned one and the
+    checker's gradient, the neighbours untouched, with and without accumulation (grad_scale lifts the gradient to
+    where the rounding of the sum with the buffer's 0.25 does not hide it)."""
+    T, V, scale = 300, 515, 4096.0
     wl, h, W = make(T, H, V, sigma_w=2.0 / np.sqrt(H))
     ga = orc.group_advantage(wl.rewards, wl.lengths, wl.group_offsets, wl.keep_priority, AdvParams())
-    bwd = dict(old=np.full(T, -6.0), adv=ga["adv"], weight=ga["weight"])
+    a32, w32 = ga["adv"].astype(np.float32), ga["weight"].astype(np.float32)
+    old = np.full(T, -6.0, np.float32)
+    want = orc.lmhead_fused(h, W, wl.targets, old, wl.token_rollout, a32, w32, np.float32(0.2), np.float32(0.2),
+                            scale)["dweight"]
+    assert np.median(np.abs(want)) > 0.02
+    bwd = dict(old=old, adv=a32, weight=w32, grad_scale=scale)
 
-    def into(offset):
-        flat = torch.full((V * H + 8,), 0.25, dtype=dtype, device=gh.DEV)
-        run_fused(gh, wl, h, W, wl.targets, bwd=bwd, dw_into=flat[offset:offset + V * H].view(V, H))
-        assert (flat[:offset] == 0.25).all() and (flat[offset + V * H:] == 0.25).all()
-        return flat[offset:offset + V * H]
-    assert torch.equal(into(0), into(1))
+    def into(front):
+        flat = torch.full((V * H + 16,), 7.0, dtype=dtype, device=gh.DEV)
+        inside = flat[front:front + V * H]
+        inside.fill_(0.25)
+        assert (inside.data_ptr() % 16 == 0) == (front == 8)
+        run_fused(gh, wl, h, W, wl.targets, bwd=bwd, dw_into=inside.view(V, H), accumulate=accumulate)
+        assert (flat[:front] == 7.0).all() and (flat[front + V * H:] == 7.0).all()
+        return inside
+    aligned, off = into(8), into(9)
+    assert torch.equal(aligned, off)
+    got = off.double().cpu().numpy().reshape(V, H)
+    start = 0.25 if accumulate else 0.0
+    # bf16: the stored value's rounding, half a step, on top of the bound on the gradient itself
+    rounding = 2.0 ** -8 * np.abs(start + want) if dtype == torch.bfloat16 else 0.0
+    assert (np.abs(got - start - want) <= 1e-2 * np.abs(want).max(axis=1, keepdims=True) + rounding + 1e-6).all()
 
 
 @pytest.mark.parametrize("seed", range(10))
