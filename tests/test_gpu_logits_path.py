@@ -658,6 +658,53 @@ def test_streaming_kernel_optional_terms_several_rows_per_workgroup(gh):
     check_loss_bwd(gh, wl(), dict(reject_enable=1), use_oracle_lse=False, inplace=True, stats=True)
 
 
+@pytest.mark.parametrize("inplace,terms", [(False, False), (True, True), (True, False), (False, True)])
+@pytest.mark.parametrize("dtype,V,ld,T", [("bf16", 70003, 70005, 624), ("f16", 65549, 65551, 2496), ("f32", 32777, 32779, 2496),
+                                          ("f8e4m3", 230001, 230003, 1456)])
+def test_streaming_rows_of_changing_alignment(gh, dtype, V, ld, T, inplace, terms):
+    """Several rows per workgroup of the streaming kernel, each at another offset from 16 bytes than the one whose slots
+    it takes over, after gradient rows and after rows that are only filled with zeros (padding, advantage 0) or
+    left alone: bit for bit what calls on 208 rows give, where every workgroup has one row (208 rows begin on the
+    16-byte grid at any pitch)."""
+    R, step = 24, 208
+    g = torch.Generator(device=gh.DEV)
+    g.manual_seed(V)
+    store = {"f8e4m3": torch.float8_e4m3fn, "f16": torch.float16, "bf16": torch.bfloat16, "f32": torch.float32}[dtype]
+    z = torch.empty(T, ld, dtype=store, device=gh.DEV)
+    for a in range(0, T, step):
+        z[a:a + step] = (torch.randn(min(step, T - a), ld, generator=g, device=gh.DEV) * 3).to(store)
+    rng = np.random.default_rng(V)
+    tg = rng.integers(0, V, size=T).astype(np.int32)
+    tg[:8], tg[8:16] = np.arange(8), V - 1 - np.arange(8)          # in the ragged ends
+    tr = np.where(rng.random(T) < 0.25, rng.integers(-2, 0, size=T), rng.integers(0, R, size=T)).astype(np.int32)
+    adv, weight = rng.normal(size=R), rng.uniform(0.5, 1.0, size=R)
+    adv[:6], weight[6:9] = 0.0, 0.0
+    lp, _, _, _ = gh.run_fwd(z, T, V, ld, tg, want_entropy=False)
+    old = lp.cpu().numpy() + rng.normal(0, 0.1, size=T).astype(np.float32)
+    kw = dict(grad_scale={"f16": 4096.0, "f8e4m3": 256.0}.get(dtype, 1.0), inplace=inplace, stats=True)
+    if terms:
+        kw.update(entropy_coef=0.02, kl_coef=0.04)
+
+    def run(a, b):
+        part = z[a:b].clone() if a == 0 and b == T else z[a:b]   # the whole call on a copy: in place, the parts follow
+        if terms:
+            kw["ref_logprob"] = old[a:b] + 0.05
+        return gh.run_loss_bwd(part, b - a, V, ld, tg[a:b], None, old[a:b], tr[a:b], adv, weight, **kw)
+    whole = run(0, T)
+    assert whole["err"] == 0 and torch.isfinite(whole["loss"]).all()
+    loss = 0.0
+    for a in range(0, T, step):
+        b = min(T, a + step)
+        out = run(a, b)
+        loss += out["loss"].item()
+        for k in ("logprob", "entropy", "lse"):
+            assert torch.equal(out[k], whole[k][a:b]), k
+        assert torch.equal(gh.raw_bits(out["dlogits"])[:, :V], gh.raw_bits(whole["dlogits"][a:b])[:, :V])
+    written = gh.raw_bits(whole["dlogits"])[torch.from_numpy(tr >= 0).to(gh.DEV)][:, :V]
+    assert written.any(dim=1).float().mean() > 0.5
+    assert abs(loss - whole["loss"].item()) <= 1e-6 * T
+
+
 # 151936 with 384 rows: the streaming kernel with several rows per workgroup; 32768: one workgroup per row;
 # 4999 / 1000: the forward + gradient route (row kernels); with the checker's lse: the gradient kernels alone
 # (151936: one vector per thread in segments).
