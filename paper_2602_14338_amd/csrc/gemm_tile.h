@@ -105,14 +105,7 @@ __device__ __forceinline__ int xcd_position(int pid, int n) {
 __device__ __forceinline__ bool tile_of_block(int tiles_m, int tiles_n, int tile0, int n, int& tm, int& tn) {
   const int pos = xcd_position(blockIdx.x, n);
   if (pos < 0) return false;
-  const int npid = tile0 + pos;
-  constexpr int GM = 8;
-  const int group_sz = GM * tiles_n;
-  const int first_m = (npid / group_sz) * GM;
-  const int gm = min(GM, tiles_m - first_m);
-  const int within = npid % group_sz;
-  tm = first_m + within % gm;
-  tn = within / gm;
+  tile_of_index(tile0 + pos, tiles_m, tiles_n, tm, tn);
   return true;
 }
 

@@ -9,8 +9,8 @@
 //           k_fused_stats    tile of z^T (vocab rows x token columns): every lane owns one token column
 //                            per block, so the running (offset, sum exp, sum exp*z) is a per-lane
 //                            register recurrence with no shuffles.  On the candidates' token tiles it
-//                            also leaves P = exp(z - zy) in bf16 in K-slabs [vocab/64][token][64] and
-//                            [vocab chunk][token/64][vocab in chunk][64], both in fragment order, that
+//                            also leaves P = exp(z - zy) in bf16 in K-slabs, tokens x vocabulary and
+//                            (by vocabulary chunk) vocabulary x tokens, both in fragment order, that
 //                            the two gradient contractions read (2 x T x V x 2 bytes are held)
 //           k_fused_rows     merges the per-tile partials of a token -> logprob, entropy, lse, and in the same
 //                            breath the candidates' loss terms and gradient scalars:
@@ -25,7 +25,8 @@
 //           k_gemm_dh        dhidden partials = (P or dz) @ weight   (split-K over the vocabulary, fp32)
 //           k_gemm_dw        dweight = (P or dz)^T @ (scale * hidden)
 //           k_scatter_dh     fp32 partials summed in fixed order, times scale -> bf16 dhidden at the original rows
-// All contractions use the same 256 x 256 x 64 MFMA tile with both operands K-contiguous.
+// All contractions use the same 256 x 256 x 64 MFMA tile, both operands K-contiguous but for the weight in k_gemm_dh<true>,
+// whose rows are the contraction index and which a transposing LDS read turns (see kDirectRows).
 #include <mutex>
 
 #include "gemm_tile.h"
@@ -611,50 +612,17 @@ __global__ __launch_bounds__(kRowsNT) void k_fused_rows(
 // ------------------------------------------------------------------------------------------
 // backward: transposes
 // ------------------------------------------------------------------------------------------
-// Transposes (and optionally gathers) a row-major bf16 matrix into the K-slab layout the GEMM
-// tile reads: source row r becomes K index r, source column c becomes operand row c:
-//   out[(r / 64) * C_pad * 64 + c * 64 + r % 64] = in[src(r)][c]
-// for r < n_k (src = idx[r] if idx else r; src < 0 or src >= rows_in_valid gives 0) and c < C_pad
-// (columns c >= C do not exist in `in` and give 0).  Also writes the gathered row-major copy
-// gath[r][c] (c < C) when gath != null.  With scale != null the transposed copy holds scale[r] * in[src(r)][c]
-// (product in fp32, rounded to bf16 once).  64 x 64 tiles through LDS; grid (n_k / 64, C_pad / 64).
-__global__ __launch_bounds__(256) void k_gather_transpose(
-    const uint16_t* __restrict__ in, int64_t ld_in, int64_t rows_in_valid, int C, int C_pad,
-    const int32_t* __restrict__ idx, int64_t n_k, uint16_t* __restrict__ out, uint16_t* __restrict__ gath,
-    int64_t ld_gath, const float* __restrict__ scale) {
-  __shared__ uint16_t tile[64][66];
-  const int64_t r0 = int64_t(blockIdx.x) * 64;
-  const int c0 = blockIdx.y * 64;
-  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-  for (int rr = ty; rr < 64; rr += 4) {
-    const int64_t r = r0 + rr;
-    const int c = c0 + tx;
-    uint16_t v = 0;
-    if (r < n_k && c < C) {
-      const int64_t src = idx ? int64_t(idx[r]) : r;
-      if (src >= 0 && src < rows_in_valid) v = in[src * ld_in + c];
-      if (gath) gath[r * ld_gath + c] = v;
-      if (scale) v = f32_to_bf16(bf16_to_f32(v) * scale[r]);
-    }
-    tile[rr][tx] = v;
-  }
-  __syncthreads();
-  // one K-slab holds 64 consecutive r: this block writes rows c0 .. c0+63 of slab blockIdx.x
-  uint16_t* slab = out + int64_t(blockIdx.x) * C_pad * 64;
-  for (int cc = ty; cc < 64; cc += 4) {
-    const int c = c0 + cc;
-    if (c < C_pad) slab[int64_t(c) * 64 + tx] = tile[tx][cc];
-  }
-}
-
-// Same contract, for C % 8 == 0, ld_in % 8 == 0 and 16-byte aligned pointers: every global access
-// is a 16-byte vector.  The tile is held in LDS as [r][c] with 32-bit writes; a thread then
-// collects 8 consecutive r of one column c for one 16-byte store, threads ordered so that a
-// workgroup writes its 64 x 64 block of the slab as one contiguous 8 KB run.
-__global__ __launch_bounds__(256) void k_gather_transpose_vec(
-    const uint16_t* __restrict__ in, int64_t ld_in, int64_t rows_in_valid, int C, int C_pad,
-    const int32_t* __restrict__ idx, int64_t n_k, uint16_t* __restrict__ out, uint16_t* __restrict__ gath,
-    int64_t ld_gath, const float* __restrict__ scale) {
+// Transposes a row-major bf16 matrix of rows_in rows and C columns (C % 8 == 0, 16-byte aligned) into the K-slab layout
+// the GEMM tile reads: source row r becomes K index r, source column c becomes operand row c:
+//   out[(r / 64) * C_pad * 64 + c * 64 + r % 64] = in[r][c]
+// for c < C_pad; rows from rows_in and columns from C on do not exist in `in` and give 0.  With
+// scale != null the copy holds scale[r] * in[r][c] (product in fp32, rounded to bf16 once).
+// 64 x 64 tiles through LDS, one per workgroup of the grid (rows / 64, C_pad / 64).  Every global access is a 16-byte
+// vector: the tile is held in LDS as [r][c] with 32-bit writes; a thread then collects 8 consecutive r of one
+// column c for one 16-byte store, threads ordered so that a workgroup writes its 64 x 64 block of the slab as one
+// contiguous 8 KB run.
+__global__ __launch_bounds__(256) void k_transpose(const uint16_t* __restrict__ in, int64_t rows_in, int C, int C_pad,
+                                                   uint16_t* __restrict__ out, const float* __restrict__ scale) {
   __shared__ uint32_t tile[64][33];   // [r][c / 2]
   const int64_t r0 = int64_t(blockIdx.x) * 64;
   const int c0 = blockIdx.y * 64;
@@ -665,10 +633,8 @@ __global__ __launch_bounds__(256) void k_gather_transpose_vec(
     const int64_t r = r0 + rr;
     const int c = c0 + c8;
     u32x4_t v = {0u, 0u, 0u, 0u};
-    if (r < n_k && c < C) {
-      const int64_t src = idx ? int64_t(idx[r]) : r;
-      if (src >= 0 && src < rows_in_valid) v = *reinterpret_cast<const u32x4_t*>(in + src * ld_in + c);
-      if (gath) *reinterpret_cast<u32x4_t*>(gath + r * ld_gath + c) = v;
+    if (r < rows_in && c < C) {
+      v = *reinterpret_cast<const u32x4_t*>(in + r * C + c);
       if (scale) {
         const float f = scale[r];
         float x[8];
@@ -705,10 +671,9 @@ __global__ __launch_bounds__(256) void k_gather_transpose_vec(
 // backward: dz tiles, whole vocabulary
 // ------------------------------------------------------------------------------------------
 // z^T tile rows = vocab [m0, m0 + 256), columns = compacted tokens.  The bf16 gradient leaves in
-// the two K-slab layouts the next two contractions read: dz as [v / 64][token][64] (K = vocab)
-// and dzT as [v / VC][token / 64][v % VC][64] (K = tokens, in vocabulary chunks of VC rows so that
-// one chunk, whose slabs are in fragment order like those of dz, stays below the 4 GiB a buffer descriptor can address); entries outside the
-// vocabulary or the candidate tokens are zero.
+// the two layouts the next two contractions read, both K-slabs in fragment order (frag_order_offset): dz tokens x
+// vocabulary, and dzT vocabulary x tokens in chunks of VC vocabulary rows, so that one chunk stays below the 4 GiB a
+// buffer descriptor can address; entries outside the vocabulary or the candidate tokens are zero.
 // ENT: rows also carry the entropy-bonus term, dz = pi (ac z + bc) + gc onehot; otherwise ac = 0
 // and the scale is the per-token constant bc = -g.
 // The kernel is the recompute mode of the backward pass (see FusedTerms): with force == 0 it
@@ -1075,14 +1040,12 @@ extern "C" aero_status aero_lmhead_logprob_fused(
                          terms.bc, dz, dzT);
   }
   // the candidates' hidden rows, each times its scale, transposed to hTc: K-slabs over the candidate positions
-  const bool vec_tr = (H % 8 == 0) && (reinterpret_cast<uintptr_t>(Hp) % 16 == 0) && (reinterpret_cast<uintptr_t>(Wp) % 16 == 0);
-  const auto transpose = vec_tr ? k_gather_transpose_vec : k_gather_transpose;
-  hipLaunchKernelGGL(transpose, dim3(unsigned(p.T_pad / 64), unsigned(p.H_pad / 64)), dim3(256), 0, s, hf,
-                     int64_t(H), p.T_pad, H, p.H_pad, nullptr, p.T_pad, hTc, nullptr, int64_t(0), terms.scale);
+  hipLaunchKernelGGL(k_transpose, dim3(unsigned(p.T_pad / 64), unsigned(p.H_pad / 64)), dim3(256), 0, s, hf, p.T_pad, H,
+                     p.H_pad, hTc, terms.scale);
   // weight transposed to WT, K-slabs over the vocabulary; rows V..V_ld of the source do not exist -> zeros
   if (!p.direct)
-    hipLaunchKernelGGL(transpose, dim3(unsigned(p.V_ld / 64), unsigned(p.H_pad / 64)), dim3(256), 0, s, Wp,
-                       int64_t(H), int64_t(V), H, p.H_pad, nullptr, int64_t(p.V_ld), WT, nullptr, int64_t(0), nullptr);
+    hipLaunchKernelGGL(k_transpose, dim3(unsigned(p.V_ld / 64), unsigned(p.H_pad / 64)), dim3(256), 0, s, Wp, int64_t(V), H,
+                       p.H_pad, WT, nullptr);
 
   // ---- the two gradient contractions over the whole vocabulary ----
   if (T > 0) {
