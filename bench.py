@@ -341,7 +341,9 @@ def run_logits(args, name, mods, headline):
     bwd_gbs = bwd_bytes / (ms_bwd * 1e-3) / 1e9
     single_gbs = single_bytes / (ms_single * 1e-3) / 1e9
     valid_only_gbs = valid_only_bytes / (ms_single * 1e-3) / 1e9
-    single_kernel = "k_row_stream" if V // 8 > 8 * 1024 else ("k_row_single_pass" if V >= 8192 else "k_logprob_fwd + k_dlogits")
+    # bf16 rows: up to 20 vectors of 8 logits per thread of 1024
+    single_kernel = ("k_row_single_pass" if V // 8 <= 8 * 1024 else "k_row_stream" if V // 8 <= 20 * 1024
+                     else "k_logprob_fwd + k_dlogits")
     traffic = measured_traffic(name)
     out = {
         "metric": "tokens/s, GRPO logprob+loss fwd/bwd at V=%d" % V,

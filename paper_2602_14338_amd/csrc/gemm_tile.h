@@ -4,12 +4,13 @@
 // v_mfma_f32_16x16x32_bf16.  Two waves per SIMD let one wave's waits (barrier, LDS latency,
 // epilogue arithmetic) hide behind the other's matrix instructions.
 //
-// The loop is bound by the power limit: on Gaussian operands the clock settles near 1.75 GHz
-// (2.4 GHz on zeros), so the energy per flop of the matrix instruction sets the rate.  A stream
-// of nothing but 16 x 16 x 32 reaches 2.11 PFLOP/s on Gaussian data where 32 x 32 x 16 reaches
-// 1.85 (both 2.4-2.5 on zeros), and 2.13 when consecutive instructions always share one operand
-// (the column order alternates from row to row).  The bare loop below: 1.45 PFLOP/s at
-// 151936 x 16384 x 1536 and 1.44 at 152064 x 32768 x 3584, against 1.36 / 1.34 with 32 x 32 x 16.
+// Two things bound the loop, in about equal parts.  The power limit: k_fused_stats<false> at 151936 x 16384 x 1536 takes
+// 5.92 ms on Gaussian operands at 1.97 GHz and 4.95 on zeros at 2.39, the matrix units busy in 62 % of the cycles both
+// times, so the energy per flop of the matrix instruction counts; a stream of nothing but 16 x 16 x 32 reaches 2.11
+// PFLOP/s on Gaussian data where 32 x 32 x 16 reaches 1.85 (both 2.4-2.5 on zeros), and 2.13 when consecutive
+// instructions always share one operand (the column order alternates from row to row).  And the other 38 % of the
+// cycles, part of which the clock would take back: the library's 81 % at K = 3584 come with 1.70 GHz.  The bare loop below:
+// 1.45 PFLOP/s at 151936 x 16384 x 1536 and 1.44 at 152064 x 32768 x 3584, against 1.36 / 1.34 with 32 x 32 x 16.
 //
 // Two main loops share the accumulator layout:
 //   gemm_tile_dma  operands go HBM -> LDS directly (buffer_load ... lds), two stages of

@@ -75,10 +75,10 @@ static int64_t dh_part_rows(int64_t T_pad, int H, int V_ld) {
 // The dhidden contraction wants the weight with the vocabulary as the contiguous index.  Copying it into
 // that form costs a read and a write of the weight per call whatever the token count (165 us at H = 1536, 430 at
 // H = 3584 with V = 152 K); reading it as it is through the transposing LDS read makes the contraction
-// itself 13-15 % slower (LDS bound).  The two meet near 2800 candidate rows whatever V and H are, and candidates
-// are about two thirds of a call's rows.  Whole calls, copy against as it is, at H = 1536, V = 151936: 300 tokens
-// 1012 / 841 us, 1200 tokens 1676 / 1538, 4000 tokens 4222 / 4105, 5000 and 7000 tokens even; at H = 3584: 1200 tokens
-// 3396 / 3080, 4000 tokens even.
+// itself 13-15 % slower (LDS bound).  The two meet near 2800 candidate rows whatever V and H are, and the host knows only
+// the rows.  Whole calls, time with the copy / as it is, H from 896 to 3584, V from 32000 to 152064: two thirds of the rows
+// candidates 1.03-1.05 at 2048 rows, 1.00-1.02 at 3072, 0.99-1.01 at 4096; all of them 1.01-1.04, 0.99-1.01 and
+// 0.98-1.00.  300 tokens at H = 1536, V = 151936 1012 / 841 us; 5000 and 7000 tokens even.
 constexpr int64_t kDirectRows = 4096;
 
 static FusedPlan make_plan(int64_t T, int V, int H) {
