@@ -115,30 +115,41 @@ __global__ __launch_bounds__(NT) void k_row_single_pass(
     float z[1] = {zr};
     stat_update<1>(st, z);
   }
-  // Orders the loads of the row before the stores over it, for a gradient in place: by its barrier, and with one
-  // wave (no barrier) because every lane's result needs every lane's loads.
-  st = stat_block_reduce<NT>(st, lds);
+  st = stat_block_reduce<NT>(st, lds);   // contains the barrier that orders loads before stores
   const RowLogProb own = row_logprob(st, zy);
   const float lse = own.lse, lp = own.lp;
 
   // ---- token terms (every thread computes the same scalars) ----
-  TokenTerm r{0.f, 0.f, 0};
-  if (signal || bonus)
-    r = token_term(LossHyper{eps_lo, eps_hi, grad_scale, ent_coef, ENT ? kl_coef : 0.f}, A, w, lp, own.low,
-                   signal ? old_logprob[t] : 0.f, ENT && kl_coef != 0.f ? ref_logprob[t] : 0.f);
+  float g = 0.f, term = 0.f;
+  int flag = 0;
+  if (signal) {
+    const float rho = expf(lp - old_logprob[t] + own.low);
+    const float lo = 1.f - eps_lo, hi = 1.f + eps_hi;
+    const float clipped = fminf(fmaxf(rho, lo), hi);
+    const float s = fminf(rho * A, clipped * A);
+    const bool unclipped = A > 0.f ? (rho <= hi) : (rho >= lo);
+    term = -w * s;
+    g = unclipped ? -grad_scale * w * A * rho : 0.f;
+    flag = unclipped ? 1 : 2;
+  }
   const float ent = lse - st.sz / st.s;
   // gradient row: dz_j = pi_j (a z_j + b) + g 1[j = y]; without the entropy bonus a = 0, b = -g
-  const float g = r.g;
+  if (bonus && kl_coef != 0.f) {   // Eq. 2's beta term: exp(d) - d - 1, d = log pi_ref - log pi
+    const float d = ref_logprob[t] - lp - own.low;
+    const float ed = expf(d);
+    term += kl_coef * w * (ed - d - 1.f);
+    g += grad_scale * kl_coef * w * (1.f - ed);
+  }
   float a = 0.f, ng = -g;
   if (bonus) {
-    r.term -= ent_coef * w * ent;
+    term -= ent_coef * w * ent;
     a = grad_scale * ent_coef * w;
     ng = a * (ent - lse) - g;
   }
   if (tid == 0) {
     g_out[t] = g;
-    term_out[t] = r.term;
-    flag_out[t] = r.flag;
+    term_out[t] = term;
+    flag_out[t] = flag;
     if (logprob_out) logprob_out[t] = lp;
     if (entropy_out) entropy_out[t] = ent;
     if (lse_out) lse_out[t] = lse;
@@ -323,10 +334,10 @@ __global__ __launch_bounds__(kSpNT) void k_row_stream(
         v[u] = __builtin_amdgcn_raw_buffer_load_b128(zsrc, voff_ld + uint32_t(NL + u) * (kSpNT * 16u), 0, 2);
       zr = jr >= 0 ? load_elt<DT>(zrow, jr) : 0.f;
       const float zy = load_elt<DT>(zrow, cur.y);   // read before any thread may overwrite the row in place
-      // Loads return in order and at least NR of them were issued just above (the sampled token's may be a scalar
-      // load, which counts elsewhere): once no more than NR memory operations are outstanding, the older loads
-      // into this wave's LDS slots have landed (the compiler does not track those; stores may retire in any order,
-      // they only make the wait longer).
+      // Loads return in order and at least NR + 1 of them were issued just above: once no more
+      // than NR memory operations are outstanding, the older loads into this wave's LDS slots
+      // have landed (the compiler does not track those; stores may retire in any order, they
+      // only make the wait longer).
       static_assert(NR <= 15, "immediate below holds vmcnt in 4 bits");
       asm volatile("" ::: "memory");
       __builtin_amdgcn_s_waitcnt(0x0F70 | NR);
@@ -360,14 +371,24 @@ __global__ __launch_bounds__(kSpNT) void k_row_stream(
       lse = own.lse;
       lp = own.lp;
       ent = lse - st.sz / st.s;
-      if (cur.signal || (ENT && cur.bonus)) {   // every thread computes the same scalars
-        const TokenTerm r = token_term(LossHyper{eps_lo, eps_hi, grad_scale, ent_coef, ENT ? kl_coef : 0.f}, cur.A, cur.w, lp,
-                                       own.low, cur.signal ? old_logprob[t] : 0.f,
-                                       ENT && kl_coef != 0.f ? ref_logprob[t] : 0.f);
-        g = r.g;
-        term = r.term;
-        flag = r.flag;
-        if constexpr (ENT) {
+      if (cur.signal) {   // every thread computes the same scalars
+        const float rho = expf(lp - old_logprob[t] + own.low);
+        const float lo = 1.f - eps_lo, hi = 1.f + eps_hi;
+        const float clipped = fminf(fmaxf(rho, lo), hi);
+        const float s = fminf(rho * cur.A, clipped * cur.A);
+        const bool unclipped = cur.A > 0.f ? (rho <= hi) : (rho >= lo);
+        term = -cur.w * s;
+        g = unclipped ? -grad_scale * cur.w * cur.A * rho : 0.f;
+        flag = unclipped ? 1 : 2;
+      }
+      if constexpr (ENT) {
+        if (cur.bonus) {
+          if (kl_coef != 0.f) {   // Eq. 2's beta term: exp(d) - d - 1, d = log pi_ref - log pi
+            const float d = ref_logprob[t] - lp - own.low;
+            const float ed = expf(d);
+            term += kl_coef * cur.w * (ed - d - 1.f);
+            g += grad_scale * kl_coef * cur.w * (1.f - ed);
+          }
           term -= ent_coef * cur.w * ent;
           ea = grad_scale * ent_coef * cur.w;
         }
