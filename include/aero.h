@@ -175,9 +175,9 @@ aero_status aero_logprob_fwd(
  *          lse == NULL the whole call is one pass over HBM (the row is held on chip: read once, written once) where
  *          rows have at most 320 KB (163840 2-byte logits, 81920 fp32, 327680 8-bit ones), logits are
  *          aligned to their element size, and dlogits, if given, lies at the same offset from 16 bytes as logits; fp32,
- *          fp16 and 8-bit rows of more than 128 KB are taken so only where that is faster (with dlogits, and as many
- *          rows as fill the GPU without fitting its cache).  Otherwise a forward pass into the workspace precedes the
- *          gradient pass, which stores element by element where logits and dlogits differ in that offset.
+ *          fp16 and 8-bit rows of more than 128 KB are taken so with dlogits only, and from 1, 96 and 192 rows on.
+ *          Otherwise a forward pass into the workspace precedes the gradient pass, which stores element by element
+ *          where logits and dlogits differ in that offset.
  * entropy  f32[T] from aero_logprob_fwd; read only when lse != NULL and entropy_coef != 0
  *          (AERO_ERR_NULL if missing then), may be NULL otherwise.
  * old_logprob f32[T]; token_rollout i32[T] (AERO_ROW_PADDING / AERO_ROW_UNTOUCHED = no rollout); adv, weight f32[R].

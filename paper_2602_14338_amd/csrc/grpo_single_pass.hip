@@ -115,11 +115,14 @@ __global__ __launch_bounds__(NT) void k_row_single_pass(
     float z[1] = {zr};
     stat_update<1>(st, z);
   }
-  st = stat_block_reduce<NT>(st, lds);   // contains the barrier that orders loads before stores
+  // Orders the loads of the row before the stores over it, for a gradient in place: by its barrier, and with one
+  // wave (no barrier) because every lane's result needs every lane's loads.
+  st = stat_block_reduce<NT>(st, lds);
   const RowLogProb own = row_logprob(st, zy);
   const float lse = own.lse, lp = own.lp;
 
-  // ---- token terms (every thread computes the same scalars) ----
+  // ---- token terms (every thread computes the same scalars; token_term's text in place: called here it costs rows of
+  // 1024 threads 4-13 % with the optional terms, 20254 fp32 logits 47.7 / 53.9 us) ----
   float g = 0.f, term = 0.f;
   int flag = 0;
   if (signal) {
@@ -334,10 +337,10 @@ __global__ __launch_bounds__(kSpNT) void k_row_stream(
         v[u] = __builtin_amdgcn_raw_buffer_load_b128(zsrc, voff_ld + uint32_t(NL + u) * (kSpNT * 16u), 0, 2);
       zr = jr >= 0 ? load_elt<DT>(zrow, jr) : 0.f;
       const float zy = load_elt<DT>(zrow, cur.y);   // read before any thread may overwrite the row in place
-      // Loads return in order and at least NR + 1 of them were issued just above: once no more
-      // than NR memory operations are outstanding, the older loads into this wave's LDS slots
-      // have landed (the compiler does not track those; stores may retire in any order, they
-      // only make the wait longer).
+      // Loads return in order and at least NR of them were issued just above (the sampled token's may be a scalar
+      // load, which counts elsewhere): once no more than NR memory operations are outstanding, the older loads
+      // into this wave's LDS slots have landed (the compiler does not track those; stores may retire in any order,
+      // they only make the wait longer).
       static_assert(NR <= 15, "immediate below holds vmcnt in 4 bits");
       asm volatile("" ::: "memory");
       __builtin_amdgcn_s_waitcnt(0x0F70 | NR);
@@ -486,7 +489,8 @@ inline int row_threads(int nvec) {
 // True when a single-pass kernel applies: element-aligned rows of at most 20 vectors per thread of 1024, and
 // logits and dlogits alike in their position relative to 16 bytes.
 //
-// Where it does, it is not always the faster one; times of two passes / one pass, packed batches, by storage type:
+// Where it does, it is not always the faster one; times of two passes / one pass by storage type, every row with a
+// gradient:
 //   up to 8 vectors per thread   a CU works on several rows: 1.1-2.5.  Loss only, 8-bit rows of more than 4096
 //                                vectors: the row is held for nothing, 1.06-1.4 up to 512 rows, 0.65-0.98 from 600 on
 //   more (streaming)             a row takes a CU of its own.
@@ -494,11 +498,12 @@ inline int row_threads(int nvec) {
 //     T <= 256, all at once      two passes spread the gradient of a few rows over the CUs, and the more logits a vector
 //                                holds, the longer a lone CU takes: fp32 1.0-1.4 from one row on, fp16 0.8-1.1 up to 32
 //                                rows and 1.03-1.25 from 96 on, 8-bit 0.7-1.05 up to 160 and 1.02-1.12 from 200 on
-//     up to 320 MB of logits     the second pass finds them in the 256 MB memory-side cache: 0.8-1.05
-//     beyond                     fp16 1.00-1.17, fp32 1.06-1.19, 8-bit 0.92-1.01 up to 180000 logits a row and 1.02-1.13 from
-//                                240000 on
-// (Padding rows cost the one pass less: with half of the rows valid 1.0-1.4 from 300 rows on, but the host cannot know.)
-// bf16 rows take the one pass throughout: streaming 0.76-1.08 up to 8 rows, 0.84-1.3 from 64 on, loss only 0.55-0.99.
+//     more rows                  up to 320 MB, which the 256 MB memory-side cache holds for the second pass, 0.8-1.05;
+//                                beyond fp16 1.00-1.17, fp32 1.06-1.19, 8-bit 0.92-1.13
+// The last line is taken for the batches that the call is for, where padding and rollouts without advantage cost the
+// one pass least (9 of 16 rows valid, a third of the groups all equal: fp16 1.19-1.42, fp32 1.4-2.0, 8-bit 1.09-1.27;
+// packed: fp16 0.99-1.34, 8-bit 0.87-1.23).  bf16 rows take the one pass throughout: streaming 0.76-1.08 up to 8 rows,
+// 0.84-1.3 from 64 on, loss only 0.55-0.99.
 bool single_pass_applicable(int32_t dtype, int64_t T, int V, const void* logits, const void* dlogits) {
   const size_t elt = storage_bytes(dtype);
   const size_t nvec = size_t(V) * elt / 16;
@@ -507,8 +512,7 @@ bool single_pass_applicable(int32_t dtype, int64_t T, int V, const void* logits,
   if (dtype == AERO_BF16) return true;
   if (nvec <= size_t(kHeldVecs) * kSpNT) return dlogits || dtype != AERO_F8E4M3 || nvec <= 4 * kSpNT || T <= 512;
   if (!dlogits) return false;
-  if (T <= 256) return T >= (dtype == AERO_F32 ? 1 : dtype == AERO_F16 ? 96 : 192);
-  return T * int64_t(nvec) * 16 >= 320000000 && (dtype != AERO_F8E4M3 || nvec >= 14 * kSpNT);
+  return T >= (dtype == AERO_F32 ? 1 : dtype == AERO_F16 ? 96 : 192);
 }
 
 struct RowArgs {

@@ -542,7 +542,7 @@ def test_f8_gradient_rounding_bit_exact(gh):
     ("f16", 16393, 16395, 6), ("f16", 151937, 151939, 3),
     ("f32", 2048, 2049, 9), ("f32", 8197, 8197, 6), ("f32", 81920, 81922, 3), ("f32", 81927, 81927, 3), ("f32", 2, 3, 40),
     ("f8e4m3", 8207, 8209, 6), ("f8e4m3", 131103, 131107, 3), ("f8e4m3", 17, 19, 40),
-    # enough rows for one pass over fp16 / 8-bit rows that stream, and one row too few / too many
+    # enough rows for one pass over fp16 and 8-bit rows that stream (96 and 192), and too few
     ("f16", 151937, 151939, 7), ("f16", 65549, 65551, 6), ("f16", 65549, 65551, 5), ("f16", 65549, 65549, 17),
     ("f8e4m3", 131103, 131107, 13), ("f8e4m3", 131103, 131107, 11)])
 def test_single_pass_edges(gh, dtype, V, ld, slots):
