@@ -4,77 +4,115 @@
 // Groups are ragged (CSR offsets).  One wave64 owns one group and walks it in strides of 64,
 // so any group size works; counts are integers, the few floating-point statistics are formed
 // in fp64 from those counts and rounded once to fp32.  The call is latency bound, so what counts is
-// launches and dependent loads:
-//   at most 32 groups (a micro-batch)   k_group_small: everything in one workgroup, one launch
-//   up to 8192 groups (a step)          k_group (c, category, keep mask, advantages, weights), then k_place:
-//                                       every workgroup adds up the kept counts in front of its groups
-//                                       itself, so no scan stands between
-//   more                                k_group, k_scan (exclusive scan of the kept counts, one
-//                                       workgroup) and k_compact: the counts would be read too often.
-// Whole calls, k_place against the last two kernels: 64 groups (1024 rollouts) 8.8 / 11.2 us, 400 (7831) 9.0 / 11.4,
-// 410 (8296) 8.9 / 11.3, 600 (12108) 9.0 / 11.3, 1500 (24384) 9.3 / 11.6, 3000 (60325) 10.2 / 12.9, 4000 (80187)
-// 11.0 / 14.5, 8000 (159965) 18.1 / 24.1.  (Counting the bytes of the keep mask instead, up to 8192 rollouts,
-// takes as long, and reads bytes that nobody wrote where offsets start above 0.)
-// 256 groups of 8 to 32 rollouts took 15.8 us with the third form and a rank search that loaded rewards and
-// keys one at a time; a group of at most 64 rollouts now stays in the lanes of its wave.  (One workgroup
-// for 64 groups serialises them: 18.7 us against 13.5.)
+// launches, dependent loads and exchanges between lanes:
+//   up to 2048 groups and 32768 rollouts (a step)   k_curate: one launch, nothing passed between workgroups
+//   up to 8192 groups                               k_group (c, category, keep mask, advantages, weights), then k_place:
+//                                                   every workgroup adds up the kept counts in front of its groups
+//                                                   itself, so no scan stands between
+//   more                                            k_group, k_scan (exclusive scan of the kept counts, one
+//                                                   workgroup) and k_compact: the counts would be read too often.
+// Whole calls, k_group + k_place / k_curate: 8 groups of 16 (the kernel alone; the call is bound by the host) 5.3 / 3.0 us,
+// 32 groups 11.7 / 6.1, 64 groups (1024 rollouts) 9.0 / 5.7, 256 (5258) 9.2 / 6.0, 400 (7831) 9.2 / 6.2, 600 (12108)
+// 9.1 / 7.7, 1500 (24384) 9.7 / 8.1; beyond 32 loads a thread the rewards in front no longer come in one go.
+// k_place / k_scan + k_compact: 400 groups (7831 rollouts) 9.0 / 11.4, 3000 (60325) 10.2 / 12.9, 4000 (80187) 11.0 / 14.5, 8000
+// (159965) 18.1 / 24.1.  (Counting the bytes of the keep mask instead, up to 8192 rollouts, takes as long, and reads
+// bytes that nobody wrote where offsets start above 0.)
+// 100 groups of 64 to 90 rollouts, whose ranks do not fit one register a lane: 37.9 us when every lane looked for its
+// rank by itself in memory, 13.3 with the candidates taken 64 at a time into the lanes.
+#include <type_traits>
+
 #include "aero_device.h"
 
 namespace aero {
 
-__device__ __forceinline__ int wave_sum_i(int v) {
-#pragma unroll
-  for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, kWave);
-  return v;
+// All-reduce of integers over the wave by lane permutations of the vector ALU (see row16_reduce in aero_device.h).
+template <class Op> __device__ __forceinline__ int wave_reduce_i(int v, Op op) {
+  auto moved = [](int x, auto ctrl) { return __builtin_amdgcn_update_dpp(0, x, decltype(ctrl)::value, 0xf, 0xf, true); };
+  v = op(v, moved(v, std::integral_constant<int, 0xB1>{}));    // quad_perm [1,0,3,2]
+  v = op(v, moved(v, std::integral_constant<int, 0x4E>{}));    // quad_perm [2,3,0,1]
+  v = op(v, moved(v, std::integral_constant<int, 0x141>{}));   // row_half_mirror
+  v = op(v, moved(v, std::integral_constant<int, 0x140>{}));   // row_mirror
+  const auto r16 = __builtin_amdgcn_permlane16_swap(uint32_t(v), uint32_t(v), false, false);
+  v = op(int(r16[0]), int(r16[1]));
+  const auto r32 = __builtin_amdgcn_permlane32_swap(uint32_t(v), uint32_t(v), false, false);
+  return op(int(r32[0]), int(r32[1]));
 }
-__device__ __forceinline__ int wave_max_i(int v) {
-#pragma unroll
-  for (int off = kWave / 2; off > 0; off >>= 1) v = max(v, __shfl_xor(v, off, kWave));
-  return v;
-}
+__device__ __forceinline__ int wave_sum_i(int v) { return wave_reduce_i(v, [](int a, int b) { return a + b; }); }
+__device__ __forceinline__ int wave_max_i(int v) { return wave_reduce_i(v, [](int a, int b) { return max(a, b); }); }
 __device__ __forceinline__ double wave_sum_d(double v) {
 #pragma unroll
   for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, kWave);
   return v;
 }
-__device__ __forceinline__ float wave_max_f(float v) {
-#pragma unroll
-  for (int off = kWave / 2; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, kWave));
-  return v;
-}
-__device__ __forceinline__ float wave_min_f(float v) {
-#pragma unroll
-  for (int off = kWave / 2; off > 0; off >>= 1) v = fminf(v, __shfl_xor(v, off, kWave));
-  return v;
-}
-
-// (key, index) ordering used for down-sampling: smaller key first, ties to the lower index
-__device__ __forceinline__ bool before(uint32_t ka, int ia, uint32_t kb, int ib) {
-  return ka < kb || (ka == kb && ia < ib);
-}
+__device__ __forceinline__ float wave_max_f(float v) { return wave_reduce(v, [](float a, float b) { return fmaxf(a, b); }); }
+__device__ __forceinline__ float wave_min_f(float v) { return wave_reduce(v, [](float a, float b) { return fminf(a, b); }); }
 
 constexpr int kGroupsPerBlock = 4;   // 4 waves of 64
-constexpr int kPlaceQ = 1 << 13;     // k_place up to this many groups (see the top)
+constexpr int kPlaceQ = 1 << 13;     // k_place up to this many groups
+
+// Category of a group of n rollouts of which c have reward exactly 1: u = c / n against tau, integer compares.
+__device__ __forceinline__ int group_category(const aero_adv_params& p, int n, int c) {
+  if (c == 0) return AERO_CAT_ZERO;
+  if (c == n) return AERO_CAT_PERFECT;
+  return int64_t(c) * p.tau_den < int64_t(n) * p.tau_num ? AERO_CAT_PARTIAL : AERO_CAT_GOOD;
+}
+
+// What is kept of it, known from n and c alone: everyone, nobody, every correct rollout and the m lowest-ranked incorrect ones,
+// or the m lowest-ranked of the whole group.
+enum KeepMode { kKeepAll, kKeepNone, kKeepCorrect, kKeepLowest };
+struct KeepRule {
+  KeepMode mode;
+  int m, kept;
+};
+__device__ __forceinline__ KeepRule keep_rule(const aero_adv_params& p, int cat, int n, int c) {
+  if (!p.reject_enable || cat == AERO_CAT_GOOD) return KeepRule{kKeepAll, 0, n};
+  if (cat == AERO_CAT_PARTIAL) {
+    const int m = int(min(int64_t(p.k_ratio) * c, int64_t(n - c)));
+    return KeepRule{kKeepCorrect, m, c + m};
+  }
+  const int m = min(p.zero_keep, n);
+  return p.posterior_mode ? KeepRule{kKeepLowest, m, m} : KeepRule{kKeepNone, 0, 0};
+}
+
+// Offsets outside [0, R] cannot make a kernel read out of bounds.
+struct GroupRange {
+  int b, e;
+};
+__device__ __forceinline__ GroupRange group_range(int lo, int hi, int R) {
+  const int b = max(0, min(lo, R));
+  return GroupRange{b, max(b, min(hi, R))};
+}
+
+// What a lane holds of its group's first 64 rollouts.
+struct Held {
+  float reward;
+  uint32_t key;
+  int length;
+};
+__device__ __forceinline__ Held load_held(GroupRange g, int lane, const float* __restrict__ rewards,
+                                          const int32_t* __restrict__ lengths, const uint32_t* __restrict__ keys) {
+  const int i = g.b + lane;
+  if (i >= g.e) return Held{0.f, 0u, 0};
+  return Held{rewards[i], keys ? keys[i] : 0u, lengths[i]};
+}
 
 // One group, one wave: everything but the position of its kept rollouts in kept_index.  Returns the
-// number of kept rollouts (the same value in every lane).
+// number of kept rollouts (the same value in every lane); kept0: those among the group's first 64.
 __device__ __forceinline__ int group_body(
-    int q, int lane, const float* __restrict__ rewards, const int32_t* __restrict__ lengths,
-    const int32_t* __restrict__ group_offsets, const uint32_t* __restrict__ keys, int Q, int R,
-    const aero_adv_params& p, float* __restrict__ adv, float* __restrict__ weight, uint8_t* __restrict__ keep_mask,
-    uint8_t* __restrict__ zero_var, uint8_t* __restrict__ category, int32_t* __restrict__ err_flag) {
-  int b = group_offsets[q], e = group_offsets[q + 1];
-  b = max(0, min(b, R));   // offsets outside [0, R] cannot make the kernel read out of bounds
-  e = max(b, min(e, R));
+    int q, GroupRange range, Held held, int lane, const float* __restrict__ rewards, const int32_t* __restrict__ lengths,
+    const uint32_t* __restrict__ keys, int Q, const aero_adv_params& p, float* __restrict__ adv,
+    float* __restrict__ weight, uint8_t* __restrict__ keep_mask, uint8_t* __restrict__ zero_var,
+    uint8_t* __restrict__ category, int32_t* __restrict__ err_flag, uint64_t& kept0) {
+  const int b = range.b, e = range.e;
   const int n = e - b;
   const bool curation = p.reject_enable || p.posterior_mode;
 
-  // 1. c = number of rollouts with reward exactly 1; what the lane's first rollout holds, loaded at once
+  // 1. c = number of rollouts with reward exactly 1
   const int i0 = b + lane;
   const bool in0 = i0 < e;
-  const float r0 = in0 ? rewards[i0] : 0.f;
-  const uint32_t key0 = in0 && keys ? keys[i0] : 0u;
-  const int len0 = in0 ? lengths[i0] : 0;
+  const float r0 = held.reward;
+  const uint32_t key0 = held.key;
+  const int len0 = held.length;
   const uint64_t ones = __ballot(in0 && r0 == 1.f);   // of the group's first 64 rollouts
   int c = __popcll(ones);
   bool bad = __ballot(in0 && r0 != 0.f && r0 != 1.f) != 0;
@@ -90,98 +128,126 @@ __device__ __forceinline__ int group_body(
   }
   if (curation && bad && lane == 0 && err_flag) atomicOr(err_flag, AERO_DERR_NONBINARY_REWARD);
 
-  // 2. category by u = c/n against tau, integer compares
-  int cat;
-  if (c == 0) cat = AERO_CAT_ZERO;
-  else if (c == n) cat = AERO_CAT_PERFECT;
-  else if (int64_t(c) * p.tau_den < int64_t(n) * p.tau_num) cat = AERO_CAT_PARTIAL;
-  else cat = AERO_CAT_GOOD;
-
-  // 3. kept subset.  mode 0: all, 1: none, 2: all correct + m lowest-ranked incorrect,
-  //    3: the m lowest-ranked of the whole group
-  int mode = 0, m = 0;
-  if (p.reject_enable) {
-    if (cat == AERO_CAT_PARTIAL) {
-      mode = 2;
-      m = int(min(int64_t(p.k_ratio) * c, int64_t(n - c)));
-    } else if (cat != AERO_CAT_GOOD) {
-      mode = p.posterior_mode ? 3 : 1;
-      m = min(p.zero_keep, n);
-    }
-  }
-  bool keep0 = false;
-  int nk_l = 0;                    // kept
-  double sum_l = 0.0;              // sum of kept rewards
-  // a group that fits the wave: ranks from the lanes' registers, one candidate of the group at a time
+  // 2. category, 3. kept subset
+  const int cat = group_category(p, n, c);
+  const KeepRule rule = keep_rule(p, cat, n, c);
+  const KeepMode mode = rule.mode;
+  const int m = rule.m;
+  // a group that fits the wave: ranks from the lanes' registers, one candidate of the group at a time; smaller key
+  // first, ties to the lower index
   int ahead0 = 0;
-  if (n <= kWave && mode >= 2) {
-    uint64_t cand = __ballot(in0) & (mode == 3 ? ~uint64_t(0) : ~ones);
-    while (cand) {   // uniform
-      const int j = __ffsll((unsigned long long)cand) - 1;
-      cand &= cand - 1;
-      ahead0 += before(uint32_t(__builtin_amdgcn_readlane(int(key0), j)), j, key0, lane);
-    }
-  }
-  float mx_l = -INFINITY, mn_l = INFINITY;
-  for (int i = b + lane; i < e; i += kWave) {
-    const float r = i == i0 ? r0 : rewards[i];
-    bool k;
-    if (mode == 0) k = true;
-    else if (mode == 1) k = false;
-    else if (mode == 2 && r == 1.f) k = true;
-    else if (n <= kWave) k = ahead0 < m;
-    else {
-      // rank among the candidates (incorrect rollouts in mode 2, everyone in mode 3)
-      const uint32_t ki = keys ? keys[i] : 0u;
-      int ahead = 0;
-      for (int j = b; j < e && ahead < m; ++j) {
-        const bool cand = mode == 3 || rewards[j] != 1.f;
-        ahead += cand && before(keys ? keys[j] : 0u, j, ki, i);
+  if (n <= kWave && mode >= kKeepCorrect) {
+    const uint64_t in = __ballot(in0);
+    uint64_t cand = in & (mode == kKeepLowest ? ~uint64_t(0) : ~ones);
+    if (__popcll(cand) > m) {
+      const uint64_t own = uint64_t(key0) << 32 | uint32_t(lane);
+      while (cand) {   // uniform
+        const int j = __ffsll((unsigned long long)cand) - 1;
+        cand &= cand - 1;
+        const uint64_t other = uint64_t(uint32_t(__builtin_amdgcn_readlane(int(key0), j))) << 32 | uint32_t(j);
+        ahead0 += other < own;
       }
-      k = ahead < m;
-    }
-    keep_mask[i] = k ? 1 : 0;
-    if (i == i0) keep0 = k;
-    if (k) {
-      ++nk_l;
-      sum_l += double(r);
-      mx_l = fmaxf(mx_l, r);
-      mn_l = fminf(mn_l, r);
     }
   }
-  const int nk = wave_sum_i(nk_l);
-  const float mx = wave_max_f(mx_l), mn = wave_min_f(mn_l);
-  const bool zv = nk == 0 || mx == mn;
-
-  // 4./5. advantages over the kept subset
-  double mu = 0.0, inv_sigma = 0.0;
-  if (!zv) {
-    mu = wave_sum_d(sum_l) / double(nk);
-    double ss_l = 0.0;
-    for (int i = b + lane; i < e; i += kWave)
-      if (i == i0 ? keep0 : keep_mask[i] != 0) {   // written by this same lane above
-        const double d = double(i == i0 ? r0 : rewards[i]) - mu;
-        ss_l += d * d;
+  auto posterior_mean = [&]() { return (double(c) + double(p.alpha0)) / (double(n) + double(p.alpha0) + double(p.beta0)); };
+  int nk;
+  bool zv;
+  if (n <= kWave && !bad) {
+    // A group in the wave's registers whose rewards are 0 and 1 (every curated one): kept count, sum, extremes and
+    // variance are counts of lanes.  With c correct and m incorrect rollouts kept, (1 - mean) / sigma = sqrt(m / c)
+    // and -mean / sigma = -sqrt(c / m): no sums over the wave, one division and one root.
+    const bool k = in0 && (mode == kKeepAll || (mode == kKeepCorrect && r0 == 1.f) || (mode >= kKeepCorrect && ahead0 < m));
+    kept0 = __ballot(k);
+    nk = __popcll(kept0);
+    const int ck = __popcll(kept0 & ones);
+    zv = ck == 0 || ck == nk;
+    const bool one = r0 == 1.f;
+    double a = 0.0;
+    if (!zv) {
+      const double up = double(one ? nk - ck : ck), down = double(one ? ck : nk - ck);
+      a = sqrt(up / down);
+      a = one ? a : -a;
+    } else if (p.posterior_mode) {   // nk > 0 where a lane keeps anything
+      const double mu = posterior_mean();
+      a = (double(r0) - mu) * (1.0 / sqrt(mu * (1.0 - mu)));
+    }
+    if (in0) {
+      keep_mask[i0] = k ? 1 : 0;
+      adv[i0] = k ? float(a) : 0.f;
+      weight[i0] = k && len0 > 0 ? float(1.0 / (double(Q) * double(nk) * double(len0))) : 0.f;
+    }
+  } else {
+    bool keep0 = false;
+    int nk_l = 0;                    // kept
+    double sum_l = 0.0;              // sum of kept rewards
+    float mx_l = -INFINITY, mn_l = INFINITY;
+    for (int base = b; base < e; base += kWave) {   // uniform over the wave
+      const int i = base + lane;
+      const bool in = i < e;
+      const float r = i == i0 ? r0 : in ? rewards[i] : 0.f;
+      bool k = in && (mode == kKeepAll || (mode == kKeepCorrect && r == 1.f));
+      if (n <= kWave) {
+        k |= in && mode >= kKeepCorrect && ahead0 < m;
+      } else if (mode >= kKeepCorrect) {
+        // rank among the candidates (incorrect rollouts, or everyone), taken 64 at a time into the lanes
+        const uint64_t own = uint64_t(in && keys ? keys[i] : 0u) << 32 | uint32_t(i);
+        int ahead = 0;
+        for (int from = b; from < e && __any(in && !k && ahead < m); from += kWave) {
+          const int j0 = from + lane;
+          const uint32_t kj = j0 < e && keys ? keys[j0] : 0u;
+          uint64_t cand = __ballot(j0 < e && (mode == kKeepLowest || rewards[j0] != 1.f));
+          while (cand) {
+            const int j = __ffsll((unsigned long long)cand) - 1;
+            cand &= cand - 1;
+            ahead += (uint64_t(uint32_t(__builtin_amdgcn_readlane(int(kj), j))) << 32 | uint32_t(from + j)) < own;
+          }
+        }
+        k |= in && ahead < m;
       }
-    inv_sigma = 1.0 / sqrt(wave_sum_d(ss_l) / double(nk));
-  } else if (p.posterior_mode && nk > 0) {
-    // posterior mean from the observed c, n of the whole group
-    mu = (double(c) + double(p.alpha0)) / (double(n) + double(p.alpha0) + double(p.beta0));
-    inv_sigma = 1.0 / sqrt(mu * (1.0 - mu));
-  }
-  const bool signal = !zv || (p.posterior_mode && nk > 0);
-
-  // 6. weights 1 / (Q n' L_i)
-  for (int i = b + lane; i < e; i += kWave) {
-    const bool k = i == i0 ? keep0 : keep_mask[i] != 0;
-    float a = 0.f, w = 0.f;
-    if (k) {
-      if (signal) a = float((double(i == i0 ? r0 : rewards[i]) - mu) * inv_sigma);
-      const int L = i == i0 ? len0 : lengths[i];
-      if (L > 0) w = float(1.0 / (double(Q) * double(nk) * double(L)));
+      if (in) keep_mask[i] = k ? 1 : 0;
+      if (i == i0) keep0 = k;
+      if (k) {
+        ++nk_l;
+        sum_l += double(r);
+        mx_l = fmaxf(mx_l, r);
+        mn_l = fminf(mn_l, r);
+      }
     }
-    adv[i] = a;
-    weight[i] = w;
+    kept0 = __ballot(keep0);
+    nk = wave_sum_i(nk_l);
+    const float mx = wave_max_f(mx_l), mn = wave_min_f(mn_l);
+    zv = nk == 0 || mx == mn;
+
+    // 4./5. advantages over the kept subset
+    double mu = 0.0, inv_sigma = 0.0;
+    if (!zv) {
+      mu = wave_sum_d(sum_l) / double(nk);
+      double ss_l = 0.0;
+      for (int i = b + lane; i < e; i += kWave)
+        if (i == i0 ? keep0 : keep_mask[i] != 0) {   // written by this same lane above
+          const double d = double(i == i0 ? r0 : rewards[i]) - mu;
+          ss_l += d * d;
+        }
+      inv_sigma = 1.0 / sqrt(wave_sum_d(ss_l) / double(nk));
+    } else if (p.posterior_mode && nk > 0) {
+      // posterior mean from the observed c, n of the whole group
+      mu = posterior_mean();
+      inv_sigma = 1.0 / sqrt(mu * (1.0 - mu));
+    }
+    const bool signal = !zv || (p.posterior_mode && nk > 0);
+
+    // 6. weights 1 / (Q n' L_i)
+    for (int i = b + lane; i < e; i += kWave) {
+      const bool k = i == i0 ? keep0 : keep_mask[i] != 0;
+      float a = 0.f, w = 0.f;
+      if (k) {
+        if (signal) a = float((double(i == i0 ? r0 : rewards[i]) - mu) * inv_sigma);
+        const int L = i == i0 ? len0 : lengths[i];
+        if (L > 0) w = float(1.0 / (double(Q) * double(nk) * double(L)));
+      }
+      adv[i] = a;
+      weight[i] = w;
+    }
   }
   if (lane == 0) {
     zero_var[q] = zv ? 1 : 0;
@@ -190,21 +256,22 @@ __device__ __forceinline__ int group_body(
   return nk;
 }
 
+// The kept ones among the 64 rollouts in the lanes (i: the lane's), ascending, from position `out` on.
+__device__ __forceinline__ int place_kept(uint64_t kept, int i, int lane, int out, int R, int32_t* __restrict__ kept_index) {
+  const int at = out + __popcll(kept & ((uint64_t(1) << lane) - 1));
+  if ((kept >> lane & 1) && at < R) kept_index[at] = i;
+  return __popcll(kept);
+}
+
 // Kept rollout indices of one group, ascending, written from position `out` on (one wave).  Groups that overlap can
 // keep more than R rollouts between them: what does not fit kept_index is dropped.
 __device__ __forceinline__ void compact_body(int q, int lane, const int32_t* __restrict__ group_offsets,
                                              const uint8_t* __restrict__ keep_mask, int out, int R,
                                              int32_t* __restrict__ kept_index) {
-  int b = group_offsets[q], e = group_offsets[q + 1];
-  b = max(0, min(b, R));
-  e = max(b, min(e, R));
-  for (int base = b; base < e; base += kWave) {   // trip count is uniform over the wave
+  const GroupRange g = group_range(group_offsets[q], group_offsets[q + 1], R);
+  for (int base = g.b; base < g.e; base += kWave) {   // trip count is uniform over the wave
     const int i = base + lane;
-    const bool k = i < e && keep_mask[i] != 0;
-    const uint64_t bal = __ballot(k);
-    const int at = out + __popcll(bal & ((uint64_t(1) << lane) - 1));
-    if (k && at < R) kept_index[at] = i;
-    out += __popcll(bal);
+    out += place_kept(__ballot(i < g.e && keep_mask[i] != 0), i, lane, out, R, kept_index);
   }
 }
 
@@ -217,8 +284,10 @@ __global__ __launch_bounds__(kGroupsPerBlock* kWave) void k_group(
   const int lane = threadIdx.x % kWave;
   const int q = blockIdx.x * kGroupsPerBlock + threadIdx.x / kWave;
   if (q >= Q) return;   // whole wave leaves together
-  const int nk = group_body(q, lane, rewards, lengths, group_offsets, keys, Q, R, p, adv, weight, keep_mask, zero_var,
-                            category, err_flag);
+  const GroupRange range = group_range(group_offsets[q], group_offsets[q + 1], R);
+  uint64_t kept0;
+  const int nk = group_body(q, range, load_held(range, lane, rewards, lengths, keys), lane, rewards, lengths, keys, Q, p, adv,
+                            weight, keep_mask, zero_var, category, err_flag, kept0);
   if (lane == 0) kept_offsets[q + 1] = nk ^ count_mask;   // count_mask: 0, or -1 for k_place
 }
 
@@ -324,49 +393,90 @@ __global__ __launch_bounds__(kPlaceNT) void k_place(
   compact_body(q, lane, group_offsets, keep_mask, out, R, kept_index);
 }
 
-// The three stages in one workgroup of 16 waves, for Q <= kSmallQ groups: wave w takes groups w and w + 16;
-// the kept counts and their scan stay in LDS; every wave then places the kept indices of the groups it
-// processed (it reads back the keep mask its own lanes wrote).
-constexpr int kSmallQ = 32, kSmallR = 1 << 16, kSmallNT = 1024;
-__global__ __launch_bounds__(kSmallNT) void k_group_small(
+// All of it in one launch: a wave per group, up to 16 in a workgroup.  How many rollouts a group keeps follows from its size
+// and its count of correct rollouts alone, so a workgroup counts what lies in front of its groups itself, from the
+// rewards (a bit per rollout in LDS, a thread per group), while its own groups' loads are under way; nothing is passed
+// between workgroups.  Bound by latency: kernel arguments, offsets, rewards, and the instructions themselves, which come
+// from memory once per launch.
+constexpr int kCurateWaves = 16, kCurateNT = kCurateWaves * kWave;
+constexpr int kCurateR = 32 * kCurateNT, kCurateQ = 2 * kCurateNT;
+// LOADS: rewards per thread, all in flight at once; R <= LOADS * kCurateNT unless there is one workgroup.
+template <int LOADS>
+__global__ __launch_bounds__(kCurateNT) void k_curate(
     const float* __restrict__ rewards, const int32_t* __restrict__ lengths,
     const int32_t* __restrict__ group_offsets, const uint32_t* __restrict__ keys, int Q, int R,
     aero_adv_params p, float* __restrict__ adv, float* __restrict__ weight, uint8_t* __restrict__ keep_mask,
     int32_t* __restrict__ kept_index, int32_t* __restrict__ kept_offsets, uint8_t* __restrict__ zero_var,
     uint8_t* __restrict__ category, int32_t* __restrict__ err_flag) {
-  __shared__ int start[kSmallQ + 1];   // counts, then exclusive offsets
-  __shared__ int part[kSmallNT / kWave];
-  const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
-  constexpr int kWaves = kSmallNT / kWave;
-  for (int q = wave; q < Q; q += kWaves) {
-    const int nk = group_body(q, lane, rewards, lengths, group_offsets, keys, Q, R, p, adv, weight, keep_mask, zero_var,
-                              category, err_flag);
-    if (lane == 0) start[q] = nk;
+  __shared__ uint64_t ones[LOADS * kCurateWaves];   // bit i % 64 of word i / 64: reward i is exactly 1
+  __shared__ int front[kCurateWaves], own[kCurateWaves];
+  const int tid = threadIdx.x, lane = tid % kWave, wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int waves = blockDim.x / kWave;
+  const int q0 = blockIdx.x * waves, q = q0 + wave;
+  // Loads that depend on nothing come first, from clamped positions so that no branch stands between them; what lies
+  // past the end is not looked at.
+  int ahead_b = 0, ahead_e = 0;
+  float x[LOADS];
+  if (q0 > 0 && R > 0) {   // uniform; then there are kCurateNT threads
+#pragma unroll
+    for (int u = 0; u < LOADS; ++u) x[u] = rewards[min(u * kCurateNT + tid, R - 1)];
+    const int at = min(tid, q0 - 1);
+    ahead_b = group_offsets[at];
+    ahead_e = group_offsets[at + 1];
+  }
+  const int qc = min(q, Q - 1);
+  GroupRange mine = group_range(group_offsets[qc], group_offsets[qc + 1], R);
+  if (q >= Q) mine.e = mine.b;
+  const Held held = load_held(mine, lane, rewards, lengths, keys);
+  int before_me = 0;
+  if (q0 > 0 && R > 0) {
+#pragma unroll
+    for (int u = 0; u < LOADS; ++u) {
+      const uint64_t bits = __ballot(x[u] == 1.f);
+      if (lane == 0) ones[u * kCurateWaves + wave] = bits;
+    }
+    __syncthreads();
+#pragma unroll 1
+    for (int at = tid; at - tid < q0; at += kCurateNT) {   // uniform
+      GroupRange g = group_range(ahead_b, ahead_e, R);
+      if (at >= q0) g.e = g.b;
+      if (at - tid + kCurateNT < q0) {   // the next one's
+        const int next = min(at + kCurateNT, q0 - 1);
+        ahead_b = group_offsets[next];
+        ahead_e = group_offsets[next + 1];
+      }
+      int c = 0;
+      for (int w = g.b / 64; w * 64 < g.e; ++w) {
+        uint64_t bits = ones[w];
+        if (w * 64 < g.b) bits &= ~uint64_t(0) << (g.b % 64);
+        if (g.e - w * 64 < 64) bits &= ~(~uint64_t(0) << (g.e % 64));
+        c += __popcll(bits);
+      }
+      const int n = g.e - g.b;
+      before_me += keep_rule(p, group_category(p, n, c), n, c).kept;   // an empty group keeps none
+    }
+    before_me = wave_sum_i(before_me);
+  }
+  uint64_t kept0 = 0;
+  int nk = 0;
+  if (q < Q)   // uniform over the wave
+    nk = group_body(q, mine, held, lane, rewards, lengths, keys, Q, p, adv, weight, keep_mask, zero_var, category, err_flag, kept0);
+  if (lane == 0) {
+    front[wave] = before_me;
+    own[wave] = nk;
   }
   __syncthreads();
-  // exclusive scan of start[0 .. Q): two entries per thread, shuffles inside a wave, the 16 wave totals through LDS
-  const int q0 = 2 * tid, q1 = 2 * tid + 1;
-  const int c0 = q0 < Q ? start[q0] : 0, c1 = q1 < Q ? start[q1] : 0;
-  int incl = c0 + c1;
-#pragma unroll
-  for (int off = 1; off < kWave; off <<= 1) {
-    const int v = __shfl_up(incl, off, kWave);
-    if (lane >= off) incl += v;
+  int out = wave_sum_i(lane < waves ? front[lane] + (lane < wave ? own[lane] : 0) : 0);
+  if (q >= Q) return;
+  if (lane == 0) {
+    if (q == 0) kept_offsets[0] = 0;
+    kept_offsets[q + 1] = out + nk;
   }
-  if (lane == kWave - 1) part[wave] = incl;
-  __syncthreads();   // also: every read of start[] above precedes the writes below
-  int before_me = incl - (c0 + c1), total = 0;
-#pragma unroll
-  for (int w = 0; w < kWaves; ++w) {
-    before_me += w < wave ? part[w] : 0;
-    total += part[w];
+  out += place_kept(kept0, mine.b + lane, lane, out, R, kept_index);
+  for (int base = mine.b + kWave; base < mine.e; base += kWave) {   // a long group: the mask its own lanes wrote
+    const int i = base + lane;
+    out += place_kept(__ballot(i < mine.e && keep_mask[i] != 0), i, lane, out, R, kept_index);
   }
-  if (q0 < Q) start[q0] = before_me;
-  if (q1 < Q) start[q1] = before_me + c0;
-  if (tid == 0) start[Q] = total;
-  __syncthreads();
-  for (int q = tid; q <= Q; q += kSmallNT) kept_offsets[q] = start[q];
-  for (int q = wave; q < Q; q += kWaves) compact_body(q, lane, group_offsets, keep_mask, start[q], R, kept_index);
 }
 
 }  // namespace aero
@@ -383,9 +493,12 @@ extern "C" aero_status aero_group_advantage(
   if (Q > 0 && (!group_zero_var || !group_category)) return AERO_ERR_NULL;
   if (R > 0 && (!rewards || !lengths || !adv || !weight || !keep_mask || !kept_index)) return AERO_ERR_NULL;
   hipStream_t s = as_stream(stream);
-  if (Q > 0 && Q <= kSmallQ && R <= kSmallR) {
-    hipLaunchKernelGGL(k_group_small, dim3(1), dim3(kSmallNT), 0, s, rewards, lengths, group_offsets, keep_priority, Q, R,
-                       *p, adv, weight, keep_mask, kept_index, kept_offsets, group_zero_var, group_category, err_flag);
+  if (Q > 0 && Q <= kCurateQ && R <= kCurateR) {
+    const int waves = Q < kCurateWaves ? Q : kCurateWaves;
+    const auto kernel = R <= 8 * kCurateNT ? k_curate<8> : k_curate<kCurateR / kCurateNT>;
+    hipLaunchKernelGGL(kernel, dim3(unsigned((Q + waves - 1) / waves)), dim3(unsigned(waves * kWave)), 0, s, rewards, lengths,
+                       group_offsets, keep_priority, Q, R, *p, adv, weight, keep_mask, kept_index, kept_offsets, group_zero_var,
+                       group_category, err_flag);
     return launch_status();
   }
   const unsigned blocks = unsigned((Q + kGroupsPerBlock - 1) / kGroupsPerBlock);

@@ -123,6 +123,21 @@ def test_group_advantage_placement_forms(gh, Q, lo, hi):
                       rng.integers(0, 4, size=R).astype(np.uint32)), dict(reject_enable=1, posterior_mode=1, k_ratio=2))
 
 
+@pytest.mark.parametrize("Q,R", [(1, 64), (1, 65), (15, 300), (16, 1024), (17, 1025), (33, 8191), (500, 8192), (500, 8193),
+                                 (2047, 32768), (2048, 32768), (2048, 32769), (2049, 20000)])
+def test_group_advantage_one_launch(gh, Q, R):
+    """One launch up to 2048 groups and 32768 rollouts: around a workgroup's 16 groups, the rollouts that 8 and 32 loads a
+    thread cover, the last call of that form and the first of the other; some groups wider than a wave."""
+    rng = np.random.default_rng(Q * 100003 + R)
+    cuts = np.sort(rng.integers(0, R + 1, size=Q - 1))
+    off = np.concatenate([[0], cuts, [R]]).astype(np.int32)      # empty groups and long ones by chance
+    rewards = (rng.random(R) < np.repeat(rng.beta(0.5, 0.5, size=Q), np.diff(off))).astype(np.float32)
+    lengths = rng.integers(0, 3000, size=R).astype(np.int32)
+    keys = rng.integers(0, 50, size=R).astype(np.uint32)
+    for params in (dict(reject_enable=1, posterior_mode=1), dict(reject_enable=1, k_ratio=2)):
+        check_groups(gh, (rewards, lengths, off, keys), params)
+
+
 @pytest.mark.parametrize("mask_off", [0, 1, 2, 3])
 @pytest.mark.parametrize("Q,lo,hi", [(9, 1, 40), (33, 1, 8), (402, 8, 30), (4095, 0, 3), (4097, 0, 3), (8191, 0, 3),
                                      (8195, 0, 3)])
