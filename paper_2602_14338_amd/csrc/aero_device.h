@@ -350,6 +350,13 @@ inline bool rows_alike(const void* logits, const void* dlogits, size_t elt) {
 // A launch has fewer than 2^32 threads in all (and fewer than 2^31 workgroups).
 inline bool grid_fits(int64_t blocks, int threads) { return blocks < (int64_t(1) << 31) && blocks * threads < (int64_t(1) << 32); }
 
+// Compute units of the current device (256 where it cannot be asked).
+inline int compute_units() {
+  int dev = 0, n = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return 256;
+  return hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0 ? n : 256;
+}
+
 inline hipStream_t as_stream(void* s) { return reinterpret_cast<hipStream_t>(s); }
 
 inline aero_status launch_status() {

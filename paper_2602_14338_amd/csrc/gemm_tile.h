@@ -12,12 +12,12 @@
 // cycles, part of which the clock would take back: the library's 81 % at K = 3584 come with 1.70 GHz.  The bare loop below:
 // 1.45 PFLOP/s at 151936 x 16384 x 1536 and 1.44 at 152064 x 32768 x 3584, against 1.36 / 1.34 with 32 x 32 x 16.
 //
-// Two main loops share the accumulator layout:
-//   gemm_tile_dma  operands go HBM -> LDS directly (buffer_load ... lds), two stages of
-//                  256 x 64 slices, L2 warmed two slices ahead; needs K % 64 == 0 and
-//                  16-byte aligned rows
-//   gemm_tile      register-staged 256 x 64 slices with explicit predication; any K % 8 == 0
+// Operands go HBM -> LDS directly (buffer_load ... lds) in two stages of 256 x 64 slices; rows start on 16 bytes, K is any
+// multiple of 8.  (A loop that staged slices through registers took the rows whose length is no multiple of 64: forward of
+// 2500 tokens at H = 600, V = 32000 220 us, 130 this way.)
 #pragma once
+#include <type_traits>
+
 #include "aero_device.h"
 
 namespace aero {
@@ -30,7 +30,8 @@ constexpr int kGemmNT = 512;        // threads per workgroup (8 waves)
 constexpr int kMB = 8, kNB = 4;     // 16 x 16 blocks per wave: 128 rows x 64 columns
 constexpr size_t kGemmStageBytes = 131072;  // two stages of (256 + 256) x 64 bf16
 constexpr size_t kWarmSinkOff = kGemmStageBytes;   // past the stages
-constexpr size_t kGemmLdsBytes = kWarmSinkOff + 2048;   // + a 256-byte sink per wave for the warm-up loads
+constexpr size_t kEpilogueOff = kWarmSinkOff + 2048;   // + a 256-byte sink per wave for the warm-up loads
+constexpr size_t kGemmLdsBytes = kEpilogueOff + 5120;   // + what an epilogue uses: the stages hold the next tile's slices
 
 // Position of an accumulator element inside the 256 x 256 tile.
 //   block (mb, nb) of wave (wm in 0..1, wn in 0..3); register i of lane l:
@@ -50,11 +51,22 @@ __device__ __forceinline__ int acc_col_swapped(int wn, int nb, int lane) { retur
 // 1400 tokens at H = 3584, V = 32000 826 -> 815; 300 tokens at H = 896, V = 8000 102.2 -> 103.7.
 struct WavePos {
   int wm, wn;
-  bool active;   // false: all of the wave's rows (columns) are padding, its accumulators stay zero
+  bool active;            // false: all of the wave's rows (columns) are padding, its accumulators stay zero
+  int warm_a, warm_b;     // this tile's share of the L2 warm-up: bit q is quarter q of the operand's slice
+  int warm_from;          // it is done for tiles of at least this many slices
 };
+// From how many slices on.  With several token tiles: worth 2-4 % per contraction from about 50 slices on, nothing or a
+// small loss at 24, and a loss on the split-K dhidden contraction (the touches are traffic into the CU like any other).  With
+// one token tile every slice of the weight comes from memory for the first time: forward of 200 tokens at H = 1536,
+// V = 151936 162 -> 145 us, dhidden of 250 at H = 3584 297 -> 267 us.
+constexpr int kWarmSlices = 32, kWarmSlicesAlone = 8;
+// A quarter to each of four tiles that have the operand's slice in common, or what fewer of them can share out.
+__device__ __forceinline__ int warm_share(int index, int sharers) {
+  return sharers >= 4 ? 1 << (index & 3) : sharers >= 2 ? 5 << (index & 1) : 15;
+}
 template <bool RAGGED_COLS> __device__ __forceinline__ WavePos wave_pos() {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  return RAGGED_COLS ? WavePos{wave & 1, wave >> 1, true} : WavePos{wave >> 2, wave & 3, true};
+  return RAGGED_COLS ? WavePos{wave & 1, wave >> 1, true, 0, 0, 0} : WavePos{wave >> 2, wave & 3, true, 0, 0, 0};
 }
 
 typedef f32x4_t Acc[kMB][kNB];
@@ -101,13 +113,13 @@ __device__ __forceinline__ int xcd_position(int pid, int n) {
   return pos < n ? pos : -1;
 }
 
-// tile0: position in the tile order of this launch's first tile, n: tiles of this launch (a
-// kernel's tiles may be spread over several launches).  False: a surplus workgroup.
-__device__ __forceinline__ bool tile_of_block(int tiles_m, int tiles_n, int tile0, int n, int& tm, int& tn) {
-  const int pos = xcd_position(blockIdx.x, n);
-  if (pos < 0) return false;
-  tile_of_index(tile0 + pos, tiles_m, tiles_n, tm, tn);
-  return true;
+// The tile that a workgroup of a walking grid (a multiple of 8 workgroups, so that a walk stays on its XCD) has at
+// step pid = blockIdx.x, + gridDim.x, ...  tile0: position in the tile order of the launch's first tile, n: its tiles (a
+// kernel's tiles may be spread over several launches).  False: none, the walk has ended.
+__device__ __forceinline__ bool tile_of_step(int pid, int tiles_m, int tiles_n, int tile0, int n, int& tm, int& tn) {
+  const int pos = xcd_position(pid, n);
+  tile_of_index(tile0 + max(pos, 0), tiles_m, max(tiles_n, 1), tm, tn);
+  return pos >= 0;
 }
 
 // Fragments of one 32-wide K step: lane l holds K 8 (l/16) .. + 7 of row l%16 of a 16-row block.
@@ -128,97 +140,51 @@ __device__ __forceinline__ void frags_mma(const Frags& a, const Frags& b, int ha
     }
 }
 
-// ------------------------------------------------------------------------------------------
-// Register-staged loop (fallback): 256 x 64 slices, double buffered, explicit predication.
-// ------------------------------------------------------------------------------------------
-constexpr int kBK = 64;
-constexpr int kSliceElems = kTile * kBK;
-static_assert(size_t(4) * kSliceElems * 2 <= kGemmStageBytes, "double buffer must fit the LDS budget");
-constexpr int kVecPerThread = kTile * (kBK / 8) / kGemmNT;   // 4
-
-__device__ __forceinline__ void slice_load(const uint16_t* __restrict__ base, int64_t ld, int row0,
-                                           int rows_valid, int k0, int K, u32x4_t (&r)[kVecPerThread]) {
-  const int tid = threadIdx.x;
-#pragma unroll
-  for (int v = 0; v < kVecPerThread; ++v) {
-    const int idx = tid + v * kGemmNT;
-    const int row = row0 + (idx >> 3), k = k0 + ((idx & 7) << 3);
-    if (row < rows_valid && k < K)
-      r[v] = *reinterpret_cast<const u32x4_t*>(base + int64_t(row) * ld + k);
-    else
-      r[v] = u32x4_t{0u, 0u, 0u, 0u};
-  }
-}
+constexpr int kDK = 64;                          // K slice of the loop
+constexpr int kDStageElems = 2 * kTile * kDK;    // A then B
+static_assert(size_t(2) * kDStageElems * 2 <= kGemmStageBytes, "two stages must fit the LDS budget");
 
 // Rows are 128 bytes; rows of equal parity share a 128-byte half of the 256-byte bank line, so
 // the chunk index is swizzled with bits 1..3 of the row: 16 consecutive rows -> 16 distinct slots.
 __device__ __forceinline__ int lds_off(int row, int chunk) {
-  return row * kBK + ((chunk ^ ((row >> 1) & 7)) << 3);
+  return row * kDK + ((chunk ^ ((row >> 1) & 7)) << 3);
 }
 
-__device__ __forceinline__ void slice_store(uint16_t* lds, const u32x4_t (&r)[kVecPerThread]) {
-  const int tid = threadIdx.x;
-#pragma unroll
-  for (int v = 0; v < kVecPerThread; ++v) {
-    const int idx = tid + v * kGemmNT;
-    *reinterpret_cast<u32x4_t*>(lds + lds_off(idx >> 3, idx & 7)) = r[v];
-  }
+// Where a lane finds its fragments in an operand's slice, as LDS byte addresses: `at` per K step or per block, whichever
+// the layout's swizzle makes differ, everything else in the instructions' offsets.  They are kept in registers from slice
+// to slice (formed behind the barrier they cost the first reads 1 % of the dhidden contraction).
+typedef __attribute__((address_space(3))) uint16_t lds_u16_t;
+__device__ __forceinline__ uint32_t lds_address(const uint16_t* p) { return uint32_t(uintptr_t((lds_u16_t*)p)); }
+__device__ __forceinline__ bf16x8_t lds_fragment(uint32_t address) {
+  typedef __attribute__((address_space(3))) const bf16x8_t lds_frag_t;
+  return *(lds_frag_t*)uintptr_t(address);
 }
-
-// Fragments of K step ks (0, 1) of a 64-wide slice held in LDS: four 16-row blocks from row0 on.
-__device__ __forceinline__ void frags_load(Frags& f, const uint16_t* lds, int row0, int ks, int lane) {
+template <int N> struct FragAddr {
+  uint32_t at[N];
+  __device__ __forceinline__ void move(uint32_t by) {
 #pragma unroll
-  for (int i = 0; i < kFragBlocks; ++i)
-    f[i] = *reinterpret_cast<const bf16x8_t*>(lds + lds_off(row0 + i * 16 + (lane & 15), ks * 4 + (lane >> 4)));
-}
-
-template <bool SWAP>
-__device__ __forceinline__ void slice_mma(const uint16_t* As, const uint16_t* Bs, int wm, int wn, int lane, Acc& acc) {
-#pragma unroll
-  for (int ks = 0; ks < kBK / 32; ++ks) {
-    Frags a, b;
-    frags_load(b, Bs, wn * 64, ks, lane);
-#pragma unroll
-    for (int half = 0; half < 2; ++half) {
-      frags_load(a, As, wm * 128 + half * 64, ks, lane);
-      frags_mma<SWAP>(a, b, half, acc);
+    for (int k = 0; k < N; ++k) {
+      at[k] += by;
+      asm volatile("" : "+v"(at[k]));
     }
   }
+};
+// K-contiguous rows, swizzled: at[ks] is K step ks of row row0; block i lies 16 rows behind.
+__device__ __forceinline__ FragAddr<2> frag_addr(const uint16_t* lds, int row0, int lane) {
+  const int row = row0 + (lane & 15), g = lane >> 4;
+  return FragAddr<2>{{lds_address(lds) + lds_off(row, g) * 2, lds_address(lds) + lds_off(row, 4 + g) * 2}};
 }
-
-// Full K loop for one tile.  A rows [m0, m0+256) clipped to M, B rows [n0, n0+256) clipped to
-// N, columns [0, K).  smem: kGemmLdsBytes.  Ends with a barrier: smem is free afterwards.
-template <bool SWAP>
-__device__ __forceinline__ void gemm_tile(const uint16_t* __restrict__ A, int64_t lda, int M,
-                                          const uint16_t* __restrict__ B, int64_t ldb, int N, int K,
-                                          int m0, int n0, const WavePos& pos, uint16_t* smem, Acc& acc) {
-  const int lane = threadIdx.x & 63;
-  const int wm = pos.wm, wn = pos.wn;
-  acc_zero(acc);
-  const int nk = (K + kBK - 1) / kBK;
-  if (nk == 0) return;
-  uint16_t* As[2] = {smem, smem + 2 * kSliceElems};
-  uint16_t* Bs[2] = {smem + kSliceElems, smem + 3 * kSliceElems};
-  u32x4_t ra[kVecPerThread], rb[kVecPerThread];
-  slice_load(A, lda, m0, M, 0, K, ra);
-  slice_load(B, ldb, n0, N, 0, K, rb);
-  slice_store(As[0], ra);
-  slice_store(Bs[0], rb);
-  __syncthreads();
-  for (int kt = 0; kt < nk; ++kt) {
-    const int cur = kt & 1;
-    const bool more = kt + 1 < nk;
-    if (more) {
-      slice_load(A, lda, m0, M, (kt + 1) * kBK, K, ra);
-      slice_load(B, ldb, n0, N, (kt + 1) * kBK, K, rb);
-    }
-    slice_mma<SWAP>(As[cur], Bs[cur], wm, wn, lane, acc);
-    if (more) {
-      slice_store(As[cur ^ 1], ra);
-      slice_store(Bs[cur ^ 1], rb);
-    }
-    __syncthreads();
-  }
+__device__ __forceinline__ void frags_load(Frags& f, const FragAddr<2>& from, int first, int ks) {
+#pragma unroll
+  for (int i = 0; i < kFragBlocks; ++i) f[i] = lds_fragment(from.at[ks] + (first + i) * 16 * kDK * 2);
+}
+// Fragment order: blocks of 2 KB, the two K steps one after the other.
+__device__ __forceinline__ FragAddr<1> frag_addr_af(const uint16_t* lds, int row0, int lane) {
+  return FragAddr<1>{{lds_address(lds) + row0 * kDK * 2 + lane * 16}};
+}
+__device__ __forceinline__ void frags_load(Frags& f, const FragAddr<1>& from, int first, int ks) {
+#pragma unroll
+  for (int i = 0; i < kFragBlocks; ++i) f[i] = lds_fragment(from.at[0] + (first + i) * 2048 + ks * 1024);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -228,32 +194,18 @@ __device__ __forceinline__ void gemm_tile(const uint16_t* __restrict__ A, int64_
 // 256 x 64: every row contributes one full 128-byte line per slice (32-wide slices fetch half
 // lines and lose a tenth of the throughput), two stages of 64 KB.
 //
-// Completion of these loads is tracked by hand: vmcnt(0) at the top of an iteration means this
+// Completion of these loads is tracked by hand: vmcnt(0) in front of the barrier means this
 // wave's part of the slice has landed, the barrier then makes every wave's part visible and
 // also guarantees that the other stage is no longer being read.  The compiler does not model
 // these dependencies, hence the explicit waits and compiler fences.
 // ------------------------------------------------------------------------------------------
-constexpr int kDK = kBK;                         // K slice of the fast loop
-constexpr int kDStageElems = 2 * kTile * kDK;    // A then B
-static_assert(size_t(2) * kDStageElems * 2 <= kGemmStageBytes, "two stages must fit the LDS budget");
-
-// An operand of the fast loop: rows of 64-wide K slices.  Element (row, k) lives at
+// An operand: rows of 64-wide K slices.  Element (row, k) lives at
 //   base + (k / 64) * kstep + row * ld + k % 64
 //   row-major [rows, K]:            ld = row pitch, kstep = 64
 //   K-slab layout [K/64][rows][64]: ld = 64,        kstep = rows * 64  (a 256-row slice is one
 //                                   contiguous 32 KB block: the layout of the library's own
 //                                   intermediate operands)
-// bytes bounds the buffer: loads past it return zeros.
-struct DmaOperand {
-  const uint16_t* base;
-  int64_t ld, kstep, bytes;
-};
-__device__ __forceinline__ DmaOperand operand_row_major(const uint16_t* base, int64_t ld, int rows_valid, int K) {
-  return DmaOperand{base, ld, kDK, rows_valid > 0 ? ((int64_t(rows_valid) - 1) * ld + K) * 2 : 0};
-}
-__device__ __forceinline__ DmaOperand operand_slabs(const uint16_t* base, int64_t rows, int K) {
-  return DmaOperand{base, kDK, rows * kDK, int64_t(K / kDK) * rows * kDK * 2};
-}
+// and loads past its bytes return zeros.
 // K-slabs in fragment order (AF): inside a slab every 16 rows are one 2 KB block, the two 32-wide K steps one after
 // the other, each as the 16 x 16 x 32 instruction's lanes hold it: element (row, k) at
 //   (row / 16) * 1024 + (k % 64 / 32) * 512 + (k % 32 / 8) * 128 + (row % 16) * 8 + k % 8
@@ -262,44 +214,29 @@ __device__ __forceinline__ DmaOperand operand_slabs(const uint16_t* base, int64_
 __device__ __forceinline__ int64_t frag_order_offset(int64_t rows, int64_t row, int64_t k) {
   return (k / 64) * rows * 64 + (row / 16) * 1024 + (k % 64 / 32) * 512 + (k % 32 / 8) * 128 + (row % 16) * 8 + k % 8;
 }
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t operand_rsrc(const DmaOperand& o) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(o.base), 0, int(o.bytes), 0x00020000);
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t operand_rsrc(const uint16_t* base, int64_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(base), 0, int(bytes), 0x00020000);
 }
 
 #define AERO_CFENCE() asm volatile("" ::: "memory")
 
-// Per-lane byte offsets of the DMA loads of one operand.  Wave w fills rows [32 w, 32 w + 32)
-// with 4 instructions of 8 rows; lane l covers row l/8 of those 8 and LDS slot l%8, and the
+// Per-lane byte offsets of the DMA loads of one operand, from the tile's first row on.  Wave w fills rows
+// [32 w, 32 w + 32) with 4 instructions of 8 rows; lane l covers row l/8 of those 8 and LDS slot l%8, and the
 // chunk that belongs in that slot is slot ^ ((row >> 1) & 7) with row = 32 w + 8 j + l/8, i.e.
 // (l % 8) ^ ((4 j + l / 16) & 7): one offset for even j, one for odd j.
 struct DmaLane {
   uint32_t even, odd, row_step, k_step;
 };
-__device__ __forceinline__ DmaLane dma_lane(int row0, const DmaOperand& o, int wave, int lane) {
-  const uint32_t row = uint32_t((int64_t(row0 + wave * 32 + (lane >> 3)) * o.ld) * 2);
-  const uint32_t c0 = uint32_t((lane & 7) ^ ((lane >> 4) & 7)), c1 = uint32_t((lane & 7) ^ ((4 + (lane >> 4)) & 7));
-  return DmaLane{row + c0 * 16, row + c1 * 16, uint32_t(8 * o.ld * 2), uint32_t(o.kstep * 2)};
+__device__ __forceinline__ uint32_t dma_chunk(int lane, int j) { return uint32_t((lane & 7) ^ ((4 * j + (lane >> 4)) & 7)); }
+__device__ __forceinline__ DmaLane dma_lane(int64_t ld, int64_t kstep, int wave, int lane) {
+  const uint32_t row = uint32_t(int64_t(wave * 32 + (lane >> 3)) * ld * 2);
+  return DmaLane{row + dma_chunk(lane, 0) * 16, row + dma_chunk(lane, 1) * 16, uint32_t(8 * ld * 2), uint32_t(kstep * 2)};
 }
 
 // The same for an operand in fragment order: a wave's 32 rows are 4 KB in one piece.
-__device__ __forceinline__ DmaLane dma_lane_af(int row0, const DmaOperand& o, int wave, int lane) {
-  const uint32_t at = uint32_t((row0 + wave * 32) * kDK * 2 + lane * 16);
-  return DmaLane{at, at, 1024u, uint32_t(o.kstep * 2)};
-}
-
-// The whole byte offset travels in the vector offset: the hardware bounds check covers the
-// vector offset only, not the scalar one.
-__device__ __forceinline__ void dma_issue(__amdgpu_buffer_rsrc_t ra, __amdgpu_buffer_rsrc_t rb, const DmaLane& la,
-                                          const DmaLane& lb, int kt, uint16_t* stage, int wave) {
-  uint16_t* a_dst = stage + wave * 32 * kDK;
-  uint16_t* b_dst = stage + kTile * kDK + wave * 32 * kDK;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, a_dst + j * 8 * kDK, 16,
-                                             ((j & 1) ? la.odd : la.even) + uint32_t(kt) * la.k_step + j * la.row_step, 0, 0, 0);
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, b_dst + j * 8 * kDK, 16,
-                                             ((j & 1) ? lb.odd : lb.even) + uint32_t(kt) * lb.k_step + j * lb.row_step, 0, 0, 0);
-  }
+__device__ __forceinline__ DmaLane dma_lane_af(int64_t kstep, int wave, int lane) {
+  const uint32_t at = uint32_t(wave * 32 * kDK * 2 + lane * 16);
+  return DmaLane{at, at, 1024u, uint32_t(kstep * 2)};
 }
 
 // An operand stored the other way round (BT): a row-major matrix whose rows are the contraction index, [K][rows],
@@ -309,167 +246,274 @@ __device__ __forceinline__ void dma_issue(__amdgpu_buffer_rsrc_t ra, __amdgpu_bu
 // receives column j of those four rows, so two reads make the eight K values of a fragment.  The 32-byte
 // segments of a row are XORed with f(row) = row % 4 + 4 ((row / 8) % 2): the eight rows that 32 lanes touch at once
 // fall on distinct banks.
-__device__ __forceinline__ DmaLane dma_lane_bt(int col0, int64_t ld, int wave, int lane) {
+__device__ __forceinline__ DmaLane dma_lane_bt(int64_t ld, int wave, int lane) {
   // wave w fills rows [8 w, 8 w + 8) with 4 instructions of 2 rows; lane l covers chunk l % 32 of row l / 32
-  const uint32_t row = uint32_t(int64_t(wave * 8 + (lane >> 5)) * ld * 2 + int64_t(col0) * 2) + uint32_t(lane & 1) * 16;
+  const uint32_t row = uint32_t(int64_t(wave * 8 + (lane >> 5)) * ld * 2) + uint32_t(lane & 1) * 16;
   const uint32_t seg = (lane & 31) >> 1, f = uint32_t(lane >> 5) | uint32_t(wave & 1) << 2;
   return DmaLane{row + (seg ^ f) * 32, row + (seg ^ (f | 2)) * 32, uint32_t(4 * ld), uint32_t(kDK * ld * 2)};
 }
-__device__ __forceinline__ void frags_load_bt(Frags& f, const uint16_t* lds, int col0, int ks, int lane) {
+__device__ __forceinline__ FragAddr<4> frag_addr_bt(const uint16_t* lds, int col0, int lane) {
+  const int group = lane >> 4, j = lane & 15;
+  const int swz = (j >> 2) | (group & 1) << 2;
+  FragAddr<4> a;
+#pragma unroll
+  for (int i = 0; i < kFragBlocks; ++i)
+    a.at[i] = lds_address(lds) + ((group * 8 + (j >> 2)) * kTile + (j & 3) * 4 + ((col0 / 16 + i) ^ swz) * 16) * 2;
+  return a;
+}
+__device__ __forceinline__ void frags_load(Frags& f, const FragAddr<4>& from, int, int ks) {
   typedef short s16x4_t __attribute__((ext_vector_type(4)));
   typedef short s16x8_t __attribute__((ext_vector_type(8)));
   typedef __attribute__((address_space(3))) s16x4_t lds_s16x4_t;
-  const int group = lane >> 4, j = lane & 15;
-  const int swz = (j >> 2) | (group & 1) << 2;
-  const uint16_t* base = lds + (ks * 32 + group * 8 + (j >> 2)) * kTile + (j & 3) * 4;
 #pragma unroll
   for (int i = 0; i < kFragBlocks; ++i) {
-    const uint16_t* at = base + ((col0 / 16 + i) ^ swz) * 16;
-    const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)at);
-    const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)(at + 4 * kTile));
+    const uint32_t at = from.at[i] + ks * 32 * kTile * 2;
+    const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)uintptr_t(at));
+    const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)uintptr_t(at + 4 * kTile * 2));
     const s16x8_t both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
     f[i] = __builtin_bit_cast(bf16x8_t, both);
   }
 }
 
-// WARM: L2 warm-up two slices ahead (see below); a few per cent on the contractions whose
-// operands come from large read-only arrays, a loss on the split-K dhidden contraction.
-// BT: operand B is [K][rows] (B.base, B.ld, B.bytes; B.kstep is not looked at).  AF: operand A is in K-slabs in
-// fragment order (m0 a multiple of 16).  SKIP: waves with pos.active == false only move operands.
-template <bool WARM, bool SWAP, bool BT = false, bool AF = false, bool SKIP = false>
-__device__ __forceinline__ void gemm_tile_dma(const DmaOperand& A, const DmaOperand& B, int K, int m0, int n0,
-                                              const WavePos& pos, uint16_t* smem, Acc& acc) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wm = pos.wm, wn = pos.wn;
-  acc_zero(acc);
-  const int nk = K / kDK;
-  if (nk == 0) return;
-  const __amdgpu_buffer_rsrc_t ra = operand_rsrc(A), rb = operand_rsrc(B);
-  static_assert(!(WARM && BT), "the warm-up assumes K-contiguous operands");
-  const DmaLane la = AF ? dma_lane_af(m0, A, wave, lane) : dma_lane(m0, A, wave, lane);
-  const DmaLane lb = BT ? dma_lane_bt(n0, B.ld, wave, lane) : dma_lane(n0, B, wave, lane);
-  auto load_b = [&](Frags& f, const uint16_t* Bs, int ks) {
-    if constexpr (BT) frags_load_bt(f, Bs, wn * 64, ks, lane);
-    else frags_load(f, Bs, wn * 64, ks, lane);
-  };
-  auto load_a = [&](Frags& f, const uint16_t* As, int half, int ks) {
-    if constexpr (AF) {
-#pragma unroll
-      for (int i = 0; i < kFragBlocks; ++i)
-        f[i] = *reinterpret_cast<const bf16x8_t*>(As + (wm * 8 + half * kFragBlocks + i) * 1024 + ks * 512 + lane * 8);
-    } else {
-      frags_load(f, As, wm * 128 + half * 64, ks, lane);
-    }
-  };
-  dma_issue(ra, rb, la, lb, 0, smem, wave);
-  // L2 warm-up.  A fifth of a slice's lines miss L2 (the 32 workgroups resident on an XCD form an
-  // 8 x 4 block of tiles: 12 operand slices for 32 tiles), and loads return in order, so one late
-  // line holds back everything queued behind it.  Each slice is therefore touched two slices
-  // early with one 4-byte load per 128-byte line (sunk into a scratch corner of LDS), the lines
-  // shared out over the workgroups that will read them: wave 0 takes a quarter of the A rows
-  // (which quarter: by tile column), wave 4 an eighth of the B rows (by tile row).  The touch is
-  // issued late in the slice, when every wave's requests for the next slice are already queued
-  // ahead of it, and it may stay in flight across the next barrier (vmcnt(1)).
-  constexpr int kWarmAhead = 2;
-  const int wave_u = __builtin_amdgcn_readfirstlane(wave);   // wave-uniform: the descriptor stays scalar
-  const bool warm_a = wave_u < 4, warm_wave = WARM && (wave_u & 3) == 0;
-  const __amdgpu_buffer_rsrc_t rw = warm_a ? ra : rb;
-  const int warm_row = warm_a ? m0 + ((n0 / kTile) & 3) * 64 + lane : n0 + ((m0 / kTile) & 7) * 32 + (lane & 31);
-  const uint32_t warm_off = uint32_t(int64_t(warm_row) * (warm_a ? A.ld : B.ld) * 2) + (warm_a ? 0u : uint32_t(lane >> 5) * 64u);
-  const uint32_t warm_kstep = uint32_t((warm_a ? A.kstep : B.kstep) * 2);
-  uint16_t* const warm_sink = smem + kWarmSinkOff / 2 + wave * 128;
-  if constexpr (SKIP) {
-    if (!pos.active) {   // uniform over the wave: its part of the transfers, the same barriers, no arithmetic
-      for (int kt = 0; kt < nk; ++kt) {
-        __builtin_amdgcn_s_waitcnt(0x0070);   // vmcnt(0) lgkmcnt(0)
-        AERO_CFENCE();
-        __builtin_amdgcn_s_barrier();
-        AERO_CFENCE();
-        if (kt + 1 < nk) dma_issue(ra, rb, la, lb, kt + 1, smem + ((kt + 1) & 1) * kDStageElems, wave);
-      }
-      __syncthreads();
-      return;
-    }
-  }
-  // One iteration = one 64-wide slice = two 32-wide K steps of two halves, 16 MFMAs per wave each.
-  // The order is pinned with scheduling barriers: the first step's fragments are read up front, the
-  // next slice is requested only after the first MFMA group (issuing the 8 loads right after the
-  // barrier would hold back every wave's first MFMAs: measured 8 % slower), and the other fragment
-  // reads are interleaved with MFMAs, two per read.
-  // warm: touch slice kt + kWarmAhead; warm_pending: the previous slice issued a touch.
-  auto slice = [&](int kt, bool prefetch, bool warm, bool warm_pending) {
-    // slice kt landed (the youngest load may be a touch: loads return in order), own LDS reads done
-    if (warm_pending && warm_wave) __builtin_amdgcn_s_waitcnt(0x0071);   // vmcnt(1) lgkmcnt(0)
-    else __builtin_amdgcn_s_waitcnt(0x0070);                             // vmcnt(0) lgkmcnt(0)
-    AERO_CFENCE();
-    __builtin_amdgcn_s_barrier();
-    AERO_CFENCE();
-    const uint16_t* As = smem + (kt & 1) * kDStageElems;
-    const uint16_t* Bs = As + kTile * kDK;
-    Frags b0, b1, a0, a1, a2;
-    load_a(a0, As, 0, 0);
-    load_b(b0, Bs, 0);
-    load_a(a1, As, 1, 0);
-    frags_mma<SWAP>(a0, b0, 0, acc);
-    if (prefetch) dma_issue(ra, rb, la, lb, kt + 1, smem + ((kt + 1) & 1) * kDStageElems, wave);
-    load_a(a2, As, 0, 1);
-    load_b(b1, Bs, 1);
-    frags_mma<SWAP>(a1, b0, 1, acc);
-    load_a(a0, As, 1, 1);
-    frags_mma<SWAP>(a2, b1, 0, acc);
-    constexpr int kMfma = 0x008, kVmemRd = 0x020, kDsRd = 0x100;
-    constexpr int kMfmas = kFragBlocks * kNB;
-    constexpr int kReadsB = BT ? 2 * kFragBlocks : kFragBlocks;
-    __builtin_amdgcn_sched_group_barrier(kDsRd, 2 * kFragBlocks + kReadsB, 0);
-    __builtin_amdgcn_sched_group_barrier(kMfma, kMfmas, 0);
-    if (prefetch) __builtin_amdgcn_sched_group_barrier(kVmemRd, 8, 0);
-#pragma unroll
-    for (int r = 0; r < kFragBlocks; ++r) {
-      __builtin_amdgcn_sched_group_barrier(kMfma, 2, 0);
-      __builtin_amdgcn_sched_group_barrier(kDsRd, 1, 0);
-      __builtin_amdgcn_sched_group_barrier(kMfma, 2, 0);
-      __builtin_amdgcn_sched_group_barrier(kDsRd, kReadsB / kFragBlocks, 0);
-    }
-#pragma unroll
-    for (int r = 0; r < kFragBlocks; ++r) {
-      __builtin_amdgcn_sched_group_barrier(kMfma, 2, 0);
-      __builtin_amdgcn_sched_group_barrier(kDsRd, 1, 0);
-    }
-    __builtin_amdgcn_sched_group_barrier(kMfma, 2 * kMfmas - 6 * kFragBlocks, 0);
-    if (WARM) {
-      __builtin_amdgcn_sched_barrier(0);
-      if (warm && warm_wave)
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, warm_sink, 4, warm_off + uint32_t(kt + kWarmAhead) * warm_kstep, 0, 0, 0);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    frags_mma<SWAP>(a0, b1, 1, acc);
-    if (!WARM) __builtin_amdgcn_sched_group_barrier(kMfma, kMfmas, 0);
-  };
-  // Every call site passes constants, so that each copy of the slice is one scheduling region.
-  // Measured: worth 2-4 % per contraction from about 50 slices on, nothing or a small loss at 24.
-  constexpr int kWarmMinSlices = 32;
-  if (WARM && nk >= kWarmMinSlices) {   // slice kt touches slice kt + 2: all but the last two do
-    slice(0, true, true, false);
-    for (int kt = 1; kt + kWarmAhead < nk; ++kt) slice(kt, true, true, true);
-    slice(nk - 2, true, false, true);
-    slice(nk - 1, false, false, false);
-  } else {
-    for (int kt = 0; kt + 1 < nk; ++kt) slice(kt, true, false, false);
-    slice(nk - 1, false, false, false);
-  }
-  __syncthreads();
+__device__ __forceinline__ void slice_barrier() {
+  AERO_CFENCE();
+  __builtin_amdgcn_s_barrier();
+  AERO_CFENCE();
+}
+// Barrier of an epilogue that exchanges through LDS: waits for the wave's own LDS accesses, not for the next tile's
+// operands on their way, as __syncthreads would.
+__device__ __forceinline__ void lds_barrier() {
+  AERO_CFENCE();
+  __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0)
+  slice_barrier();
+}
+// A copy that the compiler does not see through: what an epilogue derives from it is formed per tile, not kept in
+// registers beside the main loop's.
+__device__ __forceinline__ int opaque(int v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+// Nothing that a wave has requested into LDS is on its way when it leaves.
+__device__ __forceinline__ void end_of_walk() {
+  AERO_CFENCE();
+  __builtin_amdgcn_s_waitcnt(0x0070);
 }
 
-// Picks the fast loop when its preconditions hold (uniform over the launch).
-__device__ __forceinline__ void gemm_tile_auto(const uint16_t* __restrict__ A, int64_t lda, int M,
-                                               const uint16_t* __restrict__ B, int64_t ldb, int N, int K,
-                                               int m0, int n0, const WavePos& pos, uint16_t* smem, Acc& acc) {
-  const bool fast = (K % kDK == 0) && (lda % 8 == 0) && (ldb % 8 == 0) &&
-                    (reinterpret_cast<uintptr_t>(A) % 16 == 0) && (reinterpret_cast<uintptr_t>(B) % 16 == 0) &&
-                    ((int64_t(M) - 1) * lda + K) < (int64_t(1) << 31) && ((int64_t(N) - 1) * ldb + K) < (int64_t(1) << 31);
-  if (fast) gemm_tile_dma<true, false, false, false, true>(operand_row_major(A, lda, M, K), operand_row_major(B, ldb, N, K), K, m0,
-                                                           n0, pos, smem, acc);
-  else gemm_tile<false>(A, lda, M, B, ldb, N, K, m0, n0, pos, smem, acc);
-}
+// One tile's operands: where its K range starts in each (a: bytes from a_base to row m0's first slice, likewise b), the
+// bytes that bound them, and how many slices there are.
+struct TileSrc {
+  const uint16_t *a_base, *b_base;
+  int64_t a_bytes, b_bytes;
+  uint32_t a, b;
+  int nk;
+};
+
+// What follows a workgroup's last tile: no bytes, so that requesting it moves nothing.
+__device__ __forceinline__ TileSrc no_tile(const TileSrc& t) { return TileSrc{t.a_base, t.b_base, 0, 0, 0u, 0u, 1}; }
+
+// The main loop of a workgroup that walks tiles.  Slices form one stream across tiles: every slice requests the next one,
+// and a tile's last slice the next tile's first, so that a tile's epilogue runs while its successor's operands are on
+// their way.  A workgroup per tile lost between 3 and 8 us a tile to the launch, the first slice's latency and
+// the drain of the stores, of 45 us at 24 slices and 17 at 7.  Tile by tile / walking: k_fused_stats<true> with 16384 tokens at
+// H = 1536, V = 151936 6.72 / 6.44 ms, at H = 3584 13.88 / 13.77, 1200 tokens 614 / 595 us; k_gemm_dw 600 tokens 229 / 215 us, with
+// 16384 tokens (160 slices) 1-2 % slower.  Tried on top and not taken: starts staggered over the CUs (0 to +20 %: tiles
+// do not wait for each other's stores), waves 4 to 7 free of loads and warming L2 four slices ahead (dweight of 1000
+// tokens -8 %, everything long +3 to +12 %: bytes into the CU are what counts).
+// WARM: L2 warm-up two slices ahead (see kWarmSlices).
+// BT: operand B is [K][rows].  AF: operand A is in K-slabs in fragment order (tiles start at multiples of 16 rows).
+// TAIL: K need not be a multiple of 64: the 16-byte chunks of the last slice that lie past a row's end are requested from
+// behind the buffer, which gives zeros.
+template <bool WARM, bool SWAP, bool BT, bool AF, bool TAIL>
+struct GemmStream {
+  DmaLane la, lb;
+  int lane, wave, stage;   // stage: where the next slice lies
+  int tail;                // 16-byte chunks of a row's last slice
+
+  // lda, ldb: row pitches; kstep_a, kstep_b: elements between slices; K: the row length with TAIL
+  __device__ __forceinline__ GemmStream(int64_t lda, int64_t kstep_a, int64_t ldb, int64_t kstep_b, int K) {
+    lane = threadIdx.x & 63;
+    wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    stage = 0;
+    la = AF ? dma_lane_af(kstep_a, wave, lane) : dma_lane(lda, kstep_a, wave, lane);
+    lb = BT ? dma_lane_bt(ldb, wave, lane) : dma_lane(ldb, kstep_b, wave, lane);
+    tail = TAIL ? (K - 1) % kDK / 8 + 1 : 8;
+  }
+
+  // Requests slice kt of a tile into a stage; LAST: it may be the tile's last one.  The whole byte offset travels in the vector offset: the hardware bounds
+  // check covers the vector offset only, not the scalar one.
+  template <bool LAST>
+  __device__ __forceinline__ void issue(const TileSrc& t, int kt, uint16_t* to) {
+    const __amdgpu_buffer_rsrc_t ra = operand_rsrc(t.a_base, t.a_bytes), rb = operand_rsrc(t.b_base, t.b_bytes);
+    uint16_t* a_dst = to + wave * 32 * kDK;
+    uint16_t* b_dst = to + kTile * kDK + wave * 32 * kDK;
+    const uint32_t a = t.a + uint32_t(kt) * la.k_step, b = t.b + uint32_t(kt) * lb.k_step;
+    uint32_t past_even = 0, past_odd = 0;   // all ones (but 16) where the lane's chunk does not exist
+    if constexpr (TAIL && LAST) {
+      const int l = opaque(lane), chunks = kt + 1 == t.nk ? tail : 8;
+      past_even = int(dma_chunk(l, 0)) >= chunks ? ~15u : 0u;
+      past_odd = int(dma_chunk(l, 1)) >= chunks ? ~15u : 0u;
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      uint32_t oa = ((j & 1) ? la.odd : la.even) + (a + j * la.row_step), ob = ((j & 1) ? lb.odd : lb.even) + (b + j * lb.row_step);
+      if constexpr (TAIL && LAST) {
+        oa |= (j & 1) ? past_odd : past_even;
+        ob |= (j & 1) ? past_odd : past_even;
+      }
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, a_dst + j * 8 * kDK, 16, oa, 0, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, b_dst + j * 8 * kDK, 16, ob, 0, 0, 0);
+    }
+  }
+
+  __device__ __forceinline__ void start(const TileSrc& t, uint16_t* smem) { issue<true>(t, 0, smem + stage * kDStageElems); }
+
+  // acc = the tile's product.  Its first slice has been requested; on return the first one of `next` has (one of no bytes,
+  // which moves nothing, if the walk ends here).  PENDING: how many memory operations every wave is sure to have issued
+  // since then, in program order, if `stores` (they need not have completed).
+  // active == false: all of the wave's rows (columns) are padding, it only moves operands.
+  template <int PENDING>
+  __device__ __forceinline__ void run(const TileSrc& t, const TileSrc& next, const WavePos& pos, bool stores, uint16_t* smem, Acc& acc) {
+    const int wm = pos.wm, wn = pos.wn, nk = t.nk;
+    acc_zero(acc);
+    // the first slice has landed: requested before the epilogue's stores
+    if (stores) __builtin_amdgcn_s_waitcnt(0x0070 | (PENDING & 15) | (PENDING >> 4) << 14);
+    else __builtin_amdgcn_s_waitcnt(0x0070);   // vmcnt(0) lgkmcnt(0)
+    slice_barrier();
+    if (!pos.active) {   // uniform over the wave: its part of the transfers, the same barriers, no arithmetic
+      for (int kt = 0; kt + 1 < nk; ++kt) {
+        issue<true>(t, kt + 1, smem + (stage ^ 1) * kDStageElems);
+        stage ^= 1;
+        __builtin_amdgcn_s_waitcnt(0x0070);
+        slice_barrier();
+      }
+      issue<true>(next, 0, smem + (stage ^ 1) * kDStageElems);
+      stage ^= 1;
+      return;
+    }
+    // L2 warm-up.  A fifth of a slice's lines miss L2 (the 32 workgroups resident on an XCD form an
+    // 8 x 4 block of tiles: 12 operand slices for 32 tiles), and loads return in order, so one late
+    // line holds back everything queued behind it.  Each slice is therefore touched two slices
+    // early with one 4-byte load per 128-byte line (sunk into a scratch corner of LDS), the lines
+    // shared out over the workgroups that will read them (warm_share): wave q takes quarter q of the A rows, wave
+    // 4 + q of the B rows (BT: of each row's columns).  The touch is issued late in the slice, when every wave's
+    // requests for the next slice are already queued ahead of it, and it may stay in flight across the next barrier
+    // (vmcnt(1)).
+    constexpr int kWarmAhead = 2;
+    const bool warm_a = wave < 4;
+    const bool warm_wave = ((warm_a ? pos.warm_a : pos.warm_b) >> (wave & 3)) & 1;
+    const __amdgpu_buffer_rsrc_t rw = warm_a ? operand_rsrc(t.a_base, t.a_bytes) : operand_rsrc(t.b_base, t.b_bytes);
+    const uint32_t warm_off = warm_a ? t.a + uint32_t(wave * 64 + lane) * (la.row_step / 8)
+                              : BT   ? t.b + uint32_t(lane) * (lb.k_step / kDK) + uint32_t(wave & 3) * 128
+                                     : t.b + uint32_t((wave & 3) * 64 + lane) * (lb.row_step / 8);
+    const uint32_t warm_kstep = warm_a ? la.k_step : lb.k_step;
+    uint16_t* const warm_sink = smem + kWarmSinkOff / 2 + wave * 128;
+    const uint16_t* const first = smem + stage * kDStageElems;
+    auto fa = [&] {
+      if constexpr (AF) return frag_addr_af(first, wm * 128, lane);
+      else return frag_addr(first, wm * 128, lane);
+    }();
+    auto fb = [&] {
+      if constexpr (BT) return frag_addr_bt(first + kTile * kDK, wn * 64, lane);
+      else return frag_addr(first + kTile * kDK, wn * 64, lane);
+    }();
+    // One iteration = one 64-wide slice = two 32-wide K steps of two halves, 16 MFMAs per wave each.
+    // The order is pinned with scheduling barriers: the first step's fragments are read up front, the
+    // next slice is requested only after the first MFMA group (issuing the 8 loads right after the
+    // barrier would hold back every wave's first MFMAs: measured 8 % slower), and the other fragment
+    // reads are interleaved with MFMAs, two per read.
+    // (src, kn): the slice after this one; touch: the one that is touched.
+    auto slice = [&](auto last, auto touching, const TileSrc& src, int kn, int touch) {
+      Frags b0, b1, a0, a1, a2;
+      constexpr int kMfma = 0x008, kVmemRd = 0x020, kDsRd = 0x100;
+      constexpr int kMfmas = kFragBlocks * kNB;
+      frags_load(a0, fa, 0, 0);
+      frags_load(b0, fb, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);   // these first: the matrix instructions start with them
+      frags_load(a1, fa, kFragBlocks, 0);
+      // The compiler lets a transposing read wait for every load into LDS that it finds on its way, the next slice's
+      // too (the loop of 600 tokens' dhidden stood still for their latency, 2.0 us a slice): all of them come before the request.
+      if constexpr (BT) frags_load(b1, fb, 0, 1);
+      frags_mma<SWAP>(a0, b0, 0, acc);
+      issue<decltype(last)::value>(src, kn, smem + (stage ^ 1) * kDStageElems);
+      frags_load(a2, fa, 0, 1);
+      if constexpr (!BT) frags_load(b1, fb, 0, 1);
+      frags_mma<SWAP>(a1, b0, 1, acc);
+      frags_load(a0, fa, kFragBlocks, 1);
+      frags_mma<SWAP>(a2, b1, 0, acc);
+      if constexpr (BT) {
+        __builtin_amdgcn_sched_group_barrier(kDsRd, kFragBlocks, 0);
+#pragma unroll
+        for (int r = 0; r < kFragBlocks; ++r) {
+          __builtin_amdgcn_sched_group_barrier(kMfma, 2, 0);
+          __builtin_amdgcn_sched_group_barrier(kDsRd, 2, 0);
+        }
+        __builtin_amdgcn_sched_group_barrier(kMfma, kMfmas - 2 * kFragBlocks, 0);
+        __builtin_amdgcn_sched_group_barrier(kVmemRd, 8, 0);
+#pragma unroll
+        for (int r = 0; r < kFragBlocks; ++r) {
+          __builtin_amdgcn_sched_group_barrier(kMfma, 4, 0);
+          __builtin_amdgcn_sched_group_barrier(kDsRd, 1, 0);
+        }
+      } else {
+        __builtin_amdgcn_sched_group_barrier(kDsRd, kFragBlocks, 0);
+        __builtin_amdgcn_sched_group_barrier(kMfma, kMfmas, 0);
+        __builtin_amdgcn_sched_group_barrier(kVmemRd, 8, 0);
+#pragma unroll
+        for (int r = 0; r < 2 * kFragBlocks; ++r) {
+          __builtin_amdgcn_sched_group_barrier(kMfma, 2, 0);
+          __builtin_amdgcn_sched_group_barrier(kDsRd, 1, 0);
+        }
+      }
+#pragma unroll
+      for (int r = 0; r < kFragBlocks; ++r) {
+        __builtin_amdgcn_sched_group_barrier(kMfma, 2, 0);
+        __builtin_amdgcn_sched_group_barrier(kDsRd, 1, 0);
+      }
+      __builtin_amdgcn_sched_group_barrier(kMfma, 2 * kMfmas - 6 * kFragBlocks, 0);
+      constexpr bool kTouch = decltype(touching)::value;
+      if constexpr (kTouch) {
+        __builtin_amdgcn_sched_barrier(0);
+        if (warm_wave)
+          __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, warm_sink, 4, warm_off + uint32_t(touch) * warm_kstep, 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      frags_mma<SWAP>(a0, b1, 1, acc);
+      if constexpr (!kTouch) __builtin_amdgcn_sched_group_barrier(kMfma, kMfmas, 0);
+      stage ^= 1;
+      __builtin_amdgcn_sched_barrier(0);   // what follows stays behind the last matrix instruction
+    };
+    auto landed = [&](auto touched) {   // the next slice (the youngest load may be a touch: loads return in order), own LDS reads done
+      const uint32_t by = stage ? uint32_t(kDStageElems * 2) : 0u - uint32_t(kDStageElems * 2);   // stage: that slice's
+      fa.move(by);
+      fb.move(by);
+      if (decltype(touched)::value && warm_wave) __builtin_amdgcn_s_waitcnt(0x0071);   // vmcnt(1) lgkmcnt(0)
+      else __builtin_amdgcn_s_waitcnt(0x0070);
+      slice_barrier();
+    };
+    constexpr std::false_type kNo{};
+    constexpr std::true_type kYes{};
+    constexpr int kPeel = TAIL ? 2 : 1;
+    // A scalar load on its way into the loop (an argument that only the epilogue needs) would make the compiler wait for
+    // every fragment before the first matrix instruction of each slice.
+    __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0)
+    int kt = 0;
+    if constexpr (WARM) {
+      if (nk >= pos.warm_from)
+        for (; kt + kWarmAhead < nk; ++kt) {
+          slice(kNo, kYes, t, kt + 1, kt + kWarmAhead);
+          landed(kYes);
+        }
+    }
+    for (; kt + kPeel < nk; ++kt) {
+      slice(kNo, kNo, t, kt + 1, 0);
+      landed(kNo);
+    }
+    if (TAIL && kt + 1 < nk) {
+      slice(kYes, kNo, t, kt + 1, 0);
+      landed(kNo);
+    }
+    slice(kYes, kNo, next, 0, 0);
+  }
+};
 
 }  // namespace aero

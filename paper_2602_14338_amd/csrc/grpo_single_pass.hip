@@ -565,11 +565,7 @@ static aero_status single_pass_launch_t(const RowArgs& r, int32_t* row_counter, 
                                     kLdsBytes);
     });
     if (attr_rc != hipSuccess) return AERO_ERR_HIP;
-    int dev = 0, cus = 256;
-    if (hipGetDevice(&dev) == hipSuccess) {
-      int n = 0;
-      if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0) cus = n;
-    }
+    const int cus = compute_units();
     const unsigned grid = unsigned(r.T < cus ? r.T : cus);   // one persistent workgroup per CU
     hipLaunchKernelGGL(k_set_counter, dim3(1), dim3(1), 0, s, row_counter, int32_t(grid));
     hipLaunchKernelGGL(k_row_order, dim3(unsigned((r.T + 255) / 256)), dim3(256), 0, s, r.T, r.V, r.R, r.targets,

@@ -25,8 +25,9 @@
 //           k_gemm_dh        dhidden partials = (P or dz) @ weight   (split-K over the vocabulary, fp32)
 //           k_gemm_dw        dweight = (P or dz)^T @ (scale * hidden)
 //           k_scatter_dh     fp32 partials summed in fixed order, times scale -> bf16 dhidden at the original rows
-// All contractions use the same 256 x 256 x 64 MFMA tile, both operands K-contiguous but for the weight in k_gemm_dh<true>,
-// whose rows are the contraction index and which a transposing LDS read turns (see kDirectRows).
+// All contractions use the same 256 x 256 x 64 MFMA tile, both operands K-contiguous but for the weight in k_gemm_dh,
+// whose rows are the contraction index and which a transposing LDS read turns.  In all but k_gemm_dh (whose split count
+// fills the CUs once or twice) a workgroup per CU walks the tiles.
 #include <mutex>
 
 #include "gemm_tile.h"
@@ -45,9 +46,8 @@ inline size_t up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 struct FusedPlan {
   int64_t T, T_pad;
   int V, V_ld, H, H_pad, tiles_v, VC, n_chunks;   // VC: vocabulary rows per chunk of the transposed dz
-  bool direct;   // dhidden reads the weight as it is, no transposed copy
   size_t off_part, off_fidx, off_nf, off_term, off_flag, off_zy, off_pos, off_nact, off_gc, off_lsec, off_yc, off_ac, off_bc, off_scale,
-      off_hc, off_hTc, off_WT, off_dz, off_dzT, off_dhacc, total;
+      off_hc, off_hTc, off_dz, off_dzT, off_dhacc, total;
 };
 
 // dhidden is formed as S split-K partials of the active rows, S chosen on the device so that
@@ -71,15 +71,6 @@ static int64_t dh_part_rows(int64_t T_pad, int H, int V_ld) {
   const int64_t by_cap = 64 * T_pad;                                                // S <= 64
   return by_grid < by_cap ? by_grid : by_cap;                                       // >= S * active rows for every S
 }
-
-// The dhidden contraction wants the weight with the vocabulary as the contiguous index.  Copying it into
-// that form costs a read and a write of the weight per call whatever the token count (165 us at H = 1536, 430 at
-// H = 3584 with V = 152 K); reading it as it is through the transposing LDS read makes the contraction
-// itself 13-15 % slower (LDS bound).  The two meet near 2800 candidate rows whatever V and H are, and the host knows only
-// the rows.  Whole calls, time with the copy / as it is, H from 896 to 3584, V from 32000 to 152064: two thirds of the rows
-// candidates 1.03-1.05 at 2048 rows, 1.00-1.02 at 3072, 0.99-1.01 at 4096; all of them 1.01-1.04, 0.99-1.01 and
-// 0.98-1.00.  300 tokens at H = 1536, V = 151936 1012 / 841 us; 5000 and 7000 tokens even.
-constexpr int64_t kDirectRows = 4096;
 
 static FusedPlan make_plan(int64_t T, int V, int H) {
   FusedPlan p{};
@@ -115,8 +106,6 @@ static FusedPlan make_plan(int64_t T, int V, int H) {
   p.off_scale = take(size_t(p.T_pad) * 4);
   p.off_hc = take(size_t(p.T_pad) * H * 2);
   p.off_hTc = take(size_t(p.H_pad) * p.T_pad * 2);
-  p.direct = p.T_pad <= kDirectRows;
-  p.off_WT = take(p.direct ? 0 : size_t(p.H_pad) * p.V_ld * 2);
   p.off_dz = take(size_t(p.T_pad) * p.V_ld * 2);
   p.off_dzT = take(size_t(p.n_chunks) * p.VC * p.T_pad * 2);
   p.off_dhacc = take(size_t(dh_part_rows(p.T_pad, H, p.V_ld)) * H * 4);
@@ -275,76 +264,65 @@ __global__ __launch_bounds__(256) void k_gather_rows(const uint16_t* __restrict_
   if (lane == 0) zy[j] = dot;
 }
 
-// Exchange with a neighbouring lane inside a quad by a lane permutation of the vector ALU (no LDS traffic).
-template <int CTRL> __device__ __forceinline__ uint32_t quad_perm(uint32_t v) {
-  return uint32_t(__builtin_amdgcn_update_dpp(0, int(v), CTRL, 0xf, 0xf, true));
-}
-constexpr int kQuadXor1 = 0xB1, kQuadXor2 = 0x4E;   // quad_perm [1,0,3,2] and [2,3,0,1]
-// The value of the lane four apart (lane ^ 4): a shift down for the lower four of eight, a shift up for the others.
-__device__ __forceinline__ uint32_t xor4_lane(uint32_t v) {
-  const int low = __builtin_amdgcn_update_dpp(0, int(v), 0x104, 0xf, 0x5, false);       // row_shl:4
-  return uint32_t(__builtin_amdgcn_update_dpp(low, int(v), 0x114, 0xf, 0xa, false));    // row_shr:4
-}
-
 // A 256 x 256 bf16 tile (vocabulary rows m0.., token columns n0..) held as packed pairs in the accumulator
 // layout, pk[nb][mb] = the four rows acc_row(wm, mb, 0 .. 3) of column acc_col(wn, nb), leaves in the two
 // layouts the gradient contractions read, both K-slabs in fragment order (frag_order_offset): tokens x vocabulary, and
-// vocabulary chunk by chunk x tokens.  Lanes exchange until each holds eight consecutive K values, and every
-// instruction stores one 1 KB block, so nothing is staged in LDS and no wave waits for another.  (Staged through LDS in
-// both orientations, with four barriers: k_fused_stats 6.98 ms with 16384 tokens at H = 1536, 6.81 this way; whole
-// calls 15.24 / 15.06 ms, with 600 tokens 1045 / 1020 us.)
-__device__ __forceinline__ void store_tile_both_layouts(const uint32_t (&pk)[kNB][kMB][2], const WavePos& wp, int m0, int n0,
+// vocabulary chunk by chunk x tokens.  Every instruction stores one 1 KB block, so nothing is staged in LDS and no wave
+// waits for another.  A block is turned round by the matrix unit: its registers are also the left operand
+// of a 16 x 16 x 16 instruction (rows = tokens), and times the identity it comes back exactly with the tokens in a lane's
+// registers and the vocabulary across the lanes - one instruction and two conversions in place of some twenty exchanges and
+// selections between lanes.
+constexpr int kTileStores = 2 * kNB * kMB / 2;   // per wave
+__device__ __forceinline__ void store_tile_both_layouts(const uint32_t (&pk)[kNB][kMB][2], const WavePos& wp, int lane, int m0, int n0,
                                                         int64_t T_pad, int VC, uint16_t* __restrict__ dz, uint16_t* __restrict__ dzT) {
-  const int lane = threadIdx.x & 63;
-  const int wm = wp.wm, wn = wp.wn;
+  typedef short s16x4_t __attribute__((ext_vector_type(4)));
+  typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
   const int group = lane >> 4;
-  // ---- tokens x vocabulary: the odd 16-lane rows of one block change places with the even ones of the next; lane
-  // group 0 then holds vocabulary 0..7 of its token, group 2 8..15, group 1 16..23, group 3 24..31 ----
-  const int v0 = m0 + wm * 128, t0 = n0 + wn * 64;   // multiples of 64: the wave's slab and token positions
-  uint16_t* const dst = dz + frag_order_offset(T_pad, t0 + (lane & 15), v0 + (group & 1) * 16 + (group >> 1) * 8);
+  constexpr int kNonTemporal = 2;
+  // Two neighbouring blocks along K: the odd 16-lane rows of the first change places with the even ones of the second; lane
+  // group 0 then holds K 0..7 of its row, group 2 8..15, group 1 16..23, group 3 24..31.
+  auto store = [&](__amdgpu_buffer_rsrc_t to, const u32x2_t& first, const u32x2_t& second, uint32_t lane_off, uint32_t off) {
+    const auto lo = __builtin_amdgcn_permlane16_swap(first.x, second.x, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap(first.y, second.y, false, false);
+    // The whole offset in the vector register: with a part of it in a scalar one the compiler writes the data registers
+    // again in the very next instruction, and some lanes stored the values of the block behind.
+    __builtin_amdgcn_raw_buffer_store_b128(u32x4_t{lo[0], hi[0], lo[1], hi[1]}, to, lane_off + off, 0, kNonTemporal);
+  };
+  const uint32_t in_block = uint32_t((lane & 15) * 8 + ((group & 1) * 2 + (group >> 1)) * 128) * 2;   // row lane % 16, that K
+  // ---- tokens x vocabulary: four slabs of T_pad rows; the wave's 128 vocabulary rows are two of them ----
+  const uint32_t slab = uint32_t(T_pad) * 128;   // bytes
+  const __amdgpu_buffer_rsrc_t rz = __builtin_amdgcn_make_buffer_rsrc(dz + int64_t(m0 / 64) * T_pad * 64, 0, int(4 * slab), 0x00020000);
+  const uint32_t at = uint32_t(n0 + wp.wn * 64) * 128 + wp.wm * 2 * slab;
 #pragma unroll
   for (int nb = 0; nb < kNB; ++nb)
 #pragma unroll
-    for (int mb = 0; mb < kMB; mb += 2) {
-      const auto lo = __builtin_amdgcn_permlane16_swap(pk[nb][mb][0], pk[nb][mb + 1][0], false, false);
-      const auto hi = __builtin_amdgcn_permlane16_swap(pk[nb][mb][1], pk[nb][mb + 1][1], false, false);
-      __builtin_nontemporal_store(u32x4_t{lo[0], hi[0], lo[1], hi[1]},
-                                  reinterpret_cast<u32x4_t*>(dst + int64_t(mb / 4) * T_pad * 64 + (mb / 2 % 2) * 512 + nb * 1024));
-    }
-  // ---- vocabulary x tokens: the four lanes of a quad hold rows r .. r + 3 of tokens t .. t + 3 and transpose that
-  // 4 x 4 block in two exchanges, so that lane q holds row r + q of all four tokens; lanes four apart then swap
-  // halves between two neighbouring token blocks, which leaves eight tokens of a row in each ----
-  const bool odd = lane & 1, upper = lane & 2, far = lane & 4;
-  // a tile lies inside one chunk (VC is a multiple of the tile height)
-  uint16_t* const dstT = dzT + int64_t(m0 / VC) * VC * T_pad +
-                         frag_order_offset(VC, m0 % VC + wm * 128 + group * 4 + (lane & 3), t0 + (far ? 16 : 0) + (lane & 8));
+    for (int mb = 0; mb < kMB; mb += 2)
+      store(rz, u32x2_t{pk[nb][mb][0], pk[nb][mb][1]}, u32x2_t{pk[nb][mb + 1][0], pk[nb][mb + 1][1]}, in_block,
+            at + (mb / 4) * slab + (mb / 2 % 2) * 1024 + nb * 2048);
+  // ---- vocabulary x tokens: a tile lies inside one chunk (VC is a multiple of the tile height), the wave's 64 tokens are
+  // one slab of it ----
+  const uint32_t slabT = uint32_t(VC) * 128;
+  const __amdgpu_buffer_rsrc_t rzT = __builtin_amdgcn_make_buffer_rsrc(
+      dzT + int64_t(m0 / VC) * VC * T_pad + int64_t(n0 / 64) * VC * 64, 0, int(4 * slabT), 0x00020000);
+  const uint32_t atT = uint32_t(m0 % VC + wp.wm * 128) * 128 + wp.wn * slabT;
+  const int diag = (lane & 15) - 4 * group;   // the lane's register of the identity that is 1
+  const u32x2_t one = {diag == 0 ? 0x3f80u : diag == 1 ? 0x3f800000u : 0u, diag == 2 ? 0x3f80u : diag == 3 ? 0x3f800000u : 0u};
+  auto turned = [&](const uint32_t (&block)[2]) {
+    const f32x4_t t = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4_t, u32x2_t{block[0], block[1]}),
+                                                                __builtin_bit_cast(s16x4_t, one), f32x4_t{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+    return u32x2_t{pack_bf16x2(t.x, t.y), pack_bf16x2(t.z, t.w)};
+  };
 #pragma unroll
-  for (int nb = 0; nb < kNB; nb += 2)
+  for (int mb = 0; mb < kMB; ++mb)
 #pragma unroll
-    for (int mb = 0; mb < kMB; ++mb) {
-      uint32_t four[2][2];   // of blocks nb, nb + 1: this lane's row, four tokens
-#pragma unroll
-      for (int k = 0; k < 2; ++k) {
-        uint32_t pair[2];    // rows r + (lane & 1) and r + 2 + (lane & 1), tokens of this lane pair
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const uint32_t own = pk[nb + k][mb][h], got = quad_perm<kQuadXor1>(own);
-          pair[h] = odd ? ((got >> 16) | (own & 0xffff0000u)) : ((own & 0xffffu) | (got << 16));
-        }
-        const uint32_t got = quad_perm<kQuadXor2>(upper ? pair[0] : pair[1]);
-        four[k][0] = upper ? got : pair[0];
-        four[k][1] = upper ? pair[1] : got;
-      }
-      const uint32_t got0 = xor4_lane(far ? four[0][0] : four[1][0]), got1 = xor4_lane(far ? four[0][1] : four[1][1]);
-      const u32x4_t eight = far ? u32x4_t{got0, got1, four[1][0], four[1][1]} : u32x4_t{four[0][0], four[0][1], got0, got1};
-      __builtin_nontemporal_store(eight, reinterpret_cast<u32x4_t*>(dstT + mb * 1024 + (nb / 2) * 512));
-    }
+    for (int nb = 0; nb < kNB; nb += 2)
+      store(rzT, turned(pk[nb][mb]), turned(pk[nb + 1][mb]), in_block, atT + mb * 2048 + (nb / 2) * 1024);
 }
 
 // ------------------------------------------------------------------------------------------
 // forward: per-tile softmax partials
 // ------------------------------------------------------------------------------------------
-// grid: xcd_grid(tiles_v * T_pad / 256) workgroups.  Hf holds the compacted rows ([T_pad][H], zero
+// grid: xcd_grid(tiles_v * T_pad / 256) workgroups, at most one per CU.  Hf holds the compacted rows ([T_pad][H], zero
 // past the count); part_* are [tiles_v][T_pad], indexed by compact row.
 //
 // STORE (a backward pass follows and its rows have the plain form dz = g (onehot - pi)): the token tiles that
@@ -396,102 +374,135 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_fused_stats(
     int32_t* __restrict__ nact, uint16_t* __restrict__ dz, uint16_t* __restrict__ dzT) {
   extern __shared__ __align__(16) uint16_t smem[];
   // the tile order covers only the token tiles that hold rows with a target (count known on the
-  // device), so that every XCD gets the same number of real tiles; the rest of the grid leaves
-  const int tiles_t_act = nf[1] / kTile;
-  int tv, tt;
-  if (!tile_of_block(tiles_v, tiles_t_act, 0, tiles_v * tiles_t_act, tv, tt)) return;
-  const int m0 = tv * kTile, n0 = tt * kTile;
-  Acc acc;
-  WavePos wp = wave_pos<true>();
-  wp.active = n0 + wp.wn * 64 < nf[0];
-  gemm_tile_auto(W, H, V, Hf, H, int(T_pad), H, m0, n0, wp, smem, acc);
-
+  // device), so that every XCD gets the same number of real tiles
+  const int tiles_t_act = nf[1] / kTile, n_rows = nf[0], n_cand = STORE ? nf[2] : 0;
+  const int n_tiles = tiles_v * tiles_t_act;
   const int lane = threadIdx.x & 63;
+  WavePos wp = wave_pos<true>();
   const int wm = wp.wm, wn = wp.wn;
-  const bool full = m0 + kTile <= V;
-  const int n_cand = STORE ? nf[2] : 0;
-  const bool store = STORE && n0 < n_cand;   // uniform over the workgroup
-  uint32_t pk[kNB][kMB][2];
-  bool wide = false;
-  RowStat st[kNB];
-  constexpr int kGroup = 4;   // accumulator blocks per statistics update: 16 values
+  GemmStream<true, false, false, false, true> stream(H, kDK, H, kDK, H);
+  auto source = [&](int tv, int tt) {
+    return TileSrc{W, Hf, (int64_t(V) * H) * 2, (T_pad * H) * 2, uint32_t(int64_t(tv) * kTile * H * 2),
+                   uint32_t(int64_t(tt) * kTile * H * 2), (H + kDK - 1) / kDK};
+  };
+  RowStat* const xch = reinterpret_cast<RowStat*>(smem + kEpilogueOff / 2);   // [256 token columns]
+  // zy of a tile's columns, sent to LDS right behind its first slice: a load in the epilogue would wait for everything
+  // that the next tile has requested by then.  Two buffers, taken in turn.
+  float* const ref_buf = reinterpret_cast<float*>(xch + kTile);
+  auto request_ref = [&](int tt, int buf) {
+    if (!STORE || stream.wave >= kTile / kWave) return;
+    const __amdgpu_buffer_rsrc_t rz = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(zy), 0, int(T_pad * 4), 0x00020000);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rz, ref_buf + buf * kTile + stream.wave * kWave, 4,
+                                             uint32_t(tt * kTile + stream.wave * kWave + lane) * 4, 0, 0, 0);
+  };
+  int pid = blockIdx.x, tv, tt, buf = 0;
+  bool more = tile_of_step(pid, tiles_v, tiles_t_act, 0, n_tiles, tv, tt), stored = false;
+  if (!more) return;   // uniform over the workgroup
+  TileSrc src = source(tv, tt);
+  stream.start(src, smem);
+  request_ref(tt, buf);
+  while (more) {
+    const int m0 = tv * kTile, n0 = tt * kTile;
+    const bool store = STORE && n0 < n_cand;   // uniform over the workgroup
+    wp.active = n0 + wn * 64 < n_rows;
+    wp.warm_a = warm_share(tt, tiles_t_act);
+    wp.warm_b = warm_share(tv, tiles_v);
+    wp.warm_from = tiles_t_act > 1 ? kWarmSlices : kWarmSlicesAlone;
+    const int tv_now = tv;
+    pid += gridDim.x;
+    more = tile_of_step(pid, tiles_v, tiles_t_act, 0, n_tiles, tv, tt);
+    const TileSrc next = more ? source(tv, tt) : no_tile(src);
+    Acc acc;
+    stream.run<kTileStores>(src, next, wp, stored, smem, acc);
+    src = next;
+    stored = store;
+    request_ref(tt, buf ^ 1);
+
+    const int lane = opaque(threadIdx.x & 63);
+    const bool full = m0 + kTile <= V;
+    uint32_t pk[kNB][kMB][2] = {};   // a value on every path: not carried around the walk
+    bool wide = false;
+    RowStat st[kNB];
+    constexpr int kGroup = 4;   // accumulator blocks per statistics update: 16 values
 #pragma unroll
-  for (int nb = 0; nb < kNB; ++nb) {
-    st[nb] = stat_identity();
-    const int col = n0 + acc_col(wn, nb, lane);
-    const bool col_cand = store && col < n_cand;
-    const float ref = col_cand ? zy[col] : 0.f;
+    for (int nb = 0; nb < kNB; ++nb) {
+      st[nb] = stat_identity();
+      const int col = n0 + acc_col(wn, nb, lane);
+      const bool col_cand = store && col < n_cand;
+      const float ref = store ? ref_buf[buf * kTile + acc_col(wn, nb, lane)] : 0.f;
 #pragma unroll
-    for (int mg = 0; mg < kMB; mg += kGroup) {
-      if (full) {
-        float z[16], e[16];
+      for (int mg = 0; mg < kMB; mg += kGroup) {
+        if (full) {
+          float z[16], e[16];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) z[i] = acc[mg + i / 4][nb][i % 4];
-        if (store) {
-          const float vm = stat_update_keep(st[nb], z, e);
-          // columns past the candidates keep zeros: their rows of the other operand are zero as well
-          const float f = col_cand ? exp2_fast((st[nb].m - ref) * kLog2e) : 0.f;
-          wide |= col_cand && vm - ref > kStoreRange;
+          for (int i = 0; i < 16; ++i) z[i] = acc[mg + i / 4][nb][i % 4];
+          if (store) {
+            const float vm = stat_update_keep(st[nb], z, e);
+            // columns past the candidates keep zeros: their rows of the other operand are zero as well
+            const float f = col_cand ? exp2_fast((st[nb].m - ref) * kLog2e) : 0.f;
+            wide |= col_cand && vm - ref > kStoreRange;
 #pragma unroll
-          for (int k = 0; k < kGroup; ++k) {
-            pk[nb][mg + k][0] = pack_bf16x2(e[4 * k] * f, e[4 * k + 1] * f);
-            pk[nb][mg + k][1] = pack_bf16x2(e[4 * k + 2] * f, e[4 * k + 3] * f);
+            for (int k = 0; k < kGroup; ++k) {
+              pk[nb][mg + k][0] = pack_bf16x2(e[4 * k] * f, e[4 * k + 1] * f);
+              pk[nb][mg + k][1] = pack_bf16x2(e[4 * k + 2] * f, e[4 * k + 3] * f);
+            }
+          } else {
+            stat_update<16>(st[nb], z);
           }
         } else {
-          stat_update<16>(st[nb], z);
-        }
-      } else {
-        float d[16];
+          float d[16];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          d[i] = 0.f;
-          if (m0 + acc_row(wm, mg + i / 4, i % 4, lane) < V) {
-            const float zi = acc[mg + i / 4][nb][i % 4];
-            float z[1] = {zi};
-            stat_update<1>(st[nb], z);
-            if (store && col_cand) {
-              d[i] = exp2_fast((zi - ref) * kLog2e);
-              wide |= zi - ref > kStoreRange;
+          for (int i = 0; i < 16; ++i) {
+            d[i] = 0.f;
+            if (m0 + acc_row(wm, mg + i / 4, i % 4, lane) < V) {
+              const float zi = acc[mg + i / 4][nb][i % 4];
+              float z[1] = {zi};
+              stat_update<1>(st[nb], z);
+              if (store && col_cand) {
+                d[i] = exp2_fast((zi - ref) * kLog2e);
+                wide |= zi - ref > kStoreRange;
+              }
             }
           }
-        }
-        if (store) {
+          if (store) {
 #pragma unroll
-          for (int k = 0; k < kGroup; ++k) {
-            pk[nb][mg + k][0] = pack_bf16x2(d[4 * k], d[4 * k + 1]);
-            pk[nb][mg + k][1] = pack_bf16x2(d[4 * k + 2], d[4 * k + 3]);
+            for (int k = 0; k < kGroup; ++k) {
+              pk[nb][mg + k][0] = pack_bf16x2(d[4 * k], d[4 * k + 1]);
+              pk[nb][mg + k][1] = pack_bf16x2(d[4 * k + 2], d[4 * k + 3]);
+            }
           }
         }
       }
     }
-  }
-  // Four lanes (l % 16 equal) share a column and hold the same four columns each: two exchanges in which a
-  // lane passes on half of its columns leave every lane with one of the wave's 64 columns, whole.
-  static_assert(kNB == 4, "the exchange below halves four columns twice");
-  const bool hi16 = lane & 16, hi32 = lane & 32;
-  RowStat two[2];
+    // Four lanes (l % 16 equal) share a column and hold the same four columns each: two exchanges in which a
+    // lane passes on half of its columns leave every lane with one of the wave's 64 columns, whole.
+    static_assert(kNB == 4, "the exchange below halves four columns twice");
+    const bool hi16 = lane & 16, hi32 = lane & 32;
+    RowStat two[2];
 #pragma unroll
-  for (int k = 0; k < 2; ++k)
-    two[k] = stat_merge(hi16 ? st[2 + k] : st[k], stat_shfl_xor(hi16 ? st[k] : st[2 + k], 16));
-  const RowStat mine = stat_merge(hi32 ? two[1] : two[0], stat_shfl_xor(hi32 ? two[0] : two[1], 32));
-  const int my_col = acc_col(wn, (hi16 ? 2 : 0) + (hi32 ? 1 : 0), lane);
-  // the two waves that share these token columns (wm = 0, 1) merge through LDS
-  RowStat* xch = reinterpret_cast<RowStat*>(smem);   // [256 token columns]
-  if (wm == 1) xch[my_col] = mine;
-  __syncthreads();
-  if (wm == 0) {
-    const RowStat r = stat_merge(mine, xch[my_col]);
-    const int64_t o = int64_t(tv) * T_pad + n0 + my_col;   // column < T_pad
-    part_m[o] = r.m;
-    part_s[o] = r.s;
-    part_sz[o] = r.sz;
-  }
-  if constexpr (STORE) {
-    if (store) {
-      if (__any(wide) && lane == 0) atomicOr(nact + 2, 1);
-      store_tile_both_layouts(pk, wp, m0, n0, T_pad, VC, dz, dzT);
+    for (int k = 0; k < 2; ++k)
+      two[k] = stat_merge(hi16 ? st[2 + k] : st[k], stat_shfl_xor(hi16 ? st[k] : st[2 + k], 16));
+    const RowStat mine = stat_merge(hi32 ? two[1] : two[0], stat_shfl_xor(hi32 ? two[0] : two[1], 32));
+    const int my_col = acc_col(wn, (hi16 ? 2 : 0) + (hi32 ? 1 : 0), lane);
+    // the two waves that share these token columns (wm = 0, 1) merge through LDS
+    buf ^= 1;
+    if (wm == 1) xch[my_col] = mine;
+    lds_barrier();   // the slices of the next tile put barriers between these reads and the next writes
+    if (wm == 0) {
+      const RowStat r = stat_merge(mine, xch[my_col]);
+      const int64_t o = int64_t(tv_now) * T_pad + n0 + my_col;   // column < T_pad
+      part_m[o] = r.m;
+      part_s[o] = r.s;
+      part_sz[o] = r.sz;
+    }
+    if constexpr (STORE) {
+      if (store) {
+        if (__any(wide) && lane == 0) atomicOr(nact + 2, 1);
+        store_tile_both_layouts(pk, wp, lane, m0, n0, T_pad, VC, dz, dzT);
+      }
     }
   }
+  end_of_walk();
 }
 
 // ------------------------------------------------------------------------------------------
@@ -688,50 +699,70 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_fused_dz(
   extern __shared__ __align__(16) uint16_t smem[];
   if (!force && nact[2] == 0) return;   // uniform over the launch
   // tile order over the candidates' token tiles only (see k_fused_stats)
-  const int tiles_t_act = nact[1] / kTile;
-  int tv, tt;
-  if (!tile_of_block(tiles_v, tiles_t_act, 0, tiles_v * tiles_t_act, tv, tt)) return;
-  const int m0 = tv * kTile, n0 = tt * kTile;
-  Acc acc;
+  const int tiles_t_act = nact[1] / kTile, n_cand = nact[0];
+  const int n_tiles = tiles_v * tiles_t_act;
   WavePos wp = wave_pos<true>();
-  wp.active = n0 + wp.wn * 64 < nact[0];
-  gemm_tile_auto(W, H, V, Hc, H, int(T_pad), H, m0, n0, wp, smem, acc);
-
-  const int lane = threadIdx.x & 63;
   const int wm = wp.wm, wn = wp.wn;
-  // dz for this lane's columns, packed to bf16 pairs: pk[nb][mb] = four consecutive rows
-  uint32_t pk[kNB][kMB][2];
+  GemmStream<true, false, false, false, true> stream(H, kDK, H, kDK, H);
+  auto source = [&](int tv, int tt) {
+    return TileSrc{W, Hc, (int64_t(V) * H) * 2, (T_pad * H) * 2, uint32_t(int64_t(tv) * kTile * H * 2),
+                   uint32_t(int64_t(tt) * kTile * H * 2), (H + kDK - 1) / kDK};
+  };
+  int pid = blockIdx.x, tv, tt;
+  bool more = tile_of_step(pid, tiles_v, tiles_t_act, 0, n_tiles, tv, tt), stored = false;
+  if (!more) return;
+  TileSrc src = source(tv, tt);
+  stream.start(src, smem);
+  while (more) {
+    const int m0 = tv * kTile, n0 = tt * kTile;
+    wp.active = n0 + wn * 64 < n_cand;
+    wp.warm_a = warm_share(tt, tiles_t_act);
+    wp.warm_b = warm_share(tv, tiles_v);
+    wp.warm_from = tiles_t_act > 1 ? kWarmSlices : kWarmSlicesAlone;
+    pid += gridDim.x;
+    more = tile_of_step(pid, tiles_v, tiles_t_act, 0, n_tiles, tv, tt);
+    const TileSrc next = more ? source(tv, tt) : no_tile(src);
+    Acc acc;
+    stream.run<kTileStores>(src, next, wp, stored, smem, acc);
+    src = next;
+    stored = true;
+
+    const int lane = opaque(threadIdx.x & 63);
+    // dz for this lane's columns, packed to bf16 pairs: pk[nb][mb] = four consecutive rows
+    uint32_t pk[kNB][kMB][2];
 #pragma unroll
-  for (int nb = 0; nb < kNB; ++nb) {
-    const int64_t t = n0 + acc_col(wn, nb, lane);
-    const float g = gc[t], ng = bc[t];   // bc = -g without the entropy bonus
-    const float a = ENT ? ac[t] : 0.f;
-    const float c = -lsec[t] * kLog2e;
-    const int yrel = yc[t];        // vocabulary row of the sampled token (-1 on padding columns)
-    // Almost every wave holds neither a sampled token's row nor rows past the vocabulary: that
-    // case (uniform over the wave) runs without the two per-element tests.
-    const bool plain = (m0 + kTile <= V) && !__any(unsigned(yrel - m0 - wm * 128) < 128u);
+    for (int nb = 0; nb < kNB; ++nb) {
+      const int64_t t = n0 + acc_col(wn, nb, lane);
+      const float g = gc[t], ng = bc[t];   // bc = -g without the entropy bonus
+      const float a = ENT ? ac[t] : 0.f;
+      const float c = -lsec[t] * kLog2e;
+      const int yrel = yc[t];        // vocabulary row of the sampled token (-1 on padding columns)
+      // Almost every wave holds neither a sampled token's row nor rows past the vocabulary: that
+      // case (uniform over the wave) runs without the two per-element tests.
+      const bool plain = (m0 + kTile <= V) && !__any(unsigned(yrel - m0 - wm * 128) < 128u);
 #pragma unroll
-    for (int mb = 0; mb < kMB; ++mb) {
-      float d[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const float z = acc[mb][nb][j];
-        d[j] = (ENT ? fmaf(a, z, ng) : ng) * exp2_fast(fmaf(z, kLog2e, c));
-      }
-      if (!plain) {
+      for (int mb = 0; mb < kMB; ++mb) {
+        float d[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          const int row = m0 + acc_row(wm, mb, j, lane);
-          if (row == yrel) d[j] += g;
-          if (row >= V) d[j] = 0.f;
+          const float z = acc[mb][nb][j];
+          d[j] = (ENT ? fmaf(a, z, ng) : ng) * exp2_fast(fmaf(z, kLog2e, c));
         }
+        if (!plain) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const int row = m0 + acc_row(wm, mb, j, lane);
+            if (row == yrel) d[j] += g;
+            if (row >= V) d[j] = 0.f;
+          }
+        }
+        pk[nb][mb][0] = pack_bf16x2(d[0], d[1]);
+        pk[nb][mb][1] = pack_bf16x2(d[2], d[3]);
       }
-      pk[nb][mb][0] = pack_bf16x2(d[0], d[1]);
-      pk[nb][mb][1] = pack_bf16x2(d[2], d[3]);
     }
+    store_tile_both_layouts(pk, wp, lane, m0, n0, T_pad, VC, dz, dzT);
   }
-  store_tile_both_layouts(pk, wp, m0, n0, T_pad, VC, dz, dzT);
+  end_of_walk();
 }
 
 // ------------------------------------------------------------------------------------------
@@ -739,46 +770,61 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_fused_dz(
 // ------------------------------------------------------------------------------------------
 // dh_part[s][t][h] = sum_{k in split s} X[t][k] W[k][h], X = the stored exponentials P (or dz itself on the recompute
 // route)     M = candidate tokens, N = H, K = vocabulary (padded)
-// DIRECT: the weight as the caller holds it, [V][H], through the transposing LDS read; otherwise WT, its copy in
-// K-slabs (see kDirectRows).
-template <bool DIRECT>
+// The weight is read as the caller holds it, [V][H], and turned by the transposing LDS read.  (A copy of it in K-slabs costs a
+// pass over the weight per call, 170 us at H = 1536 and 430 at 3584 with V = 152 K, and the contraction gains at most 2 % by
+// it: copy + contraction / as it is 557 + 168 / 559 us with 2048 tokens at H = 1536, 1531 + 170 / 1550 with 6000, 3972 + 173 /
+// 4036 with 16384; 4803 + 419 / 4915 with 8192 at H = 3584, 9713 + 423 / 9550 with 16384.)
 __global__ __launch_bounds__(kGemmNT, 2) void k_gemm_dh(
-    const uint16_t* __restrict__ dz, const uint16_t* __restrict__ W, const uint16_t* __restrict__ WT, int V, int H_pad,
-    int vK, int H, int tiles_h, int64_t T_pad, const int32_t* __restrict__ nact, float* __restrict__ dh_part) {
+    const uint16_t* __restrict__ dz, const uint16_t* __restrict__ W, int V, int vK, int H, int tiles_h, int64_t T_pad,
+    const int32_t* __restrict__ nact, float* __restrict__ dh_part) {
   extern __shared__ __align__(16) uint16_t smem[];
-  const int n_pad = nact[1];
+  const int n_pad = nact[1], n_cand = nact[0];
   const int tiles_t = n_pad / kTile;
   const int nslices = vK / kDK;
   const int S = nact[3];
-  const int base = tiles_t * tiles_h;
-  const int pid = blockIdx.x;
-  if (S == 0 || pid >= base * S) return;   // uniform exit
+  const int base = tiles_t * tiles_h, n = base * S;
+  if (int(blockIdx.x) >= n) return;   // uniform over the workgroup
+  const int per = (nslices + S - 1) / S;
+  WavePos wp = wave_pos<false>();
+  const int wm = wp.wm, wn = wp.wn;
+  GemmStream<true, true, true, true, false> stream(kDK, T_pad * kDK, H, 0, 0);
+  auto source = [&](int split, int tt, int th) {
+    const int k_begin = min(vK, split * per * kDK);
+    const int k_len = max(0, min(vK, (split + 1) * per * kDK) - k_begin);
+    TileSrc t;
+    t.a_base = dz + int64_t(k_begin / kDK) * T_pad * kDK;
+    t.a_bytes = int64_t(k_len / kDK) * T_pad * kDK * 2;
+    t.a = uint32_t(tt * kTile * kDK * 2);
+    // weight rows past the vocabulary (the split may start there) lie past the operand's bytes and read as zeros
+    t.b_base = W + int64_t(min(k_begin, V)) * H;
+    t.b_bytes = int64_t(max(V - k_begin, 0)) * H * 2;
+    t.b = uint32_t(th * kTile * 2);
+    t.nk = k_len / kDK;
+    if (t.nk == 0) {   // an empty split: one slice of nothing
+      t.nk = 1;
+      t.b_bytes = 0;
+    }
+    return t;
+  };
   // per-XCD contiguous order, split-major: the workgroups resident on one XCD work on the same
   // K range of neighbouring tiles and share their operand slices in that XCD's L2
-  const int npid = xcd_regroup(pid, base * S);
+  const int npid = xcd_regroup(blockIdx.x, n);
   const int split = npid / base;
   int tt, th;
   tile_of_index(npid % base, tiles_t, tiles_h, tt, th);
   const int m0 = tt * kTile, n0 = th * kTile;
-  const int per = (nslices + S - 1) / S;
-  const int k_begin = min(vK, split * per * kDK);
-  const int k_len = max(0, min(vK, (split + 1) * per * kDK) - k_begin);
+  wp.active = m0 + wm * 128 < n_cand;
+  wp.warm_a = warm_share(th, tiles_h);
+  wp.warm_b = warm_share(tt, tiles_t);
+  wp.warm_from = tiles_t > 1 ? INT32_MAX : kWarmSlicesAlone;   // see kWarmSlices
+  const TileSrc src = source(split, tt, th);
   Acc acc;
-  WavePos wp = wave_pos<false>();
-  wp.active = m0 + wp.wm * 128 < nact[0];
-  const DmaOperand x = operand_slabs(dz + int64_t(k_begin / kDK) * T_pad * kDK, T_pad, k_len);
-  if constexpr (DIRECT) {
-    // weight rows past the vocabulary (the split may start there) lie past the operand's bytes and read as zeros
-    const DmaOperand w{W + int64_t(min(k_begin, V)) * H, H, 0, int64_t(max(V - k_begin, 0)) * H * 2};
-    gemm_tile_dma<false, true, true, true, true>(x, w, k_len, m0, n0, wp, smem, acc);
-  } else {
-    gemm_tile_dma<false, true, false, true, true>(x, operand_slabs(WT + int64_t(k_begin / kDK) * H_pad * kDK, H_pad, k_len),
-                                                  k_len, m0, n0, wp, smem, acc);
-  }
+  stream.start(src, smem);
+  stream.run<0>(src, no_tile(src), wp, false, smem, acc);
+  end_of_walk();
   if (!wp.active) return;   // padding rows of the partials are not read
   const int lane = threadIdx.x & 63;
-  const int wm = wp.wm, wn = wp.wn;
-  float* out = dh_part + int64_t(split) * n_pad * H;
+  float* const out = dh_part + int64_t(split) * n_pad * H;
 #pragma unroll
   for (int mb = 0; mb < kMB; ++mb) {
     float* row = out + int64_t(m0 + acc_row_swapped(wm, mb, lane)) * H;
@@ -791,26 +837,22 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_gemm_dh(
 }
 
 // dW[m][h] = sum_t XT[m][t] hTc[h][t], hTc = the candidates' hidden rows times their scale     M = V, N = H, K = candidate tokens (padded)
-template <bool OUT_BF16>
+template <bool OUT_BF16, bool ACC>
 __global__ __launch_bounds__(kGemmNT, 2) void k_gemm_dw(
     const uint16_t* __restrict__ dzT, const uint16_t* __restrict__ hTc, int VC, int H_pad, int V, int H,
-    int tile0, int n_tiles, int tiles_v, int tiles_h, int64_t T_pad, const int32_t* __restrict__ nact,
-    int accumulate, int vec, void* dW) {
+    int tile0, int n_tiles, int tiles_v, int tiles_h, int64_t T_pad, const int32_t* __restrict__ nact, int vec, void* dW) {
   extern __shared__ __align__(16) uint16_t smem[];
-  int tv, th;
-  if (!tile_of_block(tiles_v, tiles_h, tile0, n_tiles, tv, th)) return;
-  const int m0 = tv * kTile, n0 = th * kTile;
-  // the tile's rows lie inside one vocabulary chunk of the transposed dz
-  const uint16_t* const dzT_chunk = dzT + int64_t(m0 / VC) * VC * T_pad;
-  Acc acc;
   // the contraction ends with the slice of the last candidate, not with its tile: the positions behind it are zeros
   // (whole calls at H = 1536, V = 151936: 600 tokens 949 -> 905 us, 1100 tokens 1376 -> 1357, 16384 tokens -0.4 %)
   const int K = (nact[0] + kDK - 1) / kDK * kDK;
-  const WavePos wp = wave_pos<false>();
-  gemm_tile_dma<true, true, false, true>(operand_slabs(dzT_chunk, VC, K), operand_slabs(hTc, H_pad, K), K, m0 % VC, n0,
-                                         wp, smem, acc);
-  const int lane = threadIdx.x & 63;
+  WavePos wp = wave_pos<false>();
   const int wm = wp.wm, wn = wp.wn;
+  GemmStream<true, true, false, true, false> stream(kDK, int64_t(VC) * kDK, kDK, int64_t(H_pad) * kDK, 0);
+  auto source = [&](int tv, int th) {
+    const int m0 = tv * kTile;   // the tile's rows lie inside one vocabulary chunk of the transposed dz
+    return TileSrc{dzT + int64_t(m0 / VC) * VC * T_pad, hTc, int64_t(K) * VC * 2, int64_t(K) * H_pad * 2,
+                   uint32_t(m0 % VC) * (kDK * 2), uint32_t(th * kTile * kDK * 2), max(K / kDK, 1)};   // no candidates: one slice of nothing
+  };
   // accumulate (uniform): the tile is added to what the caller's buffer holds (gradient accumulation over
   // micro-batches).  vec (uniform): that buffer is 16-byte aligned, as every allocation is.  Plain stores: an
   // instruction writes 64 bytes per row and L2 joins the two halves of a line; non-temporal ones leave it in
@@ -818,35 +860,49 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_gemm_dw(
   // V = 151936 in bf16 while the contraction took whole token tiles - 223 us since it ends earlier -, 1690 against
   // 1660 us per chunk with 16384 in fp32).
   constexpr int kDT = OUT_BF16 ? kBF16 : kF32;
+  int pid = blockIdx.x, tv, th;
+  bool more = tile_of_step(pid, tiles_v, tiles_h, tile0, n_tiles, tv, th), stored = false;
+  if (!more) return;
+  TileSrc src = source(tv, th);
+  stream.start(src, smem);
+  while (more) {
+    const int m0 = tv * kTile, n0 = th * kTile;
+    wp.warm_a = warm_share(th, tiles_h);
+    wp.warm_b = warm_share(tv, tiles_v);
+    wp.warm_from = kWarmSlices;
+    pid += gridDim.x;
+    more = tile_of_step(pid, tiles_v, tiles_h, tile0, n_tiles, tv, th);
+    const TileSrc next = more ? source(tv, th) : no_tile(src);
+    Acc acc;
+    stream.template run<OUT_BF16 ? kMB * kNB / 2 : kMB * kNB>(src, next, wp, stored, smem, acc);
+    src = next;
+    stored = vec && m0 + kTile <= V && n0 + kTile <= H;   // then every store below is issued
+    const int lane = opaque(threadIdx.x & 63);
 #pragma unroll
-  for (int mb = 0; mb < kMB; ++mb) {
-    const int row = m0 + acc_row_swapped(wm, mb, lane);
-    const int64_t row_off = int64_t(row) * H;
-    const bool row_in = row < V;
-#pragma unroll
-    for (int nb = 0; nb < kNB; ++nb) {
-      const int col = n0 + acc_col_swapped(wn, nb, lane);   // four columns; H is a multiple of 8
-      const bool in = row_in && col < H;
+    for (int mb = 0; mb < kMB; ++mb) {
+      const int row = m0 + acc_row_swapped(wm, mb, lane);
+      const int64_t row_off = int64_t(row) * H;
+      const bool row_in = row < V;
       if (!vec) {
-        if (in) {
+#pragma unroll
+        for (int nb = 0; nb < kNB; ++nb) {
+          const int col = n0 + acc_col_swapped(wn, nb, lane);
+          if (!row_in || col >= H) continue;
 #pragma unroll
           for (int i = 0; i < 4; ++i)
-            store_elt<kDT>(dW, row_off + col + i, acc[mb][nb][i] + (accumulate ? load_elt<kDT>(dW, row_off + col + i) : 0.f));
+            store_elt<kDT>(dW, row_off + col + i, acc[mb][nb][i] + (ACC ? load_elt<kDT>(dW, row_off + col + i) : 0.f));
         }
       } else if constexpr (OUT_BF16) {
-        if (accumulate && in) {
-          const uint64_t old = __builtin_nontemporal_load(reinterpret_cast<const uint64_t*>(reinterpret_cast<uint16_t*>(dW) + row_off + col));
-          const uint32_t lo = uint32_t(old), hi = uint32_t(old >> 32);
-          acc[mb][nb] += f32x4_t{bf16_lo(lo), bf16_hi(lo), bf16_lo(hi), bf16_hi(hi)};
+        if constexpr (ACC) {
+#pragma unroll
+          for (int nb = 0; nb < kNB; ++nb) {
+            const int col = n0 + acc_col_swapped(wn, nb, lane);
+            if (!row_in || col >= H) continue;
+            const uint64_t old = __builtin_nontemporal_load(reinterpret_cast<const uint64_t*>(reinterpret_cast<uint16_t*>(dW) + row_off + col));
+            const uint32_t lo = uint32_t(old), hi = uint32_t(old >> 32);
+            acc[mb][nb] += f32x4_t{bf16_lo(lo), bf16_hi(lo), bf16_lo(hi), bf16_hi(hi)};
+          }
         }
-      } else if (in) {
-        f32x4_t* p = reinterpret_cast<f32x4_t*>(reinterpret_cast<float*>(dW) + row_off + col);
-        if (accumulate) acc[mb][nb] += __builtin_nontemporal_load(p);
-        *p = acc[mb][nb];
-      }
-    }
-    if constexpr (OUT_BF16) {
-      if (vec) {
         // Two neighbouring blocks: the odd 16-lane rows of the first change places with the even ones of the
         // second, so that every lane holds eight consecutive columns and an instruction writes 64 contiguous
         // bytes per vocabulary row.  (8-byte stores, 32 contiguous bytes: 454 us where these take 312, at
@@ -862,9 +918,19 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_gemm_dw(
           if (row_in && col < H)
             *reinterpret_cast<u32x4_t*>(reinterpret_cast<uint16_t*>(dW) + row_off + col) = u32x4_t{lo[0], hi[0], lo[1], hi[1]};
         }
+      } else {
+#pragma unroll
+        for (int nb = 0; nb < kNB; ++nb) {
+          const int col = n0 + acc_col_swapped(wn, nb, lane);
+          if (!row_in || col >= H) continue;
+          f32x4_t* const p = reinterpret_cast<f32x4_t*>(reinterpret_cast<float*>(dW) + row_off + col);
+          if constexpr (ACC) acc[mb][nb] += __builtin_nontemporal_load(p);
+          *p = acc[mb][nb];
+        }
       }
     }
   }
+  end_of_walk();
 }
 
 // dhidden[t] = bf16(scale[pos[t]] * sum over the split-K partials of row pos[t]) or +0.  One workgroup per
@@ -955,6 +1021,9 @@ extern "C" aero_status aero_lmhead_logprob_fused(
   const int tiles_t = int(p.T_pad / kTile);
   const int tiles_h = (H + kTile - 1) / kTile;
   const int grid_dh = dh_grid(p.T_pad, H, p.V_ld);
+  // contractions: one workgroup per CU walks the tiles; a multiple of 8 keeps a walk on its XCD
+  const int cus = compute_units() / 8 * 8 > 0 ? compute_units() / 8 * 8 : 8;
+  auto walkers = [&](int n) { return dim3(unsigned(n < cus ? n : cus)); };
   const int64_t rows_max = p.T_pad > p.H_pad ? p.T_pad : int64_t(p.H_pad);
 
   // raising the dynamic-LDS limit is per function; done once per process, safely from any thread
@@ -965,10 +1034,11 @@ extern "C" aero_status aero_lmhead_logprob_fused(
         set_lds(reinterpret_cast<const void*>(k_fused_stats<true>)) != AERO_OK ||
         set_lds(reinterpret_cast<const void*>(k_fused_dz<false>)) != AERO_OK ||
         set_lds(reinterpret_cast<const void*>(k_fused_dz<true>)) != AERO_OK ||
-        set_lds(reinterpret_cast<const void*>(k_gemm_dh<true>)) != AERO_OK ||
-        set_lds(reinterpret_cast<const void*>(k_gemm_dh<false>)) != AERO_OK ||
-        set_lds(reinterpret_cast<const void*>(k_gemm_dw<true>)) != AERO_OK ||
-        set_lds(reinterpret_cast<const void*>(k_gemm_dw<false>)) != AERO_OK)
+        set_lds(reinterpret_cast<const void*>(k_gemm_dh)) != AERO_OK ||
+        set_lds(reinterpret_cast<const void*>(k_gemm_dw<true, true>)) != AERO_OK ||
+        set_lds(reinterpret_cast<const void*>(k_gemm_dw<true, false>)) != AERO_OK ||
+        set_lds(reinterpret_cast<const void*>(k_gemm_dw<false, true>)) != AERO_OK ||
+        set_lds(reinterpret_cast<const void*>(k_gemm_dw<false, false>)) != AERO_OK)
       attr_rc = AERO_ERR_HIP;
   });
   if (attr_rc != AERO_OK) return attr_rc;
@@ -1002,10 +1072,10 @@ extern "C" aero_status aero_lmhead_logprob_fused(
     {
       const int n = p.tiles_v * tiles_t;
       if (stored)
-        hipLaunchKernelGGL(k_fused_stats<true>, dim3(unsigned(xcd_grid(n))), dim3(kGemmNT), kGemmLdsBytes, s, Wp, hf,
+        hipLaunchKernelGGL(k_fused_stats<true>, walkers(xcd_grid(n)), dim3(kGemmNT), kGemmLdsBytes, s, Wp, hf,
                            V, H, p.tiles_v, p.T_pad, nf, part_m, part_s, part_sz, zy, p.VC, nact, dz, dzT);
       else
-        hipLaunchKernelGGL(k_fused_stats<false>, dim3(unsigned(xcd_grid(n))), dim3(kGemmNT), kGemmLdsBytes, s, Wp, hf,
+        hipLaunchKernelGGL(k_fused_stats<false>, walkers(xcd_grid(n)), dim3(kGemmNT), kGemmLdsBytes, s, Wp, hf,
                            V, H, p.tiles_v, p.T_pad, nf, part_m, part_s, part_sz, zy, p.VC, nact, dz, dzT);
     }
     if (p.T_pad <= kFewRows)
@@ -1019,7 +1089,6 @@ extern "C" aero_status aero_lmhead_logprob_fused(
 
   // ---- loss, operand copies ----
   uint16_t* hTc = reinterpret_cast<uint16_t*>(ws + p.off_hTc);
-  uint16_t* WT = reinterpret_cast<uint16_t*>(ws + p.off_WT);
   float* dh_acc = reinterpret_cast<float*>(ws + p.off_dhacc);
   if (T == 0) {   // no forward kernel ran: an empty candidate set for the kernels below
     hipLaunchKernelGGL(k_compact_valid, dim3(1), dim3(1024), 0, s, targets, T, p.T_pad, V, token_rollout, adv,
@@ -1032,45 +1101,34 @@ extern "C" aero_status aero_lmhead_logprob_fused(
   if (T > 0) {   // recompute mode only (the kernel leaves at once otherwise)
     const int n = p.tiles_v * tiles_t;
     if (ent)
-      hipLaunchKernelGGL(k_fused_dz<true>, dim3(unsigned(xcd_grid(n))), dim3(kGemmNT), kGemmLdsBytes, s, Wp, hf, V,
+      hipLaunchKernelGGL(k_fused_dz<true>, walkers(xcd_grid(n)), dim3(kGemmNT), kGemmLdsBytes, s, Wp, hf, V,
                          H, p.tiles_v, p.T_pad, p.VC, terms.force_recompute, nact, terms.gc, terms.lsec, terms.yc, terms.ac,
                          terms.bc, dz, dzT);
     else
-      hipLaunchKernelGGL(k_fused_dz<false>, dim3(unsigned(xcd_grid(n))), dim3(kGemmNT), kGemmLdsBytes, s, Wp, hf, V,
+      hipLaunchKernelGGL(k_fused_dz<false>, walkers(xcd_grid(n)), dim3(kGemmNT), kGemmLdsBytes, s, Wp, hf, V,
                          H, p.tiles_v, p.T_pad, p.VC, terms.force_recompute, nact, terms.gc, terms.lsec, terms.yc, terms.ac,
                          terms.bc, dz, dzT);
   }
   // the candidates' hidden rows, each times its scale, transposed to hTc: K-slabs over the candidate positions
   hipLaunchKernelGGL(k_transpose, dim3(unsigned(p.T_pad / 64), unsigned(p.H_pad / 64)), dim3(256), 0, s, hf, p.T_pad, H,
                      p.H_pad, hTc, terms.scale);
-  // weight transposed to WT, K-slabs over the vocabulary; rows V..V_ld of the source do not exist -> zeros
-  if (!p.direct)
-    hipLaunchKernelGGL(k_transpose, dim3(unsigned(p.V_ld / 64), unsigned(p.H_pad / 64)), dim3(256), 0, s, Wp, int64_t(V), H,
-                       p.H_pad, WT, nullptr);
-
   // ---- the two gradient contractions over the whole vocabulary ----
   if (T > 0) {
-    // dz columns [V, V_ld) are zero and WT is zero past V: the contraction runs over the padded vocabulary
-    if (p.direct)
-      hipLaunchKernelGGL(k_gemm_dh<true>, dim3(unsigned(grid_dh)), dim3(kGemmNT), kGemmLdsBytes, s, dz, Wp, nullptr, V,
-                         p.H_pad, p.V_ld, H, tiles_h, p.T_pad, nact, dh_acc);
-    else
-      hipLaunchKernelGGL(k_gemm_dh<false>, dim3(unsigned(grid_dh)), dim3(kGemmNT), kGemmLdsBytes, s, dz, Wp, WT, V,
-                         p.H_pad, p.V_ld, H, tiles_h, p.T_pad, nact, dh_acc);
+    // dz columns [V, V_ld) are zero, weight rows past V read as zeros: the contraction runs over the padded vocabulary
+    hipLaunchKernelGGL(k_gemm_dh, dim3(unsigned(grid_dh)), dim3(kGemmNT), kGemmLdsBytes, s, dz, Wp, V, p.V_ld, H, tiles_h, p.T_pad,
+                       nact, dh_acc);
   }
   // dweight: one launch per chunk of the transposed dz.  VC is sized so that a full chunk is a whole
-  // number of rounds of 256 tiles at the two model shapes (measured: 1 % faster than one long launch)
+  // number of rounds of 256 tiles at the two model shapes (measured: 1-3 % faster than one long walk)
   {
     const int total = p.tiles_v * tiles_h, per = (p.VC / kTile) * tiles_h;
     const int vec_dw = reinterpret_cast<uintptr_t>(dweight) % 16 == 0;   // rows are multiples of 16 bytes
+    const auto kernel = dweight_dtype == AERO_BF16 ? (accumulate ? k_gemm_dw<true, true> : k_gemm_dw<true, false>)
+                                                   : (accumulate ? k_gemm_dw<false, true> : k_gemm_dw<false, false>);
     for (int t0 = 0; t0 < total; t0 += per) {
       const int n = total - t0 < per ? total - t0 : per;
-      if (dweight_dtype == AERO_BF16)
-        hipLaunchKernelGGL((k_gemm_dw<true>), dim3(unsigned(xcd_grid(n))), dim3(kGemmNT), kGemmLdsBytes, s, dzT,
-                           hTc, p.VC, p.H_pad, V, H, t0, n, p.tiles_v, tiles_h, p.T_pad, nact, accumulate, vec_dw, dweight);
-      else
-        hipLaunchKernelGGL((k_gemm_dw<false>), dim3(unsigned(xcd_grid(n))), dim3(kGemmNT), kGemmLdsBytes, s, dzT,
-                           hTc, p.VC, p.H_pad, V, H, t0, n, p.tiles_v, tiles_h, p.T_pad, nact, accumulate, vec_dw, dweight);
+      hipLaunchKernelGGL(kernel, walkers(xcd_grid(n)), dim3(kGemmNT), kGemmLdsBytes, s, dzT, hTc, p.VC, p.H_pad, V, H, t0, n,
+                         p.tiles_v, tiles_h, p.T_pad, nact, vec_dw, dweight);
     }
   }
   if (T > 0)

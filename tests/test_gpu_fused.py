@@ -139,13 +139,23 @@ def test_fused_backward(gh, T, H, V):
     check_bwd(gh, wl, h, W, dict(reject_enable=1, posterior_mode=1), dweight_dtype=torch.bfloat16, grad_scale=8.0)
 
 
-# up to 4096 rows dhidden reads the weight as it is, beyond through a transposed copy; splits that start past the
+# around 4096 rows, where dhidden once went over to a transposed copy of the weight; splits that start past the
 # vocabulary, columns past H in the last tile, a tile of rows with one candidate
 @pytest.mark.parametrize("T,H,V", [(4096, 136, 520), (4097, 136, 520), (257, 264, 130), (33, 320, 1217)])
 def test_fused_backward_weight_forms(gh, T, H, V):
     wl, h, W = make(T, H, V, sigma_w=2.0 / np.sqrt(H), len_hi=200 if T > 300 else None, Q=40 if T > 300 else 6)
     check_bwd(gh, wl, h, W, dict())
     check_bwd(gh, wl, h, W, dict(reject_enable=1, posterior_mode=1), entropy_coef=0.01, dweight_dtype=torch.bfloat16)
+
+
+@pytest.mark.parametrize("T,H,V", [(600, 200, 70013), (300, 1080, 33000), (513, 56, 66048), (40, 696, 65792)])
+def test_fused_workgroups_that_walk_several_tiles(gh, T, H, V):
+    """More tiles than CUs in the forward and the dweight contraction, so that a workgroup takes several, with stored and
+    unstored, full and ragged ones in turn; rows whose last 64-wide slice holds 1, 7, 7 and 7 chunks of 8; one slice a
+    tile and many."""
+    wl, h, W = make(T, H, V, sigma_w=2.0 / np.sqrt(H))
+    check_bwd(gh, wl, h, W, dict())
+    check_bwd(gh, wl, h, W, dict(reject_enable=1, posterior_mode=1), dweight_dtype=torch.bfloat16, grad_scale=8.0)
 
 
 @pytest.mark.parametrize("accumulate", [False, True])
