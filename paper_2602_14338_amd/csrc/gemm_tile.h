@@ -16,8 +16,6 @@
 // multiple of 8.  (A loop that staged slices through registers took the rows whose length is no multiple of 64: forward of
 // 2500 tokens at H = 600, V = 32000 220 us, 130 this way.)
 #pragma once
-#include <type_traits>
-
 #include "aero_device.h"
 
 namespace aero {

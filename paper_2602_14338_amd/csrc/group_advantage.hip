@@ -19,31 +19,10 @@
 // bytes that nobody wrote where offsets start above 0.)
 // 100 groups of 64 to 90 rollouts, whose ranks do not fit one register a lane: 37.9 us when every lane looked for its
 // rank by itself in memory, 13.3 with the candidates taken 64 at a time into the lanes.
-#include <type_traits>
-
 #include "aero_device.h"
 
 namespace aero {
 
-// All-reduce of integers over the wave by lane permutations of the vector ALU (see row16_reduce in aero_device.h).
-template <class Op> __device__ __forceinline__ int wave_reduce_i(int v, Op op) {
-  auto moved = [](int x, auto ctrl) { return __builtin_amdgcn_update_dpp(0, x, decltype(ctrl)::value, 0xf, 0xf, true); };
-  v = op(v, moved(v, std::integral_constant<int, 0xB1>{}));    // quad_perm [1,0,3,2]
-  v = op(v, moved(v, std::integral_constant<int, 0x4E>{}));    // quad_perm [2,3,0,1]
-  v = op(v, moved(v, std::integral_constant<int, 0x141>{}));   // row_half_mirror
-  v = op(v, moved(v, std::integral_constant<int, 0x140>{}));   // row_mirror
-  const auto r16 = __builtin_amdgcn_permlane16_swap(uint32_t(v), uint32_t(v), false, false);
-  v = op(int(r16[0]), int(r16[1]));
-  const auto r32 = __builtin_amdgcn_permlane32_swap(uint32_t(v), uint32_t(v), false, false);
-  return op(int(r32[0]), int(r32[1]));
-}
-__device__ __forceinline__ int wave_sum_i(int v) { return wave_reduce_i(v, [](int a, int b) { return a + b; }); }
-__device__ __forceinline__ int wave_max_i(int v) { return wave_reduce_i(v, [](int a, int b) { return max(a, b); }); }
-__device__ __forceinline__ double wave_sum_d(double v) {
-#pragma unroll
-  for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, kWave);
-  return v;
-}
 __device__ __forceinline__ float wave_max_f(float v) { return wave_reduce(v, [](float a, float b) { return fmaxf(a, b); }); }
 __device__ __forceinline__ float wave_min_f(float v) { return wave_reduce(v, [](float a, float b) { return fminf(a, b); }); }
 

@@ -124,49 +124,9 @@ __global__ __launch_bounds__(256) void k_token_terms(
 
 // ---------------------------------------------------------------- loss reduce
 constexpr int kReduceNT = 1024;
-// count: number of terms when only the device knows it (nullable, then T)
-__global__ __launch_bounds__(kReduceNT) void k_loss_reduce(
-    const float* __restrict__ term, const int32_t* __restrict__ flag, int64_t T, const int32_t* __restrict__ count,
-    float* __restrict__ loss, float* __restrict__ clip_frac) {
-  if (count) T = *count;
-  __shared__ double s_sum[kReduceNT];
-  __shared__ int s_sig[kReduceNT], s_clip[kReduceNT];
-  double acc = 0.0;
-  int nsig = 0, nclip = 0;
-  // fixed order per thread; eight tokens' loads in flight (one at a time: 7.6 us at 16384 tokens)
-  constexpr int kAhead = 8;
-  for (int64_t t0 = threadIdx.x; t0 < T; t0 += kAhead * kReduceNT) {
-    float x[kAhead];
-    int f[kAhead];
-#pragma unroll
-    for (int u = 0; u < kAhead; ++u) {
-      const int64_t t = t0 + int64_t(u) * kReduceNT;
-      x[u] = t < T ? term[t] : 0.f;
-      f[u] = t < T ? flag[t] : 0;
-    }
-#pragma unroll
-    for (int u = 0; u < kAhead; ++u) {
-      acc += double(x[u]);
-      nsig += f[u] != 0;
-      nclip += f[u] == 2;
-    }
-  }
-  s_sum[threadIdx.x] = acc;
-  s_sig[threadIdx.x] = nsig;
-  s_clip[threadIdx.x] = nclip;
-  __syncthreads();
-  for (int off = kReduceNT / 2; off > 0; off >>= 1) {      // fixed tree
-    if (threadIdx.x < off) {
-      s_sum[threadIdx.x] += s_sum[threadIdx.x + off];
-      s_sig[threadIdx.x] += s_sig[threadIdx.x + off];
-      s_clip[threadIdx.x] += s_clip[threadIdx.x + off];
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    loss[0] = float(s_sum[0]);
-    if (clip_frac) clip_frac[0] = s_sig[0] ? float(s_clip[0]) / float(s_sig[0]) : 0.f;
-  }
+__global__ __launch_bounds__(kReduceNT) void k_loss_reduce(const float* __restrict__ term, const int32_t* __restrict__ flag,
+                                                           int64_t T, float* __restrict__ loss, float* __restrict__ clip_frac) {
+  loss_reduce<kReduceNT>(term, flag, T, loss, clip_frac);
 }
 
 // ---------------------------------------------------------------- dlogits
@@ -343,12 +303,6 @@ static void dispatch_dlogits_dtype(int32_t dtype, bool vec, const void* logits, 
   }
 }
 
-// Shared with the fused LM-head path: the reduction over `count` (device) terms.
-void loss_reduce_launch(const float* term, const int32_t* flag, const int32_t* count, float* loss, float* clip_frac,
-                        hipStream_t s) {
-  hipLaunchKernelGGL(k_loss_reduce, dim3(1), dim3(kReduceNT), 0, s, term, flag, int64_t(0), count, loss, clip_frac);
-}
-
 // The loss call proper; both entry points below end here.
 static aero_status loss_bwd_run(
     const void* logits, int32_t dtype, int64_t T, int32_t V, int64_t ld, const int32_t* targets,
@@ -371,7 +325,7 @@ static aero_status loss_bwd_run(
     return AERO_ERR_WORKSPACE;
   LossWorkspace ws = carve(workspace, T);
   if (T == 0) {
-    hipLaunchKernelGGL(k_loss_reduce, dim3(1), dim3(kReduceNT), 0, s, nullptr, nullptr, T, nullptr, loss, clip_frac);
+    hipLaunchKernelGGL(k_loss_reduce, dim3(1), dim3(kReduceNT), 0, s, nullptr, nullptr, T, loss, clip_frac);
     return launch_status();
   }
   const unsigned blocks = unsigned((T + 255) / 256);
@@ -387,7 +341,7 @@ static aero_status loss_bwd_run(
                                                 logprob_out, entropy_out, lse_out, dlogits, err_flag, ws.counter,
                                                 reinterpret_cast<int32_t*>(ws.lp_tmp), s);
       if (sp != AERO_OK) return sp;
-      hipLaunchKernelGGL(k_loss_reduce, dim3(1), dim3(kReduceNT), 0, s, ws.loss_term, ws.flag, T, nullptr, loss, clip_frac);
+      hipLaunchKernelGGL(k_loss_reduce, dim3(1), dim3(kReduceNT), 0, s, ws.loss_term, ws.flag, T, loss, clip_frac);
       return launch_status();
     }
     hipLaunchKernelGGL(k_signal_mask, dim3(blocks), dim3(256), 0, s, T, V, targets, token_rollout, adv, weight,
@@ -411,7 +365,7 @@ static aero_status loss_bwd_run(
   hipLaunchKernelGGL(token_terms, dim3(blocks), dim3(256), 0, s, logits, T, V, ld, targets, lse, old_logprob,
                      token_rollout, adv, weight, R, hyper, entropy, ref_logprob, ws.g, ws.loss_term, ws.flag,
                      ent ? ws.ea : nullptr, ent ? ws.eb : nullptr, lp_dst, err_flag);
-  hipLaunchKernelGGL(k_loss_reduce, dim3(1), dim3(kReduceNT), 0, s, ws.loss_term, ws.flag, T, nullptr, loss, clip_frac);
+  hipLaunchKernelGGL(k_loss_reduce, dim3(1), dim3(kReduceNT), 0, s, ws.loss_term, ws.flag, T, loss, clip_frac);
   if (dlogits) {
     const bool vec = rows_alike(logits, dlogits, storage_bytes(dtype));
     if (ent) dispatch_dlogits_dtype<true>(dtype, vec, logits, T, V, ld, targets, lse, ws.g, ws.ea, ws.eb, dlogits, s);

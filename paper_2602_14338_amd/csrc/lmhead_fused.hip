@@ -18,10 +18,10 @@
 //                            per token, except the sampled token's own entry, which is written here; the
 //                            scale travels with the other operand (dweight) or is applied after the
 //                            contraction (dhidden), so z is never formed a second time
-// Backward  loss reduce (shared with the logits path), then
-//           k_fused_dz       only when that does not apply (an entropy term in the rows, or a sampled
+// Backward  k_fused_dz       only when that does not apply (an entropy term in the rows, or a sampled
 //                            token more than 40 nats below another logit, where P would leave its safe
 //                            range): recompute the z^T tile and store dz itself in the same layouts
+//           k_hidden_and_loss  hidden rows times their scale, transposed; the loss sum
 //           k_gemm_dh        dhidden partials = (P or dz) @ weight   (split-K over the vocabulary, fp32)
 //           k_gemm_dw        dweight = (P or dz)^T @ (scale * hidden)
 //           k_scatter_dh     fp32 partials summed in fixed order, times scale -> bf16 dhidden at the original rows
@@ -33,9 +33,6 @@
 #include "gemm_tile.h"
 
 namespace aero {
-
-void loss_reduce_launch(const float* term, const int32_t* flag, const int32_t* count, float* loss, float* clip_frac,
-                        hipStream_t s);
 
 constexpr size_t kWsAlign = 256;
 inline size_t up(size_t x, size_t a) { return (x + a - 1) / a * a; }
@@ -621,22 +618,29 @@ __global__ __launch_bounds__(kRowsNT) void k_fused_rows(
 }
 
 // ------------------------------------------------------------------------------------------
-// backward: transposes
+// backward: the other operand of dweight, and the loss
 // ------------------------------------------------------------------------------------------
-// Transposes a row-major bf16 matrix of rows_in rows and C columns (C % 8 == 0, 16-byte aligned) into the K-slab layout
-// the GEMM tile reads: source row r becomes K index r, source column c becomes operand row c:
-//   out[(r / 64) * C_pad * 64 + c * 64 + r % 64] = in[r][c]
-// for c < C_pad; rows from rows_in and columns from C on do not exist in `in` and give 0.  With
-// scale != null the copy holds scale[r] * in[r][c] (product in fp32, rounded to bf16 once).
-// 64 x 64 tiles through LDS, one per workgroup of the grid (rows / 64, C_pad / 64).  Every global access is a 16-byte
+// The candidates' hidden rows ([T_pad][H], H % 8 == 0, 16-byte aligned), each times its scale (product in fp32, rounded to
+// bf16 once), transposed into the K-slab layout the GEMM tile reads: row r becomes K index r, column c operand row c:
+//   out[(r / 64) * C_pad * 64 + c * 64 + r % 64] = scale[r] * in[r][c]
+// for c < C_pad; columns from H on do not exist in `in` and give 0.
+// 64 x 64 tiles through LDS, one per workgroup of the grid (T_pad / 64 + 1, C_pad / 64); the first workgroup of the last
+// column forms the loss from the candidates' terms meanwhile (a launch of its own: 4.7 us a call).  Every global access is a 16-byte
 // vector: the tile is held in LDS as [r][c] with 32-bit writes; a thread then collects 8 consecutive r of one
 // column c for one 16-byte store, threads ordered so that a workgroup writes its 64 x 64 block of the slab as one
 // contiguous 8 KB run.
-__global__ __launch_bounds__(256) void k_transpose(const uint16_t* __restrict__ in, int64_t rows_in, int C, int C_pad,
-                                                   uint16_t* __restrict__ out, const float* __restrict__ scale) {
+__global__ __launch_bounds__(256) void k_hidden_and_loss(const uint16_t* __restrict__ in, int64_t T_pad, int C, int C_pad,
+                                                         uint16_t* __restrict__ out, const float* __restrict__ scale,
+                                                         const float* __restrict__ term, const int32_t* __restrict__ flag,
+                                                         const int32_t* __restrict__ nact, float* __restrict__ loss,
+                                                         float* __restrict__ clip_frac) {
   __shared__ uint32_t tile[64][33];   // [r][c / 2]
   const int64_t r0 = int64_t(blockIdx.x) * 64;
   const int c0 = blockIdx.y * 64;
+  if (r0 >= T_pad) {   // uniform over the workgroup
+    if (blockIdx.y == 0) loss_reduce<256>(term, flag, nact[0], loss, clip_frac);
+    return;
+  }
 #pragma unroll
   for (int k = 0; k < 2; ++k) {
     const int u = threadIdx.x + k * 256;
@@ -644,17 +648,15 @@ __global__ __launch_bounds__(256) void k_transpose(const uint16_t* __restrict__ 
     const int64_t r = r0 + rr;
     const int c = c0 + c8;
     u32x4_t v = {0u, 0u, 0u, 0u};
-    if (r < rows_in && c < C) {
+    if (c < C) {
       v = *reinterpret_cast<const u32x4_t*>(in + r * C + c);
-      if (scale) {
-        const float f = scale[r];
-        float x[8];
-        unpack8(v, x);
-        v.x = pack_bf16x2(x[0] * f, x[1] * f);
-        v.y = pack_bf16x2(x[2] * f, x[3] * f);
-        v.z = pack_bf16x2(x[4] * f, x[5] * f);
-        v.w = pack_bf16x2(x[6] * f, x[7] * f);
-      }
+      const float f = scale[r];
+      float x[8];
+      unpack8(v, x);
+      v.x = pack_bf16x2(x[0] * f, x[1] * f);
+      v.y = pack_bf16x2(x[2] * f, x[3] * f);
+      v.z = pack_bf16x2(x[4] * f, x[5] * f);
+      v.w = pack_bf16x2(x[6] * f, x[7] * f);
     }
     tile[rr][c8 / 2 + 0] = v.x;
     tile[rr][c8 / 2 + 1] = v.y;
@@ -953,14 +955,20 @@ __global__ __launch_bounds__(256) void k_scatter_dh(const float* __restrict__ dh
     const float* src = dh_part + int64_t(j) * H + k;
     const int64_t step = int64_t(n_pad) * H;
     int s = 0;
-    for (; s + 4 <= S; s += 4) {   // four loads in flight, added in split order
-      f32x4_t v[4];
+    auto add = [&](auto count) {   // so many loads in flight, added in split order
+      constexpr int N = decltype(count)::value;
+      f32x4_t v[N];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) v[u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(src + (s + u) * step));
+      for (int u = 0; u < N; ++u) v[u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(src + (s + u) * step));
 #pragma unroll
-      for (int u = 0; u < 4; ++u) acc += v[u];
-    }
-    for (; s < S; ++s) acc += __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(src + s * step));
+      for (int u = 0; u < N; ++u) acc += v[u];
+      s += N;
+    };
+    while (s + 12 <= S) add(std::integral_constant<int, 12>{});
+    if (s + 8 <= S) add(std::integral_constant<int, 8>{});
+    if (s + 4 <= S) add(std::integral_constant<int, 4>{});
+    if (s + 2 <= S) add(std::integral_constant<int, 2>{});
+    if (s < S) add(std::integral_constant<int, 1>{});
     uint2 o;
     o.x = pack_bf16x2(acc.x * f, acc.y * f);
     o.y = pack_bf16x2(acc.z * f, acc.w * f);
@@ -1087,7 +1095,7 @@ extern "C" aero_status aero_lmhead_logprob_fused(
   }
   if (!bwd) return launch_status();
 
-  // ---- loss, operand copies ----
+  // ---- loss, operand copy ----
   uint16_t* hTc = reinterpret_cast<uint16_t*>(ws + p.off_hTc);
   float* dh_acc = reinterpret_cast<float*>(ws + p.off_dhacc);
   if (T == 0) {   // no forward kernel ran: an empty candidate set for the kernels below
@@ -1097,7 +1105,6 @@ extern "C" aero_status aero_lmhead_logprob_fused(
     hipLaunchKernelGGL(k_fused_rows<16>, dim3(unsigned(p.T_pad / 16)), dim3(kRowsNT), 0, s, p.tiles_v, p.T_pad, fidx, nf,
                        part_m, part_s, part_sz, zy, logprob, entropy, lse, terms);
   }
-  loss_reduce_launch(terms.term, terms.flag, nact, loss, clip_frac, s);
   if (T > 0) {   // recompute mode only (the kernel leaves at once otherwise)
     const int n = p.tiles_v * tiles_t;
     if (ent)
@@ -1109,9 +1116,9 @@ extern "C" aero_status aero_lmhead_logprob_fused(
                          H, p.tiles_v, p.T_pad, p.VC, terms.force_recompute, nact, terms.gc, terms.lsec, terms.yc, terms.ac,
                          terms.bc, dz, dzT);
   }
-  // the candidates' hidden rows, each times its scale, transposed to hTc: K-slabs over the candidate positions
-  hipLaunchKernelGGL(k_transpose, dim3(unsigned(p.T_pad / 64), unsigned(p.H_pad / 64)), dim3(256), 0, s, hf, p.T_pad, H,
-                     p.H_pad, hTc, terms.scale);
+  hipLaunchKernelGGL(k_hidden_and_loss, dim3(unsigned(p.T_pad / 64 + 1), unsigned(p.H_pad / 64)), dim3(256), 0, s, hf, p.T_pad, H,
+                     p.H_pad, hTc, terms.scale, terms.term, terms.flag, nact, loss, clip_frac);
+
   // ---- the two gradient contractions over the whole vocabulary ----
   if (T > 0) {
     // dz columns [V, V_ld) are zero, weight rows past V read as zeros: the contraction runs over the padded vocabulary
