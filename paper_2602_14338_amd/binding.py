@@ -109,19 +109,26 @@ def _ptr(t: Optional[torch.Tensor], dtype=None, name: str = "") -> Optional[int]
 
 
 class _Marshal:
-    """``pointers(t, dtype, name, ...)``: `_ptr` of every triple in one native call (csrc/marshal.cpp)."""
+    """The native module (csrc/marshal.cpp).  ``pointers(t, dtype, name, ...)``: `_ptr` of every triple in one call;
+    ``group_advantage`` and the others: a whole call whose arguments are all plain, NotImplemented for any other."""
 
     def __getattr__(self, name):
-        if name != "pointers":
+        if name not in ("pointers", "group_advantage", "logprob_fwd", "loss_bwd", "fused"):
             raise AttributeError(name)
         try:
             from . import _marshal
         except ImportError as e:
             raise AeroError("the package's _marshal module is missing: build it with "
                             "`python -m paper_2602_14338_amd.build` (there is no fallback path)") from e
-        _marshal.setup(AeroError, _ptr)
-        self.pointers = _marshal.pointers
-        return self.pointers
+        if name == "pointers":
+            _marshal.setup(AeroError, _ptr)
+        else:
+            entries = (_lib.aero_group_advantage, _lib.aero_logprob_fwd, _lib.aero_grpo_loss_bwd,
+                       _lib.aero_grpo_loss_bwd_noalloc, _lib.aero_lmhead_logprob_fused)
+            _marshal.bind(torch._C._cuda_getCurrentRawStream, AdvParams, *(C.cast(f, C.c_void_p).value for f in entries))
+        fn = getattr(_marshal, name)
+        setattr(self, name, fn)
+        return fn
 
 
 _m = _Marshal()
@@ -151,6 +158,10 @@ def aero_workspace_bytes(op: int, T: int = 0, V: int = 0, H: int = 0, R: int = 0
 def aero_group_advantage(rewards, lengths, group_offsets, keep_priority, Q: int, R: int, params: AdvParams,
                          adv, weight, keep_mask, kept_index, kept_offsets, group_zero_var, group_category,
                          err_flag=None) -> None:
+    st = _m.group_advantage(rewards, lengths, group_offsets, keep_priority, Q, R, params, adv, weight, keep_mask,
+                            kept_index, kept_offsets, group_zero_var, group_category, err_flag)
+    if st is not NotImplemented:
+        return _check(st, "aero_group_advantage")
     pc = params.to_c()
     p = _m.pointers(rewards, _F32, "rewards", lengths, _I32, "lengths", group_offsets, _I32, "group_offsets",
                     keep_priority, None, "keep_priority", adv, _F32, "adv", weight, _F32, "weight",
@@ -163,6 +174,9 @@ def aero_group_advantage(rewards, lengths, group_offsets, keep_priority, Q: int,
 
 def aero_logprob_fwd(logits, T: int, V: int, ld: int, targets, row_active, logprob, entropy, lse,
                      err_flag=None) -> None:
+    st = _m.logprob_fwd(logits, T, V, ld, targets, row_active, logprob, entropy, lse, err_flag)
+    if st is not NotImplemented:
+        return _check(st, "aero_logprob_fwd")
     z, *p = _m.pointers(logits, None, "logits", targets, _I32, "targets", row_active, _U8, "row_active",
                         logprob, _F32, "logprob", entropy, _F32, "entropy", lse, _F32, "lse",
                         err_flag, _I32, "err_flag")
@@ -186,6 +200,11 @@ def aero_grpo_loss_bwd(logits, T: int, V: int, ld: int, targets, lse, old_logpro
                        R: int, eps_lo: float, eps_hi: float, grad_scale: float, loss, clip_frac, logprob_out,
                        dlogits, workspace, err_flag=None, entropy_out=None, lse_out=None,
                        entropy_coef: float = 0.0, entropy=None, kl_coef: float = 0.0, ref_logprob=None) -> None:
+    st = _m.loss_bwd(logits, T, V, ld, targets, lse, entropy, old_logprob, token_rollout, adv, weight, R, eps_lo, eps_hi,
+                     grad_scale, entropy_coef, kl_coef, ref_logprob, loss, clip_frac, logprob_out, entropy_out, lse_out,
+                     dlogits, err_flag, workspace)
+    if st is not NotImplemented:
+        return _check(st, "aero_grpo_loss_bwd")
     z, *p = _loss_pointers(logits, targets, lse, entropy, old_logprob, token_rollout, adv, weight, ref_logprob, loss,
                            clip_frac, logprob_out, entropy_out, lse_out, dlogits, err_flag)
     ws, = _m.pointers(workspace, None, "workspace")
@@ -201,6 +220,11 @@ def aero_grpo_loss_bwd_noalloc(logits, T: int, V: int, ld: int, targets, lse, ol
                                entropy_coef: float = 0.0, entropy=None, kl_coef: float = 0.0,
                                ref_logprob=None) -> None:
     """aero_grpo_loss_bwd without a workspace argument: the library's own fixed scratch is used."""
+    st = _m.loss_bwd(logits, T, V, ld, targets, lse, entropy, old_logprob, token_rollout, adv, weight, R, eps_lo, eps_hi,
+                     grad_scale, entropy_coef, kl_coef, ref_logprob, loss, clip_frac, logprob_out, entropy_out, lse_out,
+                     dlogits, err_flag)
+    if st is not NotImplemented:
+        return _check(st, "aero_grpo_loss_bwd_noalloc")
     z, *p = _loss_pointers(logits, targets, lse, entropy, old_logprob, token_rollout, adv, weight, ref_logprob, loss,
                            clip_frac, logprob_out, entropy_out, lse_out, dlogits, err_flag)
     st = _lib.aero_grpo_loss_bwd_noalloc(z, _dtype_code(logits), T, V, ld, *p[:7], R, eps_lo, eps_hi, grad_scale,
@@ -214,6 +238,11 @@ def aero_lmhead_logprob_fused(hidden, weight, T: int, H: int, V: int, targets, l
                               loss=None, clip_frac=None, dhidden=None, dweight=None, workspace=None,
                               err_flag=None, entropy_coef: float = 0.0, kl_coef: float = 0.0,
                               ref_logprob=None, dweight_accumulate: bool = False) -> None:
+    st = _m.fused(hidden, weight, T, H, V, targets, logprob, entropy, lse, old_logprob, token_rollout, adv, weight_rollout,
+                  R, eps_lo, eps_hi, grad_scale, entropy_coef, kl_coef, ref_logprob, loss, clip_frac, dhidden, dweight,
+                  dweight_accumulate, err_flag, workspace)
+    if st is not NotImplemented:
+        return _check(st, "aero_lmhead_logprob_fused")
     p = _m.pointers(
         hidden, _BF16, "hidden", weight, _BF16, "weight", targets, _I32, "targets", logprob, _F32, "logprob",
         entropy, _F32, "entropy", lse, _F32, "lse", old_logprob, _F32, "old_logprob",

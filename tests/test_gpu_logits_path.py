@@ -204,6 +204,47 @@ def test_group_advantage_general_rewards_and_error_flag(gh):
     assert int(out["err"].item()) & orc.ERR_NONBINARY_REWARD
 
 
+def test_binding_native_and_general_ways_agree(gh, monkeypatch):
+    """A call whose arguments are all plain goes to the library in one native step; forms that are not (an int subclass,
+    parameters of a subclass) are converted as ever, with the same results, and what was refused raises the same on both ways."""
+    b = gh.aero.binding
+    wl = ai.make_config("cfg1")
+    rew, ln, off = gh.dev(wl.rewards), gh.dev(wl.lengths), gh.dev(wl.group_offsets)
+
+    class Small(int):
+        pass
+
+    class Params(gh.aero.AdvParams):
+        pass
+
+    def call(Q=wl.Q, p=gh.aero.AdvParams(reject_enable=1), rewards=rew, mask_dtype=torch.uint8):
+        out = [torch.zeros(wl.R, device=gh.DEV), torch.zeros(wl.R, device=gh.DEV),
+               torch.zeros(wl.R, dtype=mask_dtype, device=gh.DEV), torch.zeros(wl.R, dtype=torch.int32, device=gh.DEV),
+               torch.zeros(wl.Q + 1, dtype=torch.int32, device=gh.DEV), torch.zeros(wl.Q, dtype=torch.uint8, device=gh.DEV),
+               torch.zeros(wl.Q, dtype=torch.uint8, device=gh.DEV)]
+        b.aero_group_advantage(rewards, ln, off, None, Q, wl.R, p, *out, None)
+        return out
+
+    def outcome(**kw):
+        try:
+            return [o.cpu() for o in call(**kw)]
+        except Exception as e:   # noqa: BLE001
+            return type(e), str(e)
+
+    assert b._m.group_advantage is not None
+    forms = [dict(), dict(Q=Small(wl.Q)), dict(p=Params(reject_enable=1)), dict(p=gh.aero.AdvParams(reject_enable=True)),
+             dict(Q=float(wl.Q)), dict(Q=2 ** 40), dict(Q=-1), dict(p=None), dict(rewards=rew.cpu()), dict(rewards=rew.double()),
+             dict(rewards=rew.repeat(2)[::2]), dict(mask_dtype=torch.int32), dict(p=gh.aero.AdvParams(k_ratio=0))]
+    native = [outcome(**f) for f in forms]
+    monkeypatch.setattr(b._m, "group_advantage", lambda *a: NotImplemented)
+    for f, got in zip(forms, native):
+        want = outcome(**f)
+        if isinstance(want, tuple):
+            assert got == want, f
+        else:
+            assert all(torch.equal(x, y) for x, y in zip(got, want)), f
+
+
 # ------------------------------------------------------------------ softmax statistics
 
 def check_fwd(gh, wl, row_active=None, targets=None, offset_elems=0):
