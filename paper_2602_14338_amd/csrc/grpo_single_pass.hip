@@ -3,7 +3,8 @@
 // into registers (and LDS where it is long: 20 x 16 bytes per thread of 1024 at V = 151936 in bf16),
 // the log-partition is reduced across the workgroup, and the gradient row is produced from the
 // copy on chip - twice the row's bytes of traffic instead of three times for a forward pass followed
-// by a backward pass.  All storage types, any row length up to 20 x 1024 vectors, any row alignment.
+// by a backward pass.  All storage types, any row length up to 20 x 1024 vectors (up to four times that with what the chip does
+// not hold read again), any row alignment.
 #include <mutex>
 
 #include "aero_device.h"
@@ -266,7 +267,8 @@ __global__ __launch_bounds__(256) void k_row_order(int64_t T, int V, int R, cons
   if (in && !need && !untouched) order[T - 1 - (base_rest + __popcll(m_rest & below))] = int32_t(t);
 }
 
-template <int DT, int NV, int NL, bool ENT>
+constexpr int kTailAhead = 4;
+template <int DT, int NV, int NL, bool ENT, bool LONG>
 __global__ __launch_bounds__(kSpNT) void k_row_stream(
     const void* logits, int64_t T, int V, int64_t ld, const int32_t* __restrict__ targets,
     const float* __restrict__ old_logprob, const int32_t* __restrict__ token_rollout,
@@ -365,6 +367,23 @@ __global__ __launch_bounds__(kSpNT) void k_row_stream(
         }
         __builtin_amdgcn_sched_barrier(0);
       }
+      if constexpr (LONG) {   // what the CU does not hold: plain loads, so that the memory-side cache has it for the second time
+        for (int from = NV * kSpNT; from < nvec; from += kTailAhead * kSpNT) {   // uniform
+          u32x4_t w[kTailAhead];
+#pragma unroll
+          for (int u = 0; u < kTailAhead; ++u)
+            w[u] = __builtin_amdgcn_raw_buffer_load_b128(zsrc, voff_ld + uint32_t(from + u * kSpNT) * 16u, 0, 0);
+#pragma unroll
+          for (int u = 0; u < kTailAhead; ++u) {
+            if (tid < nvec - from - u * kSpNT) {
+              float z[E];
+              unpack_vec<DT>(w[u], z);
+              stat_update<E>(st, z);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        }
+      }
       if (jr >= 0) {
         float z[1] = {zr};
         stat_update<1>(st, z);
@@ -437,6 +456,23 @@ __global__ __launch_bounds__(kSpNT) void k_row_stream(
                                                  voff_st + uint32_t(NL + u) * (kSpNT * 16u), 0, 2);
         __builtin_amdgcn_sched_barrier(0);
       }
+      if constexpr (LONG) {
+        const __amdgpu_buffer_rsrc_t zsrc = row_vectors<DT>(logits, t, ld, geom);
+        for (int from = NV * kSpNT; from < nvec; from += kTailAhead * kSpNT) {   // uniform
+          u32x4_t w[kTailAhead];
+#pragma unroll
+          for (int u = 0; u < kTailAhead; ++u)
+            w[u] = __builtin_amdgcn_raw_buffer_load_b128(zsrc, voff_st + uint32_t(from + u * kSpNT) * 16u, 0, 2);
+#pragma unroll
+          for (int u = 0; u < kTailAhead; ++u) {
+            const int k = from + u * kSpNT;
+            if (tid < nvec - k)
+              __builtin_amdgcn_raw_buffer_store_b128(grad_vec<DT, ENT>(w[u], a, ng, c, g, tid == yvec - k, ye), dsrc,
+                                                     voff_st + uint32_t(k) * 16u, 0, 2);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        }
+      }
       if (jr >= 0) {
         float d = (ENT ? fmaf(a, zr, ng) : ng) * exp2_fast(fmaf(zr, kLog2e, c));
         if (jr == y) d += g;
@@ -477,7 +513,7 @@ __global__ void k_set_counter(int32_t* ctr, int32_t v) {
   ctr[3] = 0;
 }
 
-constexpr int kStreamVecs = 20, kHeldVecs = 8;
+constexpr int kStreamVecs = 20, kHeldVecs = 8, kLongVecs = 80;
 
 // Threads of the workgroup that takes a row of at most kHeldVecs x 1024 vectors: the fewest that hold it in kHeldVecs
 // vectors each, so that a CU works on several rows.
@@ -486,8 +522,8 @@ inline int row_threads(int nvec) {
   return nvec <= kHeldVecs * 64 ? 64 : nvec <= kHeldVecs * 256 ? 256 : nvec <= kHeldVecs * 512 ? 512 : kSpNT;
 }
 
-// True when a single-pass kernel applies: element-aligned rows of at most 20 vectors per thread of 1024, and
-// logits and dlogits alike in their position relative to 16 bytes.
+// True when a single-pass kernel applies: element-aligned rows of at most 20 vectors per thread of 1024 (80, of which a CU
+// holds 20 and reads the others again), and logits and dlogits alike in their position relative to 16 bytes.
 //
 // Where it does, it is not always the faster one; times of two passes / one pass by storage type, every row with a
 // gradient:
@@ -500,15 +536,25 @@ inline int row_threads(int nvec) {
 //                                rows and 1.03-1.25 from 96 on, 8-bit 0.7-1.05 up to 160 and 1.02-1.12 from 200 on
 //     more rows                  up to 320 MB, which the 256 MB memory-side cache holds for the second pass, 0.8-1.05;
 //                                beyond fp16 1.00-1.17, fp32 1.06-1.19, 8-bit 0.92-1.13
-// The last line is taken for the batches that the call is for, where padding and rollouts without advantage cost the
+//   over 20 vectors per thread   the CU holds 20 and reads the rest again, from the memory-side cache: 4 to 6 bytes per 2-byte
+//                                logit instead of 6.  16-bit 0.78-0.99 up to 32 rows, 1.05-1.31 from 48 to 256; fp32 0.95-1.3 at
+//                                16 rows, 1.05-1.48 from 24 to 256; 8-bit 0.7-1.0 up to 160, 1.09 at 256.  Between 257 rows and
+//                                256 MB, where two passes find the rows in that cache and one starts a second round of
+//                                rows, 0.78-1.03 (padded 0.91-1.28); beyond 256 MB 1.0-1.47 (V = 262144: bf16 4577 rows 992 /
+//                                882 us, fp32 1923 / 1735; fp32 7891 rows of 152064 2206 / 1706)
+// The last line but one is taken for the batches that the call is for, where padding and rollouts without advantage cost the
 // one pass least (9 of 16 rows valid, a third of the groups all equal: fp16 1.19-1.42, fp32 1.4-2.0, 8-bit 1.09-1.27;
 // packed: fp16 0.99-1.34, 8-bit 0.87-1.23).  bf16 rows take the one pass throughout: streaming 0.76-1.08 up to 8 rows,
 // 0.84-1.3 from 64 on, loss only 0.55-0.99.
 bool single_pass_applicable(int32_t dtype, int64_t T, int V, const void* logits, const void* dlogits) {
   const size_t elt = storage_bytes(dtype);
   const size_t nvec = size_t(V) * elt / 16;
-  if (nvec > size_t(kStreamVecs) * kSpNT || !rows_alike(logits, dlogits, elt)) return false;
+  if (nvec > size_t(kLongVecs) * kSpNT || !rows_alike(logits, dlogits, elt)) return false;
   if (nvec <= size_t(kHeldVecs) * kSpNT && !grid_fits(T, row_threads(int(nvec)))) return false;
+  if (nvec > size_t(kStreamVecs) * kSpNT) {
+    const int64_t few = dtype == AERO_F32 ? 24 : dtype == AERO_F8E4M3 ? 192 : 48;
+    return dlogits && T >= few && (T <= 256 || size_t(T) * nvec * 16 >= (size_t(256) << 20));
+  }
   if (dtype == AERO_BF16) return true;
   if (nvec <= size_t(kHeldVecs) * kSpNT) return dlogits || dtype != AERO_F8E4M3 || nvec <= 4 * kSpNT || T <= 512;
   if (!dlogits) return false;
@@ -556,15 +602,20 @@ static aero_status single_pass_launch_t(const RowArgs& r, int32_t* row_counter, 
   } else {
     constexpr int NL = 9;
     constexpr int kLdsBytes = NL * kSpNT * 16;   // 144 KB of wave-private slots
-    const auto kernel = k_row_stream<DT, kStreamVecs, NL, ENT>;
     // raising the dynamic-LDS limit is per function; done once per process, safely from any thread
     static std::once_flag attr_once;
     static hipError_t attr_rc = hipSuccess;
     std::call_once(attr_once, [&] {
-      attr_rc = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    kLdsBytes);
+      const void* const kernels[] = {reinterpret_cast<const void*>(k_row_stream<DT, kStreamVecs, NL, ENT, false>),
+                                     reinterpret_cast<const void*>(k_row_stream<DT, kStreamVecs, NL, ENT, true>)};
+      for (const void* k : kernels) {
+        const hipError_t rc = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
+        if (rc != hipSuccess) attr_rc = rc;
+      }
     });
     if (attr_rc != hipSuccess) return AERO_ERR_HIP;
+    const auto kernel = nvec <= kStreamVecs * kSpNT ? k_row_stream<DT, kStreamVecs, NL, ENT, false>
+                                                    : k_row_stream<DT, kStreamVecs, NL, ENT, true>;
     const int cus = compute_units();
     const unsigned grid = unsigned(r.T < cus ? r.T : cus);   // one persistent workgroup per CU
     hipLaunchKernelGGL(k_set_counter, dim3(1), dim3(1), 0, s, row_counter, int32_t(grid));

@@ -590,8 +590,8 @@ def test_f8_gradient_rounding_bit_exact(gh):
 
 
 # One pass over the logits: a row of n 16-byte vectors goes to workgroups of 64 / 256 / 512 / 1024 threads up to
-# n = 512 / 2048 / 4096 / 8192, to the streaming kernel up to 20480 and takes two passes beyond; an odd pitch puts every
-# row at another offset from 16 bytes.
+# n = 512 / 2048 / 4096 / 8192, to the streaming kernel up to 20480, to its form that reads part of a row again up to 81920
+# and takes two passes beyond; an odd pitch puts every row at another offset from 16 bytes.
 @pytest.mark.parametrize("dtype,V,ld,slots", [
     ("bf16", 4096, 4096, 9), ("bf16", 4104, 4107, 9), ("bf16", 16391, 16391, 6), ("bf16", 32775, 32777, 5),
     ("bf16", 65543, 65543, 4), ("bf16", 163847, 163849, 3), ("bf16", 3, 5, 40), ("bf16", 9, 9, 40),
@@ -600,7 +600,11 @@ def test_f8_gradient_rounding_bit_exact(gh):
     ("f8e4m3", 8207, 8209, 6), ("f8e4m3", 131103, 131107, 3), ("f8e4m3", 17, 19, 40),
     # enough rows for one pass over fp16 and 8-bit rows that stream (96 and 192), and too few
     ("f16", 151937, 151939, 7), ("f16", 65549, 65551, 6), ("f16", 65549, 65551, 5), ("f16", 65549, 65549, 17),
-    ("f8e4m3", 131103, 131107, 13), ("f8e4m3", 131103, 131107, 11)])
+    ("f8e4m3", 131103, 131107, 13), ("f8e4m3", 131103, 131107, 11),
+    # rows that a CU does not hold: one vector more than it does, an odd number of rounds more, the longest, too few rows
+    ("bf16", 163855, 163857, 3), ("bf16", 163848, 163848, 2), ("bf16", 262144, 262144, 4), ("f16", 180001, 180003, 3),
+    ("f32", 81931, 81931, 2), ("f32", 152064, 152064, 2), ("f32", 327683, 327683, 2), ("f32", 327684, 327684, 2),
+    ("f8e4m3", 327713, 327715, 12)])
 def test_single_pass_edges(gh, dtype, V, ld, slots):
     def wl():
         return ai.make_config("cfg2", V=V, ld=ld, slots=slots, len_lo=1, len_hi=slots - 1, dtype=dtype)
@@ -716,7 +720,8 @@ def test_streaming_kernel_optional_terms_several_rows_per_workgroup(gh):
 
 @pytest.mark.parametrize("inplace,terms", [(False, False), (True, True), (True, False), (False, True)])
 @pytest.mark.parametrize("dtype,V,ld,T", [("bf16", 70003, 70005, 624), ("f16", 65549, 65551, 2496), ("f32", 32777, 32779, 2496),
-                                          ("f8e4m3", 230001, 230003, 1456)])
+                                          ("f8e4m3", 230001, 230003, 1456),
+                                          ("bf16", 164003, 164005, 832), ("f32", 110001, 110003, 624)])   # held in part
 def test_streaming_rows_of_changing_alignment(gh, dtype, V, ld, T, inplace, terms):
     """Several rows per workgroup of the streaming kernel, each at another offset from 16 bytes than the one whose slots
     it takes over, after gradient rows and after rows that are only filled with zeros (padding, advantage 0) or
