@@ -334,6 +334,10 @@ __device__ __forceinline__ void store_tile_both_layouts(const uint32_t (&pk)[kNB
 // z - zy > kStoreRange on a candidate column raises nact[2], and the backward pass then forms dz by
 // recomputing z as it does for rows with an entropy term (k_fused_dz).  The exponentials are the ones the
 // statistics take anyway: P = exp(z - m) * exp(m - zy) with m the running offset of the lane.
+// What a ragged token tile does not hold costs little: rows past the count lie behind the operand's bytes (a request for them
+// moves nothing), a wave without a row has no epilogue, 64 columns without a candidate are not stored, and the dhidden
+// contraction does not request 32 rows without one.  Whole calls at H = 1536, V = 151936: 100 tokens 462 -> 428 us, 300 602 -> 572,
+// 600 776 -> 761; forward only 300 tokens 235 -> 215; 1100 tokens at H = 896, V = 50257 348 -> 333.
 constexpr float kStoreRange = 40.f;
 
 // stat_update for 16 values that also hands back the exponentials it formed (relative to st.m on return)
@@ -379,7 +383,7 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_fused_stats(
   const int wm = wp.wm, wn = wp.wn;
   GemmStream<true, false, false, false, true> stream(H, kDK, H, kDK, H);
   auto source = [&](int tv, int tt) {
-    return TileSrc{W, Hf, (int64_t(V) * H) * 2, (T_pad * H) * 2, uint32_t(int64_t(tv) * kTile * H * 2),
+    return TileSrc{W, Hf, (int64_t(V) * H) * 2, (int64_t(n_rows) * H) * 2, uint32_t(int64_t(tv) * kTile * H * 2),
                    uint32_t(int64_t(tt) * kTile * H * 2), (H + kDK - 1) / kDK};
   };
   RowStat* const xch = reinterpret_cast<RowStat*>(smem + kEpilogueOff / 2);   // [256 token columns]
@@ -400,8 +404,9 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_fused_stats(
   request_ref(tt, buf);
   while (more) {
     const int m0 = tv * kTile, n0 = tt * kTile;
-    const bool store = STORE && n0 < n_cand;   // uniform over the workgroup
+    const bool store = STORE && n0 + wn * 64 < n_cand;   // uniform over the wave: nobody reads 64 columns without a candidate
     wp.active = n0 + wn * 64 < n_rows;
+    const bool active = !STORE || wp.active;   // the epilogue has something to do (without the stores the branch costs what it saves)
     wp.warm_a = warm_share(tt, tiles_t_act);
     wp.warm_b = warm_share(tv, tiles_v);
     wp.warm_from = tiles_t_act > 1 ? kWarmSlices : kWarmSlicesAlone;
@@ -419,73 +424,76 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_fused_stats(
     const bool full = m0 + kTile <= V;
     uint32_t pk[kNB][kMB][2] = {};   // a value on every path: not carried around the walk
     bool wide = false;
-    RowStat st[kNB];
-    constexpr int kGroup = 4;   // accumulator blocks per statistics update: 16 values
+    const int my_col = acc_col(wn, (lane & 16 ? 2 : 0) + (lane & 32 ? 1 : 0), lane);
+    RowStat mine = stat_identity();
+    if (active) {   // uniform over the wave
+      RowStat st[kNB];
+      constexpr int kGroup = 4;   // accumulator blocks per statistics update: 16 values
 #pragma unroll
-    for (int nb = 0; nb < kNB; ++nb) {
-      st[nb] = stat_identity();
-      const int col = n0 + acc_col(wn, nb, lane);
-      const bool col_cand = store && col < n_cand;
-      const float ref = store ? ref_buf[buf * kTile + acc_col(wn, nb, lane)] : 0.f;
+      for (int nb = 0; nb < kNB; ++nb) {
+        st[nb] = stat_identity();
+        const int col = n0 + acc_col(wn, nb, lane);
+        const bool col_cand = store && col < n_cand;
+        const float ref = store ? ref_buf[buf * kTile + acc_col(wn, nb, lane)] : 0.f;
 #pragma unroll
-      for (int mg = 0; mg < kMB; mg += kGroup) {
-        if (full) {
-          float z[16], e[16];
+        for (int mg = 0; mg < kMB; mg += kGroup) {
+          if (full) {
+            float z[16], e[16];
 #pragma unroll
-          for (int i = 0; i < 16; ++i) z[i] = acc[mg + i / 4][nb][i % 4];
-          if (store) {
-            const float vm = stat_update_keep(st[nb], z, e);
-            // columns past the candidates keep zeros: their rows of the other operand are zero as well
-            const float f = col_cand ? exp2_fast((st[nb].m - ref) * kLog2e) : 0.f;
-            wide |= col_cand && vm - ref > kStoreRange;
+            for (int i = 0; i < 16; ++i) z[i] = acc[mg + i / 4][nb][i % 4];
+            if (store) {
+              const float vm = stat_update_keep(st[nb], z, e);
+              // columns past the candidates keep zeros: their rows of the other operand are zero as well
+              const float f = col_cand ? exp2_fast((st[nb].m - ref) * kLog2e) : 0.f;
+              wide |= col_cand && vm - ref > kStoreRange;
 #pragma unroll
-            for (int k = 0; k < kGroup; ++k) {
-              pk[nb][mg + k][0] = pack_bf16x2(e[4 * k] * f, e[4 * k + 1] * f);
-              pk[nb][mg + k][1] = pack_bf16x2(e[4 * k + 2] * f, e[4 * k + 3] * f);
+              for (int k = 0; k < kGroup; ++k) {
+                pk[nb][mg + k][0] = pack_bf16x2(e[4 * k] * f, e[4 * k + 1] * f);
+                pk[nb][mg + k][1] = pack_bf16x2(e[4 * k + 2] * f, e[4 * k + 3] * f);
+              }
+            } else {
+              stat_update<16>(st[nb], z);
             }
           } else {
-            stat_update<16>(st[nb], z);
-          }
-        } else {
-          float d[16];
+            float d[16];
 #pragma unroll
-          for (int i = 0; i < 16; ++i) {
-            d[i] = 0.f;
-            if (m0 + acc_row(wm, mg + i / 4, i % 4, lane) < V) {
-              const float zi = acc[mg + i / 4][nb][i % 4];
-              float z[1] = {zi};
-              stat_update<1>(st[nb], z);
-              if (store && col_cand) {
-                d[i] = exp2_fast((zi - ref) * kLog2e);
-                wide |= zi - ref > kStoreRange;
+            for (int i = 0; i < 16; ++i) {
+              d[i] = 0.f;
+              if (m0 + acc_row(wm, mg + i / 4, i % 4, lane) < V) {
+                const float zi = acc[mg + i / 4][nb][i % 4];
+                float z[1] = {zi};
+                stat_update<1>(st[nb], z);
+                if (store && col_cand) {
+                  d[i] = exp2_fast((zi - ref) * kLog2e);
+                  wide |= zi - ref > kStoreRange;
+                }
               }
             }
-          }
-          if (store) {
+            if (store) {
 #pragma unroll
-            for (int k = 0; k < kGroup; ++k) {
-              pk[nb][mg + k][0] = pack_bf16x2(d[4 * k], d[4 * k + 1]);
-              pk[nb][mg + k][1] = pack_bf16x2(d[4 * k + 2], d[4 * k + 3]);
+              for (int k = 0; k < kGroup; ++k) {
+                pk[nb][mg + k][0] = pack_bf16x2(d[4 * k], d[4 * k + 1]);
+                pk[nb][mg + k][1] = pack_bf16x2(d[4 * k + 2], d[4 * k + 3]);
+              }
             }
           }
         }
       }
-    }
-    // Four lanes (l % 16 equal) share a column and hold the same four columns each: two exchanges in which a
-    // lane passes on half of its columns leave every lane with one of the wave's 64 columns, whole.
-    static_assert(kNB == 4, "the exchange below halves four columns twice");
-    const bool hi16 = lane & 16, hi32 = lane & 32;
-    RowStat two[2];
+      // Four lanes (l % 16 equal) share a column and hold the same four columns each: two exchanges in which a
+      // lane passes on half of its columns leave every lane with one of the wave's 64 columns, whole.
+      static_assert(kNB == 4, "the exchange below halves four columns twice");
+      const bool hi16 = lane & 16, hi32 = lane & 32;
+      RowStat two[2];
 #pragma unroll
-    for (int k = 0; k < 2; ++k)
-      two[k] = stat_merge(hi16 ? st[2 + k] : st[k], stat_shfl_xor(hi16 ? st[k] : st[2 + k], 16));
-    const RowStat mine = stat_merge(hi32 ? two[1] : two[0], stat_shfl_xor(hi32 ? two[0] : two[1], 32));
-    const int my_col = acc_col(wn, (hi16 ? 2 : 0) + (hi32 ? 1 : 0), lane);
+      for (int k = 0; k < 2; ++k)
+        two[k] = stat_merge(hi16 ? st[2 + k] : st[k], stat_shfl_xor(hi16 ? st[k] : st[2 + k], 16));
+      mine = stat_merge(hi32 ? two[1] : two[0], stat_shfl_xor(hi32 ? two[0] : two[1], 32));
+    }
     // the two waves that share these token columns (wm = 0, 1) merge through LDS
     buf ^= 1;
-    if (wm == 1) xch[my_col] = mine;
+    if (wm == 1 && active) xch[my_col] = mine;
     lds_barrier();   // the slices of the next tile put barriers between these reads and the next writes
-    if (wm == 0) {
+    if (wm == 0 && active) {
       const RowStat r = stat_merge(mine, xch[my_col]);
       const int64_t o = int64_t(tv_now) * T_pad + n0 + my_col;   // column < T_pad
       part_m[o] = r.m;
@@ -707,7 +715,7 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_fused_dz(
   const int wm = wp.wm, wn = wp.wn;
   GemmStream<true, false, false, false, true> stream(H, kDK, H, kDK, H);
   auto source = [&](int tv, int tt) {
-    return TileSrc{W, Hc, (int64_t(V) * H) * 2, (T_pad * H) * 2, uint32_t(int64_t(tv) * kTile * H * 2),
+    return TileSrc{W, Hc, (int64_t(V) * H) * 2, (int64_t(n_cand) * H) * 2, uint32_t(int64_t(tv) * kTile * H * 2),
                    uint32_t(int64_t(tt) * kTile * H * 2), (H + kDK - 1) / kDK};
   };
   int pid = blockIdx.x, tv, tt;
@@ -727,7 +735,8 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_fused_dz(
     Acc acc;
     stream.run<kTileStores>(src, next, wp, stored, smem, acc);
     src = next;
-    stored = true;
+    stored = n0 + wn * 64 < n_cand;   // uniform over the wave: nobody reads 64 columns without a candidate
+    if (!stored) continue;
 
     const int lane = opaque(threadIdx.x & 63);
     // dz for this lane's columns, packed to bf16 pairs: pk[nb][mb] = four consecutive rows
@@ -795,7 +804,8 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_gemm_dh(
     const int k_len = max(0, min(vK, (split + 1) * per * kDK) - k_begin);
     TileSrc t;
     t.a_base = dz + int64_t(k_begin / kDK) * T_pad * kDK;
-    t.a_bytes = int64_t(k_len / kDK) * T_pad * kDK * 2;
+    // a wave requests 32 of the tile's rows: nothing where there is no candidate among them
+    t.a_bytes = tt * kTile + stream.wave * 32 < n_cand ? int64_t(k_len / kDK) * T_pad * kDK * 2 : 0;
     t.a = uint32_t(tt * kTile * kDK * 2);
     // weight rows past the vocabulary (the split may start there) lie past the operand's bytes and read as zeros
     t.b_base = W + int64_t(min(k_begin, V)) * H;
@@ -815,7 +825,7 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_gemm_dh(
   int tt, th;
   tile_of_index(npid % base, tiles_t, tiles_h, tt, th);
   const int m0 = tt * kTile, n0 = th * kTile;
-  wp.active = m0 + wm * 128 < n_cand;
+  wp.active = m0 + wm * 128 < n_cand && n0 + wn * 64 < H;
   wp.warm_a = warm_share(th, tiles_h);
   wp.warm_b = warm_share(tt, tiles_t);
   wp.warm_from = tiles_t > 1 ? INT32_MAX : kWarmSlicesAlone;   // see kWarmSlices
@@ -824,7 +834,7 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_gemm_dh(
   stream.start(src, smem);
   stream.run<0>(src, no_tile(src), wp, false, smem, acc);
   end_of_walk();
-  if (!wp.active) return;   // padding rows of the partials are not read
+  if (!wp.active) return;   // padding rows of the partials are not read, columns past H do not exist
   const int lane = threadIdx.x & 63;
   float* const out = dh_part + int64_t(split) * n_pad * H;
 #pragma unroll
@@ -847,12 +857,13 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_gemm_dw(
   // the contraction ends with the slice of the last candidate, not with its tile: the positions behind it are zeros
   // (whole calls at H = 1536, V = 151936: 600 tokens 949 -> 905 us, 1100 tokens 1376 -> 1357, 16384 tokens -0.4 %)
   const int K = (nact[0] + kDK - 1) / kDK * kDK;
-  WavePos wp = wave_pos<false>();
+  WavePos wp = wave_pos<true>();
   const int wm = wp.wm, wn = wp.wn;
   GemmStream<true, true, false, true, false> stream(kDK, int64_t(VC) * kDK, kDK, int64_t(H_pad) * kDK, 0);
   auto source = [&](int tv, int th) {
     const int m0 = tv * kTile;   // the tile's rows lie inside one vocabulary chunk of the transposed dz
-    return TileSrc{dzT + int64_t(m0 / VC) * VC * T_pad, hTc, int64_t(K) * VC * 2, int64_t(K) * H_pad * 2,
+    const bool any = th * kTile + stream.wave * 32 < H;   // of the 32 columns that the wave requests
+    return TileSrc{dzT + int64_t(m0 / VC) * VC * T_pad, hTc, int64_t(K) * VC * 2, any ? int64_t(K) * H_pad * 2 : 0,
                    uint32_t(m0 % VC) * (kDK * 2), uint32_t(th * kTile * kDK * 2), max(K / kDK, 1)};   // no candidates: one slice of nothing
   };
   // accumulate (uniform): the tile is added to what the caller's buffer holds (gradient accumulation over
@@ -869,6 +880,7 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_gemm_dw(
   stream.start(src, smem);
   while (more) {
     const int m0 = tv * kTile, n0 = th * kTile;
+    wp.active = n0 + wn * 64 < H;
     wp.warm_a = warm_share(th, tiles_h);
     wp.warm_b = warm_share(tv, tiles_v);
     wp.warm_from = kWarmSlices;

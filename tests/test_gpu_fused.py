@@ -25,9 +25,10 @@ def gh():
     return gpu_helpers
 
 
-def run_fused(gh, wl, h_bits, w_bits, targets, bwd=None, dweight_dtype=torch.float32, dw_into=None, accumulate=True):
+def run_fused(gh, wl, h_bits, w_bits, targets, bwd=None, dweight_dtype=torch.float32, dw_into=None, accumulate=True,
+              ws_byte=None):
     """dw_into: a dweight buffer to use instead of a fresh one, to accumulate into (AERO_DW_ACCUMULATE) unless
-    accumulate is False."""
+    accumulate is False.  ws_byte: what every byte of the workspace holds before the call."""
     import paper_2602_14338_amd as aero
     from paper_2602_14338_amd import binding
     dev = gh.DEV
@@ -38,6 +39,8 @@ def run_fused(gh, wl, h_bits, w_bits, targets, bwd=None, dweight_dtype=torch.flo
     err = torch.zeros(1, dtype=torch.int32, device=dev)
     ws = torch.empty(aero.aero_workspace_bytes(binding.OP_LMHEAD_FUSED, T=T, V=V, H=H, R=wl.R), dtype=torch.uint8,
                      device=dev)
+    if ws_byte is not None:
+        ws.fill_(ws_byte)
     out = dict(logprob=lp, entropy=ent, lse=lse)
     if bwd is None:
         aero.aero_lmhead_logprob_fused(hd, wd, T, H, V, gh.dev(targets), lp, ent, lse, workspace=ws, err_flag=err)
@@ -156,6 +159,33 @@ def test_fused_workgroups_that_walk_several_tiles(gh, T, H, V):
     wl, h, W = make(T, H, V, sigma_w=2.0 / np.sqrt(H))
     check_bwd(gh, wl, h, W, dict())
     check_bwd(gh, wl, h, W, dict(reject_enable=1, posterior_mode=1), dweight_dtype=torch.bfloat16, grad_scale=8.0)
+
+
+@pytest.mark.parametrize("entropy_coef", [0.0, 0.01])
+@pytest.mark.parametrize("H", [72, 200, 320])
+@pytest.mark.parametrize("candidates", [1, 32, 33, 64, 65, 129, 257, 320])
+def test_fused_nothing_unwritten_is_read(gh, candidates, H, entropy_coef):
+    """A workspace of NaNs: what the gradient operands do not hold (64 token columns without a candidate are not written,
+    32 rows without one not requested, nor 32 columns past H) reaches no output, on either side of those edges."""
+    T, V = 330, 700
+    wl, h, W = make(T, H, V, sigma_w=2.0 / np.sqrt(H))
+    rng = np.random.default_rng(candidates * 1000 + H)
+    wl.R, wl.token_rollout = T, np.arange(T, dtype=np.int32)
+    targets = wl.targets.copy()
+    targets[rng.permutation(T)[:5]] = -1
+    with_target = np.flatnonzero(targets >= 0)
+    adv, weight = rng.normal(size=T).astype(np.float32), np.zeros(T, np.float32)
+    weight[rng.permutation(with_target)[:candidates]] = 1.0 / T
+    old = ai.draw_old_logprob(orc.lmhead_fused(h, W, targets)["logprob"], wl.seed, sigma=0.3)
+    ref = orc.lmhead_fused(h, W, targets, old, wl.token_rollout, adv, weight, np.float32(0.2), np.float32(0.2), 1.0,
+                           entropy_coef=entropy_coef)
+    out = run_fused(gh, wl, h, W, targets, bwd=dict(old=old, adv=adv, weight=weight, entropy_coef=entropy_coef), ws_byte=255)
+    gh.assert_loss(out["loss"].item(), ref["loss"], ref["loss_terms"])
+    for k in ("logprob", "entropy", "lse"):
+        assert np.abs(out[k].cpu().numpy().astype(np.float64) - ref[k]).max() <= 2e-3, k
+    for k in ("dhidden", "dweight"):
+        got = out[k].double().cpu().numpy()
+        assert np.isfinite(got).all() and rowwise_close(got, ref[k]), k
 
 
 @pytest.mark.parametrize("accumulate", [False, True])
