@@ -53,11 +53,19 @@ struct WavePos {
   int warm_a, warm_b;     // this tile's share of the L2 warm-up: bit q is quarter q of the operand's slice
   int warm_from;          // it is done for tiles of at least this many slices
 };
-// From how many slices on.  With several token tiles: worth 2-4 % per contraction from about 50 slices on, nothing or a
-// small loss at 24, and a loss on the split-K dhidden contraction (the touches are traffic into the CU like any other).  With
-// one token tile every slice of the weight comes from memory for the first time: forward of 200 tokens at H = 1536,
-// V = 151936 162 -> 145 us, dhidden of 250 at H = 3584 297 -> 267 us.
-constexpr int kWarmSlices = 32, kWarmSlicesAlone = 8;
+// From how many slices on.
+//   dweight     from 32: worth 2-4 % from about 50 slices on, from 8 on it cost 0-1.5 % up to 6000 tokens.
+//   forward     from 12, with one token tile from 8: the weight comes from memory once per band of tiles, and a workgroup that walks its
+//               tiles waits for a late line itself.  Without / with it, the kernel at H = 1536, V = 151936: 400 tokens 266 / 246 us, 900
+//               423 / 400, 1500 (gradient) 635 / 594, 2500 942 / 914, 4000 (gradient) 1586 / 1523, 16384 (gradient) 6.30 / 6.22 ms; 2000 tokens
+//               at H = 768, V = 100000 375 / 354, at 9 slices (H = 520) 300 tokens 84 / 90.  Three token tiles cannot share a slice's quarters
+//               out evenly and stay with 32: 600 tokens 326 / 331, 700 320 / 326 (also with shares of 1, 1 and 2 quarters or 2, 2 and none).
+//   dhidden     from 8 with one token tile (250 tokens at H = 3584 297 / 267 us); with more of them a loss: the touches are traffic into
+//               the CU like any other (16384 tokens at H = 1536 3.90 / 4.00 ms with the weight's alone, 1500 451 / 474 us with both).
+constexpr int kWarmSlices = 32, kWarmSlicesForward = 12, kWarmSlicesAlone = 8;
+__device__ __forceinline__ int forward_warm_from(int token_tiles) {
+  return token_tiles == 1 ? kWarmSlicesAlone : token_tiles == 3 ? kWarmSlices : kWarmSlicesForward;
+}
 // A quarter to each of four tiles that have the operand's slice in common, or what fewer of them can share out.
 __device__ __forceinline__ int warm_share(int index, int sharers) {
   return sharers >= 4 ? 1 << (index & 3) : sharers >= 2 ? 5 << (index & 1) : 15;

@@ -409,7 +409,7 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_fused_stats(
     const bool active = !STORE || wp.active;   // the epilogue has something to do (without the stores the branch costs what it saves)
     wp.warm_a = warm_share(tt, tiles_t_act);
     wp.warm_b = warm_share(tv, tiles_v);
-    wp.warm_from = tiles_t_act > 1 ? kWarmSlices : kWarmSlicesAlone;
+    wp.warm_from = forward_warm_from(tiles_t_act);
     const int tv_now = tv;
     pid += gridDim.x;
     more = tile_of_step(pid, tiles_v, tiles_t_act, 0, n_tiles, tv, tt);
@@ -728,7 +728,7 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_fused_dz(
     wp.active = n0 + wn * 64 < n_cand;
     wp.warm_a = warm_share(tt, tiles_t_act);
     wp.warm_b = warm_share(tv, tiles_v);
-    wp.warm_from = tiles_t_act > 1 ? kWarmSlices : kWarmSlicesAlone;
+    wp.warm_from = forward_warm_from(tiles_t_act);
     pid += gridDim.x;
     more = tile_of_step(pid, tiles_v, tiles_t_act, 0, n_tiles, tv, tt);
     const TileSrc next = more ? source(tv, tt) : no_tile(src);
