@@ -812,6 +812,25 @@ def test_loss_strict_tolerance_posterior_mode(gh, cfg, kw):
         assert (ref["g"] != 0).any() and ref["loss"] > 0
 
 
+# up to 4096 tokens of the shortest rows and 16384 of longer ones the loss takes the first workgroup of the gradient launch
+@pytest.mark.parametrize("T,V", [(1, 8), (63, 8), (4096, 8), (4097, 8), (16384, 1040), (16385, 1040), (700, 17000), (65, 40001)])
+def test_loss_beside_the_gradient_rows(gh, T, V):
+    """The loss and the clip fraction of a call that writes gradient rows are those of one that does not: the same terms in
+    64-bit sums of another order, so they differ by one rounding to 32 bits at most."""
+    rng = np.random.default_rng(T + V)
+    z = gh.logits_to_dev((rng.normal(size=(T, V)) * 2).astype(np.float32), torch.float32)
+    y = rng.integers(0, V, size=T).astype(np.int32)
+    lp, _, lse = gh.run_fwd(z, T, V, V, y)[:3]
+    R = min(T, 50)
+    args = (z, T, V, V, y, lse, lp.cpu().numpy() + rng.normal(size=T) * 0.3, (np.arange(T) % R).astype(np.int32),
+            rng.normal(size=R) + 0.5, np.full(R, 1.0 / T))
+    alone, beside = gh.run_loss_bwd(*args, want_dlogits=False), gh.run_loss_bwd(*args)
+    a, b = alone["loss"].item(), beside["loss"].item()
+    assert a != 7.0 and abs(a - b) <= 2.0 ** -23 * abs(a)
+    assert alone["clip_frac"].item() == beside["clip_frac"].item()
+    assert torch.isfinite(beside["dlogits"]).all() and not (beside["dlogits"] == 7.0).any()
+
+
 def test_loss_is_run_to_run_identical_and_loss_only_mode(gh):
     wl = ai.make_config("cfg3", V=8000, T=3000, Q=64, len_lo=1, len_hi=40)
     host = wl.logits_rows(0, wl.T)
