@@ -321,8 +321,8 @@ __device__ __forceinline__ TileSrc no_tile(const TileSrc& t) { return TileSrc{t.
 // and a tile's last slice the next tile's first, so that a tile's epilogue runs while its successor's operands are on
 // their way.  A workgroup per tile lost between 3 and 8 us a tile to the launch, the first slice's latency and
 // the drain of the stores, of 45 us at 24 slices and 17 at 7.  Tile by tile / walking: k_fused_stats<true> with 16384 tokens at
-// H = 1536, V = 151936 6.72 / 6.44 ms, at H = 3584 13.88 / 13.77, 1200 tokens 614 / 595 us; k_gemm_dw 600 tokens 229 / 215 us, with
-// 16384 tokens (160 slices) 1-2 % slower.  Tried on top and not taken: starts staggered over the CUs (0 to +20 %: tiles
+// H = 1536, V = 151936 6.72 / 6.44 ms, at H = 3584 13.88 / 13.77, 1200 tokens 614 / 595 us; k_gemm_dw 600 tokens 229 / 215 us; from
+// about 100 slices on a workgroup per tile is the faster way there (kDwTileRows), by launching one.  Tried on top and not taken: starts staggered over the CUs (0 to +20 %: tiles
 // do not wait for each other's stores), waves 4 to 7 free of loads and warming L2 four slices ahead (dweight of 1000
 // tokens -8 %, everything long +3 to +12 %: bytes into the CU are what counts).
 // WARM: L2 warm-up two slices ahead (see kWarmSlices).

@@ -27,7 +27,7 @@
 //           k_scatter_dh     fp32 partials summed in fixed order, times scale -> bf16 dhidden at the original rows
 // All contractions use the same 256 x 256 x 64 MFMA tile, both operands K-contiguous but for the weight in k_gemm_dh,
 // whose rows are the contraction index and which a transposing LDS read turns.  In all but k_gemm_dh (whose split count
-// fills the CUs once or twice) a workgroup per CU walks the tiles.
+// fills the CUs once or twice) and the longer k_gemm_dw (kDwTileRows) a workgroup per CU walks the tiles.
 #include <mutex>
 
 #include "gemm_tile.h"
@@ -848,6 +848,14 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_gemm_dh(
   }
 }
 
+// Calls of at least so many rows get a workgroup per tile, smaller ones a workgroup per CU that walks the tiles: walking pays for
+// a tile's start and drain, which counts where the contraction is short, and loses 0.5-3 % of a call where it is long.
+// Walking / per tile, whole calls: every row a candidate, H = 1536, V = 151936: 64 slices 4881 / 4895 us (bf16), 128 9854 / 9838, 160
+// 12799 / 12703, 250 20215 / 19900 (added to dweight 20523 / 20054), 330 27545 / 27152; H = 2048 128 slices 10696 / 10587; H = 3584
+// 96 slices 16593 / 16610, 375 68040 / 66109.  62 % of the rows: 8192 rows 7403 / 7408, 10240 9600 / 9573, 16384 14568 / 14541.  The
+// host knows the rows, not how many are candidates.
+constexpr int64_t kDwTileRows = 8192;
+
 // dW[m][h] = sum_t XT[m][t] hTc[h][t], hTc = the candidates' hidden rows times their scale     M = V, N = H, K = candidate tokens (padded)
 template <bool OUT_BF16, bool ACC>
 __global__ __launch_bounds__(kGemmNT, 2) void k_gemm_dw(
@@ -1041,7 +1049,7 @@ extern "C" aero_status aero_lmhead_logprob_fused(
   const int tiles_t = int(p.T_pad / kTile);
   const int tiles_h = (H + kTile - 1) / kTile;
   const int grid_dh = dh_grid(p.T_pad, H, p.V_ld);
-  // contractions: one workgroup per CU walks the tiles; a multiple of 8 keeps a walk on its XCD
+  // contractions: one workgroup per CU walks the tiles (dweight: see kDwTileRows); a multiple of 8 keeps a walk on its XCD
   const int cus = compute_units() / 8 * 8 > 0 ? compute_units() / 8 * 8 : 8;
   auto walkers = [&](int n) { return dim3(unsigned(n < cus ? n : cus)); };
   const int64_t rows_max = p.T_pad > p.H_pad ? p.T_pad : int64_t(p.H_pad);
@@ -1146,7 +1154,8 @@ extern "C" aero_status aero_lmhead_logprob_fused(
                                                    : (accumulate ? k_gemm_dw<false, true> : k_gemm_dw<false, false>);
     for (int t0 = 0; t0 < total; t0 += per) {
       const int n = total - t0 < per ? total - t0 : per;
-      hipLaunchKernelGGL(kernel, walkers(xcd_grid(n)), dim3(kGemmNT), kGemmLdsBytes, s, dzT, hTc, p.VC, p.H_pad, V, H, t0, n,
+      const dim3 grid = p.T_pad < kDwTileRows ? walkers(xcd_grid(n)) : dim3(unsigned(xcd_grid(n)));
+      hipLaunchKernelGGL(kernel, grid, dim3(kGemmNT), kGemmLdsBytes, s, dzT, hTc, p.VC, p.H_pad, V, H, t0, n,
                          p.tiles_v, tiles_h, p.T_pad, nact, vec_dw, dweight);
     }
   }

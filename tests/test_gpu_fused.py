@@ -223,6 +223,37 @@ def test_fused_dweight_off_the_16_byte_grid(gh, dtype, H, accumulate):
     assert (np.abs(got - start - want) <= 1e-2 * np.abs(want).max(axis=1, keepdims=True) + rounding + 1e-6).all()
 
 
+@pytest.mark.parametrize("rows", [600, 8192])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_fused_dweight_forms_beyond_a_tile_per_cu(gh, dtype, rows):
+    """More dweight tiles than CUs, full and ragged ones, on both sides of the row count (8192) from which every tile has a
+    workgroup of its own: the same candidates give the same bits however many rows without a target surround them, whether the
+    buffer is aligned or not, and added to what it holds exactly that sum, rounded once."""
+    T, H, V = 600, 200, 70013
+    wl, h, W = make(T, H, V, sigma_w=2.0 / np.sqrt(H))
+    ga = orc.group_advantage(wl.rewards, wl.lengths, wl.group_offsets, wl.keep_priority, AdvParams())
+    bwd = dict(old=np.full(T, -11.0, np.float32), adv=ga["adv"].astype(np.float32), weight=ga["weight"].astype(np.float32),
+               grad_scale=4096.0)
+    want = orc.lmhead_fused(h, W, wl.targets, bwd["old"], wl.token_rollout, bwd["adv"], bwd["weight"], np.float32(0.2),
+                            np.float32(0.2), 4096.0)["dweight"]
+    plain = run_fused(gh, wl, h, W, wl.targets, bwd=bwd)["dweight"]   # fp32
+    assert rowwise_close(plain.double().cpu().numpy(), want) and np.abs(want).max() > 0.02
+
+    more = rows - T
+    wl.T, wl.token_rollout = rows, np.concatenate([wl.token_rollout, np.full(more, -1, np.int32)])
+    h = np.concatenate([h, h[np.arange(more) % T]])
+    targets = np.concatenate([wl.targets, np.full(more, -1, wl.targets.dtype)])
+    bwd["old"] = np.full(rows, -11.0, np.float32)
+    for front, accumulate in ((8, False), (9, False), (8, True), (9, True)):
+        flat = torch.full((V * H + 16,), 7.0, dtype=dtype, device=gh.DEV)
+        inside = flat[front:front + V * H]
+        inside.fill_(0.25)
+        assert (inside.data_ptr() % 16 == 0) == (front == 8)
+        run_fused(gh, wl, h, W, targets, bwd=bwd, dw_into=inside.view(V, H), accumulate=accumulate)
+        assert torch.equal(inside.view(V, H), (plain + 0.25 if accumulate else plain).to(dtype)), (front, accumulate)
+        assert (flat[:front] == 7.0).all() and (flat[front + V * H:] == 7.0).all()
+
+
 @pytest.mark.parametrize("seed", range(10))
 def test_fused_random_shapes(gh, seed):
     """Seeded random token counts, hidden sizes (multiples of 8, with and without whole 64-wide K slices)
