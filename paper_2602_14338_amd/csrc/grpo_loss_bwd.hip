@@ -130,9 +130,12 @@ __global__ __launch_bounds__(kReduceNT) void k_loss_reduce(const float* __restri
 }
 
 // What the loss is formed from.  Where rows follow (k_dlogits, k_dlogits_seg), it takes the first workgroup of their launch instead of
-// a launch of its own, up to so many tokens that it ends before the rows do: 64 rounds of loads, or 512 behind long rows.
+// a launch of its own, up to so many tokens that it ends before rows that move do: 64 rounds of loads, or 512 behind long rows.
 // Forward and loss call together, with the launch / this way: 1000 rows of 2000 bf16 logits 17.4 / 14.4 us, of 8000 21.4 / 18.8, of 152064
 // 147.9 / 145.3; 4000 of 152064 528.0 / 524.8, 8192 of 32000 249.6 / 248.9.
+// The first workgroup is set aside whether the sum is in it or not (then of no terms, for nobody): a workgroup knows its row without
+// waiting for an argument that says so.  That wait, before the load of the other arguments, cost batches of rows that
+// are left alone 3-7 %.
 struct LossSum {
   const float* term;
   const int32_t* flag;
@@ -142,11 +145,17 @@ struct LossSum {
 static void launch_loss_reduce(const LossSum& l, hipStream_t s) {
   hipLaunchKernelGGL(k_loss_reduce, dim3(1), dim3(kReduceNT), 0, s, l.term, l.flag, l.T, l.loss, l.clip_frac);
 }
-// 1: the rows' launch begins with the loss; 0: it has been launched by itself.
-static int loss_first(const LossSum& l, int64_t up_to, hipStream_t s) {
-  if (l.T <= up_to) return 1;
+// What the rows' launch begins with: the loss, or nothing if it has been launched by itself.
+static LossSum loss_in_rows(const LossSum& l, int64_t up_to, hipStream_t s) {
+  if (l.T <= up_to) return l;
   launch_loss_reduce(l, s);
-  return 0;
+  return LossSum{};
+}
+// True in the first workgroup, which has no row.
+template <int NT> __device__ __forceinline__ bool loss_workgroup(const LossSum& l) {
+  if (blockIdx.x != 0) return false;
+  loss_reduce<NT>(l.term, l.flag, l.T, l.loss, l.clip_frac);
+  return true;
 }
 
 // ---------------------------------------------------------------- dlogits
@@ -175,14 +184,11 @@ __device__ __forceinline__ u32x4_t dlogits_vec(const u32x4_t& v, int k, int y, f
 // ENT: the row also carries the entropy-bonus term, dz_j = pi_j (a z_j + b) + g 1[j = y].
 template <int NT, int DT, bool VEC, bool ENT>
 __global__ __launch_bounds__(NT) void k_dlogits(
-    const void* logits, int64_t T, int V, int64_t ld, const int32_t* __restrict__ targets,
+    const void* logits, int V, int64_t ld, const int32_t* __restrict__ targets,
     const float* __restrict__ lse, const float* __restrict__ g_arr, const float* __restrict__ ea,
-    const float* __restrict__ eb, void* dlogits, LossSum sum, int first) {
-  if (int(blockIdx.x) < first) {
-    loss_reduce<NT>(sum.term, sum.flag, sum.T, sum.loss, sum.clip_frac);
-    return;
-  }
-  const int64_t t = blockIdx.x - unsigned(first);
+    const float* __restrict__ eb, void* dlogits, LossSum sum) {
+  if (loss_workgroup<NT>(sum)) return;
+  const int64_t t = blockIdx.x - 1u;
   const float g = g_arr[t];
   float a = 0.f;
   if constexpr (ENT) a = ea[t];
@@ -249,12 +255,9 @@ template <int DT, bool ENT>
 __global__ __launch_bounds__(kSegNT) void k_dlogits_seg(
     const void* logits, int V, int64_t ld, int segs, const int32_t* __restrict__ targets,
     const float* __restrict__ lse, const float* __restrict__ g_arr, const float* __restrict__ ea,
-    const float* __restrict__ eb, void* dlogits, LossSum sum, int first) {
-  if (int(blockIdx.x) < first) {
-    loss_reduce<kSegNT>(sum.term, sum.flag, sum.T, sum.loss, sum.clip_frac);
-    return;
-  }
-  const unsigned block = blockIdx.x - unsigned(first);
+    const float* __restrict__ eb, void* dlogits, LossSum sum) {
+  if (loss_workgroup<kSegNT>(sum)) return;
+  const unsigned block = blockIdx.x - 1u;
   const int64_t t = block / segs;
   const int seg = block % segs;
   const float g = g_arr[t];
@@ -291,9 +294,16 @@ __global__ __launch_bounds__(kSegNT) void k_dlogits_seg(
 template <int NT, int DT, bool VEC, bool ENT>
 static void launch_dlogits(const void* logits, int64_t T, int V, int64_t ld, const int32_t* targets, const float* lse,
                            const float* g, const float* ea, const float* eb, void* dlogits, const LossSum& sum, hipStream_t s) {
-  const int first = loss_first(sum, 64 * NT, s);
-  hipLaunchKernelGGL((k_dlogits<NT, DT, VEC, ENT>), dim3(unsigned(T + first)), dim3(NT), 0, s, logits, T, V, ld, targets,
-                     lse, g, ea, eb, dlogits, sum, first);
+  const LossSum in_rows = loss_in_rows(sum, 64 * NT, s);
+  auto launch = [&](int64_t from, int64_t rows, const LossSum& l) {
+    const int64_t at = from * ld * Storage<DT>::kBytes;
+    hipLaunchKernelGGL((k_dlogits<NT, DT, VEC, ENT>), dim3(unsigned(rows + 1)), dim3(NT), 0, s, reinterpret_cast<const char*>(logits) + at, V,
+                       ld, targets + from, lse + from, g + from, ENT ? ea + from : nullptr, ENT ? eb + from : nullptr,
+                       reinterpret_cast<char*>(dlogits) + at, l);
+  };
+  if (grid_fits(T + 1, NT)) return launch(0, T, in_rows);
+  launch(0, T - 1, in_rows);   // as many rows as a launch holds: the first workgroup takes the place of the last row's
+  launch(T - 1, 1, LossSum{});
 }
 
 template <int DT, bool VEC, bool ENT>
@@ -305,9 +315,8 @@ static void dispatch_dlogits(const void* logits, int64_t T, int V, int64_t ld, c
   if constexpr (VEC) {
     const int64_t segs = (V / per_vec + kSegNT - 1) / kSegNT;
     if (work > 16 * 256 && grid_fits(T * segs + 1, kSegNT)) {
-      const int first = loss_first(sum, 512 * kSegNT, s);
-      hipLaunchKernelGGL((k_dlogits_seg<DT, ENT>), dim3(unsigned(T * segs + first)), dim3(kSegNT), 0, s, logits, V, ld,
-                         int(segs), targets, lse, g, ea, eb, dlogits, sum, first);
+      hipLaunchKernelGGL((k_dlogits_seg<DT, ENT>), dim3(unsigned(T * segs + 1)), dim3(kSegNT), 0, s, logits, V, ld,
+                         int(segs), targets, lse, g, ea, eb, dlogits, loss_in_rows(sum, 512 * kSegNT, s));
       return;
     }
   }
