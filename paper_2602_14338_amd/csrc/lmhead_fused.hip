@@ -319,7 +319,7 @@ __device__ __forceinline__ void store_tile_both_layouts(const uint32_t (&pk)[kNB
 // ------------------------------------------------------------------------------------------
 // forward: per-tile softmax partials
 // ------------------------------------------------------------------------------------------
-// grid: xcd_grid(tiles_v * T_pad / 256) workgroups, at most one per CU.  Hf holds the compacted rows ([T_pad][H], zero
+// grid: xcd_grid(tiles_v * T_pad / 256) workgroups, at most one per CU unless tiles are long (kForwardTileSlices).  Hf holds the compacted rows ([T_pad][H], zero
 // past the count); part_* are [tiles_v][T_pad], indexed by compact row.
 //
 // STORE (a backward pass follows and its rows have the plain form dz = g (onehot - pi)): the token tiles that
@@ -339,6 +339,13 @@ __device__ __forceinline__ void store_tile_both_layouts(const uint32_t (&pk)[kNB
 // contraction does not request 32 rows without one.  Whole calls at H = 1536, V = 151936: 100 tokens 462 -> 428 us, 300 602 -> 572,
 // 600 776 -> 761; forward only 300 tokens 235 -> 215; 1100 tokens at H = 896, V = 50257 348 -> 333.
 constexpr float kStoreRange = 40.f;
+
+// From so many K slices on the forward contraction and the recomputation have a workgroup per tile, as the long dweight has.
+// Forward-only calls, walking / per tile: H = 3584 4000 tokens 3274 / 3306 us, 600 711 / 704, 16384 (V = 152064) 13.50 / 13.26 ms; H = 4096 700
+// tokens 675 / 681, 4096 3170 / 3200, 16384 6294 / 6327; H = 4352 300 tokens 436 / 439, 600 894 / 808, 1400 1299 / 1244, 8000 6595 / 6432; H = 5120
+// 600 tokens 1106 / 958, 1400 1731 / 1707, 8000 9615 / 9108; H = 7168 1000 tokens 1748 / 1495; H = 8192 300 tokens 745 / 748, 3000 4715 / 4729,
+// 16000 6618 / 6255.
+constexpr int kForwardTileSlices = 65;
 
 // stat_update for 16 values that also hands back the exponentials it formed (relative to st.m on return)
 // and the largest of the 16 values.
@@ -1052,6 +1059,7 @@ extern "C" aero_status aero_lmhead_logprob_fused(
   // contractions: one workgroup per CU walks the tiles (dweight: see kDwTileRows); a multiple of 8 keeps a walk on its XCD
   const int cus = compute_units() / 8 * 8 > 0 ? compute_units() / 8 * 8 : 8;
   auto walkers = [&](int n) { return dim3(unsigned(n < cus ? n : cus)); };
+  auto forward_grid = [&](int n) { return (H + kDK - 1) / kDK < kForwardTileSlices ? walkers(xcd_grid(n)) : dim3(unsigned(xcd_grid(n))); };
   const int64_t rows_max = p.T_pad > p.H_pad ? p.T_pad : int64_t(p.H_pad);
 
   // raising the dynamic-LDS limit is per function; done once per process, safely from any thread
@@ -1100,10 +1108,10 @@ extern "C" aero_status aero_lmhead_logprob_fused(
     {
       const int n = p.tiles_v * tiles_t;
       if (stored)
-        hipLaunchKernelGGL(k_fused_stats<true>, walkers(xcd_grid(n)), dim3(kGemmNT), kGemmLdsBytes, s, Wp, hf,
+        hipLaunchKernelGGL(k_fused_stats<true>, forward_grid(n), dim3(kGemmNT), kGemmLdsBytes, s, Wp, hf,
                            V, H, p.tiles_v, p.T_pad, nf, part_m, part_s, part_sz, zy, p.VC, nact, dz, dzT);
       else
-        hipLaunchKernelGGL(k_fused_stats<false>, walkers(xcd_grid(n)), dim3(kGemmNT), kGemmLdsBytes, s, Wp, hf,
+        hipLaunchKernelGGL(k_fused_stats<false>, forward_grid(n), dim3(kGemmNT), kGemmLdsBytes, s, Wp, hf,
                            V, H, p.tiles_v, p.T_pad, nf, part_m, part_s, part_sz, zy, p.VC, nact, dz, dzT);
     }
     if (p.T_pad <= kFewRows)
@@ -1128,11 +1136,11 @@ extern "C" aero_status aero_lmhead_logprob_fused(
   if (T > 0) {   // recompute mode only (the kernel leaves at once otherwise)
     const int n = p.tiles_v * tiles_t;
     if (ent)
-      hipLaunchKernelGGL(k_fused_dz<true>, walkers(xcd_grid(n)), dim3(kGemmNT), kGemmLdsBytes, s, Wp, hf, V,
+      hipLaunchKernelGGL(k_fused_dz<true>, forward_grid(n), dim3(kGemmNT), kGemmLdsBytes, s, Wp, hf, V,
                          H, p.tiles_v, p.T_pad, p.VC, terms.force_recompute, nact, terms.gc, terms.lsec, terms.yc, terms.ac,
                          terms.bc, dz, dzT);
     else
-      hipLaunchKernelGGL(k_fused_dz<false>, walkers(xcd_grid(n)), dim3(kGemmNT), kGemmLdsBytes, s, Wp, hf, V,
+      hipLaunchKernelGGL(k_fused_dz<false>, forward_grid(n), dim3(kGemmNT), kGemmLdsBytes, s, Wp, hf, V,
                          H, p.tiles_v, p.T_pad, p.VC, terms.force_recompute, nact, terms.gc, terms.lsec, terms.yc, terms.ac,
                          terms.bc, dz, dzT);
   }

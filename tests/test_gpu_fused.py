@@ -298,6 +298,27 @@ def test_fused_backward_wide_logits(gh, z_std):
               kl_coef=0.04)
 
 
+@pytest.mark.parametrize("H", [64, 4096, 4104])
+def test_fused_recompute_beyond_a_tile_per_cu(gh, H):
+    """Forward tiles that raise the range flag, and the recomputation behind it, with more of them than CUs: workgroups that
+    walk (up to 64 K slices) and a workgroup per tile (65).  The same with an entropy term."""
+    T, V = 270, 33100
+    wl, h, W = make(T, H, V, sigma_w=25.0 / np.sqrt(H))
+    assert 2 * -(-V // 256) > 256
+    ga = orc.group_advantage(wl.rewards, wl.lengths, wl.group_offsets, wl.keep_priority, AdvParams())
+    cand = np.flatnonzero(ga["adv"][wl.token_rollout] != 0)
+    z = orc.lmhead_logits(h[cand], W)
+    assert (z.max(axis=1) - z[np.arange(cand.size), wl.targets[cand]]).max() > 40.0
+    # Advantages of one sign, so that the loss terms do not cancel: a logit of up to 100 is rounded to 2^-18, 4e-6, at every one of H
+    # additions in 32 bits, so terms carry some 1e-5 of themselves, a tenth of the loss's bound (with cancelling advantages,
+    # sum |term| = 23 |loss|, the loss was seen 2.3e-4 off at H = 5064).
+    check_bwd(gh, wl, h, W, dict(), adv_map=np.abs, strict_loss=True)
+    # logits a few nats wide: where one token has nearly all of the probability, the entropy term's gradient is what is left of
+    # ln pi + H after cancellation
+    W = make(T, H, V, sigma_w=2.0 / np.sqrt(H))[2]
+    check_bwd(gh, wl, h, W, dict(reject_enable=1, posterior_mode=1), dweight_dtype=torch.bfloat16, entropy_coef=0.01)
+
+
 def test_fused_backward_several_chunks_and_recipe_scale(gh):
     """Vocabulary wider than one backward chunk at this T (2 x 24576 > chunk), paper-scale weights."""
     wl, h, W = make(2816, 128, 40000, Q=8, len_hi=500)
