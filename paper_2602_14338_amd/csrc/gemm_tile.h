@@ -42,6 +42,11 @@ __device__ __forceinline__ int acc_col(int wn, int nb, int lane) { return wn * 6
 __device__ __forceinline__ int acc_row_swapped(int wm, int mb, int lane) { return wm * 128 + mb * 16 + (lane & 15); }
 __device__ __forceinline__ int acc_col_swapped(int wn, int nb, int lane) { return wn * 64 + nb * 16 + 4 * (lane >> 4); }
 
+// Lines of an operand's slice (256) that a tile touches for all that share them: wave `turn` of four takes the first 64.
+struct WarmShare {
+  int first, last, turn;
+};
+
 // Which part of the tile a wave owns.  Waves w and w + 4 run on the same SIMD; the two that share one are the halves
 // of the dimension that may be ragged, so that skipping waves whose rows or columns are all padding halves the work
 // of every SIMD: rows of A (wave_pos<false>) or columns of B, in steps of two blocks of 64 (wave_pos<true>).
@@ -49,30 +54,34 @@ __device__ __forceinline__ int acc_col_swapped(int wn, int nb, int lane) { retur
 // 1400 tokens at H = 3584, V = 32000 826 -> 815; 300 tokens at H = 896, V = 8000 102.2 -> 103.7.
 struct WavePos {
   int wm, wn;
-  bool active;            // false: all of the wave's rows (columns) are padding, its accumulators stay zero
-  int warm_a, warm_b;     // this tile's share of the L2 warm-up: bit q is quarter q of the operand's slice
-  int warm_from;          // it is done for tiles of at least this many slices
+  bool active;                // false: all of the wave's rows (columns) are padding, its accumulators stay zero
+  WarmShare warm_a, warm_b;   // this tile's share of the L2 warm-up
+  int warm_from;              // it is done for tiles of at least this many slices
 };
 // From how many slices on.
 //   dweight     from 32: worth 2-4 % from about 50 slices on, from 8 on it cost 0-1.5 % up to 6000 tokens.
-//   forward     from 12, with one token tile from 8: the weight comes from memory once per band of tiles, and a workgroup that walks its
-//               tiles waits for a late line itself.  Without / with it, the kernel at H = 1536, V = 151936: 400 tokens 266 / 246 us, 900
-//               423 / 400, 1500 (gradient) 635 / 594, 2500 942 / 914, 4000 (gradient) 1586 / 1523, 16384 (gradient) 6.30 / 6.22 ms; 2000 tokens
-//               at H = 768, V = 100000 375 / 354, at 9 slices (H = 520) 300 tokens 84 / 90.  Three token tiles cannot share a slice's quarters
-//               out evenly and stay with 32: 600 tokens 326 / 331, 700 320 / 326 (also with shares of 1, 1 and 2 quarters or 2, 2 and none).
+//   forward     from 16, with one token tile from 8: the weight comes from memory once per band of tiles, and a workgroup that walks its
+//               tiles waits for a late line itself.  Forward-only calls without / with it: 24 slices (H = 1536, V = 151936) 256 tokens 172 / 159
+//               us, 500 251 / 222, 700 319 / 323, 768 329 / 329, 900 418 / 397, 1200 520 / 505, 1700 688 / 682, 2300 891 / 873, 3300 1262 /
+//               1232; 16 slices (same V) 256 tokens 116 / 109, 500 171 / 158, 700 212 / 210, 1024 311 / 292, 1400 392 / 391, 3300 850 / 853;
+//               14 slices (V = 50257) 256 tokens 37.9 / 37.3, 700 82 / 84, 1700 151 / 157; 12 slices (V = 100000) 256 tokens 59.2 / 58.5, 700
+//               117 / 121, 1700 240 / 247, 3300 434 / 443.
 //   dhidden     from 8 with one token tile (250 tokens at H = 3584 297 / 267 us); with more of them a loss: the touches are traffic into
 //               the CU like any other (16384 tokens at H = 1536 3.90 / 4.00 ms with the weight's alone, 1500 451 / 474 us with both).
-constexpr int kWarmSlices = 32, kWarmSlicesForward = 12, kWarmSlicesAlone = 8;
+constexpr int kWarmSlices = 32, kWarmSlicesForward = 16, kWarmSlicesAlone = 8;
 __device__ __forceinline__ int forward_warm_from(int token_tiles) {
-  return token_tiles == 1 ? kWarmSlicesAlone : token_tiles == 3 ? kWarmSlices : kWarmSlicesForward;
+  return token_tiles == 1 ? kWarmSlicesAlone : kWarmSlicesForward;
 }
-// A quarter to each of four tiles that have the operand's slice in common, or what fewer of them can share out.
-__device__ __forceinline__ int warm_share(int index, int sharers) {
-  return sharers >= 4 ? 1 << (index & 3) : sharers >= 2 ? 5 << (index & 1) : 15;
+// The lines in equal parts to the tiles that have the slice in common, a quarter where there are four or more.  (Three tiles with
+// whole quarters, two of them twice: 768 tokens at H = 3584 815 us forward, 724 this way.)
+__device__ __forceinline__ WarmShare warm_share(int index, int sharers) {
+  const int parts = min(max(sharers, 1), 4), part = index % parts;
+  const int lines = (kTile + parts - 1) / parts;
+  return WarmShare{part * lines, min((part + 1) * lines, kTile) - 1, part};
 }
 template <bool RAGGED_COLS> __device__ __forceinline__ WavePos wave_pos() {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  return RAGGED_COLS ? WavePos{wave & 1, wave >> 1, true, 0, 0, 0} : WavePos{wave >> 2, wave & 3, true, 0, 0, 0};
+  return RAGGED_COLS ? WavePos{wave & 1, wave >> 1, true, {}, {}, 0} : WavePos{wave >> 2, wave & 3, true, {}, {}, 0};
 }
 
 typedef f32x4_t Acc[kMB][kNB];
@@ -400,17 +409,20 @@ struct GemmStream {
     // 8 x 4 block of tiles: 12 operand slices for 32 tiles), and loads return in order, so one late
     // line holds back everything queued behind it.  Each slice is therefore touched two slices
     // early with one 4-byte load per 128-byte line (sunk into a scratch corner of LDS), the lines
-    // shared out over the workgroups that will read them (warm_share): wave q takes quarter q of the A rows, wave
-    // 4 + q of the B rows (BT: of each row's columns).  The touch is issued late in the slice, when every wave's
+    // shared out over the workgroups that will read them (warm_share): waves 0 to 3 take the A rows' lines, 4 to 7 those of B (line
+    // l: row l; BT: row l % 64, 128-byte piece l / 64).  The touch is issued late in the slice, when every wave's
     // requests for the next slice are already queued ahead of it, and it may stay in flight across the next barrier
     // (vmcnt(1)).
     constexpr int kWarmAhead = 2;
     const bool warm_a = wave < 4;
-    const bool warm_wave = ((warm_a ? pos.warm_a : pos.warm_b) >> (wave & 3)) & 1;
+    const WarmShare& warm = warm_a ? pos.warm_a : pos.warm_b;
+    const int warm_at = warm.first + ((wave - warm.turn) & 3) * 64;
+    const bool warm_wave = warm_at <= warm.last;
     const __amdgpu_buffer_rsrc_t rw = warm_a ? operand_rsrc(t.a_base, t.a_bytes) : operand_rsrc(t.b_base, t.b_bytes);
-    const uint32_t warm_off = warm_a ? t.a + uint32_t(wave * 64 + lane) * (la.row_step / 8)
-                              : BT   ? t.b + uint32_t(lane) * (lb.k_step / kDK) + uint32_t(wave & 3) * 128
-                                     : t.b + uint32_t((wave & 3) * 64 + lane) * (lb.row_step / 8);
+    const uint32_t line = uint32_t(min(warm_at + lane, warm.last));
+    const uint32_t warm_off = warm_a ? t.a + line * (la.row_step / 8)
+                              : BT   ? t.b + (line & 63) * (lb.k_step / kDK) + (line >> 6) * 128
+                                     : t.b + line * (lb.row_step / 8);
     const uint32_t warm_kstep = warm_a ? la.k_step : lb.k_step;
     uint16_t* const warm_sink = smem + kWarmSinkOff / 2 + wave * 128;
     const uint16_t* const first = smem + stage * kDStageElems;
