@@ -5,15 +5,18 @@
 // so any group size works; counts are integers, the few floating-point statistics are formed
 // in fp64 from those counts and rounded once to fp32.  The call is latency bound, so what counts is
 // launches, dependent loads and exchanges between lanes:
-//   up to 2048 groups and 32768 rollouts (a step)   k_curate: one launch, nothing passed between workgroups
+//   up to 2048 groups and 8192 rollouts (a step)    k_curate: one launch, nothing passed between workgroups; without rejection
+//                                                   up to 32768 rollouts of groups that fit a wave on average
 //   up to 8192 groups                               k_group (c, category, keep mask, advantages, weights), then k_place:
 //                                                   every workgroup adds up the kept counts in front of its groups
 //                                                   itself, so no scan stands between
 //   more                                            k_group, k_scan (exclusive scan of the kept counts, one
 //                                                   workgroup) and k_compact: the counts would be read too often.
-// Whole calls, k_group + k_place / k_curate: 8 groups of 16 (the kernel alone; the call is bound by the host) 5.3 / 3.0 us,
-// 32 groups 11.7 / 6.1, 64 groups (1024 rollouts) 9.0 / 5.7, 256 (5258) 9.2 / 6.0, 400 (7831) 9.2 / 6.2, 600 (12108)
-// 9.1 / 7.7, 1500 (24384) 9.7 / 8.1; beyond 32 loads a thread the rewards in front no longer come in one go.
+// Whole calls, k_group + k_place / k_curate, without rejection and with it where two pairs stand: 8 groups of 8 7.4 / 5.4, 7.2 / 5.3 us;
+// 64 of 64 7.2 / 5.2, 9.5 / 9.7; 256 of 32 7.3 / 5.4, 7.8 / 8.0; 64 of 128 7.4 / 7.1, 18.6 / 19.6; 16 of 500 13.2 / 13.0, 194 / 204.  Over 8192
+// rollouts, where the rewards in front take 32 loads a thread and ranks 16 waves on one CU: 300 of 30 7.3 / 6.7, 7.8 / 9.2; 600 of 20 7.3 /
+// 6.8, 7.5 / 8.6; 1000 of 32 7.3 / 6.8, 8.3 / 9.6; 2048 of 9 7.3 / 7.2, 7.4 / 8.2; wide groups: 500 of 65 8.0 / 9.1, 13.5 / 16.1; 200 of 160 8.5 /
+// 10.0, 30.6 / 34.4; 64 of 512 13.5 / 16.0, 197 / 254; 16 of 2048 41.5 / 43.3; one of 32768 559 / 537.
 // k_place / k_scan + k_compact: 400 groups (7831 rollouts) 9.0 / 11.4, 3000 (60325) 10.2 / 12.9, 4000 (80187) 11.0 / 14.5, 8000
 // (159965) 18.1 / 24.1.  (Counting the bytes of the keep mask instead, up to 8192 rollouts, takes as long, and reads
 // bytes that nobody wrote where offsets start above 0.)
@@ -160,36 +163,43 @@ __device__ __forceinline__ int group_body(
     int nk_l = 0;                    // kept
     double sum_l = 0.0;              // sum of kept rewards
     float mx_l = -INFINITY, mn_l = INFINITY;
-    for (int base = b; base < e; base += kWave) {   // uniform over the wave
-      const int i = base + lane;
-      const bool in = i < e;
-      const float r = i == i0 ? r0 : in ? rewards[i] : 0.f;
-      bool k = in && (mode == kKeepAll || (mode == kKeepCorrect && r == 1.f));
-      if (n <= kWave) {
-        k |= in && mode >= kKeepCorrect && ahead0 < m;
-      } else if (mode >= kKeepCorrect) {
-        // rank among the candidates (incorrect rollouts, or everyone), taken 64 at a time into the lanes
-        const uint64_t own = uint64_t(in && keys ? keys[i] : 0u) << 32 | uint32_t(i);
-        int ahead = 0;
-        for (int from = b; from < e && __any(in && !k && ahead < m); from += kWave) {
-          const int j0 = from + lane;
-          const uint32_t kj = j0 < e && keys ? keys[j0] : 0u;
-          uint64_t cand = __ballot(j0 < e && (mode == kKeepLowest || rewards[j0] != 1.f));
-          while (cand) {
-            const int j = __ffsll((unsigned long long)cand) - 1;
-            cand &= cand - 1;
-            ahead += (uint64_t(uint32_t(__builtin_amdgcn_readlane(int(kj), j))) << 32 | uint32_t(from + j)) < own;
-          }
-        }
-        k |= in && ahead < m;
-      }
-      if (in) keep_mask[i] = k ? 1 : 0;
+    auto take = [&](int i, float r, bool k) {
+      keep_mask[i] = k ? 1 : 0;
       if (i == i0) keep0 = k;
       if (k) {
         ++nk_l;
         sum_l += double(r);
         mx_l = fmaxf(mx_l, r);
         mn_l = fminf(mn_l, r);
+      }
+    };
+    if (mode < kKeepCorrect) {   // no ranks, and no exchange in the loop: loads of several steps go together
+      for (int i = i0; i < e; i += kWave) take(i, i == i0 ? r0 : rewards[i], mode == kKeepAll);
+    } else {
+      for (int base = b; base < e; base += kWave) {   // uniform over the wave
+        const int i = base + lane;
+        const bool in = i < e;
+        const float r = i == i0 ? r0 : in ? rewards[i] : 0.f;
+        bool k = in && mode == kKeepCorrect && r == 1.f;
+        if (n <= kWave) {
+          k |= in && ahead0 < m;
+        } else {
+          // rank among the candidates (incorrect rollouts, or everyone), taken 64 at a time into the lanes
+          const uint64_t own = uint64_t(in && keys ? keys[i] : 0u) << 32 | uint32_t(i);
+          int ahead = 0;
+          for (int from = b; from < e && __any(in && !k && ahead < m); from += kWave) {
+            const int j0 = from + lane;
+            const uint32_t kj = j0 < e && keys ? keys[j0] : 0u;
+            uint64_t cand = __ballot(j0 < e && (mode == kKeepLowest || rewards[j0] != 1.f));
+            while (cand) {
+              const int j = __ffsll((unsigned long long)cand) - 1;
+              cand &= cand - 1;
+              ahead += (uint64_t(uint32_t(__builtin_amdgcn_readlane(int(kj), j))) << 32 | uint32_t(from + j)) < own;
+            }
+          }
+          k |= in && ahead < m;
+        }
+        if (in) take(i, r, k);
       }
     }
     kept0 = __ballot(keep0);
@@ -472,9 +482,10 @@ extern "C" aero_status aero_group_advantage(
   if (Q > 0 && (!group_zero_var || !group_category)) return AERO_ERR_NULL;
   if (R > 0 && (!rewards || !lengths || !adv || !weight || !keep_mask || !kept_index)) return AERO_ERR_NULL;
   hipStream_t s = as_stream(stream);
-  if (Q > 0 && Q <= kCurateQ && R <= kCurateR) {
+  const bool few = R <= 8 * kCurateNT, ranks = p->reject_enable;
+  if (Q > 0 && Q <= kCurateQ && (few || (R <= kCurateR && R <= kWave * Q && !ranks))) {   // see the top
     const int waves = Q < kCurateWaves ? Q : kCurateWaves;
-    const auto kernel = R <= 8 * kCurateNT ? k_curate<8> : k_curate<kCurateR / kCurateNT>;
+    const auto kernel = few ? k_curate<8> : k_curate<kCurateR / kCurateNT>;
     hipLaunchKernelGGL(kernel, dim3(unsigned((Q + waves - 1) / waves)), dim3(unsigned(waves * kWave)), 0, s, rewards, lengths,
                        group_offsets, keep_priority, Q, R, *p, adv, weight, keep_mask, kept_index, kept_offsets, group_zero_var,
                        group_category, err_flag);

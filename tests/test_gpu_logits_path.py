@@ -124,17 +124,19 @@ def test_group_advantage_placement_forms(gh, Q, lo, hi):
 
 
 @pytest.mark.parametrize("Q,R", [(1, 64), (1, 65), (15, 300), (16, 1024), (17, 1025), (33, 8191), (500, 8192), (500, 8193),
-                                 (2047, 32768), (2048, 32768), (2048, 32769), (2049, 20000)])
+                                 (2047, 32768), (2048, 32768), (2048, 32769), (2049, 20000), (1, 8192), (1, 8193), (129, 8256),
+                                 (129, 8257), (512, 32768), (511, 32768)])
 def test_group_advantage_one_launch(gh, Q, R):
-    """One launch up to 2048 groups and 32768 rollouts: around a workgroup's 16 groups, the rollouts that 8 and 32 loads a
-    thread cover, the last call of that form and the first of the other; some groups wider than a wave."""
+    """One launch up to 2048 groups and 8192 rollouts, without rejection up to 32768 of at most 64 a group on average: around a
+    workgroup's 16 groups, the rollouts that 8 and 32 loads a thread cover, the last call of each form and the first of the other;
+    some groups wider than a wave."""
     rng = np.random.default_rng(Q * 100003 + R)
     cuts = np.sort(rng.integers(0, R + 1, size=Q - 1))
     off = np.concatenate([[0], cuts, [R]]).astype(np.int32)      # empty groups and long ones by chance
     rewards = (rng.random(R) < np.repeat(rng.beta(0.5, 0.5, size=Q), np.diff(off))).astype(np.float32)
     lengths = rng.integers(0, 3000, size=R).astype(np.int32)
     keys = rng.integers(0, 50, size=R).astype(np.uint32)
-    for params in (dict(reject_enable=1, posterior_mode=1), dict(reject_enable=1, k_ratio=2)):
+    for params in (dict(reject_enable=1, posterior_mode=1), dict(reject_enable=1, k_ratio=2), dict(), dict(posterior_mode=1)):
         check_groups(gh, (rewards, lengths, off, keys), params)
 
 
