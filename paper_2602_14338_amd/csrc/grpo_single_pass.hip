@@ -537,14 +537,17 @@ inline int row_threads(int nvec) {
 //     more rows                  up to 320 MB, which the 256 MB memory-side cache holds for the second pass, 0.8-1.05;
 //                                beyond fp16 1.00-1.17, fp32 1.06-1.19, 8-bit 0.92-1.13
 //   over 20 vectors per thread   the CU holds 20 and reads the rest again, from the memory-side cache: 4 to 6 bytes per 2-byte
-//                                logit instead of 6.  16-bit 0.78-0.99 up to 32 rows, 1.05-1.31 from 48 to 256; fp32 0.95-1.3 at
-//                                16 rows, 1.05-1.48 from 24 to 256; 8-bit 0.7-1.0 up to 160, 1.09 at 256.  Between 257 rows and
-//                                256 MB, where two passes find the rows in that cache and one starts a second round of
-//                                rows, 0.78-1.03 (padded 0.91-1.28); beyond 256 MB 1.0-1.47 (V = 262144: bf16 4577 rows 992 /
-//                                882 us, fp32 1923 / 1735; fp32 7891 rows of 152064 2206 / 1706)
-// The last line but one is taken for the batches that the call is for, where padding and rollouts without advantage cost the
+//                                logit instead of 6.  With a gradient in every row / right-padded, 9 of 16 rows valid:
+//     up to 256 rows             16-bit up to 64 rows 0.9-1.0 / 0.85-1.0, 96 0.92-1.1 / 0.86-0.95, 128 0.98-1.16 / 0.87-0.97, from
+//                                192 on 1.06-1.33 / 0.97-1.16; fp32 24 rows 0.82-1.16 / 1.0-1.2, from 32 on 0.95-1.3 / 1.0-1.2, but over 64
+//                                vectors per thread 48 to 96 rows 0.96-1.1 / 0.92-1.12; 8-bit 192 0.97-1.1 / 0.82-0.93, 256 1.04-1.16 /
+//                                0.85-0.95
+//     more, up to 256 MB         two passes find the rows in that cache and one starts a second round of rows: 0.78-1.03 / 0.91-1.28
+//     beyond                     1.0-1.4 / 1.0-1.5 (V = 262144: bf16 3072 rows 670 / 534 us, fp32 1536 667 / 560; V = 600000, 8-bit 2688
+//                                rows 798 / 614)
+// For held rows, more than 256 of them take the one pass for the batches that the call is for, where padding and rollouts without advantage cost the
 // one pass least (9 of 16 rows valid, a third of the groups all equal: fp16 1.19-1.42, fp32 1.4-2.0, 8-bit 1.09-1.27;
-// packed: fp16 0.99-1.34, 8-bit 0.87-1.23).  bf16 rows take the one pass throughout: streaming 0.76-1.08 up to 8 rows,
+// packed: fp16 0.99-1.34, 8-bit 0.87-1.23).  Held bf16 rows take it throughout: streaming 0.76-1.08 up to 8 rows,
 // 0.84-1.3 from 64 on, loss only 0.55-0.99.
 bool single_pass_applicable(int32_t dtype, int64_t T, int V, const void* logits, const void* dlogits) {
   const size_t elt = storage_bytes(dtype);
@@ -552,8 +555,9 @@ bool single_pass_applicable(int32_t dtype, int64_t T, int V, const void* logits,
   if (nvec > size_t(kLongVecs) * kSpNT || !rows_alike(logits, dlogits, elt)) return false;
   if (nvec <= size_t(kHeldVecs) * kSpNT && !grid_fits(T, row_threads(int(nvec)))) return false;
   if (nvec > size_t(kStreamVecs) * kSpNT) {
-    const int64_t few = dtype == AERO_F32 ? 24 : dtype == AERO_F8E4M3 ? 192 : 48;
-    return dlogits && T >= few && (T <= 256 || size_t(T) * nvec * 16 >= (size_t(256) << 20));
+    if (!dlogits) return false;
+    if (size_t(T) * nvec * 16 >= (size_t(256) << 20)) return true;
+    return T <= 256 && dtype != AERO_F8E4M3 && T >= (dtype == AERO_F32 && nvec <= 64 * kSpNT ? 32 : 192);
   }
   if (dtype == AERO_BF16) return true;
   if (nvec <= size_t(kHeldVecs) * kSpNT) return dlogits || dtype != AERO_F8E4M3 || nvec <= 4 * kSpNT || T <= 512;

@@ -603,10 +603,12 @@ def test_f8_gradient_rounding_bit_exact(gh):
     # enough rows for one pass over fp16 and 8-bit rows that stream (96 and 192), and too few
     ("f16", 151937, 151939, 7), ("f16", 65549, 65551, 6), ("f16", 65549, 65551, 5), ("f16", 65549, 65549, 17),
     ("f8e4m3", 131103, 131107, 13), ("f8e4m3", 131103, 131107, 11),
-    # rows that a CU does not hold: one vector more than it does, an odd number of rounds more, the longest, too few rows
+    # rows that a CU does not hold: one vector more than it does, an odd number of rounds more, the longest, too few rows (16-bit
+    # under 192, fp32 under 32 and, over 65536 vectors, under 192, 8-bit under 256 MB)
     ("bf16", 163855, 163857, 3), ("bf16", 163848, 163848, 2), ("bf16", 262144, 262144, 4), ("f16", 180001, 180003, 3),
     ("f32", 81931, 81931, 2), ("f32", 152064, 152064, 2), ("f32", 327683, 327683, 2), ("f32", 327684, 327684, 2),
-    ("f8e4m3", 327713, 327715, 12)])
+    ("f8e4m3", 327713, 327715, 12), ("bf16", 163855, 163857, 12), ("f16", 180001, 180003, 12), ("bf16", 163847, 163847, 11),
+    ("f32", 262144, 262147, 2), ("f32", 262148, 262148, 2)])
 def test_single_pass_edges(gh, dtype, V, ld, slots):
     def wl():
         return ai.make_config("cfg2", V=V, ld=ld, slots=slots, len_lo=1, len_hi=slots - 1, dtype=dtype)
@@ -666,6 +668,51 @@ def test_loss_bwd_at_element_offsets(gh, V, off_z, off_d):
     assert ((dz_a - dz_b).abs() <= 2.0 ** -7 * dz_a.abs() + 1e-30).all()
 
 
+@pytest.mark.parametrize("dtype,V,T,terms", [("f8e4m3", 1310720, 206, False), ("f8e4m3", 327713, 820, True),
+                                             ("bf16", 655360, 205, False), ("f16", 655360, 205, True), ("f32", 327680, 205, False)])
+def test_rows_held_in_part_against_two_passes(gh, dtype, V, T, terms):
+    """256 MB of rows that a CU does not hold, among them the longest it takes: the gradient of one pass (dlogits as aligned as the
+    logits) and of two (one element off), up to a step of the stored entry; a quarter of the rows padding or left alone."""
+    store = {"f8e4m3": torch.float8_e4m3fn, "f16": torch.float16, "bf16": torch.bfloat16, "f32": torch.float32}[dtype]
+    assert T * (V * store.itemsize // 16) * 16 >= 2 ** 28
+    R, n = 24, T * V
+    g = torch.Generator(device=gh.DEV)
+    g.manual_seed(V)
+    z = torch.empty(T, V, dtype=store, device=gh.DEV)
+    for a in range(0, T, 32):
+        z[a:a + 32] = (torch.randn(min(32, T - a), V, generator=g, device=gh.DEV) * 3).to(store)
+    rng = np.random.default_rng(V)
+    tg = rng.integers(0, V, size=T).astype(np.int32)
+    tr = np.where(rng.random(T) < 0.25, rng.integers(-2, 0, size=T), rng.integers(0, R, size=T)).astype(np.int32)
+    adv, weight = rng.normal(size=R).astype(np.float32), rng.uniform(0.5, 1.0, size=R).astype(np.float32)
+    lp = gh.run_fwd(z, T, V, V, tg, want_entropy=False)[0].cpu().numpy()
+    old = lp + rng.normal(0, 0.1, size=T).astype(np.float32)
+    scale = {"f16": 4096.0, "f8e4m3": 256.0}.get(dtype, 1.0)
+
+    def run(front):
+        dz = torch.zeros(n + 32, dtype=store, device=gh.DEV)
+        ws = torch.empty(gh.aero.aero_workspace_bytes(gh.binding.OP_GRPO_LOSS_BWD, T=T, V=V, R=R), dtype=torch.uint8, device=gh.DEV)
+        loss = torch.zeros(1, device=gh.DEV)
+        kw = dict(entropy_coef=0.02, kl_coef=0.04, ref_logprob=gh.dev(old + np.float32(0.05))) if terms else {}
+        gh.aero.aero_grpo_loss_bwd(z, T, V, V, gh.dev(tg), None, gh.dev(old), gh.dev(tr), gh.dev(adv), gh.dev(weight), R, 0.2, 0.2,
+                                   scale, loss, None, None, dz[front:front + n].view(T, V), ws, **kw)
+        assert not dz[:front].float().any() and not dz[front + n:].float().any()
+        return loss.item(), dz[front:front + n].view(T, V)
+    (one, d1), (two, d2) = run(0), run(1)
+    assert abs(one - two) <= 1e-6 * weight.sum() * T
+    # Statistics summed in another order, and the log-partition of two passes rounded to 32 bits (2^-20 at 13), move an entry by some
+    # 2e-6 of itself, a stored one by a step of its type on top: 2^-7, 2^-10 and 2^-3 of itself, or the smallest step (bf16: none
+    # to speak of, fp16 2^-24, 8-bit 2^-9).  fp32 goes without the entropy term, whose entries are what cancellation in
+    # ln pi + H leaves: there such a move is not small against the entry.
+    step = {"bf16": (2.0 ** -7, 0.0), "f16": (2.0 ** -10, 2.0 ** -24), "f8e4m3": (2.0 ** -3, 2.0 ** -9), "f32": (2.0 ** -22, 0.0)}[dtype]
+    for a in range(0, T, 16):
+        x, y = d1[a:a + 16].float(), d2[a:a + 16].float()
+        bound = (step[0] + 1e-5) * x.abs() + step[1] + 1e-30
+        assert ((x - y).abs() <= bound).all(), a
+    live = torch.from_numpy(tr >= 0).to(gh.DEV)
+    assert d1[live][:8].float().any(dim=1).any() and not d1[~live].float().any()
+
+
 @pytest.mark.parametrize("seed", range(16))
 def test_random_shapes_all_storage_types(gh, seed):
     """Seeded random vocabulary sizes, row pitches (aligned and not), batch shapes, storage types and call
@@ -723,7 +770,8 @@ def test_streaming_kernel_optional_terms_several_rows_per_workgroup(gh):
 @pytest.mark.parametrize("inplace,terms", [(False, False), (True, True), (True, False), (False, True)])
 @pytest.mark.parametrize("dtype,V,ld,T", [("bf16", 70003, 70005, 624), ("f16", 65549, 65551, 2496), ("f32", 32777, 32779, 2496),
                                           ("f8e4m3", 230001, 230003, 1456),
-                                          ("bf16", 164003, 164005, 832), ("f32", 110001, 110003, 624)])   # held in part
+                                          ("bf16", 164003, 164005, 832), ("f32", 110001, 110003, 624),
+                                          ("f8e4m3", 1300001, 1300003, 416)])   # held in part
 def test_streaming_rows_of_changing_alignment(gh, dtype, V, ld, T, inplace, terms):
     """Several rows per workgroup of the streaming kernel, each at another offset from 16 bytes than the one whose slots
     it takes over, after gradient rows and after rows that are only filled with zeros (padding, advantage 0) or
