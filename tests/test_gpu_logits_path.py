@@ -247,6 +247,108 @@ def test_binding_native_and_general_ways_agree(gh, monkeypatch):
             assert all(torch.equal(x, y) for x, y in zip(got, want)), f
 
 
+class _Int(int):
+    pass
+
+
+@pytest.mark.parametrize("entry", ["group_advantage", "logprob_fwd", "loss_bwd", "loss_bwd noalloc", "loss_bwd given lse", "fused"])
+def test_binding_native_step_of_every_call(gh, monkeypatch, entry):
+    """Plain arguments go through the native step, which answers with a status; what is not plain it leaves alone, with
+    NotImplemented.  Either way the results, or the error, are those of the general way.  Every argument has a value of its own, so that
+    two that change places show."""
+    b, native = gh.aero.binding, entry.split()[0]
+    T, V, H, R, ld = 70, 333, 40, 7, 340
+    rng = np.random.default_rng(5)
+    f = lambda *s, scale=1.0: gh.dev((rng.normal(size=s) * scale).astype(np.float32))   # noqa: E731
+    z = f(T, ld, scale=2.0).bfloat16()
+    hid, w = f(T, H).bfloat16(), f(V, H, scale=0.3).bfloat16()
+    tg = gh.dev(rng.integers(-1, V, size=T).astype(np.int32))
+    own = gh.dev(rng.integers(-2, R, size=T).astype(np.int32))
+    active = gh.dev(rng.integers(0, 2, size=T).astype(np.uint8))
+    old, ref, lse, ent = f(T, scale=0.1) - 5.8, f(T, scale=0.1) - 5.7, f(T, scale=0.1) + 7.0, f(T, scale=0.1) + 4.0
+    adv, wt = f(R) + 0.3, f(R, scale=0.1).abs() + 0.05
+    sizes = np.array([8, 30, 2, 65, 9, 1, 5])
+    off = gh.dev(np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32))
+    n = int(sizes.sum())
+    rew = gh.dev(rng.integers(0, 2, size=n).astype(np.float32))
+    lens, keys = (gh.dev(rng.integers(1, 999, size=n).astype(np.int32)) for _ in range(2))
+    ws = torch.empty(max(gh.aero.aero_workspace_bytes(op, T=T, V=V, H=H, R=R) for op in (b.OP_GRPO_LOSS_BWD, b.OP_LMHEAD_FUSED)),
+                     dtype=torch.uint8, device=gh.DEV)
+    new = lambda *s, dtype=torch.float32: torch.full(s, 7, dtype=dtype, device=gh.DEV)   # noqa: E731
+
+    def call(**kw):
+        g = lambda k, v: kw.get(k, v)   # noqa: E731
+        err = new(1, dtype=torch.int32) * 0
+        lp, en, ls, loss, clip = new(T), new(T), new(T), new(1), new(1)
+        mid = (g("T", T), g("V", V))
+        tail = dict(entropy_coef=g("entropy_coef", 0.03), kl_coef=0.05, ref_logprob=g("ref", ref))
+        rest = (g("old", old), own, adv, wt, g("R", R), 0.15, g("eps_hi", 0.25), 3.0)
+        if entry == "group_advantage":
+            p = gh.aero.AdvParams(k_ratio=g("k_ratio", 2), s_rescue=1, tau_num=2, tau_den=3, zero_keep=3, reject_enable=1,
+                                  posterior_mode=1, alpha0=g("alpha0", 1.5), beta0=0.5)
+            out = [new(n), new(n), new(n, dtype=torch.uint8), new(n, dtype=torch.int32), new(8, dtype=torch.int32),
+                   new(7, dtype=torch.uint8), new(7, dtype=torch.uint8)]
+            b.aero_group_advantage(g("old", rew), lens, off, keys, g("R", 7), n, p, *out, err)
+        elif entry == "logprob_fwd":
+            out = [lp, en, ls]
+            b.aero_logprob_fwd(g("z", z), *mid, ld, g("tg", tg), active, *out, err)
+        elif entry == "fused":
+            out = [lp, en, ls, loss, clip, new(T, H, dtype=torch.bfloat16), new(V, H, dtype=g("dw", torch.float32))]
+            b.aero_lmhead_logprob_fused(g("z", hid), w, mid[0], H, mid[1], g("tg", tg), lp, en, ls, *rest, loss, clip, out[5], out[6],
+                                        ws, err, dweight_accumulate=g("accumulate", False), **tail)
+        else:
+            d = new(T, ld, dtype=g("dw", torch.bfloat16))
+            given = entry == "loss_bwd given lse"
+            out = [loss, clip, lp, d] + ([] if given else [en, ls])
+            head = (g("z", z), *mid, ld, g("tg", tg), lse if given else None, *rest, loss, clip, lp, d)
+            tail.update(dict(entropy=ent) if given else dict(entropy_out=en, lse_out=ls))
+            if entry == "loss_bwd noalloc":
+                b.aero_grpo_loss_bwd_noalloc(*head, err, **tail)
+            else:
+                b.aero_grpo_loss_bwd(*head, ws, err, **tail)
+        return out + [err]
+
+    answers = []
+    step = getattr(b._m, native)
+    general = []
+
+    def watched(*a):
+        answers.append(NotImplemented if general else step(*a))
+        return answers[-1]
+    monkeypatch.setattr(b._m, native, watched)
+
+    def outcome(kw):
+        try:
+            return call(**kw)
+        except Exception as e:   # noqa: BLE001
+            return type(e), str(e)
+
+    plain = [dict(), dict(R=-1)] + {"group_advantage": [dict(k_ratio=1, alpha0=2)], "logprob_fwd": [dict(V=300)],
+                                    "fused": [dict(dw=torch.bfloat16, accumulate=True), dict(dw=torch.float16)]}.get(entry, [dict(eps_hi=1)])
+    if entry == "logprob_fwd":
+        plain[1] = dict(T=-1)
+    other = {"group_advantage": [dict(R=_Int(7)), dict(R=2.0), dict(k_ratio=True), dict(k_ratio=1.5), dict(alpha0="x"), dict(old=rew.cpu()),
+                                 dict(old=rew.double())]}.get(
+        entry, [dict(T=_Int(T)), dict(T=float(T)), dict(V=2 ** 40), dict(tg=tg.long()), dict(tg=tg.cpu()), dict(z=z.double()),
+                dict(z=z.t().contiguous().t())])
+    if entry.startswith("loss"):
+        other += [dict(dw=torch.float32), dict(eps_hi=np.float64(0.25)), dict(eps_hi="x"), dict(ref=ref.double())]
+    if entry == "fused":
+        other += [dict(accumulate=1), dict(dw=torch.float64), dict(z=hid.float())]
+    for kw in plain + other:
+        answers.clear()
+        got = outcome(kw)
+        assert len(answers) == 1 and (type(answers[0]) is int if kw in plain else answers[0] is NotImplemented), (kw, answers)
+        general.append(True)
+        want = outcome(kw)
+        general.clear()
+        if isinstance(want, tuple):
+            assert got == want, kw
+        else:
+            assert isinstance(got, list) and all(torch.equal(x, y) for x, y in zip(got, want)), kw
+            assert not (got[0] == 7).all(), kw
+
+
 # ------------------------------------------------------------------ softmax statistics
 
 def check_fwd(gh, wl, row_active=None, targets=None, offset_elems=0):
