@@ -60,15 +60,16 @@ struct WavePos {
 };
 // From how many slices on.
 //   dweight     from 32: worth 2-4 % from about 50 slices on, from 8 on it cost 0-1.5 % up to 6000 tokens.
-//   forward     from 16, with one token tile from 8: the weight comes from memory once per band of tiles, and a workgroup that walks its
-//               tiles waits for a late line itself.  Forward-only calls without / with it: 24 slices (H = 1536, V = 151936) 256 tokens 172 / 159
-//               us, 500 251 / 222, 700 319 / 323, 768 329 / 329, 900 418 / 397, 1200 520 / 505, 1700 688 / 682, 2300 891 / 873, 3300 1262 /
-//               1232; 16 slices (same V) 256 tokens 116 / 109, 500 171 / 158, 700 212 / 210, 1024 311 / 292, 1400 392 / 391, 3300 850 / 853;
-//               14 slices (V = 50257) 256 tokens 37.9 / 37.3, 700 82 / 84, 1700 151 / 157; 12 slices (V = 100000) 256 tokens 59.2 / 58.5, 700
-//               117 / 121, 1700 240 / 247, 3300 434 / 443.
+//   forward     from 12, with one token tile from 8: the weight comes from memory once per band of tiles, and a workgroup that walks its
+//               tiles waits for a late line itself.  Forward-only calls without / with it, the weight not in the memory-side cache (other
+//               work came between) and, in brackets, left there by the call before: H = 1536, V = 151936 500 tokens 286 / 249 us (251 / 221),
+//               700 340 / 331 (316 / 321), 900 455 / 385 (418 / 391), 1700 695 / 675 (680 / 676), 3300 1288 / 1219 (1255 / 1217); H = 1024 500
+//               tokens 202 / 171 (169 / 156), 700 233 / 234 (206 / 206), 1400 398 / 374 (386 / 384); H = 768 500 tokens 174 / 143 (120 / 121), 700
+//               200 / 192 (156 / 158), 900 265 / 225 (204 / 210), 1700 366 / 359 (347 / 349), 3300 656 / 643 (639 / 640); with a gradient 0.94-1.02
+//               of the time without.
 //   dhidden     from 8 with one token tile (250 tokens at H = 3584 297 / 267 us); with more of them a loss: the touches are traffic into
 //               the CU like any other (16384 tokens at H = 1536 3.90 / 4.00 ms with the weight's alone, 1500 451 / 474 us with both).
-constexpr int kWarmSlices = 32, kWarmSlicesForward = 16, kWarmSlicesAlone = 8;
+constexpr int kWarmSlices = 32, kWarmSlicesForward = 12, kWarmSlicesAlone = 8;
 __device__ __forceinline__ int forward_warm_from(int token_tiles) {
   return token_tiles == 1 ? kWarmSlicesAlone : kWarmSlicesForward;
 }

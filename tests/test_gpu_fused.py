@@ -130,7 +130,7 @@ def check_bwd(gh, wl, h, W, params, sigma_old=0.3, dweight_dtype=torch.float32, 
 
 # (300, 2112, 1000) and (4500, 64, 600) reach 32 K slices in the recompute (H = 2112) and in the dweight contraction (> 2048 tokens
 # with gradient), where the loop warms L2 ahead of its operand requests; then 1024 vocabulary tiles, a hidden size of 8192,
-# and 13 and 17 slices with five and three token tiles: the forward contraction warms L2 from 16 on, the last slice is not whole
+# and 13 and 17 slices with five and three token tiles: the forward contraction warms L2 from 12 on, the last slice is not whole
 @pytest.mark.parametrize("T,H,V", [(256, 64, 256), (300, 64, 1000), (17, 72, 77), (700, 512, 5000),
                                    (512, 1536, 3000), (1100, 256, 4096), (300, 2112, 1000), (4500, 64, 600),
                                    (300, 64, 262144), (130, 8192, 700), (1100, 776, 600), (700, 1032, 600)])
