@@ -133,9 +133,13 @@ __global__ __launch_bounds__(kReduceNT) void k_loss_reduce(const float* __restri
 // a launch of its own, up to so many tokens that it ends before rows that move do: 64 rounds of loads, or 512 behind long rows.
 // Forward and loss call together, with the launch / this way: 1000 rows of 2000 bf16 logits 17.4 / 14.4 us, of 8000 21.4 / 18.8, of 152064
 // 147.9 / 145.3; 4000 of 152064 528.0 / 524.8, 8192 of 32000 249.6 / 248.9.
-// The first workgroup is set aside whether the sum is in it or not (then of no terms, for nobody): a workgroup knows its row without
-// waiting for an argument that says so.  That wait, before the load of the other arguments, cost batches of rows that
-// are left alone 3-7 %.
+// The first eight workgroups are set aside whether the sum is in them or not (then of no terms, for nobody):
+//   - a workgroup knows its row without waiting for an argument that says so.  That wait, before the load of the other
+//     arguments, cost batches of rows that are left alone 3-7 %;
+//   - eight, one on every XCD, because one would move each row's segments to the next XCD.  The last segment of a row is short,
+//     and which XCDs get the short ones matters where the segments of a row are an even number: 6127 fp32 rows of 50257
+//     logits (50 segments), not in the caches, 400 us with a launch for the sum, 437 behind one workgroup, 401 behind eight; 8-bit rows
+//     of 152064 (38) 302 / 320 / 302.
 struct LossSum {
   const float* term;
   const int32_t* flag;
@@ -151,10 +155,13 @@ static LossSum loss_in_rows(const LossSum& l, int64_t up_to, hipStream_t s) {
   launch_loss_reduce(l, s);
   return LossSum{};
 }
-// True in the first workgroup, which has no row.
-template <int NT> __device__ __forceinline__ bool loss_workgroup(const LossSum& l) {
-  if (blockIdx.x != 0) return false;
-  loss_reduce<NT>(l.term, l.flag, l.T, l.loss, l.clip_frac);
+constexpr unsigned kAside = 8;
+// True in a workgroup that is set aside; the first one forms the loss.  One branch, so that the rows' code follows it (a second
+// branch here put it behind the sum's, and 131072 rows that are left alone took 876 us, 833 this way).
+template <int NT> __device__ __forceinline__ bool set_aside(const LossSum& l) {
+  if (__builtin_expect(blockIdx.x >= kAside, 1)) return false;
+  const bool first = blockIdx.x == 0;
+  loss_reduce<NT>(l.term, l.flag, first ? l.T : 0, first ? l.loss : nullptr, first ? l.clip_frac : nullptr);
   return true;
 }
 
@@ -187,8 +194,8 @@ __global__ __launch_bounds__(NT) void k_dlogits(
     const void* logits, int V, int64_t ld, const int32_t* __restrict__ targets,
     const float* __restrict__ lse, const float* __restrict__ g_arr, const float* __restrict__ ea,
     const float* __restrict__ eb, void* dlogits, LossSum sum) {
-  if (loss_workgroup<NT>(sum)) return;
-  const int64_t t = blockIdx.x - 1u;
+  if (set_aside<NT>(sum)) return;
+  const int64_t t = blockIdx.x - kAside;
   const float g = g_arr[t];
   float a = 0.f;
   if constexpr (ENT) a = ea[t];
@@ -256,8 +263,8 @@ __global__ __launch_bounds__(kSegNT) void k_dlogits_seg(
     const void* logits, int V, int64_t ld, int segs, const int32_t* __restrict__ targets,
     const float* __restrict__ lse, const float* __restrict__ g_arr, const float* __restrict__ ea,
     const float* __restrict__ eb, void* dlogits, LossSum sum) {
-  if (loss_workgroup<kSegNT>(sum)) return;
-  const unsigned block = blockIdx.x - 1u;
+  if (set_aside<kSegNT>(sum)) return;
+  const unsigned block = blockIdx.x - kAside;
   const int64_t t = block / segs;
   const int seg = block % segs;
   const float g = g_arr[t];
@@ -297,13 +304,13 @@ static void launch_dlogits(const void* logits, int64_t T, int V, int64_t ld, con
   const LossSum in_rows = loss_in_rows(sum, 64 * NT, s);
   auto launch = [&](int64_t from, int64_t rows, const LossSum& l) {
     const int64_t at = from * ld * Storage<DT>::kBytes;
-    hipLaunchKernelGGL((k_dlogits<NT, DT, VEC, ENT>), dim3(unsigned(rows + 1)), dim3(NT), 0, s, reinterpret_cast<const char*>(logits) + at, V,
+    hipLaunchKernelGGL((k_dlogits<NT, DT, VEC, ENT>), dim3(unsigned(rows + kAside)), dim3(NT), 0, s, reinterpret_cast<const char*>(logits) + at, V,
                        ld, targets + from, lse + from, g + from, ENT ? ea + from : nullptr, ENT ? eb + from : nullptr,
                        reinterpret_cast<char*>(dlogits) + at, l);
   };
-  if (grid_fits(T + 1, NT)) return launch(0, T, in_rows);
-  launch(0, T - 1, in_rows);   // as many rows as a launch holds: the first workgroup takes the place of the last row's
-  launch(T - 1, 1, LossSum{});
+  if (T <= kAside || grid_fits(T + kAside, NT)) return launch(0, T, in_rows);
+  launch(0, T - kAside, in_rows);   // as many rows as a launch holds: the workgroups set aside take the places of the last rows'
+  launch(T - kAside, kAside, LossSum{});
 }
 
 template <int DT, bool VEC, bool ENT>
@@ -314,8 +321,8 @@ static void dispatch_dlogits(const void* logits, int64_t T, int V, int64_t ld, c
   const int64_t work = (V + per_vec - 1) / per_vec;
   if constexpr (VEC) {
     const int64_t segs = (V / per_vec + kSegNT - 1) / kSegNT;
-    if (work > 16 * 256 && grid_fits(T * segs + 1, kSegNT)) {
-      hipLaunchKernelGGL((k_dlogits_seg<DT, ENT>), dim3(unsigned(T * segs + 1)), dim3(kSegNT), 0, s, logits, V, ld,
+    if (work > 16 * 256 && grid_fits(T * segs + kAside, kSegNT)) {
+      hipLaunchKernelGGL((k_dlogits_seg<DT, ENT>), dim3(unsigned(T * segs + kAside)), dim3(kSegNT), 0, s, logits, V, ld,
                          int(segs), targets, lse, g, ea, eb, dlogits, loss_in_rows(sum, 512 * kSegNT, s));
       return;
     }
