@@ -538,10 +538,11 @@ inline int row_threads(int nvec) {
 //                                beyond fp16 1.00-1.17, fp32 1.06-1.19, 8-bit 0.92-1.13
 //   over 20 vectors per thread   the CU holds 20 and reads the rest again, from the memory-side cache: 4 to 6 bytes per 2-byte
 //                                logit instead of 6.  With a gradient in every row / right-padded, 9 of 16 rows valid:
-//     up to 256 rows             16-bit up to 64 rows 0.9-1.0 / 0.85-1.0, 96 0.92-1.1 / 0.86-0.95, 128 0.98-1.16 / 0.87-0.97, from
-//                                192 on 1.06-1.33 / 0.97-1.16; fp32 24 rows 0.82-1.16 / 1.0-1.2, from 32 on 0.95-1.3 / 1.0-1.2, but over 64
-//                                vectors per thread 48 to 96 rows 0.96-1.1 / 0.92-1.12; 8-bit 192 0.97-1.1 / 0.82-0.93, 256 1.04-1.16 /
-//                                0.85-0.95
+//     up to 256 rows             the longer a 16-bit row, the more of them it takes, one per 6 KB: V = 170000 64 rows 0.98 / 0.95, 96 1.06 / 0.94, 128
+//                                1.13 / 0.93, 256 1.14 / 1.04; 262144 64 rows 0.99 / 0.91, 96 1.05 / 0.93, 128 1.11 / 0.93; 400000 64 rows
+//                                0.95 / 0.87, 96 0.99 / 0.89, 128 1.08 / 0.95, 256 1.27 / 1.14; 650000 96 rows 0.93 / 0.86, 128 1.0 / 0.89, 192
+//                                1.18 / 1.02.  fp32 from 24 rows and 10 MB on 0.95-1.25 / 1.0-1.2 (24 of 90000 0.82 / 1.01, of 164000
+//                                1.13 / 1.18; over 64 vectors per thread 96 rows 0.97 / 0.93, 256 1.19 / 1.18).  8-bit 192 rows 0.97-1.1 / 0.82-0.93, 256 1.04-1.16 / 0.85-0.95
 //     more, up to 256 MB         two passes find the rows in that cache and one starts a second round of rows: 0.78-1.03 / 0.91-1.28
 //     beyond                     1.0-1.4 / 1.0-1.5 (V = 262144: bf16 3072 rows 670 / 534 us, fp32 1536 667 / 560; V = 600000, 8-bit 2688
 //                                rows 798 / 614)
@@ -557,7 +558,8 @@ bool single_pass_applicable(int32_t dtype, int64_t T, int V, const void* logits,
   if (nvec > size_t(kStreamVecs) * kSpNT) {
     if (!dlogits) return false;
     if (size_t(T) * nvec * 16 >= (size_t(256) << 20)) return true;
-    return T <= 256 && dtype != AERO_F8E4M3 && T >= (dtype == AERO_F32 && nvec <= 64 * kSpNT ? 32 : 192);
+    if (T > 256 || dtype == AERO_F8E4M3) return false;
+    return dtype == AERO_F32 ? T >= 24 && size_t(T) * nvec >= 640 * kSpNT : T >= int64_t(nvec / 384);
   }
   if (dtype == AERO_BF16) return true;
   if (nvec <= size_t(kHeldVecs) * kSpNT) return dlogits || dtype != AERO_F8E4M3 || nvec <= 4 * kSpNT || T <= 512;
