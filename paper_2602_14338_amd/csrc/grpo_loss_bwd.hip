@@ -322,8 +322,9 @@ static void dispatch_dlogits(const void* logits, int64_t T, int V, int64_t ld, c
   if constexpr (VEC) {
     const int64_t segs = (V / per_vec + kSegNT - 1) / kSegNT;
     if (work > 16 * 256 && grid_fits(T * segs + kAside, kSegNT)) {
+      const LossSum in_rows = loss_in_rows(sum, 512 * kSegNT, s);
       hipLaunchKernelGGL((k_dlogits_seg<DT, ENT>), dim3(unsigned(T * segs + kAside)), dim3(kSegNT), 0, s, logits, V, ld,
-                         int(segs), targets, lse, g, ea, eb, dlogits, loss_in_rows(sum, 512 * kSegNT, s));
+                         int(segs), targets, lse, g, ea, eb, dlogits, in_rows);
       return;
     }
   }

@@ -295,6 +295,40 @@ def test_gradient_rows_beyond_one_segmented_launch(gh):
     torch.cuda.empty_cache()
 
 
+@pytest.mark.parametrize("T", [131072, 131073])
+def test_loss_sum_of_many_segmented_rows(gh, T):
+    """Rows of 32777 bf16 logits, a workgroup per segment: up to 131072 of them the launch of the gradient rows forms the loss, beyond
+    a launch in front of it does.  All but four rows at either end are left untouched."""
+    V = 32777
+    if torch.cuda.mem_get_info()[0] < 20e9:
+        pytest.skip("needs 9 GB")
+    z = torch.full((T, V), 7.0, dtype=torch.bfloat16, device=gh.DEV)
+    rng = np.random.default_rng(T)
+    rows = np.r_[0:4, T - 4:T]
+    host = ai.f32_to_bf16_bits(rng.normal(0, 3, size=(8, V)).astype(np.float32)).reshape(8, V)
+    at = torch.from_numpy(rows).to(gh.DEV)
+    z[at] = gh.logits_to_dev(host, "bf16")
+    tr = np.full(T, gh.binding.AERO_ROW_UNTOUCHED, np.int32)
+    tr[rows] = [0, 1, -1, 1, 0, -1, 1, 0]
+    tg = np.zeros(T, np.int32)
+    tg[rows] = rng.integers(0, V, size=8)
+    lp, _, lse = orc.logprob_fwd(host, "bf16", V, tg[rows])
+    lse_d = torch.zeros(T, device=gh.DEV)
+    lse_d[at] = gh.dev(lse.astype(np.float32))
+    old = np.zeros(T, np.float32)
+    old[rows] = lp - 0.01
+    adv, weight = np.float32([1.0, -0.5]), np.float32([0.25, 0.5])
+    ref = orc.grpo_loss_bwd(host, "bf16", V, tg[rows], old[rows], tr[rows], adv, weight, np.float32(0.2), np.float32(0.2), 1.0)
+    out = gh.run_loss_bwd(z, T, V, V, tg, lse_d, old, tr, adv, weight, inplace=True)
+    gh.assert_loss(out["loss"].item(), ref["loss"], ref["loss_terms"])
+    got = gh.to_np64(z[at])
+    assert (np.abs(got - ref["dlogits"]) <= 1e-2 * np.abs(ref["g"])[:, None] + 2.0 ** -8 * np.abs(ref["dlogits"])).all()
+    z[at] = 7.0
+    assert (z == 7.0).all()
+    del z, out
+    torch.cuda.empty_cache()
+
+
 def test_gradient_rows_that_fill_a_launch(gh):
     """2^26 - 1 rows of 8 bf16 logits, a wave each: as many as a launch holds, so that the last eight rows, whose
     places the workgroups set aside for the loss sum take, have a launch of their own.  All but two rows at either end and four
