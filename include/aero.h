@@ -172,10 +172,14 @@ aero_status aero_logprob_fwd(
  *
  * logits / dlogits  [T, ld], same dtype and ld; dlogits may alias logits (in place).
  * lse      f32[T] from aero_logprob_fwd, or NULL: then the statistics are computed here.  With
- *          lse == NULL the whole call is one pass over HBM (the row is held on chip: read once, written once) where
- *          rows have at most 320 KB (163840 2-byte logits, 81920 fp32, 327680 8-bit ones), logits are
- *          aligned to their element size, and dlogits, if given, lies at the same offset from 16 bytes as logits; fp32,
- *          fp16 and 8-bit rows of more than 128 KB are taken so with dlogits only, and from 1, 96 and 192 rows on.
+ *          lse == NULL the whole call is one pass over the rows where logits are aligned to their element size and
+ *          dlogits, if given, lies at the same offset from 16 bytes as logits, for
+ *            rows of at most 320 KB (163840 2-byte logits, 81920 fp32, 327680 8-bit ones), which are held on chip: read once,
+ *            written once.  fp32, fp16 and 8-bit rows of more than 128 KB with dlogits only, and from 1, 96 and 192 rows
+ *            on; 8-bit rows of more than 64 KB without dlogits up to 512 rows;
+ *            rows of at most 1280 KB with dlogits, of which 320 KB are held on chip and the rest is read a second time:
+ *            from 256 MB of rows on, below that up to 256 rows of fp32 (at least 24 and 10 MB) and of 2-byte
+ *            logits (at least one for every 6 KB of a row's length).
  *          Otherwise a forward pass into the workspace precedes the gradient pass, which stores element by element
  *          where logits and dlogits differ in that offset.
  * entropy  f32[T] from aero_logprob_fwd; read only when lse != NULL and entropy_coef != 0

@@ -5,11 +5,11 @@
 // epilogue arithmetic) hide behind the other's matrix instructions.
 //
 // Two things bound the loop, in about equal parts.  The power limit: k_fused_stats<false> at 151936 x 16384 x 1536 takes
-// 5.92 ms on Gaussian operands at 1.97 GHz and 4.95 on zeros at 2.39, the matrix units busy in 62 % of the cycles both
+// 5.74 ms on Gaussian operands at 1.85 GHz and 4.54 on zeros at 2.39, the matrix units busy in 66-69 % of the cycles both
 // times, so the energy per flop of the matrix instruction counts; a stream of nothing but 16 x 16 x 32 reaches 2.11
 // PFLOP/s on Gaussian data where 32 x 32 x 16 reaches 1.85 (both 2.4-2.5 on zeros), and 2.13 when consecutive
-// instructions always share one operand (the column order alternates from row to row).  And the other 38 % of the
-// cycles, part of which the clock would take back: the library's 81 % at K = 3584 come with 1.70 GHz.  The bare loop below:
+// instructions always share one operand (the column order alternates from row to row).  And the other third of the
+// cycles, part of which the clock would take back: the library's 81 % at K = 3584 come with 1.73 GHz.  The bare loop below:
 // 1.45 PFLOP/s at 151936 x 16384 x 1536 and 1.44 at 152064 x 32768 x 3584, against 1.36 / 1.34 with 32 x 32 x 16.
 //
 // Operands go HBM -> LDS directly (buffer_load ... lds) in two stages of 256 x 64 slices; rows start on 16 bytes, K is any

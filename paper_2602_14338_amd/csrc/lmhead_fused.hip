@@ -27,7 +27,8 @@
 //           k_scatter_dh     fp32 partials summed in fixed order, times scale -> bf16 dhidden at the original rows
 // All contractions use the same 256 x 256 x 64 MFMA tile, both operands K-contiguous but for the weight in k_gemm_dh,
 // whose rows are the contraction index and which a transposing LDS read turns.  In all but k_gemm_dh (whose split count
-// fills the CUs once or twice) and the longer k_gemm_dw (kDwTileRows) a workgroup per CU walks the tiles.
+// fills the CUs once or twice), the longer k_gemm_dw (kDwTileRows) and forward tiles of many slices (kForwardTileSlices) a workgroup
+// per CU walks the tiles.
 #include <mutex>
 
 #include "gemm_tile.h"
@@ -1056,7 +1057,7 @@ extern "C" aero_status aero_lmhead_logprob_fused(
   const int tiles_t = int(p.T_pad / kTile);
   const int tiles_h = (H + kTile - 1) / kTile;
   const int grid_dh = dh_grid(p.T_pad, H, p.V_ld);
-  // contractions: one workgroup per CU walks the tiles (dweight: see kDwTileRows); a multiple of 8 keeps a walk on its XCD
+  // contractions: one workgroup per CU walks the tiles (exceptions: kDwTileRows, kForwardTileSlices); a multiple of 8 keeps a walk on its XCD
   const int cus = compute_units() / 8 * 8 > 0 ? compute_units() / 8 * 8 : 8;
   auto walkers = [&](int n) { return dim3(unsigned(n < cus ? n : cus)); };
   auto forward_grid = [&](int n) { return (H + kDK - 1) / kDK < kForwardTileSlices ? walkers(xcd_grid(n)) : dim3(unsigned(xcd_grid(n))); };
