@@ -10,7 +10,7 @@
 //                            per block, so the running (offset, sum exp, sum exp*z) is a per-lane
 //                            register recurrence with no shuffles.  On the candidates' token tiles it
 //                            also leaves P = exp(z - zy) in bf16 in K-slabs, tokens x vocabulary and
-//                            (by vocabulary chunk) vocabulary x tokens, both in fragment order, that
+//                            vocabulary x tokens, both in fragment order, that
 //                            the two gradient contractions read (2 x T x V x 2 bytes are held)
 //           k_fused_rows     merges the per-tile partials of a token -> logprob, entropy, lse, and in the same
 //                            breath the candidates' loss terms and gradient scalars:
@@ -43,7 +43,7 @@ inline size_t up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 // ------------------------------------------------------------------------------------------
 struct FusedPlan {
   int64_t T, T_pad;
-  int V, V_ld, H, H_pad, tiles_v, VC, n_chunks;   // VC: vocabulary rows per chunk of the transposed dz
+  int V, V_ld, H, H_pad, tiles_v;
   size_t off_part, off_fidx, off_nf, off_term, off_flag, off_zy, off_pos, off_nact, off_gc, off_lsec, off_yc, off_ac, off_bc, off_scale,
       off_hc, off_hTc, off_dz, off_dzT, off_dhacc, total;
 };
@@ -52,7 +52,7 @@ struct FusedPlan {
 // (candidate token tiles) x (H tiles) x S fills the launch grid in whole rounds; the buffer holds S
 // stacked copies of the active rows, never more rows than the launch grid covers.  A split's
 // operands are addressed with 32-bit byte offsets, so a split may span at most 4 GiB of the dz
-// slabs: the grid leaves room for that many splits (plus one) when every token is active.
+// slabs of rows_max rows: the grid leaves room for that many splits (plus one) when every token is active.
 constexpr int kDhGridMin = 4096;
 constexpr int64_t kOperandBytes = int64_t(1) << 32;
 static int dh_grid(int64_t T_pad, int H, int V_ld) {
@@ -79,13 +79,6 @@ static FusedPlan make_plan(int64_t T, int V, int H) {
   p.H = H;
   p.H_pad = int(up(size_t(H), kTile));
   p.tiles_v = p.V_ld / kTile;
-  // the transposed dz is stored in vocabulary chunks of at most 2 GiB (T_pad x VC bf16), so that
-  // the dweight contraction can address a chunk with 32-bit offsets
-  int64_t vc = (int64_t(1024) << 20) / p.T_pad / kTile * kTile;
-  if (vc < kTile) vc = kTile;
-  if (vc > p.V_ld) vc = p.V_ld;
-  p.VC = int(vc);
-  p.n_chunks = (p.V_ld + p.VC - 1) / p.VC;
   size_t o = 0;
   auto take = [&](size_t bytes) { size_t at = o; o += up(bytes, kWsAlign); return at; };
   p.off_part = take(size_t(3) * p.tiles_v * p.T_pad * 4);
@@ -105,7 +98,7 @@ static FusedPlan make_plan(int64_t T, int V, int H) {
   p.off_hc = take(size_t(p.T_pad) * H * 2);
   p.off_hTc = take(size_t(p.H_pad) * p.T_pad * 2);
   p.off_dz = take(size_t(p.T_pad) * p.V_ld * 2);
-  p.off_dzT = take(size_t(p.n_chunks) * p.VC * p.T_pad * 2);
+  p.off_dzT = take(size_t(p.V_ld) * p.T_pad * 2);
   p.off_dhacc = take(size_t(dh_part_rows(p.T_pad, H, p.V_ld)) * H * 4);
   p.total = o;
   return p;
@@ -265,14 +258,14 @@ __global__ __launch_bounds__(256) void k_gather_rows(const uint16_t* __restrict_
 // A 256 x 256 bf16 tile (vocabulary rows m0.., token columns n0..) held as packed pairs in the accumulator
 // layout, pk[nb][mb] = the four rows acc_row(wm, mb, 0 .. 3) of column acc_col(wn, nb), leaves in the two
 // layouts the gradient contractions read, both K-slabs in fragment order (frag_order_offset): tokens x vocabulary, and
-// vocabulary chunk by chunk x tokens.  Every instruction stores one 1 KB block, so nothing is staged in LDS and no wave
+// vocabulary x tokens.  Every instruction stores one 1 KB block, so nothing is staged in LDS and no wave
 // waits for another.  A block is turned round by the matrix unit: its registers are also the left operand
 // of a 16 x 16 x 16 instruction (rows = tokens), and times the identity it comes back exactly with the tokens in a lane's
 // registers and the vocabulary across the lanes - one instruction and two conversions in place of some twenty exchanges and
 // selections between lanes.
 constexpr int kTileStores = 2 * kNB * kMB / 2;   // per wave
 __device__ __forceinline__ void store_tile_both_layouts(const uint32_t (&pk)[kNB][kMB][2], const WavePos& wp, int lane, int m0, int n0,
-                                                        int64_t T_pad, int VC, uint16_t* __restrict__ dz, uint16_t* __restrict__ dzT) {
+                                                        int64_t T_pad, int V_ld, uint16_t* __restrict__ dz, uint16_t* __restrict__ dzT) {
   typedef short s16x4_t __attribute__((ext_vector_type(4)));
   typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
   const int group = lane >> 4;
@@ -287,22 +280,21 @@ __device__ __forceinline__ void store_tile_both_layouts(const uint32_t (&pk)[kNB
     __builtin_amdgcn_raw_buffer_store_b128(u32x4_t{lo[0], hi[0], lo[1], hi[1]}, to, lane_off + off, 0, kNonTemporal);
   };
   const uint32_t in_block = uint32_t((lane & 15) * 8 + ((group & 1) * 2 + (group >> 1)) * 128) * 2;   // row lane % 16, that K
-  // ---- tokens x vocabulary: four slabs of T_pad rows; the wave's 128 vocabulary rows are two of them ----
-  const uint32_t slab = uint32_t(T_pad) * 128;   // bytes
-  const __amdgpu_buffer_rsrc_t rz = __builtin_amdgcn_make_buffer_rsrc(dz + int64_t(m0 / 64) * T_pad * 64, 0, int(4 * slab), 0x00020000);
-  const uint32_t at = uint32_t(n0 + wp.wn * 64) * 128 + wp.wm * 2 * slab;
+  // ---- tokens x vocabulary: four slabs of a token tile, the wave's 128 vocabulary rows are two of them ----
+  constexpr uint32_t slab = kSlabElems * 2;   // bytes
+  const __amdgpu_buffer_rsrc_t rz =
+      __builtin_amdgcn_make_buffer_rsrc(dz + slab_offset(V_ld / 64, n0 / kTile, m0 / 64), 0, int(4 * slab), 0x00020000);
+  const uint32_t at = uint32_t(wp.wn * 64) * 128 + wp.wm * 2 * slab;
 #pragma unroll
   for (int nb = 0; nb < kNB; ++nb)
 #pragma unroll
     for (int mb = 0; mb < kMB; mb += 2)
       store(rz, u32x2_t{pk[nb][mb][0], pk[nb][mb][1]}, u32x2_t{pk[nb][mb + 1][0], pk[nb][mb + 1][1]}, in_block,
             at + (mb / 4) * slab + (mb / 2 % 2) * 1024 + nb * 2048);
-  // ---- vocabulary x tokens: a tile lies inside one chunk (VC is a multiple of the tile height), the wave's 64 tokens are
-  // one slab of it ----
-  const uint32_t slabT = uint32_t(VC) * 128;
-  const __amdgpu_buffer_rsrc_t rzT = __builtin_amdgcn_make_buffer_rsrc(
-      dzT + int64_t(m0 / VC) * VC * T_pad + int64_t(n0 / 64) * VC * 64, 0, int(4 * slabT), 0x00020000);
-  const uint32_t atT = uint32_t(m0 % VC + wp.wm * 128) * 128 + wp.wn * slabT;
+  // ---- vocabulary x tokens: four slabs of a vocabulary tile, the wave's 64 tokens are one of them ----
+  const __amdgpu_buffer_rsrc_t rzT =
+      __builtin_amdgcn_make_buffer_rsrc(dzT + slab_offset(T_pad / 64, m0 / kTile, n0 / 64), 0, int(4 * slab), 0x00020000);
+  const uint32_t atT = uint32_t(wp.wm * 128) * 128 + wp.wn * slab;
   const int diag = (lane & 15) - 4 * group;   // the lane's register of the identity that is 1
   const u32x2_t one = {diag == 0 ? 0x3f80u : diag == 1 ? 0x3f800000u : 0u, diag == 2 ? 0x3f80u : diag == 3 ? 0x3f800000u : 0u};
   auto turned = [&](const uint32_t (&block)[2]) {
@@ -379,7 +371,7 @@ template <bool STORE>
 __global__ __launch_bounds__(kGemmNT, 2) void k_fused_stats(
     const uint16_t* __restrict__ W, const uint16_t* __restrict__ Hf, int V, int H, int tiles_v,
     int64_t T_pad, const int32_t* __restrict__ nf, float* __restrict__ part_m,
-    float* __restrict__ part_s, float* __restrict__ part_sz, const float* __restrict__ zy, int VC,
+    float* __restrict__ part_s, float* __restrict__ part_sz, const float* __restrict__ zy, int V_ld,
     int32_t* __restrict__ nact, uint16_t* __restrict__ dz, uint16_t* __restrict__ dzT) {
   extern __shared__ __align__(16) uint16_t smem[];
   // the tile order covers only the token tiles that hold rows with a target (count known on the
@@ -511,7 +503,7 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_fused_stats(
     if constexpr (STORE) {
       if (store) {
         if (__any(wide) && lane == 0) atomicOr(nact + 2, 1);
-        store_tile_both_layouts(pk, wp, lane, m0, n0, T_pad, VC, dz, dzT);
+        store_tile_both_layouts(pk, wp, lane, m0, n0, T_pad, V_ld, dz, dzT);
       }
     }
   }
@@ -537,7 +529,7 @@ struct FusedTerms {
   LossHyper hyper;
   const int32_t* nact;
   int64_t T_pad;
-  int VC, force_recompute;
+  int V_ld, force_recompute;
   float* term;
   int32_t* flag;
   float *gc, *lsec;
@@ -571,8 +563,8 @@ __device__ __forceinline__ void candidate_row(const FusedTerms& q, int64_t j, in
   }
   q.scale[j] = -r.g * expf(lp);
   const uint16_t own = f32_to_bf16(-expm1f(-lp));
-  q.dz[frag_order_offset(q.T_pad, j, y)] = own;
-  q.dzT[int64_t(y / q.VC) * q.VC * q.T_pad + frag_order_offset(q.VC, y % q.VC, j)] = own;
+  q.dz[frag_order_offset(q.V_ld / 64, j, y)] = own;
+  q.dzT[frag_order_offset(q.T_pad / 64, y, j)] = own;
 }
 
 // TOK consecutive compact rows per workgroup of 1024 threads.  The tiles_v partials of a row are split over
@@ -638,7 +630,7 @@ __global__ __launch_bounds__(kRowsNT) void k_fused_rows(
 // ------------------------------------------------------------------------------------------
 // The candidates' hidden rows ([T_pad][H], H % 8 == 0, 16-byte aligned), each times its scale (product in fp32, rounded to
 // bf16 once), transposed into the K-slab layout the GEMM tile reads: row r becomes K index r, column c operand row c:
-//   out[(r / 64) * C_pad * 64 + c * 64 + r % 64] = scale[r] * in[r][c]
+//   out[slab_offset(T_pad / 64, c / 256, r / 64) + c % 256 * 64 + r % 64] = scale[r] * in[r][c]
 // for c < C_pad; columns from H on do not exist in `in` and give 0.
 // 64 x 64 tiles through LDS, one per workgroup of the grid (T_pad / 64 + 1, C_pad / 64); the first workgroup of the last
 // column forms the loss from the candidates' terms meanwhile (a launch of its own: 4.7 us a call).  Every global access is a 16-byte
@@ -680,7 +672,7 @@ __global__ __launch_bounds__(256) void k_hidden_and_loss(const uint16_t* __restr
     tile[rr][c8 / 2 + 3] = v.w;
   }
   __syncthreads();
-  uint16_t* slab = out + int64_t(blockIdx.x) * C_pad * 64;
+  uint16_t* slab = out + slab_offset(T_pad / 64, c0 / kTile, blockIdx.x) + c0 % kTile * 64;
 #pragma unroll
   for (int k = 0; k < 2; ++k) {
     const int u = threadIdx.x + k * 256;
@@ -692,7 +684,7 @@ __global__ __launch_bounds__(256) void k_hidden_and_loss(const uint16_t* __restr
       w[e] = (cc & 1) ? ((lo >> 16) | (hi & 0xffff0000u)) : ((lo & 0xffffu) | (hi << 16));
     }
     const u32x4_t v = {w[0], w[1], w[2], w[3]};
-    if (c0 + cc < C_pad) *reinterpret_cast<u32x4_t*>(slab + int64_t(c0 + cc) * 64 + 8 * q) = v;
+    *reinterpret_cast<u32x4_t*>(slab + cc * 64 + 8 * q) = v;
   }
 }
 
@@ -701,8 +693,7 @@ __global__ __launch_bounds__(256) void k_hidden_and_loss(const uint16_t* __restr
 // ------------------------------------------------------------------------------------------
 // z^T tile rows = vocab [m0, m0 + 256), columns = compacted tokens.  The bf16 gradient leaves in
 // the two layouts the next two contractions read, both K-slabs in fragment order (frag_order_offset): dz tokens x
-// vocabulary, and dzT vocabulary x tokens in chunks of VC vocabulary rows, so that one chunk stays below the 4 GiB a
-// buffer descriptor can address; entries outside the vocabulary or the candidate tokens are zero.
+// vocabulary, and dzT vocabulary x tokens; entries outside the vocabulary or the candidate tokens are zero.
 // ENT: rows also carry the entropy-bonus term, dz = pi (ac z + bc) + gc onehot; otherwise ac = 0
 // and the scale is the per-token constant bc = -g.
 // The kernel is the recompute mode of the backward pass (see FusedTerms): with force == 0 it
@@ -710,7 +701,7 @@ __global__ __launch_bounds__(256) void k_hidden_and_loss(const uint16_t* __restr
 template <bool ENT>
 __global__ __launch_bounds__(kGemmNT, 2) void k_fused_dz(
     const uint16_t* __restrict__ W, const uint16_t* __restrict__ Hc, int V, int H,
-    int tiles_v, int64_t T_pad, int VC, int force, const int32_t* __restrict__ nact,
+    int tiles_v, int64_t T_pad, int V_ld, int force, const int32_t* __restrict__ nact,
     const float* __restrict__ gc, const float* __restrict__ lsec, const int32_t* __restrict__ yc,
     const float* __restrict__ ac, const float* __restrict__ bc, uint16_t* __restrict__ dz,
     uint16_t* __restrict__ dzT) {
@@ -779,7 +770,7 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_fused_dz(
         pk[nb][mb][1] = pack_bf16x2(d[2], d[3]);
       }
     }
-    store_tile_both_layouts(pk, wp, lane, m0, n0, T_pad, VC, dz, dzT);
+    store_tile_both_layouts(pk, wp, lane, m0, n0, T_pad, V_ld, dz, dzT);
   }
   end_of_walk();
 }
@@ -806,15 +797,15 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_gemm_dh(
   const int per = (nslices + S - 1) / S;
   WavePos wp = wave_pos<false>();
   const int wm = wp.wm, wn = wp.wn;
-  GemmStream<true, true, true, true, false> stream(kDK, T_pad * kDK, H, 0, 0);
+  GemmStream<true, true, true, true, false> stream(kDK, kSlabElems, H, 0, 0);
   auto source = [&](int split, int tt, int th) {
     const int k_begin = min(vK, split * per * kDK);
     const int k_len = max(0, min(vK, (split + 1) * per * kDK) - k_begin);
     TileSrc t;
-    t.a_base = dz + int64_t(k_begin / kDK) * T_pad * kDK;
+    t.a_base = dz + slab_offset(nslices, tt, k_begin / kDK);
     // a wave requests 32 of the tile's rows: nothing where there is no candidate among them
-    t.a_bytes = tt * kTile + stream.wave * 32 < n_cand ? int64_t(k_len / kDK) * T_pad * kDK * 2 : 0;
-    t.a = uint32_t(tt * kTile * kDK * 2);
+    t.a_bytes = tt * kTile + stream.wave * 32 < n_cand ? int64_t(k_len) * kTile * 2 : 0;
+    t.a = 0;
     // weight rows past the vocabulary (the split may start there) lie past the operand's bytes and read as zeros
     t.b_base = W + int64_t(min(k_begin, V)) * H;
     t.b_bytes = int64_t(max(V - k_begin, 0)) * H * 2;
@@ -867,7 +858,7 @@ constexpr int64_t kDwTileRows = 8192;
 // dW[m][h] = sum_t XT[m][t] hTc[h][t], hTc = the candidates' hidden rows times their scale     M = V, N = H, K = candidate tokens (padded)
 template <bool OUT_BF16, bool ACC>
 __global__ __launch_bounds__(kGemmNT, 2) void k_gemm_dw(
-    const uint16_t* __restrict__ dzT, const uint16_t* __restrict__ hTc, int VC, int H_pad, int V, int H,
+    const uint16_t* __restrict__ dzT, const uint16_t* __restrict__ hTc, int V, int H,
     int tile0, int n_tiles, int tiles_v, int tiles_h, int64_t T_pad, const int32_t* __restrict__ nact, int vec, void* dW) {
   extern __shared__ __align__(16) uint16_t smem[];
   // the contraction ends with the slice of the last candidate, not with its tile: the positions behind it are zeros
@@ -875,19 +866,18 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_gemm_dw(
   const int K = (nact[0] + kDK - 1) / kDK * kDK;
   WavePos wp = wave_pos<true>();
   const int wm = wp.wm, wn = wp.wn;
-  GemmStream<true, true, false, true, false> stream(kDK, int64_t(VC) * kDK, kDK, int64_t(H_pad) * kDK, 0);
+  GemmStream<true, true, false, true, false> stream(kDK, kSlabElems, kDK, kSlabElems, 0);
   auto source = [&](int tv, int th) {
-    const int m0 = tv * kTile;   // the tile's rows lie inside one vocabulary chunk of the transposed dz
     const bool any = th * kTile + stream.wave * 32 < H;   // of the 32 columns that the wave requests
-    return TileSrc{dzT + int64_t(m0 / VC) * VC * T_pad, hTc, int64_t(K) * VC * 2, any ? int64_t(K) * H_pad * 2 : 0,
-                   uint32_t(m0 % VC) * (kDK * 2), uint32_t(th * kTile * kDK * 2), max(K / kDK, 1)};   // no candidates: one slice of nothing
+    return TileSrc{dzT + slab_offset(T_pad / 64, tv, 0), hTc + slab_offset(T_pad / 64, th, 0), int64_t(K) * kTile * 2,
+                   any ? int64_t(K) * kTile * 2 : 0, 0u, 0u, max(K / kDK, 1)};   // no candidates: one slice of nothing
   };
   // accumulate (uniform): the tile is added to what the caller's buffer holds (gradient accumulation over
   // micro-batches).  vec (uniform): that buffer is 16-byte aligned, as every allocation is.  Plain stores: an
   // instruction writes 64 bytes per row and L2 joins the two halves of a line; non-temporal ones leave it in
   // halves (1.4 times the gradient's bytes written, 312 against 287 us with 600 tokens at H = 1536,
   // V = 151936 in bf16 while the contraction took whole token tiles - 223 us since it ends earlier -, 1690 against
-  // 1660 us per chunk with 16384 in fp32).
+  // 1660 us per 1536 tiles with 16384 in fp32).
   constexpr int kDT = OUT_BF16 ? kBF16 : kF32;
   int pid = blockIdx.x, tv, th;
   bool more = tile_of_step(pid, tiles_v, tiles_h, tile0, n_tiles, tv, th), stored = false;
@@ -1035,7 +1025,7 @@ extern "C" aero_status aero_lmhead_logprob_fused(
   const FusedPlan p = make_plan(T, V, H);
   // operands are addressed with 32-bit byte offsets: every slab operand must stay below 4 GiB
   constexpr size_t kOperandLimit = size_t(1) << 32;
-  if (size_t(p.H_pad) * size_t(p.T_pad) * 2 >= kOperandLimit || size_t(p.T_pad) * size_t(p.VC) * 2 >= kOperandLimit ||
+  if (size_t(p.H_pad) * size_t(p.T_pad) * 2 >= kOperandLimit || size_t(p.T_pad) * kTile * 2 >= kOperandLimit ||
       size_t(V) * size_t(H) * 2 >= kOperandLimit)
     return AERO_ERR_SHAPE;
   {  // the split-K dhidden contraction must find a split count whose K ranges stay below that limit
@@ -1095,7 +1085,7 @@ extern "C" aero_status aero_lmhead_logprob_fused(
   FusedTerms terms{};
   if (bwd)
     terms = FusedTerms{targets, token_rollout, old_logprob, adv, weight_rollout, ref_logprob,
-                       LossHyper{eps_lo, eps_hi, grad_scale, entropy_coef, kl_coef}, nact, p.T_pad, p.VC, stored ? 0 : 1,
+                       LossHyper{eps_lo, eps_hi, grad_scale, entropy_coef, kl_coef}, nact, p.T_pad, p.V_ld, stored ? 0 : 1,
                        reinterpret_cast<float*>(ws + p.off_term), reinterpret_cast<int32_t*>(ws + p.off_flag),
                        reinterpret_cast<float*>(ws + p.off_gc), reinterpret_cast<float*>(ws + p.off_lsec),
                        reinterpret_cast<int32_t*>(ws + p.off_yc), reinterpret_cast<float*>(ws + p.off_ac),
@@ -1110,10 +1100,10 @@ extern "C" aero_status aero_lmhead_logprob_fused(
       const int n = p.tiles_v * tiles_t;
       if (stored)
         hipLaunchKernelGGL(k_fused_stats<true>, forward_grid(n), dim3(kGemmNT), kGemmLdsBytes, s, Wp, hf,
-                           V, H, p.tiles_v, p.T_pad, nf, part_m, part_s, part_sz, zy, p.VC, nact, dz, dzT);
+                           V, H, p.tiles_v, p.T_pad, nf, part_m, part_s, part_sz, zy, p.V_ld, nact, dz, dzT);
       else
         hipLaunchKernelGGL(k_fused_stats<false>, forward_grid(n), dim3(kGemmNT), kGemmLdsBytes, s, Wp, hf,
-                           V, H, p.tiles_v, p.T_pad, nf, part_m, part_s, part_sz, zy, p.VC, nact, dz, dzT);
+                           V, H, p.tiles_v, p.T_pad, nf, part_m, part_s, part_sz, zy, p.V_ld, nact, dz, dzT);
     }
     if (p.T_pad <= kFewRows)
       hipLaunchKernelGGL(k_fused_rows<16>, dim3(unsigned(p.T_pad / 16)), dim3(kRowsNT), 0, s, p.tiles_v, p.T_pad, fidx, nf,
@@ -1138,11 +1128,11 @@ extern "C" aero_status aero_lmhead_logprob_fused(
     const int n = p.tiles_v * tiles_t;
     if (ent)
       hipLaunchKernelGGL(k_fused_dz<true>, forward_grid(n), dim3(kGemmNT), kGemmLdsBytes, s, Wp, hf, V,
-                         H, p.tiles_v, p.T_pad, p.VC, terms.force_recompute, nact, terms.gc, terms.lsec, terms.yc, terms.ac,
+                         H, p.tiles_v, p.T_pad, p.V_ld, terms.force_recompute, nact, terms.gc, terms.lsec, terms.yc, terms.ac,
                          terms.bc, dz, dzT);
     else
       hipLaunchKernelGGL(k_fused_dz<false>, forward_grid(n), dim3(kGemmNT), kGemmLdsBytes, s, Wp, hf, V,
-                         H, p.tiles_v, p.T_pad, p.VC, terms.force_recompute, nact, terms.gc, terms.lsec, terms.yc, terms.ac,
+                         H, p.tiles_v, p.T_pad, p.V_ld, terms.force_recompute, nact, terms.gc, terms.lsec, terms.yc, terms.ac,
                          terms.bc, dz, dzT);
   }
   hipLaunchKernelGGL(k_hidden_and_loss, dim3(unsigned(p.T_pad / 64 + 1), unsigned(p.H_pad / 64)), dim3(256), 0, s, hf, p.T_pad, H,
@@ -1154,17 +1144,18 @@ extern "C" aero_status aero_lmhead_logprob_fused(
     hipLaunchKernelGGL(k_gemm_dh, dim3(unsigned(grid_dh)), dim3(kGemmNT), kGemmLdsBytes, s, dz, Wp, V, p.V_ld, H, tiles_h, p.T_pad,
                        nact, dh_acc);
   }
-  // dweight: one launch per chunk of the transposed dz.  VC is sized so that a full chunk is a whole
-  // number of rounds of 256 tiles at the two model shapes (measured: 1-3 % faster than one long walk)
+  // dweight: one launch where a workgroup walks; where it has one tile, eight rounds of tiles a launch, so that the workgroups
+  // that share operand slices stay close along K (32768 tokens at H = 3584, V = 152064, whole call: one launch 67.1, 16 rounds
+  // 66.7, eight 66.1, four 66.8 ms; 16384 at H = 1536 even)
   {
-    const int total = p.tiles_v * tiles_h, per = (p.VC / kTile) * tiles_h;
+    const int total = p.tiles_v * tiles_h, per = p.T_pad < kDwTileRows ? total : 8 * cus;
     const int vec_dw = reinterpret_cast<uintptr_t>(dweight) % 16 == 0;   // rows are multiples of 16 bytes
     const auto kernel = dweight_dtype == AERO_BF16 ? (accumulate ? k_gemm_dw<true, true> : k_gemm_dw<true, false>)
                                                    : (accumulate ? k_gemm_dw<false, true> : k_gemm_dw<false, false>);
     for (int t0 = 0; t0 < total; t0 += per) {
       const int n = total - t0 < per ? total - t0 : per;
       const dim3 grid = p.T_pad < kDwTileRows ? walkers(xcd_grid(n)) : dim3(unsigned(xcd_grid(n)));
-      hipLaunchKernelGGL(kernel, grid, dim3(kGemmNT), kGemmLdsBytes, s, dzT, hTc, p.VC, p.H_pad, V, H, t0, n,
+      hipLaunchKernelGGL(kernel, grid, dim3(kGemmNT), kGemmLdsBytes, s, dzT, hTc, V, H, t0, n,
                          p.tiles_v, tiles_h, p.T_pad, nact, vec_dw, dweight);
     }
   }
