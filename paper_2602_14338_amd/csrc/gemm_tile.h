@@ -67,8 +67,7 @@ struct WavePos {
 //               tokens 202 / 171 (169 / 156), 700 233 / 234 (206 / 206), 1400 398 / 374 (386 / 384); H = 768 500 tokens 174 / 143 (120 / 121), 700
 //               200 / 192 (156 / 158), 900 265 / 225 (204 / 210), 1700 366 / 359 (347 / 349), 3300 656 / 643 (639 / 640); with a gradient 0.94-1.02
 //               of the time without.
-//   dhidden     from 8 with one token tile (250 tokens at H = 3584 297 / 267 us); with more of them a loss: the touches are traffic into
-//               the CU like any other (16384 tokens at H = 1536 3.90 / 4.00 ms with the weight's alone, 1500 451 / 474 us with both).
+//   dhidden     not at all: its loop requests further ahead (GemmRing), and has more than one touch of a line to lose by it.
 constexpr int kWarmSlices = 32, kWarmSlicesForward = 12, kWarmSlicesAlone = 8;
 __device__ __forceinline__ int forward_warm_from(int token_tiles) {
   return token_tiles == 1 ? kWarmSlicesAlone : kWarmSlicesForward;
@@ -258,18 +257,12 @@ __device__ __forceinline__ DmaLane dma_lane_af(int64_t kstep, int wave, int lane
 }
 
 // An operand stored the other way round (BT): a row-major matrix whose rows are the contraction index, [K][rows],
-// e.g. the weight in dhidden = dz weight.  A slice is 64 rows of 256 columns (512 bytes, whole lines again); its LDS
-// image keeps that orientation, [64][256], and fragments come out of it with the transposing LDS read
+// e.g. the weight in dhidden = dz weight (GemmRing).  A step is 32 rows of 256 columns (512 bytes, whole lines); its LDS
+// image keeps that orientation, [32][256], and fragments come out of it with the transposing LDS read
 // (ds_read_b64_tr_b16): of every 16 lanes, lane j names four consecutive columns 4 (j % 4) .. of row j / 4, and
 // receives column j of those four rows, so two reads make the eight K values of a fragment.  The 32-byte
 // segments of a row are XORed with f(row) = row % 4 + 4 ((row / 8) % 2): the eight rows that 32 lanes touch at once
 // fall on distinct banks.
-__device__ __forceinline__ DmaLane dma_lane_bt(int64_t ld, int wave, int lane) {
-  // wave w fills rows [8 w, 8 w + 8) with 4 instructions of 2 rows; lane l covers chunk l % 32 of row l / 32
-  const uint32_t row = uint32_t(int64_t(wave * 8 + (lane >> 5)) * ld * 2) + uint32_t(lane & 1) * 16;
-  const uint32_t seg = (lane & 31) >> 1, f = uint32_t(lane >> 5) | uint32_t(wave & 1) << 2;
-  return DmaLane{row + (seg ^ f) * 32, row + (seg ^ (f | 2)) * 32, uint32_t(4 * ld), uint32_t(kDK * ld * 2)};
-}
 __device__ __forceinline__ FragAddr<4> frag_addr_bt(const uint16_t* lds, int col0, int lane) {
   const int group = lane >> 4, j = lane & 15;
   const int swz = (j >> 2) | (group & 1) << 2;
@@ -338,10 +331,10 @@ __device__ __forceinline__ TileSrc no_tile(const TileSrc& t) { return TileSrc{t.
 // do not wait for each other's stores), waves 4 to 7 free of loads and warming L2 four slices ahead (dweight of 1000
 // tokens -8 %, everything long +3 to +12 %: bytes into the CU are what counts).
 // WARM: L2 warm-up two slices ahead (see kWarmSlices).
-// BT: operand B is [K][rows].  AF: operand A is in K-slabs in fragment order (tiles start at multiples of 16 rows).
+// AF: operand A is in K-slabs in fragment order (tiles start at multiples of 16 rows).
 // TAIL: K need not be a multiple of 64: the 16-byte chunks of the last slice that lie past a row's end are requested from
 // behind the buffer, which gives zeros.
-template <bool WARM, bool SWAP, bool BT, bool AF, bool TAIL>
+template <bool WARM, bool SWAP, bool AF, bool TAIL>
 struct GemmStream {
   DmaLane la, lb;
   int lane, wave, stage;   // stage: where the next slice lies
@@ -353,7 +346,7 @@ struct GemmStream {
     wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     stage = 0;
     la = AF ? dma_lane_af(kstep_a, wave, lane) : dma_lane(lda, kstep_a, wave, lane);
-    lb = BT ? dma_lane_bt(ldb, wave, lane) : dma_lane(ldb, kstep_b, wave, lane);
+    lb = dma_lane(ldb, kstep_b, wave, lane);
     tail = TAIL ? (K - 1) % kDK / 8 + 1 : 8;
   }
 
@@ -412,8 +405,7 @@ struct GemmStream {
     // 8 x 4 block of tiles: 12 operand slices for 32 tiles), and loads return in order, so one late
     // line holds back everything queued behind it.  Each slice is therefore touched two slices
     // early with one 4-byte load per 128-byte line (sunk into a scratch corner of LDS), the lines
-    // shared out over the workgroups that will read them (warm_share): waves 0 to 3 take the A rows' lines, 4 to 7 those of B (line
-    // l: row l; BT: row l % 64, 128-byte piece l / 64).  The touch is issued late in the slice, when every wave's
+    // shared out over the workgroups that will read them (warm_share): waves 0 to 3 take the A rows' lines, 4 to 7 those of B.  The touch is issued late in the slice, when every wave's
     // requests for the next slice are already queued ahead of it, and it may stay in flight across the next barrier
     // (vmcnt(1)).
     constexpr int kWarmAhead = 2;
@@ -423,9 +415,7 @@ struct GemmStream {
     const bool warm_wave = warm_at <= warm.last;
     const __amdgpu_buffer_rsrc_t rw = warm_a ? operand_rsrc(t.a_base, t.a_bytes) : operand_rsrc(t.b_base, t.b_bytes);
     const uint32_t line = uint32_t(min(warm_at + lane, warm.last));
-    const uint32_t warm_off = warm_a ? t.a + line * (la.row_step / 8)
-                              : BT   ? t.b + (line & 63) * (lb.k_step / kDK) + (line >> 6) * 128
-                                     : t.b + line * (lb.row_step / 8);
+    const uint32_t warm_off = warm_a ? t.a + line * (la.row_step / 8) : t.b + line * (lb.row_step / 8);
     const uint32_t warm_kstep = warm_a ? la.k_step : lb.k_step;
     uint16_t* const warm_sink = smem + kWarmSinkOff / 2 + wave * 128;
     const uint16_t* const first = smem + stage * kDStageElems;
@@ -433,10 +423,7 @@ struct GemmStream {
       if constexpr (AF) return frag_addr_af(first, wm * 128, lane);
       else return frag_addr(first, wm * 128, lane);
     }();
-    auto fb = [&] {
-      if constexpr (BT) return frag_addr_bt(first + kTile * kDK, wn * 64, lane);
-      else return frag_addr(first + kTile * kDK, wn * 64, lane);
-    }();
+    auto fb = frag_addr(first + kTile * kDK, wn * 64, lane);
     // One iteration = one 64-wide slice = two 32-wide K steps of two halves, 16 MFMAs per wave each.
     // The order is pinned with scheduling barriers: the first step's fragments are read up front, the
     // next slice is requested only after the first MFMA group (issuing the 8 loads right after the
@@ -451,39 +438,20 @@ struct GemmStream {
       frags_load(b0, fb, 0, 0);
       __builtin_amdgcn_sched_barrier(0);   // these first: the matrix instructions start with them
       frags_load(a1, fa, kFragBlocks, 0);
-      // The compiler lets a transposing read wait for every load into LDS that it finds on its way, the next slice's
-      // too (the loop of 600 tokens' dhidden stood still for their latency, 2.0 us a slice): all of them come before the request.
-      if constexpr (BT) frags_load(b1, fb, 0, 1);
       frags_mma<SWAP>(a0, b0, 0, acc);
       issue<decltype(last)::value>(src, kn, smem + (stage ^ 1) * kDStageElems);
       frags_load(a2, fa, 0, 1);
-      if constexpr (!BT) frags_load(b1, fb, 0, 1);
+      frags_load(b1, fb, 0, 1);
       frags_mma<SWAP>(a1, b0, 1, acc);
       frags_load(a0, fa, kFragBlocks, 1);
       frags_mma<SWAP>(a2, b1, 0, acc);
-      if constexpr (BT) {
-        __builtin_amdgcn_sched_group_barrier(kDsRd, kFragBlocks, 0);
+      __builtin_amdgcn_sched_group_barrier(kDsRd, kFragBlocks, 0);
+      __builtin_amdgcn_sched_group_barrier(kMfma, kMfmas, 0);
+      __builtin_amdgcn_sched_group_barrier(kVmemRd, 8, 0);
 #pragma unroll
-        for (int r = 0; r < kFragBlocks; ++r) {
-          __builtin_amdgcn_sched_group_barrier(kMfma, 2, 0);
-          __builtin_amdgcn_sched_group_barrier(kDsRd, 2, 0);
-        }
-        __builtin_amdgcn_sched_group_barrier(kMfma, kMfmas - 2 * kFragBlocks, 0);
-        __builtin_amdgcn_sched_group_barrier(kVmemRd, 8, 0);
-#pragma unroll
-        for (int r = 0; r < kFragBlocks; ++r) {
-          __builtin_amdgcn_sched_group_barrier(kMfma, 4, 0);
-          __builtin_amdgcn_sched_group_barrier(kDsRd, 1, 0);
-        }
-      } else {
-        __builtin_amdgcn_sched_group_barrier(kDsRd, kFragBlocks, 0);
-        __builtin_amdgcn_sched_group_barrier(kMfma, kMfmas, 0);
-        __builtin_amdgcn_sched_group_barrier(kVmemRd, 8, 0);
-#pragma unroll
-        for (int r = 0; r < 2 * kFragBlocks; ++r) {
-          __builtin_amdgcn_sched_group_barrier(kMfma, 2, 0);
-          __builtin_amdgcn_sched_group_barrier(kDsRd, 1, 0);
-        }
+      for (int r = 0; r < 2 * kFragBlocks; ++r) {
+        __builtin_amdgcn_sched_group_barrier(kMfma, 2, 0);
+        __builtin_amdgcn_sched_group_barrier(kDsRd, 1, 0);
       }
 #pragma unroll
       for (int r = 0; r < kFragBlocks; ++r) {
@@ -534,6 +502,159 @@ struct GemmStream {
       landed(kNo);
     }
     slice(kYes, kNo, next, 0, 0);
+  }
+};
+
+// ------------------------------------------------------------------------------------------
+// Ring loop: A in K-slabs in fragment order, B stored the other way round ([K][rows], see above), operands of the matrix
+// instruction exchanged; one tile per workgroup.
+//
+// A stage of the loop above is requested one slice ahead, and with a transposed operand only behind all of that slice's
+// transposing reads, which the compiler holds back for every load into LDS that it knows of.  Here a stage is one 32-wide K
+// step (both layouts keep whole lines: 1 KB blocks of A, 512-byte rows of B), four of them lie in LDS, and a step is requested
+// three steps before it is read, in instructions that the compiler does not count.  The second half of a step's matrix
+// instructions waits until the barrier behind it, and covers the reads of the next step's first fragments.
+// k_gemm_dh, two stages of 64 / this loop: 600 tokens at H = 1536, V = 151936 233 / 213 us, 16384 4047 / 3635, 32768 at H = 3584,
+// V = 152064 20.15 / 18.08 ms; the requests in front of the first group of matrix instructions 3781 and 19033, one every four
+// instructions 3743 and 18567 where the chosen place took 3690 and 18400, by half of the waves 4200.
+// (For dweight, whose operands are both in fragment order, 1612 / 1539: it keeps the loop above.)
+// ------------------------------------------------------------------------------------------
+constexpr int kStepK = 32, kRing = 4;
+constexpr int kStepBytes = 2 * kTile * kStepK * 2;   // A, then B
+static_assert(size_t(kRing) * kStepBytes <= kGemmStageBytes, "the ring must fit the LDS budget");
+
+typedef uint32_t rsrc_words_t __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ rsrc_words_t rsrc_words(const uint16_t* base, uint32_t bytes) {
+  const uint64_t b = reinterpret_cast<uint64_t>(base);
+  return rsrc_words_t{uint32_t(__builtin_amdgcn_readfirstlane(uint32_t(b))), uint32_t(__builtin_amdgcn_readfirstlane(uint32_t(b >> 32))) & 0xffffu,
+                      uint32_t(__builtin_amdgcn_readfirstlane(bytes)), 0x00020000u};
+}
+// buffer_load_dwordx4 ... lds: 16 bytes a lane, to LDS byte address `to` (uniform) + 16 lane.  It has no destination register
+// that the compiler could take for written; the loop waits for it by vmcnt.
+__device__ __forceinline__ void request_lds16(rsrc_words_t r, uint32_t to, uint32_t off) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(to), "v"(off), "s"(r));
+}
+
+struct RingSrc {
+  const uint16_t *a_base, *b_base;   // the K range's first slab of the tile, the first K row
+  uint32_t a_bytes, b_bytes, b;      // b: bytes to the tile's first column
+  int a_rows, nk;                    // rows of A that count (nobody looks at the others); steps: even, at least 4
+};
+
+struct GemmRing {
+  static constexpr int kPer = 2;     // requests of a wave per operand and step
+  int lane, wave;
+  uint32_t lds, b_step, b_two_rows, b_lane[kPer];
+
+  // ldb: row pitch of B
+  __device__ __forceinline__ GemmRing(int64_t ldb, const uint16_t* smem) {
+    lane = threadIdx.x & 63;
+    wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    lds = __builtin_amdgcn_readfirstlane(lds_address(smem));
+    b_step = uint32_t(kStepK * ldb * 2);
+    b_two_rows = uint32_t(2 * ldb * 2);
+    // request j of wave w covers rows 4 w + 2 j and the next: lane l takes 16-byte piece l % 32 of row l / 32, whose 32-byte
+    // segments are XORed with f(row)
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+      const int row = wave * 4 + 2 * j + (lane >> 5);
+      const uint32_t f = uint32_t(row & 3) | uint32_t(row >> 3 & 1) << 2;
+      b_lane[j] = uint32_t(int64_t(lane >> 5) * ldb * 2) + (((lane & 31) >> 1) ^ f) * 32 + (lane & 1) * 16;
+    }
+  }
+
+  // Requests step kt: wave w blocks 2 w and 2 w + 1 of A and rows 4 w .. 4 w + 3 of B.
+  __device__ __forceinline__ void issue(const RingSrc& t, int kt) const {
+    const rsrc_words_t ra = rsrc_words(t.a_base, t.a_bytes), rb = rsrc_words(t.b_base, t.b_bytes);
+    const uint32_t to = lds + uint32_t(kt & (kRing - 1)) * kStepBytes + wave * (kPer * 1024);
+    // past every operand's end (which lies below 4 GiB by more than that), which gives zeros and moves nothing
+    const uint32_t a = wave * 32 < t.a_rows ? uint32_t(kt >> 1) * (kSlabElems * 2) + uint32_t(kt & 1) * 1024 + wave * 4096 : ~0u - 8191;
+    const uint32_t b = t.b + uint32_t(kt) * b_step + uint32_t(wave) * (kPer * b_two_rows);
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+      request_lds16(ra, to + j * 1024, lane * 16 + (a + j * 2048));
+      request_lds16(rb, to + kTile * kStepK * 2 + j * 1024, b_lane[j] + (b + j * b_two_rows));
+    }
+  }
+
+  // Until the wave has no more than N requests on their way and its own LDS reads are done, then the others as well.
+  template <int N> __device__ __forceinline__ void landed() const {
+    static_assert(N < 16, "four bits");
+    AERO_CFENCE();
+    __builtin_amdgcn_s_waitcnt(0x0070 | N);
+    slice_barrier();
+  }
+
+  // acc = the tile's product.  active == false: all of the wave's rows (columns) are padding, it only moves operands.
+  __device__ __forceinline__ void run(const RingSrc& t, const WavePos& pos, const uint16_t* smem, Acc& acc) const {
+    constexpr int kStep = 2 * kPer;   // requests per step
+    static_assert(kRing == 4, "the last steps below");
+    const int nk = t.nk;
+    acc_zero(acc);
+#pragma unroll
+    for (int kt = 0; kt < kRing - 1; ++kt) issue(t, kt);
+    landed<2 * kStep>();
+    if (!pos.active) {   // uniform over the wave
+      for (int kt = 0; kt < nk - 3; ++kt) {
+        issue(t, kt + 3);
+        landed<2 * kStep>();
+      }
+      landed<kStep>();
+      landed<0>();
+      return;
+    }
+    const uint32_t fa0 = lds + pos.wm * 8 * 1024 + lane * 16;
+    const FragAddr<4> fb0 = frag_addr_bt(smem + kTile * kStepK, pos.wn * 64, lane);
+    Frags a1, b_even, b_odd;   // a1, b_odd: of the step before step 0
+#pragma unroll
+    for (int i = 0; i < kFragBlocks; ++i) a1[i] = b_odd[i] = bf16x8_t{};
+    // Step kt, whose operands have landed; the order is pinned.
+    auto step = [&](int kt, Frags& b, const Frags& b_before, bool more) {
+      constexpr int kMfma = 0x008, kDsRd = 0x100;
+      const uint32_t at = uint32_t(kt & (kRing - 1)) * kStepBytes;
+      uint32_t fa = fa0 + at;
+      asm volatile("" : "+v"(fa));   // one address, the blocks in the instructions' offsets
+      FragAddr<4> fb;
+      Frags a0;
+#pragma unroll
+      for (int i = 0; i < kFragBlocks; ++i) {
+        a0[i] = lds_fragment(fa + i * 1024);
+        fb.at[i] = fb0.at[i] + at;
+      }
+      frags_load(b, fb, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      frags_mma<true>(a1, b_before, 1, acc);
+      __builtin_amdgcn_sched_barrier(0);
+      if (more) issue(t, kt + 3);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < kFragBlocks; ++i) a1[i] = lds_fragment(fa + (kFragBlocks + i) * 1024);
+      frags_mma<true>(a0, b, 0, acc);
+#pragma unroll
+      for (int r = 0; r < kFragBlocks; ++r) {
+        __builtin_amdgcn_sched_group_barrier(kMfma, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(kDsRd, 1, 0);
+      }
+      __builtin_amdgcn_sched_group_barrier(kMfma, kFragBlocks * (kNB - 1), 0);
+      __builtin_amdgcn_sched_barrier(0);   // what follows stays behind the last matrix instruction
+    };
+    __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): see GemmStream
+    int kt = 0;
+#pragma unroll 1
+    for (; kt < nk - 4; kt += 2) {
+      step(kt, b_even, b_odd, true);
+      landed<2 * kStep>();
+      step(kt + 1, b_odd, b_even, true);
+      landed<2 * kStep>();
+    }
+    step(kt, b_even, b_odd, true);
+    landed<2 * kStep>();
+    step(kt + 1, b_odd, b_even, false);
+    landed<kStep>();
+    step(kt + 2, b_even, b_odd, false);
+    landed<0>();
+    step(kt + 3, b_odd, b_even, false);
+    frags_mma<true>(a1, b_odd, 1, acc);
   }
 };
 

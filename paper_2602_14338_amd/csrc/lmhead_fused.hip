@@ -381,7 +381,7 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_fused_stats(
   const int lane = threadIdx.x & 63;
   WavePos wp = wave_pos<true>();
   const int wm = wp.wm, wn = wp.wn;
-  GemmStream<true, false, false, false, true> stream(H, kDK, H, kDK, H);
+  GemmStream<true, false, false, true> stream(H, kDK, H, kDK, H);
   auto source = [&](int tv, int tt) {
     return TileSrc{W, Hf, (int64_t(V) * H) * 2, (int64_t(n_rows) * H) * 2, uint32_t(int64_t(tv) * kTile * H * 2),
                    uint32_t(int64_t(tt) * kTile * H * 2), (H + kDK - 1) / kDK};
@@ -712,7 +712,7 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_fused_dz(
   const int n_tiles = tiles_v * tiles_t_act;
   WavePos wp = wave_pos<true>();
   const int wm = wp.wm, wn = wp.wn;
-  GemmStream<true, false, false, false, true> stream(H, kDK, H, kDK, H);
+  GemmStream<true, false, false, true> stream(H, kDK, H, kDK, H);
   auto source = [&](int tv, int tt) {
     return TileSrc{W, Hc, (int64_t(V) * H) * 2, (int64_t(n_cand) * H) * 2, uint32_t(int64_t(tv) * kTile * H * 2),
                    uint32_t(int64_t(tt) * kTile * H * 2), (H + kDK - 1) / kDK};
@@ -781,9 +781,8 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_fused_dz(
 // dh_part[s][t][h] = sum_{k in split s} X[t][k] W[k][h], X = the stored exponentials P (or dz itself on the recompute
 // route)     M = candidate tokens, N = H, K = vocabulary (padded)
 // The weight is read as the caller holds it, [V][H], and turned by the transposing LDS read.  (A copy of it in K-slabs costs a
-// pass over the weight per call, 170 us at H = 1536 and 430 at 3584 with V = 152 K, and the contraction gains at most 2 % by
-// it: copy + contraction / as it is 557 + 168 / 559 us with 2048 tokens at H = 1536, 1531 + 170 / 1550 with 6000, 3972 + 173 /
-// 4036 with 16384; 4803 + 419 / 4915 with 8192 at H = 3584, 9713 + 423 / 9550 with 16384.)
+// pass over the weight per call, 170 us at H = 1536 and 430 at 3584 with V = 152 K; with two stages of 64 the contraction gained
+// at most 2 % by it.)
 __global__ __launch_bounds__(kGemmNT, 2) void k_gemm_dh(
     const uint16_t* __restrict__ dz, const uint16_t* __restrict__ W, int V, int vK, int H, int tiles_h, int64_t T_pad,
     const int32_t* __restrict__ nact, float* __restrict__ dh_part) {
@@ -797,24 +796,19 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_gemm_dh(
   const int per = (nslices + S - 1) / S;
   WavePos wp = wave_pos<false>();
   const int wm = wp.wm, wn = wp.wn;
-  GemmStream<true, true, true, true, false> stream(kDK, kSlabElems, H, 0, 0);
+  const GemmRing ring(H, smem);
   auto source = [&](int split, int tt, int th) {
     const int k_begin = min(vK, split * per * kDK);
     const int k_len = max(0, min(vK, (split + 1) * per * kDK) - k_begin);
-    TileSrc t;
+    RingSrc t;
     t.a_base = dz + slab_offset(nslices, tt, k_begin / kDK);
-    // a wave requests 32 of the tile's rows: nothing where there is no candidate among them
-    t.a_bytes = tt * kTile + stream.wave * 32 < n_cand ? int64_t(k_len) * kTile * 2 : 0;
-    t.a = 0;
+    t.a_bytes = uint32_t(k_len) * (kTile * 2);
+    t.a_rows = n_cand - tt * kTile;   // blocks of rows without a candidate are not requested
     // weight rows past the vocabulary (the split may start there) lie past the operand's bytes and read as zeros
     t.b_base = W + int64_t(min(k_begin, V)) * H;
-    t.b_bytes = int64_t(max(V - k_begin, 0)) * H * 2;
+    t.b_bytes = uint32_t(max(min(V - k_begin, k_len), 0)) * uint32_t(H) * 2;
     t.b = uint32_t(th * kTile * 2);
-    t.nk = k_len / kDK;
-    if (t.nk == 0) {   // an empty split: one slice of nothing
-      t.nk = 1;
-      t.b_bytes = 0;
-    }
+    t.nk = max(k_len / kStepK, 4);    // steps past a short split's end are zeros
     return t;
   };
   // per-XCD contiguous order, split-major: the workgroups resident on one XCD work on the same
@@ -825,14 +819,8 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_gemm_dh(
   tile_of_index(npid % base, tiles_t, tiles_h, tt, th);
   const int m0 = tt * kTile, n0 = th * kTile;
   wp.active = m0 + wm * 128 < n_cand && n0 + wn * 64 < H;
-  wp.warm_a = warm_share(th, tiles_h);
-  wp.warm_b = warm_share(tt, tiles_t);
-  wp.warm_from = tiles_t > 1 ? INT32_MAX : kWarmSlicesAlone;   // see kWarmSlices
-  const TileSrc src = source(split, tt, th);
   Acc acc;
-  stream.start(src, smem);
-  stream.run<0>(src, no_tile(src), wp, false, smem, acc);
-  end_of_walk();
+  ring.run(source(split, tt, th), wp, smem, acc);
   if (!wp.active) return;   // padding rows of the partials are not read, columns past H do not exist
   const int lane = threadIdx.x & 63;
   float* const out = dh_part + int64_t(split) * n_pad * H;
@@ -866,7 +854,7 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_gemm_dw(
   const int K = (nact[0] + kDK - 1) / kDK * kDK;
   WavePos wp = wave_pos<true>();
   const int wm = wp.wm, wn = wp.wn;
-  GemmStream<true, true, false, true, false> stream(kDK, kSlabElems, kDK, kSlabElems, 0);
+  GemmStream<true, true, true, false> stream(kDK, kSlabElems, kDK, kSlabElems, 0);
   auto source = [&](int tv, int th) {
     const bool any = th * kTile + stream.wave * 32 < H;   // of the 32 columns that the wave requests
     return TileSrc{dzT + slab_offset(T_pad / 64, tv, 0), hTc + slab_offset(T_pad / 64, th, 0), int64_t(K) * kTile * 2,

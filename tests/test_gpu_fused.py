@@ -152,6 +152,15 @@ def test_fused_backward_weight_forms(gh, T, H, V):
     check_bwd(gh, wl, h, W, dict(reject_enable=1, posterior_mode=1), entropy_coef=0.01, dweight_dtype=torch.bfloat16)
 
 
+@pytest.mark.parametrize("T,H,V", [(5, 8, 40), (300, 264, 257), (40, 16, 600), (70, 72, 20001), (260, 1032, 9000), (520, 264, 20481)])
+def test_fused_dhidden_split_lengths(gh, T, H, V):
+    """Splits of the dhidden contraction of one slice of 64 (shorter than the loop's ring of four 32-wide steps), of a few, an odd
+    number of them, and splits that start past the vocabulary; one tile of tokens and several, ragged rows and columns."""
+    wl, h, W = make(T, H, V, sigma_w=2.0 / np.sqrt(H))
+    check_bwd(gh, wl, h, W, dict())
+    check_bwd(gh, wl, h, W, dict(reject_enable=1, posterior_mode=1), entropy_coef=0.01)
+
+
 @pytest.mark.parametrize("T,H,V", [(600, 200, 70013), (300, 1080, 33000), (513, 56, 66048), (40, 696, 65792)])
 def test_fused_workgroups_that_walk_several_tiles(gh, T, H, V):
     """More tiles than CUs in the forward and the dweight contraction, so that a workgroup takes several, with stored and
