@@ -417,6 +417,23 @@ def test_fwd_f8_shapes(gh, V, ld):
     assert check_fwd(gh, wl, offset_elems=3) == 0          # misaligned base: scalar path
 
 
+@pytest.mark.parametrize("dtype,V", [("bf16", 32776), ("bf16", 40961), ("f32", 16385), ("f32", 70003)])
+@pytest.mark.parametrize("T", [255, 256, 257])
+def test_fwd_rows_around_one_per_cu(gh, T, V, dtype):
+    """Long rows take 1024 threads each up to a row per CU, 512 beyond."""
+    rng = np.random.default_rng(T + V)
+    z = rng.normal(0, 3, size=(T, V)).astype(np.float32)
+    host = z if dtype == "f32" else ai.f32_to_bf16_bits(z)
+    tg = rng.integers(0, V, size=T).astype(np.int32)
+    tg[::7] = -1
+    ref = orc.logprob_fwd(host, dtype, V, tg)
+    lp, ent, lse, err = gh.run_fwd(gh.logits_to_dev(host, dtype), T, V, V, tg)
+    assert err == 0
+    for got, want, tol in ((lp, ref[0], LP_TOL), (ent, ref[1], ENT_TOL), (lse, ref[2], LP_TOL)):
+        g = got.cpu().numpy()
+        assert np.abs(g - want).max() <= tol and not g[tg < 0].any()
+
+
 def test_fwd_misaligned_base_and_bad_targets(gh):
     wl = ai.make_config("cfg2", V=4096, slots=6, len_lo=1, len_hi=6)
     assert check_fwd(gh, wl, offset_elems=3) == 0
