@@ -60,7 +60,10 @@ __global__ __launch_bounds__(NT) void k_row_single_pass(
   }
   const bool signal = valid && A != 0.f && w != 0.f;
   const bool bonus = ENT && valid && w != 0.f;          // entropy bonus: every token of a weighted rollout
-  const bool need = signal || bonus || (valid && stats_all);   // uniform over the workgroup
+  const bool need = (valid && stats_all) || signal || bonus;   // uniform over the workgroup
+  // asked for in front of the row: behind the row's reduction it is one more wait (8-12 us calls 0 to 3 %)
+  const float old = old_logprob[t];
+  const float ref = ENT && kl_coef != 0.f ? ref_logprob[t] : 0.f;
   const RowGeom geom = row_geom<DT>(logits, t, ld, V);
   const int nvec = geom.nvec, jr = ragged_elt<DT>(geom, V, tid);
   const char* zrow = row_ptr<DT>(logits, t, ld);
@@ -127,7 +130,7 @@ __global__ __launch_bounds__(NT) void k_row_single_pass(
   float g = 0.f, term = 0.f;
   int flag = 0;
   if (signal) {
-    const float rho = expf(lp - old_logprob[t] + own.low);
+    const float rho = expf(lp - old + own.low);
     const float lo = 1.f - eps_lo, hi = 1.f + eps_hi;
     const float clipped = fminf(fmaxf(rho, lo), hi);
     const float s = fminf(rho * A, clipped * A);
@@ -139,7 +142,7 @@ __global__ __launch_bounds__(NT) void k_row_single_pass(
   const float ent = lse - st.sz / st.s;
   // gradient row: dz_j = pi_j (a z_j + b) + g 1[j = y]; without the entropy bonus a = 0, b = -g
   if (bonus && kl_coef != 0.f) {   // Eq. 2's beta term: exp(d) - d - 1, d = log pi_ref - log pi
-    const float d = ref_logprob[t] - lp - own.low;
+    const float d = ref - lp - own.low;
     const float ed = expf(d);
     term += kl_coef * w * (ed - d - 1.f);
     g += grad_scale * kl_coef * w * (1.f - ed);
@@ -228,43 +231,65 @@ __device__ __forceinline__ RowInfo row_info(int64_t t, int64_t T, int V, int R, 
 }
 
 // order[0 .. n) = rows with need, order[T - m .. T) = the m rows that are only zero-filled, each part in
-// no particular order (wave-sized runs are placed by two atomic counters: ctr[1] from the front, ctr[2]
+// no particular order (wave-sized runs are placed by two counters: ctr[1] from the front, ctr[2]
 // from the back).  The u rows marked AERO_ROW_UNTOUCHED are placed nowhere (n + m + u = T, the gap in the
 // middle has u entries; ctr[3] counts them) and get their per-row scalars, all zero, here.
-__global__ __launch_bounds__(256) void k_row_order(int64_t T, int V, int R, const int32_t* __restrict__ targets,
-                                                   const int32_t* __restrict__ token_rollout,
-                                                   const float* __restrict__ adv, const float* __restrict__ weight,
-                                                   int stats_all, int every_weighted, int32_t* __restrict__ ctr,
-                                                   int32_t* __restrict__ order, float* __restrict__ g_out,
-                                                   float* __restrict__ term_out, int32_t* __restrict__ flag_out,
-                                                   float* __restrict__ logprob_out, float* __restrict__ entropy_out,
-                                                   float* __restrict__ lse_out) {
-  const int64_t t = int64_t(blockIdx.x) * 256 + threadIdx.x;
+// Up to kOrderRows rows (ONE) one workgroup does it, which counts in LDS and presets ctr[0], so that the launch in front that clears
+// the counters falls away: whole calls, two launches / one, 16 rows of 151936 bf16 logits 26.2 / 25.2 us, 200 32.4 / 30.9, 992 88.6 /
+// 87.2, 1984 (fp16) 160.6 / 159.6.  It is the slower way for more rows, which one workgroup takes turn by turn: 16384 1210 / 1218.
+constexpr int kOrderNT = 1024, kOrderAhead = 2;
+constexpr int64_t kOrderRows = kOrderNT * kOrderAhead;
+template <bool ONE>
+__global__ __launch_bounds__(ONE ? kOrderNT : 256) void k_row_order(
+    int64_t T, int V, int R, const int32_t* __restrict__ targets, const int32_t* __restrict__ token_rollout,
+    const float* __restrict__ adv, const float* __restrict__ weight, int stats_all, int every_weighted, int first_next,
+    int32_t* __restrict__ ctr, int32_t* __restrict__ order, float* __restrict__ g_out, float* __restrict__ term_out,
+    int32_t* __restrict__ flag_out, float* __restrict__ logprob_out, float* __restrict__ entropy_out,
+    float* __restrict__ lse_out) {
+  constexpr int NT = ONE ? kOrderNT : 256, kAhead = ONE ? kOrderAhead : 1;
+  __shared__ int32_t own[4];
   const int lane = threadIdx.x & 63;
-  const bool in = t < T;
-  const bool untouched = in && token_rollout[t] == AERO_ROW_UNTOUCHED;
-  const bool need = row_info(t, T, V, R, targets, token_rollout, adv, weight, stats_all, every_weighted != 0).need;
-  const uint64_t m_need = __ballot(in && need), m_rest = __ballot(in && !need && !untouched);
-  const uint64_t m_unt = __ballot(untouched);
-  const uint64_t below = (uint64_t(1) << lane) - 1;
-  int base_need = 0, base_rest = 0;
-  if (lane == 0) {
-    if (m_need) base_need = atomicAdd(ctr + 1, __popcll(m_need));
-    if (m_rest) base_rest = atomicAdd(ctr + 2, __popcll(m_rest));
-    if (m_unt) atomicAdd(ctr + 3, __popcll(m_unt));
+  if constexpr (ONE) {
+    if (threadIdx.x < 4) own[threadIdx.x] = threadIdx.x == 0 ? first_next : 0;
+    __syncthreads();
   }
-  if (untouched) {
-    g_out[t] = 0.f;
-    term_out[t] = 0.f;
-    flag_out[t] = 0;
-    if (logprob_out) logprob_out[t] = 0.f;
-    if (entropy_out) entropy_out[t] = 0.f;
-    if (lse_out) lse_out[t] = 0.f;
+  int32_t* const count = ONE ? own : ctr;
+  bool untouched[kAhead], need[kAhead];
+#pragma unroll
+  for (int u = 0; u < kAhead; ++u) {
+    const int64_t t = (int64_t(blockIdx.x) * kAhead + u) * NT + threadIdx.x;
+    untouched[u] = t < T && token_rollout[t] == AERO_ROW_UNTOUCHED;
+    need[u] = row_info(t, T, V, R, targets, token_rollout, adv, weight, stats_all, every_weighted != 0).need;
   }
-  base_need = __shfl(base_need, 0, kWave);
-  base_rest = __shfl(base_rest, 0, kWave);
-  if (in && need) order[base_need + __popcll(m_need & below)] = int32_t(t);
-  if (in && !need && !untouched) order[T - 1 - (base_rest + __popcll(m_rest & below))] = int32_t(t);
+#pragma unroll
+  for (int u = 0; u < kAhead; ++u) {
+    const int64_t t = (int64_t(blockIdx.x) * kAhead + u) * NT + threadIdx.x;
+    const bool rest = t < T && !need[u] && !untouched[u];
+    const uint64_t m_need = __ballot(need[u]), m_rest = __ballot(rest), m_unt = __ballot(untouched[u]);
+    const uint64_t below = (uint64_t(1) << lane) - 1;
+    int base_need = 0, base_rest = 0;
+    if (lane == 0) {
+      if (m_need) base_need = atomicAdd(count + 1, __popcll(m_need));
+      if (m_rest) base_rest = atomicAdd(count + 2, __popcll(m_rest));
+      if (m_unt) atomicAdd(count + 3, __popcll(m_unt));
+    }
+    if (untouched[u]) {
+      g_out[t] = 0.f;
+      term_out[t] = 0.f;
+      flag_out[t] = 0;
+      if (logprob_out) logprob_out[t] = 0.f;
+      if (entropy_out) entropy_out[t] = 0.f;
+      if (lse_out) lse_out[t] = 0.f;
+    }
+    base_need = __shfl(base_need, 0, kWave);
+    base_rest = __shfl(base_rest, 0, kWave);
+    if (need[u]) order[base_need + __popcll(m_need & below)] = int32_t(t);
+    if (rest) order[T - 1 - (base_rest + __popcll(m_rest & below))] = int32_t(t);
+  }
+  if constexpr (ONE) {
+    __syncthreads();
+    if (threadIdx.x < 4) ctr[threadIdx.x] = own[threadIdx.x];
+  }
 }
 
 constexpr int kTailAhead = 4;
@@ -505,7 +530,7 @@ __global__ __launch_bounds__(kSpNT) void k_row_stream(
 }
 
 // ctr[0]: row counter of k_row_stream (starts past the rows assigned by workgroup id),
-// ctr[1], ctr[2]: fill counters of k_row_order, ctr[3]: its count of untouched rows
+// ctr[1], ctr[2]: fill counters of k_row_order<false>, ctr[3]: its count of untouched rows
 __global__ void k_set_counter(int32_t* ctr, int32_t v) {
   ctr[0] = v;
   ctr[1] = 0;
@@ -624,9 +649,11 @@ static aero_status single_pass_launch_t(const RowArgs& r, int32_t* row_counter, 
                                                     : k_row_stream<DT, kStreamVecs, NL, ENT, true>;
     const int cus = compute_units();
     const unsigned grid = unsigned(r.T < cus ? r.T : cus);   // one persistent workgroup per CU
-    hipLaunchKernelGGL(k_set_counter, dim3(1), dim3(1), 0, s, row_counter, int32_t(grid));
-    hipLaunchKernelGGL(k_row_order, dim3(unsigned((r.T + 255) / 256)), dim3(256), 0, s, r.T, r.V, r.R, r.targets,
-                       r.token_rollout, r.adv, r.weight, r.stats_all, ENT ? 1 : 0, row_counter, row_order, r.g, r.term,
+    const bool one = r.T <= kOrderRows;
+    if (!one) hipLaunchKernelGGL(k_set_counter, dim3(1), dim3(1), 0, s, row_counter, int32_t(grid));
+    const auto order = one ? k_row_order<true> : k_row_order<false>;
+    hipLaunchKernelGGL(order, dim3(one ? 1u : unsigned((r.T + 255) / 256)), dim3(one ? kOrderNT : 256), 0, s, r.T, r.V, r.R, r.targets,
+                       r.token_rollout, r.adv, r.weight, r.stats_all, ENT ? 1 : 0, int(grid), row_counter, row_order, r.g, r.term,
                        r.flag, r.logprob_out, r.entropy_out, r.lse_out);
     hipLaunchKernelGGL(kernel, dim3(grid), dim3(kSpNT), kLdsBytes, s, r.logits, r.T, r.V, r.ld, r.targets,
                        r.old_logprob, r.token_rollout, r.adv, r.weight, r.R, r.eps_lo, r.eps_hi, r.grad_scale, r.ent_coef,

@@ -891,6 +891,7 @@ def test_streaming_kernel_optional_terms_several_rows_per_workgroup(gh):
 @pytest.mark.parametrize("inplace,terms", [(False, False), (True, True), (True, False), (False, True)])
 @pytest.mark.parametrize("dtype,V,ld,T", [("bf16", 70003, 70005, 624), ("f16", 65549, 65551, 2496), ("f32", 32777, 32779, 2496),
                                           ("f8e4m3", 230001, 230003, 1456),
+                                          ("bf16", 66003, 66005, 2048), ("bf16", 66003, 66005, 2049),   # the order's one workgroup, several
                                           ("bf16", 164003, 164005, 832), ("f32", 110001, 110003, 624),
                                           ("f8e4m3", 1300001, 1300003, 416)])   # held in part
 def test_streaming_rows_of_changing_alignment(gh, dtype, V, ld, T, inplace, terms):
