@@ -142,33 +142,65 @@ __device__ __forceinline__ int dh_splits(int active_tiles, int tiles_h, int grid
 //   exponential left its safe range (see k_fused_stats), nact[3] the split count of the dhidden contraction.
 // token_rollout == null (forward-only call): no candidates, pos / nact are not written.
 // Ignored rows get their zero outputs here; a target >= V or a rollout index >= R raises its device error bit.
+template <int kAhead>
 __global__ __launch_bounds__(1024) void k_compact_valid(
     const int32_t* __restrict__ targets, int64_t T, int64_t T_pad, int V, const int32_t* __restrict__ token_rollout,
     const float* __restrict__ adv, const float* __restrict__ weight, int R, int every_weighted,
     int32_t* __restrict__ fidx, int32_t* __restrict__ nf, int32_t* __restrict__ pos, int32_t* __restrict__ nact,
     float* __restrict__ logprob, float* __restrict__ entropy, float* __restrict__ lse_out,
     int32_t* __restrict__ err_flag, int tiles_h, int dh_grid, int slices, int64_t rows_max) {
-  // each of the 16 waves owns one contiguous range of rows and walks it 64 rows at a time (coalesced
-  // reads, ballot + popcount inside the wave): count, exchange the 16 counts, then place
+  // Each of the 16 waves owns one contiguous range of rows, 64 at a time (coalesced reads, ballot + popcount inside the
+  // wave): count, exchange the 16 counts, then place.  Latency bound: the loads of kAhead steps go out together, those that need
+  // another's answer from clamped positions so that no branch stands between them, and the first kKept steps' classes stay in
+  // a register for the second time.  (Steps one by one, their loads one behind the other and all of it twice / this way: 600 rows 4.2 / 3.5 us,
+  // 2048 6.2 / 5.3, 4096 9.9 / 5.8, 8192 17.0 / 8.4, 16384 31.8 / 14.0, 32768 64.3 / 25.3, 40000 96.2 / 34.9; eight or sixteen steps at a
+  // time 13.7 and 14.4 for 16384: the code, which comes from memory once per launch, grows with them.)
+  constexpr int kKept = 32;
+  static_assert(kKept % kAhead == 0, "whole blocks of steps");
   __shared__ int wsum_c[16], wsum_o[16];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int64_t seg = ((T + 15) / 16 + 63) / 64 * 64;
   const int64_t lo = min(T, wave * seg), hi = min(T, lo + seg);
   const uint64_t below = (uint64_t(1) << lane) - 1;
-  // class of row t: 0 = no target, 1 = target only, 2 = candidate
-  auto row_class = [&](int64_t t) -> int {
-    if (unsigned(targets[t]) >= unsigned(V)) return 0;
-    if (!token_rollout) return 1;
-    const int i = token_rollout[t];
-    if (i < 0 || i >= R) return 1;
-    return (weight[i] != 0.f && (every_weighted || adv[i] != 0.f)) ? 2 : 1;
+  bool bad_y = false, bad_i = false;
+  // classes of the rows lo + 64 (it + u) + lane: 0 = no target, 1 = target only, 2 = candidate
+  auto classes = [&](int it, int (&cls)[kAhead]) {
+    int y[kAhead], i[kAhead];
+    float w[kAhead], A[kAhead];
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      const int64_t t = min(lo + int64_t(it + u) * 64 + lane, T - 1);
+      y[u] = targets[t];
+      i[u] = token_rollout ? token_rollout[t] : -1;
+    }
+    const bool rollouts = token_rollout && R > 0;   // uniform
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      const int at = min(max(i[u], 0), R - 1);
+      w[u] = rollouts ? weight[at] : 0.f;
+      A[u] = rollouts ? adv[at] : 0.f;
+    }
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      const bool in = lo + int64_t(it + u) * 64 + lane < hi, target = in && unsigned(y[u]) < unsigned(V);
+      const bool rollout = i[u] >= 0 && i[u] < R;
+      cls[u] = !target ? 0 : rollout && w[u] != 0.f && (every_weighted || A[u] != 0.f) ? 2 : 1;
+      bad_y |= in && y[u] >= V;
+      bad_i |= in && y[u] >= 0 && i[u] >= R;
+    }
   };
+  const int steps = int((hi - lo + 63) / 64);
+  uint64_t kept = 0;
   int cnt_c = 0, cnt_o = 0;
-  for (int64_t t0 = lo; t0 < hi; t0 += 64) {
-    const int64_t t = t0 + lane;
-    const int cls = t < hi ? row_class(t) : 0;
-    cnt_c += __popcll(__ballot(cls == 2));
-    cnt_o += __popcll(__ballot(cls == 1));
+  for (int it = 0; it < steps; it += kAhead) {
+    int cls[kAhead];
+    classes(it, cls);
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      cnt_c += __popcll(__ballot(cls[u] == 2));
+      cnt_o += __popcll(__ballot(cls[u] == 1));
+      if (it < kKept) kept |= uint64_t(cls[u]) << (2 * (it + u));
+    }
   }
   if (lane == 0) {
     wsum_c[wave] = cnt_c;
@@ -185,28 +217,34 @@ __global__ __launch_bounds__(1024) void k_compact_valid(
   }
   run_o += total_c;   // the other rows follow the candidates
   const int total = total_c + total_o;
-  bool bad_y = false, bad_i = false;
-  for (int64_t t0 = lo; t0 < hi; t0 += 64) {
-    const int64_t t = t0 + lane;
-    const bool in = t < hi;
-    const int cls = in ? row_class(t) : 0;
-    const uint64_t m_c = __ballot(cls == 2), m_o = __ballot(cls == 1);
-    int at = -1;
-    if (cls == 2) {
-      at = run_c + __popcll(m_c & below);
-      fidx[at] = int(t);
-    } else if (cls == 1) {
-      fidx[run_o + __popcll(m_o & below)] = int(t);
-    } else if (in) {
-      logprob[t] = 0.f;
-      lse_out[t] = 0.f;
-      if (entropy) entropy[t] = 0.f;
-      bad_y |= targets[t] >= V;
+  for (int it = 0; it < steps; it += kAhead) {
+    int cls[kAhead];
+    if (it < kKept) {   // uniform
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) cls[u] = int(kept >> (2 * (it + u))) & 3;
+    } else {
+      classes(it, cls);
     }
-    if (in && token_rollout) bad_i |= targets[t] >= 0 && token_rollout[t] >= R;
-    if (in && pos) pos[t] = at;
-    run_c += __popcll(m_c);
-    run_o += __popcll(m_o);
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      const int64_t t = lo + int64_t(it + u) * 64 + lane;
+      const bool in = t < hi;
+      const uint64_t m_c = __ballot(cls[u] == 2), m_o = __ballot(cls[u] == 1);
+      int at = -1;
+      if (cls[u] == 2) {
+        at = run_c + __popcll(m_c & below);
+        fidx[at] = int(t);
+      } else if (cls[u] == 1) {
+        fidx[run_o + __popcll(m_o & below)] = int(t);
+      } else if (in) {
+        logprob[t] = 0.f;
+        lse_out[t] = 0.f;
+        if (entropy) entropy[t] = 0.f;
+      }
+      if (in && pos) pos[t] = at;
+      run_c += __popcll(m_c);
+      run_o += __popcll(m_o);
+    }
   }
   if ((bad_y || bad_i) && err_flag)
     atomicOr(err_flag, (bad_y ? AERO_DERR_BAD_TARGET : 0) | (bad_i ? AERO_DERR_BAD_ROLLOUT : 0));
@@ -1078,8 +1116,9 @@ extern "C" aero_status aero_lmhead_logprob_fused(
                        reinterpret_cast<float*>(ws + p.off_gc), reinterpret_cast<float*>(ws + p.off_lsec),
                        reinterpret_cast<int32_t*>(ws + p.off_yc), reinterpret_cast<float*>(ws + p.off_ac),
                        reinterpret_cast<float*>(ws + p.off_bc), reinterpret_cast<float*>(ws + p.off_scale), dz, dzT};
+  const auto compact = T <= 2048 ? k_compact_valid<1> : k_compact_valid<4>;   // steps of 1024 rows at a time
   if (T > 0) {
-    hipLaunchKernelGGL(k_compact_valid, dim3(1), dim3(1024), 0, s, targets, T, p.T_pad, V,
+    hipLaunchKernelGGL(compact, dim3(1), dim3(1024), 0, s, targets, T, p.T_pad, V,
                        bwd ? token_rollout : nullptr, adv, weight_rollout, R, (ent || kl_coef != 0.f) ? 1 : 0, fidx, nf,
                        bwd ? pos : nullptr, bwd ? nact : nullptr, logprob, entropy, lse, err_flag, tiles_h, grid_dh,
                        p.V_ld / kDK, rows_max);
@@ -1106,7 +1145,7 @@ extern "C" aero_status aero_lmhead_logprob_fused(
   uint16_t* hTc = reinterpret_cast<uint16_t*>(ws + p.off_hTc);
   float* dh_acc = reinterpret_cast<float*>(ws + p.off_dhacc);
   if (T == 0) {   // no forward kernel ran: an empty candidate set for the kernels below
-    hipLaunchKernelGGL(k_compact_valid, dim3(1), dim3(1024), 0, s, targets, T, p.T_pad, V, token_rollout, adv,
+    hipLaunchKernelGGL(compact, dim3(1), dim3(1024), 0, s, targets, T, p.T_pad, V, token_rollout, adv,
                        weight_rollout, R, 0, fidx, nf, pos, nact, logprob, entropy, lse, err_flag, tiles_h, grid_dh,
                        p.V_ld / kDK, rows_max);
     hipLaunchKernelGGL(k_fused_rows<16>, dim3(unsigned(p.T_pad / 16)), dim3(kRowsNT), 0, s, p.tiles_v, p.T_pad, fidx, nf,

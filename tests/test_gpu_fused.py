@@ -161,6 +161,18 @@ def test_fused_dhidden_split_lengths(gh, T, H, V):
     check_bwd(gh, wl, h, W, dict(reject_enable=1, posterior_mode=1), entropy_coef=0.01)
 
 
+@pytest.mark.parametrize("T", [2048, 2049, 8193, 33793])
+def test_fused_compaction_steps(gh, T):
+    """Around the row counts at which the compaction takes several steps at a time, and past the 32 steps whose classes it
+    remembers; rows without a target, without a rollout and of rollouts without advantage among them."""
+    wl, h, W = make(T, 8, 40, sigma_w=1.0, Q=60, len_hi=T // 200)
+    rng = np.random.default_rng(T)
+    wl.targets = np.where(rng.random(T) < 0.1, -1, wl.targets).astype(np.int32)
+    wl.token_rollout = np.where(rng.random(T) < 0.1, -1, wl.token_rollout).astype(np.int32)
+    ref, _ = check_bwd(gh, wl, h, W, dict())
+    assert (ref["g"] != 0).any()
+
+
 @pytest.mark.parametrize("T,H,V", [(600, 200, 70013), (300, 1080, 33000), (513, 56, 66048), (40, 696, 65792)])
 def test_fused_workgroups_that_walk_several_tiles(gh, T, H, V):
     """More tiles than CUs in the forward and the dweight contraction, so that a workgroup takes several, with stored and
