@@ -29,6 +29,7 @@
 // whose rows are the contraction index and which a transposing LDS read turns.  In all but k_gemm_dh (whose split count
 // fills the CUs once or twice), the longer k_gemm_dw (kDwTileRows) and forward tiles of many slices (kForwardTileSlices) a workgroup
 // per CU walks the tiles.
+#include <algorithm>
 #include <mutex>
 
 #include "gemm_tile.h"
@@ -881,22 +882,41 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_gemm_dh(
 // host knows the rows, not how many are candidates.
 constexpr int64_t kDwTileRows = 8192;
 
+// A gradient of few tiles leaves CUs idle however many tokens there are: up to kDwSplitTiles tiles the candidates' range is
+// split, each part leaves its sums in fp32 where the dhidden partials were (after k_scatter_dh), and k_sum_dw adds them up in
+// order.  It costs a launch and the parts' way to memory and back, so that the more tiles there are (and so the fewer parts), the more
+// rows it takes to pay: kDwSplitRows, and kDwSplitRowsPerTile for each tile.  Whole calls, one range / split, every row valid, by tiles: 16
+// (H = 64, V = 4000) 1500 rows 80.8 / 74.2 us, 4000 117 / 83, 16000 354 / 179; 32 (256, 8000) 1024 93.7 / 98.6, 1500 105 / 98, 16000 520 / 340; 57
+// (640, 4753) 1500 112.6 / 110.4, 2500 129 / 119, 16000 502 / 360; 72 (424, 9000) 1500 103.7 / 104.6, 2500 142 / 134, 16000 576 / 453; 125 (208,
+// 32000) 2500 193 / 198, 4000 277 / 275, 16000 912 / 844; 128 (896, 8000) 2500 171 / 174, 4000 209 / 202, 16000 698 / 632.
+constexpr int kDwSplitTiles = 128, kDwSplitMax = 16, kDwSplitSlices = 8;
+constexpr int64_t kDwSplitRows = 1280, kDwSplitRowsPerTile = 32;
+// So many parts are taken (device side): each has at least kDwSplitSlices slices, but for the last.
+__device__ __forceinline__ int dw_splits(int most, int n_cand) {
+  return max(min(most, (n_cand + kDK - 1) / kDK / kDwSplitSlices), 1);
+}
+
 // dW[m][h] = sum_t XT[m][t] hTc[h][t], hTc = the candidates' hidden rows times their scale     M = V, N = H, K = candidate tokens (padded)
 template <bool OUT_BF16, bool ACC>
 __global__ __launch_bounds__(kGemmNT, 2) void k_gemm_dw(
     const uint16_t* __restrict__ dzT, const uint16_t* __restrict__ hTc, int V, int H,
-    int tile0, int n_tiles, int tiles_v, int tiles_h, int64_t T_pad, const int32_t* __restrict__ nact, int vec, void* dW) {
+    int tile0, int n_tiles, int tiles_v, int tiles_h, int64_t T_pad, const int32_t* __restrict__ nact, int vec, int most, void* dW) {
   extern __shared__ __align__(16) uint16_t smem[];
   // the contraction ends with the slice of the last candidate, not with its tile: the positions behind it are zeros
   // (whole calls at H = 1536, V = 151936: 600 tokens 949 -> 905 us, 1100 tokens 1376 -> 1357, 16384 tokens -0.4 %)
-  const int K = (nact[0] + kDK - 1) / kDK * kDK;
+  const int slices = (nact[0] + kDK - 1) / kDK;
+  // split (most > 1): the parts are further rows of tiles, part by part; tv counts through them
+  const int parts = most > 1 ? dw_splits(most, nact[0]) : 1, per = (slices + parts - 1) / parts;
+  if (most > 1) n_tiles = parts * tiles_v * tiles_h;
   WavePos wp = wave_pos<true>();
   const int wm = wp.wm, wn = wp.wn;
   GemmStream<true, true, true, false> stream(kDK, kSlabElems, kDK, kSlabElems, 0);
   auto source = [&](int tv, int th) {
     const bool any = th * kTile + stream.wave * 32 < H;   // of the 32 columns that the wave requests
-    return TileSrc{dzT + slab_offset(T_pad / 64, tv, 0), hTc + slab_offset(T_pad / 64, th, 0), int64_t(K) * kTile * 2,
-                   any ? int64_t(K) * kTile * 2 : 0, 0u, 0u, max(K / kDK, 1)};   // no candidates: one slice of nothing
+    const int part = most > 1 ? tv / tiles_v : 0, begin = part * per, n = max(min(per, slices - begin), 0);
+    if (most > 1) tv -= part * tiles_v;
+    return TileSrc{dzT + slab_offset(T_pad / 64, tv, begin), hTc + slab_offset(T_pad / 64, th, begin), int64_t(n) * kSlabElems * 2,
+                   any ? int64_t(n) * kSlabElems * 2 : 0, 0u, 0u, max(n, 1)};   // no candidates: one slice of nothing
   };
   // accumulate (uniform): the tile is added to what the caller's buffer holds (gradient accumulation over
   // micro-batches).  vec (uniform): that buffer is 16-byte aligned, as every allocation is.  Plain stores: an
@@ -906,18 +926,19 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_gemm_dw(
   // 1660 us per 1536 tiles with 16384 in fp32).
   constexpr int kDT = OUT_BF16 ? kBF16 : kF32;
   int pid = blockIdx.x, tv, th;
-  bool more = tile_of_step(pid, tiles_v, tiles_h, tile0, n_tiles, tv, th), stored = false;
+  bool more = tile_of_step(pid, parts * tiles_v, tiles_h, tile0, n_tiles, tv, th), stored = false;
   if (!more) return;
   TileSrc src = source(tv, th);
   stream.start(src, smem);
   while (more) {
-    const int m0 = tv * kTile, n0 = th * kTile;
+    const int part = most > 1 ? tv / tiles_v : 0;
+    const int m0 = (tv - part * tiles_v) * kTile, n0 = th * kTile;
     wp.active = n0 + wn * 64 < H;
     wp.warm_a = warm_share(th, tiles_h);
     wp.warm_b = warm_share(tv, tiles_v);
     wp.warm_from = kWarmSlices;
     pid += gridDim.x;
-    more = tile_of_step(pid, tiles_v, tiles_h, tile0, n_tiles, tv, th);
+    more = tile_of_step(pid, parts * tiles_v, tiles_h, tile0, n_tiles, tv, th);
     const TileSrc next = more ? source(tv, th) : no_tile(src);
     Acc acc;
     stream.template run<OUT_BF16 ? kMB * kNB / 2 : kMB * kNB>(src, next, wp, stored, smem, acc);
@@ -927,7 +948,7 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_gemm_dw(
 #pragma unroll
     for (int mb = 0; mb < kMB; ++mb) {
       const int row = m0 + acc_row_swapped(wm, mb, lane);
-      const int64_t row_off = int64_t(row) * H;
+      const int64_t row_off = (int64_t(part) * V + row) * H;
       const bool row_in = row < V;
       if (!vec) {
 #pragma unroll
@@ -977,6 +998,46 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_gemm_dw(
     }
   }
   end_of_walk();
+}
+
+// dweight from its parts: [parts][V][H] fp32, added up in order, eight entries (n of them) a thread.
+template <bool OUT_BF16, bool ACC>
+__global__ __launch_bounds__(256) void k_sum_dw(const float* __restrict__ part, const int32_t* __restrict__ nact, int most,
+                                                int64_t n, int vec, void* dW) {
+  constexpr int kDT = OUT_BF16 ? kBF16 : kF32;
+  const int parts = dw_splits(most, nact[0]);
+  const int64_t at = (int64_t(blockIdx.x) * 256 + threadIdx.x) * 8;
+  if (at >= n) return;
+  f32x4_t lo = {0.f, 0.f, 0.f, 0.f}, hi = lo;
+#pragma unroll 4
+  for (int p = 0; p < parts; ++p) {
+    const f32x4_t* const src = reinterpret_cast<const f32x4_t*>(part + p * n + at);
+    lo += src[0];
+    hi += src[1];
+  }
+  float x[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+  if (!vec) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) store_elt<kDT>(dW, at + e, x[e] + (ACC ? load_elt<kDT>(dW, at + e) : 0.f));
+    return;
+  }
+  u32x4_t* const out = reinterpret_cast<u32x4_t*>(reinterpret_cast<char*>(dW) + at * Storage<kDT>::kBytes);
+  if constexpr (OUT_BF16) {
+    if constexpr (ACC) {
+      float old[8];
+      unpack8(out[0], old);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) x[e] += old[e];
+    }
+    out[0] = pack_vec<kBF16>(x);
+  } else {
+    if constexpr (ACC) {
+      lo += *reinterpret_cast<const f32x4_t*>(out);
+      hi += *reinterpret_cast<const f32x4_t*>(out + 1);
+    }
+    *reinterpret_cast<f32x4_t*>(out) = lo;
+    *reinterpret_cast<f32x4_t*>(out + 1) = hi;
+  }
 }
 
 // dhidden[t] = bf16(scale[pos[t]] * sum over the split-K partials of row pos[t]) or +0.  One workgroup per
@@ -1171,6 +1232,8 @@ extern "C" aero_status aero_lmhead_logprob_fused(
     hipLaunchKernelGGL(k_gemm_dh, dim3(unsigned(grid_dh)), dim3(kGemmNT), kGemmLdsBytes, s, dz, Wp, V, p.V_ld, H, tiles_h, p.T_pad,
                        nact, dh_acc);
   }
+  if (T > 0)
+    hipLaunchKernelGGL(k_scatter_dh, dim3(unsigned(T)), dim3(256), 0, s, dh_acc, pos, nact, H, terms.scale, reinterpret_cast<uint16_t*>(dhidden));
   // dweight: one launch where a workgroup walks; where it has one tile, eight rounds of tiles a launch, so that the workgroups
   // that share operand slices stay close along K (32768 tokens at H = 3584, V = 152064, whole call: one launch 67.1, 16 rounds
   // 66.7, eight 66.1, four 66.8 ms; 16384 at H = 1536 even)
@@ -1179,14 +1242,25 @@ extern "C" aero_status aero_lmhead_logprob_fused(
     const int vec_dw = reinterpret_cast<uintptr_t>(dweight) % 16 == 0;   // rows are multiples of 16 bytes
     const auto kernel = dweight_dtype == AERO_BF16 ? (accumulate ? k_gemm_dw<true, true> : k_gemm_dw<true, false>)
                                                    : (accumulate ? k_gemm_dw<false, true> : k_gemm_dw<false, false>);
+    int most = 1;
+    if (total <= kDwSplitTiles && T >= std::max(kDwSplitRows, kDwSplitRowsPerTile * total))   // no more than the partials' buffer holds
+      most = int(std::min<int64_t>(std::min(cus / total, kDwSplitMax), dh_part_rows(p.T_pad, H, p.V_ld) / V));
+    if (most > 1) {
+      const dim3 grid = walkers(xcd_grid(most * total));
+      hipLaunchKernelGGL((k_gemm_dw<false, false>), grid, dim3(kGemmNT), kGemmLdsBytes, s, dzT, hTc, V, H, 0, most * total, p.tiles_v, tiles_h,
+                         p.T_pad, nact, 1, most, dh_acc);
+      const auto sum = dweight_dtype == AERO_BF16 ? (accumulate ? k_sum_dw<true, true> : k_sum_dw<true, false>)
+                                                  : (accumulate ? k_sum_dw<false, true> : k_sum_dw<false, false>);
+      const int64_t n = int64_t(V) * H;
+      hipLaunchKernelGGL(sum, dim3(unsigned((n / 8 + 255) / 256)), dim3(256), 0, s, dh_acc, nact, most, n, vec_dw, dweight);
+      return launch_status();
+    }
     for (int t0 = 0; t0 < total; t0 += per) {
       const int n = total - t0 < per ? total - t0 : per;
       const dim3 grid = p.T_pad < kDwTileRows ? walkers(xcd_grid(n)) : dim3(unsigned(xcd_grid(n)));
       hipLaunchKernelGGL(kernel, grid, dim3(kGemmNT), kGemmLdsBytes, s, dzT, hTc, V, H, t0, n,
-                         p.tiles_v, tiles_h, p.T_pad, nact, vec_dw, dweight);
+                         p.tiles_v, tiles_h, p.T_pad, nact, vec_dw, 1, dweight);
     }
   }
-  if (T > 0)
-    hipLaunchKernelGGL(k_scatter_dh, dim3(unsigned(T)), dim3(256), 0, s, dh_acc, pos, nact, H, terms.scale, reinterpret_cast<uint16_t*>(dhidden));
   return launch_status();
 }

@@ -161,6 +161,63 @@ def test_fused_dhidden_split_lengths(gh, T, H, V):
     check_bwd(gh, wl, h, W, dict(reject_enable=1, posterior_mode=1), entropy_coef=0.01)
 
 
+@pytest.mark.parametrize("accumulate", [False, True])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("T,H,V,off", [(1280, 64, 300, 0), (1300, 264, 1001, 1), (4400, 264, 5000, 0), (9000, 40, 77, 1)])
+def test_fused_dweight_of_few_tiles(gh, T, H, V, off, dtype, accumulate):
+    """Split over the candidates' range: parts of 8 slices and more, the last one shorter, one part only; a buffer off the 16-byte
+    grid; added to what it holds.  Against the checker, with the bound of the other gradient tests: an entry's error is that of its
+    operands' rounding (2^-9 relative each, uncorrelated), 0.23-0.28 % of the row's largest entry in the median row and up to 0.70 % of
+    it over 5000 rows of 264.  (Rows of 24 entries have a smaller largest one: over 32700 of them the tail touches the bound, 1.00 %, with
+    one range as with two, so that the shape with the most tiles is left to the comparison of the two in test_fused_dweight_parts_add_up.)"""
+    wl, h, W = make(T, H, V, sigma_w=2.0 / np.sqrt(H), Q=60, len_hi=max(2, T // 200))
+    ga = orc.group_advantage(wl.rewards, wl.lengths, wl.group_offsets, wl.keep_priority, AdvParams())
+    fwd = orc.lmhead_fused(h, W, wl.targets)
+    old = ai.draw_old_logprob(fwd["logprob"], wl.seed, sigma=0.3)
+    a32, w32 = ga["adv"].astype(np.float32), ga["weight"].astype(np.float32)
+    ref = orc.lmhead_fused(h, W, wl.targets, old, wl.token_rollout, a32, w32, np.float32(0.2), np.float32(0.2), 1.0)["dweight"]
+    buf = torch.full((V * H + 8,), 7.0, dtype=dtype, device=gh.DEV)
+    into = buf[off:off + V * H].view(V, H)
+    start = np.abs(ref).max()
+    into.copy_(torch.full((V, H), float(start), device=gh.DEV))
+    out = run_fused(gh, wl, h, W, wl.targets, bwd=dict(old=old, adv=a32, weight=w32), dweight_dtype=dtype, dw_into=into,
+                    accumulate=accumulate)
+    assert out["err"] == 0
+    got = into.float().cpu().numpy().astype(np.float64)
+    want = ref + float(into.new_tensor(float(start)).float()) if accumulate else ref
+    # the row bound of the gradient itself, and the rounding of the stored sum on top
+    scale = np.abs(ref).max(axis=1, keepdims=True)
+    stored = (2.0 ** -8 if dtype == torch.bfloat16 else 2.0 ** -23) * np.abs(want)
+    assert (np.abs(got - want) <= 1e-2 * scale + stored + 1e-30).all()
+    rest = buf.float().cpu()
+    assert (rest[:off] == 7.0).all() and (rest[off + V * H:] == 7.0).all()
+
+
+@pytest.mark.parametrize("T,H,V", [(4400, 24, 32700), (4400, 264, 16129), (2100, 8, 4097)])
+def test_fused_dweight_parts_add_up(gh, T, H, V):
+    """The most tiles that are split: the whole call against its tokens in calls of 900, which are not split, added up in one fp32
+    buffer.  The operands are the same but for the scales of the hidden rows, which differ by the order in which a token's statistics are
+    merged (calls of more than 4096 rows take another one): an ulp in fp32, and so here and there the next bf16 value, 2^-8 of one
+    term.  If every term differed by that the sums would by 2^-8 of their norm; a part that is lost, doubled or in the wrong place
+    differs by its whole size."""
+    wl, h, W = make(T, H, V, sigma_w=2.0 / np.sqrt(H), Q=60, len_hi=max(2, T // 200))
+    ga = orc.group_advantage(wl.rewards, wl.lengths, wl.group_offsets, wl.keep_priority, AdvParams())
+    lp = run_fused(gh, wl, h, W, wl.targets)["logprob"].cpu().numpy()
+    old = lp + np.random.default_rng(5).normal(0, 0.1, size=T).astype(np.float32)
+    bwd = dict(old=old, adv=ga["adv"].astype(np.float32), weight=ga["weight"].astype(np.float32))
+    whole = run_fused(gh, wl, h, W, wl.targets, bwd=bwd)["dweight"]
+    parts = torch.zeros_like(whole)
+    import copy
+    for a in range(0, T, 900):
+        part = copy.copy(wl)
+        part.T, part.token_rollout = min(900, T - a), wl.token_rollout[a:a + 900]
+        run_fused(gh, part, h[a:a + 900], W, wl.targets[a:a + 900], bwd=dict(bwd, old=old[a:a + 900]), dw_into=parts)
+    diff = (whole - parts).double()
+    for tile in range(0, V, 256):   # tile by tile
+        assert diff[tile:tile + 256].norm() <= 2.0 ** -8 * parts[tile:tile + 256].double().norm()
+    assert (whole != 0).any()
+
+
 @pytest.mark.parametrize("T", [2048, 2049, 8193, 33793])
 def test_fused_compaction_steps(gh, T):
     """Around the row counts at which the compaction takes several steps at a time, and past the 32 steps whose classes it
