@@ -822,16 +822,15 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_fused_dz(
 // The weight is read as the caller holds it, [V][H], and turned by the transposing LDS read.  (A copy of it in K-slabs costs a
 // pass over the weight per call, 170 us at H = 1536 and 430 at 3584 with V = 152 K; with two stages of 64 the contraction gained
 // at most 2 % by it.)
-__global__ __launch_bounds__(kGemmNT, 2) void k_gemm_dh(
-    const uint16_t* __restrict__ dz, const uint16_t* __restrict__ W, int V, int vK, int H, int tiles_h, int64_t T_pad,
-    const int32_t* __restrict__ nact, float* __restrict__ dh_part) {
-  extern __shared__ __align__(16) uint16_t smem[];
+__device__ __forceinline__ void dh_tile(int block, uint16_t* smem, const uint16_t* __restrict__ dz, const uint16_t* __restrict__ W,
+                                        int V, int vK, int H, int tiles_h, const int32_t* __restrict__ nact,
+                                        float* __restrict__ dh_part) {
   const int n_pad = nact[1], n_cand = nact[0];
   const int tiles_t = n_pad / kTile;
   const int nslices = vK / kDK;
   const int S = nact[3];
   const int base = tiles_t * tiles_h, n = base * S;
-  if (int(blockIdx.x) >= n) return;   // uniform over the workgroup
+  if (block >= n) return;   // uniform over the workgroup
   const int per = (nslices + S - 1) / S;
   WavePos wp = wave_pos<false>();
   const int wm = wp.wm, wn = wp.wn;
@@ -852,7 +851,7 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_gemm_dh(
   };
   // per-XCD contiguous order, split-major: the workgroups resident on one XCD work on the same
   // K range of neighbouring tiles and share their operand slices in that XCD's L2
-  const int npid = xcd_regroup(blockIdx.x, n);
+  const int npid = xcd_regroup(block, n);
   const int split = npid / base;
   int tt, th;
   tile_of_index(npid % base, tiles_t, tiles_h, tt, th);
@@ -872,6 +871,13 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_gemm_dh(
       if (col < H) *reinterpret_cast<f32x4_t*>(row + col) = acc[mb][nb];
     }
   }
+}
+
+__global__ __launch_bounds__(kGemmNT, 2) void k_gemm_dh(
+    const uint16_t* __restrict__ dz, const uint16_t* __restrict__ W, int V, int vK, int H, int tiles_h,
+    const int32_t* __restrict__ nact, float* __restrict__ dh_part) {
+  extern __shared__ __align__(16) uint16_t smem[];
+  dh_tile(blockIdx.x, smem, dz, W, V, vK, H, tiles_h, nact, dh_part);
 }
 
 // Calls of at least so many rows get a workgroup per tile, smaller ones a workgroup per CU that walks the tiles: walking pays for
@@ -897,11 +903,11 @@ __device__ __forceinline__ int dw_splits(int most, int n_cand) {
 }
 
 // dW[m][h] = sum_t XT[m][t] hTc[h][t], hTc = the candidates' hidden rows times their scale     M = V, N = H, K = candidate tokens (padded)
+// Workgroup `block` of `blocks`.
 template <bool OUT_BF16, bool ACC>
-__global__ __launch_bounds__(kGemmNT, 2) void k_gemm_dw(
-    const uint16_t* __restrict__ dzT, const uint16_t* __restrict__ hTc, int V, int H,
-    int tile0, int n_tiles, int tiles_v, int tiles_h, int64_t T_pad, const int32_t* __restrict__ nact, int vec, int most, void* dW) {
-  extern __shared__ __align__(16) uint16_t smem[];
+__device__ __forceinline__ void dw_tiles(int block, int blocks, uint16_t* smem, const uint16_t* __restrict__ dzT,
+                                         const uint16_t* __restrict__ hTc, int V, int H, int tile0, int n_tiles, int tiles_v, int tiles_h,
+                                         int64_t T_pad, const int32_t* __restrict__ nact, int vec, int most, void* dW) {
   // the contraction ends with the slice of the last candidate, not with its tile: the positions behind it are zeros
   // (whole calls at H = 1536, V = 151936: 600 tokens 949 -> 905 us, 1100 tokens 1376 -> 1357, 16384 tokens -0.4 %)
   const int slices = (nact[0] + kDK - 1) / kDK;
@@ -925,7 +931,7 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_gemm_dw(
   // V = 151936 in bf16 while the contraction took whole token tiles - 223 us since it ends earlier -, 1690 against
   // 1660 us per 1536 tiles with 16384 in fp32).
   constexpr int kDT = OUT_BF16 ? kBF16 : kF32;
-  int pid = blockIdx.x, tv, th;
+  int pid = block, tv, th;
   bool more = tile_of_step(pid, parts * tiles_v, tiles_h, tile0, n_tiles, tv, th), stored = false;
   if (!more) return;
   TileSrc src = source(tv, th);
@@ -937,7 +943,7 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_gemm_dw(
     wp.warm_a = warm_share(th, tiles_h);
     wp.warm_b = warm_share(tv, tiles_v);
     wp.warm_from = kWarmSlices;
-    pid += gridDim.x;
+    pid += blocks;
     more = tile_of_step(pid, parts * tiles_v, tiles_h, tile0, n_tiles, tv, th);
     const TileSrc next = more ? source(tv, th) : no_tile(src);
     Acc acc;
@@ -998,6 +1004,32 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_gemm_dw(
     }
   }
   end_of_walk();
+}
+
+template <bool OUT_BF16, bool ACC>
+__global__ __launch_bounds__(kGemmNT, 2) void k_gemm_dw(
+    const uint16_t* __restrict__ dzT, const uint16_t* __restrict__ hTc, int V, int H, int tile0, int n_tiles, int tiles_v, int tiles_h,
+    int64_t T_pad, const int32_t* __restrict__ nact, int vec, int most, void* dW) {
+  extern __shared__ __align__(16) uint16_t smem[];
+  dw_tiles<OUT_BF16, ACC>(blockIdx.x, gridDim.x, smem, dzT, hTc, V, H, tile0, n_tiles, tiles_v, tiles_h, T_pad, nact, vec, most, dW);
+}
+
+// Both contractions in one launch: the workgroups that walk dweight's tiles, then (from dw_blocks on, a multiple of 8) dhidden's, which
+// take the CUs that the former leave idle or are through with.  For H up to 256, where dhidden has at most 64 splits of a few tiles, and
+// for gradients of up to a tile per CU; calls of kDwTileRows rows and more fill the chip with either.  Whole calls, two launches / one: H = 208,
+// V = 152064 144 rows 133.7 / 122.7 us, 500 248 / 217, 2000 659 / 601, 6000 1593 / 1542; H = 256, V = 60000 500 120.6 / 117.9, 4000 470 / 444; H = 360,
+// V = 4249 1080 rows 83.9 / 70.9; H = 896, V = 5504 1001 103.5 / 97.3; H = 2048, V = 6678 240 108.5 / 107.1.  Where both fill the chip it is a matter of
+// how their last rounds fall: H = 896, V = 33846 500 rows 172.5 / 174.3, 4000 693 / 659; H = 640, V = 30000 4000 451 / 460; H = 3584, V = 32000 300 272 / 280.
+template <bool OUT_BF16, bool ACC>
+__global__ __launch_bounds__(kGemmNT, 2) void k_gemm_grads(
+    const uint16_t* __restrict__ dz, const uint16_t* __restrict__ W, int vK, float* __restrict__ dh_part, int dw_blocks,
+    const uint16_t* __restrict__ dzT, const uint16_t* __restrict__ hTc, int V, int H, int n_tiles, int tiles_v, int tiles_h,
+    int64_t T_pad, const int32_t* __restrict__ nact, int vec, void* dW) {
+  extern __shared__ __align__(16) uint16_t smem[];
+  if (int(blockIdx.x) < dw_blocks)
+    dw_tiles<OUT_BF16, ACC>(blockIdx.x, dw_blocks, smem, dzT, hTc, V, H, 0, n_tiles, tiles_v, tiles_h, T_pad, nact, vec, 1, dW);
+  else
+    dh_tile(int(blockIdx.x) - dw_blocks, smem, dz, W, V, vK, H, tiles_h, nact, dh_part);
 }
 
 // dweight from its parts: [parts][V][H] fp32, added up in order, eight entries (n of them) a thread.
@@ -1149,6 +1181,10 @@ extern "C" aero_status aero_lmhead_logprob_fused(
         set_lds(reinterpret_cast<const void*>(k_fused_dz<false>)) != AERO_OK ||
         set_lds(reinterpret_cast<const void*>(k_fused_dz<true>)) != AERO_OK ||
         set_lds(reinterpret_cast<const void*>(k_gemm_dh)) != AERO_OK ||
+        set_lds(reinterpret_cast<const void*>(k_gemm_grads<true, true>)) != AERO_OK ||
+        set_lds(reinterpret_cast<const void*>(k_gemm_grads<true, false>)) != AERO_OK ||
+        set_lds(reinterpret_cast<const void*>(k_gemm_grads<false, true>)) != AERO_OK ||
+        set_lds(reinterpret_cast<const void*>(k_gemm_grads<false, false>)) != AERO_OK ||
         set_lds(reinterpret_cast<const void*>(k_gemm_dw<true, true>)) != AERO_OK ||
         set_lds(reinterpret_cast<const void*>(k_gemm_dw<true, false>)) != AERO_OK ||
         set_lds(reinterpret_cast<const void*>(k_gemm_dw<false, true>)) != AERO_OK ||
@@ -1227,40 +1263,47 @@ extern "C" aero_status aero_lmhead_logprob_fused(
                      p.H_pad, hTc, terms.scale, terms.term, terms.flag, nact, loss, clip_frac);
 
   // ---- the two gradient contractions over the whole vocabulary ----
-  if (T > 0) {
-    // dz columns [V, V_ld) are zero, weight rows past V read as zeros: the contraction runs over the padded vocabulary
-    hipLaunchKernelGGL(k_gemm_dh, dim3(unsigned(grid_dh)), dim3(kGemmNT), kGemmLdsBytes, s, dz, Wp, V, p.V_ld, H, tiles_h, p.T_pad,
-                       nact, dh_acc);
+  // dz columns [V, V_ld) are zero, weight rows past V read as zeros: the contraction runs over the padded vocabulary
+  const int total = p.tiles_v * tiles_h;
+  const int vec_dw = reinterpret_cast<uintptr_t>(dweight) % 16 == 0;   // rows are multiples of 16 bytes
+  const bool dw_bf16 = dweight_dtype == AERO_BF16;
+  int most = 1;
+  if (total <= kDwSplitTiles && T >= std::max(kDwSplitRows, kDwSplitRowsPerTile * total))   // no more than the partials' buffer holds
+    most = int(std::min<int64_t>(std::min(cus / total, kDwSplitMax), dh_part_rows(p.T_pad, H, p.V_ld) / V));
+  const bool together = T > 0 && most == 1 && p.T_pad < kDwTileRows && (tiles_h == 1 || total <= cus);   // see k_gemm_grads
+  if (together) {
+    const auto kernel = dw_bf16 ? (accumulate ? k_gemm_grads<true, true> : k_gemm_grads<true, false>)
+                                : (accumulate ? k_gemm_grads<false, true> : k_gemm_grads<false, false>);
+    const int dw_blocks = int(walkers(xcd_grid(total)).x);
+    hipLaunchKernelGGL(kernel, dim3(unsigned(dw_blocks + grid_dh)), dim3(kGemmNT), kGemmLdsBytes, s, dz, Wp, p.V_ld, dh_acc, dw_blocks, dzT,
+                       hTc, V, H, total, p.tiles_v, tiles_h, p.T_pad, nact, vec_dw, dweight);
+  } else if (T > 0) {
+    hipLaunchKernelGGL(k_gemm_dh, dim3(unsigned(grid_dh)), dim3(kGemmNT), kGemmLdsBytes, s, dz, Wp, V, p.V_ld, H, tiles_h, nact, dh_acc);
   }
   if (T > 0)
     hipLaunchKernelGGL(k_scatter_dh, dim3(unsigned(T)), dim3(256), 0, s, dh_acc, pos, nact, H, terms.scale, reinterpret_cast<uint16_t*>(dhidden));
-  // dweight: one launch where a workgroup walks; where it has one tile, eight rounds of tiles a launch, so that the workgroups
+  if (together) return launch_status();
+  if (most > 1) {
+    const dim3 grid = walkers(xcd_grid(most * total));
+    hipLaunchKernelGGL((k_gemm_dw<false, false>), grid, dim3(kGemmNT), kGemmLdsBytes, s, dzT, hTc, V, H, 0, most * total, p.tiles_v, tiles_h,
+                       p.T_pad, nact, 1, most, dh_acc);
+    const auto sum = dw_bf16 ? (accumulate ? k_sum_dw<true, true> : k_sum_dw<true, false>)
+                             : (accumulate ? k_sum_dw<false, true> : k_sum_dw<false, false>);
+    const int64_t n = int64_t(V) * H;
+    hipLaunchKernelGGL(sum, dim3(unsigned((n / 8 + 255) / 256)), dim3(256), 0, s, dh_acc, nact, most, n, vec_dw, dweight);
+    return launch_status();
+  }
+  // One launch where a workgroup walks (T == 0); where it has one tile, eight rounds of tiles a launch, so that the workgroups
   // that share operand slices stay close along K (32768 tokens at H = 3584, V = 152064, whole call: one launch 67.1, 16 rounds
   // 66.7, eight 66.1, four 66.8 ms; 16384 at H = 1536 even)
-  {
-    const int total = p.tiles_v * tiles_h, per = p.T_pad < kDwTileRows ? total : 8 * cus;
-    const int vec_dw = reinterpret_cast<uintptr_t>(dweight) % 16 == 0;   // rows are multiples of 16 bytes
-    const auto kernel = dweight_dtype == AERO_BF16 ? (accumulate ? k_gemm_dw<true, true> : k_gemm_dw<true, false>)
-                                                   : (accumulate ? k_gemm_dw<false, true> : k_gemm_dw<false, false>);
-    int most = 1;
-    if (total <= kDwSplitTiles && T >= std::max(kDwSplitRows, kDwSplitRowsPerTile * total))   // no more than the partials' buffer holds
-      most = int(std::min<int64_t>(std::min(cus / total, kDwSplitMax), dh_part_rows(p.T_pad, H, p.V_ld) / V));
-    if (most > 1) {
-      const dim3 grid = walkers(xcd_grid(most * total));
-      hipLaunchKernelGGL((k_gemm_dw<false, false>), grid, dim3(kGemmNT), kGemmLdsBytes, s, dzT, hTc, V, H, 0, most * total, p.tiles_v, tiles_h,
-                         p.T_pad, nact, 1, most, dh_acc);
-      const auto sum = dweight_dtype == AERO_BF16 ? (accumulate ? k_sum_dw<true, true> : k_sum_dw<true, false>)
-                                                  : (accumulate ? k_sum_dw<false, true> : k_sum_dw<false, false>);
-      const int64_t n = int64_t(V) * H;
-      hipLaunchKernelGGL(sum, dim3(unsigned((n / 8 + 255) / 256)), dim3(256), 0, s, dh_acc, nact, most, n, vec_dw, dweight);
-      return launch_status();
-    }
-    for (int t0 = 0; t0 < total; t0 += per) {
-      const int n = total - t0 < per ? total - t0 : per;
-      const dim3 grid = p.T_pad < kDwTileRows ? walkers(xcd_grid(n)) : dim3(unsigned(xcd_grid(n)));
-      hipLaunchKernelGGL(kernel, grid, dim3(kGemmNT), kGemmLdsBytes, s, dzT, hTc, V, H, t0, n,
-                         p.tiles_v, tiles_h, p.T_pad, nact, vec_dw, 1, dweight);
-    }
+  const auto kernel = dw_bf16 ? (accumulate ? k_gemm_dw<true, true> : k_gemm_dw<true, false>)
+                              : (accumulate ? k_gemm_dw<false, true> : k_gemm_dw<false, false>);
+  const int per = p.T_pad < kDwTileRows ? total : 8 * cus;
+  for (int t0 = 0; t0 < total; t0 += per) {
+    const int n = total - t0 < per ? total - t0 : per;
+    const dim3 grid = p.T_pad < kDwTileRows ? walkers(xcd_grid(n)) : dim3(unsigned(xcd_grid(n)));
+    hipLaunchKernelGGL(kernel, grid, dim3(kGemmNT), kGemmLdsBytes, s, dzT, hTc, V, H, t0, n,
+                       p.tiles_v, tiles_h, p.T_pad, nact, vec_dw, 1, dweight);
   }
   return launch_status();
 }

@@ -218,6 +218,21 @@ def test_fused_dweight_parts_add_up(gh, T, H, V):
     assert (whole != 0).any()
 
 
+@pytest.mark.parametrize("T,H,V", [(300, 200, 70013), (700, 520, 3000), (90, 256, 66000), (1200, 8, 40)])
+@pytest.mark.parametrize("accumulate", [False, True])
+def test_fused_gradients_in_one_launch(gh, T, H, V, accumulate):
+    """Both contractions in one launch (one tile of H, or few tiles): more dweight tiles than CUs and fewer, ragged ones, a dweight in
+    bf16 and in fp32, into a fresh buffer and on top of zeros, which comes to the same."""
+    wl, h, W = make(T, H, V, sigma_w=2.0 / np.sqrt(H))
+    ref, out = check_bwd(gh, wl, h, W, dict(), dweight_dtype=torch.bfloat16 if V % 2 else torch.float32)
+    ga = orc.group_advantage(wl.rewards, wl.lengths, wl.group_offsets, wl.keep_priority, AdvParams())
+    old = ai.draw_old_logprob(orc.lmhead_fused(h, W, wl.targets)["logprob"], wl.seed, sigma=0.3)
+    into = torch.zeros_like(out["dweight"]) if accumulate else torch.full_like(out["dweight"], 7.0)
+    again = run_fused(gh, wl, h, W, wl.targets, bwd=dict(old=old, adv=ga["adv"].astype(np.float32), weight=ga["weight"].astype(np.float32)),
+                      dweight_dtype=out["dweight"].dtype, dw_into=into, accumulate=accumulate)
+    assert torch.equal(into, out["dweight"]) and torch.equal(again["dhidden"], out["dhidden"])
+
+
 @pytest.mark.parametrize("T", [2048, 2049, 8193, 33793])
 def test_fused_compaction_steps(gh, T):
     """Around the row counts at which the compaction takes several steps at a time, and past the 32 steps whose classes it
