@@ -5,23 +5,21 @@
 // so any group size works; counts are integers, the few floating-point statistics are formed
 // in fp64 from those counts and rounded once to fp32.  The call is latency bound, so what counts is
 // launches, dependent loads and exchanges between lanes:
-//   up to 2048 groups and 8192 rollouts (a step)    k_curate: one launch, nothing passed between workgroups; without rejection
-//                                                   up to 32768 rollouts of groups that fit a wave on average
+//   up to 2048 groups and 8192 rollouts (a step)    k_curate: one launch, nothing passed between workgroups
 //   up to 8192 groups                               k_group (c, category, keep mask, advantages, weights), then k_place:
 //                                                   every workgroup adds up the kept counts in front of its groups
 //                                                   itself, so no scan stands between
 //   more                                            k_group, k_scan (exclusive scan of the kept counts, one
 //                                                   workgroup) and k_compact: the counts would be read too often.
-// Whole calls, k_group + k_place / k_curate, without rejection and with it where two pairs stand: 8 groups of 8 7.4 / 5.4, 7.2 / 5.3 us;
-// 64 of 64 7.2 / 5.2, 9.5 / 9.7; 256 of 32 7.3 / 5.4, 7.8 / 8.0; 64 of 128 7.4 / 7.1, 18.6 / 19.6; 16 of 500 13.2 / 13.0, 194 / 204.  Over 8192
-// rollouts, where the rewards in front take 32 loads a thread and ranks 16 waves on one CU: 300 of 30 7.3 / 6.7, 7.8 / 9.2; 600 of 20 7.3 /
-// 6.8, 7.5 / 8.6; 1000 of 32 7.3 / 6.8, 8.3 / 9.6; 2048 of 9 7.3 / 7.2, 7.4 / 8.2; wide groups: 500 of 65 8.0 / 9.1, 13.5 / 16.1; 200 of 160 8.5 /
-// 10.0, 30.6 / 34.4; 64 of 512 13.5 / 16.0, 197 / 254; 16 of 2048 41.5 / 43.3; one of 32768 559 / 537.
+// Whole calls, k_group + k_place / k_curate, without rejection and with it: 256 groups of 16 6.6 / 4.2, 6.6 / 5.0 us; 256 of 32 6.6 / 4.2,
+// 6.5 / 5.2; 64 of 128 6.6 / 6.0, 10.6 / 10.5; 16 of 500 12.8 / 12.6, 84 / 84.  Over 8192 rollouts, where a thread has 64 of the rewards in front to
+// load: 300 of 30 6.6 / 7.4, 8.0 / 8.4; 600 of 20 6.6 / 7.6, 7.2 / 8.2; 1000 of 32 6.6 / 7.7, 7.3 / 8.4; 2048 of 9 6.8 / 8.4, 7.2 / 8.9; 500 of 64
+// 6.6 / 7.3, 7.0 / 8.4.
 // k_place / k_scan + k_compact: 400 groups (7831 rollouts) 9.0 / 11.4, 3000 (60325) 10.2 / 12.9, 4000 (80187) 11.0 / 14.5, 8000
 // (159965) 18.1 / 24.1.  (Counting the bytes of the keep mask instead, up to 8192 rollouts, takes as long, and reads
 // bytes that nobody wrote where offsets start above 0.)
 // 100 groups of 64 to 90 rollouts, whose ranks do not fit one register a lane: 37.9 us when every lane looked for its
-// rank by itself in memory, 13.3 with the candidates taken 64 at a time into the lanes.
+// rank by itself in memory, 10.4 with the candidates taken 64 at a time (ranks_before).
 #include "aero_device.h"
 
 namespace aero {
@@ -78,13 +76,30 @@ __device__ __forceinline__ Held load_held(GroupRange g, int lane, const float* _
   return Held{rewards[i], keys ? keys[i] : 0u, lengths[i]};
 }
 
+// How many of the first n lanes' values (n <= 64, uniform) lie below `own`: every lane leaves its value in LDS and reads all of them, the
+// same address in every lane.  (Handed round through the scalar side instead, a value at a time by v_readlane: a CU's waves share
+// one scalar unit, and 16 groups of 32 rollouts were 4000 of its cycles.  Whole calls 256 groups of 8 to 32 6.7 / 4.7 us, with 8
+// waves a workgroup; 8 of 32 5.0 / 3.5; 864 of 10 to 26, in two launches, 7.3 / 6.2.)
+__device__ __forceinline__ int ranks_before(uint64_t* lds /*[64]*/, int lane, uint64_t value, int n, uint64_t own) {
+  asm volatile("" ::: "memory");   // one wave's LDS accesses keep their order
+  lds[lane] = value;
+  asm volatile("" ::: "memory");
+  int before = 0;
+#pragma unroll 2
+  for (int j = 0; j < n; j += 4) {   // uniform; values past n are ~0 or count for nobody
+#pragma unroll
+    for (int u = 0; u < 4; ++u) before += lds[j + u] < own;
+  }
+  return before;
+}
+
 // One group, one wave: everything but the position of its kept rollouts in kept_index.  Returns the
 // number of kept rollouts (the same value in every lane); kept0: those among the group's first 64.
 __device__ __forceinline__ int group_body(
     int q, GroupRange range, Held held, int lane, const float* __restrict__ rewards, const int32_t* __restrict__ lengths,
     const uint32_t* __restrict__ keys, int Q, const aero_adv_params& p, float* __restrict__ adv,
     float* __restrict__ weight, uint8_t* __restrict__ keep_mask, uint8_t* __restrict__ zero_var,
-    uint8_t* __restrict__ category, int32_t* __restrict__ err_flag, uint64_t& kept0) {
+    uint8_t* __restrict__ category, int32_t* __restrict__ err_flag, uint64_t* ranks /*[64], LDS*/, uint64_t& kept0) {
   const int b = range.b, e = range.e;
   const int n = e - b;
   const bool curation = p.reject_enable || p.posterior_mode;
@@ -115,20 +130,14 @@ __device__ __forceinline__ int group_body(
   const KeepRule rule = keep_rule(p, cat, n, c);
   const KeepMode mode = rule.mode;
   const int m = rule.m;
-  // a group that fits the wave: ranks from the lanes' registers, one candidate of the group at a time; smaller key
-  // first, ties to the lower index
+  // a group that fits the wave: ranks from the lanes' own keys; smaller key first, ties to the lower index
   int ahead0 = 0;
   if (n <= kWave && mode >= kKeepCorrect) {
     const uint64_t in = __ballot(in0);
     uint64_t cand = in & (mode == kKeepLowest ? ~uint64_t(0) : ~ones);
     if (__popcll(cand) > m) {
       const uint64_t own = uint64_t(key0) << 32 | uint32_t(lane);
-      while (cand) {   // uniform
-        const int j = __ffsll((unsigned long long)cand) - 1;
-        cand &= cand - 1;
-        const uint64_t other = uint64_t(uint32_t(__builtin_amdgcn_readlane(int(key0), j))) << 32 | uint32_t(j);
-        ahead0 += other < own;
-      }
+      ahead0 = ranks_before(ranks, lane, cand >> lane & 1 ? own : ~uint64_t(0), n, own);
     }
   }
   auto posterior_mean = [&]() { return (double(c) + double(p.alpha0)) / (double(n) + double(p.alpha0) + double(p.beta0)); };
@@ -190,12 +199,8 @@ __device__ __forceinline__ int group_body(
           for (int from = b; from < e && __any(in && !k && ahead < m); from += kWave) {
             const int j0 = from + lane;
             const uint32_t kj = j0 < e && keys ? keys[j0] : 0u;
-            uint64_t cand = __ballot(j0 < e && (mode == kKeepLowest || rewards[j0] != 1.f));
-            while (cand) {
-              const int j = __ffsll((unsigned long long)cand) - 1;
-              cand &= cand - 1;
-              ahead += (uint64_t(uint32_t(__builtin_amdgcn_readlane(int(kj), j))) << 32 | uint32_t(from + j)) < own;
-            }
+            const bool cand = j0 < e && (mode == kKeepLowest || rewards[j0] != 1.f);
+            ahead += ranks_before(ranks, lane, cand ? uint64_t(kj) << 32 | uint32_t(j0) : ~uint64_t(0), kWave, own);
           }
           k |= in && ahead < m;
         }
@@ -270,13 +275,14 @@ __global__ __launch_bounds__(kGroupsPerBlock* kWave) void k_group(
     aero_adv_params p, float* __restrict__ adv, float* __restrict__ weight, uint8_t* __restrict__ keep_mask,
     int32_t* __restrict__ kept_offsets, int count_mask, uint8_t* __restrict__ zero_var, uint8_t* __restrict__ category,
     int32_t* __restrict__ err_flag) {
+  __shared__ __align__(16) uint64_t ranks[kGroupsPerBlock][kWave];
   const int lane = threadIdx.x % kWave;
   const int q = blockIdx.x * kGroupsPerBlock + threadIdx.x / kWave;
   if (q >= Q) return;   // whole wave leaves together
   const GroupRange range = group_range(group_offsets[q], group_offsets[q + 1], R);
   uint64_t kept0;
   const int nk = group_body(q, range, load_held(range, lane, rewards, lengths, keys), lane, rewards, lengths, keys, Q, p, adv,
-                            weight, keep_mask, zero_var, category, err_flag, kept0);
+                            weight, keep_mask, zero_var, category, err_flag, ranks[threadIdx.x / kWave], kept0);
   if (lane == 0) kept_offsets[q + 1] = nk ^ count_mask;   // count_mask: 0, or -1 for k_place
 }
 
@@ -382,23 +388,23 @@ __global__ __launch_bounds__(kPlaceNT) void k_place(
   compact_body(q, lane, group_offsets, keep_mask, out, R, kept_index);
 }
 
-// All of it in one launch: a wave per group, up to 16 in a workgroup.  How many rollouts a group keeps follows from its size
+// All of it in one launch: a wave per group, up to 8 in a workgroup (16 or 4: 5.1 us for 256 groups of 8 to 32 where 8 take 4.7).  How many rollouts a group keeps follows from its size
 // and its count of correct rollouts alone, so a workgroup counts what lies in front of its groups itself, from the
 // rewards (a bit per rollout in LDS, a thread per group), while its own groups' loads are under way; nothing is passed
 // between workgroups.  Bound by latency: kernel arguments, offsets, rewards, and the instructions themselves, which come
 // from memory once per launch.
-constexpr int kCurateWaves = 16, kCurateNT = kCurateWaves * kWave;
-constexpr int kCurateR = 32 * kCurateNT, kCurateQ = 2 * kCurateNT;
-// LOADS: rewards per thread, all in flight at once; R <= LOADS * kCurateNT unless there is one workgroup.
-template <int LOADS>
+constexpr int kCurateWaves = 8, kCurateNT = kCurateWaves * kWave;
+constexpr int kCurateR = 8192, kCurateQ = 2048;
 __global__ __launch_bounds__(kCurateNT) void k_curate(
     const float* __restrict__ rewards, const int32_t* __restrict__ lengths,
     const int32_t* __restrict__ group_offsets, const uint32_t* __restrict__ keys, int Q, int R,
     aero_adv_params p, float* __restrict__ adv, float* __restrict__ weight, uint8_t* __restrict__ keep_mask,
     int32_t* __restrict__ kept_index, int32_t* __restrict__ kept_offsets, uint8_t* __restrict__ zero_var,
     uint8_t* __restrict__ category, int32_t* __restrict__ err_flag) {
+  constexpr int LOADS = kCurateR / kCurateNT;   // rewards per thread, all in flight at once
   __shared__ uint64_t ones[LOADS * kCurateWaves];   // bit i % 64 of word i / 64: reward i is exactly 1
   __shared__ int front[kCurateWaves], own[kCurateWaves];
+  __shared__ __align__(16) uint64_t ranks[kCurateWaves][kWave];
   const int tid = threadIdx.x, lane = tid % kWave, wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int waves = blockDim.x / kWave;
   const int q0 = blockIdx.x * waves, q = q0 + wave;
@@ -449,7 +455,7 @@ __global__ __launch_bounds__(kCurateNT) void k_curate(
   uint64_t kept0 = 0;
   int nk = 0;
   if (q < Q)   // uniform over the wave
-    nk = group_body(q, mine, held, lane, rewards, lengths, keys, Q, p, adv, weight, keep_mask, zero_var, category, err_flag, kept0);
+    nk = group_body(q, mine, held, lane, rewards, lengths, keys, Q, p, adv, weight, keep_mask, zero_var, category, err_flag, ranks[wave], kept0);
   if (lane == 0) {
     front[wave] = before_me;
     own[wave] = nk;
@@ -482,11 +488,9 @@ extern "C" aero_status aero_group_advantage(
   if (Q > 0 && (!group_zero_var || !group_category)) return AERO_ERR_NULL;
   if (R > 0 && (!rewards || !lengths || !adv || !weight || !keep_mask || !kept_index)) return AERO_ERR_NULL;
   hipStream_t s = as_stream(stream);
-  const bool few = R <= 8 * kCurateNT, ranks = p->reject_enable;
-  if (Q > 0 && Q <= kCurateQ && (few || (R <= kCurateR && R <= kWave * Q && !ranks))) {   // see the top
+  if (Q > 0 && Q <= kCurateQ && R <= kCurateR) {   // see the top
     const int waves = Q < kCurateWaves ? Q : kCurateWaves;
-    const auto kernel = few ? k_curate<8> : k_curate<kCurateR / kCurateNT>;
-    hipLaunchKernelGGL(kernel, dim3(unsigned((Q + waves - 1) / waves)), dim3(unsigned(waves * kWave)), 0, s, rewards, lengths,
+    hipLaunchKernelGGL(k_curate, dim3(unsigned((Q + waves - 1) / waves)), dim3(unsigned(waves * kWave)), 0, s, rewards, lengths,
                        group_offsets, keep_priority, Q, R, *p, adv, weight, keep_mask, kept_index, kept_offsets, group_zero_var,
                        group_category, err_flag);
     return launch_status();
