@@ -258,8 +258,8 @@ aero_status aero_grpo_loss_bwd_noalloc(
  * target >= V is treated the same way and raises AERO_DERR_BAD_TARGET in err_flag.
  * workspace: aero_workspace_bytes(AERO_OP_LMHEAD_FUSED, T, V, H, R, 0) bytes of device memory,
  * 256-byte aligned, owned by the caller, contents undefined before and after the call.
- * Errors: AERO_ERR_SHAPE (T < 0, V < 1 or > 2^24, H < 8, H % 8 != 0, or a padded backward
- * operand of 4 GiB or more: H, T or the vocabulary chunk too large for 32-bit offsets),
+ * Errors: AERO_ERR_SHAPE (T < 0, V < 1 or > 2^24, H < 8, H % 8 != 0, or an operand too large for
+ * 32-bit offsets: hidden, weight or 256 padded rows of a gradient operand of 4 GiB or more),
  * AERO_ERR_DTYPE (dweight_dtype), AERO_ERR_NULL, AERO_ERR_ALIGN, AERO_ERR_WORKSPACE,
  * AERO_ERR_HIP (launch failure).  Asynchronous on `stream`; nothing is allocated.
  */

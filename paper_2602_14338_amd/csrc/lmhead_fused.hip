@@ -23,10 +23,12 @@
 //                            range): recompute the z^T tile and store dz itself in the same layouts
 //           k_hidden_and_loss  hidden rows times their scale, transposed; the loss sum
 //           k_gemm_dh        dhidden partials = (P or dz) @ weight   (split-K over the vocabulary, fp32)
-//           k_gemm_dw        dweight = (P or dz)^T @ (scale * hidden)
 //           k_scatter_dh     fp32 partials summed in fixed order, times scale -> bf16 dhidden at the original rows
-// All contractions use the same 256 x 256 x 64 MFMA tile, both operands K-contiguous but for the weight in k_gemm_dh,
-// whose rows are the contraction index and which a transposing LDS read turns.  In all but k_gemm_dh (whose split count
+//           k_gemm_dw        dweight = (P or dz)^T @ (scale * hidden)
+//           k_gemm_grads     k_gemm_dh and k_gemm_dw in one launch, where either leaves CUs idle
+//           k_sum_dw         the parts of a dweight whose contraction range was split (few tiles, kDwSplitTiles)
+// All contractions use the same 256 x 256 MFMA tile, both operands K-contiguous but for the weight in k_gemm_dh,
+// whose rows are the contraction index and which a transposing LDS read turns; slices are 64 wide, there 32 (GemmRing).  In all but k_gemm_dh (whose split count
 // fills the CUs once or twice), the longer k_gemm_dw (kDwTileRows) and forward tiles of many slices (kForwardTileSlices) a workgroup
 // per CU walks the tiles.
 #include <algorithm>
@@ -51,9 +53,11 @@ struct FusedPlan {
 
 // dhidden is formed as S split-K partials of the active rows, S chosen on the device so that
 // (candidate token tiles) x (H tiles) x S fills the launch grid in whole rounds; the buffer holds S
-// stacked copies of the active rows, never more rows than the launch grid covers.  A split's
-// operands are addressed with 32-bit byte offsets, so a split may span at most 4 GiB of the dz
-// slabs of rows_max rows: the grid leaves room for that many splits (plus one) when every token is active.
+// stacked copies of the active rows, never more rows than the launch grid covers.  A split's weight rows are
+// addressed with 32-bit byte offsets.  The rule asks for at most 4 GiB per split of a matrix of T_pad or H_pad columns,
+// whichever are more (rows_max), and the grid leaves room for that many splits (plus one) when every token is active.  For the
+// addresses H_pad alone would do: with it 32768 tokens take one split instead of three, which measured 0 to 0.9 % of
+// a call, and the whole vocabulary would be one chain of fp32 additions.
 constexpr int kDhGridMin = 4096;
 constexpr int64_t kOperandBytes = int64_t(1) << 32;
 static int dh_grid(int64_t T_pad, int H, int V_ld) {
@@ -113,8 +117,8 @@ size_t fused_workspace_bytes(int64_t T, int32_t V, int32_t H) {
 // Split-K factor for dhidden, from the number of candidate token tiles (device side; one wave, lane s - 1
 // prices s splits).  A workgroup's time is its share of the K slices plus a fixed tail (storing its fp32
 // partial tile, worth about 8 slices of main loop); the launch takes ceil(workgroups / 256) such rounds.
-// S minimises rounds x (slices / S + 8) among the S whose splits stay addressable: a split's
-// slab operands (rows_max rows per 64-wide slice) must span less than 4 GiB.  Chosen once per call: the
+// S minimises rounds x (slices / S + 8) among the S whose splits are small enough (see dh_grid): a split's
+// range times rows_max columns of bf16 must stay below 4 GiB.  Chosen once per call: the
 // 64-bit divisions are 50 us of latency when one thread walks the candidates, and every workgroup of
 // the contraction and of the scatter used to (400 of the 530 us of the contraction of 600 tokens).
 __device__ __forceinline__ int dh_splits(int active_tiles, int tiles_h, int grid, int slices, int64_t rows_max) {
@@ -1142,7 +1146,7 @@ extern "C" aero_status aero_lmhead_logprob_fused(
   if (reinterpret_cast<uintptr_t>(hidden) % 16 || reinterpret_cast<uintptr_t>(weight) % 16) return AERO_ERR_ALIGN;
   if (bwd && reinterpret_cast<uintptr_t>(dhidden) % 16) return AERO_ERR_ALIGN;   // rows are written as 16-byte vectors
   const FusedPlan p = make_plan(T, V, H);
-  // operands are addressed with 32-bit byte offsets: every slab operand must stay below 4 GiB
+  // operands are addressed with 32-bit byte offsets: a tile's run of slabs, the hidden rows and the weight must stay below 4 GiB
   constexpr size_t kOperandLimit = size_t(1) << 32;
   if (size_t(p.H_pad) * size_t(p.T_pad) * 2 >= kOperandLimit || size_t(p.T_pad) * kTile * 2 >= kOperandLimit ||
       size_t(V) * size_t(H) * 2 >= kOperandLimit)
