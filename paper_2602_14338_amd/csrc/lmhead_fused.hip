@@ -26,7 +26,7 @@
 //           k_scatter_dh     fp32 partials summed in fixed order, times scale -> bf16 dhidden at the original rows
 //           k_gemm_dw        dweight = (P or dz)^T @ (scale * hidden)
 //           k_gemm_grads     k_gemm_dh and k_gemm_dw in one launch, where either leaves CUs idle
-//           k_sum_dw         the parts of a dweight whose contraction range was split (few tiles, kDwSplitTiles)
+//           k_scatter_and_sum  k_scatter_dh and the sum of dweight's parts, where its range may be split (few tiles, kDwSplitTiles)
 // All contractions use the same 256 x 256 MFMA tile, both operands K-contiguous but for the weight in k_gemm_dh,
 // whose rows are the contraction index and which a transposing LDS read turns; slices are 64 wide, there 32 (GemmRing).  In all but k_gemm_dh (whose split count
 // fills the CUs once or twice), the longer k_gemm_dw (kDwTileRows) and forward tiles of many slices (kForwardTileSlices) a workgroup
@@ -93,7 +93,7 @@ static FusedPlan make_plan(int64_t T, int V, int H) {
   p.off_flag = take(size_t(p.T_pad) * 4);
   p.off_zy = take(size_t(p.T_pad) * 4);
   p.off_pos = take(size_t(p.T_pad) * 4);
-  p.off_nact = take(16);
+  p.off_nact = take(20);
   p.off_gc = take(size_t(p.T_pad) * 4);
   p.off_lsec = take(size_t(p.T_pad) * 4);
   p.off_yc = take(size_t(p.T_pad) * 4);
@@ -134,6 +134,34 @@ __device__ __forceinline__ int dh_splits(int active_tiles, int tiles_h, int grid
   return best == INT64_MAX ? 0 : int(best & 63) + 1;
 }
 
+// A gradient dweight of few tiles leaves CUs idle however many tokens there are: up to kDwSplitTiles tiles the candidates' range
+// is split into parts, whose sums lie in fp32 behind the dhidden partials until k_scatter_and_sum adds them up in order.
+// Whether it pays depends on the candidates, which only the device knows, and on the tiles: one range takes as long as its slices
+// unless dhidden's workgroups fill the idle CUs meanwhile (k_gemm_grads), and with half the CUs' number of tiles they do; the parts' way to
+// memory and back has to be shorter than what is left.  So the host says what may be (most, from the rows) and dw_parts decides,
+// by a line through the counts at which the two came out even.  Whole calls, one range / split, by tiles: 16 (H = 64, V = 4000) 1125 candidates 73.1 / 63.4 us, 4750 162 / 99; 32 (256, 8000) 1125 97.7 / 87.0; 48
+// (512, 6144) 1125 102.5 / 94.9; 57 (640, 4753) 1437 101.5 / 105.4, 2125 137 / 132; 64 (1024, 4096) 1437 113.6 / 113.5, 2125 145.4 / 138.4; 72
+// (424, 9000) 2125 140.0 / 138.9, 4750 248.5 / 237.7; 85 (256, 21760) 3000 235 / 241, 4750 326 / 323, 7500 482 / 463; 96 (768, 8192) 4750
+// 274 / 280, 7500 408 / 397; 112 (1792, 4096) 4750 284 / 301, 12500 709 / 709; 128 (896, 8000) 4750 292 / 296, 12500 727 / 720.  (Decided by the
+// rows alone, calls of 1300 to 2700 rows with 40 to 65 % of them candidates had one part, and lost 2 to 7 % by its detour.)
+constexpr int kDwSplitTiles = 128, kDwSplitMax = 16;
+constexpr int kDwSplitSlices = 8;   // of a part, at least
+struct DwSplit {
+  int most, tiles, V;   // parts at most; tiles of the gradient
+  int64_t rows;         // of the dhidden partials' buffer
+};
+__host__ __device__ inline bool dw_split_pays(int tiles, int64_t slices) {
+  return slices >= 2 * kDwSplitSlices && 2 * slices >= 3 * (tiles - 42);
+}
+__device__ __forceinline__ int dw_parts(const DwSplit& q, int n_cand, int dh_splits) {
+  const int slices = (n_cand + kDK - 1) / kDK, parts = min(q.most, slices / kDwSplitSlices);
+  const int64_t left = q.rows - int64_t(dh_splits) * ((n_cand + kTile - 1) / kTile * kTile);
+  return dw_split_pays(q.tiles, slices) && left >= int64_t(parts) * q.V ? max(parts, 1) : 1;
+}
+
+// Where the parts lie: behind the dhidden partials.
+__device__ __forceinline__ int64_t dw_part_offset(const int32_t* nact, int H) { return int64_t(nact[3]) * nact[1] * H; }
+
 // ------------------------------------------------------------------------------------------
 // forward: rows with a target, compacted
 // ------------------------------------------------------------------------------------------
@@ -143,8 +171,9 @@ __device__ __forceinline__ int dh_splits(int active_tiles, int tiles_h, int grid
 // every_weighted: an entropy or KL term is on) - then the other rows with a target.
 //   fidx[j] = row of position j (-1 past the count), nf = {rows with a target, that rounded up to a tile,
 //   candidates, that rounded up to a tile}; pos[t] = position of candidate t, -1 for every other row;
-//   nact = {candidates, rounded up, 0, splits}: nact[2] is the flag the forward pass raises when a stored
-//   exponential left its safe range (see k_fused_stats), nact[3] the split count of the dhidden contraction.
+//   nact = {candidates, rounded up, 0, splits, parts}: nact[2] is the flag the forward pass raises when a stored
+//   exponential left its safe range (see k_fused_stats), nact[3] the split count of the dhidden contraction, nact[4]
+//   the part count of dweight's.
 // token_rollout == null (forward-only call): no candidates, pos / nact are not written.
 // Ignored rows get their zero outputs here; a target >= V or a rollout index >= R raises its device error bit.
 template <int kAhead>
@@ -153,7 +182,7 @@ __global__ __launch_bounds__(1024) void k_compact_valid(
     const float* __restrict__ adv, const float* __restrict__ weight, int R, int every_weighted,
     int32_t* __restrict__ fidx, int32_t* __restrict__ nf, int32_t* __restrict__ pos, int32_t* __restrict__ nact,
     float* __restrict__ logprob, float* __restrict__ entropy, float* __restrict__ lse_out,
-    int32_t* __restrict__ err_flag, int tiles_h, int dh_grid, int slices, int64_t rows_max) {
+    int32_t* __restrict__ err_flag, int tiles_h, int dh_grid, int slices, int64_t rows_max, DwSplit split) {
   // Each of the 16 waves owns one contiguous range of rows, 64 at a time (coalesced reads, ballot + popcount inside the
   // wave): count, exchange the 16 counts, then place.  Latency bound: the loads of kAhead steps go out together, those that need
   // another's answer from clamped positions so that no branch stands between them, and the first kKept steps' classes stay in
@@ -265,6 +294,7 @@ __global__ __launch_bounds__(1024) void k_compact_valid(
       nact[1] = (total_c + kTile - 1) / kTile * kTile;
       nact[2] = 0;
       nact[3] = splits;
+      nact[4] = dw_parts(split, total_c, splits);
     }
   }
 }
@@ -892,39 +922,24 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_gemm_dh(
 // host knows the rows, not how many are candidates.
 constexpr int64_t kDwTileRows = 8192;
 
-// A gradient of few tiles leaves CUs idle however many tokens there are: up to kDwSplitTiles tiles the candidates' range is
-// split, each part leaves its sums in fp32 where the dhidden partials were (after k_scatter_dh), and k_sum_dw adds them up in
-// order.  It costs a launch and the parts' way to memory and back, so that the more tiles there are (and so the fewer parts), the more
-// rows it takes to pay: kDwSplitRows, and kDwSplitRowsPerTile for each tile.  Whole calls, one range / split, every row valid, by tiles: 16
-// (H = 64, V = 4000) 1500 rows 80.8 / 74.2 us, 4000 117 / 83, 16000 354 / 179; 32 (256, 8000) 1024 93.7 / 98.6, 1500 105 / 98, 16000 520 / 340; 57
-// (640, 4753) 1500 112.6 / 110.4, 2500 129 / 119, 16000 502 / 360; 72 (424, 9000) 1500 103.7 / 104.6, 2500 142 / 134, 16000 576 / 453; 125 (208,
-// 32000) 2500 193 / 198, 4000 277 / 275, 16000 912 / 844; 128 (896, 8000) 2500 171 / 174, 4000 209 / 202, 16000 698 / 632.
-constexpr int kDwSplitTiles = 128, kDwSplitMax = 16, kDwSplitSlices = 8;
-constexpr int64_t kDwSplitRows = 1280, kDwSplitRowsPerTile = 32;
-// So many parts are taken (device side): each has at least kDwSplitSlices slices, but for the last.
-__device__ __forceinline__ int dw_splits(int most, int n_cand) {
-  return max(min(most, (n_cand + kDK - 1) / kDK / kDwSplitSlices), 1);
-}
-
 // dW[m][h] = sum_t XT[m][t] hTc[h][t], hTc = the candidates' hidden rows times their scale     M = V, N = H, K = candidate tokens (padded)
-// Workgroup `block` of `blocks`.
+// Workgroup `block` of `blocks`.  parts > 1: dW is [parts][V][H].
 template <bool OUT_BF16, bool ACC>
 __device__ __forceinline__ void dw_tiles(int block, int blocks, uint16_t* smem, const uint16_t* __restrict__ dzT,
                                          const uint16_t* __restrict__ hTc, int V, int H, int tile0, int n_tiles, int tiles_v, int tiles_h,
-                                         int64_t T_pad, const int32_t* __restrict__ nact, int vec, int most, void* dW) {
+                                         int64_t T_pad, const int32_t* __restrict__ nact, int vec, int parts, void* dW) {
   // the contraction ends with the slice of the last candidate, not with its tile: the positions behind it are zeros
   // (whole calls at H = 1536, V = 151936: 600 tokens 949 -> 905 us, 1100 tokens 1376 -> 1357, 16384 tokens -0.4 %)
   const int slices = (nact[0] + kDK - 1) / kDK;
-  // split (most > 1): the parts are further rows of tiles, part by part; tv counts through them
-  const int parts = most > 1 ? dw_splits(most, nact[0]) : 1, per = (slices + parts - 1) / parts;
-  if (most > 1) n_tiles = parts * tiles_v * tiles_h;
+  // parts are further rows of tiles, part by part; tv counts through them
+  const int per = (slices + parts - 1) / parts;
   WavePos wp = wave_pos<true>();
   const int wm = wp.wm, wn = wp.wn;
   GemmStream<true, true, true, false> stream(kDK, kSlabElems, kDK, kSlabElems, 0);
   auto source = [&](int tv, int th) {
     const bool any = th * kTile + stream.wave * 32 < H;   // of the 32 columns that the wave requests
-    const int part = most > 1 ? tv / tiles_v : 0, begin = part * per, n = max(min(per, slices - begin), 0);
-    if (most > 1) tv -= part * tiles_v;
+    const int part = parts > 1 ? tv / tiles_v : 0, begin = part * per, n = max(min(per, slices - begin), 0);
+    if (parts > 1) tv -= part * tiles_v;
     return TileSrc{dzT + slab_offset(T_pad / 64, tv, begin), hTc + slab_offset(T_pad / 64, th, begin), int64_t(n) * kSlabElems * 2,
                    any ? int64_t(n) * kSlabElems * 2 : 0, 0u, 0u, max(n, 1)};   // no candidates: one slice of nothing
   };
@@ -941,7 +956,7 @@ __device__ __forceinline__ void dw_tiles(int block, int blocks, uint16_t* smem, 
   TileSrc src = source(tv, th);
   stream.start(src, smem);
   while (more) {
-    const int part = most > 1 ? tv / tiles_v : 0;
+    const int part = parts > 1 ? tv / tiles_v : 0;
     const int m0 = (tv - part * tiles_v) * kTile, n0 = th * kTile;
     wp.active = n0 + wn * 64 < H;
     wp.warm_a = warm_share(th, tiles_h);
@@ -1013,24 +1028,29 @@ __device__ __forceinline__ void dw_tiles(int block, int blocks, uint16_t* smem, 
 template <bool OUT_BF16, bool ACC>
 __global__ __launch_bounds__(kGemmNT, 2) void k_gemm_dw(
     const uint16_t* __restrict__ dzT, const uint16_t* __restrict__ hTc, int V, int H, int tile0, int n_tiles, int tiles_v, int tiles_h,
-    int64_t T_pad, const int32_t* __restrict__ nact, int vec, int most, void* dW) {
+    int64_t T_pad, const int32_t* __restrict__ nact, int vec, void* dW) {
   extern __shared__ __align__(16) uint16_t smem[];
-  dw_tiles<OUT_BF16, ACC>(blockIdx.x, gridDim.x, smem, dzT, hTc, V, H, tile0, n_tiles, tiles_v, tiles_h, T_pad, nact, vec, most, dW);
+  dw_tiles<OUT_BF16, ACC>(blockIdx.x, gridDim.x, smem, dzT, hTc, V, H, tile0, n_tiles, tiles_v, tiles_h, T_pad, nact, vec, 1, dW);
 }
 
 // Both contractions in one launch: the workgroups that walk dweight's tiles, then (from dw_blocks on, a multiple of 8) dhidden's, which
 // take the CUs that the former leave idle or are through with.  For H up to 256, where dhidden has at most 64 splits of a few tiles, and
-// for gradients of up to a tile per CU; calls of kDwTileRows rows and more fill the chip with either.  Whole calls, two launches / one: H = 208,
+// for gradients of up to a tile per CU; calls of kDwTileRows rows and more fill the chip with either, unless the gradient has few
+// tiles (up to kDwSplitTiles; its range in one part, two launches / one: H = 64, V = 4000 20000 rows 397 / 379 us, H = 896, V = 8000 801 / 727).  Whole calls, two launches / one: H = 208,
 // V = 152064 144 rows 133.7 / 122.7 us, 500 248 / 217, 2000 659 / 601, 6000 1593 / 1542; H = 256, V = 60000 500 120.6 / 117.9, 4000 470 / 444; H = 360,
 // V = 4249 1080 rows 83.9 / 70.9; H = 896, V = 5504 1001 103.5 / 97.3; H = 2048, V = 6678 240 108.5 / 107.1.  Where both fill the chip it is a matter of
 // how their last rounds fall: H = 896, V = 33846 500 rows 172.5 / 174.3, 4000 693 / 659; H = 640, V = 30000 4000 451 / 460; H = 3584, V = 32000 300 272 / 280.
-template <bool OUT_BF16, bool ACC>
+template <bool OUT_BF16, bool ACC, bool SPLIT>
 __global__ __launch_bounds__(kGemmNT, 2) void k_gemm_grads(
-    const uint16_t* __restrict__ dz, const uint16_t* __restrict__ W, int vK, float* __restrict__ dh_part, int dw_blocks,
+    const uint16_t* __restrict__ dz, const uint16_t* __restrict__ W, int vK, float* dh_part, int dw_blocks,
     const uint16_t* __restrict__ dzT, const uint16_t* __restrict__ hTc, int V, int H, int n_tiles, int tiles_v, int tiles_h,
     int64_t T_pad, const int32_t* __restrict__ nact, int vec, void* dW) {
   extern __shared__ __align__(16) uint16_t smem[];
-  if (int(blockIdx.x) < dw_blocks)
+  const int parts = SPLIT ? nact[4] : 1;   // uniform over the launch
+  if (int(blockIdx.x) < dw_blocks && parts > 1)
+    dw_tiles<false, false>(blockIdx.x, dw_blocks, smem, dzT, hTc, V, H, 0, parts * n_tiles, tiles_v, tiles_h, T_pad, nact, 1, parts,
+                           dh_part + dw_part_offset(nact, H));
+  else if (int(blockIdx.x) < dw_blocks)
     dw_tiles<OUT_BF16, ACC>(blockIdx.x, dw_blocks, smem, dzT, hTc, V, H, 0, n_tiles, tiles_v, tiles_h, T_pad, nact, vec, 1, dW);
   else
     dh_tile(int(blockIdx.x) - dw_blocks, smem, dz, W, V, vK, H, tiles_h, nact, dh_part);
@@ -1038,11 +1058,9 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_gemm_grads(
 
 // dweight from its parts: [parts][V][H] fp32, added up in order, eight entries (n of them) a thread.
 template <bool OUT_BF16, bool ACC>
-__global__ __launch_bounds__(256) void k_sum_dw(const float* __restrict__ part, const int32_t* __restrict__ nact, int most,
-                                                int64_t n, int vec, void* dW) {
+__device__ __forceinline__ void sum_dw(int64_t block, int parts, const float* __restrict__ part, int64_t n, int vec, void* dW) {
   constexpr int kDT = OUT_BF16 ? kBF16 : kF32;
-  const int parts = dw_splits(most, nact[0]);
-  const int64_t at = (int64_t(blockIdx.x) * 256 + threadIdx.x) * 8;
+  const int64_t at = (block * 256 + threadIdx.x) * 8;
   if (at >= n) return;
   f32x4_t lo = {0.f, 0.f, 0.f, 0.f}, hi = lo;
 #pragma unroll 4
@@ -1078,10 +1096,9 @@ __global__ __launch_bounds__(256) void k_sum_dw(const float* __restrict__ part, 
 
 // dhidden[t] = bf16(scale[pos[t]] * sum over the split-K partials of row pos[t]) or +0.  One workgroup per
 // row; the partials are summed in split order, so the result does not depend on scheduling.
-__global__ __launch_bounds__(256) void k_scatter_dh(const float* __restrict__ dh_part, const int32_t* __restrict__ pos,
-                                                    const int32_t* __restrict__ nact, int H,
-                                                    const float* __restrict__ scale, uint16_t* __restrict__ dhidden) {
-  const int64_t t = blockIdx.x;
+__device__ __forceinline__ void scatter_dh(int64_t t, const float* __restrict__ dh_part, const int32_t* __restrict__ pos,
+                                           const int32_t* __restrict__ nact, int H, const float* __restrict__ scale,
+                                           uint16_t* __restrict__ dhidden) {
   const int j = pos[t];
   uint16_t* out = dhidden + t * H;   // H % 8 == 0 and a 16-byte aligned base: rows are whole 16-byte vectors
   const float f = j < 0 ? 0.f : scale[j];
@@ -1115,6 +1132,23 @@ __global__ __launch_bounds__(256) void k_scatter_dh(const float* __restrict__ dh
     o.y = pack_bf16x2(acc.z * f, acc.w * f);
     *reinterpret_cast<uint2*>(out + k) = o;
   }
+}
+
+__global__ __launch_bounds__(256) void k_scatter_dh(const float* __restrict__ dh_part, const int32_t* __restrict__ pos,
+                                                    const int32_t* __restrict__ nact, int H,
+                                                    const float* __restrict__ scale, uint16_t* __restrict__ dhidden) {
+  scatter_dh(blockIdx.x, dh_part, pos, nact, H, scale, dhidden);
+}
+
+// The same, and dweight from its parts in the workgroups behind the first T, which leave at once where it is in one part.
+template <bool OUT_BF16, bool ACC>
+__global__ __launch_bounds__(256) void k_scatter_and_sum(const float* __restrict__ dh_part, const int32_t* __restrict__ pos,
+                                                         const int32_t* __restrict__ nact, int H, const float* __restrict__ scale,
+                                                         uint16_t* __restrict__ dhidden, unsigned T, int64_t n, int vec, void* dW) {
+  if (blockIdx.x < T)
+    scatter_dh(blockIdx.x, dh_part, pos, nact, H, scale, dhidden);
+  else if (nact[4] > 1)
+    sum_dw<OUT_BF16, ACC>(blockIdx.x - T, nact[4], dh_part + dw_part_offset(nact, H), n, vec, dW);
 }
 
 static aero_status set_lds(const void* fn) {
@@ -1185,10 +1219,14 @@ extern "C" aero_status aero_lmhead_logprob_fused(
         set_lds(reinterpret_cast<const void*>(k_fused_dz<false>)) != AERO_OK ||
         set_lds(reinterpret_cast<const void*>(k_fused_dz<true>)) != AERO_OK ||
         set_lds(reinterpret_cast<const void*>(k_gemm_dh)) != AERO_OK ||
-        set_lds(reinterpret_cast<const void*>(k_gemm_grads<true, true>)) != AERO_OK ||
-        set_lds(reinterpret_cast<const void*>(k_gemm_grads<true, false>)) != AERO_OK ||
-        set_lds(reinterpret_cast<const void*>(k_gemm_grads<false, true>)) != AERO_OK ||
-        set_lds(reinterpret_cast<const void*>(k_gemm_grads<false, false>)) != AERO_OK ||
+        set_lds(reinterpret_cast<const void*>(k_gemm_grads<true, true, true>)) != AERO_OK ||
+        set_lds(reinterpret_cast<const void*>(k_gemm_grads<true, true, false>)) != AERO_OK ||
+        set_lds(reinterpret_cast<const void*>(k_gemm_grads<true, false, true>)) != AERO_OK ||
+        set_lds(reinterpret_cast<const void*>(k_gemm_grads<true, false, false>)) != AERO_OK ||
+        set_lds(reinterpret_cast<const void*>(k_gemm_grads<false, true, true>)) != AERO_OK ||
+        set_lds(reinterpret_cast<const void*>(k_gemm_grads<false, true, false>)) != AERO_OK ||
+        set_lds(reinterpret_cast<const void*>(k_gemm_grads<false, false, true>)) != AERO_OK ||
+        set_lds(reinterpret_cast<const void*>(k_gemm_grads<false, false, false>)) != AERO_OK ||
         set_lds(reinterpret_cast<const void*>(k_gemm_dw<true, true>)) != AERO_OK ||
         set_lds(reinterpret_cast<const void*>(k_gemm_dw<true, false>)) != AERO_OK ||
         set_lds(reinterpret_cast<const void*>(k_gemm_dw<false, true>)) != AERO_OK ||
@@ -1217,12 +1255,16 @@ extern "C" aero_status aero_lmhead_logprob_fused(
                        reinterpret_cast<float*>(ws + p.off_gc), reinterpret_cast<float*>(ws + p.off_lsec),
                        reinterpret_cast<int32_t*>(ws + p.off_yc), reinterpret_cast<float*>(ws + p.off_ac),
                        reinterpret_cast<float*>(ws + p.off_bc), reinterpret_cast<float*>(ws + p.off_scale), dz, dzT};
+  const int total = p.tiles_v * tiles_h;
+  DwSplit split{1, total, V, dh_part_rows(p.T_pad, H, p.V_ld)};
+  if (bwd && total <= kDwSplitTiles && dw_split_pays(total, (T + kDK - 1) / kDK))   // if every row is a candidate
+    split.most = std::max(std::min(cus / total, kDwSplitMax), 1);
   const auto compact = T <= 2048 ? k_compact_valid<1> : k_compact_valid<4>;   // steps of 1024 rows at a time
   if (T > 0) {
     hipLaunchKernelGGL(compact, dim3(1), dim3(1024), 0, s, targets, T, p.T_pad, V,
                        bwd ? token_rollout : nullptr, adv, weight_rollout, R, (ent || kl_coef != 0.f) ? 1 : 0, fidx, nf,
                        bwd ? pos : nullptr, bwd ? nact : nullptr, logprob, entropy, lse, err_flag, tiles_h, grid_dh,
-                       p.V_ld / kDK, rows_max);
+                       p.V_ld / kDK, rows_max, split);
     hipLaunchKernelGGL(k_gather_rows, dim3(unsigned(p.T_pad / 4)), dim3(256), 0, s, Hp, Wp, H, fidx, targets, hf, zy);
     {
       const int n = p.tiles_v * tiles_t;
@@ -1248,7 +1290,7 @@ extern "C" aero_status aero_lmhead_logprob_fused(
   if (T == 0) {   // no forward kernel ran: an empty candidate set for the kernels below
     hipLaunchKernelGGL(compact, dim3(1), dim3(1024), 0, s, targets, T, p.T_pad, V, token_rollout, adv,
                        weight_rollout, R, 0, fidx, nf, pos, nact, logprob, entropy, lse, err_flag, tiles_h, grid_dh,
-                       p.V_ld / kDK, rows_max);
+                       p.V_ld / kDK, rows_max, split);
     hipLaunchKernelGGL(k_fused_rows<16>, dim3(unsigned(p.T_pad / 16)), dim3(kRowsNT), 0, s, p.tiles_v, p.T_pad, fidx, nf,
                        part_m, part_s, part_sz, zy, logprob, entropy, lse, terms);
   }
@@ -1268,34 +1310,31 @@ extern "C" aero_status aero_lmhead_logprob_fused(
 
   // ---- the two gradient contractions over the whole vocabulary ----
   // dz columns [V, V_ld) are zero, weight rows past V read as zeros: the contraction runs over the padded vocabulary
-  const int total = p.tiles_v * tiles_h;
   const int vec_dw = reinterpret_cast<uintptr_t>(dweight) % 16 == 0;   // rows are multiples of 16 bytes
   const bool dw_bf16 = dweight_dtype == AERO_BF16;
-  int most = 1;
-  if (total <= kDwSplitTiles && T >= std::max(kDwSplitRows, kDwSplitRowsPerTile * total))   // no more than the partials' buffer holds
-    most = int(std::min<int64_t>(std::min(cus / total, kDwSplitMax), dh_part_rows(p.T_pad, H, p.V_ld) / V));
-  const bool together = T > 0 && most == 1 && p.T_pad < kDwTileRows && (tiles_h == 1 || total <= cus);   // see k_gemm_grads
-  if (together) {
-    const auto kernel = dw_bf16 ? (accumulate ? k_gemm_grads<true, true> : k_gemm_grads<true, false>)
-                                : (accumulate ? k_gemm_grads<false, true> : k_gemm_grads<false, false>);
-    const int dw_blocks = int(walkers(xcd_grid(total)).x);
-    hipLaunchKernelGGL(kernel, dim3(unsigned(dw_blocks + grid_dh)), dim3(kGemmNT), kGemmLdsBytes, s, dz, Wp, p.V_ld, dh_acc, dw_blocks, dzT,
-                       hTc, V, H, total, p.tiles_v, tiles_h, p.T_pad, nact, vec_dw, dweight);
-  } else if (T > 0) {
-    hipLaunchKernelGGL(k_gemm_dh, dim3(unsigned(grid_dh)), dim3(kGemmNT), kGemmLdsBytes, s, dz, Wp, V, p.V_ld, H, tiles_h, nact, dh_acc);
-  }
-  if (T > 0)
-    hipLaunchKernelGGL(k_scatter_dh, dim3(unsigned(T)), dim3(256), 0, s, dh_acc, pos, nact, H, terms.scale, reinterpret_cast<uint16_t*>(dhidden));
-  if (together) return launch_status();
-  if (most > 1) {
-    const dim3 grid = walkers(xcd_grid(most * total));
-    hipLaunchKernelGGL((k_gemm_dw<false, false>), grid, dim3(kGemmNT), kGemmLdsBytes, s, dzT, hTc, V, H, 0, most * total, p.tiles_v, tiles_h,
-                       p.T_pad, nact, 1, most, dh_acc);
-    const auto sum = dw_bf16 ? (accumulate ? k_sum_dw<true, true> : k_sum_dw<true, false>)
-                             : (accumulate ? k_sum_dw<false, true> : k_sum_dw<false, false>);
-    const int64_t n = int64_t(V) * H;
-    hipLaunchKernelGGL(sum, dim3(unsigned((n / 8 + 255) / 256)), dim3(256), 0, s, dh_acc, nact, most, n, vec_dw, dweight);
+  uint16_t* const dh = reinterpret_cast<uint16_t*>(dhidden);
+  const bool together = total <= std::min(kDwSplitTiles, cus) || (p.T_pad < kDwTileRows && (tiles_h == 1 || total <= cus));
+  if (T > 0 && together) {   // see k_gemm_grads
+    auto launch = [&](auto out, auto acc) {
+      constexpr bool OUT = decltype(out)::value, ACC = decltype(acc)::value;
+      const int dw_blocks = int(walkers(xcd_grid(split.most * total)).x);
+      const auto grads = split.most > 1 ? k_gemm_grads<OUT, ACC, true> : k_gemm_grads<OUT, ACC, false>;
+      hipLaunchKernelGGL(grads, dim3(unsigned(dw_blocks + grid_dh)), dim3(kGemmNT), kGemmLdsBytes, s, dz, Wp, p.V_ld, dh_acc, dw_blocks,
+                         dzT, hTc, V, H, total, p.tiles_v, tiles_h, p.T_pad, nact, vec_dw, dweight);
+      const int64_t n = int64_t(V) * H;
+      if (split.most > 1)
+        hipLaunchKernelGGL((k_scatter_and_sum<OUT, ACC>), dim3(unsigned(T + (n / 8 + 255) / 256)), dim3(256), 0, s, dh_acc, pos, nact, H,
+                           terms.scale, dh, unsigned(T), n, vec_dw, dweight);
+      else
+        hipLaunchKernelGGL(k_scatter_dh, dim3(unsigned(T)), dim3(256), 0, s, dh_acc, pos, nact, H, terms.scale, dh);
+    };
+    if (dw_bf16) accumulate ? launch(std::true_type{}, std::true_type{}) : launch(std::true_type{}, std::false_type{});
+    else accumulate ? launch(std::false_type{}, std::true_type{}) : launch(std::false_type{}, std::false_type{});
     return launch_status();
+  }
+  if (T > 0) {
+    hipLaunchKernelGGL(k_gemm_dh, dim3(unsigned(grid_dh)), dim3(kGemmNT), kGemmLdsBytes, s, dz, Wp, V, p.V_ld, H, tiles_h, nact, dh_acc);
+    hipLaunchKernelGGL(k_scatter_dh, dim3(unsigned(T)), dim3(256), 0, s, dh_acc, pos, nact, H, terms.scale, dh);
   }
   // One launch where a workgroup walks (T == 0); where it has one tile, eight rounds of tiles a launch, so that the workgroups
   // that share operand slices stay close along K (32768 tokens at H = 3584, V = 152064, whole call: one launch 67.1, 16 rounds
@@ -1307,7 +1346,7 @@ extern "C" aero_status aero_lmhead_logprob_fused(
     const int n = total - t0 < per ? total - t0 : per;
     const dim3 grid = p.T_pad < kDwTileRows ? walkers(xcd_grid(n)) : dim3(unsigned(xcd_grid(n)));
     hipLaunchKernelGGL(kernel, grid, dim3(kGemmNT), kGemmLdsBytes, s, dzT, hTc, V, H, t0, n,
-                       p.tiles_v, tiles_h, p.T_pad, nact, vec_dw, 1, dweight);
+                       p.tiles_v, tiles_h, p.T_pad, nact, vec_dw, dweight);
   }
   return launch_status();
 }

@@ -57,7 +57,7 @@ def run_fused(gh, wl, h_bits, w_bits, targets, bwd=None, dweight_dtype=torch.flo
             dweight_accumulate=dw_into is not None and accumulate)
         out.update(loss=loss, clip_frac=clip, dhidden=dh, dweight=dw)
     torch.cuda.synchronize()
-    out["err"] = int(err.item())
+    out["err"], out["ws"] = int(err.item()), ws
     return out
 
 
@@ -163,7 +163,7 @@ def test_fused_dhidden_split_lengths(gh, T, H, V):
 
 @pytest.mark.parametrize("accumulate", [False, True])
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
-@pytest.mark.parametrize("T,H,V,off", [(1280, 64, 300, 0), (1300, 264, 1001, 1), (4400, 264, 5000, 0), (9000, 40, 77, 1)])
+@pytest.mark.parametrize("T,H,V,off", [(1280, 64, 300, 0), (1300, 264, 1001, 1), (2000, 264, 1001, 1), (4400, 264, 5000, 0), (9000, 40, 77, 1)])
 def test_fused_dweight_of_few_tiles(gh, T, H, V, off, dtype, accumulate):
     """Split over the candidates' range: parts of 8 slices and more, the last one shorter, one part only; a buffer off the 16-byte
     grid; added to what it holds.  Against the checker, with the bound of the other gradient tests: an entry's error is that of its
@@ -193,9 +193,9 @@ def test_fused_dweight_of_few_tiles(gh, T, H, V, off, dtype, accumulate):
     assert (rest[:off] == 7.0).all() and (rest[off + V * H:] == 7.0).all()
 
 
-@pytest.mark.parametrize("T,H,V", [(4400, 24, 32700), (4400, 264, 16129), (2100, 8, 4097)])
+@pytest.mark.parametrize("T,H,V", [(4400, 24, 32700), (14000, 24, 32700), (4400, 264, 16129), (2100, 8, 4097)])
 def test_fused_dweight_parts_add_up(gh, T, H, V):
-    """The most tiles that are split: the whole call against its tokens in calls of 900, which are not split, added up in one fp32
+    """The most tiles that are split, with too few candidates for it and with enough: the whole call against its tokens in calls of 900, which are not split, added up in one fp32
     buffer.  The operands are the same but for the scales of the hidden rows, which differ by the order in which a token's statistics are
     merged (calls of more than 4096 rows take another one): an ulp in fp32, and so here and there the next bf16 value, 2^-8 of one
     term.  If every term differed by that the sums would by 2^-8 of their norm; a part that is lost, doubled or in the wrong place
@@ -216,6 +216,36 @@ def test_fused_dweight_parts_add_up(gh, T, H, V):
     for tile in range(0, V, 256):   # tile by tile
         assert diff[tile:tile + 256].norm() <= 2.0 ** -8 * parts[tile:tile + 256].double().norm()
     assert (whole != 0).any()
+
+
+def few_candidates(gh, T, H, V, candidates):
+    """Rows that are a rollout each, the first `candidates` of them with a weight."""
+    wl, h, W = make(T, H, V, sigma_w=2.0 / np.sqrt(H))
+    rng = np.random.default_rng(T + candidates)
+    wl.R, wl.token_rollout = T, np.arange(T, dtype=np.int32)
+    weight = np.zeros(T, np.float32)
+    weight[:candidates] = 1.0 / T
+    return wl, h, W, dict(old=np.full(T, -6.0, np.float32), adv=rng.normal(size=T).astype(np.float32), weight=weight)
+
+
+def partial_rows(ws, T, H):
+    """The end of the workspace of a call of up to 2^18 rows and H <= 256: rows of partial sums, [4097 * 256 or fewer][H] fp32,
+    as bytes."""
+    rows = min(4097, 64 * -(-T // 256)) * 256
+    return ws[ws.numel() - rows * H * 4:].view(rows, H * 4)
+
+
+def test_fused_dweight_of_one_part_goes_straight_to_the_buffer(gh):
+    """A gradient of few tiles whose rows would do for a split but whose candidates do not: it takes no way through the partial
+    sums of dhidden (64 splits of one tile of tokens at most), and the same candidates give the same bits without the other rows."""
+    T, H, V, candidates = 3600, 64, 20000, 100
+    wl, h, W, bwd = few_candidates(gh, T, H, V, candidates)
+    out = run_fused(gh, wl, h, W, wl.targets, bwd=bwd, ws_byte=255)
+    assert (partial_rows(out["ws"], T, H)[64 * 256:] == 255).all()
+    wl.T, wl.token_rollout = candidates, wl.token_rollout[:candidates]
+    alone = run_fused(gh, wl, h[:candidates], W, wl.targets[:candidates], bwd=dict(bwd, old=bwd["old"][:candidates]))
+    assert (alone["dweight"] != 0).any() and torch.equal(out["dweight"], alone["dweight"])
+    assert torch.equal(out["dhidden"][:candidates], alone["dhidden"]) and not out["dhidden"][candidates:].any()
 
 
 @pytest.mark.parametrize("T,H,V", [(300, 200, 70013), (700, 520, 3000), (90, 256, 66000), (1200, 8, 40)])
