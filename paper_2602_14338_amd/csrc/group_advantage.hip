@@ -388,23 +388,26 @@ __global__ __launch_bounds__(kPlaceNT) void k_place(
   compact_body(q, lane, group_offsets, keep_mask, out, R, kept_index);
 }
 
-// All of it in one launch: a wave per group, up to 8 in a workgroup (16 or 4: 5.1 us for 256 groups of 8 to 32 where 8 take 4.7).  How many rollouts a group keeps follows from its size
+// All of it in one launch: a wave per group, up to WAVES in a workgroup.  Eight (16 or 4: 5.1 us for 256 groups of 8 to 32 where 8
+// take 4.7) but for more than kCurateManyQ groups, where half as many workgroups read the rewards in front and each goes over
+// the groups in front in half the turns: 8 / 16 waves, with rejection and without, 2048 groups of 2 5.39 / 5.28, 5.19 / 5.06 us; 1700 of 3 5.72 /
+// 5.55, 5.35 / 5.20; 1500 of 5 5.55 / 5.64, 5.18 / 5.19; 850 of 8 5.10 / 5.22, 4.74 / 4.72; 512 of 8 4.43 / 4.80, 4.11 / 4.30.  How many rollouts a group keeps follows from its size
 // and its count of correct rollouts alone, so a workgroup counts what lies in front of its groups itself, from the
 // rewards (a bit per rollout in LDS, a thread per group), while its own groups' loads are under way; nothing is passed
 // between workgroups.  Bound by latency: kernel arguments, offsets, rewards, and the instructions themselves, which come
 // from memory once per launch.
-constexpr int kCurateWaves = 8, kCurateNT = kCurateWaves * kWave;
-constexpr int kCurateR = 8192, kCurateQ = 2048;
-__global__ __launch_bounds__(kCurateNT) void k_curate(
+constexpr int kCurateR = 8192, kCurateQ = 2048, kCurateManyQ = 1536;
+template <int WAVES>
+__global__ __launch_bounds__(WAVES* kWave) void k_curate(
     const float* __restrict__ rewards, const int32_t* __restrict__ lengths,
     const int32_t* __restrict__ group_offsets, const uint32_t* __restrict__ keys, int Q, int R,
     aero_adv_params p, float* __restrict__ adv, float* __restrict__ weight, uint8_t* __restrict__ keep_mask,
     int32_t* __restrict__ kept_index, int32_t* __restrict__ kept_offsets, uint8_t* __restrict__ zero_var,
     uint8_t* __restrict__ category, int32_t* __restrict__ err_flag) {
-  constexpr int LOADS = kCurateR / kCurateNT;   // rewards per thread, all in flight at once
-  __shared__ uint64_t ones[LOADS * kCurateWaves];   // bit i % 64 of word i / 64: reward i is exactly 1
-  __shared__ int front[kCurateWaves], own[kCurateWaves];
-  __shared__ __align__(16) uint64_t ranks[kCurateWaves][kWave];
+  constexpr int NT = WAVES * kWave, LOADS = kCurateR / NT;   // rewards per thread, all in flight at once
+  __shared__ uint64_t ones[LOADS * WAVES];   // bit i % 64 of word i / 64: reward i is exactly 1
+  __shared__ int front[WAVES], own[WAVES];
+  __shared__ __align__(16) uint64_t ranks[WAVES][kWave];
   const int tid = threadIdx.x, lane = tid % kWave, wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int waves = blockDim.x / kWave;
   const int q0 = blockIdx.x * waves, q = q0 + wave;
@@ -412,9 +415,9 @@ __global__ __launch_bounds__(kCurateNT) void k_curate(
   // past the end is not looked at.
   int ahead_b = 0, ahead_e = 0;
   float x[LOADS];
-  if (q0 > 0 && R > 0) {   // uniform; then there are kCurateNT threads
+  if (q0 > 0 && R > 0) {   // uniform; then there are NT threads
 #pragma unroll
-    for (int u = 0; u < LOADS; ++u) x[u] = rewards[min(u * kCurateNT + tid, R - 1)];
+    for (int u = 0; u < LOADS; ++u) x[u] = rewards[min(u * NT + tid, R - 1)];
     const int at = min(tid, q0 - 1);
     ahead_b = group_offsets[at];
     ahead_e = group_offsets[at + 1];
@@ -428,15 +431,15 @@ __global__ __launch_bounds__(kCurateNT) void k_curate(
 #pragma unroll
     for (int u = 0; u < LOADS; ++u) {
       const uint64_t bits = __ballot(x[u] == 1.f);
-      if (lane == 0) ones[u * kCurateWaves + wave] = bits;
+      if (lane == 0) ones[u * WAVES + wave] = bits;
     }
     __syncthreads();
 #pragma unroll 1
-    for (int at = tid; at - tid < q0; at += kCurateNT) {   // uniform
+    for (int at = tid; at - tid < q0; at += NT) {   // uniform
       GroupRange g = group_range(ahead_b, ahead_e, R);
       if (at >= q0) g.e = g.b;
-      if (at - tid + kCurateNT < q0) {   // the next one's
-        const int next = min(at + kCurateNT, q0 - 1);
+      if (at - tid + NT < q0) {   // the next one's
+        const int next = min(at + NT, q0 - 1);
         ahead_b = group_offsets[next];
         ahead_e = group_offsets[next + 1];
       }
@@ -489,8 +492,8 @@ extern "C" aero_status aero_group_advantage(
   if (R > 0 && (!rewards || !lengths || !adv || !weight || !keep_mask || !kept_index)) return AERO_ERR_NULL;
   hipStream_t s = as_stream(stream);
   if (Q > 0 && Q <= kCurateQ && R <= kCurateR) {   // see the top
-    const int waves = Q < kCurateWaves ? Q : kCurateWaves;
-    hipLaunchKernelGGL(k_curate, dim3(unsigned((Q + waves - 1) / waves)), dim3(unsigned(waves * kWave)), 0, s, rewards, lengths,
+    const int most = Q > kCurateManyQ ? 16 : 8, waves = Q < most ? Q : most;
+    hipLaunchKernelGGL(most == 16 ? k_curate<16> : k_curate<8>, dim3(unsigned((Q + waves - 1) / waves)), dim3(unsigned(waves * kWave)), 0, s, rewards, lengths,
                        group_offsets, keep_priority, Q, R, *p, adv, weight, keep_mask, kept_index, kept_offsets, group_zero_var,
                        group_category, err_flag);
     return launch_status();

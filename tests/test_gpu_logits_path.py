@@ -124,11 +124,12 @@ def test_group_advantage_placement_forms(gh, Q, lo, hi):
 
 
 @pytest.mark.parametrize("Q,R", [(1, 64), (1, 65), (7, 448), (8, 512), (9, 513), (15, 300), (16, 1024), (17, 1025), (33, 8191), (500, 8192), (500, 8193),
+                                 (1536, 8192), (1537, 8191), (2047, 2500), (2048, 8192),
                                  (2047, 32768), (2048, 32768), (2048, 32769), (2049, 20000), (1, 8192), (1, 8193), (129, 8256),
                                  (129, 8257), (512, 32768), (511, 32768)])
 def test_group_advantage_one_launch(gh, Q, R):
-    """One launch up to 2048 groups and 8192 rollouts: around a workgroup's 8 groups, the rollouts that a workgroup's loads cover, the
-    last call of each form and the first of the other; some groups wider than a wave."""
+    """One launch up to 2048 groups and 8192 rollouts: around a workgroup's 8 groups (16 from 1537 groups on), the rollouts that a
+    workgroup's loads cover, the last call of each form and the first of the other; some groups wider than a wave."""
     rng = np.random.default_rng(Q * 100003 + R)
     cuts = np.sort(rng.integers(0, R + 1, size=Q - 1))
     off = np.concatenate([[0], cuts, [R]]).astype(np.int32)      # empty groups and long ones by chance
