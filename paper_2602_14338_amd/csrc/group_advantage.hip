@@ -5,16 +5,18 @@
 // so any group size works; counts are integers, the few floating-point statistics are formed
 // in fp64 from those counts and rounded once to fp32.  The call is latency bound, so what counts is
 // launches, dependent loads and exchanges between lanes:
-//   up to 2048 groups and 8192 rollouts (a step)    k_curate: one launch, nothing passed between workgroups
+//   up to 2048 groups and 8192 rollouts (a step)    k_curate: one launch, nothing passed between workgroups; without rejection
+//                                                   up to 32768 rollouts of groups that fit a wave on average
 //   up to 8192 groups                               k_group (c, category, keep mask, advantages, weights), then k_place:
 //                                                   every workgroup adds up the kept counts in front of its groups
 //                                                   itself, so no scan stands between
 //   more                                            k_group, k_scan (exclusive scan of the kept counts, one
 //                                                   workgroup) and k_compact: the counts would be read too often.
 // Whole calls, k_group + k_place / k_curate, without rejection and with it: 256 groups of 16 6.6 / 4.2, 6.6 / 5.0 us; 256 of 32 6.6 / 4.2,
-// 6.5 / 5.2; 64 of 128 6.6 / 6.0, 10.6 / 10.5; 16 of 500 12.8 / 12.6, 84 / 84.  Over 8192 rollouts, where a thread has 64 of the rewards in front to
-// load: 300 of 30 6.6 / 7.4, 8.0 / 8.4; 600 of 20 6.6 / 7.6, 7.2 / 8.2; 1000 of 32 6.6 / 7.7, 7.3 / 8.4; 2048 of 9 6.8 / 8.4, 7.2 / 8.9; 500 of 64
-// 6.6 / 7.3, 7.0 / 8.4.
+// 6.5 / 5.2; 64 of 128 6.6 / 6.0, 10.6 / 10.5; 16 of 500 12.8 / 12.6, 84 / 84.  Over 8192 rollouts, where a thread of 16 waves has 32 of the
+// rewards in front to load, two launches are as fast where the host launches quickly and lose where it does not: 300 of 30 7.3 / 6.5, 7.7 / 7.5; 600 of 20
+// 7.3 / 6.7, 7.5 / 7.3; 1000 of 32 7.4 / 6.6, 7.4 / 7.4; 2048 of 9 7.3 / 7.0, 7.5 / 7.7; 500 of 64 7.2 / 6.6, 7.4 / 7.8; on another box, without rejection,
+// 6.6 / 6.7, 6.6 / 6.8, 6.6 / 6.8, 6.8 / 7.2.
 // k_place / k_scan + k_compact: 400 groups (7831 rollouts) 9.0 / 11.4, 3000 (60325) 10.2 / 12.9, 4000 (80187) 11.0 / 14.5, 8000
 // (159965) 18.1 / 24.1.  (Counting the bytes of the keep mask instead, up to 8192 rollouts, takes as long, and reads
 // bytes that nobody wrote where offsets start above 0.)
@@ -396,15 +398,16 @@ __global__ __launch_bounds__(kPlaceNT) void k_place(
 // rewards (a bit per rollout in LDS, a thread per group), while its own groups' loads are under way; nothing is passed
 // between workgroups.  Bound by latency: kernel arguments, offsets, rewards, and the instructions themselves, which come
 // from memory once per launch.
-constexpr int kCurateR = 8192, kCurateQ = 2048, kCurateManyQ = 1536;
-template <int WAVES>
+constexpr int kCurateR = 8192, kCurateWideR = 32768, kCurateQ = 2048, kCurateManyQ = 1536;
+// LOADS: rewards per thread, all in flight at once; R <= LOADS * WAVES * 64 unless there is one workgroup.
+template <int WAVES, int LOADS>
 __global__ __launch_bounds__(WAVES* kWave) void k_curate(
     const float* __restrict__ rewards, const int32_t* __restrict__ lengths,
     const int32_t* __restrict__ group_offsets, const uint32_t* __restrict__ keys, int Q, int R,
     aero_adv_params p, float* __restrict__ adv, float* __restrict__ weight, uint8_t* __restrict__ keep_mask,
     int32_t* __restrict__ kept_index, int32_t* __restrict__ kept_offsets, uint8_t* __restrict__ zero_var,
     uint8_t* __restrict__ category, int32_t* __restrict__ err_flag) {
-  constexpr int NT = WAVES * kWave, LOADS = kCurateR / NT;   // rewards per thread, all in flight at once
+  constexpr int NT = WAVES * kWave;
   __shared__ uint64_t ones[LOADS * WAVES];   // bit i % 64 of word i / 64: reward i is exactly 1
   __shared__ int front[WAVES], own[WAVES];
   __shared__ __align__(16) uint64_t ranks[WAVES][kWave];
@@ -491,9 +494,13 @@ extern "C" aero_status aero_group_advantage(
   if (Q > 0 && (!group_zero_var || !group_category)) return AERO_ERR_NULL;
   if (R > 0 && (!rewards || !lengths || !adv || !weight || !keep_mask || !kept_index)) return AERO_ERR_NULL;
   hipStream_t s = as_stream(stream);
-  if (Q > 0 && Q <= kCurateQ && R <= kCurateR) {   // see the top
-    const int most = Q > kCurateManyQ ? 16 : 8, waves = Q < most ? Q : most;
-    hipLaunchKernelGGL(most == 16 ? k_curate<16> : k_curate<8>, dim3(unsigned((Q + waves - 1) / waves)), dim3(unsigned(waves * kWave)), 0, s, rewards, lengths,
+  const bool few = R <= kCurateR, ranks = p->reject_enable;
+  if (Q > 0 && Q <= kCurateQ && (few || (R <= kCurateWideR && R <= kWave * Q && !ranks))) {   // see the top
+    const int most = few && Q <= kCurateManyQ ? 8 : 16, waves = Q < most ? Q : most;
+    const auto kernel = !few        ? k_curate<16, kCurateWideR / (16 * kWave)>
+                        : most == 8 ? k_curate<8, kCurateR / (8 * kWave)>
+                                    : k_curate<16, kCurateR / (16 * kWave)>;
+    hipLaunchKernelGGL(kernel, dim3(unsigned((Q + waves - 1) / waves)), dim3(unsigned(waves * kWave)), 0, s, rewards, lengths,
                        group_offsets, keep_priority, Q, R, *p, adv, weight, keep_mask, kept_index, kept_offsets, group_zero_var,
                        group_category, err_flag);
     return launch_status();

@@ -159,3 +159,18 @@ def assert_loss(got, loss_ref, loss_terms, strict=False):
                               "1e-4 relative" if ratio <= CANCEL_RATIO_STRICT else "1e-4 relative + 2^-22 sum|term|",
                               ratio))
     return ratio
+
+
+def launches(call):
+    """How many kernels a call launches: the nodes of a graph that records it (which is not run).  Its tensors have to exist."""
+    import ctypes as C
+    call()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        call()
+    with open("/proc/self/maps") as f:
+        hip = C.CDLL(next(line.split()[-1] for line in f if "libamdhip64" in line))
+    n = C.c_size_t(0)
+    assert hip.hipGraphGetNodes(C.c_void_p(graph.raw_cuda_graph()), None, C.byref(n)) == 0
+    return n.value

@@ -128,8 +128,9 @@ def test_group_advantage_placement_forms(gh, Q, lo, hi):
                                  (2047, 32768), (2048, 32768), (2048, 32769), (2049, 20000), (1, 8192), (1, 8193), (129, 8256),
                                  (129, 8257), (512, 32768), (511, 32768)])
 def test_group_advantage_one_launch(gh, Q, R):
-    """One launch up to 2048 groups and 8192 rollouts: around a workgroup's 8 groups (16 from 1537 groups on), the rollouts that a
-    workgroup's loads cover, the last call of each form and the first of the other; some groups wider than a wave."""
+    """One launch up to 2048 groups and 8192 rollouts, without rejection up to 32768 of at most 64 a group on average: around a
+    workgroup's 8 groups (16 from 1537 groups on), the rollouts that a workgroup's loads cover, the last call of each form and the
+    first of the other; some groups wider than a wave."""
     rng = np.random.default_rng(Q * 100003 + R)
     cuts = np.sort(rng.integers(0, R + 1, size=Q - 1))
     off = np.concatenate([[0], cuts, [R]]).astype(np.int32)      # empty groups and long ones by chance
@@ -138,6 +139,20 @@ def test_group_advantage_one_launch(gh, Q, R):
     keys = rng.integers(0, 50, size=R).astype(np.uint32)
     for params in (dict(reject_enable=1, posterior_mode=1), dict(reject_enable=1, k_ratio=2), dict(), dict(posterior_mode=1)):
         check_groups(gh, (rewards, lengths, off, keys), params)
+
+
+@pytest.mark.parametrize("Q,R,rejection,launches", [(256, 8192, 1, 1), (300, 8193, 1, 2), (300, 8193, 0, 1), (512, 32768, 0, 1),
+                                                    (511, 32768, 0, 2), (1000, 32769, 0, 2), (2048, 8192, 0, 1), (2049, 8192, 0, 2),
+                                                    (8193, 20000, 0, 3)])
+def test_group_advantage_launches(gh, Q, R, rejection, launches):
+    """The call is bound by its launches; the results of every form are in test_group_advantage_one_launch."""
+    import paper_2602_14338_amd as aero
+    off = np.linspace(0, R, Q + 1).astype(np.int32)
+    ints = [gh.dev(np.ones(R, np.int32)), gh.dev(off), gh.dev(np.arange(R, dtype=np.int32))]
+    f, b = (lambda n: torch.zeros(n, device=gh.DEV)), (lambda n: torch.zeros(n, dtype=torch.uint8, device=gh.DEV))
+    out = [f(R), f(R), b(R), torch.zeros_like(ints[0]), torch.zeros_like(ints[1]), b(Q), b(Q), torch.zeros_like(ints[0][:1])]
+    rewards = f(R)
+    assert gh.launches(lambda: aero.aero_group_advantage(rewards, *ints, Q, R, aero.AdvParams(reject_enable=rejection), *out)) == launches
 
 
 @pytest.mark.parametrize("mask_off", [0, 1, 2, 3])
