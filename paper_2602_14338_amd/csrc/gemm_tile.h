@@ -529,11 +529,19 @@ __device__ __forceinline__ rsrc_words_t rsrc_words(const uint16_t* base, uint32_
   return rsrc_words_t{uint32_t(__builtin_amdgcn_readfirstlane(uint32_t(b))), uint32_t(__builtin_amdgcn_readfirstlane(uint32_t(b >> 32))) & 0xffffu,
                       uint32_t(__builtin_amdgcn_readfirstlane(bytes)), 0x00020000u};
 }
-// buffer_load_dwordx4 ... lds: 16 bytes a lane, to LDS byte address `to` (uniform) + 16 lane.  It has no destination register
-// that the compiler could take for written; the loop waits for it by vmcnt.
+// buffer_load_dwordx4 ... lds: 16 bytes a lane, to LDS byte address `to` (uniform, in M0) + 16 lane.  It has no destination register
+// that the compiler could take for written; the loop waits for it by vmcnt.  What the compiler does not know of it:
+//   M0, which its own loads into LDS use as well, is written: declared, as an output, since it takes no clobber of it.  (As an
+//     input that the compiler puts there, the calls of 16384 tokens and more were 0.6 % slower.)
+//   LDS is written, later.  That is not declared (a "memory" clobber would hold back the step's reads of other stages): a stage is never
+//     read and requested between the same two calls of landed, whose wait, barrier and fence order the ones behind the others.
+//   A scalar register that a vector instruction wrote (v_readfirstlane) may be read by a load only five wait states later: the
+//     descriptors are formed once, in front of the loop, and the wait states follow them there (descriptors_settled).
 __device__ __forceinline__ void request_lds16(rsrc_words_t r, uint32_t to, uint32_t off) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(to), "v"(off), "s"(r));
+  uint32_t m0;
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %3, 0 offen lds" : "=&{m0}"(m0) : "s"(to), "v"(off), "s"(r));
 }
+__device__ __forceinline__ void descriptors_settled(rsrc_words_t a, rsrc_words_t b) { asm volatile("s_nop 4" ::"s"(a), "s"(b)); }
 
 struct RingSrc {
   const uint16_t *a_base, *b_base;   // the K range's first slab of the tile, the first K row
@@ -564,8 +572,7 @@ struct GemmRing {
   }
 
   // Requests step kt: wave w blocks 2 w and 2 w + 1 of A and rows 4 w .. 4 w + 3 of B.
-  __device__ __forceinline__ void issue(const RingSrc& t, int kt) const {
-    const rsrc_words_t ra = rsrc_words(t.a_base, t.a_bytes), rb = rsrc_words(t.b_base, t.b_bytes);
+  __device__ __forceinline__ void issue(const RingSrc& t, rsrc_words_t ra, rsrc_words_t rb, int kt) const {
     const uint32_t to = lds + uint32_t(kt & (kRing - 1)) * kStepBytes + wave * (kPer * 1024);
     // past every operand's end (which lies below 4 GiB by more than that), which gives zeros and moves nothing
     const uint32_t a = wave * 32 < t.a_rows ? uint32_t(kt >> 1) * (kSlabElems * 2) + uint32_t(kt & 1) * 1024 + wave * 4096 : ~0u - 8191;
@@ -591,12 +598,14 @@ struct GemmRing {
     static_assert(kRing == 4, "the last steps below");
     const int nk = t.nk;
     acc_zero(acc);
+    const rsrc_words_t ra = rsrc_words(t.a_base, t.a_bytes), rb = rsrc_words(t.b_base, t.b_bytes);
+    descriptors_settled(ra, rb);
 #pragma unroll
-    for (int kt = 0; kt < kRing - 1; ++kt) issue(t, kt);
+    for (int kt = 0; kt < kRing - 1; ++kt) issue(t, ra, rb, kt);
     landed<2 * kStep>();
     if (!pos.active) {   // uniform over the wave
       for (int kt = 0; kt < nk - 3; ++kt) {
-        issue(t, kt + 3);
+        issue(t, ra, rb, kt + 3);
         landed<2 * kStep>();
       }
       landed<kStep>();
@@ -625,7 +634,7 @@ struct GemmRing {
       __builtin_amdgcn_sched_barrier(0);
       frags_mma<true>(a1, b_before, 1, acc);
       __builtin_amdgcn_sched_barrier(0);
-      if (more) issue(t, kt + 3);
+      if (more) issue(t, ra, rb, kt + 3);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int i = 0; i < kFragBlocks; ++i) a1[i] = lds_fragment(fa + (kFragBlocks + i) * 1024);
