@@ -99,12 +99,11 @@ static void dispatch_nt(const void* logits, int64_t T, int V, int64_t ld, const 
   // 512 / 1024 threads: 90 rows of 151936 bf16 16.3 / 12.4 us, 200 17.2 / 13.1, 256 17.8 / 14.6; of 50257 7.4 / 6.6, 7.6 / 6.8, 7.8 / 6.9; of 154295
   // fp32 27.7 / 18.4, 30.6 / 22.1, 32.0 / 25.6; of 262144 fp16 25.4 / 18.4, 26.8 / 20.3, 27.7 / 23.5; of 262144 8-bit 18.1 / 16.3, 18.8 / 16.7,
   // 19.0 / 16.9.  330 rows 0.93-1.06 of the rate, 520 0.91-1.03, 1500 0.98-1.02.  (Eight loads a thread instead of four: 0.92-1.09.)
-  constexpr int64_t kCus = 256;
   const int per_vec = VEC ? Storage<DT>::kPerVec : 1;
   const int64_t work = (V + per_vec - 1) / per_vec;
   if (work <= 4 * 64) launch_fwd<64, DT, VEC>(logits, T, V, ld, targets, row_active, logprob, entropy, lse, err_flag, s);
   else if (work <= 16 * 256) launch_fwd<256, DT, VEC>(logits, T, V, ld, targets, row_active, logprob, entropy, lse, err_flag, s);
-  else if (T <= kCus) launch_fwd<1024, DT, VEC>(logits, T, V, ld, targets, row_active, logprob, entropy, lse, err_flag, s);
+  else if (T <= compute_units()) launch_fwd<1024, DT, VEC>(logits, T, V, ld, targets, row_active, logprob, entropy, lse, err_flag, s);
   else launch_fwd<512, DT, VEC>(logits, T, V, ld, targets, row_active, logprob, entropy, lse, err_flag, s);
 }
 
