@@ -145,7 +145,7 @@ __device__ __forceinline__ int dh_splits(int active_tiles, int tiles_h, int grid
 // 274 / 280, 7500 408 / 397; 112 (1792, 4096) 4750 284 / 301, 12500 709 / 709; 128 (896, 8000) 4750 292 / 296, 12500 727 / 720.  (Decided by the
 // rows alone, calls of 1300 to 2700 rows with 40 to 65 % of them candidates had one part, and lost 2 to 7 % by its detour.)
 constexpr int kDwSplitTiles = 128, kDwSplitMax = 16;
-constexpr int kDwSplitSlices = 8;   // of a part, at least
+constexpr int kDwSplitSlices = 8;   // of a part, at least, but for the last
 struct DwSplit {
   int most, tiles, V;   // parts at most; tiles of the gradient
   int64_t rows;         // of the dhidden partials' buffer
@@ -156,7 +156,9 @@ __host__ __device__ inline bool dw_split_pays(int tiles, int64_t slices) {
 __device__ __forceinline__ int dw_parts(const DwSplit& q, int n_cand, int dh_splits) {
   const int slices = (n_cand + kDK - 1) / kDK, parts = min(q.most, slices / kDwSplitSlices);
   const int64_t left = q.rows - int64_t(dh_splits) * ((n_cand + kTile - 1) / kTile * kTile);
-  return dw_split_pays(q.tiles, slices) && left >= int64_t(parts) * q.V ? max(parts, 1) : 1;
+  if (parts < 2 || !dw_split_pays(q.tiles, slices) || left < int64_t(parts) * q.V) return 1;
+  const int per = (slices + parts - 1) / parts;
+  return (slices + per - 1) / per;   // none of them empty (97 slices in 12 parts are ten of 9, one of 7 and nothing)
 }
 
 // Where the parts lie: behind the dhidden partials.

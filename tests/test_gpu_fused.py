@@ -248,6 +248,20 @@ def test_fused_dweight_of_one_part_goes_straight_to_the_buffer(gh):
     assert torch.equal(out["dhidden"][:candidates], alone["dhidden"]) and not out["dhidden"][candidates:].any()
 
 
+@pytest.mark.parametrize("slices,parts", [(17, 2), (81, 9), (97, 11), (113, 13)])
+def test_fused_dweight_has_no_empty_part(gh, slices, parts):
+    """16 tiles: so many parts as have 8 slices of 64 candidates each, but none that the rounding up of the others' length leaves
+    nothing for: the partial sums end with the last of them (they lie behind dhidden's, of whole tiles of tokens)."""
+    T, H, V, candidates = slices * 64, 64, 3999, slices * 64 - 5
+    wl, h, W, bwd = few_candidates(gh, T, H, V, candidates)
+    ref = orc.lmhead_fused(h, W, wl.targets, bwd["old"], wl.token_rollout, bwd["adv"], bwd["weight"], np.float32(0.2), np.float32(0.2), 1.0)
+    out = run_fused(gh, wl, h, W, wl.targets, bwd=bwd, ws_byte=255)
+    assert rowwise_close(out["dweight"].double().cpu().numpy(), ref["dweight"])
+    written = (partial_rows(out["ws"], T, H) != 255).any(dim=1).nonzero()[-1].item() + 1
+    tiles_end = written - parts * V
+    assert tiles_end > 0 and tiles_end % (-(-candidates // 256) * 256) == 0
+
+
 @pytest.mark.parametrize("T,H,V", [(300, 200, 70013), (700, 520, 3000), (90, 256, 66000), (1200, 8, 40)])
 @pytest.mark.parametrize("accumulate", [False, True])
 def test_fused_gradients_in_one_launch(gh, T, H, V, accumulate):
