@@ -165,8 +165,8 @@ def test_fused_dhidden_split_lengths(gh, T, H, V):
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("T,H,V,off", [(1280, 64, 300, 0), (1300, 264, 1001, 1), (2000, 264, 1001, 1), (4400, 264, 5000, 0), (9000, 40, 77, 1)])
 def test_fused_dweight_of_few_tiles(gh, T, H, V, off, dtype, accumulate):
-    """Split over the candidates' range: parts of 8 slices and more, the last one shorter, one part only; a buffer off the 16-byte
-    grid; added to what it holds.  Against the checker, with the bound of the other gradient tests: an entry's error is that of its
+    """A range that may be split: one part (too few candidates in the first two, stored straight into the buffer), several, the last one
+    shorter; a buffer off the 16-byte grid; added to what it holds.  Against the checker, with the bound of the other gradient tests: an entry's error is that of its
     operands' rounding (2^-9 relative each, uncorrelated), 0.23-0.28 % of the row's largest entry in the median row and up to 0.70 % of
     it over 5000 rows of 264.  (Rows of 24 entries have a smaller largest one: over 32700 of them the tail touches the bound, 1.00 %, with
     one range as with two, so that the shape with the most tiles is left to the comparison of the two in test_fused_dweight_parts_add_up.)"""
@@ -266,15 +266,40 @@ def test_fused_dweight_has_no_empty_part(gh, slices, parts):
 @pytest.mark.parametrize("accumulate", [False, True])
 def test_fused_gradients_in_one_launch(gh, T, H, V, accumulate):
     """Both contractions in one launch (one tile of H, or few tiles): more dweight tiles than CUs and fewer, ragged ones, a dweight in
-    bf16 and in fp32, into a fresh buffer and on top of zeros, which comes to the same."""
+    bf16 and in fp32, into a fresh buffer (the same bits as before) and on top of a constant (the sum, rounded once; grad_scale lifts the
+    gradient to where that rounding does not hide it)."""
     wl, h, W = make(T, H, V, sigma_w=2.0 / np.sqrt(H))
     ref, out = check_bwd(gh, wl, h, W, dict(), dweight_dtype=torch.bfloat16 if V % 2 else torch.float32)
     ga = orc.group_advantage(wl.rewards, wl.lengths, wl.group_offsets, wl.keep_priority, AdvParams())
     old = ai.draw_old_logprob(orc.lmhead_fused(h, W, wl.targets)["logprob"], wl.seed, sigma=0.3)
-    into = torch.zeros_like(out["dweight"]) if accumulate else torch.full_like(out["dweight"], 7.0)
-    again = run_fused(gh, wl, h, W, wl.targets, bwd=dict(old=old, adv=ga["adv"].astype(np.float32), weight=ga["weight"].astype(np.float32)),
-                      dweight_dtype=out["dweight"].dtype, dw_into=into, accumulate=accumulate)
-    assert torch.equal(into, out["dweight"]) and torch.equal(again["dhidden"], out["dhidden"])
+    bwd = dict(old=old, adv=ga["adv"].astype(np.float32), weight=ga["weight"].astype(np.float32))
+    if not accumulate:
+        into = torch.full_like(out["dweight"], 7.0)
+        again = run_fused(gh, wl, h, W, wl.targets, bwd=bwd, dweight_dtype=into.dtype, dw_into=into, accumulate=False)
+        assert torch.equal(into, out["dweight"]) and torch.equal(again["dhidden"], out["dhidden"])
+        return
+    bwd["grad_scale"] = 4096.0
+    plain = run_fused(gh, wl, h, W, wl.targets, bwd=bwd)["dweight"]   # fp32
+    assert plain.abs().max() > 0.02
+    into = torch.full_like(out["dweight"], 0.25)
+    run_fused(gh, wl, h, W, wl.targets, bwd=bwd, dweight_dtype=into.dtype, dw_into=into)
+    assert torch.equal(into, (plain + 0.25).to(into.dtype))
+
+
+@pytest.mark.parametrize("T,H,V,z_std,entropy_coef", [(1300, 264, 1001, 2.0, 0.01), (2600, 72, 1500, 25.0, 0.0), (400, 136, 30000, 2.0, 0.01),
+                                                      (400, 136, 30000, 25.0, 0.0)])
+def test_fused_gradients_in_one_launch_of_recomputed_logits(gh, T, H, V, z_std, entropy_coef):
+    """The same where the operands come from the recomputation (an entropy term; logits past the stored exponentials' range): a
+    range in parts, and more tiles in one."""
+    wl, h, W = make(T, H, V, sigma_w=z_std / np.sqrt(H), Q=60, len_hi=max(2, T // 60))
+    # advantages of one sign: see test_fused_recompute_beyond_a_tile_per_cu
+    ref, _ = check_bwd(gh, wl, h, W, dict(), adv_map=np.abs, strict_loss=entropy_coef == 0.0, entropy_coef=entropy_coef,
+                       dweight_dtype=torch.bfloat16 if T > 2000 else torch.float32)
+    candidates = (ref["e"] != 0) if entropy_coef else (ref["g"] != 0)
+    assert candidates.sum() >= 1024 or T < 1000
+    if z_std > 20.0:
+        z = orc.lmhead_logits(h[candidates], W)
+        assert (z.max(axis=1) - z[np.arange(z.shape[0]), wl.targets[candidates]]).max() > 40.0
 
 
 @pytest.mark.parametrize("T", [2048, 2049, 8193, 33793])
@@ -361,12 +386,13 @@ def test_fused_dweight_off_the_16_byte_grid(gh, dtype, H, accumulate):
 
 
 @pytest.mark.parametrize("rows", [600, 8192])
+@pytest.mark.parametrize("H,V", [(200, 70013), (264, 40013)])
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
-def test_fused_dweight_forms_beyond_a_tile_per_cu(gh, dtype, rows):
-    """More dweight tiles than CUs, full and ragged ones, on both sides of the row count (8192) from which every tile has a
-    workgroup of its own: the same candidates give the same bits however many rows without a target surround them, whether the
-    buffer is aligned or not, and added to what it holds exactly that sum, rounded once."""
-    T, H, V = 600, 200, 70013
+def test_fused_dweight_forms_beyond_a_tile_per_cu(gh, dtype, H, V, rows):
+    """More dweight tiles than CUs, full and ragged ones: walked in the launch of both gradients (one tile of H, 600 rows), walked in a
+    launch of their own (two tiles of H), and a workgroup each (8192 rows).  The same candidates give the same bits however many rows
+    without a target surround them, whether the buffer is aligned or not, and added to what it holds exactly that sum, rounded once."""
+    T = 600
     wl, h, W = make(T, H, V, sigma_w=2.0 / np.sqrt(H))
     ga = orc.group_advantage(wl.rewards, wl.lengths, wl.group_offsets, wl.keep_priority, AdvParams())
     bwd = dict(old=np.full(T, -11.0, np.float32), adv=ga["adv"].astype(np.float32), weight=ga["weight"].astype(np.float32),
