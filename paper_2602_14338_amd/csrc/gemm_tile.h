@@ -514,8 +514,8 @@ struct GemmStream {
 // step (both layouts keep whole lines: 1 KB blocks of A, 512-byte rows of B), four of them lie in LDS, and a step is requested
 // three steps before it is read, in instructions that the compiler does not count.  The second half of a step's matrix
 // instructions waits until the barrier behind it, and covers the reads of the next step's first fragments.
-// k_gemm_dh, two stages of 64 / this loop: 600 tokens at H = 1536, V = 151936 233 / 213 us, 16384 4047 / 3635, 32768 at H = 3584,
-// V = 152064 20.15 / 18.08 ms.  Where the requests stand: in front of the first group of matrix instructions 3781 and 19033 against
+// k_gemm_dh, two stages of 64 / this loop: 600 tokens at H = 1536, V = 151936 with 390 candidates 208 / 184 us, with 600 296 / 267, 16384 with
+// 5/8 of them candidates 4047 / 3635, 32768 at H = 3584, V = 152064 with 65 % 20.15 / 18.08 ms.  Where the requests stand: in front of the first group of matrix instructions 3781 and 19033 against
 // 3635 and 18085; one every four instructions and by half of the waves no better, the latter 4200.
 // (For dweight, whose operands are both in fragment order, 1612 / 1539: it keeps the loop above.)
 // ------------------------------------------------------------------------------------------
