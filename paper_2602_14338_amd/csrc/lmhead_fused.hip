@@ -1040,7 +1040,8 @@ __global__ __launch_bounds__(kGemmNT, 2) void k_gemm_dw(
 // for gradients of up to a tile per CU; calls of kDwTileRows rows and more fill the chip with either, unless the gradient has few
 // tiles (up to kDwSplitTiles; its range in one part, two launches / one: H = 64, V = 4000 20000 rows 397 / 379 us, H = 896, V = 8000 801 / 727).  Whole calls, two launches / one: H = 208,
 // V = 152064 144 rows 133.7 / 122.7 us, 500 248 / 217, 2000 659 / 601, 6000 1593 / 1542; H = 256, V = 60000 500 120.6 / 117.9, 4000 470 / 444; H = 360,
-// V = 4249 1080 rows 83.9 / 70.9; H = 896, V = 5504 1001 103.5 / 97.3; H = 2048, V = 6678 240 108.5 / 107.1.  Where both fill the chip it is a matter of
+// V = 4249 1080 rows 83.9 / 70.9; H = 896, V = 5504 1001 103.5 / 97.3; H = 2048, V = 6678 240 108.5 / 107.1; 75 calls drawn over
+// the rule's range (128 to 8192 rows, H to 2560, V to 150 K) 0.99 to 1.23 times as fast, 1.09 in the median.  Where both fill the chip it is a matter of
 // how their last rounds fall: H = 896, V = 33846 500 rows 172.5 / 174.3, 4000 693 / 659; H = 640, V = 30000 4000 451 / 460; H = 3584, V = 32000 300 272 / 280.
 template <bool OUT_BF16, bool ACC, bool SPLIT>
 __global__ __launch_bounds__(kGemmNT, 2) void k_gemm_grads(

@@ -193,7 +193,7 @@ def test_fused_dweight_of_few_tiles(gh, T, H, V, off, dtype, accumulate):
     assert (rest[:off] == 7.0).all() and (rest[off + V * H:] == 7.0).all()
 
 
-@pytest.mark.parametrize("T,H,V", [(4400, 24, 32700), (14000, 24, 32700), (4400, 264, 16129), (2100, 8, 4097)])
+@pytest.mark.parametrize("T,H,V", [(4400, 24, 32700), (8192, 24, 32700), (14000, 24, 32700), (4400, 264, 16129), (2100, 8, 4097)])
 def test_fused_dweight_parts_add_up(gh, T, H, V):
     """The most tiles that are split, with too few candidates for it and with enough: the whole call against its tokens in calls of 900, which are not split, added up in one fp32
     buffer.  The operands are the same but for the scales of the hidden rows, which differ by the order in which a token's statistics are
